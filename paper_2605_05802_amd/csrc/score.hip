@@ -8,9 +8,14 @@
 // accumulate_logprob_kernel: one thread per sequence adds the per-token values of a chunk to the
 // sequence's running log-likelihood in token order (double), so the sum does not depend on scheduling.
 //
-// grpo_loss_kernel: one thread per group computes the advantages of Eq. 1 (population standard
+// grpo_share_kernel: one thread per group computes the advantages of Eq. 1 (population standard
 // deviation; exactly zero when all rewards of the group are equal) and the group's share of
-// sum_i A_i log p(tau_i); thread 0 adds the shares in group order.
+// sum_i A_i log p(tau_i).  The shares are added in group order, by one lane, so that the loss is the
+// same to the last bit whatever the launch shape: a chain of dependent 64-bit additions, which is
+// what bounds the call from a few hundred groups on.  The lane therefore reads from LDS only
+// (grpo_sum_kernel: the other wavefronts bring in the next chunk meanwhile); reading the shares from
+// global memory itself cost it 80 ns per group (336 us at 4096 groups of 8, 30 us now; 512 groups and fewer, in
+// one launch, are not bound by it).
 #include <mutex>
 
 #include "sr_internal.h"
@@ -69,11 +74,32 @@ __global__ void accumulate_logprob_kernel(const float *__restrict__ tok_lp, int 
     logprob[u] = acc;
 }
 
-__global__ __launch_bounds__(256) void grpo_loss_kernel(const double *__restrict__ logprob,
-                                                        const float *__restrict__ rewards, int n_groups, int G,
-                                                        double eps, float *__restrict__ adv, double *__restrict__ share,
-                                                        double *__restrict__ loss) {
-    for (int g = threadIdx.x; g < n_groups; g += blockDim.x) {
+// acc + v[0] + ... + v[n-1], in that order; v in LDS
+__device__ __forceinline__ double add_in_order(double acc, const double *v, int n) {
+    int i = 0;
+    for (; i + 16 <= n; i += 16) {
+        double x[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) x[k] = v[i + k];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) acc += x[k];
+    }
+    for (; i < n; ++i) acc += v[i];
+    return acc;
+}
+
+constexpr int kShareThreads = 64;      // many small workgroups: the groups spread over the compute units
+constexpr int kOneBlock = 512;         // up to so many groups one workgroup does shares and sum in one launch
+constexpr int kSumChunk = 2048;        // shares per LDS buffer of the ordered sum
+
+// ONE: a single workgroup of kOneBlock threads holds every group and adds the shares itself
+template <bool ONE>
+__global__ void grpo_share_kernel(const double *__restrict__ logprob, const float *__restrict__ rewards, int n_groups,
+                                  int G, double eps, float *__restrict__ adv, double *__restrict__ share,
+                                  double *__restrict__ loss) {
+    __shared__ __align__(16) double s_share[ONE ? kOneBlock : 1];
+    const int g = blockIdx.x * blockDim.x + threadIdx.x;
+    if (g < n_groups) {
         const float *r = rewards + (size_t)g * G;
         bool all_equal = true;
         double mean = 0.0;
@@ -92,13 +118,48 @@ __global__ __launch_bounds__(256) void grpo_loss_kernel(const double *__restrict
             acc += A * logprob[(size_t)g * G + i];
         }
         share[g] = acc;
+        if (ONE) s_share[g] = acc;
     }
-    __syncthreads();          // one workgroup: the shares written above are visible to thread 0
-    if (threadIdx.x == 0) {
-        double acc = 0.0;
-        for (int g = 0; g < n_groups; ++g) acc += share[g];
-        *loss = -acc / ((double)n_groups * G);
+    if (!ONE) return;
+    __syncthreads();
+    if (threadIdx.x == 0) *loss = -add_in_order(0.0, s_share, n_groups) / ((double)n_groups * G);
+}
+
+__global__ __launch_bounds__(256) void grpo_sum_kernel(const double *__restrict__ share, int n_groups, int G,
+                                                       double *__restrict__ loss) {
+    __shared__ __align__(16) double buf[2][kSumChunk];
+    const int n_chunks = (n_groups + kSumChunk - 1) / kSumChunk;
+    auto fetch = [&](int c, int from, int step) {
+        const int n = min(kSumChunk, n_groups - c * kSumChunk);
+        for (int i = from; i < n; i += step) buf[c & 1][i] = share[(size_t)c * kSumChunk + i];
+    };
+    fetch(0, threadIdx.x, 256);
+    double acc = 0.0;
+    for (int c = 0; c < n_chunks; ++c) {
+        __syncthreads();                 // chunk c is in LDS, and nobody reads the other buffer any more
+        if (threadIdx.x >= 64) {
+            if (c + 1 < n_chunks) fetch(c + 1, threadIdx.x - 64, 192);
+        } else if (threadIdx.x == 0) {
+            acc = add_in_order(acc, buf[c & 1], min(kSumChunk, n_groups - c * kSumChunk));
+        }
     }
+    if (threadIdx.x == 0) *loss = -acc / ((double)n_groups * G);
+}
+
+int launch_grpo_loss(const double *logprob, const float *rewards, int n_groups, int G, double eps, float *advantages,
+                     double *share, double *loss, hipStream_t stream) {
+    if (n_groups <= kOneBlock) {
+        grpo_share_kernel<true><<<dim3(1), dim3(kOneBlock), 0, stream>>>(logprob, rewards, n_groups, G, eps, advantages,
+                                                                         share, loss);
+        SR_HIP(hipGetLastError());
+        return SR_OK;
+    }
+    grpo_share_kernel<false><<<dim3((n_groups + kShareThreads - 1) / kShareThreads), dim3(kShareThreads), 0, stream>>>(
+        logprob, rewards, n_groups, G, eps, advantages, share, loss);
+    SR_HIP(hipGetLastError());
+    grpo_sum_kernel<<<dim3(1), dim3(256), 0, stream>>>(share, n_groups, G, loss);
+    SR_HIP(hipGetLastError());
+    return SR_OK;
 }
 
 }  // namespace
@@ -123,10 +184,7 @@ int launch_accumulate_logprob(const float *tok_lp, int n_seq, int chunk_len, dou
 extern "C" int sr_grpo_loss(const double *logprob, const float *rewards, int n_groups, int G, double eps,
                             float *advantages, double *group_scratch, double *loss, void *stream) {
     if (!logprob || !rewards || !group_scratch || !loss || n_groups < 1 || G < 1 || !(eps >= 0.0)) return SR_E_ARG;
-    sr::grpo_loss_kernel<<<dim3(1), dim3(256), 0, (hipStream_t)stream>>>(logprob, rewards, n_groups, G, eps, advantages,
-                                                                         group_scratch, loss);
-    SR_HIP(hipGetLastError());
-    return SR_OK;
+    return sr::launch_grpo_loss(logprob, rewards, n_groups, G, eps, advantages, group_scratch, loss, (hipStream_t)stream);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -168,8 +226,5 @@ extern "C" int sr_grpo_loss_static(const double *logprob, const float *rewards, 
     double *share = nullptr;
     SR_TRY(static_scratch(&share));
     // every share[g], g < n_groups, is written before it is read: nothing of an earlier call is used
-    sr::grpo_loss_kernel<<<dim3(1), dim3(256), 0, (hipStream_t)stream>>>(logprob, rewards, n_groups, G, eps, advantages,
-                                                                         share, loss);
-    SR_HIP(hipGetLastError());
-    return SR_OK;
+    return sr::launch_grpo_loss(logprob, rewards, n_groups, G, eps, advantages, share, loss, (hipStream_t)stream);
 }

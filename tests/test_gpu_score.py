@@ -176,3 +176,24 @@ def test_scoring_a_few_hundred_rows_with_split_k_projections():
     print(f"mid-size scoring: worst per-token error {err:.3e}")
     assert err <= TOK_TOL
     assert np.abs(total - ref.sum(axis=(0, 2))).max() <= TOK_TOL * cfg.act_len
+
+
+@pytest.mark.parametrize("n_groups", [1, 511, 512, 513, 2048, 2049, 6145])
+def test_loss_adds_the_groups_in_index_order(n_groups):
+    """One workgroup, and shares and sum in two launches (chunks of 2048 shares): every size gives the sum that adding
+    the groups' shares one after the other gives, to the last bit."""
+    G = 3
+    rng = np.random.default_rng(n_groups)
+    r = rng.integers(0, 2, size=(n_groups, G)).astype(np.float32)
+    lp = -rng.uniform(5.0, 400.0, size=(n_groups, G))
+    share = torch.empty(n_groups, dtype=torch.float64, device="cuda")
+    loss = torch.empty(1, dtype=torch.float64, device="cuda")
+    sr.sr_grpo_loss(torch.from_numpy(lp).cuda(), torch.from_numpy(r).cuda(), G, 1e-6, None, share, loss)
+    torch.cuda.synchronize()
+    acc = np.float64(0.0)
+    for x in share.cpu().numpy():
+        acc = acc + x
+    assert loss.item() == -acc / (n_groups * G)
+    sd = r.astype(np.float64).std(axis=1, keepdims=True)
+    adv = np.where(sd > 0, (r - r.mean(axis=1, keepdims=True, dtype=np.float64)) / (sd + 1e-6), 0.0)
+    assert np.allclose(share.cpu().numpy(), (adv * lp).sum(axis=1), rtol=0, atol=1e-9)
