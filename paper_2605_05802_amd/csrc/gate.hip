@@ -1,20 +1,19 @@
 // Selective-Rollout gate: mean pairwise prefix edit distance of a group's action sequences
 // (paper Section 3.2) compared with the threshold d_L (Eq. 2), in exact integer arithmetic.
 //
-// Work decomposition.  The work is G(G-1)/2 independent Levenshtein tables per group and is
-// bound by integer ALU throughput, not by memory (a group is G*K*4 bytes in, 5 bytes out).
-// One lane owns one pair and runs the whole dynamic programme for it, row by row, with the
-// current table row and both sequences held in registers; all loops are unrolled, so there
-// is no cross-lane traffic and every active lane does useful work on every instruction.
-// (Spreading one table over the lanes of an anti-diagonal leaves half of the lanes idle in
-// the triangular ramp-up and ramp-down and pays an LDS round trip per diagonal.)
-// A 256-thread workgroup serves floor(256 / pairs) whole groups; their sequences are staged
-// once through LDS and the per-group sums are accumulated with LDS integer atomics, which
-// are order-independent and therefore deterministic.
+// Work decomposition.  One lane owns one of the G(G-1)/2 pairs of a group and runs its whole Levenshtein table in
+// registers, one row at a time with the row as two bit masks (prefix_match.h), so there is no cross-lane traffic in
+// the recurrence.  A workgroup of up to 256 lanes serves whole groups (nine at G = 8); the equality masks come from
+// LDS tables built once per group, and the per-group sums are accumulated with LDS integer atomics, which are
+// order-independent and therefore deterministic.
 //
-// Prefix nesting: cell (k,k) of the table of two length-Kmax sequences is the distance of
-// their length-k prefixes, so one table serves every requested prefix length.
-#include "sr_internal.h"
+// Prefix nesting: cell (k,k) of the table of two length-L sequences is the distance of their length-k prefixes, so one
+// table serves every requested prefix length.
+//
+// Bound: vector ALU (about 65 % busy, 530 instructions per wavefront: 180 of them the recurrence) with the LDS latency of
+// the table build behind it; the 64 MB of input would be 12 us.  65 536 groups of 8, prefixes 5, 10 and 15: 41 us (62 with
+// symbols beyond the table's range), 72 us with one table cell at a time in registers; at 32 steps 120 against 284 us.
+#include "prefix_match.h"
 
 namespace sr {
 
@@ -28,7 +27,7 @@ int64_t gate_bound(double d_L, int G, int K) {
 namespace {
 
 constexpr int kGateThreads = 256;
-constexpr int kGateLdsInts = 4096;
+constexpr int kGateLds = 48 * 1024;      // tables of one workgroup: three workgroups or more per compute unit
 
 __device__ __forceinline__ unsigned min3u(unsigned a, unsigned b, unsigned c) {
     return min(a, min(b, c));
@@ -36,67 +35,51 @@ __device__ __forceinline__ unsigned min3u(unsigned a, unsigned b, unsigned c) {
 
 template <int KMAX>
 __global__ __launch_bounds__(kGateThreads) void gate_kernel(
-    const int32_t *__restrict__ actions, int n_groups, int G, int stride, int pairs,
-    int groups_per_block, GateLens lens, int32_t *__restrict__ sums, uint8_t *__restrict__ retire) {
-    __shared__ int32_t s_act[kGateLdsInts];          // [groups_per_block][G][KMAX]
-    __shared__ int s_sum[8][kGateThreads];           // [len index][group in block]
+    const int32_t *__restrict__ actions, int n_groups, int stride, int pairs, PrefixGeom q, GateLens lens,
+    int32_t *__restrict__ sums, uint8_t *__restrict__ retire) {
+    extern __shared__ __align__(16) char lds[];      // prefix tables
+    __shared__ unsigned s_sum[4][kGateThreads];      // [len index / 2][group in block]: two sums of at most 120 * 32 each
 
-    const int tid = threadIdx.x;
-    const int g0 = blockIdx.x * groups_per_block;
-    const int n_here = min(groups_per_block, n_groups - g0);
+    const int tid = threadIdx.x, G = q.G;
+    const int g0 = blockIdx.x * q.groups;
+    const int n_here = min(q.groups, n_groups - g0);
+    const PrefixLds off = prefix_lds(q, q.groups, KMAX);
+    for (int i = tid; i < q.groups; i += blockDim.x) s_sum[0][i] = s_sum[1][i] = s_sum[2][i] = s_sum[3][i] = 0;
+    prefix_build<KMAX>(lds, q, off, n_here * G, actions + (size_t)g0 * G * stride, stride);
 
-    for (int i = tid; i < 8 * kGateThreads; i += kGateThreads) (&s_sum[0][0])[i] = 0;
-    // stage the first KMAX actions of every member (pad with distinct negative ids: never compared,
-    // because no requested prefix reaches a padded column)
-    const int rows = n_here * G;
-    for (int i = tid; i < rows * KMAX; i += kGateThreads) {
-        const int r = i / KMAX, c = i - r * KMAX;
-        s_act[i] = (c < stride) ? actions[((size_t)g0 * G + r) * stride + c] : -1 - c;
-    }
-    __syncthreads();
-
-    const int gl = tid / pairs;                       // group within the block
+    const int gl = (int)(((float)tid + 0.5f) * (1.0f / (float)pairs));     // group within the block
     if (gl < n_here) {
-        int p = tid - gl * pairs, i = 0;              // pair index -> (i, j), i < j
-        while (p >= G - 1 - i) { p -= G - 1 - i; ++i; }
-        const int j = i + 1 + p;
-        int32_t a[KMAX], b[KMAX];
-        const int32_t *sa = s_act + (gl * G + i) * KMAX, *sb = s_act + (gl * G + j) * KMAX;
+        int i, j;
+        pair_members(tid - gl * pairs, G, &i, &j);
+        unsigned wanted = 0;                          // bit k: prefix length k + 1 is asked for
+        for (int l = 0; l < lens.n; ++l) wanted |= 1u << (lens.len[l] - 1);
+        unsigned pv = 0xFFFFFFFFu, mv = 0, res[4] = {0, 0, 0, 0};
 #pragma unroll
-        for (int c = 0; c < KMAX; ++c) { a[c] = sa[c]; b[c] = sb[c]; }
-
-        int maxlen = 0;
-        for (int l = 0; l < lens.n; ++l) maxlen = max(maxlen, lens.len[l]);
-
-        unsigned row[KMAX + 1];
-        unsigned res[8];
+        for (int r0 = 0; r0 < KMAX; r0 += 8) {
+            if (r0 < q.L) {                           // uniform
+                unsigned eq[8];
+                prefix_masks8<KMAX>(lds, q, off, gl * G + i, gl * G + j, r0, eq);
 #pragma unroll
-        for (int l = 0; l < 8; ++l) res[l] = 0;
+                for (int t = 0; t < 8; ++t) {
+                    prefix_row(eq[t], pv, mv);
+                    if ((wanted >> (r0 + t)) & 1u) {  // uniform
+                        const unsigned d = (unsigned)prefix_cell(r0 + t + 1, r0 + t + 1, pv, mv);
 #pragma unroll
-        for (int c = 0; c <= KMAX; ++c) row[c] = c;
-#pragma unroll
-        for (int r = 1; r <= KMAX; ++r) {
-            if (r <= maxlen) {                        // uniform across the workgroup
-                unsigned diag = row[0];
-                row[0] = r;
-#pragma unroll
-                for (int c = 1; c <= KMAX; ++c) {
-                    const unsigned up = row[c];
-                    row[c] = min3u(diag + (a[r - 1] != b[c - 1] ? 1u : 0u), up + 1u, row[c - 1] + 1u);
-                    diag = up;
+                        for (int l = 0; l < 8; ++l)
+                            if (l < lens.n && lens.len[l] == r0 + t + 1) res[l >> 1] += d << (16 * (l & 1));
+                    }
                 }
-#pragma unroll
-                for (int l = 0; l < 8; ++l)
-                    if (l < lens.n && lens.len[l] == r) res[l] = row[r];
             }
         }
-        for (int l = 0; l < lens.n; ++l) atomicAdd(&s_sum[l][gl], (int)res[l]);
+#pragma unroll
+        for (int l = 0; l < 4; ++l)
+            if (2 * l < lens.n) atomicAdd(&s_sum[l][gl], res[l]);
     }
     __syncthreads();
 
-    for (int i = tid; i < lens.n * n_here; i += kGateThreads) {
+    for (int i = tid; i < lens.n * n_here; i += blockDim.x) {
         const int l = i / n_here, g = i - l * n_here;
-        const int s = s_sum[l][g];
+        const int s = (int)((s_sum[l >> 1][g] >> (16 * (l & 1))) & 0xFFFFu);
         if (sums) sums[(size_t)l * n_groups + g0 + g] = s;
         if (retire) retire[(size_t)l * n_groups + g0 + g] = (uint8_t)(s < lens.bound[l]);
     }
@@ -197,17 +180,15 @@ int launch_gate(const int32_t *actions, int n_groups, int G, int stride, const G
     for (int l = 0; l < lens.n; ++l) maxlen = lens.len[l] > maxlen ? lens.len[l] : maxlen;
     const int pairs = G * (G - 1) / 2;
     const int kmax = maxlen <= 8 ? 8 : maxlen <= 16 ? 16 : maxlen <= 24 ? 24 : 32;
-    int gpb = kGateThreads / pairs;
-    const int lds_cap = kGateLdsInts / (G * kmax);
-    if (gpb > lds_cap) gpb = lds_cap;
-    if (gpb < 1) return SR_E_ARG;
-    const int blocks = (n_groups + gpb - 1) / gpb;
-    dim3 grid(blocks), block(kGateThreads);
+    PrefixGeom q{};
+    if (!prefix_geometry(n_groups, G, maxlen, kmax, kGateLds, 0, &q)) return SR_E_ARG;
+    const size_t lds = prefix_lds(q, q.groups, kmax).total;
+    dim3 grid((n_groups + q.groups - 1) / q.groups), block(q.threads);
     switch (kmax) {
-        case 8:  gate_kernel<8><<<grid, block, 0, stream>>>(actions, n_groups, G, stride, pairs, gpb, lens, sums, retire); break;
-        case 16: gate_kernel<16><<<grid, block, 0, stream>>>(actions, n_groups, G, stride, pairs, gpb, lens, sums, retire); break;
-        case 24: gate_kernel<24><<<grid, block, 0, stream>>>(actions, n_groups, G, stride, pairs, gpb, lens, sums, retire); break;
-        default: gate_kernel<32><<<grid, block, 0, stream>>>(actions, n_groups, G, stride, pairs, gpb, lens, sums, retire); break;
+        case 8:  gate_kernel<8><<<grid, block, lds, stream>>>(actions, n_groups, stride, pairs, q, lens, sums, retire); break;
+        case 16: gate_kernel<16><<<grid, block, lds, stream>>>(actions, n_groups, stride, pairs, q, lens, sums, retire); break;
+        case 24: gate_kernel<24><<<grid, block, lds, stream>>>(actions, n_groups, stride, pairs, q, lens, sums, retire); break;
+        default: gate_kernel<32><<<grid, block, lds, stream>>>(actions, n_groups, stride, pairs, q, lens, sums, retire); break;
     }
     SR_HIP(hipGetLastError());
     return SR_OK;

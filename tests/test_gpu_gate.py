@@ -93,3 +93,16 @@ def test_device_weight_fill_matches_host_generator():
     for l in range(2):
         for k, v in host.layers[l].items():
             assert same(layers[l][k], v), (l, k)
+
+
+@pytest.mark.parametrize("n_groups,G,lens", [(14337, 2, [32]), (9001, 3, [8, 1]), (6001, 12, [24, 7]), (1537, 16, [32, 31, 17]),
+                                             (4099, 8, [32]), (4099, 8, [16, 9]), (1, 16, [16]), (1025, 7, [24])])
+def test_gate_groups_per_workgroup(n_groups, G, lens):
+    """Enough groups that a workgroup takes as many as its lanes and LDS tables hold, a ragged last workgroup, symbols at
+    both ends of the 32-bit range (the empty-slot marker of the symbol table is not a symbol)."""
+    acts, _ = synth.gate_actions(n_groups, G, max(lens), 6, seed=n_groups)
+    values = np.array([0, -1, 1, -2 ** 31, 2 ** 31 - 1, 0x01000000], dtype=np.int32)
+    acts = values[acts]
+    s_ref, r_ref = oracle.gate_batch(acts, lens, 0.25)
+    s_gpu, r_gpu = run_gpu(acts, lens, 0.25)
+    assert np.array_equal(s_gpu, s_ref) and np.array_equal(r_gpu, r_ref)
