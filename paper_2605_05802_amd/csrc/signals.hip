@@ -9,17 +9,20 @@
 //     observation counts, the step-K action entropy and the number of finished members;
 //   - the decisions  d_K < d_L  (Eq. 2) and  d_K < d_L or tau_K >= tau_H  (Eq. 3) in integers.
 //
-// Work decomposition, as for the equal-length gate: one lane owns one pair and keeps both
-// sequences and the current table row in registers.  Cell (r, c) of the table of two sequences
-// is the distance of their prefixes of lengths r and c, so one table serves every requested K:
-// the lane picks cell (len_i, len_j) when row len_i is complete.  Bigram sets need no second pass
-// per K either: a bigram position is the first occurrence of its bigram in every prefix that
-// contains it, so the lane computes once a bit mask of first occurrences per sequence and, per
-// position of a, the mask of positions of b holding the same bigram; each K is then a few mask
-// operations.  Lanes leave five small integers per (K, pair) in LDS; one thread per (K, group)
-// turns them into the outputs, adding the pair terms in pair order (i, j), i < j, so that the
-// floating-point results do not depend on scheduling.
-#include "sr_internal.h"
+// Work decomposition, as for the equal-length gate: one lane owns one pair and runs its table bit-parallel
+// (prefix_match.h).  Cell (r, c) of the table of two sequences is the distance of their prefixes of lengths r and c, so
+// one pass serves every requested K: the lane reads cell (K, len_j) when row K is complete, and keeps the masks of row
+// end_i for the K beyond it.  The same equality masks give the bigrams: bit u of eq_t & (eq_{t+1} >> 1) says that b holds
+// bigram t of a at position u; a bigram position is the first occurrence of its bigram in every prefix that contains it,
+// so one mask of first occurrences per member and one mask per position of a serve every K.
+// What is per member (first occurrences, step-K counts, entropy terms) is done by one lane per member and K, what is
+// per pair (quotients included) by the pair lanes; one thread per (K, group) is left with adding the pair terms in pair
+// order (i, j), i < j, and the entropy terms in member order, so that the floating-point results do not depend on
+// scheduling.
+// Bound: vector ALU (70 % busy).  65 536 groups of 8 with early finishers, K = 5, 10, 15: 126 us; 361 us with one table cell
+// at a time, K * K compares per pair for the bigrams and the quotients left to the thread of a (K, group).  At 32 steps
+// 272 against 1266 us, at G = 16 and 16 steps 112 against 990 us (16 384 groups).
+#include "prefix_match.h"
 
 static_assert(sizeof(sr_signals_t) == 64, "sr_signals_t is part of the C boundary");
 
@@ -27,7 +30,8 @@ namespace sr {
 namespace {
 
 constexpr int kSigThreads = 256;
-constexpr int kSigLdsInts = 4096;
+constexpr int kSigLds = 52 * 1024;                   // three workgroups per compute unit where the shape allows it
+constexpr int kSigLdsMost = 64 * 1024;               // G = 16 with 32 steps and 8 prefix lengths needs 62 KiB
 constexpr int kSigMaxLens = 8;
 constexpr long long kLcm32 = 144403552893600LL;      // lcm(1..32)
 
@@ -36,192 +40,229 @@ struct SigLens {
     int len[kSigMaxLens];
     long long d_bound;                // d_K < d_L  <=>  lev_scaled < d_bound
     long long tau_num;                // tau_K >= tau_H  <=>  n_done * 1e6 >= tau_num * G
+    long long lcm_over[33];           // lcm(1..32) / n
 };
 
-struct PairRec {                       // what a pair lane leaves for one K
-    uint8_t lev, longer, inter, uni, same;
+// What the workgroup keeps behind the prefix tables: byte offsets, 8-byte arrays first.
+struct SigLds {
+    int d, j, h, out, pair, obs, hold, end, first, total;
 };
+__host__ __device__ inline SigLds sig_lds(int G, int pairs, int groups, int n_lens) {
+    SigLds o;
+    const int P = n_lens * groups * pairs, R = n_lens * groups * G;
+    o.out = 0;                                    // [K][group] sr_signals_t
+    o.d = o.out + n_lens * groups * 64;           // [K][pair] double: distance / longer length
+    o.j = o.d + P * 8;                            // [K][pair] double: Jaccard term
+    o.h = o.j + P * 8;                            // [K][member] double: log p of an action, at its first holder
+    o.obs = o.h + R * 8;                          // [K][member] o_{i,K}
+    o.hold = o.obs + R * 4;                       // [K][member] see below
+    o.end = o.hold + R * 4;                       // [member]
+    o.first = o.end + groups * G * 4;             // [member] positions of first occurrences of bigrams
+    o.pair = o.first + groups * G * 4;            // [K][pair] 16 bits: distance | longer length << 6 | equal prefixes << 12
+    o.total = o.pair + round_up(P * 2, 16);
+    return o;
+}
 
 template <int KMAX>
 __global__ __launch_bounds__(kSigThreads) void signals_kernel(
     const int32_t *__restrict__ actions, const int32_t *__restrict__ obs, const int32_t *__restrict__ end_step,
-    int n_groups, int G, int stride, int pairs, int groups_per_block, SigLens lens, sr_signals_t *__restrict__ out) {
-    __shared__ int32_t s_act[kSigLdsInts];                    // [groups_per_block][G][KMAX]
-    __shared__ int32_t s_obs[kSigMaxLens][kSigThreads];       // [K index][group in block * G + member]: o_{i,K}
-    __shared__ int32_t s_end[kSigThreads];                    // [group in block * G + member]
-    __shared__ PairRec s_pair[kSigMaxLens][kSigThreads];      // [K index][group in block * pairs + pair]
+    int n_groups, int stride, int pairs, PrefixGeom q, SigLens lens, sr_signals_t *__restrict__ out) {
+    extern __shared__ __align__(16) char lds[];
+    __shared__ long long s_lcm[33];                          // lcm(1..32) / n
+    const int tid = threadIdx.x, nt = blockDim.x, G = q.G, NL = lens.n;
+    const int g0 = blockIdx.x * q.groups;
+    const int n_here = min(q.groups, n_groups - g0);
+    const int rows = n_here * G, n_pairs = q.groups * pairs, n_rows = q.groups * G;
+    const PrefixLds off = prefix_lds(q, q.groups, KMAX);
+    const SigLds so = sig_lds(G, pairs, q.groups, NL);
+    char *mine = lds + off.total;
+    sr_signals_t *s_out = (sr_signals_t *)(mine + so.out);
+    double *s_d = (double *)(mine + so.d), *s_j = (double *)(mine + so.j), *s_h = (double *)(mine + so.h);
+    int32_t *s_obs = (int32_t *)(mine + so.obs), *s_end = (int32_t *)(mine + so.end);
+    // holders of the member's step-K action if it is the first of them, | 32 the first to hold its observation
+    // | 64 its prefix reaches step K | 128 it has finished by step K
+    int *s_hold = (int *)(mine + so.hold);
+    unsigned *s_first = (unsigned *)(mine + so.first);
+    uint16_t *s_pair = (uint16_t *)(mine + so.pair);
+    const float inv_G = 1.0f / (float)G, inv_rows = 1.0f / (float)rows;
 
-    const int tid = threadIdx.x;
-    const int g0 = blockIdx.x * groups_per_block;
-    const int n_here = min(groups_per_block, n_groups - g0);
-    const int rows = n_here * G;
-
-    // stage the first KMAX actions of every member (columns past the stride are never part of a prefix)
-    for (int i = tid; i < rows * KMAX; i += kSigThreads) {
-        const int r = i / KMAX, c = i - r * KMAX;
-        s_act[i] = (c < stride) ? actions[((size_t)g0 * G + r) * stride + c] : -1 - c;
+    if (tid < 33) s_lcm[tid] = lens.lcm_over[tid];
+    for (int i = tid; i < rows; i += nt) s_end[i] = end_step ? max(end_step[(size_t)g0 * G + i], 0) : 0x7FFFFFFF;
+    for (int w = tid; w < NL * rows; w += nt) {
+        const int l = min((int)(((float)w + 0.5f) * inv_rows), NL - 1), r = w - l * rows;
+        s_obs[l * n_rows + r] = obs ? obs[((size_t)g0 * G + r) * stride + lens.len[l] - 1] : 0;
     }
-    for (int i = tid; i < rows; i += kSigThreads) {
-        s_end[i] = end_step ? max(end_step[(size_t)g0 * G + i], 0) : 0x7FFFFFFF;
-        for (int l = 0; l < lens.n; ++l)
-            s_obs[l][i] = obs ? obs[((size_t)g0 * G + i) * stride + lens.len[l] - 1] : 0;
+    prefix_build<KMAX>(lds, q, off, rows, actions + (size_t)g0 * G * stride, stride);
+    const uint16_t *ids = (const uint16_t *)(lds + off.id);
+
+    // One lane per (member, position): is it the first occurrence of its bigram?  A member's lanes are neighbours, so
+    // the wavefront's vote holds the members' masks side by side.
+    constexpr int KP = KMAX <= 8 ? 8 : KMAX <= 16 ? 16 : 32;
+    for (int e0 = 0; e0 < rows * KP; e0 += nt) {             // whole wavefronts take part
+        const int e = e0 + tid, r = e / KP, t = e % KP;
+        bool first = false;
+        if (r < rows && t + 1 < q.L) {
+            const unsigned here = prefix_mask<KMAX>(lds, q, r, ids[r * KMAX + t]);
+            const unsigned next = prefix_mask<KMAX>(lds, q, r, ids[r * KMAX + t + 1]);
+            first = (here & (next >> 1) & low_bits(t)) == 0u;
+        }
+        const unsigned long long vote = __ballot(first);
+        if (t == 0 && r < rows) s_first[r] = (unsigned)(vote >> (tid & 63)) & low_bits(KP);
+    }
+    // One lane per (member, K): members that reach step K, and whether this one is the first to hold its action or
+    // observation
+    for (int w = tid; w < NL * rows; w += nt) {
+        const int l = min((int)(((float)w + 0.5f) * inv_rows), NL - 1), r = w - l * rows, g = small_div(r, inv_G), K = lens.len[l];
+        int hold = s_end[r] <= K ? 128 : 0;
+        if (s_end[r] >= K) {
+            const unsigned a = ids[r * KMAX + K - 1];
+            const int32_t o = s_obs[l * n_rows + r];
+            int n_at = 0, count = 0;
+            bool first_act = true, first_obs = true;
+#pragma unroll 4
+            for (int i = g * G; i < g * G + G; ++i) {
+                const bool at = s_end[i] >= K, same = at & (ids[i * KMAX + K - 1] == a);
+                n_at += at ? 1 : 0;
+                count += same ? 1 : 0;
+                first_act &= !((i < r) & same);
+                first_obs &= !((i < r) & at & (s_obs[l * n_rows + i] == o));
+            }
+            hold |= 64 | (first_act ? count : 0) | (first_obs ? 32 : 0);
+            if (first_act) s_h[l * n_rows + r] = log((double)count / (double)n_at);
+        }
+        s_hold[l * n_rows + r] = hold;
     }
     __syncthreads();
 
-    const int gl = tid / pairs;                       // group within the block
+    // per pair
+    const int gl = (int)(((float)tid + 0.5f) * (1.0f / (float)pairs));     // group within the block
     if (gl < n_here) {
-        int p = tid - gl * pairs, i = 0;              // pair index -> (i, j), i < j
-        while (p >= G - 1 - i) { p -= G - 1 - i; ++i; }
-        const int j = i + 1 + p;
-        int32_t a[KMAX], b[KMAX];
-        const int32_t *sa = s_act + (gl * G + i) * KMAX, *sb = s_act + (gl * G + j) * KMAX;
+        int i, j;
+        pair_members(tid - gl * pairs, G, &i, &j);
+        const int ri = gl * G + i, rj = gl * G + j;
+        const int ei = s_end[ri], ej = s_end[rj];
+        unsigned wanted = 0;                          // bit k: prefix length k + 1 is asked for
+        for (int l = 0; l < NL; ++l) wanted |= 1u << (lens.len[l] - 1);
+        int res[kSigMaxLens];
 #pragma unroll
-        for (int c = 0; c < KMAX; ++c) { a[c] = sa[c]; b[c] = sb[c]; }
-        const int ei = s_end[gl * G + i], ej = s_end[gl * G + j];
+        for (int l = 0; l < kSigMaxLens; ++l) res[l] = 0;
 
-        int li[kSigMaxLens], lj[kSigMaxLens];
-        unsigned res[kSigMaxLens];
-        int maxlen = 0;
+        unsigned pv = 0xFFFFFFFFu, mv = 0, pv_end = 0xFFFFFFFFu, mv_end = 0;      // row 0: distance from the empty prefix
+        unsigned big[KMAX], eq_last = 0;              // big[t]: positions of b that hold bigram t of a
+#pragma unroll
+        for (int r0 = 0; r0 < KMAX; r0 += 8) {
+            unsigned eq[8];
+            if (r0 < q.L) {                           // uniform
+                prefix_masks8<KMAX>(lds, q, off, ri, rj, r0, eq);
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    const int r = r0 + t + 1;
+                    prefix_row(eq[t], pv, mv);
+                    if (ei == r) { pv_end = pv; mv_end = mv; }
+                    if ((wanted >> (r - 1)) & 1u) {   // uniform
+                        const int d = prefix_cell(r, min(r, ej), pv, mv);
+#pragma unroll
+                        for (int l = 0; l < kSigMaxLens; ++l)
+                            if (l < NL && lens.len[l] == r) res[l] = d;
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int t = 0; t < 8; ++t) eq[t] = 0;
+            }
+            if (r0 > 0) big[r0 - 1] = eq_last & (eq[0] >> 1);
+#pragma unroll
+            for (int t = 0; t < 7; ++t) big[r0 + t] = eq[t] & (eq[t + 1] >> 1);
+            eq_last = eq[7];
+        }
+        const unsigned first_a = s_first[ri], first_b = s_first[rj];
 #pragma unroll
         for (int l = 0; l < kSigMaxLens; ++l) {
-            const int K = l < lens.n ? lens.len[l] : 0;
-            li[l] = min(K, ei);
-            lj[l] = min(K, ej);
-            res[l] = (unsigned)lj[l];                 // row 0 of the table: distance from the empty prefix
-            maxlen = max(maxlen, K);
-        }
-
-        // edit-distance table, one row at a time; cell (len_i, len_j) is picked when row len_i is complete
-        unsigned row[KMAX + 1];
+            if (l < NL) {
+                const int K = lens.len[l], li = min(K, ei), lj = min(K, ej);
+                const int lev = ei < K ? prefix_cell(li, lj, pv_end, mv_end) : res[l];
+                // a prefix of length n holds bigram positions 0 .. n-2
+                const unsigned ma = low_bits(max(li - 1, 0)), mb = low_bits(max(lj - 1, 0));
+                unsigned held = 0;
 #pragma unroll
-        for (int c = 0; c <= KMAX; ++c) row[c] = c;
-#pragma unroll
-        for (int r = 1; r <= KMAX; ++r) {
-            if (r <= maxlen) {                        // uniform across the workgroup
-                unsigned diag = row[0];
-                row[0] = r;
-#pragma unroll
-                for (int c = 1; c <= KMAX; ++c) {
-                    const unsigned up = row[c];
-                    row[c] = min(min(diag + (a[r - 1] != b[c - 1] ? 1u : 0u), up + 1u), row[c - 1] + 1u);
-                    diag = up;
-                }
-#pragma unroll
-                for (int l = 0; l < kSigMaxLens; ++l)
-                    if (li[l] == r) {
-                        unsigned v = row[0];
-#pragma unroll
-                        for (int c = 1; c <= KMAX; ++c) v = (lj[l] == c) ? row[c] : v;
-                        res[l] = v;
-                    }
+                for (int t = 0; t < KMAX - 1; ++t) held |= (big[t] & mb) != 0u ? 1u << t : 0u;
+                const int inter = __popc(first_a & ma & held);
+                const int uni = __popc(first_a & ma) + __popc(first_b & mb) - inter;
+                const int longer = max(li, lj);
+                s_d[l * n_pairs + tid] = longer > 0 ? (double)lev / (double)longer : 0.0;
+                s_j[l * n_pairs + tid] = uni > 0 ? 1.0 - (double)inter / (double)uni : 0.0;
+                s_pair[l * n_pairs + tid] = (uint16_t)(lev | longer << 6 | (lev == 0 && li == lj ? 1 << 12 : 0));
             }
-        }
-
-        // bigram t = (x[t], x[t+1]), t = 0 .. KMAX-2.  first_x: positions holding the first occurrence of
-        // their bigram in x; in_b[t]: positions of b whose bigram equals bigram t of a.
-        unsigned first_a = 0, first_b = 0, in_b[KMAX - 1];
-#pragma unroll
-        for (int t = 0; t < KMAX - 1; ++t) {
-            bool seen_a = false, seen_b = false;
-            unsigned m = 0;
-#pragma unroll
-            for (int u = 0; u < KMAX - 1; ++u) {
-                if (u < t) {
-                    seen_a |= (a[u] == a[t]) & (a[u + 1] == a[t + 1]);
-                    seen_b |= (b[u] == b[t]) & (b[u + 1] == b[t + 1]);
-                }
-                m |= ((b[u] == a[t]) & (b[u + 1] == a[t + 1])) ? (1u << u) : 0u;
-            }
-            first_a |= seen_a ? 0u : (1u << t);
-            first_b |= seen_b ? 0u : (1u << t);
-            in_b[t] = m;
-        }
-
-        for (int l = 0; l < lens.n; ++l) {
-            // a prefix of length n holds bigram positions 0 .. n-2
-            const unsigned ma = li[l] >= 2 ? (0xFFFFFFFFu >> (33 - li[l])) : 0u;
-            const unsigned mb = lj[l] >= 2 ? (0xFFFFFFFFu >> (33 - lj[l])) : 0u;
-            const int na = __popc(first_a & ma), nb = __popc(first_b & mb);
-            int inter = 0;
-#pragma unroll
-            for (int t = 0; t < KMAX - 1; ++t) inter += (((first_a & ma) >> t) & 1u) & ((in_b[t] & mb) != 0u ? 1u : 0u);
-            PairRec rec;
-            rec.lev = (uint8_t)res[l];
-            rec.longer = (uint8_t)max(li[l], lj[l]);
-            rec.inter = (uint8_t)inter;
-            rec.uni = (uint8_t)(na + nb - inter);
-            rec.same = (uint8_t)(li[l] == lj[l] && res[l] == 0u);
-            s_pair[l][tid] = rec;
         }
     }
     __syncthreads();
 
-    // one thread per (K, group): pair terms in pair order, then the per-member counts
-    for (int w = tid; w < lens.n * n_here; w += kSigThreads) {
-        const int l = w / n_here, g = w - l * n_here;
-        const int K = lens.len[l];
-        const PairRec *pr = &s_pair[l][g * pairs];
-        double dsum = 0.0, jsum = 0.0;
-        long long scaled = 0;
-        int lev_sum = 0;
-        for (int q = 0; q < pairs; ++q) {
-            const PairRec r = pr[q];
-            lev_sum += r.lev;
-            if (r.longer > 0) {
-                dsum += (double)r.lev / (double)r.longer;
-                scaled += (long long)r.lev * (kLcm32 / r.longer);
+    // Four sums per (K, group), a wavefront for each where the workgroup has four: pair terms in pair order, entropy
+    // terms in member order.
+    const int n_rec = NL * n_here, waves = nt >> 6;
+    const float inv_here = 1.0f / (float)n_here;
+    for (int kind = tid >> 6; kind < 4; kind += waves) {
+        for (int w = tid & 63; w < n_rec; w += 64) {
+            const int l = min((int)(((float)w + 0.5f) * inv_here), NL - 1), g = w - l * n_here;
+            sr_signals_t *o = s_out + l * q.groups + g;
+            if (kind < 2) {
+                const double *t = (kind == 0 ? s_d : s_j) + l * n_pairs + g * pairs;
+                double sum = 0.0;
+#pragma unroll 4
+                for (int k = 0; k < pairs; ++k) sum += t[k];
+                sum /= (double)pairs;
+                if (kind == 0) o->d_K = sum;
+                else o->bigram_jaccard = sum;
+            } else if (kind == 2) {
+                const uint16_t *t = s_pair + l * n_pairs + g * pairs;
+                long long scaled = 0;
+                int lev_sum = 0;
+                unsigned repeats = 0;                 // members whose prefix an earlier member has
+                int i = 0, j = 1;
+#pragma unroll 4
+                for (int k = 0; k < pairs; ++k) {
+                    const int x = t[k], lev = x & 63;
+                    lev_sum += lev;
+                    scaled += lev * s_lcm[(x >> 6) & 63];
+                    repeats |= (unsigned)(x >> 12) << j;
+                    if (++j == G) { ++i; j = i + 1; }
+                }
+                o->lev_scaled = scaled;
+                o->lev_sum = lev_sum;
+                o->unique_prefix = G - __popc(repeats);
+            } else {
+                const int *t = s_hold + l * n_rows + g * G;
+                const double *lg = s_h + l * n_rows + g * G;
+                int n_at = 0, n_done = 0, ua = 0, uo = 0;
+                for (int k = 0; k < G; ++k) {
+                    n_at += (t[k] >> 6) & 1;
+                    n_done += t[k] >> 7;
+                    uo += (t[k] >> 5) & 1;
+                    ua += (t[k] & 31) ? 1 : 0;
+                }
+                double H = 0.0;
+                for (int k = 0; k < G; ++k)
+                    if (t[k] & 31) H = __builtin_fma(-((double)(t[k] & 31) / (double)n_at), lg[k], H);
+                o->action_entropy = H;
+                o->n_at_step = n_at;
+                o->unique_action = ua;
+                o->unique_obs = obs ? uo : 0;
+                o->n_done = n_done;
             }
-            jsum += r.uni > 0 ? 1.0 - (double)r.inter / (double)r.uni : 0.0;
         }
-        // member j repeats an earlier prefix iff some pair (i, j), i < j, is marked `same`
-        int uniq = 0, n_at = 0, ua = 0, uo = 0, n_done = 0;
-        double H = 0.0;
-        const int32_t *acts = s_act + g * G * KMAX;
-        const int32_t *ends = s_end + g * G;
-        const int32_t *ob = &s_obs[l][g * G];
-        for (int j = 0; j < G; ++j) n_at += min(K, ends[j]) == K ? 1 : 0;
-        for (int j = 0; j < G; ++j) {
-            bool dup = false;
-            for (int i = 0; i < j; ++i) {
-                const int q = i * G - i * (i + 1) / 2 + (j - i - 1);     // index of pair (i, j)
-                dup |= pr[q].same != 0;
-            }
-            uniq += dup ? 0 : 1;
-            n_done += ends[j] <= K ? 1 : 0;
-            if (min(K, ends[j]) != K) continue;
-            const int32_t aj = acts[j * KMAX + K - 1];
-            bool first_act = true, first_obs = true;
-            int count = 0;
-            for (int i = 0; i < G; ++i) {
-                if (min(K, ends[i]) != K) continue;
-                const bool same_a = acts[i * KMAX + K - 1] == aj;
-                count += same_a ? 1 : 0;
-                if (i < j && same_a) first_act = false;
-                if (i < j && ob[i] == ob[j]) first_obs = false;
-            }
-            if (first_act) {
-                ++ua;
-                const double pj = (double)count / (double)n_at;
-                H -= pj * log(pj);
-            }
-            if (first_obs) ++uo;
-        }
-        sr_signals_t o;
-        const double P = (double)pairs;
-        o.d_K = dsum / P;
-        o.lev_scaled = scaled;
-        o.bigram_jaccard = jsum / P;
-        o.action_entropy = H;
-        o.unique_prefix = uniq;
-        o.n_at_step = n_at;
-        o.unique_action = ua;
-        o.unique_obs = obs ? uo : 0;
-        o.n_done = n_done;
-        o.lev_sum = lev_sum;
-        o.cut_d = (uint8_t)(scaled < lens.d_bound);
-        o.cut_or = (uint8_t)(o.cut_d || (long long)n_done * 1000000LL >= lens.tau_num * G);
-        for (int i = 0; i < 6; ++i) o.reserved[i] = 0;
-        out[(size_t)l * n_groups + g0 + g] = o;
+    }
+    __syncthreads();
+    for (int w = tid; w < n_rec; w += nt) {
+        const int l = min((int)(((float)w + 0.5f) * inv_here), NL - 1), g = w - l * n_here;
+        sr_signals_t *o = s_out + l * q.groups + g;
+        o->cut_d = (uint8_t)(o->lev_scaled < lens.d_bound);
+        o->cut_or = (uint8_t)(o->cut_d || (long long)o->n_done * 1000000LL >= lens.tau_num * G);
+        for (int i = 0; i < 6; ++i) o->reserved[i] = 0;
+    }
+    __syncthreads();
+    for (int w = tid; w < n_rec * 4; w += nt) {              // 16 bytes per lane, whole records of a K in a row
+        const int rec = w >> 2, l = min((int)(((float)rec + 0.5f) * inv_here), NL - 1), g = rec - l * n_here;
+        ((uint4 *)(out + (size_t)l * n_groups + g0 + g))[w & 3] = ((const uint4 *)(s_out + l * q.groups + g))[w & 3];
     }
 }
 
@@ -289,17 +330,20 @@ extern "C" int sr_signals_batch(const int32_t *actions, const int32_t *obs, cons
     if (n_groups == 0) return SR_OK;
     const int pairs = G * (G - 1) / 2;
     const int kmax = maxlen <= 8 ? 8 : maxlen <= 16 ? 16 : maxlen <= 24 ? 24 : 32;
-    int gpb = kSigThreads / pairs;
-    if (gpb > kSigLdsInts / (G * kmax)) gpb = kSigLdsInts / (G * kmax);
-    if (gpb > kSigThreads / G) gpb = kSigThreads / G;         // per-member staging arrays hold 256 entries
-    if (gpb < 1) return SR_E_ARG;
-    dim3 grid((n_groups + gpb - 1) / gpb), block(kSigThreads);
+    for (int n = 1; n <= 32; ++n) lens.lcm_over[n] = kLcm32 / n;
+    PrefixGeom q{};
+    const int extra = sig_lds(G, pairs, 1, n_lens).total;
+    if (!prefix_geometry(n_groups, G, maxlen, kmax, kSigLds, extra, &q) &&
+        !prefix_geometry(n_groups, G, maxlen, kmax, kSigLdsMost, extra, &q))
+        return SR_E_ARG;
+    const size_t lds = prefix_lds(q, q.groups, kmax).total + (size_t)sig_lds(G, pairs, q.groups, n_lens).total;
+    dim3 grid((n_groups + q.groups - 1) / q.groups), block(q.threads);
     hipStream_t st = (hipStream_t)stream;
     switch (kmax) {
-        case 8:  signals_kernel<8><<<grid, block, 0, st>>>(actions, obs, end_step, n_groups, G, stride, pairs, gpb, lens, out); break;
-        case 16: signals_kernel<16><<<grid, block, 0, st>>>(actions, obs, end_step, n_groups, G, stride, pairs, gpb, lens, out); break;
-        case 24: signals_kernel<24><<<grid, block, 0, st>>>(actions, obs, end_step, n_groups, G, stride, pairs, gpb, lens, out); break;
-        default: signals_kernel<32><<<grid, block, 0, st>>>(actions, obs, end_step, n_groups, G, stride, pairs, gpb, lens, out); break;
+        case 8:  signals_kernel<8><<<grid, block, lds, st>>>(actions, obs, end_step, n_groups, stride, pairs, q, lens, out); break;
+        case 16: signals_kernel<16><<<grid, block, lds, st>>>(actions, obs, end_step, n_groups, stride, pairs, q, lens, out); break;
+        case 24: signals_kernel<24><<<grid, block, lds, st>>>(actions, obs, end_step, n_groups, stride, pairs, q, lens, out); break;
+        default: signals_kernel<32><<<grid, block, lds, st>>>(actions, obs, end_step, n_groups, stride, pairs, q, lens, out); break;
     }
     SR_HIP(hipGetLastError());
     return SR_OK;

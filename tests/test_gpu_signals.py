@@ -105,3 +105,14 @@ def test_bad_arguments():
     with pytest.raises(sr.SrError):
         sr.sr_signals_batch(torch.zeros((4, 1, 10), dtype=torch.int32, device="cuda"), [5], 0.3, 0.5, out)
     sr.sr_signals_batch(a[:0], [5], 0.3, 0.5, out)                         # no groups: nothing to do
+
+
+@pytest.mark.parametrize("n_groups,G,lens", [(9001, 2, [32, 2]), (4099, 8, [16, 1, 2]), (2051, 8, [32]), (1025, 16, [32, 31, 30, 17, 16, 8, 2, 1]),
+                                             (6001, 5, [24])])
+def test_signals_groups_per_workgroup(n_groups, G, lens):
+    """As many groups per workgroup as lanes and LDS hold, the largest table (16 members, 32 steps, 8 prefix lengths),
+    members that finish before the first step."""
+    acts, obs, end = make(n_groups, G, max(lens), 4, seed=n_groups)
+    end[::7, 0] = 0
+    end[::11, :2] = 0
+    check(acts, lens, d_L=0.25, tau_H=0.5, obs=obs, end=end)
