@@ -35,20 +35,112 @@ __device__ __forceinline__ bf16x8 load_frag(const uint16_t *p) {
     else return __builtin_bit_cast(bf16x8, *(const u32x4 *)p);
 }
 
-// One launch may cover two phases (decode: the shared-prompt phase followed by the private phase), so
-// that the short, narrow shared phase overlaps the private one instead of running alone.
+// Reductions over the four lanes (c, g), g = 0 .. 3, that hold one query row: the halves of the wavefront, then the
+// neighbouring 16-lane rows, exchanged by vector instructions instead of a round trip through LDS each.
+__device__ __forceinline__ float row_max(float x) {
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(h[0]), __uint_as_float(h[1]));
+    const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
+
+// Online softmax of one 32-token block for one row tile.  s holds the raw scores of tokens t0 + tt*16 + 4g + e of query row
+// c; tokens above `lim` are invisible (MASKED; otherwise every token is visible to every used row).  The running maximum is
+// kept in units of score * scale * log2(e), the scale is folded into the exponent's multiply-add, and the exponentials are
+// the hardware's base-2 exponential as it is (arguments <= 0; results below 2^-126 of the row maximum may flush to zero).
+// Leaves the probabilities packed for the P^T operand and the factor by which earlier sums shrink.
+template <bool MASKED>
+__device__ __forceinline__ void softmax_block(f32x4 (&s)[2], int t, int lim, float scale_log2, float &mrun, float &lrun,
+                                              bf16x8 &pf, float &alpha) {
+    bool ok[2][4];
+#pragma unroll
+    for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            ok[tt][e] = !MASKED || t + tt * 16 + e <= lim;
+            if (MASKED) s[tt][e] = ok[tt][e] ? s[tt][e] : kNegBig;
+        }
+    const float bmax = row_max(fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
+                                     fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3]))));
+    const float mnew = fmaxf(mrun, bmax * scale_log2);
+    alpha = __builtin_amdgcn_exp2f(mrun - mnew);
+    mrun = mnew;
+    float pv[8], psum = 0.f;
+#pragma unroll
+    for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float pe = __builtin_amdgcn_exp2f(fmaf(s[tt][e], scale_log2, -mnew));
+            pv[tt * 4 + e] = ok[tt][e] ? pe : 0.f;
+            psum += pv[tt * 4 + e];
+        }
+    lrun = lrun * alpha + psum;
+    pf = __builtin_bit_cast(bf16x8, make_uint4(pack_bf16x2(pv[0], pv[1]), pack_bf16x2(pv[2], pv[3]),
+                                               pack_bf16x2(pv[4], pv[5]), pack_bf16x2(pv[6], pv[7])));
+}
+
+// Write the results of one work item: O^T tile lane (c, g) holds head dims dt*16 + 4g .. 4g+3 of row (rt, c).
 template <int D, int RT>
-__global__ __launch_bounds__(256, RT == 1 ? 3 : 2) void attn_kernel(AttnArgs a, AttnPhase p0, AttnPhase p1, int n0, int n_items) {
+__device__ __forceinline__ void store_item(const AttnArgs &a, const AttnPhase &p, const f32x4 (&o)[D / 16][RT],
+                                           const float (&mrun)[RT], const float (&lrun)[RT], const int (&limit)[RT],
+                                           int item, size_t first_tok, int kvh, int n_rep, int c, int g) {
+    constexpr int DT = D / 16;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+        float l = lrun[rt];
+        l += __shfl_xor(l, 16, 64);
+        l += __shfl_xor(l, 32, 64);
+        if (limit[rt] < 0) continue;            // padding row of the tile: nobody reads it
+        const int row = rt * 16 + c;
+        if (a.direct_out) {
+            // the only partial result of its rows: what the merge of one item computes, o / l (0 for an empty row)
+            const int col = (kvh * n_rep + row % n_rep) * D + 4 * g;
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) {
+                float r[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) r[e] = l > 0.f ? o[dt][rt][e] / l : 0.f;
+                *(uint2 *)(a.direct_out + frag_offset((int)(first_tok + row / n_rep), col + dt * 16, a.out_mt_total)) =
+                    make_uint2(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]));
+            }
+            continue;
+        }
+        const size_t prow = (size_t)item * (16 * RT) + row;
+        float *po = p.part_o + prow * D;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) *(f32x4 *)(po + dt * 16 + 4 * g) = o[dt][rt];
+        if (g == 0) *(float2 *)(p.part_ml + prow * 2) = make_float2(mrun[rt], l);
+    }
+}
+
+// Queries of one work item: operand fragments, and the last visible token of each row (-1 = row unused)
+template <int D, int RT>
+__device__ __forceinline__ void load_queries(const AttnArgs &a, const AttnPhase &p, bf16x8 (&qf)[RT][D / 32], int (&limit)[RT],
+                                             int qtile, int u_row0, int u_count, int kvh, int n_rep, int c, int g) {
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+        const int row = rt * 16 + c;
+        const int qi = qtile * p.q_per_item + row / n_rep;       // query token within the unit
+        const int hr = row % n_rep;
+        const bool used = qtile < p.items_per_unit && row < p.q_per_item * n_rep && qi < u_count;
+        limit[rt] = used ? p.causal_pos0 + qi * p.causal_stride : -1;
+        const uint16_t *qp = a.q + (((size_t)u_row0 + qi) * a.n_q + kvh * n_rep + hr) * D + 8 * g;
+#pragma unroll
+        for (int ks = 0; ks < D / 32; ++ks) {
+            uint4 raw = make_uint4(0, 0, 0, 0);
+            if (used) raw = *(const uint4 *)(qp + ks * 32);
+            qf[rt][ks] = __builtin_bit_cast(bf16x8, raw);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// One work item alone (a sequence's private context during decode; units with few query tiles).
+// ---------------------------------------------------------------------------------------------
+template <int D, int RT>
+__device__ __forceinline__ void single_item(const AttnArgs &a, const AttnPhase &p, int item, int lane) {
     constexpr int KS = D / 32;     // k-steps of the QK^T contraction
     constexpr int DT = D / 16;     // 16-wide tiles of the head dimension
-    const int lane = threadIdx.x & 63;
-    // the wavefront index is uniform: tell the compiler, so that everything derived from the work item
-    // (phase, token range, page-table reads) lives in scalar registers
-    const int gitem = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (gitem >= n_items) return;
-    const bool second = gitem >= n0;
-    const AttnPhase &p = second ? p1 : p0;
-    const int item = second ? gitem - n0 : gitem;
 
     // item -> (unit, kv head, split, q tile): the q tiles of one split are neighbours
     int rest = item;
@@ -71,35 +163,26 @@ __global__ __launch_bounds__(256, RT == 1 ? 3 : 2) void attn_kernel(AttnArgs a, 
     };
     const int t_lo = p.t_begin + split * p.split_tokens;
 
-    // query rows of this lane's column c in each row tile
     bf16x8 qf[RT][KS];
-    int limit[RT];                  // last visible token of row (rt, c); -1 = row unused
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-        const int row = rt * 16 + c;
-        const int qi = qtile * p.q_per_item + row / n_rep;       // query token within the unit
-        const int hr = row % n_rep;
-        const bool used = (row < p.q_per_item * n_rep) && (qi < u_count);
-        limit[rt] = used ? p.causal_pos0 + qi * p.causal_stride : -1;
-        const size_t qtok = (size_t)u_row0 + qi;
-        const uint16_t *qp = a.q + (qtok * a.n_q + kvh * n_rep + hr) * D + 8 * g;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            uint4 raw = make_uint4(0, 0, 0, 0);
-            if (used) raw = *(const uint4 *)(qp + ks * 32);
-            qf[rt][ks] = __builtin_bit_cast(bf16x8, raw);
-        }
-    }
+    int limit[RT];
+    load_queries<D, RT>(a, p, qf, limit, qtile, u_row0, u_count, kvh, n_rep, c, g);
 
     // token range of this split, clipped to what any row of the item can see
-    int max_limit = -1;
+    int max_limit = -1, min_limit = 0x7FFFFFFF;
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) max_limit = max(max_limit, limit[rt]);
+    for (int rt = 0; rt < RT; ++rt) {
+        max_limit = max(max_limit, limit[rt]);
+        min_limit = min(min_limit, limit[rt] < 0 ? 0x7FFFFFFF : limit[rt]);
+    }
 #pragma unroll
-    for (int off = 1; off < 16; off <<= 1) max_limit = max(max_limit, __shfl_xor(max_limit, off, 64));
-    // the same in every lane after the reduction; kept in a scalar register so that the block loop, the
+    for (int off = 1; off < 16; off <<= 1) {
+        max_limit = max(max_limit, __shfl_xor(max_limit, off, 64));
+        min_limit = min(min_limit, __shfl_xor(min_limit, off, 64));
+    }
+    // the same in every lane after the reduction; kept in scalar registers so that the block loop, the
     // page-table lookups and the block addresses stay on the scalar unit
     const int t_hi = __builtin_amdgcn_readfirstlane(min(min(p.t_end, t_lo + p.split_tokens), max_limit + 1));
+    const int t_vis = __builtin_amdgcn_readfirstlane(min(t_hi, min_limit == 0x7FFFFFFF ? 0 : min_limit + 1));
 
     f32x4 o[DT][RT];
 #pragma unroll
@@ -136,43 +219,6 @@ __global__ __launch_bounds__(256, RT == 1 ? 3 : 2) void attn_kernel(AttnArgs a, 
                     s[rt][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[tt][ks], qf[rt][ks], s[rt][tt], 0, 0, 0);
             }
     };
-    // online softmax of one block; leaves the packed probabilities and the rescale factor per row tile
-    auto softmax = [&](f32x4 (&s)[RT][2], int t0, bf16x8 (&pf)[RT], float (&alpha)[RT]) {
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            // lane holds tokens t0 + tt*16 + 4g + e of query row (rt, c)
-            const int lim = min(limit[rt], t_hi - 1);
-            float bmax = kNegBig;
-            bool ok[2][4];
-#pragma unroll
-            for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    ok[tt][e] = (t0 + tt * 16 + 4 * g + e) <= lim;
-                    s[rt][tt][e] = ok[tt][e] ? s[rt][tt][e] * scale_log2 : kNegBig;
-                    bmax = fmaxf(bmax, s[rt][tt][e]);
-                }
-            bmax = fmaxf(bmax, __shfl_xor(bmax, 16, 64));
-            bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
-            const float mnew = fmaxf(mrun[rt], bmax);
-            alpha[rt] = exp2f(mrun[rt] - mnew);
-            mrun[rt] = mnew;
-            float psum = 0.f;
-            float pv[8];
-#pragma unroll
-            for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float pe = ok[tt][e] ? exp2f(s[rt][tt][e] - mnew) : 0.f;
-                    pv[tt * 4 + e] = pe;
-                    psum += pe;
-                }
-            lrun[rt] = lrun[rt] * alpha[rt] + psum;
-            const uint4 praw = make_uint4(pack_bf16x2(pv[0], pv[1]), pack_bf16x2(pv[2], pv[3]),
-                                          pack_bf16x2(pv[4], pv[5]), pack_bf16x2(pv[6], pv[7]));
-            pf[rt] = __builtin_bit_cast(bf16x8, praw);
-        }
-    };
     // O^T = alpha O^T + V^T P^T
     auto accumulate = [&](const bf16x8 (&pf)[RT], const float (&alpha)[RT]) {
 #pragma unroll
@@ -207,7 +253,15 @@ __global__ __launch_bounds__(256, RT == 1 ? 3 : 2) void attn_kernel(AttnArgs a, 
             __builtin_amdgcn_sched_barrier(0);
             bf16x8 pf[RT];
             float alpha[RT];
-            softmax(s, t0, pf, alpha);
+            if (t0 + 32 <= t_vis) {                         // uniform: all but the last block of a range
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+                    softmax_block<false>(s[rt], 0, 0, scale_log2, mrun[rt], lrun[rt], pf[rt], alpha[rt]);
+            } else {
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+                    softmax_block<true>(s[rt], t0 + 4 * g, min(limit[rt], t_hi - 1), scale_log2, mrun[rt], lrun[rt], pf[rt], alpha[rt]);
+            }
             accumulate(pf, alpha);
             __builtin_amdgcn_sched_barrier(0);
             load_v(stream, a.vpool + base_n);
@@ -216,63 +270,50 @@ __global__ __launch_bounds__(256, RT == 1 ? 3 : 2) void attn_kernel(AttnArgs a, 
     };
     if (p.stream_loads) block_loop(std::true_type{});       // uniform: one of two copies of the loop runs
     else block_loop(std::false_type{});
+    store_item<D, RT>(a, p, o, mrun, lrun, limit, item, (size_t)u_row0 + qtile * p.q_per_item, kvh, n_rep, c, g);
+}
 
-    // results: O^T tile lane (c, g) holds head dims dt*16 + 4g..4g+3 of row (rt, c)
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-        float l = lrun[rt];
-        l += __shfl_xor(l, 16, 64);
-        l += __shfl_xor(l, 32, 64);
-        if (a.direct_out) {
-            // the only partial result of its rows: what the merge of one item computes, o / l (0 for an empty row)
-            if (limit[rt] < 0) continue;
-            const int row = rt * 16 + c;
-            const size_t qtok = (size_t)u_row0 + qtile * p.q_per_item + row / n_rep;
-            const int col = (kvh * n_rep + row % n_rep) * D + 4 * g;
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt) {
-                float r[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) r[e] = l > 0.f ? o[dt][rt][e] / l : 0.f;
-                *(uint2 *)(a.direct_out + frag_offset((int)qtok, col + dt * 16, a.out_mt_total)) =
-                    make_uint2(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]));
-            }
-            continue;
-        }
-        const size_t prow = (size_t)item * (16 * RT) + rt * 16 + c;
-        float *po = p.part_o + prow * D;
-        if (limit[rt] < 0) continue;        // padding row of the tile: the merge never reads it
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) *(f32x4 *)(po + dt * 16 + 4 * g) = o[dt][rt];
-        if (g == 0) {
-            p.part_ml[prow * 2] = mrun[rt];
-            p.part_ml[prow * 2 + 1] = l;
-        }
-    }
+// One launch may cover two phases (decode: the shared-prompt phase followed by the private phase), so
+// that the short, narrow shared phase overlaps the private one instead of running alone.
+template <int D, int RT>
+__global__ __launch_bounds__(256, RT == 1 ? 3 : 2) void attn_kernel(AttnArgs a, AttnPhase p0, AttnPhase p1, int n0, int n_items) {
+    // the wavefront index is uniform: tell the compiler, so that everything derived from the work item
+    // (phase, token range, page-table reads) lives in scalar registers
+    const int gitem = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (gitem >= n_items) return;
+    const bool second = gitem >= n0;
+    single_item<D, RT>(a, second ? p1 : p0, second ? gitem - n0 : gitem, threadIdx.x & 63);
 }
 
 // ---------------------------------------------------------------------------------------------
-// Prefill attention: the four work items of a workgroup are four consecutive query tiles of one
-// (unit, kv head) and need the same K/V blocks, so a block goes from global memory to LDS once per
-// workgroup (each thread copies its 16-byte slots, one block ahead, through registers) and every
-// wavefront takes its MFMA operands from LDS: a quarter of the vector-memory traffic of the kernel
-// above, which at a context of thousands of tokens is bound by what L2 can deliver.  Two LDS buffers,
-// one workgroup barrier per block.  One split, one phase: the normalised output is written directly.
+// Four query tiles of one (unit, kv head, split) per workgroup: they need the same K/V blocks (prefill: consecutive query
+// tiles of a chunk; decode: the members of a group over their shared prompt), so a block goes from global memory to LDS
+// once per workgroup and every wavefront takes its MFMA operands from there.  The copies are direct-to-LDS loads, a
+// quarter of a block per wavefront, two blocks ahead through three buffers (96 to 144 KiB of a compute unit's LDS in
+// flight or in use at two or three workgroups), with one barrier per block; they are issued from inline assembly, so
+// that the compiler does not wait for them before LDS reads, and the wait is placed by hand: a wavefront's
+// vector-memory operations retire in order, so "all but the newest block's copies" is a count.
+// The query tiles of one (unit, kv head) beyond the first four go to workgroups on the same XCD, whose L2 then serves
+// them.
 // ---------------------------------------------------------------------------------------------
+constexpr int kShBufs = 3;
+
 template <int D, int RT>
-__global__ __launch_bounds__(256, 2) void attn_prefill_shared_kernel(AttnArgs a, AttnPhase p) {
+__device__ __forceinline__ void shared_tiles(const AttnArgs &a, const AttnPhase &p, int wg, u32x4 *lds) {
     constexpr int KS = D / 32, DT = D / 16;
     constexpr int SLOTS = 32 * D / 8;              // 16-byte slots of one K (or V) block
-    constexpr int NS = SLOTS / 256;                // slots per thread
-    __shared__ u32x4 lds[2][2][SLOTS];             // [buffer][K, V][slot]
+    constexpr int SEGS = SLOTS / 256;              // 1 KiB copies per wavefront of one K (or V) block
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    const int groups_per_unit = (p.items_per_unit + 3) >> 2;
-    int rest = blockIdx.x;
-    const int qg = rest % groups_per_unit; rest /= groups_per_unit;
+    // workgroup -> (set = unit, kv head, split; four of its query tiles), the workgroups of a set 8 apart
+    const int per_set = (p.items_per_unit + 3) >> 2;
+    const int set = (wg >> 3) / per_set * 8 + (wg & 7), qg = (wg >> 3) % per_set;
+    int rest = set;
+    const int split = rest % p.n_splits; rest /= p.n_splits;
     const int kvh = rest % a.n_kv;
     const int unit = rest / a.n_kv;
+    if (unit >= p.n_units) return;                 // the grid is padded to whole rounds of eight sets
     const int qtile = qg * 4 + wave;               // beyond items_per_unit: this wavefront only helps with the copies
     const int n_rep = a.n_q / a.n_kv;
 
@@ -280,30 +321,11 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_shared_kernel(AttnArgs a,
     const int u_row0 = p.unit_row0 ? p.unit_row0[unit] : unit * p.q_per_unit;
     const int u_count = p.unit_count ? p.unit_count[unit] : p.q_per_unit;
     const int32_t *pt = a.page_table + (size_t)(p.unit_row0 ? u_row0 : unit * p.pt_row_stride) * a.pt_stride;
-    const int blocks_per_page = a.page_tokens >> 5;
-    auto block_base = [&](int t0) -> size_t {
-        const int page = pt[t0 / a.page_tokens];
-        const int blk = (t0 % a.page_tokens) >> 5;
-        return (((size_t)page * a.n_kv + kvh) * blocks_per_page + blk) * (size_t)(32 * D);
-    };
+    const int page_shift = 31 - __builtin_clz(a.page_tokens);      // 32, 64 or 128 tokens
 
     bf16x8 qf[RT][KS];
     int limit[RT];
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-        const int row = rt * 16 + c;
-        const int qi = qtile * p.q_per_item + row / n_rep;
-        const int hr = row % n_rep;
-        const bool used = qtile < p.items_per_unit && (row < p.q_per_item * n_rep) && (qi < u_count);
-        limit[rt] = used ? p.causal_pos0 + qi * p.causal_stride : -1;
-        const uint16_t *qp = a.q + (((size_t)u_row0 + qi) * a.n_q + kvh * n_rep + hr) * D + 8 * g;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            uint4 raw = make_uint4(0, 0, 0, 0);
-            if (used) raw = *(const uint4 *)(qp + ks * 32);
-            qf[rt][ks] = __builtin_bit_cast(bf16x8, raw);
-        }
-    }
+    load_queries<D, RT>(a, p, qf, limit, qtile, u_row0, u_count, kvh, n_rep, c, g);
     int max_limit = -1, min_limit = 0x7FFFFFFF;      // over the used rows of this wavefront
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
@@ -315,13 +337,14 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_shared_kernel(AttnArgs a,
         max_limit = max(max_limit, __shfl_xor(max_limit, off, 64));
         min_limit = min(min_limit, __shfl_xor(min_limit, off, 64));
     }
-    // tokens below t_vis are visible to every used row (unused rows hold zero queries and are never written out)
-    const int t_vis = __builtin_amdgcn_readfirstlane(min_limit == 0x7FFFFFFF ? 0 : min_limit + 1);
+    const int t_lo = p.t_begin + split * p.split_tokens, t_end = min(p.t_end, t_lo + p.split_tokens);
     // this wavefront's range, and the workgroup's: its last query token sees the most
-    const int t_hi = __builtin_amdgcn_readfirstlane(min(p.t_end, max_limit + 1));
+    const int t_hi = __builtin_amdgcn_readfirstlane(min(t_end, max_limit + 1));
+    // tokens below t_vis are visible to every used row (unused rows hold zero queries and are never written out)
+    const int t_vis = __builtin_amdgcn_readfirstlane(min(t_hi, min_limit == 0x7FFFFFFF ? 0 : min_limit + 1));
     const int last_q = min((qg * 4 + 4) * p.q_per_item, u_count) - 1;
-    const int t_hi_wg = min(p.t_end, p.causal_pos0 + last_q * p.causal_stride + 1);
-    const int n_blocks = (t_hi_wg - p.t_begin + 31) >> 5;          // t_begin is a multiple of 32
+    const int t_hi_wg = min(t_end, p.causal_pos0 + last_q * p.causal_stride + 1);
+    const int n_blocks = __builtin_amdgcn_readfirstlane((t_hi_wg - t_lo + 31) >> 5);       // t_lo is a multiple of 32
 
     f32x4 o[DT][RT];
 #pragma unroll
@@ -333,29 +356,35 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_shared_kernel(AttnArgs a,
     for (int rt = 0; rt < RT; ++rt) { mrun[rt] = kNegBig; lrun[rt] = 0.f; }
     const float scale_log2 = a.scale * 1.4426950408889634f;
 
-    u32x4 sk[NS], sv[NS];                           // this thread's slots of the block being brought in
-    auto fetch = [&](int blk) {
-        const size_t base = block_base(p.t_begin + 32 * blk);
-        const u32x4 *ksrc = (const u32x4 *)(a.kpool + base), *vsrc = (const u32x4 *)(a.vpool + base);
+    const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void *)lds;
+    // a block's page is read one block before its copies are issued, so that they do not wait for it
+    auto page_of = [&](int blk) { return pt[(t_lo + 32 * min(blk, n_blocks - 1)) >> page_shift]; };
+    auto copy = [&](int blk, int page, int buf) {    // past the end: a harmless re-read of the last block
+        const int t0 = t_lo + 32 * min(blk, n_blocks - 1);
+        const int in_page = (t0 & (a.page_tokens - 1)) >> 5;
+        const size_t base = ((((size_t)page * a.n_kv + kvh) << (page_shift - 5)) + in_page) * SLOTS + wave * (SEGS * 64) + lane;
+        const unsigned dst = lds0 + (unsigned)(buf * 2 * SLOTS + wave * (SEGS * 64)) * 16;
 #pragma unroll
-        for (int i = 0; i < NS; ++i) { sk[i] = ksrc[tid + 256 * i]; sv[i] = vsrc[tid + 256 * i]; }
-    };
-    auto stash = [&](int buf) {
+        for (int i = 0; i < SEGS; ++i) lds_dma16((const u32x4 *)a.kpool + base + i * 64, dst + i * 1024);
 #pragma unroll
-        for (int i = 0; i < NS; ++i) { lds[buf][0][tid + 256 * i] = sk[i]; lds[buf][1][tid + 256 * i] = sv[i]; }
+        for (int i = 0; i < SEGS; ++i) lds_dma16((const u32x4 *)a.vpool + base + i * 64, dst + (SLOTS + i * 64) * 16);
     };
 
     if (n_blocks > 0) {
-        fetch(0);
-        stash(0);
-        __syncthreads();
-        if (n_blocks > 1) fetch(1);
-    }
-    for (int blk = 0; blk < n_blocks; ++blk) {
-        const int buf = blk & 1;
-        const int t0 = p.t_begin + 32 * blk;
-        if (t0 < t_hi) {                            // uniform per wavefront: later blocks are invisible to all its rows
-            const u32x4 *kb = lds[buf][0], *vb = lds[buf][1];
+        copy(0, page_of(0), 0);
+        copy(1, page_of(1), 1);
+        int page = page_of(2), buf = 0;
+        for (int blk = 0; blk < n_blocks; ++blk) {
+            __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * SEGS));      // this wavefront's part of block blk has landed
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();                         // ... and everybody's; nobody reads block blk - 1 any more
+            asm volatile("" ::: "memory");
+            copy(blk + 2, page, buf == 0 ? 2 : buf - 1);
+            page = page_of(blk + 3);
+            const int t0 = t_lo + 32 * blk;
+            const u32x4 *kb = lds + buf * 2 * SLOTS, *vb = kb + SLOTS;
+            buf = buf == kShBufs - 1 ? 0 : buf + 1;
+            if (t0 >= t_hi) continue;               // uniform per wavefront: invisible to all its rows
             f32x4 s[RT][2];
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt)
@@ -373,161 +402,143 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_shared_kernel(AttnArgs a,
                 }
             bf16x8 pf[RT];
             float alpha[RT];
-            // Online softmax.  A block that every used row sees entirely (all but the last one or two of a range)
-            // skips the per-token visibility tests; the exponentials are the hardware's base-2 exponential as it is
-            // (arguments <= 0; results below 2^-126 of the row maximum may flush to zero).
-            auto softmax = [&](auto masked) __attribute__((always_inline)) {
-                constexpr bool MASKED = decltype(masked)::value;
+            if (t0 + 32 <= t_vis) {
 #pragma unroll
-                for (int rt = 0; rt < RT; ++rt) {
-                    const int lim = min(limit[rt], t_hi - 1);
-                    float bmax = kNegBig;
-                    bool ok[2][4];
+                for (int rt = 0; rt < RT; ++rt)
+                    softmax_block<false>(s[rt], 0, 0, scale_log2, mrun[rt], lrun[rt], pf[rt], alpha[rt]);
+            } else {
 #pragma unroll
-                    for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            ok[tt][e] = !MASKED || (t0 + tt * 16 + 4 * g + e) <= lim;
-                            s[rt][tt][e] = ok[tt][e] ? s[rt][tt][e] * scale_log2 : kNegBig;
-                            bmax = fmaxf(bmax, s[rt][tt][e]);
-                        }
-                    bmax = fmaxf(bmax, __shfl_xor(bmax, 16, 64));
-                    bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
-                    const float mnew = fmaxf(mrun[rt], bmax);
-                    alpha[rt] = __builtin_amdgcn_exp2f(mrun[rt] - mnew);
-                    mrun[rt] = mnew;
-                    float psum = 0.f;
-                    float pv[8];
-#pragma unroll
-                    for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const float pe = ok[tt][e] ? __builtin_amdgcn_exp2f(s[rt][tt][e] - mnew) : 0.f;
-                            pv[tt * 4 + e] = pe;
-                            psum += pe;
-                        }
-                    lrun[rt] = lrun[rt] * alpha[rt] + psum;
-                    const uint4 praw = make_uint4(pack_bf16x2(pv[0], pv[1]), pack_bf16x2(pv[2], pv[3]),
-                                                  pack_bf16x2(pv[4], pv[5]), pack_bf16x2(pv[6], pv[7]));
-                    pf[rt] = __builtin_bit_cast(bf16x8, praw);
-                }
-            };
-            if (t0 + 32 <= t_vis && t0 + 32 <= t_hi) softmax(std::false_type{});
-            else softmax(std::true_type{});
+                for (int rt = 0; rt < RT; ++rt)
+                    softmax_block<true>(s[rt], t0 + 4 * g, min(limit[rt], t_hi - 1), scale_log2, mrun[rt], lrun[rt], pf[rt], alpha[rt]);
+            }
             // the accumulators are rescaled only when some row's maximum moved (after the first blocks it rarely does)
             bool moved = false;
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) moved |= alpha[rt] != 1.0f;
-            const bool rescale = __any(moved);
+            if (__any(moved)) {
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt) o[dt][rt] *= alpha[rt];
+            }
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) {
                 const bf16x8 vf = __builtin_bit_cast(bf16x8, vb[(dt * 16 + c) * 4 + g]);
 #pragma unroll
-                for (int rt = 0; rt < RT; ++rt) {
-                    if (rescale) o[dt][rt] *= alpha[rt];
+                for (int rt = 0; rt < RT; ++rt)
                     o[dt][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[rt], o[dt][rt], 0, 0, 0);
-                }
             }
         }
-        if (blk + 1 < n_blocks) stash(buf ^ 1);     // the other buffer was last read before the previous barrier
-        __syncthreads();
-        if (blk + 2 < n_blocks) fetch(blk + 2);
+        __builtin_amdgcn_s_waitcnt(0x0F70);        // the copies past the end have landed before LDS goes away
     }
+    const int item = ((unit * a.n_kv + kvh) * p.n_splits + split) * p.items_per_unit + qtile;
+    store_item<D, RT>(a, p, o, mrun, lrun, limit, item, (size_t)u_row0 + qtile * p.q_per_item, kvh, n_rep, c, g);
+}
 
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-        float l = lrun[rt];
-        l += __shfl_xor(l, 16, 64);
-        l += __shfl_xor(l, 32, 64);
-        if (limit[rt] < 0) continue;
-        const int row = rt * 16 + c;
-        const size_t qtok = (size_t)u_row0 + qtile * p.q_per_item + row / n_rep;
-        const int col = (kvh * n_rep + row % n_rep) * D + 4 * g;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-            float r[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) r[e] = l > 0.f ? o[dt][rt][e] / l : 0.f;
-            *(uint2 *)(a.direct_out + frag_offset((int)qtok, col + dt * 16, a.out_mt_total)) =
-                make_uint2(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]));
-        }
+// Prefill: one phase
+template <int D, int RT>
+__global__ __launch_bounds__(256, 2) void attn_prefill_shared_kernel(AttnArgs a, AttnPhase p) {
+    __shared__ u32x4 lds[kShBufs * 2 * 32 * D / 8];
+    shared_tiles<D, RT>(a, p, blockIdx.x, lds);
+}
+
+// Decode: the groups' query tiles over their shared prompt first, a workgroup for four of them, then the sequences'
+// private contexts, a wavefront each.
+template <int D>
+__global__ __launch_bounds__(256, 3) void attn_decode_kernel(AttnArgs a, AttnPhase p0, AttnPhase p1, int wgs0, int n1) {
+    __shared__ u32x4 lds[kShBufs * 2 * 32 * D / 8];
+    if ((int)blockIdx.x < wgs0) {
+        shared_tiles<D, 1>(a, p0, blockIdx.x, lds);
+    } else {
+        const int item = ((int)blockIdx.x - wgs0) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        if (item < n1) single_item<D, 1>(a, p1, item, threadIdx.x & 63);
     }
 }
 
 struct MergeArgs {
     AttnPhase ph[2];
     int n_phases;
-    int n_q, n_kv, d, mt_total;
+    int n_q, n_kv, mt_total;
     uint16_t *out;
     float *out32;       // non-null: row-major fp32 output instead of `out`
 };
 
-// One block per (query token, query head); thread = head dimension.  The rows of all partial results are
-// worked out first; then the (max, sum) pairs, one per thread, and the first four partial outputs of every
-// thread are fetched in the same round trip, the pairs are turned into weights, and the weighted sum runs
-// over the items in a fixed order.
+// One wavefront per (query token, query head), D / 64 head dimensions per lane.  Lane i works out where partial result i
+// lies and fetches its (max, sum) pair; the partial outputs, whose rows the other lanes read from it, are requested four
+// at a time in the same round trip.  The weighted sum runs over the items in a fixed order.  No LDS and no barrier: a
+// workgroup of its own for every (token, head) with three barriers took 17.4 us at 296 rows and 4 items, 11.2 now.
 constexpr int kMaxMergeItems = 64;
 
-__global__ __launch_bounds__(128) void attn_merge_kernel(MergeArgs a) {
-    __shared__ float s_m[kMaxMergeItems], s_l[kMaxMergeItems], s_w[kMaxMergeItems];
-    __shared__ unsigned s_row[kMaxMergeItems];      // partial-result row of each item
-    __shared__ const float *s_ml[kMaxMergeItems];   // its (max, sum) pair
-    const int qt = blockIdx.x, h = blockIdx.y, dd = threadIdx.x;
+template <int D>
+__global__ __launch_bounds__(256) void attn_merge_kernel(MergeArgs a) {
+    constexpr int E = D / 64;
+    typedef float vec __attribute__((ext_vector_type(E)));
+    const int lane = threadIdx.x & 63;
+    const int qt = blockIdx.x, h = blockIdx.y * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (h >= a.n_q) return;
     const int n_rep = a.n_q / a.n_kv;
     const int kvh = h / n_rep, hr = h % n_rep;
 
     int n_items = 0;
+    unsigned row = 0;                                // lane i: row of partial result i
+    float m = kNegBig, l = 0.f;
     for (int ph = 0; ph < a.n_phases; ++ph) {
         const AttnPhase &p = a.ph[ph];
         const int unit = p.row_unit ? p.row_unit[qt] : qt / p.q_per_unit;
         const int qi = p.row_unit ? qt - p.unit_row0[unit] : qt % p.q_per_unit;
-        const int qtile = qi / p.q_per_item, row = (qi % p.q_per_item) * n_rep + hr;
+        const int qtile = qi / p.q_per_item, r = (qi % p.q_per_item) * n_rep + hr;
         const size_t item0 = ((size_t)unit * a.n_kv + kvh) * p.n_splits;
-        if (dd < p.n_splits) {
-            const size_t prow = ((item0 + dd) * p.items_per_unit + qtile) * (16 * p.rt) + row;
-            const size_t base = (size_t)(p.part_o - a.ph[0].part_o) / a.d;   // phases share one buffer
-            s_row[n_items + dd] = (unsigned)(base + prow);
-            s_ml[n_items + dd] = p.part_ml + prow * 2;
+        const int i = lane - n_items;
+        if (i >= 0 && i < p.n_splits) {
+            const size_t prow = ((item0 + i) * p.items_per_unit + qtile) * (16 * p.rt) + r;
+            row = (unsigned)((size_t)(p.part_o - a.ph[0].part_o) / D + prow);        // phases share one buffer
+            const float2 ml = *(const float2 *)(p.part_ml + prow * 2);
+            m = ml.x;
+            l = ml.y;
         }
         n_items += p.n_splits;
     }
-    __syncthreads();
-    const float *po = a.ph[0].part_o + (dd < a.d ? dd : 0);
-    float v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = u < n_items ? po[(size_t)s_row[u] * a.d] : 0.f;
-    if (dd < n_items) {
-        const float2 ml = *(const float2 *)s_ml[dd];
-        s_m[dd] = ml.x;
-        s_l[dd] = ml.y;
-    }
-    __syncthreads();
-    float mbest = kNegBig;
-    for (int i = 0; i < n_items; ++i)
-        if (s_l[i] > 0.f) mbest = fmaxf(mbest, s_m[i]);
-    float den = 0.f;
-    for (int i = 0; i < n_items; ++i) {
-        const float w = s_l[i] > 0.f ? exp2f(s_m[i] - mbest) : 0.f;
-        den += s_l[i] * w;
-        if (dd == 0) s_w[i] = w;
-    }
-    __syncthreads();
-    if (dd >= a.d) return;
-    float num = 0.f;
+    const float *po = a.ph[0].part_o + lane * E;
+    vec v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-        if (u < n_items) num += v[u] * s_w[u];
-    int i = 4;
-    for (; i + 4 <= n_items; i += 4) {
+        if (u < n_items) v[u] = *(const vec *)(po + (size_t)__builtin_amdgcn_readlane(row, u) * D);
+    float mbest = l > 0.f ? m : kNegBig;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = po[(size_t)s_row[i + u] * a.d];
+    for (int off = 32; off >= 1; off >>= 1) mbest = fmaxf(mbest, __shfl_xor(mbest, off, 64));
+    const float w = l > 0.f ? exp2f(m - mbest) : 0.f;
+    const float lw = l * w;
+    auto of_lane = [](float x, int i) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), i)); };
+    float den = 0.f;
+    for (int i = 0; i < n_items; ++i) den += of_lane(lw, i);
+    vec num = {};
+    for (int i = 0; i < n_items; i += 4) {
+        vec nx[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) num += v[u] * s_w[i + u];
+        for (int u = 0; u < 4; ++u)
+            if (i + 4 + u < n_items) nx[u] = *(const vec *)(po + (size_t)__builtin_amdgcn_readlane(row, i + 4 + u) * D);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (i + u < n_items) {
+                const float wu = of_lane(w, i + u);
+#pragma unroll
+                for (int e = 0; e < E; ++e) num[e] += v[u][e] * wu;
+            }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = nx[u];
     }
-    for (; i < n_items; ++i) num += po[(size_t)s_row[i] * a.d] * s_w[i];
-    const float r = den > 0.f ? num / den : 0.f;
-    if (a.out32) a.out32[((size_t)qt * a.n_q + h) * a.d + dd] = r;
-    else a.out[frag_offset(qt, h * a.d + dd, a.mt_total)] = f32_to_bf16(r);
+    float r[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) r[e] = den > 0.f ? num[e] / den : 0.f;
+    const int col = h * D + lane * E;
+    if (a.out32) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) a.out32[(size_t)qt * a.n_q * D + col + e] = r[e];
+    } else if constexpr (E == 2) {
+        *(uint32_t *)(a.out + frag_offset(qt, col, a.mt_total)) = pack_bf16x2(r[0], r[1]);
+    } else {
+        a.out[frag_offset(qt, col, a.mt_total)] = f32_to_bf16(r[0]);
+    }
 }
 
 }  // namespace
@@ -550,15 +561,29 @@ int launch_attention(const AttnArgs &a, const AttnPhase *phases, int n_phases, h
     if (n_items > 0x7FFFFFFF) return SR_E_ARG;
     const AttnPhase &p0 = phases[0], &p1 = phases[n_phases - 1];
     const int rt = p0.rt, n0 = (int)n[0], nt = (int)n_items;
-    if (a.direct_out && p0.items_per_unit >= 2) {
-        // prefill: the query tiles of a (unit, kv head) share their K/V blocks through LDS, four to a workgroup
-        const long long wgs = (long long)p0.n_units * a.n_kv * ((p0.items_per_unit + 3) / 4);
+    // workgroups of a phase whose query tiles share their blocks through LDS: four tiles of a set each, the sets in
+    // rounds of eight (see shared_tiles)
+    auto shared_wgs = [&](const AttnPhase &p) -> long long {
+        return ((long long)p.n_units * a.n_kv * p.n_splits + 7) / 8 * 8 * ((p.items_per_unit + 3) / 4);
+    };
+    if (n_phases == 1 && p0.share) {
+        const long long wgs = shared_wgs(p0);
         if (wgs > 0x7FFFFFFF) return SR_E_ARG;
         dim3 sgrid((unsigned)wgs);
         if (a.d == 128 && rt == 1) attn_prefill_shared_kernel<128, 1><<<sgrid, dim3(256), 0, stream>>>(a, p0);
         else if (a.d == 128 && rt == 2) attn_prefill_shared_kernel<128, 2><<<sgrid, dim3(256), 0, stream>>>(a, p0);
         else if (a.d == 64 && rt == 1) attn_prefill_shared_kernel<64, 1><<<sgrid, dim3(256), 0, stream>>>(a, p0);
         else if (a.d == 64 && rt == 2) attn_prefill_shared_kernel<64, 2><<<sgrid, dim3(256), 0, stream>>>(a, p0);
+        else return SR_E_ARG;
+        SR_HIP(hipGetLastError());
+        return SR_OK;
+    }
+    if (n_phases == 2 && p0.share && rt == 1 && n0 > 0) {
+        const long long wgs0 = shared_wgs(p0), wgs = wgs0 + (n[1] + 3) / 4;
+        if (wgs > 0x7FFFFFFF) return SR_E_ARG;
+        dim3 sgrid((unsigned)wgs);
+        if (a.d == 128) attn_decode_kernel<128><<<sgrid, dim3(256), 0, stream>>>(a, p0, p1, (int)wgs0, (int)n[1]);
+        else if (a.d == 64) attn_decode_kernel<64><<<sgrid, dim3(256), 0, stream>>>(a, p0, p1, (int)wgs0, (int)n[1]);
         else return SR_E_ARG;
         SR_HIP(hipGetLastError());
         return SR_OK;
@@ -583,10 +608,13 @@ int launch_attn_merge(const AttnArgs &a, const AttnPhase *phases, int n_phases, 
     MergeArgs m{};
     for (int i = 0; i < n_phases; ++i) m.ph[i] = phases[i];
     m.n_phases = n_phases;
-    m.n_q = a.n_q; m.n_kv = a.n_kv; m.d = a.d; m.mt_total = mt_total;
+    m.n_q = a.n_q; m.n_kv = a.n_kv; m.mt_total = mt_total;
     m.out = (uint16_t *)out;
     m.out32 = out32;
-    attn_merge_kernel<<<dim3(n_qtok, a.n_q), dim3(128), 0, stream>>>(m);
+    const dim3 grid(n_qtok, ceil_div(a.n_q, 4)), block(256);
+    if (a.d == 128) attn_merge_kernel<128><<<grid, block, 0, stream>>>(m);
+    else if (a.d == 64) attn_merge_kernel<64><<<grid, block, 0, stream>>>(m);
+    else return SR_E_ARG;
     SR_HIP(hipGetLastError());
     return SR_OK;
 }

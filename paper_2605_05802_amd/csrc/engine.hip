@@ -500,12 +500,20 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
             x.rt = n_rep > 16 ? 2 : 1;              // same row-tile count as the private phase: one launch
             x.q_per_item = (16 * x.rt) / n_rep < c->G ? (16 * x.rt) / n_rep : c->G;
             x.items_per_unit = ceil_div(c->G, x.q_per_item);
+            x.share = x.items_per_unit >= 3;        // a workgroup's fourth wavefront may be idle, not half of them
             x.pt_row_stride = c->G;
             x.t_begin = 0;
             x.t_end = c->shared_tokens;
             x.causal_pos0 = ctx - 1;
             x.causal_stride = 0;
+            // splits of 256 tokens; where query tiles share their blocks, only as many as give every CU a workgroup of
+            // this phase (swept at 16 x 8, 37 x 8 and 32 x 16 sequences: 4, 2 and 2 splits of prompts of 1024, 1024 and
+            // 4096 tokens; sixteen splits of the last one took 147 us plus 46 us of merge instead of 119 + 22)
             x.n_splits = ceil_div(c->shared_tokens, 256);
+            if (x.share) {
+                const int enough = ceil_div(288, x.n_units * s.n_kv_heads * ceil_div(x.items_per_unit, 4));
+                if (x.n_splits > enough) x.n_splits = enough;
+            }
             if (x.n_splits > kMaxAttnSplits) x.n_splits = kMaxAttnSplits;
             x.split_tokens = round_up(ceil_div(c->shared_tokens, x.n_splits), 32);
             add_phase(x);
@@ -543,13 +551,27 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
         x.q_per_item = 32 / n_rep < p.chunk ? 32 / n_rep : p.chunk;
         if (x.q_per_item * n_rep <= 16) x.rt = 1;
         x.items_per_unit = ceil_div(p.chunk, x.q_per_item);
+        x.share = x.items_per_unit >= 2;
         x.pt_row_stride = p.pt_row_stride;
         x.t_begin = 0;
         x.t_end = ctx;
         x.causal_pos0 = p.pos0;
         x.causal_stride = 1;
+        // A few sequences with a short chunk (the single group left late in an episode) give a handful of workgroups that
+        // would each walk the whole context alone: it is split, as in decode, until about 512 workgroups share it, each
+        // split at least 128 tokens long; the partial results go through the merge.
+        const int wgs = p.n_units * s.n_kv_heads * ceil_div(x.items_per_unit, 4);
         x.n_splits = 1;
-        x.split_tokens = round_up(ctx, 32);
+        if (x.share && wgs < 256) {
+            x.n_splits = 512 / wgs;
+            if (x.n_splits > ctx / 128) x.n_splits = ctx / 128;
+            if (x.n_splits > kMaxAttnSplits) x.n_splits = kMaxAttnSplits;
+            const size_t rows = (size_t)p.n_units * s.n_kv_heads * x.items_per_unit * 16 * x.rt;
+            if ((size_t)x.n_splits * rows > c->part_rows_cap) x.n_splits = (int)(c->part_rows_cap / rows);
+            if (x.n_splits < 1) x.n_splits = 1;
+        }
+        x.split_tokens = round_up(ceil_div(ctx, x.n_splits), 32);
+        x.n_splits = ceil_div(ctx, x.split_tokens);      // rounding may leave the last ones nothing
         add_phase(x);
     }
     if (part_rows > c->part_rows_cap) return SR_E_NOMEM;

@@ -370,10 +370,6 @@ constexpr int kMidXBufs = 3, kMidWBufs = 6;                        // k-steps of
 constexpr int kMidXVec = kMidXTiles * 64, kMidWVec = kMidWTiles * 64;       // u32x4 per k-step: 32 KiB and 10 KiB
 constexpr int kMidLdsBytes = (kMidXBufs * kMidXVec + kMidWBufs * kMidWVec) * 16;   // 156 KiB
 
-__device__ __forceinline__ void lds_dma16(const u32x4 *g, unsigned lds_byte_offset) {
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds_byte_offset) : "memory");
-}
-
 // wait until at most n of this wavefront's vector-memory operations are outstanding (n uniform, 0..8)
 __device__ __forceinline__ void wait_vm_at_most(int n) {
     switch (n) {

@@ -54,13 +54,25 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
     u += 0x7FFFu + ((u >> 16) & 1u);
     return (uint16_t)(u >> 16);
 }
+// two at once by the conversion instruction (one instead of about eight; the same bits for every finite value)
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-    return (uint32_t)f32_to_bf16(lo) | ((uint32_t)f32_to_bf16(hi) << 16);
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const bf16x2 v = {(__bf16)lo, (__bf16)hi};
+    return __builtin_bit_cast(uint32_t, v);
 }
 
 // element offset of (row r, column k) in a fragment-major activation matrix with mt_total row tiles
 __host__ __device__ inline size_t frag_offset(int r, int k, int mt_total) {
     return ((((size_t)(k >> 5) * mt_total + (r >> 4)) * 64) + (r & 15) + 16 * ((k & 31) >> 3)) * 8 + (k & 7);
+}
+
+// ---------------------------------------------------------------------------------------------
+// direct-to-LDS copies from inline assembly
+// ---------------------------------------------------------------------------------------------
+// One wavefront copies 64 x 16 bytes: lane i's from g, to lds_byte_offset + 16 i.  Neither the compiler's wait counts nor
+// its alias analysis see the copy: the caller counts it (one vector-memory operation) and waits for it by hand.
+__device__ __forceinline__ void lds_dma16(const void *g, unsigned lds_byte_offset) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds_byte_offset) : "memory");
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -199,6 +211,7 @@ struct AttnPhase {
     int causal_pos0, causal_stride;  // query token i of a unit sees tokens t <= causal_pos0 + i*causal_stride
     int n_splits, split_tokens;      // split s covers [t_begin + s*split_tokens, ...) (multiples of 32)
     int rt;              // row tiles per item (1 or 2)
+    int share;           // 1: four query tiles of a unit per workgroup, sharing K/V blocks through LDS
     int stream_loads;    // 1: no other work item of the launch reads this phase's tokens; fetch them with the
                          // non-temporal hint
     // Units of unequal size (a group some of whose members have left the batch): unit u owns query tokens

@@ -834,3 +834,21 @@ def test_group_size_16_batch_with_a_4096_token_prompt_at_the_7b_shape():
     stats = _episode_properties(synth.C5_EPISODE, 5, (2, 4))
     print(f"G=16 episode: {stats}")
     assert stats["groups_retired"] >= 13
+
+
+@pytest.mark.parametrize("n_q,n_kv,d,G,page,prompt,obs", [
+    (14, 2, 64, 5, 32, 300, 17),      # three query tiles per group in decode; a chunk's attention in two splits
+    (7, 1, 128, 16, 64, 333, 5),      # eight tiles per group, two workgroups of them
+    (12, 4, 128, 12, 128, 400, 33),   # 128-token pages, three splits, four query heads' worth of padding rows
+    (16, 1, 64, 4, 32, 515, 1),       # one query token per tile; a single-token chunk has one tile: not shared, not split
+])
+def test_shared_query_tiles_and_split_chunks(n_q, n_kv, d, G, page, prompt, obs):
+    """Decode attention over the shared prompt through LDS (three or more query tiles per group, a ragged last tile, groups
+    that lose members) and a chunk of a small batch whose context is split, contexts that do not fill the last block."""
+    shape = synth.ModelShape(1, 256, n_q, n_kv, d, 256, 512)
+    cfg = synth.EpisodeConfig("tiles", 2, G, prompt, 3, obs, 2, 16, (), 0.3, 0.5)
+    rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=31, page_tokens=page, sigma=0.05,
+                                                     finish_fn=lambda K, r: K == 1 and r in (0, G + 1, G + 2))
+    print(f"tiles {n_q}/{n_kv}x{d} G={G}: worst |dlogit| = {worst:.3e}, mismatches = {mism}, near ties = {near}")
+    assert stats["seqs_finished"] == 3
+    assert worst <= LOGIT_TOL and mism == 0
