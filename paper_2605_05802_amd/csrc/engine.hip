@@ -250,10 +250,10 @@ int pick_splits(int M, int N, int ks_total) {
 int alloc_packed(sr_ctx *c, PackedMat *m, int n_rows, int K, hipStream_t st) {
     m->N = n_rows;
     m->ks = round_up(ceil_div(K, 32), 16);       // the GEMMs consume k-steps in groups of 16
-    // row padding covers every workgroup width of the decode kernels (256, 160 and 320 features)
-    int rows = round_up(n_rows, 256);
-    if (round_up(n_rows, 160) > rows) rows = round_up(n_rows, 160);
-    if (round_up(n_rows, 320) > rows) rows = round_up(n_rows, 320);
+    // row padding covers every workgroup width of the projection kernels
+    int rows = 0;
+    for (int w : {160, 192, 224, 256, 320})
+        if (round_up(n_rows, w) > rows) rows = round_up(n_rows, w);
     const size_t elems = (size_t)rows * m->ks * 32;
     SR_TRY(dev_alloc(c, &m->p, elems));
     SR_HIP(hipMemsetAsync(m->p, 0, elems * 2, st));

@@ -13,6 +13,8 @@
 //     weight byte is fetched twice; thin matrices are split along K across workgroups and the
 //     fp32 partial results are summed, in fixed order, by the kernel that consumes them.
 // The same kernel serves prefill, where M is thousands of rows: grid.y walks 128-row blocks.
+#include <type_traits>
+
 #include "sr_internal.h"
 
 namespace sr {
@@ -176,174 +178,149 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a) {
 // ---------------------------------------------------------------------------------------------
 // Prefill (M > 128) kernel: compute bound, so the tile is sized for the matrix cores.
 //
-// A workgroup owns a 256 x 256 output tile.  Eight computing wavefronts in a 4 x 2 arrangement each take
-// 64 features x 128 rows with 32x32x16 MFMAs (128 accumulator registers); both operands reach them through
-// LDS, so every byte crosses the vector-memory path once per workgroup: 128 flop per byte fetched.
-// Two more wavefronts do nothing but fetch: one copies the W half, the other the X half of each k-step
-// (16 KiB each) from global memory straight into LDS with direct-to-LDS loads, up to three k-steps ahead
-// through four 32 KiB buffers, and join one workgroup barrier per k-step.  LDS itself is the landing zone
-// of the loads in flight, so the prefetch distance is no longer what a register staging set can hold, and
-// the computing wavefronts issue nothing but LDS reads and MFMAs (fragments of a k-half are read while the
-// MFMAs of the previous one run).  Ten wavefronts put three on two of the SIMDs: 168 registers each.
-// Workgroups are numbered so that the 32 that run together on one XCD form an 8 x 4 block of tiles
-// (2048 rows x 1024 features) whose operands they share through that XCD's L2.
+// A workgroup owns 256 rows x 32 * NT features (NT = 8 for wide matrices; see launch_gemm for the others).  Eight
+// wavefronts in a 2 x 4 arrangement each take 16 * NT features x 64 rows with 16x16x32 MFMAs; both operands reach them
+// through LDS, so every byte crosses the vector-memory path once per workgroup.  Each wavefront copies its share of a
+// k-step from global memory straight into LDS (direct-to-LDS loads issued from inline assembly and waited for by hand),
+// three k-steps ahead through four buffers, with one workgroup barrier per k-step.
+//
+// The fragments of k-step s + 1 are read from LDS while the MFMAs of k-step s run, into a second register set: the
+// barrier that starts k-step s therefore waits for the copies of s + 1, and the reads are spread over the whole k-step
+// instead of standing in front of its first MFMA.  With eight wavefronts (two per SIMD) there are 256 registers for
+// 4 * 4 * NT accumulators and two sets of NT + 4 fragments.
+//
+// The tiles are numbered in panels of eight row blocks, column by column, and every XCD takes a contiguous eighth of
+// that order: the 32 workgroups that run together on one XCD form an 8 x 4 block of tiles (2048 rows x 128 * NT
+// features) whose operands they share through that XCD's L2, and no XCD has more than one tile above its share.
 // ---------------------------------------------------------------------------------------------
-constexpr int kPfThreads = 640;            // 8 computing wavefronts + 2 loaders (W, X)
-constexpr int kPfKs = 1;                   // k-steps per stage
-constexpr int kPfStageVec = 2048 * kPfKs;  // u32x4 per stage: per k-step [W: 16 tiles x 64][X: 16 tiles x 64]
-constexpr int kPfBufs = 4;                 // stages in LDS: the loaders run up to three stages ahead
-constexpr int kPfLdsBytes = kPfBufs * kPfStageVec * 16;
+constexpr int kPfThreads = 512;
+constexpr int kPfBufs = 4;                 // k-steps in LDS
+constexpr int pf_stage_vec(int nt) { return (2 * nt + 16) * 64; }      // u32x4 per k-step: [W: 2 NT tiles][X: 16 tiles]
+constexpr int pf_lds_bytes(int nt) { return kPfBufs * pf_stage_vec(nt) * 16; }
 
-template <int EPI>
-__global__ __launch_bounds__(kPfThreads) void gemm_prefill_kernel(GemmArgs a, int m_blocks, int n_blocks, int sm_count,
-                                                                  int st_count) {
-    extern __shared__ u32x4 pf_lds[];      // [kPfBufs][kPfStageVec]
+template <int EPI, int NT>
+__global__ __launch_bounds__(kPfThreads) void gemm_prefill_kernel(GemmArgs a, int m_blocks, int n_blocks, int per_xcd) {
+    extern __shared__ u32x4 pf_lds[];      // [kPfBufs][pf_stage_vec(NT)]
+    constexpr int SV = pf_stage_vec(NT);
 
-    // linear id -> XCD -> supertile -> tile
-    const int L = blockIdx.x;
-    const int xcd = L & 7, jj = L >> 3;
-    const int w = jj & 31, sg = (jj >> 5) * 8 + xcd;
-    if (sg >= st_count) return;
-    const int mb = (sg % sm_count) * 8 + (w & 7);
-    const int nb = (sg / sm_count) * 4 + (w >> 3);
-    if (mb >= m_blocks || nb >= n_blocks) return;
+    // linear id -> XCD -> place in its share -> tile
+    const int t = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (t >= m_blocks * n_blocks) return;
+    const int panel = t / (8 * n_blocks), in_panel = t - panel * 8 * n_blocks;
+    const int panel_rows = min(8, m_blocks - panel * 8);
+    const int nb = in_panel / panel_rows, mb = panel * 8 + in_panel - nb * panel_rows;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wn = wave & 1, wm = wave >> 1;
+    const int n_stages = a.ks_total;
 
-    const int n_stages = a.ks_total / kPfKs;
-    if (wave >= 8) {
-        // loaders (wavefront 8: W, wavefront 9: X): stage s lives in buffer s % kPfBufs; barrier s is passed by
-        // the computing wavefronts when they are done with stage s - 1 and by a loader when its half of stage s
-        // has landed; then buffer (s - 1) % kPfBufs is free and receives stage s + kPfBufs - 1
-        const bool is_x = wave == 9;
-        const u32x4 *src = is_x ? (const u32x4 *)a.X + (size_t)mb * 16 * 64 + lane
-                                : (const u32x4 *)a.W + ((size_t)(nb * 16) * a.ks_total) * 64 + lane;
-        const size_t ks_stride = is_x ? (size_t)a.mt_total * 64 : 64;
-        const size_t tile_stride = is_x ? 64 : (size_t)a.ks_total * 64;
-        const int dst0 = is_x ? 1024 : 0;
-        auto copy_stage = [&](int st, int buf) {
-            const int k0 = min(st, n_stages - 1) * kPfKs;
-#pragma unroll
-            for (int kk = 0; kk < kPfKs; ++kk)
-#pragma unroll
-                for (int t = 0; t < 16; ++t)
-                    __builtin_amdgcn_global_load_lds(
-                        (const __attribute__((address_space(1))) void *)(src + t * tile_stride + (size_t)(k0 + kk) * ks_stride),
-                        (__attribute__((address_space(3))) void *)&pf_lds[buf * kPfStageVec + kk * 2048 + dst0 + t * 64], 16, 0, 0);
-        };
-#pragma unroll
-        for (int i = 0; i < kPfBufs - 1; ++i) copy_stage(i, i);
-        int buf = kPfBufs - 1;
-        constexpr int kOut = 16 * kPfKs * (kPfBufs - 2);
-        constexpr int kWait = 0x0F70 | (kOut & 15) | ((kOut >> 4) << 14);     // all but the oldest stage may stay in flight
-        for (int s = 0; s < n_stages; ++s) {
-            __builtin_amdgcn_s_waitcnt(kWait);
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-            copy_stage(s + kPfBufs - 1, buf);
-            buf = buf == kPfBufs - 1 ? 0 : buf + 1;
-        }
-        __builtin_amdgcn_s_waitcnt(0x0F70);
-        return;
-    }
+    // copies of one k-step: X tiles 2 * wave, 2 * wave + 1 and W tiles wave, wave + 8 (if there is one)
+    const bool two_w = 2 * NT == 16 || wave + 8 < 2 * NT;
+    const char *xsrc = (const char *)a.X + (size_t)(mb * 16 + wave * 2) * 1024;                     // + ks * mt_total * 1024
+    const char *wsrc = (const char *)a.W + (size_t)(nb * 2 * NT + wave) * a.ks_total * 1024;        // + ks * 1024
+    const size_t x_step = (size_t)a.mt_total * 1024, w_8 = (size_t)8 * a.ks_total * 1024;
+    const unsigned voff = lane * 16;
+    const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(__attribute__((address_space(3))) void *)pf_lds);
+    auto copy_stage = [&](int st, int buf) {         // past the end: a harmless re-read of the last k-step, never consumed
+        const int ks = min(st, n_stages - 1);
+        const unsigned base = lds0 + (unsigned)(buf * SV + wave * 64) * 16;
+        const char *x = xsrc + ks * x_step, *w = wsrc + (size_t)ks * 1024;
+        lds_dma16_uniform(w, voff, base);
+        if (two_w) lds_dma16_uniform(w + w_8, voff, base + 8 * 1024);
+        lds_dma16_uniform(x, voff, base + (unsigned)(2 * NT * 64 + wave * 64) * 16);
+        lds_dma16_uniform(x + 1024, voff, base + (unsigned)(2 * NT * 64 + wave * 64 + 64) * 16);
+    };
+    // all LDS reads of this wavefront are done and at most `stages` k-steps of its copies are still on their way (four or
+    // three copies each); then the barrier
+    auto wait_and_meet = [&](auto stages) __attribute__((always_inline)) {
+        constexpr int S = decltype(stages)::value;
+        if (two_w) __builtin_amdgcn_s_waitcnt(0x0070 | (4 * S));
+        else __builtin_amdgcn_s_waitcnt(0x0070 | (3 * S));
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
 
-    const int wn = wave & 3, wm = wave >> 2;
-    const int r32 = lane & 31, g2 = lane >> 5;
-    const int sub = r32 >> 4, slot0 = (r32 & 15) + 16 * g2;
+    f32x4 acc[NT][4];                      // [feature tile][row tile]: lane (c, g) holds features 4g .. 4g+3 of row c
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    f32x16 acc[2][4];                      // [feature group of 32][row group of 32]
+    const int woff = wn * NT * 64 + lane, xoff = (2 * NT + wm * 4) * 64 + lane;
+    bf16x8 wf[2][NT], xf[2][4];            // [k-step parity]
+    auto read_frags = [&](int set, int buf) __attribute__((always_inline)) {
+        const u32x4 *base = pf_lds + buf * SV;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int j = 0; j < 4; ++j) xf[set][j] = __builtin_bit_cast(bf16x8, base[xoff + j * 64]);
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+        for (int i = 0; i < NT; ++i) wf[set][i] = __builtin_bit_cast(bf16x8, base[woff + i * 64]);
+    };
 
-    // fragment offsets inside a k-step: W group i of this wavefront, X group j
-    const int woff = (wn * 4 + sub) * 64 + slot0;          // + i * 128 (two tiles) + h * 32
-    const int xoff = 1024 + (wm * 8 + sub) * 64 + slot0;   // + j * 128 + h * 32
-
-    int buf = 0;
-    for (int s = 0; s < n_stages; ++s) {
-        __syncthreads();                   // barrier s: stage s is in LDS
-        const u32x4 *base = pf_lds + buf * kPfStageVec;
-        buf = buf == kPfBufs - 1 ? 0 : buf + 1;
-        bf16x8 wf[2][2], xf[2][4];         // [parity][group]
 #pragma unroll
-        for (int i = 0; i < 2; ++i) wf[0][i] = __builtin_bit_cast(bf16x8, base[woff + i * 128]);
+    for (int i = 0; i < kPfBufs; ++i) copy_stage(i, i);
+    wait_and_meet(std::integral_constant<int, 3>{});
+    read_frags(0, 0);
+    for (int s0 = 0; s0 < n_stages; s0 += kPfBufs) {          // ks_total is a multiple of 16
 #pragma unroll
-        for (int j = 0; j < 4; ++j) xf[0][j] = __builtin_bit_cast(bf16x8, base[xoff + j * 128]);
-        constexpr int Q = 2 * kPfKs;
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {      // q = k-step * 2 + k-half
+        for (int q = 0; q < kPfBufs; ++q) {
+            const int s = s0 + q, set = q & 1;
+            wait_and_meet(std::integral_constant<int, 2>{});      // k-step s + 1 has landed; k-step s is in everybody's registers
+            copy_stage(s + kPfBufs, q);              // into the buffer of k-step s
             __builtin_amdgcn_sched_barrier(0);
-            if (q + 1 < Q) {
-                const int o = ((q + 1) >> 1) * 2048 + ((q + 1) & 1) * 32;
+            read_frags(set ^ 1, (q + 1) % kPfBufs);
 #pragma unroll
-                for (int i = 0; i < 2; ++i) wf[(q + 1) & 1][i] = __builtin_bit_cast(bf16x8, base[woff + i * 128 + o]);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) xf[(q + 1) & 1][j] = __builtin_bit_cast(bf16x8, base[xoff + j * 128 + o]);
-            }
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
+            for (int i = 0; i < NT; ++i)
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[q & 1][i], xf[q & 1][j], acc[i][j], 0, 0, 0);
-            if (q + 1 < Q) {
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[set][i], xf[set][j], acc[i][j], 0, 0, 0);
 #pragma unroll
-                for (int f = 0; f < 6; ++f) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // 1 MFMA
-                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // 1 LDS read
-                }
-                __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+            for (int f = 0; f < NT + 4; ++f) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);   // 2 MFMAs
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // 1 LDS read
             }
+            __builtin_amdgcn_sched_group_barrier(0x008, 4 * NT - 2 * (NT + 4), 0);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_sched_barrier(0);
     }
+    __builtin_amdgcn_s_waitcnt(0x0070);              // the copies past the end have landed before LDS goes away
 
-    // accumulator (i, j): lane (r32 = row within the 32-row group, g2) holds, in register v,
-    // feature 8 * (v / 4) + 4 * g2 + v % 4 of the 32-feature group
+    const int c = lane & 15, g = lane >> 4;
     if constexpr (EPI == EPI_F32) {
         float *out = (float *)a.out;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int m = mb * 256 + wm * 128 + j * 32 + r32;
+            const int m = mb * 256 + (wm * 4 + j) * 16 + c;
             if (m < a.M) {
 #pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int vq = 0; vq < 4; ++vq) {
-                        const int n = nb * 256 + wn * 64 + i * 32 + 8 * vq + 4 * g2;
-                        if (n < a.N)
-                            *(f32x4 *)(out + (size_t)m * a.ld_out + n) =
-                                f32x4{acc[i][j][4 * vq], acc[i][j][4 * vq + 1], acc[i][j][4 * vq + 2], acc[i][j][4 * vq + 3]};
-                    }
+                for (int i = 0; i < NT; ++i) {
+                    const int n = (nb * 2 * NT + wn * NT + i) * 16 + 4 * g;
+                    if (n < a.N) *(f32x4 *)(out + (size_t)m * a.ld_out + n) = acc[i][j];
+                }
             }
         }
     } else {
+        static_assert(NT % 2 == 0, "gate and up tiles come in pairs");
         uint16_t *out = (uint16_t *)a.out;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int m = mb * 256 + wm * 128 + j * 32 + r32;
+            const int m = mb * 256 + (wm * 4 + j) * 16 + c;
             if (m < a.M) {
 #pragma unroll
-                for (int i = 0; i < 2; ++i)
+                for (int i = 0; i < NT / 2; ++i) {   // tile 2i = gate, tile 2i + 1 = up of features f .. f+15
+                    const int f = (nb * NT + wn * (NT / 2) + i) * 16 + 4 * g;
+                    if (f < a.ld_out) {
+                        float r[4];
 #pragma unroll
-                    for (int vq = 0; vq < 2; ++vq) {
-                        const int f = nb * 128 + wn * 32 + i * 16 + 8 * vq + 4 * g2;
-                        if (f < a.ld_out) {
-                            float r[4];
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                const float gt = acc[i][j][4 * vq + e];
-                                r[e] = gt / (1.0f + __expf(-gt)) * acc[i][j][4 * (vq + 2) + e];
-                            }
-                            uint2 v = make_uint2(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]));
-                            *(uint2 *)(out + frag_offset(m, f, a.mt_total)) = v;
+                        for (int e = 0; e < 4; ++e) {
+                            const float gt = acc[2 * i][j][e];
+                            r[e] = gt / (1.0f + __expf(-gt)) * acc[2 * i + 1][j][e];
                         }
+                        *(uint2 *)(out + frag_offset(m, f, a.mt_total)) =
+                            make_uint2(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]));
                     }
+                }
             }
         }
     }
@@ -673,24 +650,13 @@ int launch_pack_rows(const uint16_t *src, int n_rows, int K, uint16_t *dst, int 
 
 namespace {
 
-// 256 x 256 tiles over all of `a`
-int launch_tiles256(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream) {
-    static bool attr_set = false;
-    if (!attr_set) {
-        SR_HIP(hipFuncSetAttribute((const void *)gemm_prefill_kernel<EPI_F32>,
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, kPfLdsBytes));
-        SR_HIP(hipFuncSetAttribute((const void *)gemm_prefill_kernel<EPI_SWIGLU>,
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, kPfLdsBytes));
-        attr_set = true;
-    }
-    const int mb256 = ceil_div(a.M, 256), nb256 = ceil_div(a.N, 256);
-    const int sm_count = ceil_div(mb256, 8), sn_count = ceil_div(nb256, 4);
-    const int st_count = sm_count * sn_count;
-    dim3 pgrid((unsigned)(ceil_div(st_count, 8) * 8 * 32)), pblock(kPfThreads);
-    if (epi == EPI_F32)
-        gemm_prefill_kernel<EPI_F32><<<pgrid, pblock, kPfLdsBytes, stream>>>(a, mb256, nb256, sm_count, st_count);
-    else
-        gemm_prefill_kernel<EPI_SWIGLU><<<pgrid, pblock, kPfLdsBytes, stream>>>(a, mb256, nb256, sm_count, st_count);
+// Tiles of 256 rows x 32 * NT features over all of `a`
+template <int EPI, int NT>
+int launch_tiles(const GemmArgs &a, hipStream_t stream) {
+    SR_HIP(hipFuncSetAttribute((const void *)gemm_prefill_kernel<EPI, NT>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               pf_lds_bytes(NT)));
+    const int mb = ceil_div(a.M, 256), nb = ceil_div(a.N, 32 * NT), per_xcd = ceil_div(mb * nb, 8);
+    gemm_prefill_kernel<EPI, NT><<<dim3((unsigned)(per_xcd * 8)), dim3(kPfThreads), pf_lds_bytes(NT), stream>>>(a, mb, nb, per_xcd);
     SR_HIP(hipGetLastError());
     return SR_OK;
 }
@@ -736,18 +702,36 @@ int launch_mid(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream) {
     return SR_OK;
 }
 
-// `a` restricted to the packed columns from c0 (a multiple of 256) on
-GemmArgs columns_from(const GemmArgs &a, GemmEpilogue epi, int c0) {
-    GemmArgs b = a;
-    b.N = a.N - c0;
-    b.W = a.W + (size_t)(c0 / 16) * a.ks_total * 64;
-    if (epi == EPI_F32) {
-        b.out = (float *)a.out + c0;
-    } else {                                   // output feature c0 / 2 of the fragment-major matrix
-        b.out = (uint16_t *)a.out + frag_offset(0, c0 / 2, a.mt_total);
-        b.ld_out = a.ld_out - c0 / 2;
+// More than 128 rows, no K split: which kernel.  Times of a launch at K = 3584 in us (all are proportional to K), measured
+// on the projections of the 7B shape at 8192, 5120, 4096, 2048, 1280, 768, 512, 304 and 136 rows.
+//   256 x 32 NT tiles: a round of one per CU takes 9.3 (NT + 1.5): O at 4096 rows 86 (NT = 7) and 88 (8), QKV at 8192 rows
+//     186 (6, three rounds), 202 (7, three), 207 (5, four) and 212 (8, three), O at 5120 rows 126 (5), 142 (6), 155 (7) and
+//     165 (8), two rounds each.  Every NT that the epilogue allows is looked at: what decides is how full the last round is.
+//   128 x 128 tiles, two to a CU: 39 up to 256 of them; above 1024 rows (W read through L2 by many row blocks)
+//     0.095 a tile and 15, at least 60; up to 1024 rows 0.166 a tile.
+//   All rows in one workgroup of 160 features, up to 512 rows: 89 a round up to 192 rows, 93 up to 256, 108 up to 384, 155 up
+//     to 512.  Only for matrices of 16 384 rows and more, where it makes a round of workgroups.
+enum TileKernel { TILES_128 = 0, TILES_MID = 1 };      // otherwise NT = 5 .. 8
+int choose_tiles(const GemmArgs &a, GemmEpilogue epi) {
+    const long long mb = ceil_div(a.M, 256);
+    const long long t128 = (long long)ceil_div(a.M, 128) * ceil_div(a.N, 128);
+    double best = a.M > 1024 ? (t128 <= 256 ? 39.0 : t128 < 474 ? 60.0 : 0.095 * t128 + 15.0)
+                             : (t128 < 235 ? 39.0 : 0.166 * t128);
+    int kernel = TILES_128;
+    if (mb * 16 <= a.mt_total) {
+        for (int nt = 8; nt >= 5; --nt) {
+            if (epi == EPI_SWIGLU && nt % 2) continue;
+            const long long rounds = (mb * ceil_div(a.N, 32 * nt) + 255) / 256;
+            const double us = rounds * 9.3 * (nt + 1.5);
+            if (us < best) { best = us; kernel = nt; }
+        }
     }
-    return b;
+    if (a.M <= 512 && a.N >= 16384) {
+        const int rounds = ceil_div(ceil_div(a.N, 160), 256);
+        const double us = rounds * (a.M <= 192 ? 89.0 : a.M <= 256 ? 93.0 : a.M <= 384 ? 108.0 : 155.0);
+        if (us < best) { best = us; kernel = TILES_MID; }
+    }
+    return kernel;
 }
 
 }  // namespace
@@ -758,63 +742,18 @@ int launch_gemm(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream) {
     if (m_blocks * 8 > a.mt_total || a.splits < 1 || m_blocks > 65535 || a.splits > 65535 || a.ks_total % 16)
         return SR_E_ARG;
     if (m_blocks == 1 && a.wide) return launch_gemm_stream(a, epi, stream);
-    const int mb256 = ceil_div(a.M, 256), nb256 = ceil_div(a.N, 256);
-    if (m_blocks > 1 && a.splits == 1 && mb256 * 16 <= a.mt_total) {
-        const int tiles256 = mb256 * nb256;
-        if (a.M > 1024) {
-            // Prefill-sized batches: 256 x 256 tiles when they fill the 256 CUs well -- always for wide outputs; for
-            // N of a few thousand only if the last round of workgroups is not mostly empty.
-            const bool fills = tiles256 * 8 >= ceil_div(tiles256, 256) * 256 * 7;      // >= 87.5 % of the slots used
-            if (a.N >= 16384 || (a.N >= 2048 && fills)) return launch_tiles256(a, epi, stream);
-            // Otherwise whole rounds of large tiles over the first column blocks and small tiles over the rest, where
-            // that is cheaper than small tiles throughout.  Measured at 8192 and 5120 rows, in units of one small tile
-            // among thousands: a round of large tiles costs 810; a launch of up to 256 small tiles (one per CU) 500, of
-            // up to 512 (two per CU) 1100.  QKV at 8192 rows: two rounds and 256 small tiles, 253 against 275 us; at 5120
-            // rows every thin projection is cheaper on small tiles alone.
-            if (a.N >= 2048 && mb256 <= 256) {
-                const int cols_per_round = 256 / mb256;
-                const int rounds_a = nb256 / cols_per_round;
-                const int c0 = rounds_a * cols_per_round * 256;
-                if (rounds_a > 0 && c0 < a.N) {
-                    const long long rest = (long long)m_blocks * ceil_div(a.N - c0, 128);
-                    const long long cost_mix = (long long)rounds_a * 810 + (rest <= 256 ? 500 : rest < 1100 ? 1100 : rest);
-                    const long long cost128 = (long long)m_blocks * ceil_div(a.N, 128);
-                    if (cost_mix < cost128) {
-                        GemmArgs first = a;
-                        first.N = c0;
-                        SR_TRY(launch_tiles256(first, epi, stream));
-                        return launch_tiles128(columns_from(a, epi, c0), epi, stream);
-                    }
-                }
-            }
-            return launch_tiles128(a, epi, stream);
+    if (m_blocks > 1 && a.splits == 1) {
+        const int kernel = choose_tiles(a, epi);
+        if (kernel == TILES_MID) return launch_mid(a, epi, stream);
+        if (epi == EPI_SWIGLU) {
+            if (kernel == 8) return launch_tiles<EPI_SWIGLU, 8>(a, stream);
+            if (kernel == 6) return launch_tiles<EPI_SWIGLU, 6>(a, stream);
+        } else {
+            if (kernel == 8) return launch_tiles<EPI_F32, 8>(a, stream);
+            if (kernel == 7) return launch_tiles<EPI_F32, 7>(a, stream);
+            if (kernel == 6) return launch_tiles<EPI_F32, 6>(a, stream);
+            if (kernel == 5) return launch_tiles<EPI_F32, 5>(a, stream);
         }
-        // A few hundred rows against a wide matrix (gate|up, LM head): every row in one workgroup of 160 features
-        if (a.M <= 512 && a.N >= 16384) return launch_mid(a, epi, stream);
-        // A few hundred rows (decode steps of a large batch).  256 x 256 tiles run one workgroup per CU in whole
-        // rounds of 256; 128 x 128 tiles run two per CU and drain almost continuously.  Measured at 304 and 512
-        // rows, K = 3584: 150 us a round (the weights come from HBM: only two row blocks share them) against 0.166 us
-        // a small tile, both proportional to K, i.e. a round costs what 900 small tiles do, and a launch of small
-        // tiles at least what 200 of them do.  Third choice: whole rounds of large tiles over the first columns and
-        // small tiles over the rest, in two launches.
-        const long long cost256 = (long long)ceil_div(tiles256, 256) * 900;
-        long long cost128 = (long long)m_blocks * ceil_div(a.N, 128);
-        if (cost128 < 200) cost128 = 200;
-        const int cols_per_round = 256 / mb256;                   // column blocks of 256 in one round of large tiles
-        const int rounds_a = nb256 / cols_per_round;
-        const int c0 = rounds_a * cols_per_round * 256;           // first column of the small-tile part
-        long long cost_mix = -1;
-        if (rounds_a > 0 && c0 < a.N) {
-            const long long rest = (long long)m_blocks * ceil_div(a.N - c0, 128);
-            cost_mix = (long long)rounds_a * 900 + (rest > 200 ? rest : 200) + 20;
-        }
-        if (cost_mix >= 0 && cost_mix < cost256 && cost_mix < cost128) {
-            GemmArgs first = a;
-            first.N = c0;
-            SR_TRY(launch_tiles256(first, epi, stream));
-            return launch_tiles128(columns_from(a, epi, c0), epi, stream);
-        }
-        if (cost256 <= cost128) return launch_tiles256(a, epi, stream);
     }
     return launch_tiles128(a, epi, stream);
 }

@@ -75,6 +75,12 @@ __device__ __forceinline__ void lds_dma16(const void *g, unsigned lds_byte_offse
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds_byte_offset) : "memory");
 }
 
+// the same with a uniform address, lane i's bytes voffset (16 i) behind it: no vector register or instruction for addresses
+__device__ __forceinline__ void lds_dma16_uniform(const void *base, unsigned voffset, unsigned lds_byte_offset) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voffset), "s"(base), "s"(lds_byte_offset)
+                 : "memory");
+}
+
 // ---------------------------------------------------------------------------------------------
 // gate
 // ---------------------------------------------------------------------------------------------

@@ -852,3 +852,14 @@ def test_shared_query_tiles_and_split_chunks(n_q, n_kv, d, G, page, prompt, obs)
     print(f"tiles {n_q}/{n_kv}x{d} G={G}: worst |dlogit| = {worst:.3e}, mismatches = {mism}, near ties = {near}")
     assert stats["seqs_finished"] == 3
     assert worst <= LOGIT_TOL and mism == 0
+
+
+@pytest.mark.parametrize("hidden,ffn", [(992, 752), (1504, 1008), (1760, 128), (2016, 256)])
+def test_prefill_tile_widths(hidden, ffn):
+    """8163 prompt rows (a ragged last row block): the O and down projections take tiles of 160, 192, 224 and 256 features
+    with a ragged last column block, the gate|up projection tiles of 192 and 256 or small ones."""
+    shape = synth.ModelShape(1, hidden, 4, 2, 64, ffn, 512)
+    cfg = synth.EpisodeConfig("widths", 9, 2, 907, 1, 3, 1, 16, (), 0.3, 0.0)
+    rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=41, page_tokens=64, kv_pool_bytes=1 << 28)
+    print(f"widths {hidden}/{ffn}: worst |dlogit| = {worst:.3e}, mismatches = {mism}, near ties = {near}")
+    assert worst <= LOGIT_TOL and mism == 0
