@@ -201,31 +201,33 @@ int timed(sr_ctx *c, int kc, hipStream_t st, F &&launch) {
     return rc;
 }
 
-// Decode-time projections (M <= 128).  Matrices that are wide or deep go to the kernel with a loader
-// wavefront; the number of computing wavefronts per workgroup (32 features each) is picked so that
-// the matrix breaks into about 256 workgroups with as few K splits as possible: the packed gate|up
-// matrix (37 888 rows at the 7B shape) gives 237 workgroups of 160 features, the down projection
-// 28 blocks of 128 features x 9 splits, the LM head 320-feature workgroups over two rounds.
-// Thin ones keep the 4-wavefront kernel and are split along K so that about one workgroup per CU is
-// in flight -- more than that only adds partial-sum traffic.  Batches of 129 .. 1024 rows split thin matrices a
-// little (pick_splits); larger ones (prefill) never split.
-int decode_waves(int M, int N, int ks_total, bool swiglu) {
-    if (M > 128) return 0;
-    if (swiglu) return N >= 8192 || ks_total >= 256 ? 5 : 0;
-    // thin and shallow (QKV, O): two computing wavefronts per workgroup give enough workgroups with three or four
-    // K splits instead of seven -- the projection itself takes the same time (13.9 against 13.0 us, 11.4 against
-    // 11.8 us at the 7B shape) and the kernel that adds the partial sums reads half as many
-    if (N < 8192 && ks_total < 256) return 2;
-    if (N < 8192) return 4;
-    // wide and shallow (the LM head): 256- or 320-feature workgroups, whichever leaves fewer workgroup-rounds of work
-    // on 256 CUs (152 064 rows: 594 workgroups = 3 rounds of 8 wavefronts, or 476 = 2 rounds of 10; 226 against 246 us)
-    const int r8 = ceil_div(ceil_div(N, 256), 256) * 8, r10 = ceil_div(ceil_div(N, 320), 256) * 10;
-    return r10 < r8 ? 10 : 8;
+// Projections of up to kStreamRows rows go to the weight-streaming kernel.  The number of computing wavefronts per
+// workgroup (32 features each) is picked so that the matrix breaks into about 256 workgroups.
+constexpr int kStreamRows = 256;
+int stream_waves(int M, int N, int ks_total, bool swiglu) {
+    if (M > kStreamRows) return 0;
+    // Thin (QKV, O, down): split along K so that about one workgroup per CU is in flight -- more than that only adds
+    // partial-sum traffic.  Shallow ones take two computing wavefronts, which gives enough workgroups with three or four K
+    // splits instead of seven: the projection itself takes the same time (13.9 against 13.0 us, 11.4 against 11.8 us at
+    // the 7B shape) and the kernel that adds the partial sums reads half as many.
+    if (!swiglu && N < 8192) return ks_total < 256 ? 2 : 4;
+    // Otherwise whole rounds of workgroups on 256 CUs cost what a workgroup is wide: the width with the least work in
+    // them, the widest of equals.  gate|up at the 7B shape (37 888 packed rows): 237 workgroups of 160 features; LM head
+    // (152 064): 476 of 320 in two rounds (594 of 256 in three: 246 against 226 us); 16 384 rows: 256 of 64 features, 20
+    // against 41 us with 64 of 256 at 8 rows, 33 against 56 at 128; 1376 rows (FFN 688): 3.7 against 7.9 us with 128
+    // features at 32 rows.
+    int best = 2, least = 0;
+    for (int w : {10, 8, 5, 4, 2}) {
+        if (w >= 8 && M > 128) continue;             // not enough registers for more than four row tiles
+        const int work = ceil_div(ceil_div(N, 32 * w), 256) * w;
+        if (least == 0 || work < least) { least = work; best = w; }
+    }
+    return best;
 }
 
 int pick_splits(int M, int N, int ks_total) {
     if (M > 1024) return 1;
-    if (M > 128) {
+    if (M > kStreamRows) {
         // a few hundred rows (decode steps of a large batch): a thin matrix gives too few 128 x 128 tiles for the
         // 256 CUs (two workgroups each), so K is split until about 320 workgroups are in flight -- measured best at
         // 512 and 304 rows for the O, down and QKV projections of the 7B shape (2-3 splits, 1.5-2.3x faster)
@@ -236,14 +238,14 @@ int pick_splits(int M, int N, int ks_total) {
         if (s > 4) s = 4;
         return s < 1 ? 1 : s;
     }
-    const int waves = decode_waves(M, N, ks_total, false);
-    const int n_blocks = ceil_div(N, waves ? 32 * waves : 128);
+    const int n_blocks = ceil_div(N, 32 * stream_waves(M, N, ks_total, false));
     const int target = 256 / n_blocks;
     if (target <= 1) return 1;
     const int units = ks_total / 8;                 // a split covers whole groups of 8 k-steps
     const int ups = ceil_div(units, target);        // units per split at the target count ...
     int s = ceil_div(units, ups);                   // ... and the fewest splits that keep it
     if (s > kMaxSplitK) s = kMaxSplitK;
+    if (M > 128 && s > units / 4) s = units / 4;    // a short inner dimension is not worth twice the partial sums
     return s < 1 ? 1 : s;
 }
 
@@ -428,8 +430,7 @@ int gemm(sr_ctx *c, const uint4 *X, const PackedMat &W, int M, GemmEpilogue epi,
     a.out = out;
     a.ld_out = ld_out;
     a.splits = 1;
-    a.wide = decode_waves(M, W.N, W.ks, epi == EPI_SWIGLU);
-    a.ring = 8;
+    a.wide = stream_waves(M, W.N, W.ks, epi == EPI_SWIGLU);
     if (epi == EPI_F32 && splits_out) {
         SR_TRY(choose_splits(c, M, W, ld_out, &a.splits, &a.split_stride));
         *splits_out = a.splits;

@@ -1,18 +1,7 @@
-// Projection GEMMs  Y[M][N] = X[M][K] * W[N][K]^T  on the bf16 matrix cores.
-//
-// During decode the batch M is the number of live sequences (128 at the headline shape), so
-// every projection is a weight-streaming problem: W is read exactly once per step from HBM
-// and each byte of it is used for M multiply-adds.  The kernel is organised around that
-// stream:
-//   - W is stored pre-tiled in MFMA operand order, so each wavefront reads its 32 output
-//     features as two contiguous runs with 16-byte loads per lane straight into registers
-//     (no LDS hop for the operand that is used once);
-//   - the activations X (small, re-used by every workgroup, L2 resident) are staged through
-//     LDS in the same operand order and shared by the four wavefronts of a workgroup;
-//   - one workgroup owns all rows of a 128-row block for its 128 output features, so no
-//     weight byte is fetched twice; thin matrices are split along K across workgroups and the
-//     fp32 partial results are summed, in fixed order, by the kernel that consumes them.
-// The same kernel serves prefill, where M is thousands of rows: grid.y walks 128-row blocks.
+// Projection GEMMs  Y[M][N] = X[M][K] * W[N][K]^T  on the bf16 matrix cores, for more than 256 rows (up to there the
+// weight stream bounds them: gemm_stream.hip).  W and X are stored pre-tiled in MFMA operand order.  Three kernels, chosen
+// per launch by measured cost (choose_tiles): 128 x 128 tiles, tiles of 256 rows x 160 to 256 features, and all rows of
+// a batch of a few hundred in one workgroup of 160 features.
 #include <type_traits>
 
 #include "sr_internal.h"
@@ -27,17 +16,10 @@ constexpr int kKC = 4;                    // k-steps (of 32) per LDS chunk of X
 constexpr int kPF = 8;                    // k-steps of W held in registers ahead of the MFMAs (two X chunks)
 constexpr int kChunkVec = kKC * 512;      // uint4 per chunk: 8 row tiles x 64 lanes per k-step
 
-// Weight loads.  At decode time every weight byte is used once per launch, so the load carries the
-// non-temporal hint: the caches do not retain the line, and a pure streaming read measures 13 %
-// faster with it (6.97 against 6.15 TB/s).  Prefill re-reads W once per row block and keeps the default policy.
-template <bool STREAM>
-__device__ __forceinline__ u32x4 load_w(const u32x4 *p) {
-    if constexpr (STREAM) return __builtin_nontemporal_load(p);
-    else return *p;
-}
-
-// SKINNY = the whole batch fits one 128-row block (decode): a distinct instantiation, so that the
-// weight-streaming launches and the compute-bound prefill launches are told apart in profiles.
+// 128 x 128 tiles, two workgroups per CU.  Each wavefront reads its 32 output features as two contiguous runs with
+// 16-byte loads per lane straight into registers; X is staged through LDS and shared by the four wavefronts.  grid.y walks
+// 128-row blocks; thin matrices are split along K across workgroups (grid.z) and the fp32 partial results are summed, in
+// fixed order, by the kernel that consumes them.
 //
 // Software pipeline per wavefront: a ring of kPF k-steps of W lives in registers; every k-step is
 // consumed by 16 MFMAs and its slot is refilled at once with the k-step kPF further on, so 16 KiB of
@@ -48,12 +30,12 @@ __device__ __forceinline__ u32x4 load_w(const u32x4 *p) {
 // prefetches past the end re-read the last valid k-step (never used), and rows of X beyond M are
 // computed and never stored.  Without branches the compiler can count outstanding loads exactly,
 // so the weight prefetch survives across the workgroup barriers.
-template <int EPI, bool SKINNY>
+template <int EPI>
 __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a) {
     __shared__ u32x4 lds[2][kChunkVec];   // 2 x 32 KiB
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int nb = blockIdx.x, mb = SKINNY ? 0 : blockIdx.y, sp = blockIdx.z;
+    const int nb = blockIdx.x, mb = blockIdx.y, sp = blockIdx.z;
     int ks0, ks1;                                              // whole groups of kPF k-steps
     split_range(a.ks_total, kPF, a.splits, sp, &ks0, &ks1);
     const int nt0 = nb * 8 + wave * 2;    // first of this wavefront's two 16-feature tiles
@@ -75,8 +57,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a) {
         u32x4 w0[kPF], w1[kPF], xr[8];
 #pragma unroll
         for (int i = 0; i < kPF; ++i) {
-            w0[i] = load_w<SKINNY>(wp0 + (size_t)(ks0 + i) * 64);
-            w1[i] = load_w<SKINNY>(wp1 + (size_t)(ks0 + i) * 64);
+            w0[i] = *(wp0 + (size_t)(ks0 + i) * 64);
+            w1[i] = *(wp1 + (size_t)(ks0 + i) * 64);
         }
 #pragma unroll
         for (int r = 0; r < 8; ++r) xr[r] = xp[(size_t)(ks0 + (r >> 1)) * x_ks_stride + ((r & 1) << 8)];
@@ -116,8 +98,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a) {
                         acc[mt][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wb, xf[kk & 1][mt], acc[mt][1], 0, 0, 0);
                     }
                     const int kn = min(kc0 + kk + kPF, last);    // refill the slot just consumed
-                    w0[i] = load_w<SKINNY>(wp0 + (size_t)kn * 64);
-                    w1[i] = load_w<SKINNY>(wp1 + (size_t)kn * 64);
+                    w0[i] = *(wp0 + (size_t)kn * 64);
+                    w1[i] = *(wp1 + (size_t)kn * 64);
                     if (kk + 1 < kKC) {
 #pragma unroll
                         for (int mt = 0; mt < 8; ++mt) {
@@ -661,17 +643,11 @@ int launch_tiles(const GemmArgs &a, hipStream_t stream) {
     return SR_OK;
 }
 
-// 128 x 128 tiles over all of `a` (also the 4-wavefront decode kernel when the batch is one row block)
+// 128 x 128 tiles over all of `a`
 int launch_tiles128(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream) {
-    const int m_blocks = ceil_div(a.M, 128), n_blocks = ceil_div(a.N, 128);
-    dim3 grid(n_blocks, m_blocks, epi == EPI_F32 ? a.splits : 1), block(kThreads);
-    if (m_blocks == 1) {
-        if (epi == EPI_F32) gemm_kernel<EPI_F32, true><<<grid, block, 0, stream>>>(a);
-        else gemm_kernel<EPI_SWIGLU, true><<<grid, block, 0, stream>>>(a);
-    } else {
-        if (epi == EPI_F32) gemm_kernel<EPI_F32, false><<<grid, block, 0, stream>>>(a);
-        else gemm_kernel<EPI_SWIGLU, false><<<grid, block, 0, stream>>>(a);
-    }
+    dim3 grid(ceil_div(a.N, 128), ceil_div(a.M, 128), epi == EPI_F32 ? a.splits : 1), block(kThreads);
+    if (epi == EPI_F32) gemm_kernel<EPI_F32><<<grid, block, 0, stream>>>(a);
+    else gemm_kernel<EPI_SWIGLU><<<grid, block, 0, stream>>>(a);
     SR_HIP(hipGetLastError());
     return SR_OK;
 }
@@ -702,15 +678,14 @@ int launch_mid(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream) {
     return SR_OK;
 }
 
-// More than 128 rows, no K split: which kernel.  Times of a launch at K = 3584 in us (all are proportional to K), measured
-// on the projections of the 7B shape at 8192, 5120, 4096, 2048, 1280, 768, 512, 304 and 136 rows.
+// No K split: which kernel.  Times of a launch at K = 3584 in us (all are proportional to K), measured
+// on the projections of the 7B shape at 8192, 5120, 4096, 2048, 1280, 768, 512 and 304 rows.
 //   256 x 32 NT tiles: a round of one per CU takes 9.3 (NT + 1.5): O at 4096 rows 86 (NT = 7) and 88 (8), QKV at 8192 rows
 //     186 (6, three rounds), 202 (7, three), 207 (5, four) and 212 (8, three), O at 5120 rows 126 (5), 142 (6), 155 (7) and
 //     165 (8), two rounds each.  Every NT that the epilogue allows is looked at: what decides is how full the last round is.
 //   128 x 128 tiles, two to a CU: 39 up to 256 of them; above 1024 rows (W read through L2 by many row blocks)
 //     0.095 a tile and 15, at least 60; up to 1024 rows 0.166 a tile.
-//   All rows in one workgroup of 160 features, up to 512 rows: 89 a round up to 192 rows, 93 up to 256, 108 up to 384, 155 up
-//     to 512.  Only for matrices of 16 384 rows and more, where it makes a round of workgroups.
+//   All rows in one workgroup of 160 features, up to 512 rows: 108 a round up to 384 rows, 155 up to 512.  Only for matrices of 16 384 rows and more, where it makes a round of workgroups.
 enum TileKernel { TILES_128 = 0, TILES_MID = 1 };      // otherwise NT = 5 .. 8
 int choose_tiles(const GemmArgs &a, GemmEpilogue epi) {
     const long long mb = ceil_div(a.M, 256);
@@ -728,7 +703,7 @@ int choose_tiles(const GemmArgs &a, GemmEpilogue epi) {
     }
     if (a.M <= 512 && a.N >= 16384) {
         const int rounds = ceil_div(ceil_div(a.N, 160), 256);
-        const double us = rounds * (a.M <= 192 ? 89.0 : a.M <= 256 ? 93.0 : a.M <= 384 ? 108.0 : 155.0);
+        const double us = rounds * (a.M <= 384 ? 108.0 : 155.0);
         if (us < best) { best = us; kernel = TILES_MID; }
     }
     return kernel;
@@ -741,8 +716,8 @@ int launch_gemm(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream) {
     const int m_blocks = ceil_div(a.M, 128);
     if (m_blocks * 8 > a.mt_total || a.splits < 1 || m_blocks > 65535 || a.splits > 65535 || a.ks_total % 16)
         return SR_E_ARG;
-    if (m_blocks == 1 && a.wide) return launch_gemm_stream(a, epi, stream);
-    if (m_blocks > 1 && a.splits == 1) {
+    if (a.wide) return launch_gemm_stream(a, epi, stream);
+    if (a.splits == 1) {
         const int kernel = choose_tiles(a, epi);
         if (kernel == TILES_MID) return launch_mid(a, epi, stream);
         if (epi == EPI_SWIGLU) {

@@ -1,4 +1,4 @@
-// Decode-time projection GEMM  Y[M][N] = X[M][K] * W[N][K]^T  for M <= 128 on the bf16 matrix cores:
+// Decode-time projection GEMM  Y[M][N] = X[M][K] * W[N][K]^T  for M <= 256 on the bf16 matrix cores:
 // the weight-streaming kernel that carries most of a decode step's HBM traffic.
 #include "sr_internal.h"
 
@@ -7,15 +7,17 @@ namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kKC = 4;                    // k-steps (of 32) per LDS chunk of X
-constexpr int kChunkVec = kKC * 512;      // uint4 per chunk: 8 row tiles x 64 lanes per k-step
+// k-steps (of 32) per LDS chunk of X: three chunks of four fit in 160 KiB up to 192 rows
+constexpr int chunk_steps(int mt32) { return mt32 <= 6 ? 4 : 2; }
+// uint4 per k-step of X in LDS: the 16-row tiles a launch computes, at least eight
+constexpr int kstep_vec(int mt32) { return (mt32 <= 4 ? 8 : 2 * mt32) * 64; }
 
 // Every weight byte is used once per launch, so the load carries the non-temporal hint: the caches do
 // not retain the line, and a pure streaming read measures 13 % faster with it (6.97 against 6.15 TB/s).
 __device__ __forceinline__ u32x4 load_w_stream(const u32x4 *p) { return __builtin_nontemporal_load(p); }
 
 // ---------------------------------------------------------------------------------------------
-// Decode-time (M <= 128) weight-streaming kernel with a loader wavefront.
+// Weight-streaming kernel (M <= 256) with a loader wavefront.
 //
 // A workgroup owns 32 * WAVES output features and all rows; each of its WAVES computing wavefronts
 // owns 32 features and streams their weights through a register ring of RING k-steps (2 KiB each),
@@ -24,7 +26,7 @@ __device__ __forceinline__ u32x4 load_w_stream(const u32x4 *p) { return __builti
 // loads exactly, and prefetches past the end re-read the last valid k-step.
 //
 // The activations are brought in by one extra wavefront that does nothing else: it copies X chunks
-// (kKC k-steps, 32 KiB) from global memory straight into LDS with lane-linear 16-byte direct-to-LDS
+// (four k-steps, 32 KiB at 128 rows) from global memory straight into LDS with lane-linear 16-byte direct-to-LDS
 // loads, two chunks ahead of the MFMAs, through three buffers.  Vector-memory loads return in order
 // within a wavefront, so an activation load inside a computing wavefront would make its wait drain
 // the older weight loads too; with the loader the computing wavefronts carry only weight loads,
@@ -38,17 +40,22 @@ __device__ __forceinline__ u32x4 load_w_stream(const u32x4 *p) { return __builti
 // lane slot (r % 16) + 16 * (2h + g).
 //
 // MT32 = number of 32-row tiles computed (M <= 32 * MT32): smaller batches skip the idle rows'
-// copies, LDS reads and MFMAs.  Workgroup width matters because with one workgroup per CU a matrix
+// copies, LDS reads and MFMAs.  Up to four tiles the fragments of a whole k-step are read ahead; five to eight
+// (129 to 256 rows) read half a k-step ahead, which keeps 128 accumulators, the ring and the fragments within 256 registers.
+// At the 7B shape gate|up, QKV, O and down take 53, 17, 14 and 40 us at 136 rows and 79, 22, 20 and 54 at 256; the tiled kernels took
+// 76, 25, 18 and 58, and 87, 26, 19 and 59.  Workgroup width matters because with one workgroup per CU a matrix
 // should break into about 256 equal workgroups: 37 888 packed gate|up rows give 148 workgroups of
 // 256 features (108 CUs idle) but 237 of 160.
 // ---------------------------------------------------------------------------------------------
+constexpr int kRing = 8;                   // k-steps of W in flight per computing wavefront (16 measured slower at every width)
 constexpr int kStBufs = 3;                 // LDS chunk buffers: the loader runs two chunks ahead
-constexpr int kStLdsBytes = kStBufs * kChunkVec * 16;
+constexpr int st_lds_bytes(int mt32) { return kStBufs * chunk_steps(mt32) * kstep_vec(mt32) * 16; }
 
-// RING = k-steps of W each computing wavefront keeps in flight (8 or 16; 2 KiB per k-step)
+// RING = k-steps of W each computing wavefront keeps in flight (2 KiB per k-step)
 template <int EPI, int WAVES, int MT32, int RING>
 __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(GemmArgs a) {
-    extern __shared__ u32x4 lds_dyn[];     // [kStBufs][k-step in chunk][16-row tile 0..7][lane]
+    extern __shared__ u32x4 lds_dyn[];     // [kStBufs][k-step in chunk][16-row tile][lane]
+    constexpr int kKC = chunk_steps(MT32), kStepVec = kstep_vec(MT32), kChunkVec = kKC * kStepVec;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -64,7 +71,7 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(GemmArgs 
         if (ks0 >= ks1) return;
         const u32x4 *xp = (const u32x4 *)a.X + lane;
         const size_t x_ks_stride = (size_t)a.mt_total * 64;
-        constexpr int kCopies = kKC * 2 * MT32;         // direct-to-LDS loads per chunk (<= 32)
+        constexpr int kCopies = kKC * 2 * MT32;         // direct-to-LDS loads per chunk (<= 48)
         auto copy_chunk = [&](int kc, int buf) {
 #pragma unroll
             for (int kk = 0; kk < kKC; ++kk) {
@@ -73,7 +80,7 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(GemmArgs 
                 for (int b = 0; b < 2 * MT32; ++b)
                     __builtin_amdgcn_global_load_lds(
                         (const __attribute__((address_space(1))) void *)(src + b * 64),
-                        (__attribute__((address_space(3))) void *)&lds_dyn[buf * kChunkVec + kk * 512 + b * 64], 16,
+                        (__attribute__((address_space(3))) void *)&lds_dyn[buf * kChunkVec + kk * kStepVec + b * 64], 16,
                         0, 0);
             }
         };
@@ -127,42 +134,76 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(GemmArgs 
 #pragma unroll
             for (int q = 0; q < RING / kKC; ++q) {
                 const int kc0 = ks + q * kKC;
-                bf16x8 xf[2][NF];                                // [parity][mt32 * 2 + k-half]
                 const u32x4 *xb = &lds_dyn[buf * kChunkVec + xoff];
                 buf = buf == kStBufs - 1 ? 0 : buf + 1;
+                if constexpr (MT32 <= 4) {
+                    bf16x8 xf[2][NF];                                // [parity][mt32 * 2 + k-half]
 #pragma unroll
-                for (int f = 0; f < NF; ++f)
-                    xf[0][f] = __builtin_bit_cast(bf16x8, xb[(f >> 1) * 128 + (f & 1) * 32]);
+                    for (int f = 0; f < NF; ++f)
+                        xf[0][f] = __builtin_bit_cast(bf16x8, xb[(f >> 1) * 128 + (f & 1) * 32]);
 #pragma unroll
-                for (int kk = 0; kk < kKC; ++kk) {
-                    const int i = q * kKC + kk;
-                    __builtin_amdgcn_sched_barrier(0);
-                    const bf16x8 wa = __builtin_bit_cast(bf16x8, w0[i]);
-                    const bf16x8 wb = __builtin_bit_cast(bf16x8, w1[i]);
-                    if (kk + 1 < kKC) {
+                    for (int kk = 0; kk < kKC; ++kk) {
+                        const int i = q * kKC + kk;
+                        __builtin_amdgcn_sched_barrier(0);
+                        const bf16x8 wa = __builtin_bit_cast(bf16x8, w0[i]);
+                        const bf16x8 wb = __builtin_bit_cast(bf16x8, w1[i]);
+                        if (kk + 1 < kKC) {
 #pragma unroll
-                        for (int f = 0; f < NF; ++f)
-                            xf[(kk + 1) & 1][f] =
-                                __builtin_bit_cast(bf16x8, xb[(kk + 1) * 512 + (f >> 1) * 128 + (f & 1) * 32]);
-                    }
-#pragma unroll
-                    for (int mt = 0; mt < MT32; ++mt) {
-                        acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, xf[kk & 1][mt * 2], acc[mt], 0, 0, 0);
-                        acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wb, xf[kk & 1][mt * 2 + 1], acc[mt], 0, 0, 0);
-                    }
-                    const int kn = min(kc0 + kk + RING, last);  // refill the slot just consumed
-                    w0[i] = load_w_stream(wp0 + (size_t)kn * 64);
-                    w1[i] = load_w_stream(wp1 + (size_t)kn * 64);
-                    if (kk + 1 < kKC) {
-#pragma unroll
-                        for (int f = 0; f < NF; ++f) {
-                            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // 1 MFMA
-                            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // 1 LDS read
+                            for (int f = 0; f < NF; ++f)
+                                xf[(kk + 1) & 1][f] =
+                                    __builtin_bit_cast(bf16x8, xb[(kk + 1) * kStepVec + (f >> 1) * 128 + (f & 1) * 32]);
                         }
-                    } else {
-                        __builtin_amdgcn_sched_group_barrier(0x008, NF, 0);
+#pragma unroll
+                        for (int mt = 0; mt < MT32; ++mt) {
+                            acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, xf[kk & 1][mt * 2], acc[mt], 0, 0, 0);
+                            acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wb, xf[kk & 1][mt * 2 + 1], acc[mt], 0, 0, 0);
+                        }
+                        const int kn = min(kc0 + kk + RING, last);  // refill the slot just consumed
+                        w0[i] = load_w_stream(wp0 + (size_t)kn * 64);
+                        w1[i] = load_w_stream(wp1 + (size_t)kn * 64);
+                        if (kk + 1 < kKC) {
+#pragma unroll
+                            for (int f = 0; f < NF; ++f) {
+                                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // 1 MFMA
+                                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // 1 LDS read
+                            }
+                        } else {
+                            __builtin_amdgcn_sched_group_barrier(0x008, NF, 0);
+                        }
+                        __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);           // W refills
                     }
-                    __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);           // W refills
+                } else {
+                    bf16x8 xf[2][MT32];                              // [k-half parity][mt32]
+#pragma unroll
+                    for (int mt = 0; mt < MT32; ++mt) xf[0][mt] = __builtin_bit_cast(bf16x8, xb[mt * 128]);
+#pragma unroll
+                    for (int hh = 0; hh < 2 * kKC; ++hh) {           // k-step hh / 2, half hh % 2
+                        const int i = q * kKC + (hh >> 1);
+                        __builtin_amdgcn_sched_barrier(0);
+                        const bf16x8 wa = __builtin_bit_cast(bf16x8, (hh & 1) ? w1[i] : w0[i]);
+                        if (hh + 1 < 2 * kKC) {
+#pragma unroll
+                            for (int mt = 0; mt < MT32; ++mt)
+                                xf[(hh + 1) & 1][mt] =
+                                    __builtin_bit_cast(bf16x8, xb[((hh + 1) >> 1) * kStepVec + mt * 128 + ((hh + 1) & 1) * 32]);
+                        }
+#pragma unroll
+                        for (int mt = 0; mt < MT32; ++mt)
+                            acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, xf[hh & 1][mt], acc[mt], 0, 0, 0);
+                        const int kn = min(kc0 + (hh >> 1) + RING, last);   // refill the slot half just consumed
+                        if (hh & 1) w1[i] = load_w_stream(wp1 + (size_t)kn * 64);
+                        else w0[i] = load_w_stream(wp0 + (size_t)kn * 64);
+                        if (hh + 1 < 2 * kKC) {
+#pragma unroll
+                            for (int f = 0; f < MT32; ++f) {
+                                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // 1 MFMA
+                                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // 1 LDS read
+                            }
+                        } else {
+                            __builtin_amdgcn_sched_group_barrier(0x008, MT32, 0);
+                        }
+                        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);           // W refill
+                    }
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 __syncthreads();
@@ -217,28 +258,29 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(GemmArgs 
 
 int launch_gemm_stream(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream) {
     if (a.M <= 0) return SR_OK;
-    if (a.M > 128 || a.mt_total < 8 || a.splits < 1 || a.splits > 65535) return SR_E_ARG;
-    const int ring = a.ring == 16 ? 16 : 8;
-    if (a.ks_total % ring || (a.wide != 2 && a.wide != 4 && a.wide != 5 && a.wide != 8 && a.wide != 10)) return SR_E_ARG;
+    if (a.M > 256 || a.mt_total < (a.M > 128 ? 16 : 8) || a.splits < 1 || a.splits > 65535) return SR_E_ARG;
+    if (a.ks_total % kRing || (a.wide != 2 && a.wide != 4 && a.wide != 5 && a.wide != 8 && a.wide != 10)) return SR_E_ARG;
     dim3 sgrid(ceil_div(a.N, 32 * a.wide), 1, epi == EPI_F32 ? a.splits : 1), lblock(64 * (a.wide + 1));
     const int mt32 = ceil_div(a.M, 32);
     hipError_t attr = hipSuccess;
-#define SR_STREAM_CASE(E, W, T, R)                                                                          \
-    (attr = hipFuncSetAttribute((const void *)gemm_stream_kernel<E, W, T, R>,                                \
-                        hipFuncAttributeMaxDynamicSharedMemorySize, kStLdsBytes),                   \
-     gemm_stream_kernel<E, W, T, R><<<sgrid, lblock, kStLdsBytes, stream>>>(a))
-#define SR_STREAM_MT(E, W, R)                                                                               \
-    (mt32 == 1 ? SR_STREAM_CASE(E, W, 1, R) : mt32 == 2 ? SR_STREAM_CASE(E, W, 2, R)                         \
-     : mt32 == 3 ? SR_STREAM_CASE(E, W, 3, R) : SR_STREAM_CASE(E, W, 4, R))
-#define SR_STREAM_W(E, R)                                                                                   \
-    (a.wide == 2 ? SR_STREAM_MT(E, 2, R) : a.wide == 4 ? SR_STREAM_MT(E, 4, R)                               \
-     : a.wide == 5 ? SR_STREAM_MT(E, 5, R) : a.wide == 8 ? SR_STREAM_MT(E, 8, R) : SR_STREAM_MT(E, 10, R))
-    // nine wavefronts put three on one SIMD, which leaves too few registers for the deep ring
-#define SR_STREAM_W16(E)                                                                                    \
-    (a.wide == 2 ? SR_STREAM_MT(E, 2, 16) : a.wide == 4 ? SR_STREAM_MT(E, 4, 16) : SR_STREAM_MT(E, 5, 16))
-    if (ring == 16 && a.wide >= 8) return SR_E_ARG;
-    if (epi == EPI_F32) { if (ring == 16) SR_STREAM_W16(EPI_F32); else SR_STREAM_W(EPI_F32, 8); }
-    else { if (ring == 16) SR_STREAM_W16(EPI_SWIGLU); else SR_STREAM_W(EPI_SWIGLU, 8); }
+#define SR_STREAM_CASE(E, W, T)                                                                            \
+    (attr = hipFuncSetAttribute((const void *)gemm_stream_kernel<E, W, T, kRing>,                          \
+                        hipFuncAttributeMaxDynamicSharedMemorySize, st_lds_bytes(T)),                      \
+     gemm_stream_kernel<E, W, T, kRing><<<sgrid, lblock, st_lds_bytes(T), stream>>>(a))
+#define SR_STREAM_MT(E, W)                                                                                 \
+    (mt32 == 1 ? SR_STREAM_CASE(E, W, 1) : mt32 == 2 ? SR_STREAM_CASE(E, W, 2)                             \
+     : mt32 == 3 ? SR_STREAM_CASE(E, W, 3) : mt32 == 4 ? SR_STREAM_CASE(E, W, 4)                           \
+     : mt32 == 5 ? SR_STREAM_CASE(E, W, 5) : mt32 == 6 ? SR_STREAM_CASE(E, W, 6)                           \
+     : mt32 == 7 ? SR_STREAM_CASE(E, W, 7) : SR_STREAM_CASE(E, W, 8))
+    // nine and eleven wavefronts put three on one SIMD: 168 registers, too few for more than four row tiles
+#define SR_STREAM_MT4(E, W)                                                                                \
+    (mt32 == 1 ? SR_STREAM_CASE(E, W, 1) : mt32 == 2 ? SR_STREAM_CASE(E, W, 2)                             \
+     : mt32 == 3 ? SR_STREAM_CASE(E, W, 3) : SR_STREAM_CASE(E, W, 4))
+#define SR_STREAM_W(E)                                                                                     \
+    (a.wide == 2 ? SR_STREAM_MT(E, 2) : a.wide == 4 ? SR_STREAM_MT(E, 4)                                   \
+     : a.wide == 5 ? SR_STREAM_MT(E, 5) : a.wide == 8 ? SR_STREAM_MT4(E, 8) : SR_STREAM_MT4(E, 10))
+    if (mt32 > 4 && a.wide >= 8) return SR_E_ARG;
+    if (epi == EPI_F32) SR_STREAM_W(EPI_F32); else SR_STREAM_W(EPI_SWIGLU);
     SR_HIP(attr);
     SR_HIP(hipGetLastError());
     return SR_OK;

@@ -140,15 +140,14 @@ struct GemmArgs {
     int mt_total;        // row tiles in X (and in a fragment-major output)
     int ks_total;        // k-steps (K padded to 32) in X and W
     int splits;          // split-K factor (EPI_F32 only)
-    int wide;            // M <= 128 only: 2, 4, 5, 8 or 10 = computing wavefronts per workgroup (32 features each) of the
-                         // kernel with a loader wavefront; 0 = the 4-wavefront, 128-feature kernel
-    int ring;            // with `wide`: k-steps of weights in flight per wavefront, 8 (default) or 16
+    int wide;            // M <= 256 only: 2, 4, 5, 8 or 10 (M <= 128) = computing wavefronts per workgroup (32 features
+                         // each) of the weight-streaming kernel; 0 = one of the tiled kernels
     void *out;
     int ld_out;          // EPI_F32: row stride (elements); EPI_SWIGLU: k-steps*32 of the output matrix
     size_t split_stride; // EPI_F32: elements between consecutive splits
 };
 
-// The decode-time kernel with a loader wavefront (a.wide != 0, M <= 128); launch_gemm dispatches to it.
+// The weight-streaming kernel with a loader wavefront (a.wide != 0, M <= 256); launch_gemm dispatches to it.
 int launch_gemm_stream(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream);
 int launch_gemm(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream);
 

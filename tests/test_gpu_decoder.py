@@ -863,3 +863,15 @@ def test_prefill_tile_widths(hidden, ffn):
     rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=41, page_tokens=64, kv_pool_bytes=1 << 28)
     print(f"widths {hidden}/{ffn}: worst |dlogit| = {worst:.3e}, mismatches = {mism}, near ties = {near}")
     assert worst <= LOGIT_TOL and mism == 0
+
+
+@pytest.mark.parametrize("n_groups,G", [(43, 3), (20, 8), (23, 7), (24, 8), (32, 7), (64, 4)])
+def test_weight_streaming_projections_beyond_128_rows(n_groups, G):
+    """129, 160, 161, 192, 224 and 256 rows per decode step (five to eight row tiles, the row counts on both sides of a tile
+    edge): gate|up and LM head at three workgroup widths, the thin projections split along K, matrices that do not fill
+    the last workgroup."""
+    shape = synth.ModelShape(1, 544, 4, 2, 64, 1360, 8208)
+    cfg = synth.EpisodeConfig("stream", n_groups, G, 8, 2, 2, 2, 64, (1,), 0.3, 0.4)
+    rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=51, page_tokens=32, kv_pool_bytes=1 << 28)
+    print(f"stream {n_groups * G}: worst |dlogit| = {worst:.3e}, mismatches = {mism}, near ties = {near}")
+    assert worst <= LOGIT_TOL and mism == 0
