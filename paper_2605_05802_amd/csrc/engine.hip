@@ -26,6 +26,7 @@ struct PackedMat {
     uint16_t *p = nullptr;
     int N = 0;        // valid packed rows
     int ks = 0;       // k-steps
+    int rows = 0;     // allocated packed rows
 };
 
 struct LayerW {
@@ -108,7 +109,7 @@ struct sr_ctx {
     bool first_decode_of_turn = false, have_logits = false, gate_pending = false, pt_dirty = false;
     std::vector<int> live_orig_group;
     std::vector<std::vector<int>> pages;       // per live sequence
-    StagingRing pt_ring, rows_ring, units_ring, gate_ring;   // pinned staging of the uploads below
+    StagingRing pt_ring, rows_ring, units_ring, gate_ring, copies_ring;   // pinned staging of the uploads below
     uint8_t *h_retire = nullptr;                // pinned [n_groups0]
     int32_t *h_rows = nullptr;                  // current slot of rows_ring: [n_seq0]
 
@@ -130,6 +131,7 @@ struct sr_ctx {
 
     // device batch state
     int32_t *d_pt = nullptr;
+    int2 *d_copies = nullptr;                  // [n_seq0] page copies of one call
     int32_t *d_actions[2] = {nullptr, nullptr};
     int32_t *d_orig[2] = {nullptr, nullptr};   // original sequence id of every live row (keys the sampler)
     float *d_logits[2] = {nullptr, nullptr};
@@ -180,6 +182,27 @@ int dev_alloc(sr_ctx *c, T **p, size_t n_elems) {
     *p = (T *)v;
     return SR_OK;
 }
+
+// Buffers that are known together come from one allocation: giving back one of 64 MB or more costs the host 0.3 to
+// 0.5 ms whatever its size (sr_destroy of a two-layer 7B-width context: 5.2 ms with an allocation per buffer, 0.7 now).
+struct AllocPlan {
+    std::vector<std::pair<void *, size_t>> items;      // address of the pointer to set, bytes
+    template <typename T>
+    void want(T **p, size_t n_elems) {
+        items.push_back({(void *)p, (n_elems * sizeof(T) + 256 + 255) & ~(size_t)255});   // 256 bytes of slack each
+    }
+    int commit(sr_ctx *c) {
+        size_t total = 0;
+        for (const auto &it : items) total += it.second;
+        char *base = nullptr;
+        SR_TRY(dev_alloc(c, &base, total));
+        for (const auto &it : items) {
+            memcpy(it.first, &base, sizeof base);
+            base += it.second;
+        }
+        return SR_OK;
+    }
+};
 
 // Run one launch, bracketed by events when profiling is on.
 template <typename F>
@@ -249,22 +272,26 @@ int pick_splits(int M, int N, int ks_total) {
     return s < 1 ? 1 : s;
 }
 
-int alloc_packed(sr_ctx *c, PackedMat *m, int n_rows, int K, hipStream_t st) {
+void plan_packed(AllocPlan &plan, PackedMat *m, int n_rows, int K) {
     m->N = n_rows;
     m->ks = round_up(ceil_div(K, 32), 16);       // the GEMMs consume k-steps in groups of 16
     // row padding covers every workgroup width of the projection kernels
     int rows = 0;
     for (int w : {160, 192, 224, 256, 320})
         if (round_up(n_rows, w) > rows) rows = round_up(n_rows, w);
-    const size_t elems = (size_t)rows * m->ks * 32;
-    SR_TRY(dev_alloc(c, &m->p, elems));
-    SR_HIP(hipMemsetAsync(m->p, 0, elems * 2, st));
+    m->rows = rows;
+    plan.want(&m->p, (size_t)rows * m->ks * 32);
+}
+
+// Zero the rows behind the matrix; those in it, and their padding along K, are written when it is packed.
+int clear_padding(const PackedMat &m, hipStream_t st) {
+    const size_t used = (size_t)(m.N / 16) * 16 * m.ks * 32, all = (size_t)m.rows * m.ks * 32;
+    if (all > used) SR_HIP(hipMemsetAsync(m.p + used, 0, (all - used) * 2, st));
     return SR_OK;
 }
 
-int copy_vec(sr_ctx *c, uint16_t **dst, const void *src, size_t n, hipStream_t st) {
-    SR_TRY(dev_alloc(c, dst, n));
-    SR_HIP(hipMemcpyAsync(*dst, src, n * 2, hipMemcpyDeviceToDevice, st));
+int copy_vec(uint16_t *dst, const void *src, size_t n, hipStream_t st) {
+    SR_HIP(hipMemcpyAsync(dst, src, n * 2, hipMemcpyDeviceToDevice, st));
     return SR_OK;
 }
 
@@ -320,6 +347,8 @@ int grow_pages(sr_ctx *c, int new_len, bool shared, hipStream_t st) {
     }
     if (want > (int)c->free_list.size()) return SR_E_NOMEM;
 
+    int2 *copies = nullptr;          // pages to duplicate: (source, destination)
+    int n_copies = 0;
     for (int r = 0; r < n_seq; r += shared ? G : 1) {
         if (!shared && c->seq_len % pt != 0) {
             const int idx = c->seq_len / pt, old = c->pages[r][idx];
@@ -328,11 +357,8 @@ int grow_pages(sr_ctx *c, int new_len, bool shared, hipStream_t st) {
                 c->refcnt[np] = 1;
                 c->refcnt[old]--;
                 c->pages[r][idx] = np;
-                if (c->dbg)      // fp32 pages: the same copy over twice as many 16-bit units
-                    SR_TRY(launch_copy_page((uint16_t *)c->kpool32, (uint16_t *)c->vpool32, c->layer_stride * 2,
-                                            c->s.n_layers, c->page_elems * 2, old, np, st));
-                else
-                    SR_TRY(launch_copy_page(c->kpool, c->vpool, c->layer_stride, c->s.n_layers, c->page_elems, old, np, st));
+                if (n_copies == 0) SR_TRY(c->copies_ring.acquire((void **)&copies));
+                copies[n_copies++] = make_int2(old, np);
                 c->st.cow_page_copies++;
                 c->pt_dirty = true;
             }
@@ -348,6 +374,16 @@ int grow_pages(sr_ctx *c, int new_len, bool shared, hipStream_t st) {
             }
             c->pt_dirty = true;
         }
+    }
+    if (n_copies > 0) {
+        SR_HIP(hipMemcpyAsync(c->d_copies, copies, (size_t)n_copies * sizeof(int2), hipMemcpyHostToDevice, st));
+        SR_TRY(c->copies_ring.commit(st));
+        if (c->dbg)                  // fp32 pages: the same copy over twice as many 16-bit units
+            SR_TRY(launch_copy_pages((uint16_t *)c->kpool32, (uint16_t *)c->vpool32, c->layer_stride * 2, c->s.n_layers,
+                                     c->page_elems * 2, c->d_copies, n_copies, st));
+        else
+            SR_TRY(launch_copy_pages(c->kpool, c->vpool, c->layer_stride, c->s.n_layers, c->page_elems, c->d_copies,
+                                     n_copies, st));
     }
     return upload_page_table(c, st);
 }
@@ -787,6 +823,7 @@ void sr_destroy(sr_ctx *c) {
     c->rows_ring.destroy();
     c->units_ring.destroy();
     c->gate_ring.destroy();
+    c->copies_ring.destroy();
     if (c->h_retire) (void)hipHostFree(c->h_retire);
     for (auto &r : c->prof) { (void)hipEventDestroy(r.a); (void)hipEventDestroy(r.b); }
     for (hipEvent_t e : c->event_pool) (void)hipEventDestroy(e);
@@ -806,23 +843,6 @@ static int init_impl(sr_ctx *c) {
     c->R = round_up(max_rows > c->n_seq0 ? max_rows : c->n_seq0, 256);
     c->mt_total = c->R / 16;
 
-    // RoPE tables, computed in double: angle = pos * theta^(-2i/d)
-    {
-        const int half = d / 2;
-        std::vector<float> hc((size_t)o.max_seq_len * half), hs((size_t)o.max_seq_len * half);
-        for (int i = 0; i < half; ++i) {
-            const double inv_freq = pow((double)s.rope_theta, -2.0 * i / d);
-            for (int pos = 0; pos < o.max_seq_len; ++pos) {
-                hc[(size_t)pos * half + i] = (float)cos(pos * inv_freq);
-                hs[(size_t)pos * half + i] = (float)sin(pos * inv_freq);
-            }
-        }
-        SR_TRY(dev_alloc(c, &c->rope_cos, hc.size()));
-        SR_TRY(dev_alloc(c, &c->rope_sin, hs.size()));
-        SR_HIP(hipMemcpy(c->rope_cos, hc.data(), hc.size() * 4, hipMemcpyHostToDevice));
-        SR_HIP(hipMemcpy(c->rope_sin, hs.data(), hs.size() * 4, hipMemcpyHostToDevice));
-    }
-
     // KV pool: [layer][page][kv head][32-token block][32*d], K and V separately
     c->dbg = o.fp32_debug != 0;
     c->page_elems = (size_t)s.n_kv_heads * o.page_tokens * d;
@@ -832,18 +852,6 @@ static int init_impl(sr_ctx *c) {
     c->max_pages = ceil_div(o.max_seq_len, o.page_tokens);
     if (c->n_pages < 1) return SR_E_ARG;
     c->layer_stride = c->page_elems * c->n_pages;
-    if (c->dbg) {
-        SR_TRY(dev_alloc(c, &c->kpool32, c->layer_stride * s.n_layers));
-        SR_TRY(dev_alloc(c, &c->vpool32, c->layer_stride * s.n_layers));
-        SR_HIP(hipMemset(c->kpool32, 0, c->layer_stride * s.n_layers * 4));
-        SR_HIP(hipMemset(c->vpool32, 0, c->layer_stride * s.n_layers * 4));
-    } else {
-        SR_TRY(dev_alloc(c, &c->kpool, c->layer_stride * s.n_layers));
-        SR_TRY(dev_alloc(c, &c->vpool, c->layer_stride * s.n_layers));
-        // masked probabilities multiply V entries that were never written: they must be finite
-        SR_HIP(hipMemset(c->kpool, 0, c->layer_stride * s.n_layers * 2));
-        SR_HIP(hipMemset(c->vpool, 0, c->layer_stride * s.n_layers * 2));
-    }
     c->refcnt.assign(c->n_pages, 0);
     c->free_list.resize(c->n_pages);
     for (int i = 0; i < c->n_pages; ++i) c->free_list[i] = c->n_pages - 1 - i;
@@ -859,63 +867,100 @@ static int init_impl(sr_ctx *c) {
     for (int r = 0; r < c->n_seq0; ++r) c->row_orig[r] = r;
     c->end_step.assign(c->n_seq0, INT_MAX);
     c->fin_index.assign(c->n_seq0, -1);
+    c->pages.assign(c->n_seq0, {});
     SR_TRY(c->units_ring.init((size_t)(2 * c->n_groups0 + c->n_seq0) * 4 + 16));
     SR_TRY(c->gate_ring.init((size_t)2 * c->n_seq0 * 4 + 16));
-    SR_TRY(dev_alloc(c, &c->d_units, (size_t)2 * c->n_groups0 + c->n_seq0));
-    SR_TRY(dev_alloc(c, &c->d_gate_map, (size_t)2 * c->n_seq0));
-    SR_TRY(dev_alloc(c, &c->d_fin_actions, (size_t)c->n_seq0 * o.max_turns));
-    SR_TRY(dev_alloc(c, &c->d_gate_actions, (size_t)c->n_seq0 * o.max_turns));
-    SR_TRY(dev_alloc(c, &c->d_gate_sig, (size_t)c->n_groups0));
-    c->pages.assign(c->n_seq0, {});
+    SR_TRY(c->copies_ring.init((size_t)c->n_seq0 * sizeof(int2) + 16));
     SR_TRY(c->pt_ring.init((size_t)c->n_seq0 * c->max_pages * 4 + 16));
-    SR_HIP(hipHostMalloc((void **)&c->h_retire, c->n_groups0 + 16, hipHostMallocDefault));
     SR_TRY(c->rows_ring.init((size_t)c->n_seq0 * 4 + 16));
-    SR_TRY(dev_alloc(c, &c->d_pt, (size_t)c->n_seq0 * c->max_pages));
-    SR_HIP(hipMemset(c->d_pt, 0, (size_t)c->n_seq0 * c->max_pages * 4));
+    SR_HIP(hipHostMalloc((void **)&c->h_retire, c->n_groups0 + 16, hipHostMallocDefault));
+
+    // device buffers
+    const size_t n_seq = c->n_seq0, n_grp = c->n_groups0, R = c->R, kv_elems = c->layer_stride * s.n_layers;
+    const size_t rope_elems = (size_t)o.max_seq_len * (d / 2);
+    const int n_max = c->qkv_cols > s.hidden ? c->qkv_cols : s.hidden;
+    const size_t dec_rows = round_up(c->n_seq0, 128);
+    c->partial_elems = R * n_max;
+    if (dec_rows * n_max * kMaxSplitK > c->partial_elems) c->partial_elems = dec_rows * n_max * kMaxSplitK;
+    c->part_rows_cap = 2 * R * s.n_q_heads + n_seq * s.n_kv_heads * 32 * (2 * kMaxAttnSplits + 1);
+    AllocPlan plan;
+    plan.want(&c->rope_cos, rope_elems);
+    plan.want(&c->rope_sin, rope_elems);
+    if (c->dbg) {
+        plan.want(&c->kpool32, kv_elems);
+        plan.want(&c->vpool32, kv_elems);
+        plan.want(&c->xn32, R * (size_t)s.hidden);
+        plan.want(&c->attn32, R * (size_t)s.n_q_heads * d);
+        plan.want(&c->act32, R * (size_t)s.ffn);
+        plan.want(&c->q32, R * (size_t)s.n_q_heads * d);
+    } else {
+        plan.want(&c->kpool, kv_elems);
+        plan.want(&c->vpool, kv_elems);
+    }
+    plan.want(&c->d_copies, n_seq);
+    plan.want(&c->d_units, 2 * n_grp + n_seq);
+    plan.want(&c->d_gate_map, 2 * n_seq);
+    plan.want(&c->d_fin_actions, n_seq * o.max_turns);
+    plan.want(&c->d_gate_actions, n_seq * o.max_turns);
+    plan.want(&c->d_gate_sig, n_grp);
+    plan.want(&c->d_pt, n_seq * c->max_pages);
     for (int i = 0; i < 2; ++i) {
-        SR_TRY(dev_alloc(c, &c->d_actions[i], (size_t)c->n_seq0 * o.max_turns));
-        SR_TRY(dev_alloc(c, &c->d_logits[i], (size_t)c->n_seq0 * s.vocab));
-        SR_TRY(launch_fill_i32(c->d_actions[i], (size_t)c->n_seq0 * o.max_turns, -1, nullptr));
-        SR_TRY(dev_alloc(c, &c->d_orig[i], (size_t)c->n_seq0));
-        SR_TRY(dev_alloc(c, &c->d_logprob[i], (size_t)c->n_seq0));
-        SR_HIP(hipMemset(c->d_logprob[i], 0, (size_t)c->n_seq0 * sizeof(double)));
+        plan.want(&c->d_actions[i], n_seq * o.max_turns);
+        plan.want(&c->d_logits[i], n_seq * s.vocab);
+        plan.want(&c->d_orig[i], n_seq);
+        plan.want(&c->d_logprob[i], n_seq);
+    }
+    plan.want(&c->d_greedy, n_seq);
+    plan.want(&c->d_chosen, n_seq);
+    plan.want(&c->d_sums, n_grp);
+    plan.want(&c->d_rows, n_seq);
+    plan.want(&c->d_retire, n_grp);
+    plan.want(&c->resid, R * s.hidden);
+    plan.want(&c->partials, c->partial_elems);
+    plan.want(&c->xn, R * (size_t)(c->ks_h * 32) / 8);
+    plan.want(&c->attn_out, R * (size_t)(c->ks_q * 32) / 8);
+    plan.want(&c->act, R * (size_t)(c->ks_f * 32) / 8);
+    plan.want(&c->q, R * (size_t)s.n_q_heads * d);
+    plan.want(&c->part_o, c->part_rows_cap * d);
+    plan.want(&c->part_ml, c->part_rows_cap * 2);
+    SR_TRY(plan.commit(c));
+
+    // what is read before it is written: masked probabilities multiply V entries that were never written (they must be
+    // finite), and padded k-steps must read as zero
+    if (c->dbg) {
+        SR_HIP(hipMemset(c->kpool32, 0, kv_elems * 4));
+        SR_HIP(hipMemset(c->vpool32, 0, kv_elems * 4));
+    } else {
+        SR_HIP(hipMemset(c->kpool, 0, kv_elems * 2));
+        SR_HIP(hipMemset(c->vpool, 0, kv_elems * 2));
+    }
+    SR_HIP(hipMemset(c->xn, 0, R * (size_t)(c->ks_h * 32) * 2));
+    SR_HIP(hipMemset(c->attn_out, 0, R * (size_t)(c->ks_q * 32) * 2));
+    SR_HIP(hipMemset(c->act, 0, R * (size_t)(c->ks_f * 32) * 2));
+    SR_HIP(hipMemset(c->d_pt, 0, n_seq * c->max_pages * 4));
+    for (int i = 0; i < 2; ++i) {
+        SR_TRY(launch_fill_i32(c->d_actions[i], n_seq * o.max_turns, -1, nullptr));
+        SR_HIP(hipMemset(c->d_logprob[i], 0, n_seq * sizeof(double)));
     }
     {
         std::vector<int32_t> ids(c->n_seq0);
         for (int i = 0; i < c->n_seq0; ++i) ids[i] = i;
         SR_HIP(hipMemcpy(c->d_orig[0], ids.data(), ids.size() * 4, hipMemcpyHostToDevice));
     }
-    SR_TRY(dev_alloc(c, &c->d_greedy, (size_t)c->n_seq0));
-    SR_TRY(dev_alloc(c, &c->d_chosen, (size_t)c->n_seq0));
-    SR_TRY(dev_alloc(c, &c->d_sums, (size_t)c->n_groups0));
-    SR_TRY(dev_alloc(c, &c->d_rows, (size_t)c->n_seq0));
-    SR_TRY(dev_alloc(c, &c->d_retire, (size_t)c->n_groups0));
-
-    // scratch
-    const size_t R = c->R;
-    const int n_max = c->qkv_cols > s.hidden ? c->qkv_cols : s.hidden;
-    const size_t dec_rows = round_up(c->n_seq0, 128);
-    c->partial_elems = R * n_max;
-    if (dec_rows * n_max * kMaxSplitK > c->partial_elems) c->partial_elems = dec_rows * n_max * kMaxSplitK;
-    c->part_rows_cap = 2 * R * s.n_q_heads + (size_t)c->n_seq0 * s.n_kv_heads * 32 * (2 * kMaxAttnSplits + 1);
-    SR_TRY(dev_alloc(c, &c->resid, R * s.hidden));
-    SR_TRY(dev_alloc(c, &c->partials, c->partial_elems));
-    SR_TRY(dev_alloc(c, &c->xn, R * (size_t)(c->ks_h * 32) / 8));
-    SR_TRY(dev_alloc(c, &c->attn_out, R * (size_t)(c->ks_q * 32) / 8));
-    SR_TRY(dev_alloc(c, &c->act, R * (size_t)(c->ks_f * 32) / 8));
-    // padded k-steps are never written afterwards and must read as zero
-    SR_HIP(hipMemset(c->xn, 0, R * (size_t)(c->ks_h * 32) * 2));
-    SR_HIP(hipMemset(c->attn_out, 0, R * (size_t)(c->ks_q * 32) * 2));
-    SR_HIP(hipMemset(c->act, 0, R * (size_t)(c->ks_f * 32) * 2));
-    SR_TRY(dev_alloc(c, &c->q, R * (size_t)s.n_q_heads * d));
-    if (c->dbg) {
-        SR_TRY(dev_alloc(c, &c->xn32, R * (size_t)s.hidden));
-        SR_TRY(dev_alloc(c, &c->attn32, R * (size_t)s.n_q_heads * d));
-        SR_TRY(dev_alloc(c, &c->act32, R * (size_t)s.ffn));
-        SR_TRY(dev_alloc(c, &c->q32, R * (size_t)s.n_q_heads * d));
+    // RoPE tables, computed in double: angle = pos * theta^(-2i/d)
+    {
+        const int half = d / 2;
+        std::vector<float> hc(rope_elems), hs(rope_elems);
+        for (int i = 0; i < half; ++i) {
+            const double inv_freq = pow((double)s.rope_theta, -2.0 * i / d);
+            for (int pos = 0; pos < o.max_seq_len; ++pos) {
+                hc[(size_t)pos * half + i] = (float)cos(pos * inv_freq);
+                hs[(size_t)pos * half + i] = (float)sin(pos * inv_freq);
+            }
+        }
+        SR_HIP(hipMemcpy(c->rope_cos, hc.data(), hc.size() * 4, hipMemcpyHostToDevice));
+        SR_HIP(hipMemcpy(c->rope_sin, hs.data(), hs.size() * 4, hipMemcpyHostToDevice));
     }
-    SR_TRY(dev_alloc(c, &c->part_o, c->part_rows_cap * d));
-    SR_TRY(dev_alloc(c, &c->part_ml, c->part_rows_cap * 2));
     SR_HIP(hipDeviceSynchronize());
     return SR_OK;
 }
@@ -962,34 +1007,50 @@ int sr_load_weights(sr_ctx *c, const sr_weights *w, void *stream) {
         if (!x.wq || !x.wk || !x.wv || !x.wo || !x.wg || !x.wu || !x.wd || !x.norm1 || !x.norm2) return SR_E_ARG;
         if (s.qkv_bias && (!x.bq || !x.bk || !x.bv)) return SR_E_ARG;
     }
-    SR_TRY(copy_vec(c, &c->embed, w->embed, (size_t)s.vocab * H, st));
-    SR_TRY(copy_vec(c, &c->final_norm, w->final_norm, H, st));
-    SR_TRY(alloc_packed(c, &c->lm, s.vocab, H, st));
+    AllocPlan plan;
+    plan.want(&c->embed, (size_t)s.vocab * H);
+    plan.want(&c->final_norm, (size_t)H);
+    plan_packed(plan, &c->lm, s.vocab, H);
+    c->L.resize(s.n_layers);
+    for (LayerW &y : c->L) {
+        plan_packed(plan, &y.qkv, c->qkv_cols, H);
+        plan_packed(plan, &y.o, H, qd);
+        plan_packed(plan, &y.gu, 2 * s.ffn, H);
+        plan_packed(plan, &y.down, H, s.ffn);
+        if (s.qkv_bias) {
+            plan.want(&y.bq, (size_t)qd);
+            plan.want(&y.bk, (size_t)kd);
+            plan.want(&y.bv, (size_t)kd);
+        }
+        plan.want(&y.norm1, (size_t)H);
+        plan.want(&y.norm2, (size_t)H);
+    }
+    SR_TRY(plan.commit(c));
+
+    SR_TRY(copy_vec(c->embed, w->embed, (size_t)s.vocab * H, st));
+    SR_TRY(copy_vec(c->final_norm, w->final_norm, H, st));
+    SR_TRY(clear_padding(c->lm, st));
     // tied: the LM head is the embedding matrix, packed like any other projection
     SR_TRY(launch_pack_rows((const uint16_t *)(s.tied_lm_head ? w->embed : w->lm_head), s.vocab, H, c->lm.p, c->lm.ks,
                             0, 0, 0, st));
-    c->L.resize(s.n_layers);
     for (int l = 0; l < s.n_layers; ++l) {
         const sr_layer_weights &x = w->layers[l];
         LayerW &y = c->L[l];
-        SR_TRY(alloc_packed(c, &y.qkv, c->qkv_cols, H, st));
+        for (const PackedMat *m : {&y.qkv, &y.o, &y.gu, &y.down}) SR_TRY(clear_padding(*m, st));
         SR_TRY(launch_pack_rows((const uint16_t *)x.wq, qd, H, y.qkv.p, y.qkv.ks, 0, 0, 0, st));
         SR_TRY(launch_pack_rows((const uint16_t *)x.wk, kd, H, y.qkv.p, y.qkv.ks, qd, 0, 0, st));
         SR_TRY(launch_pack_rows((const uint16_t *)x.wv, kd, H, y.qkv.p, y.qkv.ks, qd + kd, 0, 0, st));
-        SR_TRY(alloc_packed(c, &y.o, H, qd, st));
         SR_TRY(launch_pack_rows((const uint16_t *)x.wo, H, qd, y.o.p, y.o.ks, 0, 0, 0, st));
-        SR_TRY(alloc_packed(c, &y.gu, 2 * s.ffn, H, st));
         SR_TRY(launch_pack_rows((const uint16_t *)x.wg, s.ffn, H, y.gu.p, y.gu.ks, 0, 1, 0, st));
         SR_TRY(launch_pack_rows((const uint16_t *)x.wu, s.ffn, H, y.gu.p, y.gu.ks, 0, 1, 1, st));
-        SR_TRY(alloc_packed(c, &y.down, H, s.ffn, st));
         SR_TRY(launch_pack_rows((const uint16_t *)x.wd, H, s.ffn, y.down.p, y.down.ks, 0, 0, 0, st));
         if (s.qkv_bias) {
-            SR_TRY(copy_vec(c, &y.bq, x.bq, qd, st));
-            SR_TRY(copy_vec(c, &y.bk, x.bk, kd, st));
-            SR_TRY(copy_vec(c, &y.bv, x.bv, kd, st));
+            SR_TRY(copy_vec(y.bq, x.bq, qd, st));
+            SR_TRY(copy_vec(y.bk, x.bk, kd, st));
+            SR_TRY(copy_vec(y.bv, x.bv, kd, st));
         }
-        SR_TRY(copy_vec(c, &y.norm1, x.norm1, H, st));
-        SR_TRY(copy_vec(c, &y.norm2, x.norm2, H, st));
+        SR_TRY(copy_vec(y.norm1, x.norm1, H, st));
+        SR_TRY(copy_vec(y.norm2, x.norm2, H, st));
     }
     SR_HIP(hipStreamSynchronize(st));
     c->weights_loaded = true;

@@ -309,8 +309,8 @@ int launch_fill_i32(int32_t *dst, size_t n, int32_t value, hipStream_t stream);
 // dst row r (r < n_out) = src row src_rows[r], row_bytes each (multiples of 4)
 int launch_gather_rows(void *dst, const void *src, const int32_t *src_rows, int n_out, size_t row_bytes,
                        hipStream_t stream);
-// copy `tokens` leading tokens of page src to page dst for every layer and kv head
-int launch_copy_page(uint16_t *kpool, uint16_t *vpool, size_t layer_stride, int n_layers, size_t page_elems,
-                     int src_page, int dst_page, hipStream_t stream);
+// copy page pairs[i].x to page pairs[i].y, i < n_pairs, for every layer and kv head (pairs: device)
+int launch_copy_pages(uint16_t *kpool, uint16_t *vpool, size_t layer_stride, int n_layers, size_t page_elems,
+                      const int2 *pairs, int n_pairs, hipStream_t stream);
 
 }  // namespace sr

@@ -875,3 +875,28 @@ def test_weight_streaming_projections_beyond_128_rows(n_groups, G):
     rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=51, page_tokens=32, kv_pool_bytes=1 << 28)
     print(f"stream {n_groups * G}: worst |dlogit| = {worst:.3e}, mismatches = {mism}, near ties = {near}")
     assert worst <= LOGIT_TOL and mism == 0
+
+
+def test_weights_at_any_address():
+    """Weight matrices that start 2, 6 or 14 bytes behind a 16-byte boundary (views into larger buffers) give the same
+    logits, bit for bit, as aligned ones."""
+    shape = synth.ModelShape(1, 160, 4, 1, 64, 304, 272)
+    w = synth.make_weights(shape, seed=3)
+    toks = dev(synth.uniform_ids(2 * 20, 0, 1, shape.vocab).reshape(2, 20))
+    got = []
+    for shift in (0, 1, 3, 7):
+        def up(a):
+            buf = torch.zeros(a.size + 8, dtype=torch.int16, device="cuda")
+            buf[shift:shift + a.size] = torch.from_numpy(np.ascontiguousarray(a).view(np.int16)).reshape(-1).cuda()
+            return buf[shift:shift + a.size]
+        ctx = sr.Context(shape, 2, 2, 0.3, page_tokens=32, max_seq_len=64, max_turns=1, action_mod=16, kv_pool_bytes=1 << 22)
+        aligned = lambda a: torch.from_numpy(np.ascontiguousarray(a).view(np.int16)).cuda()
+        layers = [{k: (up(v) if v.ndim == 2 else aligned(v)) for k, v in w.layers[0].items()}]
+        ctx.sr_load_weights(aligned(w.embed), up(w.lm_head), aligned(w.final_norm), layers)
+        ctx.sr_prefill_chunk(toks, True)
+        out = torch.empty((4, shape.vocab), dtype=torch.float32, device="cuda")
+        ctx.sr_get_logits(out)
+        torch.cuda.synchronize()
+        got.append(out.cpu().numpy())
+        ctx.close()
+    assert np.all(np.isfinite(got[0])) and all(np.array_equal(got[0], g) for g in got[1:])
