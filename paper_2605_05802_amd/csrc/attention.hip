@@ -35,15 +35,6 @@ __device__ __forceinline__ bf16x8 load_frag(const uint16_t *p) {
     else return __builtin_bit_cast(bf16x8, *(const u32x4 *)p);
 }
 
-// Reductions over the four lanes (c, g), g = 0 .. 3, that hold one query row: the halves of the wavefront, then the
-// neighbouring 16-lane rows, exchanged by vector instructions instead of a round trip through LDS each.
-__device__ __forceinline__ float row_max(float x) {
-    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    x = fmaxf(__uint_as_float(h[0]), __uint_as_float(h[1]));
-    const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
-}
-
 // Online softmax of one 32-token block for one row tile.  s holds the raw scores of tokens t0 + tt*16 + 4g + e of query row
 // c; tokens above `lim` are invisible (MASKED; otherwise every token is visible to every used row).  The running maximum is
 // kept in units of score * scale * log2(e), the scale is folded into the exponent's multiply-add, and the exponentials are
@@ -87,9 +78,7 @@ __device__ __forceinline__ void store_item(const AttnArgs &a, const AttnPhase &p
     constexpr int DT = D / 16;
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
-        float l = lrun[rt];
-        l += __shfl_xor(l, 16, 64);
-        l += __shfl_xor(l, 32, 64);
+        const float l = row_sum(lrun[rt]);
         if (limit[rt] < 0) continue;            // padding row of the tile: nobody reads it
         const int row = rt * 16 + c;
         if (a.direct_out) {

@@ -35,7 +35,7 @@ struct LayerW {
 };
 
 constexpr int kMaxSplitK = 16;
-constexpr int kScoreRows = 2048;         // rows of the LM head computed at a time when every position is scored
+constexpr int kScoreRows = 256;          // scoring through stored logits: rows of the LM head computed at a time
 constexpr int kMaxAttnSplits = 16;
 
 }  // namespace
@@ -138,6 +138,8 @@ struct sr_ctx {
     double *d_logprob[2] = {nullptr, nullptr};  // running teacher-forced log-likelihood of every live row
     float *d_tok_lp = nullptr;                  // per-token values of the chunk being scored [n_seq0][max_seq_len]
     float *score_logits = nullptr;              // [kScoreRows][vocab], allocated by the first scoring call
+    ScoreOut score{};                           // scoring without stored logits: buffers for R rows, allocated with it
+    int32_t *score_target = nullptr;
     int cur = 0;
     int32_t *d_greedy = nullptr, *d_chosen = nullptr, *d_sums = nullptr, *d_rows = nullptr;
     uint8_t *d_retire = nullptr;
@@ -728,8 +730,7 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
     }
 
     if (p.score) {
-        // final norm of every row, then the LM head kScoreRows rows at a time; each block of logits is
-        // reduced to one log-probability per row before the next block overwrites it
+        // final norm of every row, then the LM head, reduced to one log-probability per row
         NormArgs na{};
         na.resid = c->resid;
         na.partials = c->partials;
@@ -747,6 +748,35 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
         na.mt_total = c->mt_total;
         na.eps = s.rms_eps;
         SR_TRY(timed(c, SR_KC_NORM, st, [&] { return launch_resid_norm(na, st); }));
+        LogprobArgs la{};
+        la.vocab = s.vocab;
+        la.tokens = p.tokens;
+        la.mask = p.score_mask;
+        la.chunk_len = p.score_chunk_len;
+        la.rows_per_unit = p.chunk;
+        la.tok0 = p.tok_off + 1;                                  // a row predicts the token after it
+        la.out = c->d_tok_lp + (size_t)p.score_unit0 * p.score_chunk_len;
+        float *last = c->d_logits[c->cur] + (size_t)p.logit_row0 * s.vocab;
+        if (!dbg && M > kStreamRows) {
+            // the LM head reduces its rows itself; the last row of every unit is kept
+            GemmArgs ga{};
+            ga.X = c->xn;
+            ga.W = (const uint4 *)c->lm.p;
+            ga.M = M;
+            ga.N = s.vocab;
+            ga.mt_total = c->mt_total;
+            ga.ks_total = c->lm.ks;
+            ga.splits = 1;
+            ga.score = c->score;
+            ga.score.target = c->score_target;
+            ga.score.lse_ld = round_up(M, 256);
+            ga.score.last = p.want_logits ? last : nullptr;
+            ga.score.rows_per_unit = p.chunk;
+            SR_TRY(timed(c, SR_KC_ARGMAX, st, [&] { return launch_score_targets(la, M, c->score_target, st); }));
+            SR_TRY(timed(c, SR_KC_GEMM_LM_HEAD, st, [&] { return launch_gemm(ga, EPI_LSE, st); }));
+            SR_TRY(timed(c, SR_KC_ARGMAX, st, [&] { return launch_score_reduce(la, M, ga.score, st); }));
+            return SR_OK;
+        }
         for (int r0 = 0; r0 < M; r0 += kScoreRows) {
             const int blk = M - r0 < kScoreRows ? M - r0 : kScoreRows;
             const uint4 *x = c->xn + (size_t)(r0 / 16) * 64;      // row tile r0 / 16 of every k-step
@@ -755,17 +785,13 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
                                     nullptr, st)
                            : gemm(c, x, c->lm, blk, EPI_F32, c->score_logits, s.vocab, nullptr, st);
             }));
-            LogprobArgs la{};
             la.logits = c->score_logits;
-            la.vocab = s.vocab;
-            la.tokens = p.tokens;
-            la.mask = p.score_mask;
-            la.chunk_len = p.score_chunk_len;
-            la.rows_per_unit = p.chunk;
             la.row0 = r0;
-            la.tok0 = p.tok_off + 1;                              // a row predicts the token after it
-            la.out = c->d_tok_lp + (size_t)p.score_unit0 * p.score_chunk_len;
             SR_TRY(timed(c, SR_KC_ARGMAX, st, [&] { return launch_logprob_rows(la, blk, st); }));
+        }
+        if (M <= kScoreRows) {                                    // every row's logits are at hand
+            if (p.want_logits) SR_TRY(launch_last_rows(last, c->score_logits, p.n_units, p.chunk, s.vocab, st));
+            return SR_OK;
         }
     }
 
@@ -1114,7 +1140,18 @@ int sr_score_chunk(sr_ctx *c, const int32_t *tokens, const uint8_t *action_mask,
     hipStream_t st = (hipStream_t)stream;
     const sr_model_shape &s = c->s;
     const int n = c->n_live_seq();
-    if (!c->score_logits) SR_TRY(dev_alloc(c, &c->score_logits, (size_t)kScoreRows * s.vocab));
+    if (!c->score_logits) {
+        AllocPlan plan;
+        float *logits = nullptr;
+        plan.want(&logits, (size_t)kScoreRows * s.vocab);
+        if (!c->dbg) {
+            plan.want(&c->score_target, (size_t)c->R);
+            plan.want(&c->score.target_logit, (size_t)c->R);
+            plan.want(&c->score.lse, (size_t)2 * ceil_div(s.vocab, 256) * c->R);
+        }
+        SR_TRY(plan.commit(c));
+        c->score_logits = logits;
+    }
     if (!c->d_tok_lp) SR_TRY(dev_alloc(c, &c->d_tok_lp, (size_t)c->n_seq0 * c->o.max_seq_len));
     const int new_len = c->seq_len + chunk_len;
     SR_TRY(grow_pages(c, new_len, false, st));

@@ -282,6 +282,41 @@ __global__ __launch_bounds__(kPfThreads) void gemm_prefill_kernel(GemmArgs a, in
                 }
             }
         }
+    } else if constexpr (EPI == EPI_LSE) {
+        // a wavefront's 128 columns of a row lie in four lanes
+        const ScoreOut &so = a.score;
+        const int n0 = (nb * 2 * NT + wn * NT) * 16 + 4 * g;         // + 16 i + e
+        auto value = [&](int i, int e, int j) { return n0 + 16 * i < a.N ? acc[i][j][e] : -3.0e38f; };      // N is a multiple of 16
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int m = mb * 256 + (wm * 4 + j) * 16 + c;
+            float mx = -3.0e38f, sum = 0.f;
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) mx = fmaxf(mx, value(i, e, j));
+            mx = row_max(mx);
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    sum += n0 + 16 * i < a.N ? __builtin_amdgcn_exp2f((acc[i][j][e] - mx) * 1.4426950408889634f) : 0.f;
+            sum = row_sum(sum);
+            if (m >= a.M) continue;
+            if (g == 0) so.lse[(size_t)(nb * 2 + wn) * so.lse_ld + m] = make_float2(mx, sum);
+            const int at = so.target[m] - n0;
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (at == 16 * i + e) so.target_logit[m] = acc[i][j][e];
+            if (so.last && m % so.rows_per_unit == so.rows_per_unit - 1) {
+                float *dst = so.last + (size_t)(m / so.rows_per_unit) * a.N + n0;
+#pragma unroll
+                for (int i = 0; i < NT; ++i)
+                    if (n0 + 16 * i < a.N) *(f32x4 *)(dst + 16 * i) = acc[i][j];
+            }
+        }
     } else {
         static_assert(NT % 2 == 0, "gate and up tiles come in pairs");
         uint16_t *out = (uint16_t *)a.out;
@@ -737,6 +772,7 @@ int launch_gemm(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream) {
     const int m_blocks = ceil_div(a.M, 128);
     if (m_blocks * 8 > a.mt_total || a.splits < 1 || m_blocks > 65535 || a.splits > 65535 || a.ks_total % 16)
         return SR_E_ARG;
+    if (epi == EPI_LSE) return ceil_div(a.M, 256) * 16 <= a.mt_total ? launch_tiles<EPI_LSE, 8>(a, stream) : SR_E_ARG;
     if (a.wide) return launch_gemm_stream(a, epi, stream);
     if (a.splits == 1) {
         const int kernel = choose_tiles(a, epi);

@@ -1,5 +1,10 @@
 // Teacher-forced log-likelihood (paper Appendix C.2) and the policy-gradient loss (Section 2.1).
 //
+// More than 256 rows at a time: the LM head's epilogue leaves a (maximum, sum of exponentials) pair per row and 128
+// columns and the target's logit (EPI_LSE in gemm.hip), and score_reduce_kernel turns them into log-probabilities; the
+// logits themselves are stored for the last row of a unit only.  Writing the logits of a block of rows, reading them back
+// and computing the last rows' a second time took 0.7 ms more (of 7.8) at 4096 rows of 152 064 columns.
+// Fewer rows (the weight stream bounds the LM head) and the chunk's first token go through the logits:
 // logprob_rows_kernel: one workgroup per logits row.  log softmax(row)[target] needs the row's
 // maximum and the sum of exponentials; every thread keeps a running (max, sum) pair over its
 // strided part of the row, so the row (vocab x 4 bytes, 608 KiB at the 7B shape) is read once, and
@@ -63,6 +68,48 @@ __global__ __launch_bounds__(kLpThreads) void logprob_rows_kernel(LogprobArgs a)
         const int target = a.tokens[(size_t)u * a.chunk_len + t];
         *dst = (lg[target] - m) - logf(s);
     }
+}
+
+// Row r of a pass -> its (unit, token index in the chunk whose probability it gives); false: predicts nothing here
+__device__ __forceinline__ bool scored_token(const LogprobArgs &a, int row, size_t *at) {
+    const int u = (a.row0 + row) / a.rows_per_unit, t = a.tok0 + (a.row0 + row) % a.rows_per_unit;
+    *at = (size_t)u * a.chunk_len + t;
+    return t < a.chunk_len;
+}
+
+__global__ void score_targets_kernel(LogprobArgs a, int rows, int32_t *__restrict__ target) {
+    const int row = blockIdx.x * blockDim.x + threadIdx.x;
+    if (row >= rows) return;
+    size_t at;
+    const bool scored = scored_token(a, row, &at) && (!a.mask || a.mask[at]);
+    target[row] = scored ? a.tokens[at] : -1;
+}
+
+// Sixteen rows per workgroup, sixteen threads for the column blocks of each; the pairs lie row by row, so a wavefront
+// reads runs of 128 bytes.  Column blocks are merged in a fixed order.
+__global__ __launch_bounds__(256) void score_reduce_kernel(LogprobArgs a, int rows, ScoreOut s, int n_parts) {
+    __shared__ float s_m[16][17], s_s[16][17];
+    const int r = threadIdx.x & 15, q = threadIdx.x >> 4, row = blockIdx.x * 16 + r;
+    float m = -3.0e38f, sum = 0.f;
+    if (row < rows)
+        for (int p = q; p < n_parts; p += 16) {
+            const float2 x = s.lse[(size_t)p * s.lse_ld + row];
+            lse_merge(m, sum, x.x, x.y);
+        }
+    s_m[q][r] = m;
+    s_s[q][r] = sum;
+    __syncthreads();
+    if (q != 0 || row >= rows) return;
+    for (int k = 1; k < 16; ++k) lse_merge(m, sum, s_m[k][r], s_s[k][r]);
+    size_t at;
+    if (!scored_token(a, row, &at)) return;
+    a.out[at] = s.target[row] < 0 ? 0.f : (s.target_logit[row] - m) - logf(sum);
+}
+
+__global__ void last_rows_kernel(float4 *__restrict__ dst, const float4 *__restrict__ src, int period, int vec) {
+    const float4 *from = src + ((size_t)blockIdx.y * period + period - 1) * vec;
+    float4 *to = dst + (size_t)blockIdx.y * vec;
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < vec; i += gridDim.x * blockDim.x) to[i] = from[i];
 }
 
 __global__ void accumulate_logprob_kernel(const float *__restrict__ tok_lp, int n_seq, int chunk_len,
@@ -168,6 +215,32 @@ int launch_logprob_rows(const LogprobArgs &a, int rows, hipStream_t stream) {
     if (rows <= 0) return SR_OK;
     if (a.rows_per_unit < 1 || a.vocab < 1 || a.chunk_len < 1) return SR_E_ARG;
     logprob_rows_kernel<<<dim3(rows), dim3(kLpThreads), 0, stream>>>(a);
+    SR_HIP(hipGetLastError());
+    return SR_OK;
+}
+
+int launch_score_targets(const LogprobArgs &a, int rows, int32_t *target, hipStream_t stream) {
+    if (rows <= 0) return SR_OK;
+    if (a.rows_per_unit < 1 || a.chunk_len < 1) return SR_E_ARG;
+    score_targets_kernel<<<dim3((rows + 255) / 256), dim3(256), 0, stream>>>(a, rows, target);
+    SR_HIP(hipGetLastError());
+    return SR_OK;
+}
+
+int launch_score_reduce(const LogprobArgs &a, int rows, const ScoreOut &s, hipStream_t stream) {
+    if (rows <= 0) return SR_OK;
+    if (a.rows_per_unit < 1 || a.chunk_len < 1 || a.vocab < 1) return SR_E_ARG;
+    score_reduce_kernel<<<dim3((rows + 15) / 16), dim3(256), 0, stream>>>(a, rows, s, 2 * ceil_div(a.vocab, 256));
+    SR_HIP(hipGetLastError());
+    return SR_OK;
+}
+
+int launch_last_rows(float *dst, const float *src, int n, int period, int vocab, hipStream_t stream) {
+    if (n <= 0) return SR_OK;
+    if (vocab % 4) return SR_E_ARG;
+    const int vec = vocab / 4;
+    last_rows_kernel<<<dim3(vec < 64 * 256 ? (vec + 255) / 256 : 64, n), dim3(256), 0, stream>>>((float4 *)dst, (const float4 *)src,
+                                                                                             period, vec);
     SR_HIP(hipGetLastError());
     return SR_OK;
 }

@@ -66,6 +66,22 @@ __host__ __device__ inline size_t frag_offset(int r, int k, int mt_total) {
     return ((((size_t)(k >> 5) * mt_total + (r >> 4)) * 64) + (r & 15) + 16 * ((k & 31) >> 3)) * 8 + (k & 7);
 }
 
+// Reductions over the four lanes (c, g), g = 0 .. 3, that hold one row of a 16x16 MFMA result: the halves of the
+// wavefront, then the neighbouring 16-lane rows, exchanged by vector instructions instead of a round trip through LDS each.
+template <typename F>
+__device__ __forceinline__ float row_reduce(float x, F &&f) {
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = f(__uint_as_float(h[0]), __uint_as_float(h[1]));
+    const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return f(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
+__device__ __forceinline__ float row_max(float x) {
+    return row_reduce(x, [](float a, float b) { return fmaxf(a, b); });
+}
+__device__ __forceinline__ float row_sum(float x) {
+    return row_reduce(x, [](float a, float b) { return a + b; });
+}
+
 // ---------------------------------------------------------------------------------------------
 // direct-to-LDS copies from inline assembly
 // ---------------------------------------------------------------------------------------------
@@ -121,7 +137,19 @@ int launch_pack_rows(const uint16_t *src, int n_rows, int K, uint16_t *dst, int 
 // ---------------------------------------------------------------------------------------------
 enum GemmEpilogue {
     EPI_F32 = 0,    // out fp32 [split][M][ld_out] row-major (split-K partials, or the result if splits == 1)
-    EPI_SWIGLU = 1  // packed rows alternate 16 gate / 16 up features; out = silu(gate)*up, bf16 fragment-major
+    EPI_SWIGLU = 1, // packed rows alternate 16 gate / 16 up features; out = silu(gate)*up, bf16 fragment-major
+    EPI_LSE = 2     // nothing of Y is stored but what a log-probability per row needs: see ScoreOut
+};
+
+// EPI_LSE (scoring): per row and 128 columns the maximum and the sum of exponentials relative to it, the target
+// column's value, and -- for the last row of every unit -- the whole row.
+struct ScoreOut {
+    const int32_t *target;   // [M] target column of a row, or -1
+    float *target_logit;     // [M] written where target >= 0
+    float2 *lse;             // [2 * ceil(N / 256)][lse_ld] (max, sum)
+    int lse_ld;              // M rounded up to 256
+    float *last;             // [units][N] or null
+    int rows_per_unit;
 };
 
 // k-steps [*k0, *k1) of split sp when `units` groups of `unit` k-steps are dealt out evenly
@@ -145,6 +173,7 @@ struct GemmArgs {
     void *out;
     int ld_out;          // EPI_F32: row stride (elements); EPI_SWIGLU: k-steps*32 of the output matrix
     size_t split_stride; // EPI_F32: elements between consecutive splits
+    ScoreOut score;      // EPI_LSE
 };
 
 // The weight-streaming kernel with a loader wavefront (a.wide != 0, M <= 256); launch_gemm dispatches to it.
@@ -299,6 +328,12 @@ struct LogprobArgs {
     float *out;              // [units][chunk_len]
 };
 int launch_logprob_rows(const LogprobArgs &a, int rows, hipStream_t stream);
+// The same from an EPI_LSE projection (a.logits is not read): the target column of every row before it, the
+// log-probabilities behind it.
+int launch_score_targets(const LogprobArgs &a, int rows, int32_t *target, hipStream_t stream);
+int launch_score_reduce(const LogprobArgs &a, int rows, const ScoreOut &s, hipStream_t stream);
+// dst row r = src row r * period + period - 1, `vocab` (a multiple of 4) floats each
+int launch_last_rows(float *dst, const float *src, int n, int period, int vocab, hipStream_t stream);
 // logprob[u] += sum over t of tok_lp[u][t], in token order
 int launch_accumulate_logprob(const float *tok_lp, int n_seq, int chunk_len, double *logprob, hipStream_t stream);
 

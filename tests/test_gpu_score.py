@@ -197,3 +197,48 @@ def test_loss_adds_the_groups_in_index_order(n_groups):
     sd = r.astype(np.float64).std(axis=1, keepdims=True)
     adv = np.where(sd > 0, (r - r.mean(axis=1, keepdims=True, dtype=np.float64)) / (sd + 1e-6), 0.0)
     assert np.allclose(share.cpu().numpy(), (adv * lp).sum(axis=1), rtol=0, atol=1e-9)
+
+
+@pytest.mark.parametrize("chunk,vocab,rows_cap", [(33, 1040, 0), (40, 272, 512), (129, 528, 0), (8, 1040, 0), (1, 272, 0)])
+def test_scoring_without_stored_logits(chunk, vocab, rows_cap):
+    """Chunks of 264 and 320 rows (the LM head reduces its rows itself; one pass and two), of 1032 rows (several row blocks),
+    and of 64 and 8 (through stored logits), vocabularies that do not fill the last tile: the token values agree with
+    log softmax of the logits that the same tokens leave when they are appended one by one, and the logits kept behind
+    the chunk with those of the last one."""
+    shape = synth.ModelShape(1, 256, 4, 2, 64, 256, vocab)
+    w = synth.make_weights(shape, seed=2, sigma=0.05)
+    n, P = 8, 24
+    mk = lambda: sr.Context(shape, 2, 4, 0.3, page_tokens=32, max_seq_len=P + chunk + 8, max_turns=1, action_mod=16,
+                            max_prefill_rows=rows_cap, kv_pool_bytes=1 << 26)
+    prompts = dev(synth.uniform_ids(2 * P, 0, 1, vocab).reshape(2, P))
+    toks = synth.uniform_ids(n * chunk, 0, 2, vocab).reshape(n, chunk)
+    mask = (np.arange(n * chunk).reshape(n, chunk) % 5 != 1).astype(np.uint8)
+    a = mk()
+    load_host_weights(a, w)
+    a.sr_prefill_chunk(prompts, True)
+    lp = torch.full((n, chunk), 7.0, dtype=torch.float32, device="cuda")
+    a.sr_score_chunk(dev(toks), dev(mask), lp)
+    kept = torch.empty((n, vocab), dtype=torch.float32, device="cuda")
+    a.sr_get_logits(kept)
+    total = torch.empty(n, dtype=torch.float64, device="cuda")
+    a.sr_get_logprob(total)
+    b = mk()
+    load_host_weights(b, w)
+    b.sr_prefill_chunk(prompts, True)
+    ref = np.zeros((n, chunk))
+    lg = torch.empty((n, vocab), dtype=torch.float32, device="cuda")
+    for t in range(chunk):
+        b.sr_get_logits(lg)
+        r = torch.log_softmax(lg.double(), dim=1).cpu().numpy()
+        ref[:, t] = r[np.arange(n), toks[:, t]]
+        b.sr_decode_step(dev(np.ascontiguousarray(toks[:, t])))
+    b.sr_get_logits(lg)
+    torch.cuda.synchronize()
+    got = lp.cpu().numpy()
+    assert np.all(got[mask == 0] == 0.0)
+    # decoded and prefilled rows round their operands apart: the bound that the logits of either carry
+    assert np.abs(got - ref * mask).max() <= 2 * LOGIT_TOL
+    assert np.abs(kept.cpu().numpy() - lg.cpu().numpy()).max() <= LOGIT_TOL
+    assert np.abs(total.cpu().numpy() - got.astype(np.float64).sum(axis=1)).max() <= 1e-9 * chunk
+    a.close()
+    b.close()
