@@ -250,19 +250,8 @@ int stream_waves(int M, int N, int ks_total, bool swiglu) {
     return best;
 }
 
+// K splits of the weight-streaming kernel
 int pick_splits(int M, int N, int ks_total) {
-    if (M > 1024) return 1;
-    if (M > kStreamRows) {
-        // a few hundred rows (decode steps of a large batch): a thin matrix gives too few 128 x 128 tiles for the
-        // 256 CUs (two workgroups each), so K is split until about 320 workgroups are in flight -- measured best at
-        // 512 and 304 rows for the O, down and QKV projections of the 7B shape (2-3 splits, 1.5-2.3x faster)
-        const int tiles = ceil_div(M, 128) * ceil_div(N, 128);
-        int s = 320 / tiles;
-        const int units = ks_total / 8;
-        if (s > units / 4) s = units / 4;
-        if (s > 4) s = 4;
-        return s < 1 ? 1 : s;
-    }
     const int n_blocks = ceil_div(N, 32 * stream_waves(M, N, ks_total, false));
     const int target = 256 / n_blocks;
     if (target <= 1) return 1;
@@ -448,8 +437,8 @@ struct Pass {
 // K splits of a projection whose partial sums go to c->partials (the same choice on the normal and on the
 // single-precision debugging path)
 int choose_splits(sr_ctx *c, int M, const PackedMat &W, int ld_out, int *splits, size_t *split_stride) {
-    *splits = pick_splits(M, W.N, W.ks);
     *split_stride = (size_t)round_up(M, 128) * ld_out;
+    *splits = M > kStreamRows ? gemm_splits(M, W.N, W.ks, c->mt_total, kMaxSplitK) : pick_splits(M, W.N, W.ks);
     if (M > 128)                                     // larger batches may split only as far as the buffer allows
         while (*splits > 1 && *split_stride * *splits > c->partial_elems) --*splits;
     if (*split_stride * *splits > c->partial_elems) return SR_E_ARG;

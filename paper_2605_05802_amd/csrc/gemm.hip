@@ -160,8 +160,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a) {
 // ---------------------------------------------------------------------------------------------
 // Prefill (M > 128) kernel: compute bound, so the tile is sized for the matrix cores.
 //
-// A workgroup owns 256 rows x 32 * NT features (NT = 8 for wide matrices; see launch_gemm for the others).  Eight
-// wavefronts in a 2 x 4 arrangement each take 16 * NT features x 64 rows with 16x16x32 MFMAs; both operands reach them
+// A workgroup owns 64 * RT rows x 32 * NT features and one split of K (see plan_gemm for which).  Eight wavefronts in a
+// 2 x 4 arrangement each take 16 * NT features x 16 * RT rows with 16x16x32 MFMAs; both operands reach them
 // through LDS, so every byte crosses the vector-memory path once per workgroup.  Each wavefront copies its share of a
 // k-step from global memory straight into LDS (direct-to-LDS loads issued from inline assembly and waited for by hand),
 // three k-steps ahead through four buffers, with one workgroup barrier per k-step.
@@ -169,25 +169,28 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a) {
 // The fragments of k-step s + 1 are read from LDS while the MFMAs of k-step s run, into a second register set: the
 // barrier that starts k-step s therefore waits for the copies of s + 1, and the reads are spread over the whole k-step
 // instead of standing in front of its first MFMA.  With eight wavefronts (two per SIMD) there are 256 registers for
-// 4 * 4 * NT accumulators and two sets of NT + 4 fragments.
+// 4 * RT * NT accumulators and two sets of NT + RT fragments.
 //
-// The tiles are numbered in panels of eight row blocks, column by column, and every XCD takes a contiguous eighth of
+// The tiles are numbered split by split, in panels of eight row blocks, column by column, and every XCD takes a contiguous eighth of
 // that order: the 32 workgroups that run together on one XCD form an 8 x 4 block of tiles (2048 rows x 128 * NT
 // features) whose operands they share through that XCD's L2, and no XCD has more than one tile above its share.
 // ---------------------------------------------------------------------------------------------
 constexpr int kPfThreads = 512;
 constexpr int kPfBufs = 4;                 // k-steps in LDS
-constexpr int pf_stage_vec(int nt) { return (2 * nt + 16) * 64; }      // u32x4 per k-step: [W: 2 NT tiles][X: 16 tiles]
-constexpr int pf_lds_bytes(int nt) { return kPfBufs * pf_stage_vec(nt) * 16; }
+constexpr int pf_tiles(int nt, int rt) { return 2 * nt + 4 * rt; }      // 1 KiB tiles per k-step: W, then X
+constexpr int pf_lds_bytes(int nt, int rt) { return kPfBufs * pf_tiles(nt, rt) * 1024; }
 
-template <int EPI, int NT>
+template <int EPI, int NT, int RT>
 __global__ __launch_bounds__(kPfThreads) void gemm_prefill_kernel(GemmArgs a, int m_blocks, int n_blocks, int per_xcd) {
-    extern __shared__ u32x4 pf_lds[];      // [kPfBufs][pf_stage_vec(NT)]
-    constexpr int SV = pf_stage_vec(NT);
+    extern __shared__ u32x4 pf_lds[];      // [kPfBufs][tile][lane]
+    constexpr int TILES = pf_tiles(NT, RT), SV = TILES * 64;
+    constexpr int COPIES = (TILES + 7) / 8;          // per wavefront and k-step; some wavefronts have one less
 
-    // linear id -> XCD -> place in its share -> tile
-    const int t = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (t >= m_blocks * n_blocks) return;
+    // linear id -> XCD -> place in its share -> split, tile
+    int t = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    const int sp = t / (m_blocks * n_blocks);
+    if (sp >= a.splits) return;
+    t -= sp * m_blocks * n_blocks;
     const int panel = t / (8 * n_blocks), in_panel = t - panel * 8 * n_blocks;
     const int panel_rows = min(8, m_blocks - panel * 8);
     const int nb = in_panel / panel_rows, mb = panel * 8 + in_panel - nb * panel_rows;
@@ -195,47 +198,55 @@ __global__ __launch_bounds__(kPfThreads) void gemm_prefill_kernel(GemmArgs a, in
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave & 1, wm = wave >> 1;
-    const int n_stages = a.ks_total;
+    int ks0, ks1;
+    split_range(a.ks_total, kPfBufs, a.splits, sp, &ks0, &ks1);
+    const int n_stages = ks1 - ks0;
 
-    // copies of one k-step: X tiles 2 * wave, 2 * wave + 1 and W tiles wave, wave + 8 (if there is one)
-    const bool two_w = 2 * NT == 16 || wave + 8 < 2 * NT;
-    const char *xsrc = (const char *)a.X + (size_t)(mb * 16 + wave * 2) * 1024;                     // + ks * mt_total * 1024
-    const char *wsrc = (const char *)a.W + (size_t)(nb * 2 * NT + wave) * a.ks_total * 1024;        // + ks * 1024
-    const size_t x_step = (size_t)a.mt_total * 1024, w_8 = (size_t)8 * a.ks_total * 1024;
+    // copies of one k-step: tiles wave, wave + 8, ...
+    const bool full = TILES % 8 == 0 || wave + 8 * (COPIES - 1) < TILES;
+    const char *src[COPIES];
+    size_t step[COPIES];
+#pragma unroll
+    for (int k = 0; k < COPIES; ++k) {
+        const int tile = min(wave + 8 * k, TILES - 1);
+        const bool is_w = tile < 2 * NT;
+        step[k] = is_w ? (size_t)1024 : (size_t)a.mt_total * 1024;
+        src[k] = (is_w ? (const char *)a.W + (size_t)(nb * 2 * NT + tile) * a.ks_total * 1024
+                       : (const char *)a.X + (size_t)(mb * 4 * RT + tile - 2 * NT) * 1024) + (size_t)ks0 * step[k];
+    }
     const unsigned voff = lane * 16;
     const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(__attribute__((address_space(3))) void *)pf_lds);
     auto copy_stage = [&](int st, int buf) {         // past the end: a harmless re-read of the last k-step, never consumed
         const int ks = min(st, n_stages - 1);
         const unsigned base = lds0 + (unsigned)(buf * SV + wave * 64) * 16;
-        const char *x = xsrc + ks * x_step, *w = wsrc + (size_t)ks * 1024;
-        lds_dma16_uniform(w, voff, base);
-        if (two_w) lds_dma16_uniform(w + w_8, voff, base + 8 * 1024);
-        lds_dma16_uniform(x, voff, base + (unsigned)(2 * NT * 64 + wave * 64) * 16);
-        lds_dma16_uniform(x + 1024, voff, base + (unsigned)(2 * NT * 64 + wave * 64 + 64) * 16);
+#pragma unroll
+        for (int k = 0; k < COPIES; ++k)
+            if (k + 1 < COPIES || full) lds_dma16_uniform(src[k] + ks * step[k], voff, base + (unsigned)k * 8 * 1024);
     };
-    // all LDS reads of this wavefront are done and at most `stages` k-steps of its copies are still on their way (four or
-    // three copies each); then the barrier
+    // all LDS reads of this wavefront are done and at most `stages` k-steps of its copies are still on their way; then the
+    // barrier
     auto wait_and_meet = [&](auto stages) __attribute__((always_inline)) {
         constexpr int S = decltype(stages)::value;
-        if (two_w) __builtin_amdgcn_s_waitcnt(0x0070 | (4 * S));
-        else __builtin_amdgcn_s_waitcnt(0x0070 | (3 * S));
+        static_assert(COPIES * 3 < 16, "the count's low four bits");
+        if (full) __builtin_amdgcn_s_waitcnt(0x0070 | (COPIES * S));
+        else __builtin_amdgcn_s_waitcnt(0x0070 | ((COPIES - 1) * S));
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     };
 
-    f32x4 acc[NT][4];                      // [feature tile][row tile]: lane (c, g) holds features 4g .. 4g+3 of row c
+    f32x4 acc[NT][RT];                      // [feature tile][row tile]: lane (c, g) holds features 4g .. 4g+3 of row c
 #pragma unroll
     for (int i = 0; i < NT; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < RT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    const int woff = wn * NT * 64 + lane, xoff = (2 * NT + wm * 4) * 64 + lane;
-    bf16x8 wf[2][NT], xf[2][4];            // [k-step parity]
+    const int woff = wn * NT * 64 + lane, xoff = (2 * NT + wm * RT) * 64 + lane;
+    bf16x8 wf[2][NT], xf[2][RT];           // [k-step parity]
     auto read_frags = [&](int set, int buf) __attribute__((always_inline)) {
         const u32x4 *base = pf_lds + buf * SV;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) xf[set][j] = __builtin_bit_cast(bf16x8, base[xoff + j * 64]);
+        for (int j = 0; j < RT; ++j) xf[set][j] = __builtin_bit_cast(bf16x8, base[xoff + j * 64]);
 #pragma unroll
         for (int i = 0; i < NT; ++i) wf[set][i] = __builtin_bit_cast(bf16x8, base[woff + i * 64]);
     };
@@ -244,7 +255,7 @@ __global__ __launch_bounds__(kPfThreads) void gemm_prefill_kernel(GemmArgs a, in
     for (int i = 0; i < kPfBufs; ++i) copy_stage(i, i);
     wait_and_meet(std::integral_constant<int, 3>{});
     read_frags(0, 0);
-    for (int s0 = 0; s0 < n_stages; s0 += kPfBufs) {          // ks_total is a multiple of 16
+    for (int s0 = 0; s0 < n_stages; s0 += kPfBufs) {          // a split is a multiple of four k-steps
 #pragma unroll
         for (int q = 0; q < kPfBufs; ++q) {
             const int s = s0 + q, set = q & 1;
@@ -255,14 +266,14 @@ __global__ __launch_bounds__(kPfThreads) void gemm_prefill_kernel(GemmArgs a, in
 #pragma unroll
             for (int i = 0; i < NT; ++i)
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
+                for (int j = 0; j < RT; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[set][i], xf[set][j], acc[i][j], 0, 0, 0);
 #pragma unroll
-            for (int f = 0; f < NT + 4; ++f) {
+            for (int f = 0; f < NT + RT; ++f) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);   // 2 MFMAs
                 __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // 1 LDS read
             }
-            __builtin_amdgcn_sched_group_barrier(0x008, 4 * NT - 2 * (NT + 4), 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, RT * NT - 2 * (NT + RT), 0);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -270,10 +281,10 @@ __global__ __launch_bounds__(kPfThreads) void gemm_prefill_kernel(GemmArgs a, in
 
     const int c = lane & 15, g = lane >> 4;
     if constexpr (EPI == EPI_F32) {
-        float *out = (float *)a.out;
+        float *out = (float *)a.out + (size_t)sp * a.split_stride;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int m = mb * 256 + (wm * 4 + j) * 16 + c;
+        for (int j = 0; j < RT; ++j) {
+            const int m = (mb * 4 * RT + wm * RT + j) * 16 + c;
             if (m < a.M) {
 #pragma unroll
                 for (int i = 0; i < NT; ++i) {
@@ -288,8 +299,8 @@ __global__ __launch_bounds__(kPfThreads) void gemm_prefill_kernel(GemmArgs a, in
         const int n0 = (nb * 2 * NT + wn * NT) * 16 + 4 * g;         // + 16 i + e
         auto value = [&](int i, int e, int j) { return n0 + 16 * i < a.N ? acc[i][j][e] : -3.0e38f; };      // N is a multiple of 16
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int m = mb * 256 + (wm * 4 + j) * 16 + c;
+        for (int j = 0; j < RT; ++j) {
+            const int m = (mb * 4 * RT + wm * RT + j) * 16 + c;
             float mx = -3.0e38f, sum = 0.f;
 #pragma unroll
             for (int i = 0; i < NT; ++i)
@@ -321,8 +332,8 @@ __global__ __launch_bounds__(kPfThreads) void gemm_prefill_kernel(GemmArgs a, in
         static_assert(NT % 2 == 0, "gate and up tiles come in pairs");
         uint16_t *out = (uint16_t *)a.out;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int m = mb * 256 + (wm * 4 + j) * 16 + c;
+        for (int j = 0; j < RT; ++j) {
+            const int m = (mb * 4 * RT + wm * RT + j) * 16 + c;
             if (m < a.M) {
 #pragma unroll
                 for (int i = 0; i < NT / 2; ++i) {   // tile 2i = gate, tile 2i + 1 = up of features f .. f+15
@@ -688,13 +699,14 @@ int launch_pack_rows(const uint16_t *src, int n_rows, int K, uint16_t *dst, int 
 
 namespace {
 
-// Tiles of 256 rows x 32 * NT features over all of `a`
-template <int EPI, int NT>
+// Tiles of 64 * RT rows x 32 * NT features over all of `a`
+template <int EPI, int NT, int RT>
 int launch_tiles(const GemmArgs &a, hipStream_t stream) {
-    SR_HIP(hipFuncSetAttribute((const void *)gemm_prefill_kernel<EPI, NT>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               pf_lds_bytes(NT)));
-    const int mb = ceil_div(a.M, 256), nb = ceil_div(a.N, 32 * NT), per_xcd = ceil_div(mb * nb, 8);
-    gemm_prefill_kernel<EPI, NT><<<dim3((unsigned)(per_xcd * 8)), dim3(kPfThreads), pf_lds_bytes(NT), stream>>>(a, mb, nb, per_xcd);
+    SR_HIP(hipFuncSetAttribute((const void *)gemm_prefill_kernel<EPI, NT, RT>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               pf_lds_bytes(NT, RT)));
+    const int mb = ceil_div(a.M, 64 * RT), nb = ceil_div(a.N, 32 * NT), per_xcd = ceil_div(mb * nb * a.splits, 8);
+    if (mb * 4 * RT > a.mt_total || a.splits > a.ks_total / kPfBufs || (EPI != EPI_F32 && a.splits != 1)) return SR_E_ARG;
+    gemm_prefill_kernel<EPI, NT, RT><<<dim3((unsigned)(per_xcd * 8)), dim3(kPfThreads), pf_lds_bytes(NT, RT), stream>>>(a, mb, nb, per_xcd);
     SR_HIP(hipGetLastError());
     return SR_OK;
 }
@@ -734,60 +746,73 @@ int launch_mid(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream) {
     return SR_OK;
 }
 
-// No K split: which kernel.  Times of a launch at K = 3584 in us (all are proportional to K), measured
-// on the projections of the 7B shape at 8192, 5120, 4096, 2048, 1280, 768, 512 and 304 rows.
-//   256 x 32 NT tiles: a round of one per CU takes 9.3 (NT + 1.5): O at 4096 rows 86 (NT = 7) and 88 (8), QKV at 8192 rows
-//     186 (6, three rounds), 202 (7, three), 207 (5, four) and 212 (8, three), O at 5120 rows 126 (5), 142 (6), 155 (7) and
-//     165 (8), two rounds each.  Every NT that the epilogue allows is looked at: what decides is how full the last round is.
-//   128 x 128 tiles, two to a CU: 39 up to 256 of them; above 1024 rows (W read through L2 by many row blocks)
-//     0.095 a tile and 15, at least 60; up to 1024 rows 0.166 a tile.
-//   All rows in one workgroup of 160 features, up to 512 rows: 108 a round up to 384 rows, 155 up to 512.  Only for matrices of 16 384 rows and more, where it makes a round of workgroups.
-enum TileKernel { TILES_128 = 0, TILES_MID = 1 };      // otherwise NT = 5 .. 8
-int choose_tiles(const GemmArgs &a, GemmEpilogue epi) {
-    const long long mb = ceil_div(a.M, 256);
-    const long long t128 = (long long)ceil_div(a.M, 128) * ceil_div(a.N, 128);
-    double best = a.M > 1024 ? (t128 <= 256 ? 39.0 : t128 < 474 ? 60.0 : 0.095 * t128 + 15.0)
-                             : (t128 < 235 ? 39.0 : 0.166 * t128);
-    int kernel = TILES_128;
-    if (mb * 16 <= a.mt_total) {
-        for (int nt = 8; nt >= 5; --nt) {
-            if (epi == EPI_SWIGLU && nt % 2) continue;
-            const long long rounds = (mb * ceil_div(a.N, 32 * nt) + 255) / 256;
-            const double us = rounds * 9.3 * (nt + 1.5);
-            if (us < best) { best = us; kernel = nt; }
+// More than 256 rows: which kernel, and how many K splits.  Times in us, from launches of the 7B shape's projections at
+// 8192, 5120, 4096, 2048, 1280, 768, 512 and 296 rows; k = K / 3584.
+//   64 RT x 32 NT tiles, one to a CU: a round takes 2.33 RT (NT + 1.5) k.  O at 4096 rows 86 (NT = 7) and 88 (8), QKV at
+//     8192 rows 186 (6, three rounds), 202 (7, three), 207 (5, four) and 212 (8, three), O at 5120 rows 126 (5), 142 (6),
+//     155 (7) and 165 (8), two rounds each.  Every shape is looked at: what decides is how full the last round is.
+//   128 x 128 tiles, two to a CU: 39 k up to 256 of them, 60 k up to 473; then 0.095 k a tile and 15 above 1024 rows (W read
+//     through L2 by many row blocks), 0.166 k a tile up to there.
+//   All rows in one workgroup of 160 features, up to 512 rows: 108 k a round up to 384 rows, 139 k up to 512.  Only for
+//     matrices of 16 384 rows and more, where it makes a round of workgroups.
+//   S splits divide k, cost a fixed 6 and S times the output, written here and read by the next kernel, at 4.5 TB/s.
+struct TileShape { int nt, rt; };
+constexpr TileShape kTileShapes[] = {{8, 4}, {7, 4}, {6, 4}, {5, 4}, {6, 5}, {5, 5}, {4, 5}, {4, 6}};      // {5, 6} and up spill
+enum { KERNEL_128 = -2, KERNEL_MID = -1 };             // otherwise an index into kTileShapes
+
+struct GemmPlan { int kernel, splits; };
+// splits: 0 = choose up to max_splits, otherwise given
+GemmPlan plan_gemm(int M, int N, int ks_total, int mt_total, bool swiglu, int splits, int max_splits) {
+    const double k = ks_total / 112.0;
+    const long long t128 = (long long)ceil_div(M, 128) * ceil_div(N, 128);
+    const int s_lo = splits ? splits : 1;
+    int s_hi = splits ? splits : max_splits;
+    if (!splits && s_hi > ks_total / 32) s_hi = ks_total / 32;         // at least 32 k-steps each: filling the pipeline is not free
+    GemmPlan best{KERNEL_128, s_lo};
+    double least = 0.0;
+    for (int S = s_lo; S == s_lo || S <= s_hi; ++S) {
+        const double more = (swiglu ? 0.0 : 8.0e-6 / 4.5 * S * M * N) + (S > 1 ? 6.0 : 0.0);
+        auto offer = [&](int kernel, double us) {
+            if (least == 0.0 || us + more < least) { least = us + more; best = GemmPlan{kernel, S}; }
+        };
+        const long long n128 = t128 * S;
+        offer(KERNEL_128, k / S * (n128 <= 256 ? 39.0 : n128 < 474 ? 60.0 : M > 1024 ? 0.095 * n128 + 15.0 : 0.166 * n128));
+        for (int i = 0; i < (int)(sizeof kTileShapes / sizeof kTileShapes[0]); ++i) {
+            const int nt = kTileShapes[i].nt, rt = kTileShapes[i].rt, mb = ceil_div(M, 64 * rt);
+            if ((swiglu && nt != 8 && nt != 6) || mb * 4 * rt > mt_total || S > ks_total / kPfBufs) continue;
+            const long long rounds = ((long long)mb * ceil_div(N, 32 * nt) * S + 255) / 256;
+            offer(i, rounds * 2.33 * rt * (nt + 1.5) * k / S);
         }
+        if (S == 1 && M <= 512 && N >= 16384)
+            offer(KERNEL_MID, k * ceil_div(ceil_div(N, 160), 256) * (M <= 384 ? 108.0 : 139.0));
     }
-    if (a.M <= 512 && a.N >= 16384) {
-        const int rounds = ceil_div(ceil_div(a.N, 160), 256);
-        const double us = rounds * (a.M <= 384 ? 108.0 : 155.0);
-        if (us < best) { best = us; kernel = TILES_MID; }
-    }
-    return kernel;
+    return best;
 }
 
 }  // namespace
+
+int gemm_splits(int M, int N, int ks_total, int mt_total, int max_splits) {
+    return plan_gemm(M, N, ks_total, mt_total, false, 0, max_splits).splits;
+}
 
 int launch_gemm(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream) {
     if (a.M <= 0) return SR_OK;
     const int m_blocks = ceil_div(a.M, 128);
     if (m_blocks * 8 > a.mt_total || a.splits < 1 || m_blocks > 65535 || a.splits > 65535 || a.ks_total % 16)
         return SR_E_ARG;
-    if (epi == EPI_LSE) return ceil_div(a.M, 256) * 16 <= a.mt_total ? launch_tiles<EPI_LSE, 8>(a, stream) : SR_E_ARG;
     if (a.wide) return launch_gemm_stream(a, epi, stream);
-    if (a.splits == 1) {
-        const int kernel = choose_tiles(a, epi);
-        if (kernel == TILES_MID) return launch_mid(a, epi, stream);
-        if (epi == EPI_SWIGLU) {
-            if (kernel == 8) return launch_tiles<EPI_SWIGLU, 8>(a, stream);
-            if (kernel == 6) return launch_tiles<EPI_SWIGLU, 6>(a, stream);
-        } else {
-            if (kernel == 8) return launch_tiles<EPI_F32, 8>(a, stream);
-            if (kernel == 7) return launch_tiles<EPI_F32, 7>(a, stream);
-            if (kernel == 6) return launch_tiles<EPI_F32, 6>(a, stream);
-            if (kernel == 5) return launch_tiles<EPI_F32, 5>(a, stream);
-        }
-    }
-    return launch_tiles128(a, epi, stream);
+    if (epi == EPI_LSE) return launch_tiles<EPI_LSE, 8, 4>(a, stream);
+    if (epi == EPI_SWIGLU && a.splits != 1) return SR_E_ARG;
+    const GemmPlan plan = plan_gemm(a.M, a.N, a.ks_total, a.mt_total, epi == EPI_SWIGLU, a.splits, a.splits);
+    if (plan.kernel == KERNEL_128) return launch_tiles128(a, epi, stream);
+    if (plan.kernel == KERNEL_MID) return launch_mid(a, epi, stream);
+    const TileShape t = kTileShapes[plan.kernel];
+#define SR_TILE_CASE(E, NT, RT) if (epi == E && t.nt == NT && t.rt == RT) return launch_tiles<E, NT, RT>(a, stream);
+    SR_TILE_CASE(EPI_SWIGLU, 8, 4) SR_TILE_CASE(EPI_SWIGLU, 6, 4) SR_TILE_CASE(EPI_SWIGLU, 6, 5)
+    SR_TILE_CASE(EPI_F32, 8, 4) SR_TILE_CASE(EPI_F32, 7, 4) SR_TILE_CASE(EPI_F32, 6, 4) SR_TILE_CASE(EPI_F32, 5, 4)
+    SR_TILE_CASE(EPI_F32, 6, 5) SR_TILE_CASE(EPI_F32, 5, 5) SR_TILE_CASE(EPI_F32, 4, 5)
+    SR_TILE_CASE(EPI_F32, 4, 6)
+    return SR_E_ARG;
 }
 
 }  // namespace sr

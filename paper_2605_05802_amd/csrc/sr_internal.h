@@ -179,6 +179,8 @@ struct GemmArgs {
 // The weight-streaming kernel with a loader wavefront (a.wide != 0, M <= 256); launch_gemm dispatches to it.
 int launch_gemm_stream(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream);
 int launch_gemm(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream);
+// K splits (EPI_F32) of a projection of more than 256 rows, at most max_splits
+int gemm_splits(int M, int N, int ks_total, int mt_total, int max_splits);
 
 // ---------------------------------------------------------------------------------------------
 // element-wise kernels

@@ -900,3 +900,17 @@ def test_weights_at_any_address():
         got.append(out.cpu().numpy())
         ctx.close()
     assert np.all(np.isfinite(got[0])) and all(np.array_equal(got[0], g) for g in got[1:])
+
+
+@pytest.mark.parametrize("n_groups", [33, 64, 75])
+def test_tall_tiles_and_split_deep_projections(n_groups):
+    """264, 512 and 600 rows against a deep down projection (12 304 inputs) and a gate|up matrix of 24 608 packed rows: row
+    blocks of 320 and 256 rows with a ragged last one, up to twelve K splits of uneven length."""
+    shape = synth.ModelShape(1, 1504, 4, 2, 64, 12304, 512)
+    cfg = synth.EpisodeConfig("deep", n_groups, 8, 4, 1, 2, 1, 64, (), 0.3, 0.0)
+    info = {}
+    rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=61, page_tokens=32, kv_pool_bytes=1 << 28,
+                                                     contract_rows=[0, 100, 263], info=info)
+    tol = tolerance(info["contract_max"])
+    print(f"deep {n_groups * 8}: worst |dlogit| = {worst:.3e}, bound {tol:.3e}, mismatches = {mism}, near ties = {near}")
+    assert worst <= tol and all(g < gap_rule(tol) for g in info["mismatch_gaps"])
