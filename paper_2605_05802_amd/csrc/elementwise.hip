@@ -234,7 +234,7 @@ __device__ __forceinline__ uint64_t smx_finalize(uint64_t z) {
 // counter-based SplitMix64 stream keyed (seed, original sequence id, position), counter = vocabulary
 // index: the argmax of the perturbed scores is a draw from softmax(logits / T).
 __global__ __launch_bounds__(1024) void argmax_kernel(const float *__restrict__ logits, int vocab,
-                                                      const int32_t *__restrict__ forced, int32_t *greedy_out,
+                                                      const int32_t *forced, int32_t *greedy_out,
                                                       int32_t *chosen, int32_t *actions, int max_turns,
                                                       int turn_idx, int action_mod, float inv_temperature,
                                                       uint64_t seed, const int32_t *__restrict__ orig_seq, int pos) {
@@ -270,8 +270,8 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float *__restrict__ 
     if (threadIdx.x == 0) {
         for (int w = 1; w < 16; ++w) best = better(best, s_best[w]);
         const int greedy = best.i;
+        const int tok = forced ? forced[r] : greedy;       // before the write: greedy_out may be the same buffer
         if (greedy_out) greedy_out[r] = greedy;
-        const int tok = forced ? forced[r] : greedy;
         chosen[r] = tok;
         if (actions) actions[(size_t)r * max_turns + turn_idx] = tok % action_mod;
     }

@@ -1214,14 +1214,18 @@ int sr_decode_step(sr_ctx *c, const int32_t *forced, int32_t *out_tokens, void *
     SR_TRY(grow_pages(c, c->seq_len + 1, false, st));
 
     const bool record = c->first_decode_of_turn && c->o.action_mod > 0 && c->turn >= 1 && c->turn <= c->o.max_turns;
+    // The library's own choices go straight to the caller; only a buffer that overlaps the forced tokens other than by being
+    // the same one is written behind the kernel that reads those.
+    const uintptr_t fa = (uintptr_t)forced, oa = (uintptr_t)out_tokens, len = (uintptr_t)n * 4;
+    const bool behind = forced && out_tokens && fa != oa && fa < oa + len && oa < fa + len;
     SR_TRY(timed(c, SR_KC_ARGMAX, st, [&] {
-        return launch_argmax(c->d_logits[c->cur], n, c->s.vocab, forced, c->d_greedy, c->d_chosen,
+        return launch_argmax(c->d_logits[c->cur], n, c->s.vocab, forced, behind ? c->d_greedy : out_tokens, c->d_chosen,
                              record ? c->d_actions[c->cur] : nullptr, c->o.max_turns, c->turn - 1,
                              c->o.action_mod > 0 ? c->o.action_mod : 1,
                              c->o.temperature > 0.f ? 1.0f / c->o.temperature : 0.f, c->o.sample_seed,
                              c->d_orig[c->cur], c->seq_len, st);
     }));
-    if (out_tokens) SR_HIP(hipMemcpyAsync(out_tokens, c->d_greedy, (size_t)n * 4, hipMemcpyDeviceToDevice, st));
+    if (behind) SR_HIP(hipMemcpyAsync(out_tokens, c->d_greedy, (size_t)n * 4, hipMemcpyDeviceToDevice, st));
     if (c->first_decode_of_turn && c->turn >= 1) {
         if (record) c->actions_recorded = c->turn;
         c->first_decode_of_turn = false;

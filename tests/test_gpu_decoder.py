@@ -914,3 +914,37 @@ def test_tall_tiles_and_split_deep_projections(n_groups):
     tol = tolerance(info["contract_max"])
     print(f"deep {n_groups * 8}: worst |dlogit| = {worst:.3e}, bound {tol:.3e}, mismatches = {mism}, near ties = {near}")
     assert worst <= tol and all(g < gap_rule(tol) for g in info["mismatch_gaps"])
+
+
+@pytest.mark.parametrize("offset", [None, 0, 1])
+def test_chosen_tokens_into_the_buffer_of_the_forced_ones(offset):
+    """out_tokens apart from `forced`, the same buffer, and one that overlaps it: the forced tokens are what is appended and
+    the library's own choices are what comes back."""
+    shape = synth.TINY
+    w = synth.make_weights(shape, seed=0)
+    n = 64
+    ctx = sr.Context(shape, 8, 8, 0.3, page_tokens=32, max_seq_len=64, max_turns=1, action_mod=0, kv_pool_bytes=1 << 26)
+    load_host_weights(ctx, w)
+    ctx.sr_prefill_chunk(dev(synth.uniform_ids(8 * 16, 0, 1, shape.vocab).reshape(8, 16)), True)
+    ctx.sr_prefill_chunk(dev(synth.uniform_ids(n * 4, 0, 2, shape.vocab).reshape(n, 4)), False)
+    logits = torch.empty((n, shape.vocab), dtype=torch.float32, device="cuda")
+    ctx.sr_get_logits(logits)
+    own = torch.argmax(logits, dim=1).to(torch.int32)
+    ids = dev(synth.uniform_ids(n, 0, 3, shape.vocab))
+    buf = torch.zeros(n + 8, dtype=torch.int32, device="cuda")
+    buf[:n] = ids
+    out = torch.empty(n, dtype=torch.int32, device="cuda") if offset is None else buf[offset:offset + n]
+    ctx.sr_decode_step(buf[:n], out)
+    got = torch.empty_like(logits)
+    ctx.sr_get_logits(got)
+    ref = sr.Context(shape, 8, 8, 0.3, page_tokens=32, max_seq_len=64, max_turns=1, action_mod=0, kv_pool_bytes=1 << 26)
+    load_host_weights(ref, w)
+    ref.sr_prefill_chunk(dev(synth.uniform_ids(8 * 16, 0, 1, shape.vocab).reshape(8, 16)), True)
+    ref.sr_prefill_chunk(dev(synth.uniform_ids(n * 4, 0, 2, shape.vocab).reshape(n, 4)), False)
+    ref.sr_decode_step(ids)
+    want = torch.empty_like(logits)
+    ref.sr_get_logits(want)
+    torch.cuda.synchronize()
+    assert torch.equal(out, own) and torch.equal(got, want)
+    ctx.close()
+    ref.close()
