@@ -2,13 +2,14 @@
 //
 // A work item is one wavefront.  It owns up to 16*RT query rows -- consecutive query tokens of
 // one unit times the n_rep query heads that share one kv head -- and one split of a token
-// range.  K and V tiles go from HBM straight into MFMA operand registers (the page layout is
-// the operand layout, so each 16-byte lane load is part of a contiguous 1 KiB run); nothing is
-// staged in LDS because a KV byte is used by exactly one wavefront.
+// range.  The page layout is the MFMA operand layout: where a KV byte is used by one wavefront
+// (a sequence's private context in decode) K and V tiles go from HBM straight into operand
+// registers, each 16-byte lane load part of a contiguous 1 KiB run; where several items walk the
+// same blocks (prefill, the shared prompt in decode) four of them share each block through LDS.
 //
 // Per 32-token block:   S^T = K Q^T   (tokens x rows; the accumulator leaves each lane holding
-// four consecutive tokens of one query row), online softmax with the row maximum reduced by
-// two cross-lane shuffles, then  O^T += V^T P^T  where the probabilities of the two 16-token
+// four consecutive tokens of one query row), online softmax with the row maximum reduced across
+// four lanes, then  O^T += V^T P^T  where the probabilities of the two 16-token
 // tiles are packed, in-lane, into the P^T operand (the V block's slot order matches).
 // Splits leave (un-normalised O, running max, running sum); a merge kernel combines the splits
 // of the shared-prompt phase and of the private phase in fixed order.
@@ -157,21 +158,14 @@ __device__ __forceinline__ void single_item(const AttnArgs &a, const AttnPhase &
     load_queries<D, RT>(a, p, qf, limit, qtile, u_row0, u_count, kvh, n_rep, c, g);
 
     // token range of this split, clipped to what any row of the item can see
-    int max_limit = -1, min_limit = 0x7FFFFFFF;
+    int max_limit = -1;
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-        max_limit = max(max_limit, limit[rt]);
-        min_limit = min(min_limit, limit[rt] < 0 ? 0x7FFFFFFF : limit[rt]);
-    }
+    for (int rt = 0; rt < RT; ++rt) max_limit = max(max_limit, limit[rt]);
 #pragma unroll
-    for (int off = 1; off < 16; off <<= 1) {
-        max_limit = max(max_limit, __shfl_xor(max_limit, off, 64));
-        min_limit = min(min_limit, __shfl_xor(min_limit, off, 64));
-    }
+    for (int off = 1; off < 16; off <<= 1) max_limit = max(max_limit, __shfl_xor(max_limit, off, 64));
     // the same in every lane after the reduction; kept in scalar registers so that the block loop, the
     // page-table lookups and the block addresses stay on the scalar unit
     const int t_hi = __builtin_amdgcn_readfirstlane(min(min(p.t_end, t_lo + p.split_tokens), max_limit + 1));
-    const int t_vis = __builtin_amdgcn_readfirstlane(min(t_hi, min_limit == 0x7FFFFFFF ? 0 : min_limit + 1));
 
     f32x4 o[DT][RT];
 #pragma unroll
@@ -242,15 +236,11 @@ __device__ __forceinline__ void single_item(const AttnArgs &a, const AttnPhase &
             __builtin_amdgcn_sched_barrier(0);
             bf16x8 pf[RT];
             float alpha[RT];
-            if (t0 + 32 <= t_vis) {                         // uniform: all but the last block of a range
+            // with the visibility tests in every block: a second copy of the softmax without them, as in shared_tiles, splits
+            // the loop body and costs the chain of a block more than the tests (36 against 43 us with all loads hits)
 #pragma unroll
-                for (int rt = 0; rt < RT; ++rt)
-                    softmax_block<false>(s[rt], 0, 0, scale_log2, mrun[rt], lrun[rt], pf[rt], alpha[rt]);
-            } else {
-#pragma unroll
-                for (int rt = 0; rt < RT; ++rt)
-                    softmax_block<true>(s[rt], t0 + 4 * g, min(limit[rt], t_hi - 1), scale_log2, mrun[rt], lrun[rt], pf[rt], alpha[rt]);
-            }
+            for (int rt = 0; rt < RT; ++rt)
+                softmax_block<true>(s[rt], t0 + 4 * g, min(limit[rt], t_hi - 1), scale_log2, mrun[rt], lrun[rt], pf[rt], alpha[rt]);
             accumulate(pf, alpha);
             __builtin_amdgcn_sched_barrier(0);
             load_v(stream, a.vpool + base_n);
@@ -270,8 +260,8 @@ __global__ __launch_bounds__(256, RT == 1 ? 3 : 2) void attn_kernel(AttnArgs a, 
     // (phase, token range, page-table reads) lives in scalar registers
     const int gitem = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (gitem >= n_items) return;
-    const bool second = gitem >= n0;
-    single_item<D, RT>(a, second ? p1 : p0, second ? gitem - n0 : gitem, threadIdx.x & 63);
+    if (gitem >= n0) single_item<D, RT>(a, p1, gitem - n0, threadIdx.x & 63);
+    else single_item<D, RT>(a, p0, gitem, threadIdx.x & 63);
 }
 
 // ---------------------------------------------------------------------------------------------

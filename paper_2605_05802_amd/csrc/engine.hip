@@ -528,22 +528,12 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
             x.rt = n_rep > 16 ? 2 : 1;              // same row-tile count as the private phase: one launch
             x.q_per_item = (16 * x.rt) / n_rep < c->G ? (16 * x.rt) / n_rep : c->G;
             x.items_per_unit = ceil_div(c->G, x.q_per_item);
-            x.share = x.items_per_unit >= 3;        // a workgroup's fourth wavefront may be idle, not half of them
             x.pt_row_stride = c->G;
             x.t_begin = 0;
             x.t_end = c->shared_tokens;
             x.causal_pos0 = ctx - 1;
             x.causal_stride = 0;
-            // splits of 256 tokens; where query tiles share their blocks, only as many as give every CU a workgroup of
-            // this phase (swept at 16 x 8, 37 x 8 and 32 x 16 sequences: 4, 2 and 2 splits of prompts of 1024, 1024 and
-            // 4096 tokens; sixteen splits of the last one took 147 us plus 46 us of merge instead of 119 + 22)
-            x.n_splits = ceil_div(c->shared_tokens, 256);
-            if (x.share) {
-                const int enough = ceil_div(288, x.n_units * s.n_kv_heads * ceil_div(x.items_per_unit, 4));
-                if (x.n_splits > enough) x.n_splits = enough;
-            }
-            if (x.n_splits > kMaxAttnSplits) x.n_splits = kMaxAttnSplits;
-            x.split_tokens = round_up(ceil_div(c->shared_tokens, x.n_splits), 32);
+            set_shared_phase(&x, c->shared_tokens, s.n_kv_heads, kMaxAttnSplits);
             add_phase(x);
         }
         AttnPhase y{};

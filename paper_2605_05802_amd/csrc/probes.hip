@@ -256,9 +256,9 @@ extern "C" int sr_probe_decode_attention(int n_groups, int G, int shared_tokens,
     x.q_per_item = 16 / n_rep < G ? 16 / n_rep : G;
     x.items_per_unit = ceil_div(G, x.q_per_item);
     x.pt_row_stride = G; x.t_begin = 0; x.t_end = shared_tokens; x.causal_pos0 = ctx - 1;
-    x.n_splits = shared_tokens ? ceil_div(shared_tokens, 256) : 1;
-    if (x.n_splits > 16) x.n_splits = 16;
-    x.split_tokens = shared_tokens ? round_up(ceil_div(shared_tokens, x.n_splits), 32) : 32;
+    x.n_splits = 1;
+    x.split_tokens = 32;
+    if (shared_tokens) set_shared_phase(&x, shared_tokens, n_kv, 16);
     y.n_units = M; y.q_per_unit = 1; y.q_per_item = 1; y.items_per_unit = 1; y.rt = 1; y.pt_row_stride = 1;
     y.t_begin = shared_tokens; y.t_end = ctx; y.causal_pos0 = ctx - 1;
     y.n_splits = priv_splits; y.split_tokens = round_up(ceil_div(priv_tokens, priv_splits), 32);

@@ -271,6 +271,21 @@ struct AttnArgs {
     uint16_t *direct_out;
     int out_mt_total;
 };
+// The shared-prompt phase of a decode step: whether its query tiles share their blocks through LDS (a workgroup's fourth
+// wavefront may be idle, not half of them) and its splits -- 256 tokens each; where tiles share, only as many as give every
+// CU a workgroup of this phase (swept at 16 x 8, 37 x 8 and 32 x 16 sequences: 4, 2 and 2 splits of prompts of 1024, 1024
+// and 4096 tokens; sixteen splits of the last one took 147 us plus 46 us of merge instead of 119 + 22).
+inline int set_shared_phase(AttnPhase *x, int shared_tokens, int n_kv, int max_splits) {
+    x->share = x->items_per_unit >= 3;
+    x->n_splits = ceil_div(shared_tokens, 256);
+    if (x->share) {
+        const int enough = ceil_div(288, x->n_units * n_kv * ceil_div(x->items_per_unit, 4));
+        if (x->n_splits > enough) x->n_splits = enough;
+    }
+    if (x->n_splits > max_splits) x->n_splits = max_splits;
+    x->split_tokens = round_up(ceil_div(shared_tokens, x->n_splits), 32);
+    return x->n_splits;
+}
 // One launch over one or two phases (same rt); phases whose token range is empty contribute no work.
 int launch_attention(const AttnArgs &a, const AttnPhase *phases, int n_phases, hipStream_t stream);
 
