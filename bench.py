@@ -387,7 +387,7 @@ def main():
     if mean_rows > 128:
         # more than 128 rows per step: the projection runs on a tiled prefill kernel and is bound by the matrix cores
         tf = 2.0 * mean_rows * 2 * shape.ffn * shape.hidden / (avg_ms * 1e-3) / 1e12 if avg_ms > 0 else 0.0
-        roofline = {"bound": "mfma", "kernel": "decode gate|up projection at more than 128 rows (128 x 128- or 256 x 256-tile kernel)",
+        roofline = {"bound": "mfma", "kernel": "decode gate|up projection at more than 128 rows (streaming kernel up to 256, tiled above)",
                     "achieved": tf, "peak": MFMA_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": tf / MFMA_PEAK_TFLOPS,
                     "peak_measured": peaks["mfma_bf16_TFLOPs"], "frac_of_measured": tf / peaks["mfma_bf16_TFLOPs"]}
     traffic = None
@@ -447,7 +447,7 @@ def main():
         "prefill_chunk": prefill_obj,
         "kernel_ms_per_profiled_step": {k: v[1] / max(len(rows), 1) for k, v in res["kernel_times"].items()},
         "gate": {"groups_per_s": gate_gps, "ms_per_launch": gate_ms, "workload": "65536 groups x G=8, prefixes 5/10/15",
-                 "kernel": "one lane per pair, table row in registers",
+                 "kernel": "one lane per pair, bit-parallel table rows, equality masks from LDS",
                  "antidiagonal_lds_variant_ms_per_launch": gate_ms_ad,
                  "antidiagonal_lds_variant_groups_per_s": 65536 / (gate_ms_ad * 1e-3)},
         "score_pass": score,
