@@ -36,6 +36,15 @@ __device__ __forceinline__ bf16x8 load_frag(const uint16_t *p) {
     else return __builtin_bit_cast(bf16x8, *(const u32x4 *)p);
 }
 
+// An entry of the page table or of a unit map: the index is uniform and nothing writes the tables while the kernel runs.
+// Read from the constant address space, because the compiler then loads it into a scalar register whatever code it stands
+// in; as an ordinary load it came through a vector register where a launch has one phase, and the wait for it drained the
+// K/V fragments in flight (chunks of one token over a context of 300 for 4 groups of 8 at head size 128: 20.1 us, 16.8 with
+// scalar loads; of two tokens for 16 groups of 8 at head size 64: 13.2 against 9.6).
+__device__ __forceinline__ int table_entry(const int32_t *table, int i) {
+    return ((const __attribute__((address_space(4))) int32_t *)(uintptr_t)table)[i];
+}
+
 // Online softmax of one 32-token block for one row tile.  s holds the raw scores of tokens t0 + tt*16 + 4g + e of query row
 // c; tokens above `lim` are invisible (MASKED; otherwise every token is visible to every used row).  The running maximum is
 // kept in units of score * scale * log2(e), the scale is folded into the exponent's multiply-add, and the exponentials are
@@ -141,13 +150,13 @@ __device__ __forceinline__ void single_item(const AttnArgs &a, const AttnPhase &
     const int n_rep = a.n_q / a.n_kv;
 
     const int c = lane & 15, g = lane >> 4;
-    const int u_row0 = p.unit_row0 ? p.unit_row0[unit] : unit * p.q_per_unit;   // first query token of the unit
-    const int u_count = p.unit_count ? p.unit_count[unit] : p.q_per_unit;       // its query tokens
+    const int u_row0 = p.unit_row0 ? table_entry(p.unit_row0, unit) : unit * p.q_per_unit;   // first query token of the unit
+    const int u_count = p.unit_count ? table_entry(p.unit_count, unit) : p.q_per_unit;       // its query tokens
     const int32_t *pt = a.page_table + (size_t)(p.unit_row0 ? u_row0 : unit * p.pt_row_stride) * a.pt_stride;
     const int blocks_per_page = a.page_tokens >> 5;
     const size_t block_elems = (size_t)32 * D;
     auto block_base = [&](int t0) -> size_t {
-        const int page = pt[t0 / a.page_tokens];
+        const int page = table_entry(pt, t0 / a.page_tokens);
         const int blk = (t0 % a.page_tokens) >> 5;
         return (((size_t)page * a.n_kv + kvh) * blocks_per_page + blk) * block_elems;
     };
@@ -260,8 +269,8 @@ __global__ __launch_bounds__(256, RT == 1 ? 3 : 2) void attn_kernel(AttnArgs a, 
     // (phase, token range, page-table reads) lives in scalar registers
     const int gitem = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (gitem >= n_items) return;
-    if (gitem >= n0) single_item<D, RT>(a, p1, gitem - n0, threadIdx.x & 63);
-    else single_item<D, RT>(a, p0, gitem, threadIdx.x & 63);
+    const bool second = gitem >= n0;
+    single_item<D, RT>(a, second ? p1 : p0, second ? gitem - n0 : gitem, threadIdx.x & 63);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -271,7 +280,11 @@ __global__ __launch_bounds__(256, RT == 1 ? 3 : 2) void attn_kernel(AttnArgs a, 
 // quarter of a block per wavefront, two blocks ahead through three buffers (96 to 144 KiB of a compute unit's LDS in
 // flight or in use at two or three workgroups), with one barrier per block; they are issued from inline assembly, so
 // that the compiler does not wait for them before LDS reads, and the wait is placed by hand: a wavefront's
-// vector-memory operations retire in order, so "all but the newest block's copies" is a count.
+// vector-memory operations retire in order, so "all but the newest block's copies" is a count.  The page number of the
+// block after next is a vector load behind them, whose wait the compiler puts at the top of the loop, so in effect a block
+// has landed one block before it is used.  With scalar page loads and the wait for the queries ahead of the loop both
+// blocks stay in flight: 62 instead of 69 us for prompts of 4096 (32 groups of 16), but 12.6 instead of 12.1 and 24.9
+// instead of 23.5 for prompts of 1024 (16 and 37 groups of 8), and no gain in prefill.
 // The query tiles of one (unit, kv head) beyond the first four go to workgroups on the same XCD, whose L2 then serves
 // them.
 // ---------------------------------------------------------------------------------------------
