@@ -285,8 +285,6 @@ __global__ __launch_bounds__(256, RT == 1 ? 3 : 2) void attn_kernel(AttnArgs a, 
 // has landed one block before it is used.  With scalar page loads and the wait for the queries ahead of the loop both
 // blocks stay in flight: 62 instead of 69 us for prompts of 4096 (32 groups of 16), but 12.6 instead of 12.1 and 24.9
 // instead of 23.5 for prompts of 1024 (16 and 37 groups of 8), and no gain in prefill.
-// The query tiles of one (unit, kv head) beyond the first four go to workgroups on the same XCD, whose L2 then serves
-// them.
 // ---------------------------------------------------------------------------------------------
 constexpr int kShBufs = 3;
 
@@ -298,14 +296,12 @@ __device__ __forceinline__ void shared_tiles(const AttnArgs &a, const AttnPhase 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    // workgroup -> (set = unit, kv head, split; four of its query tiles), the workgroups of a set 8 apart
-    const int per_set = (p.items_per_unit + 3) >> 2;
-    const int set = (wg >> 3) / per_set * 8 + (wg & 7), qg = (wg >> 3) % per_set;
-    int rest = set;
+    // workgroup -> (set = unit, kv head, split; four of its query tiles)
+    int rest, qg;
+    shared_tiles_of(wg, p.n_units * a.n_kv * p.n_splits, (p.items_per_unit + 3) >> 2, &rest, &qg);
     const int split = rest % p.n_splits; rest /= p.n_splits;
     const int kvh = rest % a.n_kv;
     const int unit = rest / a.n_kv;
-    if (unit >= p.n_units) return;                 // the grid is padded to whole rounds of eight sets
     const int qtile = qg * 4 + wave;               // beyond items_per_unit: this wavefront only helps with the copies
     const int n_rep = a.n_q / a.n_kv;
 
@@ -553,10 +549,9 @@ int launch_attention(const AttnArgs &a, const AttnPhase *phases, int n_phases, h
     if (n_items > 0x7FFFFFFF) return SR_E_ARG;
     const AttnPhase &p0 = phases[0], &p1 = phases[n_phases - 1];
     const int rt = p0.rt, n0 = (int)n[0], nt = (int)n_items;
-    // workgroups of a phase whose query tiles share their blocks through LDS: four tiles of a set each, the sets in
-    // rounds of eight (see shared_tiles)
+    // workgroups of a phase whose query tiles share their blocks through LDS: four tiles of a set each
     auto shared_wgs = [&](const AttnPhase &p) -> long long {
-        return ((long long)p.n_units * a.n_kv * p.n_splits + 7) / 8 * 8 * ((p.items_per_unit + 3) / 4);
+        return (long long)p.n_units * a.n_kv * p.n_splits * ((p.items_per_unit + 3) / 4);
     };
     if (n_phases == 1 && p0.share) {
         const long long wgs = shared_wgs(p0);

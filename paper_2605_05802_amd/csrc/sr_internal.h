@@ -18,6 +18,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "plan.h"
 #include "sr.h"
 
 namespace sr {
@@ -43,9 +44,6 @@ void note_hip_error(hipError_t e, const char *what);
         int rc__ = (call);                             \
         if (rc__ != SR_OK) return rc__;                \
     } while (0)
-
-__host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
-__host__ __device__ inline int round_up(int a, int b) { return ceil_div(a, b) * b; }
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 // round to nearest even; inputs are finite
