@@ -98,7 +98,7 @@ __device__ __forceinline__ void prefix_build(char *lds, const PrefixGeom &q, con
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int e = e0 + u * nt, r = e / KP, c = e % KP;
-            v[u] = r < rows && c < q.L ? (unsigned)src[r * stride + c] : 0u;
+            v[u] = r < rows && c < q.L ? (unsigned)src[(size_t)r * stride + c] : 0u;
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {

@@ -106,3 +106,22 @@ def test_gate_groups_per_workgroup(n_groups, G, lens):
     s_ref, r_ref = oracle.gate_batch(acts, lens, 0.25)
     s_gpu, r_gpu = run_gpu(acts, lens, 0.25)
     assert np.array_equal(s_gpu, s_ref) and np.array_equal(r_gpu, r_ref)
+
+
+def test_rows_further_apart_than_a_32_bit_index_reaches():
+    """The members' rows may lie any distance apart (views into long histories): 16 rows of 143 165 580 entries, 9.2 GB, of
+    which the first eight are looked at; gate and signals."""
+    stride = 143165580                          # 15 * stride > 2^31
+    acts, _ = synth.gate_actions(1, 16, 8, 5, seed=3)
+    s_ref, r_ref = oracle.gate_batch(acts, [8, 3], 0.25)
+    a = torch.empty((1, 16, stride), dtype=torch.int32, device="cuda")
+    a[:, :, :8] = torch.from_numpy(acts).cuda()
+    sums = torch.full((2, 1), -7, dtype=torch.int32, device="cuda")
+    retire = torch.full((2, 1), 9, dtype=torch.uint8, device="cuda")
+    sr.sr_gate_batch(a, [8, 3], 0.25, sums, retire)
+    out = torch.zeros((2, 1, sr.SIGNALS_BYTES), dtype=torch.uint8, device="cuda")
+    sr.sr_signals_batch(a, [8, 3], 0.25, 0.5, out)
+    torch.cuda.synchronize()
+    assert np.array_equal(sums.cpu().numpy(), s_ref) and np.array_equal(retire.cpu().numpy(), r_ref)
+    dtype = np.dtype([(f[0], f[1]) + tuple(f[2:]) for f in sr.SIGNALS_FIELDS], align=True)
+    assert np.array_equal(out.cpu().numpy().view(dtype)[..., 0]["lev_sum"], s_ref)
