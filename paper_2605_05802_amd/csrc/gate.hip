@@ -4,8 +4,8 @@
 // Work decomposition.  One lane owns one of the G(G-1)/2 pairs of a group and runs its whole Levenshtein table in
 // registers, one row at a time with the row as two bit masks (prefix_match.h), so there is no cross-lane traffic in
 // the recurrence.  A workgroup of up to 256 lanes serves whole groups (nine at G = 8); the equality masks come from
-// LDS tables built once per group, and the per-group sums are accumulated with LDS integer atomics, which are
-// order-independent and therefore deterministic.
+// LDS tables built once per group or from comparing in registers, and the per-group sums are accumulated with LDS
+// integer atomics, which are order-independent and therefore deterministic.
 //
 // Prefix nesting: cell (k,k) of the table of two length-L sequences is the distance of their length-k prefixes, so one
 // table serves every requested prefix length.
@@ -13,6 +13,7 @@
 // Bound: vector ALU (about 65 % busy, 530 instructions per wavefront: 180 of them the recurrence) with the LDS latency of
 // the table build behind it; the 64 MB of input would be 12 us.  65 536 groups of 8, prefixes 5, 10 and 15: 41 us (62 with
 // symbols beyond the table's range), 72 us with one table cell at a time in registers; at 32 steps 120 against 284 us.
+// Groups of 5, 12 steps: 14 us by comparison, 24 one cell at a time; groups of 16, one step: 44 against 61.
 #include "prefix_match.h"
 
 namespace sr {
@@ -33,7 +34,7 @@ __device__ __forceinline__ unsigned min3u(unsigned a, unsigned b, unsigned c) {
     return min(a, min(b, c));
 }
 
-template <int KMAX>
+template <int KMAX, bool DIRECT>
 __global__ __launch_bounds__(kGateThreads) void gate_kernel(
     const int32_t *__restrict__ actions, int n_groups, int stride, int pairs, PrefixGeom q, GateLens lens,
     int32_t *__restrict__ sums, uint8_t *__restrict__ retire) {
@@ -43,9 +44,11 @@ __global__ __launch_bounds__(kGateThreads) void gate_kernel(
     const int tid = threadIdx.x, G = q.G;
     const int g0 = blockIdx.x * q.groups;
     const int n_here = min(q.groups, n_groups - g0);
-    const PrefixLds off = prefix_lds(q, q.groups, KMAX);
+    const PrefixLds off = prefix_lds(q, q.groups, KMAX, DIRECT);
     for (int i = tid; i < q.groups; i += blockDim.x) s_sum[0][i] = s_sum[1][i] = s_sum[2][i] = s_sum[3][i] = 0;
-    prefix_build<KMAX>(lds, q, off, n_here * G, actions + (size_t)g0 * G * stride, stride);
+    const int32_t *src = actions + (size_t)g0 * G * stride;
+    if constexpr (DIRECT) prefix_stage<KMAX>(lds, q, n_here * G, src, stride);
+    else prefix_build<KMAX>(lds, q, off, n_here * G, src, stride);
 
     const int gl = (int)(((float)tid + 0.5f) * (1.0f / (float)pairs));     // group within the block
     if (gl < n_here) {
@@ -54,13 +57,22 @@ __global__ __launch_bounds__(kGateThreads) void gate_kernel(
         unsigned wanted = 0;                          // bit k: prefix length k + 1 is asked for
         for (int l = 0; l < lens.n; ++l) wanted |= 1u << (lens.len[l] - 1);
         unsigned pv = 0xFFFFFFFFu, mv = 0, res[4] = {0, 0, 0, 0};
+        constexpr int STEP = KMAX % 8 ? 4 : 8;        // rows at a time
+        int32_t b[DIRECT ? KMAX : 4];
+        if constexpr (DIRECT) prefix_symbols<KMAX>(lds, gl * G + j, 0, b);
 #pragma unroll
-        for (int r0 = 0; r0 < KMAX; r0 += 8) {
+        for (int r0 = 0; r0 < KMAX; r0 += STEP) {
             if (r0 < q.L) {                           // uniform
-                unsigned eq[8];
-                prefix_masks8<KMAX>(lds, q, off, gl * G + i, gl * G + j, r0, eq);
+                unsigned eq[STEP];
+                if constexpr (DIRECT) {
+                    int32_t a[STEP];
+                    prefix_symbols<KMAX>(lds, gl * G + i, r0, a);
+                    prefix_equal<KMAX>(a, b, eq);
+                } else {
+                    prefix_masks8<KMAX>(lds, q, off, gl * G + i, gl * G + j, r0, eq);
+                }
 #pragma unroll
-                for (int t = 0; t < 8; ++t) {
+                for (int t = 0; t < STEP; ++t) {
                     prefix_row(eq[t], pv, mv);
                     if ((wanted >> (r0 + t)) & 1u) {  // uniform
                         const unsigned d = (unsigned)prefix_cell(r0 + t + 1, r0 + t + 1, pv, mv);
@@ -179,17 +191,23 @@ int launch_gate(const int32_t *actions, int n_groups, int G, int stride, const G
     int maxlen = 0;
     for (int l = 0; l < lens.n; ++l) maxlen = lens.len[l] > maxlen ? lens.len[l] : maxlen;
     const int pairs = G * (G - 1) / 2;
-    const int kmax = maxlen <= 8 ? 8 : maxlen <= 16 ? 16 : maxlen <= 24 ? 24 : 32;
+    const bool direct = prefix_direct(n_groups, G, maxlen, 6);
+    const int kmax = maxlen <= 4 ? 4 : maxlen <= 8 ? 8 : maxlen <= 12 && direct ? 12 : maxlen <= 16 ? 16 : maxlen <= 24 ? 24 : 32;
     PrefixGeom q{};
-    if (!prefix_geometry(n_groups, G, maxlen, kmax, kGateLds, 0, &q)) return SR_E_ARG;
-    const size_t lds = prefix_lds(q, q.groups, kmax).total;
+    if (!prefix_geometry(n_groups, G, maxlen, kmax, direct, kGateLds, 0, &q)) return SR_E_ARG;
+    const size_t lds = prefix_lds(q, q.groups, kmax, direct).total;
     dim3 grid((n_groups + q.groups - 1) / q.groups), block(q.threads);
-    switch (kmax) {
-        case 8:  gate_kernel<8><<<grid, block, lds, stream>>>(actions, n_groups, stride, pairs, q, lens, sums, retire); break;
-        case 16: gate_kernel<16><<<grid, block, lds, stream>>>(actions, n_groups, stride, pairs, q, lens, sums, retire); break;
-        case 24: gate_kernel<24><<<grid, block, lds, stream>>>(actions, n_groups, stride, pairs, q, lens, sums, retire); break;
-        default: gate_kernel<32><<<grid, block, lds, stream>>>(actions, n_groups, stride, pairs, q, lens, sums, retire); break;
+#define SR_GATE(K, DIRECT) \
+    gate_kernel<K, DIRECT><<<grid, block, lds, stream>>>(actions, n_groups, stride, pairs, q, lens, sums, retire)
+    switch (kmax) {                       // up to eight steps there are no tables
+        case 4: SR_GATE(4, true); break;
+        case 8: SR_GATE(8, true); break;
+        case 12: SR_GATE(12, true); break;
+        case 16: if (direct) SR_GATE(16, true); else SR_GATE(16, false); break;
+        case 24: if (direct) SR_GATE(24, true); else SR_GATE(24, false); break;
+        default: if (direct) SR_GATE(32, true); else SR_GATE(32, false); break;
     }
+#undef SR_GATE
     SR_HIP(hipGetLastError());
     return SR_OK;
 }

@@ -6,18 +6,20 @@
 // column u + 1; information only moves from lower to higher bits, so cell (r, c) can be read for every c whatever
 // the columns beyond it hold, and one pass serves every prefix length.
 //
-// What the recurrence needs per row is the mask of positions of b that equal a[r].  A workgroup builds, once per group,
-// the table mask[member][symbol]; a row's mask is then one LDS read, and the 2 * K * K compare instructions per pair
-// that building it lane by lane costs are gone.  Symbols that all lie in the table's range index it as they are (ids
-// below 64 always do: action ids of a turn are tokens modulo a small number).  Where some symbol of the workgroup does
-// not, every symbol is first replaced by the index of one element of its group that holds it (hash insertion in
-// LDS, compare-and-swap on the slot; which of several equal elements wins does not matter).
+// What the recurrence needs per row is the mask of positions of b that equal a[r].  Two ways to have it:
+// Tables.  A workgroup builds, once per group, the table mask[member][symbol]; a row's mask is then one LDS read.  Symbols
+// that all lie in the table's range index it as they are (ids below 64 always do: action ids of a turn are tokens modulo a
+// small number).  Where some symbol of the workgroup does not, every symbol is first replaced by the index of one element
+// of its group that holds it (hash insertion in LDS, compare-and-swap on the slot; which of several equal elements
+// wins does not matter).
+// Comparison.  Every pair compares its 2 * K symbols in registers: 2 * K * K more instructions per pair, and nothing to build.
+// prefix_direct says which.
 #pragma once
 #include "sr_internal.h"
 
 namespace sr {
 
-// Sizes of one workgroup's tables; L = longest requested prefix, KMAX = its size class (8, 16, 24 or 32).
+// Sizes of one workgroup's tables; L = longest requested prefix, KMAX = its size class (4, 8, 12, 16, 24 or 32).
 struct PrefixGeom {
     int G, L;
     int slots_log2;       // hash slots per group: a power of two, at least twice its elements
@@ -27,12 +29,18 @@ struct PrefixGeom {
 };
 
 __host__ __device__ inline int prefix_mask_bytes(int kmax) { return kmax <= 16 ? 2 : 4; }
-// byte offsets of [masks | slots | act | id] for n groups; every part a multiple of 16 bytes
+// row of the directly compared symbols: an odd multiple of 16 bytes, the rows of sixteen consecutive members in different banks
+__host__ __device__ constexpr int prefix_act_stride(int kmax) { return kmax % 8 == 4 ? kmax : kmax + 4; }
+// byte offsets of [masks | slots | act | id] for n groups, or of act alone; every part a multiple of 16 bytes
 struct PrefixLds {
     int slots, act, id, total;
 };
-__host__ __device__ inline PrefixLds prefix_lds(const PrefixGeom &q, int n, int kmax) {
-    PrefixLds o;
+__host__ __device__ inline PrefixLds prefix_lds(const PrefixGeom &q, int n, int kmax, bool direct) {
+    PrefixLds o{};
+    if (direct) {
+        o.total = n * q.G * prefix_act_stride(kmax) * 4;
+        return o;
+    }
     o.slots = round_up(n * q.G * q.row_stride * prefix_mask_bytes(kmax), 16);
     o.act = o.slots + (n << q.slots_log2) * 4;
     o.id = o.act + round_up(n * q.G * q.L * 4, 16);
@@ -40,10 +48,20 @@ __host__ __device__ inline PrefixLds prefix_lds(const PrefixGeom &q, int n, int 
     return o;
 }
 
+// Compare, or build tables?  Up to eight steps the comparisons cost less than zeroing and filling a table, for every group size
+// (65 536 groups of 8, 5 steps: gate 17.6 us; with tables 18.7, 26 where symbols lie beyond their range; 3 members: 7.8, 8.3 and
+// 19).  Longer prefixes share a table among G - 1 pairs: up to `few` members comparing is cheaper still where the groups
+// fill the chip (65 536 groups of 5, 12 steps: gate 14 us, tables 17 and 29; groups of 3: signals 18, tables 28 and 38; 8
+// members: gate 41 against 33), and a long chain in too few wavefronts where they do not (64 groups of 3, 32 steps:
+// gate 10.0 us, tables 7.7; 16 384 groups of 2: 8.8 and 7.8).
+inline bool prefix_direct(int n_groups, int G, int L, int few) {
+    return L <= 8 || (G <= few && (long long)n_groups * G >= 1500LL * L);
+}
+
 // Groups per workgroup: the count that fills whole wavefronts of pair lanes best (28 pairs: nine groups leave 4 of 256
 // lanes idle) within 256 lanes and `lds_limit` bytes of tables plus `extra` bytes per group.  A few groups (an episode's
 // gate) are spread over the compute units first: no workgroup takes more than its share of 512.
-inline bool prefix_geometry(int n_groups, int G, int L, int kmax, int lds_limit, int extra, PrefixGeom *q) {
+inline bool prefix_geometry(int n_groups, int G, int L, int kmax, bool direct, int lds_limit, int extra, PrefixGeom *q) {
     const int pairs = G * (G - 1) / 2;
     q->G = G;
     q->L = L;
@@ -54,7 +72,7 @@ inline bool prefix_geometry(int n_groups, int G, int L, int kmax, int lds_limit,
     q->groups = 0;
     double best = 0.0;
     for (int n = 1; n * pairs <= 256 && n <= ceil_div(n_groups, 512); ++n) {
-        if (prefix_lds(*q, n, kmax).total + n * extra > lds_limit) break;
+        if (prefix_lds(*q, n, kmax, direct).total + n * extra > lds_limit) break;
         const double use = (double)(n * pairs) / round_up(n * pairs, 64);
         if (use >= best) {
             best = use;
@@ -79,7 +97,7 @@ __device__ __forceinline__ int small_div(int x, float inv) { return (int)(((floa
 template <int KMAX>
 __device__ __forceinline__ void prefix_build(char *lds, const PrefixGeom &q, const PrefixLds &off, int rows,
                                              const int32_t *__restrict__ src, int stride) {
-    constexpr int KP = KMAX <= 8 ? 8 : KMAX <= 16 ? 16 : 32;     // lanes per member
+    constexpr int KP = KMAX <= 16 ? 16 : 32;                     // lanes per member
     unsigned *masks = (unsigned *)lds;
     uint16_t *id = (uint16_t *)(lds + off.id);
     int32_t *act = (int32_t *)(lds + off.act);
@@ -127,11 +145,6 @@ __device__ __forceinline__ void prefix_build(char *lds, const PrefixGeom &q, con
         const int32_t *ga = act + g * GL;
         const unsigned mine = (unsigned)((r - g * q.G) * q.L + c) + 1u;      // element within the group; 0 = free slot
         unsigned rep = mine;
-        if (GL <= 16) {                              // a handful of elements: the first equal one, by looking at them all
-            for (int k = GL - 1; k >= 0; --k) rep = ga[k] == v ? (unsigned)k + 1u : rep;
-            mark(r, c, rep - 1u);
-            continue;
-        }
         unsigned h = ((unsigned)v * 0x9E3779B1u) >> (32 - q.slots_log2);
         for (unsigned probe = 0; probe <= wrap; ++probe) {                   // at most half of the slots are ever taken
             const unsigned old = atomicCAS(&table[h], 0u, mine);
@@ -142,6 +155,66 @@ __device__ __forceinline__ void prefix_build(char *lds, const PrefixGeom &q, con
         mark(r, c, rep - 1u);
     }
     __syncthreads();
+}
+
+// Without tables: the symbols of `rows` members as they are, [row][prefix_act_stride].  Entries from L on hold anything: they
+// only reach bits and rows that nobody reads.  Ends with a barrier.
+template <int KMAX>
+__device__ __forceinline__ void prefix_stage(char *lds, const PrefixGeom &q, int rows, const int32_t *__restrict__ src, int stride) {
+    constexpr int KP = KMAX <= 8 ? KMAX : KMAX <= 16 ? 16 : 32;  // lanes per member
+    int32_t *act = (int32_t *)lds;
+    const int nt = blockDim.x;
+    for (int e0 = threadIdx.x; e0 < rows * KP; e0 += 4 * nt) {   // four loads in flight per lane
+        int32_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int e = e0 + u * nt, r = e / KP, c = e % KP;
+            v[u] = r < rows && c < q.L ? src[(size_t)r * stride + c] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int e = e0 + u * nt, r = e / KP, c = e % KP;
+            if (r < rows && c < q.L) act[r * prefix_act_stride(KMAX) + c] = v[u];
+        }
+    }
+    __syncthreads();
+}
+
+// a member's staged symbols c0 .. c0 + N - 1 (multiples of four)
+template <int KMAX, int N>
+__device__ __forceinline__ void prefix_symbols(const char *lds, int row, int c0, int32_t (&x)[N]) {
+    const int4 *p = (const int4 *)((const int32_t *)lds + row * prefix_act_stride(KMAX) + c0);
+#pragma unroll
+    for (int i = 0; i < N / 4; ++i) {
+        const int4 v = p[i];
+        x[4 * i] = v.x; x[4 * i + 1] = v.y; x[4 * i + 2] = v.z; x[4 * i + 3] = v.w;
+    }
+}
+
+// m[i] = positions of b that hold a[i], for N symbols (a multiple of four): a compare and an add with carry (m = 2 m + equal)
+// per symbol and position.  Four symbols take turns in one asm block, because a vector instruction may read a compare's
+// scalar result only two instructions later; left to the compiler the same sum took two more instructions and a wait each.
+template <int KMAX, int N>
+__device__ __forceinline__ void prefix_equal(const int32_t (&a)[N], const int32_t (&b)[KMAX], unsigned (&m)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; i += 4) {
+        unsigned m0 = 0, m1 = 0, m2 = 0, m3 = 0;
+#pragma unroll
+        for (int c = KMAX - 1; c >= 0; --c) {
+            unsigned long long t0, t1, t2, t3;
+            asm("v_cmp_eq_u32_e64 %4, %8, %12\n\t"
+                "v_cmp_eq_u32_e64 %5, %9, %12\n\t"
+                "v_cmp_eq_u32_e64 %6, %10, %12\n\t"
+                "v_cmp_eq_u32_e64 %7, %11, %12\n\t"
+                "v_addc_co_u32_e64 %0, %4, %0, %0, %4\n\t"
+                "v_addc_co_u32_e64 %1, %5, %1, %1, %5\n\t"
+                "v_addc_co_u32_e64 %2, %6, %2, %2, %6\n\t"
+                "v_addc_co_u32_e64 %3, %7, %3, %3, %7"
+                : "+v"(m0), "+v"(m1), "+v"(m2), "+v"(m3), "=&s"(t0), "=&s"(t1), "=&s"(t2), "=&s"(t3)
+                : "v"(a[i]), "v"(a[i + 1]), "v"(a[i + 2]), "v"(a[i + 3]), "v"(b[c]));
+        }
+        m[i] = m0; m[i + 1] = m1; m[i + 2] = m2; m[i + 3] = m3;
+    }
 }
 
 // positions of member `row` that hold the symbol `id`

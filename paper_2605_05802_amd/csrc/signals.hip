@@ -21,7 +21,10 @@
 // scheduling.
 // Bound: vector ALU (70 % busy).  65 536 groups of 8 with early finishers, K = 5, 10, 15: 126 us; 361 us with one table cell
 // at a time, K * K compares per pair for the bigrams and the quotients left to the thread of a (K, group).  At 32 steps
-// 272 against 1266 us, at G = 16 and 16 steps 112 against 990 us (16 384 groups).
+// 272 against 1266 us, at G = 16 and 16 steps 112 against 990 us (16 384 groups).  Groups of 3, 12 steps, symbols compared in
+// registers: 18 against 33 us.
+#include <type_traits>
+
 #include "prefix_match.h"
 
 static_assert(sizeof(sr_signals_t) == 64, "sr_signals_t is part of the C boundary");
@@ -31,7 +34,7 @@ namespace {
 
 constexpr int kSigThreads = 256;
 constexpr int kSigLds = 52 * 1024;                   // three workgroups per compute unit where the shape allows it
-constexpr int kSigLdsMost = 64 * 1024;               // G = 16 with 32 steps and 8 prefix lengths needs 62 KiB
+constexpr int kSigLdsMost = 64 * 1024;               // G = 16 with 32 steps and 8 prefix lengths needs 58.6 KiB
 constexpr int kSigMaxLens = 8;
 constexpr long long kLcm32 = 144403552893600LL;      // lcm(1..32)
 
@@ -63,7 +66,7 @@ __host__ __device__ inline SigLds sig_lds(int G, int pairs, int groups, int n_le
     return o;
 }
 
-template <int KMAX>
+template <int KMAX, bool DIRECT>
 __global__ __launch_bounds__(kSigThreads) void signals_kernel(
     const int32_t *__restrict__ actions, const int32_t *__restrict__ obs, const int32_t *__restrict__ end_step,
     int n_groups, int stride, int pairs, PrefixGeom q, SigLens lens, sr_signals_t *__restrict__ out) {
@@ -73,7 +76,7 @@ __global__ __launch_bounds__(kSigThreads) void signals_kernel(
     const int g0 = blockIdx.x * q.groups;
     const int n_here = min(q.groups, n_groups - g0);
     const int rows = n_here * G, n_pairs = q.groups * pairs, n_rows = q.groups * G;
-    const PrefixLds off = prefix_lds(q, q.groups, KMAX);
+    const PrefixLds off = prefix_lds(q, q.groups, KMAX, DIRECT);
     const SigLds so = sig_lds(G, pairs, q.groups, NL);
     char *mine = lds + off.total;
     sr_signals_t *s_out = (sr_signals_t *)(mine + so.out);
@@ -92,22 +95,40 @@ __global__ __launch_bounds__(kSigThreads) void signals_kernel(
         const int l = min((int)(((float)w + 0.5f) * inv_rows), NL - 1), r = w - l * rows;
         s_obs[l * n_rows + r] = obs ? obs[((size_t)g0 * G + r) * stride + lens.len[l] - 1] : 0;
     }
-    prefix_build<KMAX>(lds, q, off, rows, actions + (size_t)g0 * G * stride, stride);
-    const uint16_t *ids = (const uint16_t *)(lds + off.id);
+    const int32_t *src = actions + (size_t)g0 * G * stride;
+    if constexpr (DIRECT) prefix_stage<KMAX>(lds, q, rows, src, stride);
+    else prefix_build<KMAX>(lds, q, off, rows, src, stride);
+    // what stands for a member's step: its symbol, or the element of the group that represents it
+    using Step = std::conditional_t<DIRECT, int32_t, uint16_t>;
+    constexpr int SS = DIRECT ? prefix_act_stride(KMAX) : KMAX;
+    const Step *steps = (const Step *)(lds + (DIRECT ? off.act : off.id));
 
-    // One lane per (member, position): is it the first occurrence of its bigram?  A member's lanes are neighbours, so
-    // the wavefront's vote holds the members' masks side by side.
-    constexpr int KP = KMAX <= 8 ? 8 : KMAX <= 16 ? 16 : 32;
-    for (int e0 = 0; e0 < rows * KP; e0 += nt) {             // whole wavefronts take part
-        const int e = e0 + tid, r = e / KP, t = e % KP;
-        bool first = false;
-        if (r < rows && t + 1 < q.L) {
-            const unsigned here = prefix_mask<KMAX>(lds, q, r, ids[r * KMAX + t]);
-            const unsigned next = prefix_mask<KMAX>(lds, q, r, ids[r * KMAX + t + 1]);
-            first = (here & (next >> 1) & low_bits(t)) == 0u;
+    if constexpr (DIRECT) {
+        // One lane per member: the positions that are the first occurrence of their bigram
+        for (int r = tid; r < rows; r += nt) {
+            int32_t b[KMAX];
+            prefix_symbols<KMAX>(lds, r, 0, b);
+            unsigned eq[KMAX], first = 0;
+            prefix_equal<KMAX>(b, b, eq);
+#pragma unroll
+            for (int t = 0; t + 1 < KMAX; ++t) first |= (eq[t] & (eq[t + 1] >> 1) & low_bits(t)) == 0u ? 1u << t : 0u;
+            s_first[r] = first & low_bits(q.L - 1);
         }
-        const unsigned long long vote = __ballot(first);
-        if (t == 0 && r < rows) s_first[r] = (unsigned)(vote >> (tid & 63)) & low_bits(KP);
+    } else {
+        // One lane per (member, position): is it the first occurrence of its bigram?  A member's lanes are neighbours, so
+        // the wavefront's vote holds the members' masks side by side.
+        constexpr int KP = KMAX <= 16 ? 16 : 32;
+        for (int e0 = 0; e0 < rows * KP; e0 += nt) {             // whole wavefronts take part
+            const int e = e0 + tid, r = e / KP, t = e % KP;
+            bool first = false;
+            if (r < rows && t + 1 < q.L) {
+                const unsigned here = prefix_mask<KMAX>(lds, q, r, steps[r * SS + t]);
+                const unsigned next = prefix_mask<KMAX>(lds, q, r, steps[r * SS + t + 1]);
+                first = (here & (next >> 1) & low_bits(t)) == 0u;
+            }
+            const unsigned long long vote = __ballot(first);
+            if (t == 0 && r < rows) s_first[r] = (unsigned)(vote >> (tid & 63)) & low_bits(KP);
+        }
     }
     // One lane per (member, K): members that reach step K, and whether this one is the first to hold its action or
     // observation
@@ -115,13 +136,13 @@ __global__ __launch_bounds__(kSigThreads) void signals_kernel(
         const int l = min((int)(((float)w + 0.5f) * inv_rows), NL - 1), r = w - l * rows, g = small_div(r, inv_G), K = lens.len[l];
         int hold = s_end[r] <= K ? 128 : 0;
         if (s_end[r] >= K) {
-            const unsigned a = ids[r * KMAX + K - 1];
+            const unsigned a = steps[r * SS + K - 1];
             const int32_t o = s_obs[l * n_rows + r];
             int n_at = 0, count = 0;
             bool first_act = true, first_obs = true;
 #pragma unroll 4
             for (int i = g * G; i < g * G + G; ++i) {
-                const bool at = s_end[i] >= K, same = at & (ids[i * KMAX + K - 1] == a);
+                const bool at = s_end[i] >= K, same = at & ((unsigned)steps[i * SS + K - 1] == a);
                 n_at += at ? 1 : 0;
                 count += same ? 1 : 0;
                 first_act &= !((i < r) & same);
@@ -149,11 +170,19 @@ __global__ __launch_bounds__(kSigThreads) void signals_kernel(
 
         unsigned pv = 0xFFFFFFFFu, mv = 0, pv_end = 0xFFFFFFFFu, mv_end = 0;      // row 0: distance from the empty prefix
         unsigned big[KMAX], eq_last = 0;              // big[t]: positions of b that hold bigram t of a
+        int32_t b[DIRECT ? KMAX : 4];
+        if constexpr (DIRECT) prefix_symbols<KMAX>(lds, rj, 0, b);
 #pragma unroll
         for (int r0 = 0; r0 < KMAX; r0 += 8) {
             unsigned eq[8];
             if (r0 < q.L) {                           // uniform
-                prefix_masks8<KMAX>(lds, q, off, ri, rj, r0, eq);
+                if constexpr (DIRECT) {
+                    int32_t a[8];
+                    prefix_symbols<KMAX>(lds, ri, r0, a);
+                    prefix_equal<KMAX>(a, b, eq);
+                } else {
+                    prefix_masks8<KMAX>(lds, q, off, ri, rj, r0, eq);
+                }
 #pragma unroll
                 for (int t = 0; t < 8; ++t) {
                     const int r = r0 + t + 1;
@@ -329,22 +358,26 @@ extern "C" int sr_signals_batch(const int32_t *actions, const int32_t *obs, cons
     lens.tau_num = (long long)__builtin_llround(tau_H * 1e6);
     if (n_groups == 0) return SR_OK;
     const int pairs = G * (G - 1) / 2;
+    const bool direct = prefix_direct(n_groups, G, maxlen, 3);
     const int kmax = maxlen <= 8 ? 8 : maxlen <= 16 ? 16 : maxlen <= 24 ? 24 : 32;
     for (int n = 1; n <= 32; ++n) lens.lcm_over[n] = kLcm32 / n;
     PrefixGeom q{};
     const int extra = sig_lds(G, pairs, 1, n_lens).total;
-    if (!prefix_geometry(n_groups, G, maxlen, kmax, kSigLds, extra, &q) &&
-        !prefix_geometry(n_groups, G, maxlen, kmax, kSigLdsMost, extra, &q))
+    if (!prefix_geometry(n_groups, G, maxlen, kmax, direct, kSigLds, extra, &q) &&
+        !prefix_geometry(n_groups, G, maxlen, kmax, direct, kSigLdsMost, extra, &q))
         return SR_E_ARG;
-    const size_t lds = prefix_lds(q, q.groups, kmax).total + (size_t)sig_lds(G, pairs, q.groups, n_lens).total;
+    const size_t lds = prefix_lds(q, q.groups, kmax, direct).total + (size_t)sig_lds(G, pairs, q.groups, n_lens).total;
     dim3 grid((n_groups + q.groups - 1) / q.groups), block(q.threads);
     hipStream_t st = (hipStream_t)stream;
-    switch (kmax) {
-        case 8:  signals_kernel<8><<<grid, block, lds, st>>>(actions, obs, end_step, n_groups, stride, pairs, q, lens, out); break;
-        case 16: signals_kernel<16><<<grid, block, lds, st>>>(actions, obs, end_step, n_groups, stride, pairs, q, lens, out); break;
-        case 24: signals_kernel<24><<<grid, block, lds, st>>>(actions, obs, end_step, n_groups, stride, pairs, q, lens, out); break;
-        default: signals_kernel<32><<<grid, block, lds, st>>>(actions, obs, end_step, n_groups, stride, pairs, q, lens, out); break;
+#define SR_SIG(K, DIRECT) \
+    signals_kernel<K, DIRECT><<<grid, block, lds, st>>>(actions, obs, end_step, n_groups, stride, pairs, q, lens, out)
+    switch (kmax) {                       // up to eight steps there are no tables
+        case 8: SR_SIG(8, true); break;
+        case 16: if (direct) SR_SIG(16, true); else SR_SIG(16, false); break;
+        case 24: if (direct) SR_SIG(24, true); else SR_SIG(24, false); break;
+        default: if (direct) SR_SIG(32, true); else SR_SIG(32, false); break;
     }
+#undef SR_SIG
     SR_HIP(hipGetLastError());
     return SR_OK;
 }

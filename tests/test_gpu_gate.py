@@ -125,3 +125,16 @@ def test_rows_further_apart_than_a_32_bit_index_reaches():
     assert np.array_equal(sums.cpu().numpy(), s_ref) and np.array_equal(retire.cpu().numpy(), r_ref)
     dtype = np.dtype([(f[0], f[1]) + tuple(f[2:]) for f in sr.SIGNALS_FIELDS], align=True)
     assert np.array_equal(out.cpu().numpy().view(dtype)[..., 0]["lev_sum"], s_ref)
+
+
+@pytest.mark.parametrize("n_groups,G,lens", [(24001, 2, [32, 31]), (16001, 3, [30, 1]), (9001, 4, [24, 9]), (4801, 5, [16, 3]),
+                                             (3001, 6, [12, 11]), (2251, 6, [9]), (777, 16, [8, 5]), (1025, 16, [4, 1]),
+                                             (513, 7, [3]), (1, 2, [1])])
+def test_gate_by_comparison(n_groups, G, lens):
+    """The symbols compared in registers: the smallest group counts of each size class that take it, prefixes at both ends of a
+    class, a ragged last workgroup, symbols at both ends of the 32-bit range."""
+    acts, _ = synth.gate_actions(n_groups, G, max(lens) + 1, 6, seed=n_groups)
+    acts = np.array([0, -1, 1, -2 ** 31, 2 ** 31 - 1, 0x01000000], dtype=np.int32)[acts]
+    s_ref, r_ref = oracle.gate_batch(acts, lens, 0.25)
+    s_gpu, r_gpu = run_gpu(acts, lens, 0.25)
+    assert np.array_equal(s_gpu, s_ref) and np.array_equal(r_gpu, r_ref)

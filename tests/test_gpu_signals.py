@@ -116,3 +116,14 @@ def test_signals_groups_per_workgroup(n_groups, G, lens):
     end[::7, 0] = 0
     end[::11, :2] = 0
     check(acts, lens, d_L=0.25, tau_H=0.5, obs=obs, end=end)
+
+
+@pytest.mark.parametrize("n_groups,G,lens", [(24001, 2, [32, 2]), (16001, 3, [30, 31, 1]), (12001, 3, [24, 17]), (6001, 3, [9, 12]),
+                                             (1025, 16, [8, 1, 2, 3, 4, 5, 6, 7]), (2049, 8, [5])])
+def test_signals_by_comparison(n_groups, G, lens):
+    """The symbols compared in registers: both ends of each size class, members that finish before the first step."""
+    acts, obs, end = make(n_groups, G, max(lens), 4, seed=n_groups)
+    acts = np.array([0, -1, 2 ** 31 - 1, -2 ** 31], dtype=np.int32)[acts]
+    end[::7, 0] = 0
+    end[::11, :2] = 0
+    check(acts, lens, d_L=0.25, tau_H=0.5, obs=obs, end=end)
