@@ -34,7 +34,6 @@ struct LayerW {
     uint16_t *bq = nullptr, *bk = nullptr, *bv = nullptr, *norm1 = nullptr, *norm2 = nullptr;
 };
 
-constexpr int kMaxSplitK = 16;
 constexpr int kScoreRows = 256;          // scoring through stored logits: rows of the LM head computed at a time
 constexpr int kMaxAttnSplits = 16;
 
@@ -224,43 +223,6 @@ int timed(sr_ctx *c, int kc, hipStream_t st, F &&launch) {
     SR_HIP(hipEventRecord(ev[1], st));
     c->prof.push_back({kc, ev[0], ev[1]});
     return rc;
-}
-
-// Projections of up to kStreamRows rows go to the weight-streaming kernel.  The number of computing wavefronts per
-// workgroup (32 features each) is picked so that the matrix breaks into about 256 workgroups.
-constexpr int kStreamRows = 256;
-int stream_waves(int M, int N, int ks_total, bool swiglu) {
-    if (M > kStreamRows) return 0;
-    // Thin (QKV, O, down): split along K so that about one workgroup per CU is in flight -- more than that only adds
-    // partial-sum traffic.  Shallow ones take two computing wavefronts, which gives enough workgroups with three or four K
-    // splits instead of seven: the projection itself takes the same time (13.9 against 13.0 us, 11.4 against 11.8 us at
-    // the 7B shape) and the kernel that adds the partial sums reads half as many.
-    if (!swiglu && N < 8192) return ks_total < 256 ? 2 : 4;
-    // Otherwise whole rounds of workgroups on 256 CUs cost what a workgroup is wide: the width with the least work in
-    // them, the widest of equals.  gate|up at the 7B shape (37 888 packed rows): 237 workgroups of 160 features; LM head
-    // (152 064): 476 of 320 in two rounds (594 of 256 in three: 246 against 226 us); 16 384 rows: 256 of 64 features, 20
-    // against 41 us with 64 of 256 at 8 rows, 33 against 56 at 128; 1376 rows (FFN 688): 3.7 against 7.9 us with 128
-    // features at 32 rows.
-    int best = 2, least = 0;
-    for (int w : {10, 8, 5, 4, 2}) {
-        if (w >= 8 && M > 128) continue;             // not enough registers for more than four row tiles
-        const int work = ceil_div(ceil_div(N, 32 * w), 256) * w;
-        if (least == 0 || work < least) { least = work; best = w; }
-    }
-    return best;
-}
-
-// K splits of the weight-streaming kernel
-int pick_splits(int M, int N, int ks_total) {
-    const int n_blocks = ceil_div(N, 32 * stream_waves(M, N, ks_total, false));
-    const int target = 256 / n_blocks;
-    if (target <= 1) return 1;
-    const int units = ks_total / 8;                 // a split covers whole groups of 8 k-steps
-    const int ups = ceil_div(units, target);        // units per split at the target count ...
-    int s = ceil_div(units, ups);                   // ... and the fewest splits that keep it
-    if (s > kMaxSplitK) s = kMaxSplitK;
-    if (M > 128 && s > units / 4) s = units / 4;    // a short inner dimension is not worth twice the partial sums
-    return s < 1 ? 1 : s;
 }
 
 void plan_packed(AllocPlan &plan, PackedMat *m, int n_rows, int K) {

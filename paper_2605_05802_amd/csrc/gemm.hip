@@ -176,7 +176,6 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a) {
 // features) whose operands they share through that XCD's L2, and no XCD has more than one tile above its share.
 // ---------------------------------------------------------------------------------------------
 constexpr int kPfThreads = 512;
-constexpr int kPfBufs = 4;                 // k-steps in LDS
 constexpr int pf_tiles(int nt, int rt) { return 2 * nt + 4 * rt; }      // 1 KiB tiles per k-step: W, then X
 constexpr int pf_lds_bytes(int nt, int rt) { return kPfBufs * pf_tiles(nt, rt) * 1024; }
 
@@ -746,54 +745,7 @@ int launch_mid(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream) {
     return SR_OK;
 }
 
-// More than 256 rows: which kernel, and how many K splits.  Times in us, from launches of the 7B shape's projections at
-// 8192, 5120, 4096, 2048, 1280, 768, 512 and 296 rows; k = K / 3584.
-//   64 RT x 32 NT tiles, one to a CU: a round takes 2.33 RT (NT + 1.5) k.  O at 4096 rows 86 (NT = 7) and 88 (8), QKV at
-//     8192 rows 186 (6, three rounds), 202 (7, three), 207 (5, four) and 212 (8, three), O at 5120 rows 126 (5), 142 (6),
-//     155 (7) and 165 (8), two rounds each.  Every shape is looked at: what decides is how full the last round is.
-//   128 x 128 tiles, two to a CU: 39 k up to 256 of them, 60 k up to 473; then 0.095 k a tile and 15 above 1024 rows (W read
-//     through L2 by many row blocks), 0.166 k a tile up to there.
-//   All rows in one workgroup of 160 features, up to 512 rows: 108 k a round up to 384 rows, 139 k up to 512.  Only for
-//     matrices of 16 384 rows and more, where it makes a round of workgroups.
-//   S splits divide k, cost a fixed 6 and S times the output, written here and read by the next kernel, at 4.5 TB/s.
-struct TileShape { int nt, rt; };
-constexpr TileShape kTileShapes[] = {{8, 4}, {7, 4}, {6, 4}, {5, 4}, {6, 5}, {5, 5}, {4, 5}, {4, 6}};      // {5, 6} and up spill
-enum { KERNEL_128 = -2, KERNEL_MID = -1 };             // otherwise an index into kTileShapes
-
-struct GemmPlan { int kernel, splits; };
-// splits: 0 = choose up to max_splits, otherwise given
-GemmPlan plan_gemm(int M, int N, int ks_total, int mt_total, bool swiglu, int splits, int max_splits) {
-    const double k = ks_total / 112.0;
-    const long long t128 = (long long)ceil_div(M, 128) * ceil_div(N, 128);
-    const int s_lo = splits ? splits : 1;
-    int s_hi = splits ? splits : max_splits;
-    if (!splits && s_hi > ks_total / 32) s_hi = ks_total / 32;         // at least 32 k-steps each: filling the pipeline is not free
-    GemmPlan best{KERNEL_128, s_lo};
-    double least = 0.0;
-    for (int S = s_lo; S == s_lo || S <= s_hi; ++S) {
-        const double more = (swiglu ? 0.0 : 8.0e-6 / 4.5 * S * M * N) + (S > 1 ? 6.0 : 0.0);
-        auto offer = [&](int kernel, double us) {
-            if (least == 0.0 || us + more < least) { least = us + more; best = GemmPlan{kernel, S}; }
-        };
-        const long long n128 = t128 * S;
-        offer(KERNEL_128, k / S * (n128 <= 256 ? 39.0 : n128 < 474 ? 60.0 : M > 1024 ? 0.095 * n128 + 15.0 : 0.166 * n128));
-        for (int i = 0; i < (int)(sizeof kTileShapes / sizeof kTileShapes[0]); ++i) {
-            const int nt = kTileShapes[i].nt, rt = kTileShapes[i].rt, mb = ceil_div(M, 64 * rt);
-            if ((swiglu && nt != 8 && nt != 6) || mb * 4 * rt > mt_total || S > ks_total / kPfBufs) continue;
-            const long long rounds = ((long long)mb * ceil_div(N, 32 * nt) * S + 255) / 256;
-            offer(i, rounds * 2.33 * rt * (nt + 1.5) * k / S);
-        }
-        if (S == 1 && M <= 512 && N >= 16384)
-            offer(KERNEL_MID, k * ceil_div(ceil_div(N, 160), 256) * (M <= 384 ? 108.0 : 139.0));
-    }
-    return best;
-}
-
 }  // namespace
-
-int gemm_splits(int M, int N, int ks_total, int mt_total, int max_splits) {
-    return plan_gemm(M, N, ks_total, mt_total, false, 0, max_splits).splits;
-}
 
 int launch_gemm(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream) {
     if (a.M <= 0) return SR_OK;

@@ -23,4 +23,103 @@ SR_HD inline void shared_tiles_of(int wg, int n_sets, int per_set, int *set, int
     *part = t < 0 ? (wg >> 3) % per_set : t % per_set;
 }
 
+// ---------------------------------------------------------------------------------------------
+// projections
+// ---------------------------------------------------------------------------------------------
+// k-steps [*k0, *k1) of split sp when `units` groups of `unit` k-steps are dealt out evenly
+SR_HD inline void split_range(int ks_total, int unit, int splits, int sp, int *k0, int *k1) {
+    const int units = ks_total / unit, q = units / splits, r = units % splits;
+    const int u0 = sp * q + (sp < r ? sp : r);
+    *k0 = u0 * unit;
+    *k1 = (u0 + q + (sp < r ? 1 : 0)) * unit;
+}
+
+constexpr int kMaxSplitK = 16;
+constexpr int kPfBufs = 4;                 // k-steps in the LDS of the tiled kernel for more than 256 rows
+
+// Projections of up to kStreamRows rows go to the weight-streaming kernel.  The number of computing wavefronts per
+// workgroup (32 features each) is picked so that the matrix breaks into about 256 workgroups.
+constexpr int kStreamRows = 256;
+inline int stream_waves(int M, int N, int ks_total, bool swiglu) {
+    if (M > kStreamRows) return 0;
+    // Thin (QKV, O, down): split along K so that about one workgroup per CU is in flight -- more than that only adds
+    // partial-sum traffic.  Shallow ones take two computing wavefronts, which gives enough workgroups with three or four K
+    // splits instead of seven: the projection itself takes the same time (13.9 against 13.0 us, 11.4 against 11.8 us at
+    // the 7B shape) and the kernel that adds the partial sums reads half as many.
+    if (!swiglu && N < 8192) return ks_total < 256 ? 2 : 4;
+    // Otherwise whole rounds of workgroups on 256 CUs cost what a workgroup is wide: the width with the least work in
+    // them, the widest of equals.  gate|up at the 7B shape (37 888 packed rows): 237 workgroups of 160 features; LM head
+    // (152 064): 476 of 320 in two rounds (594 of 256 in three: 246 against 226 us); 16 384 rows: 256 of 64 features, 20
+    // against 41 us with 64 of 256 at 8 rows, 33 against 56 at 128; 1376 rows (FFN 688): 3.7 against 7.9 us with 128
+    // features at 32 rows.
+    int best = 2, least = 0;
+    for (int w : {10, 8, 5, 4, 2}) {
+        if (w >= 8 && M > 128) continue;             // not enough registers for more than four row tiles
+        const int work = ceil_div(ceil_div(N, 32 * w), 256) * w;
+        if (least == 0 || work < least) { least = work; best = w; }
+    }
+    return best;
+}
+
+// K splits of the weight-streaming kernel
+inline int pick_splits(int M, int N, int ks_total) {
+    const int n_blocks = ceil_div(N, 32 * stream_waves(M, N, ks_total, false));
+    const int target = 256 / n_blocks;
+    if (target <= 1) return 1;
+    const int units = ks_total / 8;                 // a split covers whole groups of 8 k-steps
+    const int ups = ceil_div(units, target);        // units per split at the target count ...
+    int s = ceil_div(units, ups);                   // ... and the fewest splits that keep it
+    if (s > kMaxSplitK) s = kMaxSplitK;
+    if (M > 128 && s > units / 4) s = units / 4;    // a short inner dimension is not worth twice the partial sums
+    return s < 1 ? 1 : s;
+}
+
+// More than 256 rows: which kernel, and how many K splits.  Times in us, from launches of the 7B shape's projections at
+// 8192, 5120, 4096, 2048, 1280, 768, 512 and 296 rows; k = K / 3584.
+//   64 RT x 32 NT tiles, one to a CU: a round takes 2.33 RT (NT + 1.5) k.  O at 4096 rows 86 (NT = 7) and 88 (8), QKV at
+//     8192 rows 186 (6, three rounds), 202 (7, three), 207 (5, four) and 212 (8, three), O at 5120 rows 126 (5), 142 (6),
+//     155 (7) and 165 (8), two rounds each.  Every shape is looked at: what decides is how full the last round is.
+//   128 x 128 tiles, two to a CU: 39 k up to 256 of them, 60 k up to 473; then 0.095 k a tile and 15 above 1024 rows (W read
+//     through L2 by many row blocks), 0.166 k a tile up to there.
+//   All rows in one workgroup of 160 features, up to 512 rows: 108 k a round up to 384 rows, 139 k up to 512.  Only for
+//     matrices of 16 384 rows and more, where it makes a round of workgroups.
+//   S splits divide k, cost a fixed 6 and S times the output, written here and read by the next kernel, at 4.5 TB/s.
+struct TileShape { int nt, rt; };
+constexpr TileShape kTileShapes[] = {{8, 4}, {7, 4}, {6, 4}, {5, 4}, {6, 5}, {5, 5}, {4, 5}, {4, 6}};      // {5, 6} and up spill
+enum { KERNEL_128 = -2, KERNEL_MID = -1 };             // otherwise an index into kTileShapes
+
+struct GemmPlan { int kernel, splits; };
+// splits: 0 = choose up to max_splits, otherwise given
+inline GemmPlan plan_gemm(int M, int N, int ks_total, int mt_total, bool swiglu, int splits, int max_splits) {
+    const double k = ks_total / 112.0;
+    const long long t128 = (long long)ceil_div(M, 128) * ceil_div(N, 128);
+    const int s_lo = splits ? splits : 1;
+    int s_hi = splits ? splits : max_splits;
+    if (!splits && s_hi > ks_total / 32) s_hi = ks_total / 32;         // at least 32 k-steps each: filling the pipeline is not free
+    GemmPlan best{KERNEL_128, s_lo};
+    double least = 0.0;
+    for (int S = s_lo; S == s_lo || S <= s_hi; ++S) {
+        const double more = (swiglu ? 0.0 : 8.0e-6 / 4.5 * S * M * N) + (S > 1 ? 6.0 : 0.0);
+        auto offer = [&](int kernel, double us) {
+            if (least == 0.0 || us + more < least) { least = us + more; best = GemmPlan{kernel, S}; }
+        };
+        const long long n128 = t128 * S;
+        offer(KERNEL_128, k / S * (n128 <= 256 ? 39.0 : n128 < 474 ? 60.0 : M > 1024 ? 0.095 * n128 + 15.0 : 0.166 * n128));
+        for (int i = 0; i < (int)(sizeof kTileShapes / sizeof kTileShapes[0]); ++i) {
+            const int nt = kTileShapes[i].nt, rt = kTileShapes[i].rt, mb = ceil_div(M, 64 * rt);
+            if ((swiglu && nt != 8 && nt != 6) || mb * 4 * rt > mt_total || S > ks_total / kPfBufs) continue;
+            const long long rounds = ((long long)mb * ceil_div(N, 32 * nt) * S + 255) / 256;
+            offer(i, rounds * 2.33 * rt * (nt + 1.5) * k / S);
+        }
+        if (S == 1 && M <= 512 && N >= 16384)
+            offer(KERNEL_MID, k * ceil_div(ceil_div(N, 160), 256) * (M <= 384 ? 108.0 : 139.0));
+    }
+    return best;
+}
+
+// K splits (fp32 output) of a projection of more than 256 rows, at most max_splits
+inline int gemm_splits(int M, int N, int ks_total, int mt_total, int max_splits) {
+    return plan_gemm(M, N, ks_total, mt_total, false, 0, max_splits).splits;
+}
+
 }  // namespace sr

@@ -150,15 +150,6 @@ struct ScoreOut {
     int rows_per_unit;
 };
 
-// k-steps [*k0, *k1) of split sp when `units` groups of `unit` k-steps are dealt out evenly
-__device__ __forceinline__ void split_range(int ks_total, int unit, int splits, int sp, int *k0, int *k1) {
-    const int units = ks_total / unit, q = units / splits, r = units % splits;
-    const int u0 = sp * q + min(sp, r);
-    *k0 = u0 * unit;
-    *k1 = (u0 + q + (sp < r ? 1 : 0)) * unit;
-}
-
-
 struct GemmArgs {
     const uint4 *X;
     const uint4 *W;
@@ -177,8 +168,6 @@ struct GemmArgs {
 // The weight-streaming kernel with a loader wavefront (a.wide != 0, M <= 256); launch_gemm dispatches to it.
 int launch_gemm_stream(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream);
 int launch_gemm(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream);
-// K splits (EPI_F32) of a projection of more than 256 rows, at most max_splits
-int gemm_splits(int M, int N, int ks_total, int mt_total, int max_splits);
 
 // ---------------------------------------------------------------------------------------------
 // element-wise kernels
