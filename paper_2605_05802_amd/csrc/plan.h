@@ -1,6 +1,7 @@
 // Host-side rules that decide how work is laid out over the chip, in plain C++ so that they can be evaluated (and tested)
 // without a GPU or the HIP headers; kernels use the parts marked SR_HD.
 #pragma once
+#include <initializer_list>
 
 #ifdef __HIPCC__
 #define SR_HD __host__ __device__
