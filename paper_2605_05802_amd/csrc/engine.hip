@@ -400,7 +400,7 @@ struct Pass {
 // single-precision debugging path)
 int choose_splits(sr_ctx *c, int M, const PackedMat &W, int ld_out, int *splits, size_t *split_stride) {
     *split_stride = (size_t)round_up(M, 128) * ld_out;
-    *splits = M > kStreamRows ? gemm_splits(M, W.N, W.ks, c->mt_total, kMaxSplitK) : pick_splits(M, W.N, W.ks);
+    *splits = projection_splits(M, W.N, W.ks, c->mt_total);
     if (M > 128)                                     // larger batches may split only as far as the buffer allows
         while (*splits > 1 && *split_stride * *splits > c->partial_elems) --*splits;
     if (*split_stride * *splits > c->partial_elems) return SR_E_ARG;

@@ -38,11 +38,17 @@ SR_HD inline void split_range(int ks_total, int unit, int splits, int sp, int *k
 constexpr int kMaxSplitK = 16;
 constexpr int kPfBufs = 4;                 // k-steps in the LDS of the tiled kernel for more than 256 rows
 
-// Projections of up to kStreamRows rows go to the weight-streaming kernel.  The number of computing wavefronts per
-// workgroup (32 features each) is picked so that the matrix breaks into about 256 workgroups.
-constexpr int kStreamRows = 256;
+// Projections of up to kStreamRows rows go to the weight-streaming kernel, except that above kStreamThinRows rows small
+// matrices (up to 8192 rows and 16 MB) stay on the tiled kernels: with seven or eight row tiles a k-step of the streaming
+// kernel costs more than one of 128 x 128 tiles, and there is little weight to stream (256 rows, K = 1024: QKV 16.5 against
+// 15.1 us, O 15.5 against 14.1, gate|up 17.1 against 14.2; at 192 rows they are even, at 160 streaming is 10 % faster).
+// Larger matrices stream: at K = 3584 the whole decode step of 224 rows takes 255 us, 267 with tiles for its thin ones.
+constexpr int kStreamRows = 256, kStreamThinRows = 192;
+inline bool small_matrix(int N, int ks_total) { return N <= 8192 && (long long)N * ks_total * 64 <= 16 << 20; }
+// The number of computing wavefronts per workgroup (32 features each) is picked so that the matrix breaks into about 256
+// workgroups; 0 = a tiled kernel.
 inline int stream_waves(int M, int N, int ks_total, bool swiglu) {
-    if (M > kStreamRows) return 0;
+    if (M > kStreamRows || (M > kStreamThinRows && small_matrix(N, ks_total))) return 0;
     // Thin (QKV, O, down): split along K so that about one workgroup per CU is in flight -- more than that only adds
     // partial-sum traffic.  Shallow ones take two computing wavefronts, which gives enough workgroups with three or four K
     // splits instead of seven: the projection itself takes the same time (13.9 against 13.0 us, 11.4 against 11.8 us at
@@ -62,9 +68,9 @@ inline int stream_waves(int M, int N, int ks_total, bool swiglu) {
     return best;
 }
 
-// K splits of the weight-streaming kernel
+// K splits up to kStreamRows rows, whichever kernel it is
 inline int pick_splits(int M, int N, int ks_total) {
-    const int n_blocks = ceil_div(N, 32 * stream_waves(M, N, ks_total, false));
+    const int n_blocks = ceil_div(N, 32 * stream_waves(M < kStreamThinRows ? M : kStreamThinRows, N, ks_total, false));
     const int target = 256 / n_blocks;
     if (target <= 1) return 1;
     const int units = ks_total / 8;                 // a split covers whole groups of 8 k-steps
@@ -75,7 +81,7 @@ inline int pick_splits(int M, int N, int ks_total) {
     return s < 1 ? 1 : s;
 }
 
-// More than 256 rows: which kernel, and how many K splits.  Times in us, from launches of the 7B shape's projections at
+// The tiled kernels: which one, and how many K splits.  Times in us, from launches of the 7B shape's projections at
 // 8192, 5120, 4096, 2048, 1280, 768, 512 and 296 rows; k = K / 3584.
 //   64 RT x 32 NT tiles, one to a CU: a round takes 2.33 RT (NT + 1.5) k.  O at 4096 rows 86 (NT = 7) and 88 (8), QKV at
 //     8192 rows 186 (6, three rounds), 202 (7, three), 207 (5, four) and 212 (8, three), O at 5120 rows 126 (5), 142 (6),
@@ -118,9 +124,9 @@ inline GemmPlan plan_gemm(int M, int N, int ks_total, int mt_total, bool swiglu,
     return best;
 }
 
-// K splits (fp32 output) of a projection of more than 256 rows, at most max_splits
-inline int gemm_splits(int M, int N, int ks_total, int mt_total, int max_splits) {
-    return plan_gemm(M, N, ks_total, mt_total, false, 0, max_splits).splits;
+// K splits of a projection whose partial sums another kernel adds (fp32 output)
+inline int projection_splits(int M, int N, int ks_total, int mt_total) {
+    return M <= kStreamRows ? pick_splits(M, N, ks_total) : plan_gemm(M, N, ks_total, mt_total, false, 0, kMaxSplitK).splits;
 }
 
 }  // namespace sr

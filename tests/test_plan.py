@@ -13,6 +13,8 @@ extern "C" {
 void shared_tiles(int n_sets, int per_set, int *set, int *part) {
     for (int wg = 0; wg < n_sets * per_set; ++wg) sr::shared_tiles_of(wg, n_sets, per_set, set + wg, part + wg);
 }
+int stream_waves(int M, int N, int ks, int swiglu) { return sr::stream_waves(M, N, ks, swiglu); }
+int projection_splits(int M, int N, int ks, int mt_total) { return sr::projection_splits(M, N, ks, mt_total); }
 }
 """
 
@@ -41,3 +43,14 @@ def test_shared_query_tiles_use_every_xcd(plan, n_sets, per_set):
         if s[wg] < n_sets // 8 * 8:
             assert home.setdefault(s[wg], wg % 8) == wg % 8
     assert max(load) <= -(-n // 8)
+
+
+@pytest.mark.parametrize("M", [1, 128, 129, 192, 193, 256, 257])
+def test_small_matrices_leave_the_streaming_kernel_at_193_rows(plan, M):
+    """Matrices of up to 16 MB lost 10 % on the streaming kernel at 193 to 256 rows; larger ones gain up to half."""
+    for N, ks, swiglu in ((3072, 32, 0), (1024, 32, 0), (5632, 32, 1), (8192, 16, 1), (8192, 32, 0), (512, 256, 0)):
+        assert (plan.stream_waves(M, N, ks, swiglu) == 0) == (M > 192)
+    for N, ks, swiglu in ((16384, 112, 0), (37888, 112, 1), (8208, 16, 0), (3584, 592, 0), (4608, 112, 0)):
+        assert (plan.stream_waves(M, N, ks, swiglu) == 0) == (M > 256)
+    for N, ks in ((3584, 592), (3072, 32), (512, 256)):
+        assert 1 <= plan.projection_splits(M, N, ks, 512) <= 16
