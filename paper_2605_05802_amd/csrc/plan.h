@@ -54,16 +54,19 @@ inline int stream_waves(int M, int N, int ks_total, bool swiglu) {
     // splits instead of seven: the projection itself takes the same time (13.9 against 13.0 us, 11.4 against 11.8 us at
     // the 7B shape) and the kernel that adds the partial sums reads half as many.
     if (!swiglu && N < 8192) return ks_total < 256 ? 2 : 4;
-    // Otherwise whole rounds of workgroups on 256 CUs cost what a workgroup is wide: the width with the least work in
-    // them, the widest of equals.  gate|up at the 7B shape (37 888 packed rows): 237 workgroups of 160 features; LM head
-    // (152 064): 476 of 320 in two rounds (594 of 256 in three: 246 against 226 us); 16 384 rows: 256 of 64 features, 20
-    // against 41 us with 64 of 256 at 8 rows, 33 against 56 at 128; 1376 rows (FFN 688): 3.7 against 7.9 us with 128
-    // features at 32 rows.
+    // Otherwise: the width w with the cheapest rounds of workgroups on 256 CUs, the widest of equals.  A round costs w and a
+    // part that does not depend on it, which grows with the rows (the activations' way through LDS): 0.5 up to 32 rows, 1 up
+    // to 64, 4 beyond, in halves below; at K = 3584 a round of w = 2, 4, 5, 8, 10 takes 22, 40, 49, 77, 96 us at 8 rows and 34,
+    // 49, 60, 89, 109 at 128.  gate|up at the 7B shape (37 888 packed rows): 237 workgroups of 160 features; LM head (152 064):
+    // 476 of 320 in two rounds (594 of 256 in three: 246 against 226 us); 49 152 rows at 128: 192 of 256 features, 77 us, 99
+    // with 768 of 64 in three rounds; 106 496: 416 of 256, 164 us, 212 with 64; 16 384 rows: 256 of 64 features, 20 against
+    // 41 us with 64 of 256 at 8 rows, 33 against 56 at 128.
     int best = 2, least = 0;
+    const int fixed = M <= 32 ? 1 : M <= 64 ? 2 : 8;
     for (int w : {10, 8, 5, 4, 2}) {
         if (w >= 8 && M > 128) continue;             // not enough registers for more than four row tiles
-        const int work = ceil_div(ceil_div(N, 32 * w), 256) * w;
-        if (least == 0 || work < least) { least = work; best = w; }
+        const int cost = ceil_div(ceil_div(N, 32 * w), 256) * (2 * w + fixed);
+        if (least == 0 || cost < least) { least = cost; best = w; }
     }
     return best;
 }

@@ -54,3 +54,11 @@ def test_small_matrices_leave_the_streaming_kernel_at_193_rows(plan, M):
         assert (plan.stream_waves(M, N, ks, swiglu) == 0) == (M > 256)
     for N, ks in ((3584, 592), (3072, 32), (512, 256)):
         assert 1 <= plan.projection_splits(M, N, ks, 512) <= 16
+
+
+@pytest.mark.parametrize("N,M,waves", [(49152, 128, 8), (45056, 64, 8), (106496, 128, 8), (114688, 64, 8), (65536, 8, 8), (98304, 8, 4),
+                                       (152064, 128, 10), (152064, 8, 10), (81920, 128, 10), (37888, 128, 5), (37888, 160, 5),
+                                       (16384, 8, 2), (16384, 128, 2), (32768, 128, 4), (106496, 160, 5), (49152, 160, 4)])
+def test_workgroup_widths_of_wide_matrices(plan, N, M, waves):
+    """The widths measured best or within a few per cent of it: a round of narrow workgroups is not proportionally cheaper."""
+    assert plan.stream_waves(M, N, 112, 0) == waves
