@@ -85,12 +85,14 @@ inline int pick_splits(int M, int N, int ks_total) {
 }
 
 // The tiled kernels: which one, and how many K splits.  Times in us, from launches of the 7B shape's projections at
-// 8192, 5120, 4096, 2048, 1280, 768, 512 and 296 rows; k = K / 3584.
+// 8192, 5120, 4096, 2048, 1280, 768, 512 and 296 rows; k = K / 3584.  A launch has about 3 us of its own, the same for all.
 //   64 RT x 32 NT tiles, one to a CU: a round takes 2.33 RT (NT + 1.5) k.  O at 4096 rows 86 (NT = 7) and 88 (8), QKV at
 //     8192 rows 186 (6, three rounds), 202 (7, three), 207 (5, four) and 212 (8, three), O at 5120 rows 126 (5), 142 (6),
 //     155 (7) and 165 (8), two rounds each.  Every shape is looked at: what decides is how full the last round is.
-//   128 x 128 tiles, two to a CU: 39 k up to 256 of them, 60 k up to 473; then 0.095 k a tile and 15 above 1024 rows (W read
-//     through L2 by many row blocks), 0.166 k a tile up to there.
+//   128 x 128 tiles, two to a CU: 39 k up to 256 of them and 60 k up to 512 (16 384 matrix rows at 512 rows: 24.1 us at K = 1024,
+//     {6, 4} 27.1; 38.8 and 42.6 at 2048); then 0.166 k a tile up to 1024 rows, and above 0.095 k a tile and 15 k (W read
+//     through L2 by many row blocks), from 16 384 matrix rows on, which no L2 holds, 0.137 k (22 016 rows, K = 4096: 541 us
+//     at 2560 rows and 658 at 3072, where tiles of {6, 5} and {6, 4} take 349 and 458).
 //   All rows in one workgroup of 160 features, up to 512 rows: 108 k a round up to 384 rows, 139 k up to 512.  Only for
 //     matrices of 16 384 rows and more, where it makes a round of workgroups.
 //   S splits divide k, cost a fixed 6 and S times the output, written here and read by the next kernel, at 4.5 TB/s.
@@ -114,7 +116,9 @@ inline GemmPlan plan_gemm(int M, int N, int ks_total, int mt_total, bool swiglu,
             if (least == 0.0 || us + more < least) { least = us + more; best = GemmPlan{kernel, S}; }
         };
         const long long n128 = t128 * S;
-        offer(KERNEL_128, k / S * (n128 <= 256 ? 39.0 : n128 < 474 ? 60.0 : M > 1024 ? 0.095 * n128 + 15.0 : 0.166 * n128));
+        const double t128_us = n128 <= 256 ? 39.0 : n128 <= (M > 1024 ? 473 : 512) ? 60.0 : M <= 1024 ? 0.166 * n128
+                               : (N < 16384 ? 0.095 : 0.137) * n128 + 15.0;
+        offer(KERNEL_128, k / S * t128_us);
         for (int i = 0; i < (int)(sizeof kTileShapes / sizeof kTileShapes[0]); ++i) {
             const int nt = kTileShapes[i].nt, rt = kTileShapes[i].rt, mb = ceil_div(M, 64 * rt);
             if ((swiglu && nt != 8 && nt != 6) || mb * 4 * rt > mt_total || S > ks_total / kPfBufs) continue;

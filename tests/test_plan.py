@@ -14,6 +14,9 @@ void shared_tiles(int n_sets, int per_set, int *set, int *part) {
     for (int wg = 0; wg < n_sets * per_set; ++wg) sr::shared_tiles_of(wg, n_sets, per_set, set + wg, part + wg);
 }
 int stream_waves(int M, int N, int ks, int swiglu) { return sr::stream_waves(M, N, ks, swiglu); }
+int plan_kernel(int M, int N, int ks, int mt_total, int swiglu, int splits) {
+    return sr::plan_gemm(M, N, ks, mt_total, swiglu, splits, 16).kernel;
+}
 int projection_splits(int M, int N, int ks, int mt_total) { return sr::projection_splits(M, N, ks, mt_total); }
 }
 """
@@ -62,3 +65,14 @@ def test_small_matrices_leave_the_streaming_kernel_at_193_rows(plan, M):
 def test_workgroup_widths_of_wide_matrices(plan, N, M, waves):
     """The widths measured best or within a few per cent of it: a round of narrow workgroups is not proportionally cheaper."""
     assert plan.stream_waves(M, N, 112, 0) == waves
+
+
+def test_tiled_kernel_choice_of_wide_matrices(plan):
+    """More than 1024 rows against 16 384 matrix rows or more: never the 128 x 128 tiles (658 us where others took 458).  512 such
+    tiles are one round of two to a CU: 8192 and 16 384 matrix rows at 1024 and 512 rows take them."""
+    for ks in (16, 64, 112, 128, 352):
+        for N in (16384, 22016, 37888):
+            for M in range(1025, 8193, 41):
+                assert plan.plan_kernel(M, N, ks, 512, 1, 1) != -2
+    for ks in (16, 32, 64):
+        assert plan.plan_kernel(1024, 8192, ks, 512, 1, 1) == -2 and plan.plan_kernel(512, 16384, ks, 512, 1, 1) == -2
