@@ -26,7 +26,7 @@ __global__ __launch_bounds__(256) void dbg_gemm_kernel(DbgGemmArgs a) {
     const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
     const int n0 = blockIdx.x * kTile, m0 = blockIdx.y * kTile, sp = blockIdx.z;
     int ks0, ks1;
-    split_range(a.ks_total, 8, a.splits, sp, &ks0, &ks1);
+    split_range(a.ks_total, a.split_steps, a.splits, sp, &ks0, &ks1);
 
     float acc[4][4];
 #pragma unroll

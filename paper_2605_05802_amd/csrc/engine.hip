@@ -444,6 +444,7 @@ int gemm32(sr_ctx *c, const float *X, int K, const PackedMat &W, int M, GemmEpil
         SR_TRY(choose_splits(c, M, W, ld_out, &a.splits, &a.split_stride));
         *splits_out = a.splits;
     }
+    a.split_steps = split_steps(M, W.N, W.ks, c->mt_total, a.splits);
     return launch_dbg_gemm(a, epi, st);
 }
 

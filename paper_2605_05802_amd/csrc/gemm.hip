@@ -13,7 +13,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
 constexpr int kKC = 4;                    // k-steps (of 32) per LDS chunk of X
-constexpr int kPF = 8;                    // k-steps of W held in registers ahead of the MFMAs (two X chunks)
 constexpr int kChunkVec = kKC * 512;      // uint4 per chunk: 8 row tiles x 64 lanes per k-step
 
 // 128 x 128 tiles, two workgroups per CU.  Each wavefront reads its 32 output features as two contiguous runs with

@@ -36,7 +36,9 @@ SR_HD inline void split_range(int ks_total, int unit, int splits, int sp, int *k
 }
 
 constexpr int kMaxSplitK = 16;
-constexpr int kPfBufs = 4;                 // k-steps in the LDS of the tiled kernel for more than 256 rows
+// k-steps that a kernel's splits cover a multiple of: kPfBufs (its LDS buffers) where tiles of kTileShapes run, kPF (the
+// k-steps of W it holds in registers) in the other kernels
+constexpr int kPfBufs = 4, kPF = 8;
 
 // Projections of up to kStreamRows rows go to the weight-streaming kernel, except that above kStreamThinRows rows small
 // matrices (up to 8192 rows and 16 MB) stay on the tiled kernels: with seven or eight row tiles a k-step of the streaming
@@ -131,6 +133,11 @@ inline GemmPlan plan_gemm(int M, int N, int ks_total, int mt_total, bool swiglu,
     return best;
 }
 
+// What split_range deals out at a time in the kernel that a projection with these splits runs on
+inline int split_steps(int M, int N, int ks_total, int mt_total, int splits) {
+    if (splits == 1 || stream_waves(M, N, ks_total, false)) return kPF;
+    return plan_gemm(M, N, ks_total, mt_total, false, splits, splits).kernel >= 0 ? kPfBufs : kPF;
+}
 // K splits of a projection whose partial sums another kernel adds (fp32 output)
 inline int projection_splits(int M, int N, int ks_total, int mt_total) {
     return M <= kStreamRows ? pick_splits(M, N, ks_total) : plan_gemm(M, N, ks_total, mt_total, false, 0, kMaxSplitK).splits;

@@ -293,6 +293,7 @@ struct DbgGemmArgs {
     int ldx;                 // = K, the valid inner dimension
     const uint16_t *W;
     int M, N, ks_total, splits;
+    int split_steps;         // dealing unit of the K splits: that of the kernel the normal path runs (plan.h)
     float *out;
     int ld_out;
     size_t split_stride;

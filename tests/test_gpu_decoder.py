@@ -603,13 +603,14 @@ def test_members_finish_early_in_a_batch_of_several_hundred_rows():
     assert stats["n_live_seq"] > 128
 
 
-@pytest.mark.parametrize("case", ["tiny", "cow", "g16", "edge", "finishers", "mid"])
+@pytest.mark.parametrize("case", ["tiny", "cow", "g16", "edge", "finishers", "mid", "deep"])
 def test_single_precision_debug_path(case):
     """sr_options.fp32_debug: fp32 activations, fp32 K/V pages and plain multiply-adds behind the same paging,
     splits, merges and compaction.  Logits within 1e-4 of the exact evaluation, tokens identical under the gap
     rule, gate and live maps exact -- on an episode with a gate, on a prompt that ends inside a page (copy on
     write of fp32 pages), on G = 16 with two gates, on widths that do not fill a tile, on groups that lose single
-    members, and on a batch of several hundred rows (tiled projections with K splits)."""
+    members, on a batch of several hundred rows (tiled projections with K splits), and on 512 rows against a deep matrix
+    (twelve K splits of uneven length)."""
     kw = dict(fp32_debug=True)
     if case == "tiny":
         shape, cfg, seed = synth.TINY, synth.TINY_EPISODE, 0
@@ -626,6 +627,9 @@ def test_single_precision_debug_path(case):
         rng = np.random.default_rng(7)
         ends = np.where(rng.random(48) < 0.45, rng.integers(1, 7, 48), 10 ** 6)
         kw.update(finish_fn=lambda K, r: ends[r] == K, tau_H=0.5)
+    elif case == "deep":
+        shape, cfg, seed = synth.ModelShape(1, 1504, 4, 2, 64, 12304, 512), synth.EpisodeConfig("deep", 64, 8, 4, 1, 2, 1, 64, (), 0.3, 0.0), 61
+        kw.update(page_tokens=32, kv_pool_bytes=1 << 28)
     else:
         shape, cfg, seed = synth.ModelShape(1, 256, 4, 2, 64, 16896, 1024), synth.EpisodeConfig("mid", 64, 8, 16, 2, 2, 2, 64, (1,), 0.3, 0.4), 4
     rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed, **kw)

@@ -17,6 +17,7 @@ int stream_waves(int M, int N, int ks, int swiglu) { return sr::stream_waves(M, 
 int plan_kernel(int M, int N, int ks, int mt_total, int swiglu, int splits) {
     return sr::plan_gemm(M, N, ks, mt_total, swiglu, splits, 16).kernel;
 }
+int split_steps(int M, int N, int ks, int mt_total, int splits) { return sr::split_steps(M, N, ks, mt_total, splits); }
 int projection_splits(int M, int N, int ks, int mt_total) { return sr::projection_splits(M, N, ks, mt_total); }
 }
 """
@@ -76,3 +77,16 @@ def test_tiled_kernel_choice_of_wide_matrices(plan):
                 assert plan.plan_kernel(M, N, ks, 512, 1, 1) != -2
     for ks in (16, 32, 64):
         assert plan.plan_kernel(1024, 8192, ks, 512, 1, 1) == -2 and plan.plan_kernel(512, 16384, ks, 512, 1, 1) == -2
+
+
+def test_debug_path_deals_k_out_like_the_kernel_it_mirrors(plan):
+    """The single-precision debugging path covers the same k-step ranges per split as the kernel that the normal path runs: tiles
+    deal out four k-steps at a time, the streaming kernel and the 128 x 128 tiles eight."""
+    tiled = 0
+    for M in (64, 136, 224, 257, 296, 384, 512, 600, 768, 1536, 2048):
+        for N, ks in ((3584, 592), (1504, 400), (1024, 592), (2048, 352), (3584, 112)):
+            s = plan.projection_splits(M, N, ks, 512)
+            on_tiles = s > 1 and plan.stream_waves(M, N, ks, 0) == 0 and plan.plan_kernel(M, N, ks, 512, 0, s) >= 0
+            assert plan.split_steps(M, N, ks, 512, s) == (4 if on_tiles else 8)
+            tiled += on_tiles and (ks // 8) % s != 0       # the two units give different ranges
+    assert tiled >= 3
