@@ -363,7 +363,9 @@ __device__ __forceinline__ void shared_tiles(const AttnArgs &a, const AttnPhase 
         copy(1, page_of(1), 1);
         int page = page_of(2), buf = 0;
         for (int blk = 0; blk < n_blocks; ++blk) {
-            __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * SEGS));      // this wavefront's part of block blk has landed
+            // this wavefront's part of block blk has landed, and its LDS reads of block blk - 1, whose buffer the copies below
+            // overwrite, are back (lgkmcnt; by now they always are: MFMAs took them)
+            __builtin_amdgcn_s_waitcnt(0x0070 | (2 * SEGS));
             asm volatile("" ::: "memory");
             __builtin_amdgcn_s_barrier();                         // ... and everybody's; nobody reads block blk - 1 any more
             asm volatile("" ::: "memory");

@@ -373,18 +373,19 @@ constexpr int kMidXBufs = 3, kMidWBufs = 6;                        // k-steps of
 constexpr int kMidXVec = kMidXTiles * 64, kMidWVec = kMidWTiles * 64;       // u32x4 per k-step: 32 KiB and 10 KiB
 constexpr int kMidLdsBytes = (kMidXBufs * kMidXVec + kMidWBufs * kMidWVec) * 16;   // 156 KiB
 
-// wait until at most n of this wavefront's vector-memory operations are outstanding (n uniform, 0..8)
+// wait until at most n of this wavefront's vector-memory operations are outstanding (n uniform, 0..8) and its LDS reads are
+// back: the buffers they came from are overwritten behind the barrier that follows
 __device__ __forceinline__ void wait_vm_at_most(int n) {
     switch (n) {
-        case 0: __builtin_amdgcn_s_waitcnt(0x0F70); break;
-        case 1: __builtin_amdgcn_s_waitcnt(0x0F71); break;
-        case 2: __builtin_amdgcn_s_waitcnt(0x0F72); break;
-        case 3: __builtin_amdgcn_s_waitcnt(0x0F73); break;
-        case 4: __builtin_amdgcn_s_waitcnt(0x0F74); break;
-        case 5: __builtin_amdgcn_s_waitcnt(0x0F75); break;
-        case 6: __builtin_amdgcn_s_waitcnt(0x0F76); break;
-        case 7: __builtin_amdgcn_s_waitcnt(0x0F77); break;
-        default: __builtin_amdgcn_s_waitcnt(0x0F78); break;
+        case 0: __builtin_amdgcn_s_waitcnt(0x0070); break;
+        case 1: __builtin_amdgcn_s_waitcnt(0x0071); break;
+        case 2: __builtin_amdgcn_s_waitcnt(0x0072); break;
+        case 3: __builtin_amdgcn_s_waitcnt(0x0073); break;
+        case 4: __builtin_amdgcn_s_waitcnt(0x0074); break;
+        case 5: __builtin_amdgcn_s_waitcnt(0x0075); break;
+        case 6: __builtin_amdgcn_s_waitcnt(0x0076); break;
+        case 7: __builtin_amdgcn_s_waitcnt(0x0077); break;
+        default: __builtin_amdgcn_s_waitcnt(0x0078); break;
     }
 }
 

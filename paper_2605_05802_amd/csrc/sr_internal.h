@@ -85,6 +85,8 @@ __device__ __forceinline__ float row_sum(float x) {
 // ---------------------------------------------------------------------------------------------
 // One wavefront copies 64 x 16 bytes: lane i's from g, to lds_byte_offset + 16 i.  Neither the compiler's wait counts nor
 // its alias analysis see the copy: the caller counts it (one vector-memory operation) and waits for it by hand.
+// m0, which the copies set, is reserved and cannot be named as clobbered: their kernels use nothing else that reads it (the
+// builtin for such copies, indexed register moves, messages).
 __device__ __forceinline__ void lds_dma16(const void *g, unsigned lds_byte_offset) {
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds_byte_offset) : "memory");
 }

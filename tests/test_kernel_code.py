@@ -28,3 +28,17 @@ def test_block_loop_keeps_its_fragments_in_flight(attention_asm, kernel):
     assert loops
     for block in loops:
         assert "global_load" in block and "vmcnt(0)" not in block
+
+
+@pytest.mark.parametrize("kernel", ["attn_prefill_shared_kernelILi64ELi1E", "attn_prefill_shared_kernelILi64ELi2E",
+                                    "attn_prefill_shared_kernelILi128ELi1E", "attn_prefill_shared_kernelILi128ELi2E",
+                                    "attn_decode_kernelILi64E", "attn_decode_kernelILi128E"])
+def test_shared_blocks_are_read_before_they_are_overwritten(attention_asm, kernel):
+    """Behind the barrier of the block loop the copies overwrite the buffer of the block before: the wait in front of it covers
+    the wavefront's LDS reads as well as its copies."""
+    body = re.search(r"^_ZN\S*" + kernel + r"\S*:[^\n]*\n(.*?)^\.Lfunc_end", attention_asm, re.S | re.M).group(1)
+    heads = body.split("s_barrier")[:-1]
+    assert heads
+    for head in heads:
+        last = re.findall(r"s_waitcnt[^\n]*", head)[-1]
+        assert "lgkmcnt(0)" in last and "vmcnt" in last
