@@ -389,7 +389,6 @@ __device__ __forceinline__ void wait_vm_at_most(int n) {
     }
 }
 
-template <int EPI>
 __global__ __launch_bounds__(kMidThreads) void gemm_mid_kernel(GemmArgs a) {
     extern __shared__ u32x4 mid_lds[];      // X ring [kMidXBufs][32 tiles x 64], then W ring [kMidWBufs][10 tiles x 64]
 
@@ -484,47 +483,28 @@ __global__ __launch_bounds__(kMidThreads) void gemm_mid_kernel(GemmArgs a) {
     if (!active) return;
 
     // accumulator (i, j): lane (r32 = row within the 32-row group, g2) holds, in register v,
-    // feature 8 * (v / 4) + 4 * g2 + v % 4 of the 32-feature group
-    if constexpr (EPI == EPI_F32) {
-        float *out = (float *)a.out;
+    // feature 8 * (v / 4) + 4 * g2 + v % 4 of the 32-feature group: 16 gate, then 16 up features
+    uint16_t *out = (uint16_t *)a.out;
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int m = wave * 64 + j * 32 + r32;
-            if (m < a.M) {
+    for (int j = 0; j < 2; ++j) {
+        const int m = wave * 64 + j * 32 + r32;
+        if (m < a.M) {
 #pragma unroll
-                for (int i = 0; i < 5; ++i)
+            for (int i = 0; i < 5; ++i)
 #pragma unroll
-                    for (int vq = 0; vq < 4; ++vq) {
-                        const int n = nb * 160 + i * 32 + 8 * vq + 4 * g2;
-                        if (n < a.N)
-                            *(f32x4 *)(out + (size_t)m * a.ld_out + n) =
-                                f32x4{acc[i][j][4 * vq], acc[i][j][4 * vq + 1], acc[i][j][4 * vq + 2], acc[i][j][4 * vq + 3]};
-                    }
-            }
-        }
-    } else {
-        uint16_t *out = (uint16_t *)a.out;
+                for (int vq = 0; vq < 2; ++vq) {
+                    const int f = nb * 80 + i * 16 + 8 * vq + 4 * g2;
+                    if (f < a.ld_out) {
+                        float r[4];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int m = wave * 64 + j * 32 + r32;
-            if (m < a.M) {
-#pragma unroll
-                for (int i = 0; i < 5; ++i)
-#pragma unroll
-                    for (int vq = 0; vq < 2; ++vq) {
-                        const int f = nb * 80 + i * 16 + 8 * vq + 4 * g2;
-                        if (f < a.ld_out) {
-                            float r[4];
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                const float gt = acc[i][j][4 * vq + e];
-                                r[e] = gt / (1.0f + __expf(-gt)) * acc[i][j][4 * (vq + 2) + e];
-                            }
-                            uint2 v = make_uint2(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]));
-                            *(uint2 *)(out + frag_offset(m, f, a.mt_total)) = v;
+                        for (int e = 0; e < 4; ++e) {
+                            const float gt = acc[i][j][4 * vq + e];
+                            r[e] = gt / (1.0f + __expf(-gt)) * acc[i][j][4 * (vq + 2) + e];
                         }
+                        uint2 v = make_uint2(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]));
+                        *(uint2 *)(out + frag_offset(m, f, a.mt_total)) = v;
                     }
-            }
+                }
         }
     }
 }
@@ -724,23 +704,20 @@ int launch_tiles128(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream) {
 int launch_mid(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream) {
     static bool attr_set = false;
     if (!attr_set) {
-        SR_HIP(hipFuncSetAttribute((const void *)gemm_mid_kernel<EPI_F32>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   kMidLdsBytes));
-        SR_HIP(hipFuncSetAttribute((const void *)gemm_mid_kernel<EPI_SWIGLU>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   kMidLdsBytes));
+        SR_HIP(hipFuncSetAttribute((const void *)gemm_mid_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kMidLdsBytes));
         SR_HIP(hipFuncSetAttribute((const void *)gemm_mid16_kernel<EPI_F32>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                    kMidLdsBytes));
         SR_HIP(hipFuncSetAttribute((const void *)gemm_mid16_kernel<EPI_SWIGLU>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                    kMidLdsBytes));
         attr_set = true;
     }
-    if (a.M > 512 || a.splits != 1 || a.ks_total < 1 || round_up(a.M, 64) > a.mt_total * 16) return SR_E_ARG;
+    if (a.M > (epi == EPI_SWIGLU ? 512 : 384) || a.splits != 1 || a.ks_total < 1 || round_up(a.M, 64) > a.mt_total * 16)
+        return SR_E_ARG;
     dim3 grid((unsigned)ceil_div(a.N, 160)), block(kMidThreads);
     if (a.M > 256 && a.M <= 384) {           // 17 .. 24 row tiles: three per wavefront, dealt out round robin
         if (epi == EPI_F32) gemm_mid16_kernel<EPI_F32><<<grid, block, kMidLdsBytes, stream>>>(a);
         else gemm_mid16_kernel<EPI_SWIGLU><<<grid, block, kMidLdsBytes, stream>>>(a);
-    } else if (epi == EPI_F32) gemm_mid_kernel<EPI_F32><<<grid, block, kMidLdsBytes, stream>>>(a);
-    else gemm_mid_kernel<EPI_SWIGLU><<<grid, block, kMidLdsBytes, stream>>>(a);
+    } else gemm_mid_kernel<<<grid, block, kMidLdsBytes, stream>>>(a);
     SR_HIP(hipGetLastError());
     return SR_OK;
 }

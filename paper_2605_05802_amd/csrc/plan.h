@@ -95,8 +95,8 @@ inline int pick_splits(int M, int N, int ks_total) {
 //     {6, 4} 27.1; 38.8 and 42.6 at 2048); then 0.166 k a tile up to 1024 rows, and above 0.095 k a tile and 15 k (W read
 //     through L2 by many row blocks), from 16 384 matrix rows on, which no L2 holds, 0.137 k (22 016 rows, K = 4096: 541 us
 //     at 2560 rows and 658 at 3072, where tiles of {6, 5} and {6, 4} take 349 and 458).
-//   All rows in one workgroup of 160 features, up to 512 rows: 108 k a round up to 384 rows, 139 k up to 512.  Only for
-//     matrices of 16 384 rows and more, where it makes a round of workgroups.
+//   All rows in one workgroup of 160 features, up to 512 rows: 108 k a round up to 384 rows, 139 k up to 512 (SwiGLU only: no
+//     fp32 matrix is cheapest there).  Only for matrices of 16 384 rows and more, where it makes a round of workgroups.
 //   S splits divide k, cost a fixed 6 and S times the output, written here and read by the next kernel, at 4.5 TB/s.
 struct TileShape { int nt, rt; };
 constexpr TileShape kTileShapes[] = {{8, 4}, {7, 4}, {6, 4}, {5, 4}, {6, 5}, {5, 5}, {4, 5}, {4, 6}};      // {5, 6} and up spill
@@ -127,7 +127,7 @@ inline GemmPlan plan_gemm(int M, int N, int ks_total, int mt_total, bool swiglu,
             const long long rounds = ((long long)mb * ceil_div(N, 32 * nt) * S + 255) / 256;
             offer(i, rounds * 2.33 * rt * (nt + 1.5) * k / S);
         }
-        if (S == 1 && M <= 512 && N >= 16384)
+        if (S == 1 && M <= (swiglu ? 512 : 384) && N >= 16384)
             offer(KERNEL_MID, k * ceil_div(ceil_div(N, 160), 256) * (M <= 384 ? 108.0 : 139.0));
     }
     return best;
