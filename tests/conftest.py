@@ -1,4 +1,6 @@
+import ctypes
 import os
+import subprocess
 import sys
 
 import pytest
@@ -25,3 +27,45 @@ def pytest_collection_modifyitems(config, items):
     for item in items:
         if "gpu" in item.keywords:
             item.add_marker(skip)
+
+
+PLAN_SOURCE = """
+#include "plan.h"
+extern "C" {
+void shared_tiles(int n_sets, int per_set, int *set, int *part) {
+    for (int wg = 0; wg < n_sets * per_set; ++wg) sr::shared_tiles_of(wg, n_sets, per_set, set + wg, part + wg);
+}
+int stream_waves(int M, int N, int ks, int swiglu) { return sr::stream_waves(M, N, ks, swiglu); }
+int plan_kernel(int M, int N, int ks, int mt_total, int swiglu, int splits) {
+    return sr::plan_gemm(M, N, ks, mt_total, swiglu, splits, 16).kernel;
+}
+int tile_nt(int i) { return sr::kTileShapes[i].nt; }
+int tile_rt(int i) { return sr::kTileShapes[i].rt; }
+int split_steps(int M, int N, int ks, int mt_total, int splits) { return sr::split_steps(M, N, ks, mt_total, splits); }
+int projection_splits(int M, int N, int ks, int mt_total) { return sr::projection_splits(M, N, ks, mt_total); }
+}
+"""
+
+
+@pytest.fixture(scope="session")
+def plan(tmp_path_factory):
+    """csrc/plan.h as a shared library: which kernel a projection runs on.  plan.kernel(rows, matrix rows, inner dimension,
+    swiglu, splits) names it for a context of up to 8192 rows per pass, so that a test can say what it means to reach."""
+    from paper_2605_05802_amd.build import CSRC
+    d = tmp_path_factory.mktemp("plan")
+    (d / "plan.cpp").write_text(PLAN_SOURCE)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I" + CSRC, str(d / "plan.cpp"), "-o", str(d / "plan.so")])
+    lib = ctypes.CDLL(str(d / "plan.so"))
+
+    def kernel(M, N, K, swiglu=False, splits=1):
+        ks = -(-(-(-K // 32)) // 16) * 16
+        waves = lib.stream_waves(M, N, ks, int(swiglu))
+        if waves:
+            return f"stream {waves}"
+        k = lib.plan_kernel(M, N, ks, 512, int(swiglu), splits)
+        if k >= 0:
+            return f"tiles {lib.tile_nt(k)}x{lib.tile_rt(k)}"
+        return "128" if k == -2 else "rows16" if M <= 384 else "rows32"
+
+    lib.kernel = kernel
+    return lib

@@ -301,9 +301,9 @@ def test_retiring_every_group_leaves_a_legal_empty_batch():
 
 
 def test_wide_shapes_exercise_every_gemm_variant():
-    """FFN 8192 and vocab 16384 are wide enough to take the 8-wavefront decode kernel and the 256x256
-    prefill kernel (the small shapes above only reach the 4-wavefront kernels); prompt and observation
-    chunks of several hundred rows; split-K on the thin projections."""
+    """FFN 8192 and vocab 16384: the weight-streaming kernel without K splits at decode time, 128 x 128 tiles for prompt and
+    observation chunks of several hundred rows, K splits of the down projection.  (Every kernel and width has a test of
+    its own below: test_tiled_kernels_by_name, test_weight_streaming_widths_by_name.)"""
     shape = synth.ModelShape(2, 512, 14, 2, 128, 8192, 16384)
     cfg = synth.EpisodeConfig("wide", 2, 8, 160, 2, 24, 3, 64, (2,), 0.3, 0.5)
     rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=9, page_tokens=64, kv_pool_bytes=1 << 29)
@@ -340,10 +340,10 @@ def test_long_shared_prompt_in_several_passes():
 
 
 def test_mid_size_batch_takes_mixed_tiles_and_split_k():
-    """512 rows per decode step, 304 after the gate (the shape of the 64-group configuration): between 129 and
-    512 rows the wide gate|up projection (here 33 792 packed columns) runs on the kernel that gives all rows of 160
-    packed columns to one workgroup, and the thin projections are split along K on the tiled kernels; every logit
-    of every row is compared with the checker."""
+    """512 rows per decode step, 304 after the gate (the shape of the 64-group configuration): at 512 rows the wide gate|up
+    projection (here 33 792 packed columns) runs on the kernel that gives all rows of 160 packed columns to one
+    workgroup, at 304 on tiles, and the thin projections are split along K; every logit of every row is compared with
+    the checker."""
     shape = synth.ModelShape(1, 256, 4, 2, 64, 16896, 1024)
     cfg = synth.EpisodeConfig("mid", 64, 8, 16, 2, 2, 2, 64, (1,), 0.3, 0.4)
     rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=4, page_tokens=32, kv_pool_bytes=1 << 28)
@@ -356,7 +356,7 @@ def test_mid_size_batch_takes_mixed_tiles_and_split_k():
 def test_mid_size_batch_at_the_full_hidden_size():
     """The same regime at the inner dimension of the 7B shape (hidden 3584, 28 query / 4 kv heads of 128, one layer):
     384 rows per decode step, fewer after the gate, so the QKV, O and down projections run split along K = 3584 /
-    16896 on the tiled kernels and the gate|up projection on the all-rows-per-workgroup kernel; every logit
+    16896 on the tiled kernels and the gate|up projection on the all-rows kernel (at 384 rows); every logit
     of every row against the checker, bound by the general rule (the contract mode on six sequences)."""
     shape = synth.ModelShape(1, 3584, 28, 4, 128, 16896, 1024)
     cfg = synth.EpisodeConfig("mid-3584", 48, 8, 8, 2, 2, 2, 64, (1,), 0.3, 0.4)
@@ -371,10 +371,9 @@ def test_mid_size_batch_at_the_full_hidden_size():
 
 
 def test_mid_size_batch_with_ragged_wide_matrices():
-    """296 rows per decode step (four 64-row slabs and one of 40 rows), fewer after the gate, against a gate|up
-    matrix of 16 416 packed columns and an LM head of 16 400 rows, neither a multiple of the 160 columns a workgroup
-    of the all-rows kernel takes: both of its epilogues (SwiGLU to bf16, fp32 logits), its ragged last workgroup and
-    its ragged last row slab, every logit of every row against the checker."""
+    """296 rows per decode step (a last row block of 40), fewer after the gate, against a gate|up matrix of 16 416 packed
+    columns and an LM head of 16 400 rows: ragged last tiles of the 128 x 128 kernel in both epilogues (SwiGLU to bf16,
+    fp32 logits), every logit of every row against the checker."""
     shape = synth.ModelShape(1, 256, 4, 2, 64, 8208, 16400)
     cfg = synth.EpisodeConfig("mid-ragged", 37, 8, 8, 2, 2, 2, 64, (1,), 0.3, 0.4)
     rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=21, page_tokens=32, kv_pool_bytes=1 << 28)
@@ -872,8 +871,8 @@ def test_prefill_tile_widths(hidden, ffn):
 @pytest.mark.parametrize("n_groups,G", [(43, 3), (20, 8), (23, 7), (24, 8), (32, 7), (64, 4)])
 def test_weight_streaming_projections_beyond_128_rows(n_groups, G):
     """129, 160, 161, 192, 224 and 256 rows per decode step (five to eight row tiles, the row counts on both sides of a tile
-    edge): gate|up and LM head at three workgroup widths, the thin projections split along K, matrices that do not fill
-    the last workgroup."""
+    edge): the LM head in workgroups of 64 features throughout, the smaller matrices with it up to 192 rows, the thin
+    projections split along K, matrices that do not fill the last workgroup."""
     shape = synth.ModelShape(1, 544, 4, 2, 64, 1360, 8208)
     cfg = synth.EpisodeConfig("stream", n_groups, G, 8, 2, 2, 2, 64, (1,), 0.3, 0.4)
     rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=51, page_tokens=32, kv_pool_bytes=1 << 28)
@@ -952,3 +951,57 @@ def test_chosen_tokens_into_the_buffer_of_the_forced_ones(offset):
     assert torch.equal(out, own) and torch.equal(got, want)
     ctx.close()
     ref.close()
+
+
+@pytest.mark.parametrize("n_groups,ffn,vocab,gate_up,lm_head", [
+    (33, 12304, 24592, "tiles 6x5", "tiles 4x5"),     # 264 rows
+    (43, 16912, 32816, "rows16", "rows16"),           # 344 rows: half a row tile in the last slab
+    (43, 12304, 24592, "tiles 8x4", "tiles 4x6"),
+    (55, 20464, 24592, "rows32", "tiles 7x4"),        # 440 rows
+    (55, 8208, 16400, "tiles 6x4", "tiles 5x4"),
+    (65, 12304, 16400, "tiles 6x4", "tiles 5x5"),     # 520 rows
+    (81, 8208, 40944, "tiles 8x4", "tiles 8x4"),      # 648 rows
+    (97, 8208, 33824, "tiles 6x4", "tiles 6x4"),      # 776 rows
+])
+def test_tiled_kernels_by_name(plan, n_groups, ffn, vocab, gate_up, lm_head):
+    """Every tile shape and the all-rows kernels, in both epilogues where they have them: the gate|up projection and the LM head
+    of a decode step are on the kernel named here, with a ragged last row block and a ragged last column block."""
+    rows = n_groups * 8
+    assert plan.kernel(rows, 2 * ffn, 128, swiglu=True) == gate_up and plan.kernel(rows, vocab, 128) == lm_head
+    shape = synth.ModelShape(1, 128, 2, 1, 64, ffn, vocab)
+    cfg = synth.EpisodeConfig("tiled", n_groups, 8, 4, 1, 1, 1, 64, (), 0.3, 0.0)
+    rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=71, page_tokens=32, kv_pool_bytes=1 << 28)
+    print(f"tiled {rows} rows, {gate_up} / {lm_head}: worst |dlogit| = {worst:.3e}, mismatches = {mism}, near ties = {near}")
+    assert worst <= LOGIT_TOL and mism == 0
+
+
+def test_fp32_tiles_of_320_rows_by_192_features(plan):
+    """5935 prompt rows: the QKV projection of 2304 rows runs on tiles of 320 rows x 192 features, a ragged last row block."""
+    assert plan.kernel(5935, 2304, 512) == "tiles 6x5" and plan.projection_splits(5935, 2304, 16, 512) == 1
+    shape = synth.ModelShape(1, 512, 14, 2, 128, 256, 512)
+    cfg = synth.EpisodeConfig("qkv-tiles", 5, 2, 1187, 1, 3, 1, 16, (), 0.3, 0.0)
+    rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=73, page_tokens=64, kv_pool_bytes=1 << 28)
+    print(f"QKV tiles: worst |dlogit| = {worst:.3e}, mismatches = {mism}, near ties = {near}")
+    assert worst <= LOGIT_TOL and mism == 0
+
+
+@pytest.mark.parametrize("n_groups,G,ffn,vocab,gate_up,lm_head", [
+    (3, 8, 24592, 57360, 8, 8), (7, 8, 24592, 57360, 8, 8), (11, 8, 24592, 57360, 8, 8), (15, 8, 24592, 57360, 8, 8),
+    (1, 3, 36880, 73744, 10, 10), (5, 8, 36880, 73744, 10, 10), (9, 8, 36880, 73744, 10, 10), (16, 8, 36880, 73744, 10, 10),
+    (1, 2, 8208, 40944, 4, 5), (6, 7, 20464, 16400, 5, 4), (13, 6, 8208, 40944, 4, 5), (14, 7, 20464, 16400, 5, 4),
+    (43, 3, 8208, 40944, 4, 5), (20, 8, 20464, 16400, 5, 4),                              # 129 and 160 rows: five row tiles
+    (23, 7, 20464, 16400, 5, 4), (24, 8, 8208, 40944, 4, 5),                              # 161 and 192: six
+    (31, 7, 16400, 24592, 5, 4), (28, 8, 8208, 40944, 4, 5),                              # 217 and 224: seven
+    (32, 8, 8208, 40944, 4, 5), (30, 8, 20464, 16400, 5, 4),                              # 256 and 240: eight
+])
+def test_weight_streaming_widths_by_name(plan, n_groups, G, ffn, vocab, gate_up, lm_head):
+    """The weight-streaming kernel at every workgroup width and number of row tiles that it has with matrices too wide to be
+    split, both epilogues, a ragged last workgroup."""
+    rows = n_groups * G
+    assert plan.kernel(rows, 2 * ffn, 128, swiglu=True) == f"stream {gate_up}"
+    assert plan.kernel(rows, vocab, 128) == f"stream {lm_head}"
+    shape = synth.ModelShape(1, 128, 2, 1, 64, ffn, vocab)
+    cfg = synth.EpisodeConfig("widths", n_groups, G, 4, 1, 1, 1, 64, (), 0.3, 0.0)
+    rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=79, page_tokens=32, kv_pool_bytes=1 << 28)
+    print(f"stream {rows} rows, {gate_up} / {lm_head}: worst |dlogit| = {worst:.3e}, mismatches = {mism}, near ties = {near}")
+    assert worst <= LOGIT_TOL and mism == 0

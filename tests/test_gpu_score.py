@@ -242,3 +242,46 @@ def test_scoring_without_stored_logits(chunk, vocab, rows_cap):
     assert np.abs(total.cpu().numpy() - got.astype(np.float64).sum(axis=1)).max() <= 1e-9 * chunk
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("vocab", [1040, 528])
+@pytest.mark.parametrize("heavy", ["last tile", 0, 1, 2, 3])
+def test_scoring_counts_every_column_of_the_last_tile(vocab, heavy):
+    """The vocabulary ends in a tile of 16 columns, four of which lie in each group of lanes.  Their LM-head rows are scaled by 16,
+    so that without them the log-sum-exp of some row moves by far more than the bound (checked on the reference); targets
+    lie among them and elsewhere."""
+    shape = synth.ModelShape(1, 256, 4, 2, 64, 256, vocab)
+    w = synth.make_weights(shape, seed=2, sigma=0.05)
+    cols = np.arange(vocab - 16, vocab) if heavy == "last tile" else vocab - 16 + 4 * heavy + np.arange(4)
+    as_f32 = (w.lm_head[cols].astype(np.uint32) << 16).view(np.float32) * 16
+    w.lm_head[cols] = (as_f32.view(np.uint32) >> 16).astype(np.uint16)          # a power of two: exact in bf16
+    n, P, chunk = 8, 24, 33
+    prompts = dev(synth.uniform_ids(2 * P, 0, 1, vocab).reshape(2, P))
+    toks = synth.uniform_ids(n * chunk, 0, 2, vocab).reshape(n, chunk)
+    toks[:, ::3] = cols[np.arange(toks[:, ::3].size).reshape(n, -1) % cols.size]
+    mk = lambda: sr.Context(shape, 2, 4, 0.3, page_tokens=32, max_seq_len=P + chunk + 8, max_turns=1, action_mod=16,
+                            kv_pool_bytes=1 << 26)
+    a = mk()
+    load_host_weights(a, w)
+    a.sr_prefill_chunk(prompts, True)
+    lp = torch.full((n, chunk), 7.0, dtype=torch.float32, device="cuda")
+    a.sr_score_chunk(dev(toks), None, lp)
+    b = mk()
+    load_host_weights(b, w)
+    b.sr_prefill_chunk(prompts, True)
+    ref, without = np.zeros((n, chunk)), np.zeros((n, chunk))
+    lg = torch.empty((n, vocab), dtype=torch.float32, device="cuda")
+    for t in range(chunk):
+        b.sr_get_logits(lg)
+        torch.cuda.synchronize()
+        x = lg.double().cpu().numpy()
+        lse = np.logaddexp.reduce(x, axis=1)
+        ref[:, t] = x[np.arange(n), toks[:, t]] - lse
+        without[:, t] = lse - np.logaddexp.reduce(np.delete(x, cols, axis=1), axis=1)
+        b.sr_decode_step(dev(np.ascontiguousarray(toks[:, t])))
+    bound = 16 * 2 * LOGIT_TOL             # the logits' bound, at LM-head rows sixteen times as long, for target and log-sum-exp
+    assert without[:, 1:].max() > 3 * bound
+    torch.cuda.synchronize()
+    assert np.abs(lp.cpu().numpy() - ref).max() <= bound
+    a.close()
+    b.close()

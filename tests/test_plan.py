@@ -1,34 +1,7 @@
 """The rules that lay work out over the chip (csrc/plan.h), evaluated on the CPU."""
 import ctypes
-import os
-import subprocess
 
 import pytest
-
-from paper_2605_05802_amd.build import CSRC
-
-SOURCE = """
-#include "plan.h"
-extern "C" {
-void shared_tiles(int n_sets, int per_set, int *set, int *part) {
-    for (int wg = 0; wg < n_sets * per_set; ++wg) sr::shared_tiles_of(wg, n_sets, per_set, set + wg, part + wg);
-}
-int stream_waves(int M, int N, int ks, int swiglu) { return sr::stream_waves(M, N, ks, swiglu); }
-int plan_kernel(int M, int N, int ks, int mt_total, int swiglu, int splits) {
-    return sr::plan_gemm(M, N, ks, mt_total, swiglu, splits, 16).kernel;
-}
-int split_steps(int M, int N, int ks, int mt_total, int splits) { return sr::split_steps(M, N, ks, mt_total, splits); }
-int projection_splits(int M, int N, int ks, int mt_total) { return sr::projection_splits(M, N, ks, mt_total); }
-}
-"""
-
-
-@pytest.fixture(scope="module")
-def plan(tmp_path_factory):
-    d = tmp_path_factory.mktemp("plan")
-    (d / "plan.cpp").write_text(SOURCE)
-    subprocess.check_call(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I" + CSRC, str(d / "plan.cpp"), "-o", str(d / "plan.so")])
-    return ctypes.CDLL(str(d / "plan.so"))
 
 
 @pytest.mark.parametrize("per_set", [1, 2, 3, 7, 313])
