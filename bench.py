@@ -384,10 +384,10 @@ def main():
     roofline = {"bound": "hbm", "kernel": "gemm_stream_kernel<EPI_SWIGLU, 5, MT32, 8> (decode gate|up projection)",
                 "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                 "peak_measured": peaks["hbm_read_nt_GBs"], "frac_of_measured": achieved / peaks["hbm_read_nt_GBs"]}
-    if mean_rows > 128:
-        # more than 128 rows per step: the projection runs on a tiled prefill kernel and is bound by the matrix cores
+    if mean_rows > 256:
+        # more than 256 rows per step: the projection runs on a tiled kernel and is bound by the matrix cores
         tf = 2.0 * mean_rows * 2 * shape.ffn * shape.hidden / (avg_ms * 1e-3) / 1e12 if avg_ms > 0 else 0.0
-        roofline = {"bound": "mfma", "kernel": "decode gate|up projection at more than 128 rows (streaming kernel up to 256, tiled above)",
+        roofline = {"bound": "mfma", "kernel": "decode gate|up projection at more than 256 rows (tiled kernels)",
                     "achieved": tf, "peak": MFMA_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": tf / MFMA_PEAK_TFLOPS,
                     "peak_measured": peaks["mfma_bf16_TFLOPs"], "frac_of_measured": tf / peaks["mfma_bf16_TFLOPs"]}
     traffic = None

@@ -144,7 +144,7 @@ struct sr_ctx {
     uint8_t *d_retire = nullptr;
 
     // scratch
-    int R = 0, mt_total = 0;                    // row capacity (multiple of 128) and its row tiles
+    int R = 0, mt_total = 0;                    // row capacity (multiple of 256) and its row tiles
     int ks_h = 0, ks_q = 0, ks_f = 0;           // k-steps of hidden, q_dim, ffn
     int qkv_cols = 0;
     float *resid = nullptr, *partials = nullptr, *part_o = nullptr, *part_ml = nullptr;

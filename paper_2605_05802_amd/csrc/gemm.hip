@@ -1,7 +1,7 @@
 // Projection GEMMs  Y[M][N] = X[M][K] * W[N][K]^T  on the bf16 matrix cores, for more than 256 rows (up to there the
-// weight stream bounds them: gemm_stream.hip).  W and X are stored pre-tiled in MFMA operand order.  Three kernels, chosen
-// per launch by measured cost (choose_tiles): 128 x 128 tiles, tiles of 256 rows x 160 to 256 features, and all rows of
-// a batch of a few hundred in one workgroup of 160 features.
+// weight stream bounds all but small matrices: gemm_stream.hip).  W and X are stored pre-tiled in MFMA operand order.  Three
+// kernels, chosen per launch by measured cost (plan_gemm in plan.h): 128 x 128 tiles, tiles of 256 to 384 rows x 128 to 256
+// features, and all rows of a batch of a few hundred in one workgroup of 160 features.
 #include <type_traits>
 
 #include "sr_internal.h"
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Prefill (M > 128) kernel: compute bound, so the tile is sized for the matrix cores.
+// Kernel for more than 256 rows: compute bound, so the tile is sized for the matrix cores.
 //
 // A workgroup owns 64 * RT rows x 32 * NT features and one split of K (see plan_gemm for which).  Eight wavefronts in a
 // 2 x 4 arrangement each take 16 * NT features x 16 * RT rows with 16x16x32 MFMAs; both operands reach them
@@ -292,7 +292,9 @@ __global__ __launch_bounds__(kPfThreads) void gemm_prefill_kernel(GemmArgs a, in
             }
         }
     } else if constexpr (EPI == EPI_LSE) {
-        // a wavefront's 128 columns of a row lie in four lanes
+        // a wavefront's 128 columns of a row lie in four lanes.  The exponentials are the hardware's base-2 exponential in fp32 as it
+        // is: arguments <= 0, results below 2^-126 of the row's maximum may flush to zero, which no sum near 1 or above sees (the
+        // error against 64 bits is the stored logits': 0.00101 both at 152 064 columns).
         const ScoreOut &so = a.score;
         const int n0 = (nb * 2 * NT + wn * NT) * 16 + 4 * g;         // + 16 i + e
         auto value = [&](int i, int e, int j) { return n0 + 16 * i < a.N ? acc[i][j][e] : -3.0e38f; };      // N is a multiple of 16

@@ -47,7 +47,7 @@ __device__ __forceinline__ u32x4 load_w_stream(const u32x4 *p) { return __builti
 // should break into about 256 equal workgroups: 37 888 packed gate|up rows give 148 workgroups of
 // 256 features (108 CUs idle) but 237 of 160.
 // ---------------------------------------------------------------------------------------------
-constexpr int kRing = kPF;                 // k-steps of W in flight per computing wavefront (16 measured slower at every width)
+constexpr int kRing = 8;                   // k-steps of W in flight per computing wavefront (16 measured slower at every width)
 constexpr int kStBufs = 3;                 // LDS chunk buffers: the loader runs two chunks ahead
 constexpr int st_lds_bytes(int mt32) { return kStBufs * chunk_steps(mt32) * kstep_vec(mt32) * 16; }
 
