@@ -7,6 +7,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -34,7 +35,7 @@ struct LayerW {
     uint16_t *bq = nullptr, *bk = nullptr, *bv = nullptr, *norm1 = nullptr, *norm2 = nullptr;
 };
 
-constexpr int kScoreRows = 256;          // scoring through stored logits: rows of the LM head computed at a time
+constexpr int kScoreRows = 256;          // scoring through stored logits: rows of the LM head at a time (but see score_rows)
 constexpr int kMaxAttnSplits = 16;
 
 }  // namespace
@@ -136,7 +137,7 @@ struct sr_ctx {
     float *d_logits[2] = {nullptr, nullptr};
     double *d_logprob[2] = {nullptr, nullptr};  // running teacher-forced log-likelihood of every live row
     float *d_tok_lp = nullptr;                  // per-token values of the chunk being scored [n_seq0][max_seq_len]
-    float *score_logits = nullptr;              // [kScoreRows][vocab], allocated by the first scoring call
+    float *score_logits = nullptr;              // rows of logits (score_rows), allocated by the first scoring call
     ScoreOut score{};                           // scoring without stored logits: buffers for R rows, allocated with it
     int32_t *score_target = nullptr;
     int cur = 0;
@@ -699,7 +700,8 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
         la.tok0 = p.tok_off + 1;                                  // a row predicts the token after it
         la.out = c->d_tok_lp + (size_t)p.score_unit0 * p.score_chunk_len;
         float *last = c->d_logits[c->cur] + (size_t)p.logit_row0 * s.vocab;
-        if (!dbg && M > kStreamRows) {
+        const int block = score_rows(M, s.vocab, kScoreRows);
+        if (!dbg && M > kStreamRows && block < M) {
             // the LM head reduces its rows itself; the last row of every unit is kept
             GemmArgs ga{};
             ga.X = c->xn;
@@ -719,8 +721,8 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
             SR_TRY(timed(c, SR_KC_ARGMAX, st, [&] { return launch_score_reduce(la, M, ga.score, st); }));
             return SR_OK;
         }
-        for (int r0 = 0; r0 < M; r0 += kScoreRows) {
-            const int blk = M - r0 < kScoreRows ? M - r0 : kScoreRows;
+        for (int r0 = 0; r0 < M; r0 += block) {
+            const int blk = M - r0 < block ? M - r0 : block;
             const uint4 *x = c->xn + (size_t)(r0 / 16) * 64;      // row tile r0 / 16 of every k-step
             SR_TRY(timed(c, SR_KC_GEMM_LM_HEAD, st, [&] {
                 return dbg ? gemm32(c, c->xn32 + (size_t)r0 * H, H, c->lm, blk, EPI_F32, c->score_logits, s.vocab,
@@ -731,7 +733,7 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
             la.row0 = r0;
             SR_TRY(timed(c, SR_KC_ARGMAX, st, [&] { return launch_logprob_rows(la, blk, st); }));
         }
-        if (M <= kScoreRows) {                                    // every row's logits are at hand
+        if (M <= block) {                                         // every row's logits are at hand
             if (p.want_logits) SR_TRY(launch_last_rows(last, c->score_logits, p.n_units, p.chunk, s.vocab, st));
             return SR_OK;
         }
@@ -1085,7 +1087,7 @@ int sr_score_chunk(sr_ctx *c, const int32_t *tokens, const uint8_t *action_mask,
     if (!c->score_logits) {
         AllocPlan plan;
         float *logits = nullptr;
-        plan.want(&logits, (size_t)kScoreRows * s.vocab);
+        plan.want(&logits, std::max((size_t)kScoreRows * s.vocab, (size_t)kSmallScore));
         if (!c->dbg) {
             plan.want(&c->score_target, (size_t)c->R);
             plan.want(&c->score.target_logit, (size_t)c->R);

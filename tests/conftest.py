@@ -42,6 +42,7 @@ int plan_kernel(int M, int N, int ks, int mt_total, int swiglu, int splits) {
 int tile_nt(int i) { return sr::kTileShapes[i].nt; }
 int tile_rt(int i) { return sr::kTileShapes[i].rt; }
 int split_steps(int M, int N, int ks, int mt_total, int splits) { return sr::split_steps(M, N, ks, mt_total, splits); }
+int score_rows(int M, int vocab, int rows) { return sr::score_rows(M, vocab, rows); }
 int projection_splits(int M, int N, int ks, int mt_total) { return sr::projection_splits(M, N, ks, mt_total); }
 }
 """

@@ -199,12 +199,17 @@ def test_loss_adds_the_groups_in_index_order(n_groups):
     assert np.allclose(share.cpu().numpy(), (adv * lp).sum(axis=1), rtol=0, atol=1e-9)
 
 
-@pytest.mark.parametrize("chunk,vocab,rows_cap", [(33, 1040, 0), (40, 272, 512), (129, 528, 0), (8, 1040, 0), (1, 272, 0)])
-def test_scoring_without_stored_logits(chunk, vocab, rows_cap):
-    """Chunks of 264 and 320 rows (the LM head reduces its rows itself; one pass and two), of 1032 rows (several row blocks),
-    and of 64 and 8 (through stored logits), vocabularies that do not fill the last tile: the token values agree with
-    log softmax of the logits that the same tokens leave when they are appended one by one, and the logits kept behind
-    the chunk with those of the last one."""
+@pytest.mark.parametrize("chunk,vocab,rows_cap", [(33, 1040, 0), (40, 272, 512), (129, 528, 0), (8, 1040, 0), (1, 272, 0),
+                                                  (33, 4112, 0), (40, 4112, 512), (129, 1040, 0), (64, 2048, 0), (64, 2064, 0)])
+def test_scoring_without_stored_logits(plan, chunk, vocab, rows_cap):
+    """Vocabularies of 1040 (at 1032 rows), 2064 and 4112 with chunks of 264 to 1032 rows: the LM head reduces its rows itself, in
+    one pass and in two.  Smaller LM heads, with as many rows, and chunks of 64 and 8 rows: through stored logits in one
+    block; 512 rows of 2048 and 2064 columns lie on both sides of the rule.  Vocabularies that do not fill the last tile: the
+    token values agree with log softmax of the logits that the same tokens leave when they are appended one by one, and the
+    logits kept behind the chunk with those of the last one."""
+    rows = 8 * chunk if not rows_cap else min(8 * chunk, rows_cap // chunk * chunk)
+    stored = plan.score_rows(rows, vocab, 256) >= rows
+    assert stored == (rows <= 256 or (vocab <= 528) or (vocab, chunk) in ((1040, 33), (2048, 64)))
     shape = synth.ModelShape(1, 256, 4, 2, 64, 256, vocab)
     w = synth.make_weights(shape, seed=2, sigma=0.05)
     n, P = 8, 24
@@ -244,12 +249,13 @@ def test_scoring_without_stored_logits(chunk, vocab, rows_cap):
     b.close()
 
 
-@pytest.mark.parametrize("vocab", [1040, 528])
+@pytest.mark.parametrize("vocab", [4112, 2064])
 @pytest.mark.parametrize("heavy", ["last tile", 0, 1, 2, 3])
-def test_scoring_counts_every_column_of_the_last_tile(vocab, heavy):
+def test_scoring_counts_every_column_of_the_last_tile(plan, vocab, heavy):
     """The vocabulary ends in a tile of 16 columns, four of which lie in each group of lanes.  Their LM-head rows are scaled by 16,
     so that without them the log-sum-exp of some row moves by far more than the bound (checked on the reference); targets
     lie among them and elsewhere."""
+    assert plan.score_rows(264, vocab, 256) == 256              # 264 rows: the LM head's epilogue reduces them
     shape = synth.ModelShape(1, 256, 4, 2, 64, 256, vocab)
     w = synth.make_weights(shape, seed=2, sigma=0.05)
     cols = np.arange(vocab - 16, vocab) if heavy == "last tile" else vocab - 16 + 4 * heavy + np.arange(4)

@@ -63,3 +63,13 @@ def test_debug_path_deals_k_out_like_the_kernel_it_mirrors(plan):
             assert plan.split_steps(M, N, ks, 512, s) == (4 if on_tiles else 8)
             tiled += on_tiles and (ks // 8) % s != 0       # the two units give different ranges
     assert tiled >= 3
+
+
+def test_small_lm_heads_are_scored_through_stored_logits(plan):
+    """Up to 16 tiles of 256 x 256 in one block, within the buffer sized for it; beyond, blocks of 256 rows (or the epilogue)."""
+    for vocab in (16, 272, 1024, 2048, 2064, 4096, 152064):
+        for M in (1, 256, 257, 512, 513, 1024, 4096, 4097, 8192):
+            rows = plan.score_rows(M, vocab, 256)
+            tiles = -(-M // 256) * -(-vocab // 256)
+            assert rows == (M if M > 256 and tiles <= 16 else 256)
+            assert rows == 256 or rows * vocab <= 16 * 65536
