@@ -1,19 +1,19 @@
 // Selective-Rollout gate: mean pairwise prefix edit distance of a group's action sequences
 // (paper Section 3.2) compared with the threshold d_L (Eq. 2), in exact integer arithmetic.
 //
-// Work decomposition.  One lane owns one of the G(G-1)/2 pairs of a group and runs its whole Levenshtein table in
-// registers, one row at a time with the row as two bit masks (prefix_match.h), so there is no cross-lane traffic in
-// the recurrence.  A workgroup of up to 256 lanes serves whole groups (nine at G = 8); the equality masks come from
-// LDS tables built once per group or from comparing in registers, and the per-group sums are accumulated with LDS
-// integer atomics, which are order-independent and therefore deterministic.
+// Work decomposition.  A lane runs the whole Levenshtein tables of one or two of a group's G(G-1)/2 pairs in registers, a row
+// at a time with the row as bit masks (prefix_match.h), so there is no cross-lane traffic in the recurrence.  A workgroup
+// of up to 256 lanes serves whole groups (sixteen at G = 8); the equality masks come from LDS tables built once per group
+// or from comparing in registers, and the per-group sums are accumulated with LDS integer atomics, which are
+// order-independent and therefore deterministic.
 //
 // Prefix nesting: cell (k,k) of the table of two length-L sequences is the distance of their length-k prefixes, so one
 // table serves every requested prefix length.
 //
-// Bound: vector ALU (about 65 % busy, 530 instructions per wavefront: 180 of them the recurrence) with the LDS latency of
-// the table build behind it; the 64 MB of input would be 12 us.  65 536 groups of 8, prefixes 5, 10 and 15: 41 us (62 with
-// symbols beyond the table's range), 72 us with one table cell at a time in registers; at 32 steps 120 against 284 us.
-// Groups of 5, 12 steps: 14 us by comparison, 24 one cell at a time; groups of 16, one step: 44 against 61.
+// Bound: memory and vector ALU about equally; the 64 MB of input alone would take 13 us.  65 536 groups of 8, prefixes 5, 10 and
+// 15: 18.3 us; 41.8 with a lane per pair, masks of one member per LDS read and 4-byte loads of the symbols.  32 steps: 42
+// against 132 us, groups of 16 with 16 steps 62 against 144.  With symbols beyond the tables' range (all different) 86 us, 104
+// before.  Compared in registers: groups of 5, 12 steps 17.5 us.
 #include "prefix_match.h"
 
 namespace sr {
@@ -28,73 +28,145 @@ int64_t gate_bound(double d_L, int G, int K) {
 namespace {
 
 constexpr int kGateThreads = 256;
-constexpr int kGateLds = 48 * 1024;      // tables of one workgroup: three workgroups or more per compute unit
+constexpr int kGateLds = 40 * 1024;      // LDS of one workgroup: four workgroups or more per compute unit
+// ... where symbols are hashed, whose tables are larger: 65 536 groups of 12, 12 steps 95 us, 109 with 16 KiB, 113 with 32, 147 with 40
+// (groups of 8, 15 steps: 86, 80, 89 and 113); 40 and more take occupancy from calls that hash nothing (20 -> 26 us)
+constexpr int kGateHashLds = 24 * 1024;
 
 __device__ __forceinline__ unsigned min3u(unsigned a, unsigned b, unsigned c) {
     return min(a, min(b, c));
 }
 
-template <int KMAX, bool DIRECT>
-__global__ __launch_bounds__(kGateThreads) void gate_kernel(
-    const int32_t *__restrict__ actions, int n_groups, int stride, int pairs, PrefixGeom q, GateLens lens,
+__device__ __forceinline__ unsigned wanted_lens(const GateLens &lens) {      // bit k: prefix length k + 1 is asked for
+    unsigned wanted = 0;
+    for (int l = 0; l < lens.n; ++l) wanted |= 1u << (lens.len[l] - 1);
+    return wanted;
+}
+// Sums of a workgroup's groups, one word of s_sum [distinct prefix length / 2][group] for two lengths: at most 120 * 32 each
+__device__ __forceinline__ int len_slot(unsigned wanted, int K) { return __popc(wanted & ((1u << (K - 1)) - 1u)); }
+// A lane's distances, shortest prefix first: two of them share an addition
+struct LaneSums {
+    unsigned word = 0;
+    __device__ __forceinline__ void add(unsigned *s_sum, int groups, int g, unsigned wanted, int K, unsigned d) {
+        const int u = len_slot(wanted, K);
+        word += d << (16 * (u & 1));
+        if ((u & 1) || (wanted >> (K - 1)) == 1) {    // uniform
+            atomicAdd(&s_sum[(u >> 1) * groups + g], word);
+            word = 0;
+        }
+    }
+};
+__device__ __forceinline__ void write_sums(const unsigned *s_sum, int groups, int n_here, size_t g0, int n_groups, const GateLens &lens,
+                                           unsigned wanted, int32_t *__restrict__ sums, uint8_t *__restrict__ retire) {
+    for (int i = threadIdx.x; i < lens.n * n_here; i += blockDim.x) {
+        const int l = i / n_here, g = i - l * n_here, u = len_slot(wanted, lens.len[l]);
+        const int s = (int)((s_sum[(u >> 1) * groups + g] >> (16 * (u & 1))) & 0xFFFFu);
+        if (sums) sums[(size_t)l * n_groups + g0 + g] = s;
+        if (retire) retire[(size_t)l * n_groups + g0 + g] = (uint8_t)(s < lens.bound[l]);
+    }
+}
+
+// Equality masks from tables
+template <int KIND>
+__global__ __launch_bounds__(kGateThreads) void gate_table_kernel(
+    const int32_t *__restrict__ actions, int n_groups, int stride, PrefixGeom q, GateLens lens,
     int32_t *__restrict__ sums, uint8_t *__restrict__ retire) {
-    extern __shared__ __align__(16) char lds[];      // prefix tables
-    __shared__ unsigned s_sum[4][kGateThreads];      // [len index / 2][group in block]: two sums of at most 120 * 32 each
+    extern __shared__ __align__(16) char lds[];      // element ids, tables, sums
+    unsigned *s_sum = (unsigned *)(lds + q.total);
+    typedef PrefixBits<KIND> Bits;
+
+    const int tid = threadIdx.x, G = q.G;
+    const int g0 = blockIdx.x * q.groups;
+    const int n_here = min(q.groups, n_groups - g0), rows = n_here * G;
+    PrefixRows<KIND> x;
+    x.load(q, rows, actions + (size_t)g0 * G * stride, stride, g0 + n_here == n_groups ? rows - 1 : -1);
+    prefix_zero(lds, q.body, q.groups * kPrefixSyms * q.row_bytes);
+    for (int i = tid; i < 4 * q.groups; i += blockDim.x) s_sum[i] = 0;
+    const bool direct = prefix_all_fit(x.fits(rows));
+
+    const int gl = small_div(tid, 1.0f / (float)q.lanes);      // group within the block
+    int i, j;
+    prefix_lane<KIND>(tid - gl * q.lanes, G, &i, &j);
+    const int ri = gl * G + i;
+    const unsigned wanted = wanted_lens(lens);
+    const bool second = j + 1 < G;
+    auto pairs = [&](int s0, int n, int group_bytes) {           // of the groups s0 .. s0 + n - 1
+        if (gl < s0 || gl >= min(s0 + n, n_here)) return;
+        const char *column = lds + q.body + (gl - s0) * group_bytes + prefix_column<KIND>(j);
+        Bits pv = Bits::all(0xFFFFFFFFu), mv = Bits::all(0);
+        LaneSums sum;
+#pragma unroll 1
+        for (int r0 = 0; r0 < q.L; r0 += 8) {
+            unsigned id[8];
+            Bits eq[8];
+            prefix_ids8<KIND>(lds, ri, r0, id);
+#pragma unroll
+            for (int t = 0; t < 8; ++t) eq[t] = prefix_masks<KIND>(column, id[t]);
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                prefix_row(eq[t], pv, mv);
+                if ((wanted >> (r0 + t)) & 1u)        // uniform
+                    sum.add(s_sum, q.groups, gl, wanted, r0 + t + 1, prefix_cells(r0 + t + 1, second, pv, mv));
+            }
+        }
+    };
+    if (direct) {
+        prefix_mark<KIND>(lds, q, rows, x);
+        __syncthreads();
+        pairs(0, q.groups, kPrefixSyms * q.row_bytes);
+    } else {
+        for (int s0 = 0; s0 < n_here; s0 += q.hash_groups) {
+            __syncthreads();                          // nobody reads the tables of the round before
+            prefix_hash<KIND>(lds, q, rows, x, s0, q.hash_groups);
+            pairs(s0, q.hash_groups, round_up(prefix_hash_rows(q), 16));
+        }
+    }
+    __syncthreads();
+    write_sums(s_sum, q.groups, n_here, g0, n_groups, lens, wanted, sums, retire);
+}
+
+// A lane per pair, symbols compared in registers
+template <int KMAX>
+__global__ __launch_bounds__(kGateThreads) void gate_direct_kernel(
+    const int32_t *__restrict__ actions, int n_groups, int stride, PrefixGeom q, GateLens lens,
+    int32_t *__restrict__ sums, uint8_t *__restrict__ retire) {
+    extern __shared__ __align__(16) char lds[];      // symbols, sums
+    unsigned *s_sum = (unsigned *)(lds + q.total);
 
     const int tid = threadIdx.x, G = q.G;
     const int g0 = blockIdx.x * q.groups;
     const int n_here = min(q.groups, n_groups - g0);
-    const PrefixLds off = prefix_lds(q, q.groups, KMAX, DIRECT);
-    for (int i = tid; i < q.groups; i += blockDim.x) s_sum[0][i] = s_sum[1][i] = s_sum[2][i] = s_sum[3][i] = 0;
-    const int32_t *src = actions + (size_t)g0 * G * stride;
-    if constexpr (DIRECT) prefix_stage<KMAX>(lds, q, n_here * G, src, stride);
-    else prefix_build<KMAX>(lds, q, off, n_here * G, src, stride);
+    const unsigned wanted = wanted_lens(lens);
+    for (int i = tid; i < 4 * q.groups; i += blockDim.x) s_sum[i] = 0;
+    prefix_stage<KMAX>(lds, q, n_here * G, actions + (size_t)g0 * G * stride, stride);
 
-    const int gl = (int)(((float)tid + 0.5f) * (1.0f / (float)pairs));     // group within the block
+    const int gl = (int)(((float)tid + 0.5f) * (1.0f / (float)q.lanes));   // group within the block
     if (gl < n_here) {
         int i, j;
-        pair_members(tid - gl * pairs, G, &i, &j);
-        unsigned wanted = 0;                          // bit k: prefix length k + 1 is asked for
-        for (int l = 0; l < lens.n; ++l) wanted |= 1u << (lens.len[l] - 1);
-        unsigned pv = 0xFFFFFFFFu, mv = 0, res[4] = {0, 0, 0, 0};
+        pair_members(tid - gl * q.lanes, G, &i, &j);
+        unsigned pv = 0xFFFFFFFFu, mv = 0;
+        LaneSums sum;
         constexpr int STEP = KMAX % 8 ? 4 : 8;        // rows at a time
-        int32_t b[DIRECT ? KMAX : 4];
-        if constexpr (DIRECT) prefix_symbols<KMAX>(lds, gl * G + j, 0, b);
+        int32_t b[KMAX];
+        prefix_symbols<KMAX>(lds, gl * G + j, 0, b);
 #pragma unroll
         for (int r0 = 0; r0 < KMAX; r0 += STEP) {
             if (r0 < q.L) {                           // uniform
                 unsigned eq[STEP];
-                if constexpr (DIRECT) {
-                    int32_t a[STEP];
-                    prefix_symbols<KMAX>(lds, gl * G + i, r0, a);
-                    prefix_equal<KMAX>(a, b, eq);
-                } else {
-                    prefix_masks8<KMAX>(lds, q, off, gl * G + i, gl * G + j, r0, eq);
-                }
+                int32_t a[STEP];
+                prefix_symbols<KMAX>(lds, gl * G + i, r0, a);
+                prefix_equal<KMAX>(a, b, eq);
 #pragma unroll
                 for (int t = 0; t < STEP; ++t) {
                     prefix_row(eq[t], pv, mv);
-                    if ((wanted >> (r0 + t)) & 1u) {  // uniform
-                        const unsigned d = (unsigned)prefix_cell(r0 + t + 1, r0 + t + 1, pv, mv);
-#pragma unroll
-                        for (int l = 0; l < 8; ++l)
-                            if (l < lens.n && lens.len[l] == r0 + t + 1) res[l >> 1] += d << (16 * (l & 1));
-                    }
+                    if ((wanted >> (r0 + t)) & 1u)    // uniform
+                        sum.add(s_sum, q.groups, gl, wanted, r0 + t + 1, (unsigned)prefix_cell(r0 + t + 1, r0 + t + 1, pv, mv));
                 }
             }
         }
-#pragma unroll
-        for (int l = 0; l < 4; ++l)
-            if (2 * l < lens.n) atomicAdd(&s_sum[l][gl], res[l]);
     }
     __syncthreads();
-
-    for (int i = tid; i < lens.n * n_here; i += blockDim.x) {
-        const int l = i / n_here, g = i - l * n_here;
-        const int s = (int)((s_sum[l >> 1][g] >> (16 * (l & 1))) & 0xFFFFu);
-        if (sums) sums[(size_t)l * n_groups + g0 + g] = s;
-        if (retire) retire[(size_t)l * n_groups + g0 + g] = (uint8_t)(s < lens.bound[l]);
-    }
+    write_sums(s_sum, q.groups, n_here, g0, n_groups, lens, wanted, sums, retire);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -190,22 +262,34 @@ int launch_gate(const int32_t *actions, int n_groups, int G, int stride, const G
     if (n_groups <= 0) return SR_OK;
     int maxlen = 0;
     for (int l = 0; l < lens.n; ++l) maxlen = lens.len[l] > maxlen ? lens.len[l] : maxlen;
-    const int pairs = G * (G - 1) / 2;
-    const bool direct = prefix_direct(n_groups, G, maxlen, 6);
-    const int kmax = maxlen <= 4 ? 4 : maxlen <= 8 ? 8 : maxlen <= 12 && direct ? 12 : maxlen <= 16 ? 16 : maxlen <= 24 ? 24 : 32;
     PrefixGeom q{};
-    if (!prefix_geometry(n_groups, G, maxlen, kmax, direct, kGateLds, 0, &q)) return SR_E_ARG;
-    const size_t lds = prefix_lds(q, q.groups, kmax, direct).total;
-    dim3 grid((n_groups + q.groups - 1) / q.groups), block(q.threads);
-#define SR_GATE(K, DIRECT) \
-    gate_kernel<K, DIRECT><<<grid, block, lds, stream>>>(actions, n_groups, stride, pairs, q, lens, sums, retire)
-    switch (kmax) {                       // up to eight steps there are no tables
-        case 4: SR_GATE(4, true); break;
-        case 8: SR_GATE(8, true); break;
-        case 12: SR_GATE(12, true); break;
-        case 16: if (direct) SR_GATE(16, true); else SR_GATE(16, false); break;
-        case 24: if (direct) SR_GATE(24, true); else SR_GATE(24, false); break;
-        default: if (direct) SR_GATE(32, true); else SR_GATE(32, false); break;
+    if (!prefix_direct(n_groups, G, maxlen, 6)) {
+        // Beyond 16 steps a lane with two pairs has twice the instructions: one pair where that still leaves no more than eight
+        // wavefronts per compute unit (300 groups of 8, 32 steps: 6.6 us, 7.6 with two; 2000 groups 6.2)
+        const int kind = maxlen <= 16 ? PREFIX_TWO16 : (long long)n_groups * G * (G - 1) / 2 <= 256 * 512 ? PREFIX_ONE32 : PREFIX_TWO32;
+        if (!prefix_geometry_tables(n_groups, G, maxlen, kind, kGateLds, kGateHashLds, 16, &q)) return SR_E_ARG;
+        const dim3 grid(ceil_div(n_groups, q.groups)), block(q.threads);
+        const size_t lds = q.total + 16 * q.groups;
+#define SR_GATE(KIND) gate_table_kernel<KIND><<<grid, block, lds, stream>>>(actions, n_groups, stride, q, lens, sums, retire)
+        if (kind == PREFIX_TWO16) SR_GATE(PREFIX_TWO16);
+        else if (kind == PREFIX_TWO32) SR_GATE(PREFIX_TWO32);
+        else SR_GATE(PREFIX_ONE32);
+#undef SR_GATE
+        SR_HIP(hipGetLastError());
+        return SR_OK;
+    }
+    const int kmax = maxlen <= 4 ? 4 : maxlen <= 8 ? 8 : maxlen <= 12 ? 12 : maxlen <= 16 ? 16 : maxlen <= 24 ? 24 : 32;
+    if (!prefix_geometry_direct(n_groups, G, maxlen, kmax, kGateLds, 16, &q)) return SR_E_ARG;
+    const dim3 grid(ceil_div(n_groups, q.groups)), block(q.threads);
+    const size_t lds = q.total + 16 * q.groups;
+#define SR_GATE(K) gate_direct_kernel<K><<<grid, block, lds, stream>>>(actions, n_groups, stride, q, lens, sums, retire)
+    switch (kmax) {
+        case 4: SR_GATE(4); break;
+        case 8: SR_GATE(8); break;
+        case 12: SR_GATE(12); break;
+        case 16: SR_GATE(16); break;
+        case 24: SR_GATE(24); break;
+        default: SR_GATE(32); break;
     }
 #undef SR_GATE
     SR_HIP(hipGetLastError());

@@ -1,17 +1,22 @@
 // Edit distances of action prefixes, bit-parallel (shared by the gate and the signals kernels).
 //
 // The table of two sequences a, b of at most 32 symbols is advanced one row (one symbol of a) at a time with its
-// vertical differences held as two 32-bit masks -- Myers' bit-vector recurrence (J. ACM 46, 1999) in Hyyro's form
-// for the global distance: eleven 32-bit operations per row instead of about five per cell.  Bit u of the masks is
+// vertical differences held as bit masks -- Myers' bit-vector recurrence (J. ACM 46, 1999) in Hyyro's form
+// for the global distance: eleven operations per row instead of about five per cell.  Bit u of the masks is
 // column u + 1; information only moves from lower to higher bits, so cell (r, c) can be read for every c whatever
 // the columns beyond it hold, and one pass serves every prefix length.
 //
 // What the recurrence needs per row is the mask of positions of b that equal a[r].  Two ways to have it:
-// Tables.  A workgroup builds, once per group, the table mask[member][symbol]; a row's mask is then one LDS read.  Symbols
-// that all lie in the table's range index it as they are (ids below 64 always do: action ids of a turn are tokens modulo a
-// small number).  Where some symbol of the workgroup does not, every symbol is first replaced by the index of one element
-// of its group that holds it (hash insertion in LDS, compare-and-swap on the slot; which of several equal elements
-// wins does not matter).
+//
+// Tables.  A workgroup builds mask[symbol][member] for its groups.  A symbol's masks of all members lie side by side, so one
+// LDS read gives a lane those of two neighbouring members, and the lane runs one a against both: the pairs (i, 2q) and
+// (i, 2q + 1).  Up to 16 steps the two masks are the halves of one register, and a step of the recurrence is one bitwise or
+// packed 16-bit instruction for both pairs; beyond, two registers.  A group of eight takes 16 lanes instead of 28.
+// Symbols below 64 (action ids of a turn are tokens modulo a small number) index the tables as they are.  Where some
+// symbol of the workgroup is not, every symbol is first replaced by the index of one element of its group that holds it
+// (hash insertion in LDS, compare-and-swap on the slot; which of several equal elements wins does not matter); such tables
+// are larger, and the groups of a workgroup take turns in the LDS, as many at a time as fit.
+//
 // Comparison.  Every pair compares its 2 * K symbols in registers: 2 * K * K more instructions per pair, and nothing to build.
 // prefix_direct says which.
 #pragma once
@@ -19,131 +24,319 @@
 
 namespace sr {
 
-// Sizes of one workgroup's tables; L = longest requested prefix, KMAX = its size class (4, 8, 12, 16, 24 or 32).
-struct PrefixGeom {
-    int G, L;
-    int slots_log2;       // hash slots per group: a power of two, at least twice its elements
-    int row_stride;       // mask entries per member: G * L (one per element of the group), at least 64, padded to an odd
-                          // number of LDS words so that one symbol's entries of several members lie in several banks
-    int groups, threads;  // groups per workgroup and its size
-};
-
-__host__ __device__ inline int prefix_mask_bytes(int kmax) { return kmax <= 16 ? 2 : 4; }
 // row of the directly compared symbols: an odd multiple of 16 bytes, the rows of sixteen consecutive members in different banks
 __host__ __device__ constexpr int prefix_act_stride(int kmax) { return kmax % 8 == 4 ? kmax : kmax + 4; }
-// byte offsets of [masks | slots | act | id] for n groups, or of act alone; every part a multiple of 16 bytes
-struct PrefixLds {
-    int slots, act, id, total;
-};
-__host__ __device__ inline PrefixLds prefix_lds(const PrefixGeom &q, int n, int kmax, bool direct) {
-    PrefixLds o{};
-    if (direct) {
-        o.total = n * q.G * prefix_act_stride(kmax) * 4;
-        return o;
-    }
-    o.slots = round_up(n * q.G * q.row_stride * prefix_mask_bytes(kmax), 16);
-    o.act = o.slots + (n << q.slots_log2) * 4;
-    o.id = o.act + round_up(n * q.G * q.L * 4, 16);
-    o.total = o.id + n * q.G * kmax * 2;
-    return o;
-}
 
-// Compare, or build tables?  Up to eight steps the comparisons cost less than zeroing and filling a table, for every group size
-// (65 536 groups of 8, 5 steps: gate 17.6 us; with tables 18.7, 26 where symbols lie beyond their range; 3 members: 7.8, 8.3 and
-// 19).  Longer prefixes share a table among G - 1 pairs: up to `few` members comparing is cheaper still where the groups
-// fill the chip (65 536 groups of 5, 12 steps: gate 14 us, tables 17 and 29; groups of 3: signals 18, tables 28 and 38; 8
-// members: gate 41 against 33), and a long chain in too few wavefronts where they do not (64 groups of 3, 32 steps:
-// gate 10.0 us, tables 7.7; 16 384 groups of 2: 8.8 and 7.8).
+// Compare, or build tables?  The symbols are not known here, so both kinds count.  Up to eight steps comparing costs little more
+// than tables of symbols in their range and much less than hashing (65 536 groups of 8, 5 steps: gate 20.5 us; with tables 17.8
+// and 31; 3 members: 6.3, 7.9 and 13).  Longer prefixes share a table among G - 1 pairs: up to `few` members comparing is
+// still the better of the two where the groups fill the chip (65 536 groups of 5, 12 steps: gate 17.5 us, tables 15.3 and 32), but
+// not in too few wavefronts (2000 groups of 5, 32 steps: gate 6.1 with tables; 64 groups of 3 10.0 by comparison and 7.7).
 inline bool prefix_direct(int n_groups, int G, int L, int few) {
     return L <= 8 || (G <= few && (long long)n_groups * G >= 1500LL * L);
 }
 
-// Groups per workgroup: the count that fills whole wavefronts of pair lanes best (28 pairs: nine groups leave 4 of 256
-// lanes idle) within 256 lanes and `lds_limit` bytes of tables plus `extra` bytes per group.  A few groups (an episode's
+// How a workgroup lays out its groups; L = longest requested prefix.
+struct PrefixGeom {
+    int G, L, Q;          // Q = member pairs: columns of the tables
+    int groups, threads;  // groups per workgroup and its size
+    int lanes;            // lanes per group: its pairs when comparing, (member, member pair) combinations with tables
+    // tables only: bytes of LDS
+    int row_bytes;        // one symbol's masks
+    int body;             // offset of the tables, behind the element ids [member][16 or 32] (16 bits: symbol * row_bytes)
+    int slots_log2;       // hash slots per group: a power of two, at least twice its elements
+    int hash_groups;      // groups that take part in a round where symbols are hashed
+    int total;
+};
+constexpr int kPrefixSyms = 64;         // table rows of a group whose symbols need no hashing
+
+// How a lane runs its pairs: two in the halves of a register (up to 16 steps), two in a register each, or one.  The last takes
+// more lanes and a shorter chain of instructions each: for launches that do not fill the chip.
+enum PrefixKind { PREFIX_TWO16, PREFIX_TWO32, PREFIX_ONE32 };
+__host__ __device__ constexpr int prefix_steps(int kind) { return kind == PREFIX_TWO16 ? 16 : 32; }
+// a group's tables when its symbols are hashed: a row per element, the slots, the symbols themselves
+__host__ __device__ inline int prefix_hash_rows(const PrefixGeom &q) { return q.G * q.L * q.row_bytes; }
+__host__ __device__ inline int prefix_hash_bytes(const PrefixGeom &q) {
+    return round_up(prefix_hash_rows(q), 16) + (4 << q.slots_log2) + round_up(q.G * q.L * 4, 16);
+}
+
+// Groups per workgroup: the count that fills whole wavefronts of lanes best within 256 lanes.  A few groups (an episode's
 // gate) are spread over the compute units first: no workgroup takes more than its share of 512.
-inline bool prefix_geometry(int n_groups, int G, int L, int kmax, bool direct, int lds_limit, int extra, PrefixGeom *q) {
-    const int pairs = G * (G - 1) / 2;
+inline bool prefix_geometry_direct(int n_groups, int G, int L, int kmax, int lds_limit, int extra, PrefixGeom *q) {
+    *q = PrefixGeom{};
     q->G = G;
     q->L = L;
-    q->slots_log2 = 4;
-    while ((1 << q->slots_log2) < 2 * G * L) ++q->slots_log2;
-    const int per_word = 4 / prefix_mask_bytes(kmax);
-    q->row_stride = (ceil_div(G * L > 64 ? G * L : 64, per_word) | 1) * per_word;
-    q->groups = 0;
+    q->lanes = G * (G - 1) / 2;
     double best = 0.0;
-    for (int n = 1; n * pairs <= 256 && n <= ceil_div(n_groups, 512); ++n) {
-        if (prefix_lds(*q, n, kmax, direct).total + n * extra > lds_limit) break;
-        const double use = (double)(n * pairs) / round_up(n * pairs, 64);
+    for (int n = 1; n * q->lanes <= 256 && n <= ceil_div(n_groups, 512); ++n) {
+        if (n * (G * prefix_act_stride(kmax) * 4 + extra) > lds_limit) break;
+        const double use = (double)(n * q->lanes) / round_up(n * q->lanes, 64);
         if (use >= best) {
             best = use;
             q->groups = n;
         }
     }
-    // lanes for the pairs, and no more than eight elements a lane while the tables are built (small groups have more
+    q->total = q->groups * G * prefix_act_stride(kmax) * 4;
+    // lanes for the pairs, and no more than eight elements a lane while the symbols are staged (small groups have more
     // elements than pairs: 16384 groups of 2 with 32 arbitrary symbols take the gate 10.5 us, 25.5 with 64 lanes)
-    const int lanes = q->groups * pairs, build = ceil_div(q->groups * G * (kmax <= 16 ? kmax : 32), 8);
+    const int lanes = q->groups * q->lanes, build = ceil_div(q->groups * G * (kmax <= 16 ? kmax : 32), 8);
     q->threads = round_up(lanes > build ? lanes : build, 64);
     if (q->threads > 256) q->threads = 256;
     return q->groups > 0;
 }
 
+constexpr int kPrefixVecs = 4;          // 16-byte pieces of the members' rows that a lane loads at most
+inline bool prefix_geometry_tables(int n_groups, int G, int L, int kind, int lds_limit, int hash_lds, int extra, PrefixGeom *q) {
+    *q = PrefixGeom{};
+    q->G = G;
+    q->L = L;
+    q->Q = ceil_div(G, 2);
+    q->lanes = kind == PREFIX_ONE32 ? G * (G - 1) / 2 : q->Q * q->Q - (G & 1);
+    q->row_bytes = q->Q * (kind == PREFIX_TWO16 ? 4 : 8);
+    q->slots_log2 = 4;
+    while ((1 << q->slots_log2) < 2 * G * L) ++q->slots_log2;
+    const int steps = prefix_steps(kind), hash = prefix_hash_bytes(*q);
+    auto body = [&](int n) { const int b = n * kPrefixSyms * q->row_bytes; return round_up(b > hash ? b : hash, 16); };
+    double best = 0.0;
+    for (int n = 1; n * q->lanes <= 256 && n * G * (steps / 4) <= 256 * kPrefixVecs && n <= ceil_div(n_groups, 512); ++n) {
+        if (n * (G * steps * 2 + extra) + body(n) > lds_limit) break;
+        const double use = (double)(n * q->lanes) / round_up(n * q->lanes, 64);
+        if (use >= best) {
+            best = use;
+            q->groups = n;
+        }
+    }
+    if (q->groups == 0) return false;
+    q->body = round_up(q->groups * G * steps * 2, 16);
+    // hashed symbols: all groups at once where that costs no workgroup its place; otherwise two at least
+    const int all = q->groups * hash, most = lds_limit - q->groups * extra - q->body;
+    int room = hash_lds - q->groups * extra - q->body;
+    if (room < 2 * hash) room = 2 * hash;
+    if (room > most || ceil_div(n_groups, q->groups) <= 512) room = most;
+    int bytes = round_up(room < all ? room / hash * hash : all, 16);
+    if (bytes < body(q->groups)) bytes = body(q->groups);
+    q->hash_groups = bytes / hash;
+    if (q->hash_groups > q->groups) q->hash_groups = q->groups;
+    q->total = q->body + bytes;
+    const int lanes = q->groups * q->lanes, build = ceil_div(q->groups * G * steps, ceil_div(n_groups, q->groups) <= 1024 ? 2 : 8);
+    q->threads = round_up(lanes > build ? lanes : build, 64);
+    if (q->threads > 256) q->threads = 256;
+    return true;
+}
+
 #ifdef __HIPCC__
-// x / d for 0 <= x < 2^14 and 1 <= d <= 32, inv = 1.0f / d: the distance of (x + 1/2) / d from an integer is at least 1/64,
+// x / d for 0 <= x < 2^14 and 1 <= d <= 64, inv = 1.0f / d: the distance of (x + 1/2) / d from an integer is at least 1/128,
 // far beyond the rounding of two 32-bit operations on values below 2^14
 __device__ __forceinline__ int small_div(int x, float inv) { return (int)(((float)x + 0.5f) * inv); }
 
-// Fill the tables for `rows` members starting at `src` ([rows][stride] in global memory).  All threads of the workgroup
-// take part; ends with a barrier.
-template <int KMAX>
-__device__ __forceinline__ void prefix_build(char *lds, const PrefixGeom &q, const PrefixLds &off, int rows,
-                                             const int32_t *__restrict__ src, int stride) {
-    constexpr int KP = KMAX <= 16 ? 16 : 32;                     // lanes per member
-    unsigned *masks = (unsigned *)lds;
-    uint16_t *id = (uint16_t *)(lds + off.id);
-    int32_t *act = (int32_t *)(lds + off.act);
-    const int tid = threadIdx.x, nt = blockDim.x;
-    auto mark = [&](int r, int c, unsigned sym) {
-        id[r * KMAX + c] = (uint16_t)sym;
-        const int m = r * q.row_stride + (int)sym;
-        if constexpr (KMAX <= 16) atomicOr(&masks[m >> 1], (1u << c) << (16 * (m & 1)));
-        else atomicOr(&masks[m], 1u << c);
-    };
-    for (int i = tid; i < off.slots / 16; i += nt) ((uint4 *)lds)[i] = make_uint4(0, 0, 0, 0);
-    __syncthreads();
-    int fits = 1;
-    for (int e0 = tid; e0 < rows * KP; e0 += 4 * nt) {           // four loads in flight per lane
-        unsigned v[4];
+// ---------------------------------------------------------------------------------------------
+// tables
+// ---------------------------------------------------------------------------------------------
+// The masks of a lane's two pairs: halves of one register (16 steps), or a register each (32 steps)
+template <int KIND>
+struct PrefixBits;
+template <>
+struct PrefixBits<PREFIX_TWO16> {
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    unsigned x;
+    __device__ static PrefixBits all(unsigned v) { return {v}; }
+    __device__ unsigned half(int h) const { return h ? x >> 16 : x & 0xFFFFu; }
+};
+template <>
+struct PrefixBits<PREFIX_TWO32> {
+    unsigned x[2];
+    __device__ static PrefixBits all(unsigned v) { return {{v, v}}; }
+    __device__ unsigned half(int h) const { return x[h]; }
+};
+template <>
+struct PrefixBits<PREFIX_ONE32> {
+    unsigned x;
+    __device__ static PrefixBits all(unsigned v) { return {v}; }
+    __device__ unsigned half(int) const { return x; }
+};
+
+// One row of the table: eq = positions of b that equal the row's symbol of a.
+__device__ __forceinline__ void prefix_row(unsigned eq, unsigned &pv, unsigned &mv) {
+    const unsigned xv = eq | mv;
+    const unsigned xh = (((eq & pv) + pv) ^ pv) | eq;
+    const unsigned ph = ((mv | ~(xh | pv)) << 1) | 1u;
+    const unsigned mh = (pv & xh) << 1;
+    pv = mh | ~(xv | ph);
+    mv = ph & xv;
+}
+__device__ __forceinline__ void prefix_row(PrefixBits<PREFIX_ONE32> eq, PrefixBits<PREFIX_ONE32> &pv, PrefixBits<PREFIX_ONE32> &mv) {
+    prefix_row(eq.x, pv.x, mv.x);
+}
+__device__ __forceinline__ void prefix_row(PrefixBits<PREFIX_TWO32> eq, PrefixBits<PREFIX_TWO32> &pv, PrefixBits<PREFIX_TWO32> &mv) {
+    prefix_row(eq.x[0], pv.x[0], mv.x[0]);
+    prefix_row(eq.x[1], pv.x[1], mv.x[1]);
+}
+__device__ __forceinline__ void prefix_row(PrefixBits<PREFIX_TWO16> eq, PrefixBits<PREFIX_TWO16> &pv, PrefixBits<PREFIX_TWO16> &mv) {
+    typedef PrefixBits<PREFIX_TWO16>::u16x2 u16x2;
+    auto v = [](unsigned x) { return __builtin_bit_cast(u16x2, x); };
+    auto u = [](u16x2 x) { return __builtin_bit_cast(unsigned, x); };
+    const unsigned xv = eq.x | mv.x;
+    const unsigned xh = (u(v(eq.x & pv.x) + v(pv.x)) ^ pv.x) | eq.x;
+    const unsigned ph = u(v(mv.x | ~(xh | pv.x)) * (unsigned short)2 + (unsigned short)1);
+    const unsigned mh = u(v(pv.x & xh) << (unsigned short)1);
+    pv.x = mh | ~(xv | ph);
+    mv.x = ph & xv;
+}
+// bits 0 .. n-1, 0 <= n <= 32
+__device__ __forceinline__ unsigned low_bits(int n) { return n >= 32 ? 0xFFFFFFFFu : (1u << n) - 1u; }
+// cell (r, c) once row r is complete
+__device__ __forceinline__ int prefix_cell(int r, int c, unsigned pv, unsigned mv) {
+    return r + __popc(pv & low_bits(c)) - __popc(mv & low_bits(c));
+}
+// cells (K, K) of a lane's two pairs, added; the second only if there is one
+__device__ __forceinline__ unsigned prefix_cells(int K, bool second, PrefixBits<PREFIX_TWO16> pv, PrefixBits<PREFIX_TWO16> mv) {
+    const unsigned m = low_bits(K) * (second ? 0x10001u : 1u);
+    return (unsigned)((second ? 2 * K : K) + __popc(pv.x & m) - __popc(mv.x & m));
+}
+__device__ __forceinline__ unsigned prefix_cells(int K, bool, PrefixBits<PREFIX_ONE32> pv, PrefixBits<PREFIX_ONE32> mv) {
+    return (unsigned)prefix_cell(K, K, pv.x, mv.x);
+}
+__device__ __forceinline__ unsigned prefix_cells(int K, bool second, PrefixBits<PREFIX_TWO32> pv, PrefixBits<PREFIX_TWO32> mv) {
+    return (unsigned)(prefix_cell(K, K, pv.x[0], mv.x[0]) + (second ? prefix_cell(K, K, pv.x[1], mv.x[1]) : 0));
+}
+
+// Pair p of a group of G -> (i, j), i < j, pairs in the order (0,1), (0,2), ..., (G-2,G-1): the largest i with
+// i * (2G - 1 - i) / 2 <= p.  (b - sqrt(b^2 - 8p)) / 2, b = 2G - 1, is an integer exactly at the first pair of an i;
+// the added 1/128 keeps rounding from missing it and is too little to reach the next one (G <= 16).
+__device__ __forceinline__ void pair_members(int p, int G, int *i, int *j) {
+    const float b = (float)(2 * G - 1);
+    const int a = (int)((b - __builtin_amdgcn_sqrtf(b * b - 8.0f * (float)p)) * 0.5f + 0.0078125f);
+    *i = a;
+    *j = p - a * (2 * G - 1 - a) / 2 + a + 1;
+}
+// Lane p of a group -> its member i and the (first) member j it is compared with.  With two pairs a lane, the members 2q and
+// 2q + 1 have the lanes q^2 .. q^2 + 2q, i = 0 .. 2q: the first is no pair when i == 2q (its distance is 0), the second when the
+// group ends at 2q.
+template <int KIND>
+__device__ __forceinline__ void prefix_lane(int p, int G, int *i, int *j) {
+    if constexpr (KIND == PREFIX_ONE32) {
+        pair_members(p, G, i, j);
+    } else {
+        const int q = (int)__builtin_amdgcn_sqrtf((float)p + 0.5f);
+        *i = p - q * q;
+        *j = 2 * q;
+    }
+}
+
+// The members' rows as every lane holds them while the tables are built: 16-byte pieces tid, tid + threads, ... of [row][16 or
+// 32 steps].  Steps from L on are 0.  `tail`: the last row of the whole input, behind which nothing may be read.
+template <int KIND>
+struct PrefixRows {
+    static constexpr int kSteps = prefix_steps(KIND), kRowVecs = kSteps / 4;
+    int32_t v[kPrefixVecs][4];
+
+    __device__ static bool used(int u, int rows) { return u * (int)blockDim.x < rows * kRowVecs; }       // uniform
+    // lanes beyond the last row take it once more
+    __device__ static int row(int u, int rows) { return min((int)(threadIdx.x + u * blockDim.x) / kRowVecs, rows - 1); }
+    __device__ static int step(int u) { return ((int)(threadIdx.x + u * blockDim.x) % kRowVecs) * 4; }
+
+    __device__ __forceinline__ void load(const PrefixGeom &q, int rows, const int32_t *__restrict__ src, int stride, int tail) {
+        typedef int32_t piece __attribute__((ext_vector_type(4), aligned(4)));
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int e = e0 + u * nt, r = e / KP, c = e % KP;
-            v[u] = r < rows && c < q.L ? (unsigned)src[(size_t)r * stride + c] : 0u;
+        for (int u = 0; u < kPrefixVecs; ++u) {
+            if (!used(u, rows)) break;
+            const int r = row(u, rows), c = step(u);
+            const int32_t *p = src + (size_t)r * stride + c;
+            piece x = {0, 0, 0, 0};
+            if (c < q.L) {
+                if (c + 4 <= stride && r != tail) x = *(const piece *)p;
+                else x = piece{p[0], p[min(1, q.L - 1 - c)], p[min(2, q.L - 1 - c)], p[min(3, q.L - 1 - c)]};
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[u][e] = c + e < q.L ? x[e] : 0;
         }
+    }
+    // every symbol of this lane's indexes the tables as it is
+    __device__ __forceinline__ bool fits(int rows) const {
+        unsigned any = 0;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int e = e0 + u * nt, r = e / KP, c = e % KP;
-            if (r < rows && c < q.L) {
-                act[r * q.L + c] = (int32_t)v[u];
-                if (v[u] < (unsigned)q.row_stride) mark(r, c, v[u]);
-                else fits = 0;
+        for (int u = 0; u < kPrefixVecs; ++u) {
+            if (!used(u, rows)) break;
+            any |= (unsigned)(v[u][0] | v[u][1]) | (unsigned)(v[u][2] | v[u][3]);
+        }
+        return any < (unsigned)kPrefixSyms;
+    }
+};
+
+// byte offset of the word that holds member m's mask within a table row, and the mask's shift in it
+template <int KIND>
+__device__ __forceinline__ int prefix_column(int m) { return KIND == PREFIX_TWO16 ? (m >> 1) * 4 : m * 4; }
+template <int KIND>
+__device__ __forceinline__ int prefix_shift(int m) { return KIND == PREFIX_TWO16 ? (m & 1) * 16 : 0; }
+
+__device__ __forceinline__ void prefix_zero(char *lds, int from, int bytes) {
+    for (int i = threadIdx.x * 16; i < bytes; i += blockDim.x * 16) *(uint4 *)(lds + from + i) = make_uint4(0, 0, 0, 0);
+}
+
+// Do all lanes' symbols index the tables as they are?  A barrier, behind which the tables are zero too.
+__device__ __forceinline__ bool prefix_all_fit(bool fits) {
+    __shared__ int s_fits[4];
+    s_fits[threadIdx.x >> 6] = __all(fits) ? 1 : 0;              // every lane of a wavefront writes the same
+    __syncthreads();
+    bool every = true;
+#pragma unroll 1
+    for (int w = 0; w < (int)blockDim.x >> 6; ++w) every &= s_fits[w] != 0;
+    return __builtin_amdgcn_readfirstlane(every);
+}
+
+// Tables of all groups from symbols that need no hashing; the tables are zero.  The caller's barrier follows.
+template <int KIND>
+__device__ __forceinline__ void prefix_mark(char *lds, const PrefixGeom &q, int rows, const PrefixRows<KIND> &x) {
+    typedef PrefixRows<KIND> R;
+    const float inv_G = 1.0f / (float)q.G;
+#pragma unroll
+    for (int u = 0; u < kPrefixVecs; ++u) {
+        if (!R::used(u, rows)) break;
+        const int r = R::row(u, rows), c = R::step(u), g = small_div(r, inv_G), m = r - g * q.G;
+        unsigned id[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) id[e] = (unsigned)(x.v[u][e] * q.row_bytes);
+        *(uint2 *)(lds + (r * R::kSteps + c) * 2) = make_uint2(id[0] | id[1] << 16, id[2] | id[3] << 16);
+        if (c < q.L) {                               // steps from L on set bits of symbol 0 that nobody looks at
+            char *t = lds + q.body + g * (kPrefixSyms * q.row_bytes) + prefix_column<KIND>(m);
+            const unsigned bit = 1u << (c + prefix_shift<KIND>(m));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) atomicOr((unsigned *)(t + id[e]), bit << e);
+        }
+    }
+}
+
+// Tables of the groups g0 .. g0 + n - 1 from any symbols, in the place of the last round's.  Ends with a barrier.
+template <int KIND>
+__device__ __forceinline__ void prefix_hash(char *lds, const PrefixGeom &q, int rows, const PrefixRows<KIND> &x, int g0, int n) {
+    typedef PrefixRows<KIND> R;
+    const int tid = threadIdx.x, nt = blockDim.x, GL = q.G * q.L, r0 = g0 * q.G, here = min(n * q.G, rows - r0);
+    const int slots_at = q.body + q.hash_groups * round_up(prefix_hash_rows(q), 16);
+    unsigned *slots = (unsigned *)(lds + slots_at);
+    int32_t *act = (int32_t *)(lds + slots_at + (q.hash_groups * 4 << q.slots_log2));
+    prefix_zero(lds, q.body, slots_at - q.body + (q.hash_groups * 4 << q.slots_log2));        // masks and slots
+#pragma unroll
+    for (int u = 0; u < kPrefixVecs; ++u) {
+        if (!R::used(u, rows)) break;
+        const int r = R::row(u, rows) - r0, c = R::step(u);
+        if (r >= 0 && r < here) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (c + e < q.L) act[r * q.L + c + e] = x.v[u][e];
+                else ((uint16_t *)lds)[(r0 + r) * R::kSteps + c + e] = 0;
             }
         }
     }
-    if (__syncthreads_and(fits)) return;
-
-    unsigned *slots = (unsigned *)(lds + off.slots);
-    const int GL = q.G * q.L;
-    const float inv_G = 1.0f / (float)q.G;
-    for (int i = tid; i < off.act / 16; i += nt) ((uint4 *)lds)[i] = make_uint4(0, 0, 0, 0);   // masks and slots
     __syncthreads();
+    const float inv_G = 1.0f / (float)q.G;
     const unsigned wrap = (1u << q.slots_log2) - 1u;
-    for (int e = tid; e < rows * KP; e += nt) {
-        const int r = e / KP, c = e % KP;
-        if (c >= q.L) continue;
-        const int g = small_div(r, inv_G);
+    const float inv_L = 1.0f / (float)q.L;
+    for (int e = tid; e < here * q.L; e += nt) {
+        const int r = small_div(e, inv_L), c = e - r * q.L, g = small_div(r, inv_G), m = r - g * q.G;
         const int32_t v = act[r * q.L + c];
         unsigned *table = slots + ((size_t)g << q.slots_log2);
         const int32_t *ga = act + g * GL;
-        const unsigned mine = (unsigned)((r - g * q.G) * q.L + c) + 1u;      // element within the group; 0 = free slot
+        const unsigned mine = (unsigned)(m * q.L + c) + 1u;                  // element within the group; 0 = free slot
         unsigned rep = mine;
         unsigned h = ((unsigned)v * 0x9E3779B1u) >> (32 - q.slots_log2);
         for (unsigned probe = 0; probe <= wrap; ++probe) {                   // at most half of the slots are ever taken
@@ -152,11 +345,36 @@ __device__ __forceinline__ void prefix_build(char *lds, const PrefixGeom &q, con
             if (ga[old - 1u] == v) { rep = old; break; }
             h = (h + 1u) & wrap;
         }
-        mark(r, c, rep - 1u);
+        const unsigned id = (rep - 1u) * (unsigned)q.row_bytes;              // below 512 * 64
+        ((uint16_t *)lds)[(r0 + r) * R::kSteps + c] = (uint16_t)id;
+        atomicOr((unsigned *)(lds + q.body + g * round_up(prefix_hash_rows(q), 16) + prefix_column<KIND>(m) + id),
+                 1u << (c + prefix_shift<KIND>(m)));
     }
     __syncthreads();
 }
 
+// Eight steps of member row `r`, from step c on (a multiple of eight): table rows as byte offsets
+template <int KIND>
+__device__ __forceinline__ void prefix_ids8(const char *lds, int r, int c, unsigned (&id)[8]) {
+    const uint4 raw = *(const uint4 *)(lds + (r * prefix_steps(KIND) + c) * 2);
+    const unsigned w[4] = {raw.x, raw.y, raw.z, raw.w};
+#pragma unroll
+    for (int t = 0; t < 8; ++t) id[t] = t & 1 ? w[t >> 1] >> 16 : w[t >> 1] & 0xFFFFu;
+}
+// the lane's masks of table row `id` (byte offset); `column`: the group's tables and the word of member j
+template <int KIND>
+__device__ __forceinline__ PrefixBits<KIND> prefix_masks(const char *column, unsigned id) {
+    if constexpr (KIND != PREFIX_TWO32) {
+        return {*(const unsigned *)(column + id)};
+    } else {
+        const uint2 m = *(const uint2 *)(column + id);
+        return {{m.x, m.y}};
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// comparison
+// ---------------------------------------------------------------------------------------------
 // Without tables: the symbols of `rows` members as they are, [row][prefix_act_stride].  Entries from L on hold anything: they
 // only reach bits and rows that nobody reads.  Ends with a barrier.
 template <int KMAX>
@@ -215,52 +433,6 @@ __device__ __forceinline__ void prefix_equal(const int32_t (&a)[N], const int32_
         }
         m[i] = m0; m[i + 1] = m1; m[i + 2] = m2; m[i + 3] = m3;
     }
-}
-
-// positions of member `row` that hold the symbol `id`
-template <int KMAX>
-__device__ __forceinline__ unsigned prefix_mask(const char *lds, const PrefixGeom &q, int row, int id) {
-    const int m = row * q.row_stride + id;
-    if constexpr (KMAX <= 16) return ((const uint16_t *)lds)[m];
-    else return ((const unsigned *)lds)[m];
-}
-
-// The masks of rows r0 .. r0 + 7 of the table of members ri (a) and rj (b), requested together so that the LDS latency is
-// paid once; rows from L on, which nobody asks for, get 0.
-template <int KMAX>
-__device__ __forceinline__ void prefix_masks8(const char *lds, const PrefixGeom &q, const PrefixLds &off, int ri, int rj,
-                                              int r0, unsigned (&eq)[8]) {
-    const uint4 raw = *(const uint4 *)(lds + off.id + (ri * KMAX + r0) * 2);      // eight 16-bit ids
-    const unsigned w[4] = {raw.x, raw.y, raw.z, raw.w};
-#pragma unroll
-    for (int t = 0; t < 8; ++t)
-        eq[t] = r0 + t < q.L ? prefix_mask<KMAX>(lds, q, rj, (int)((w[t >> 1] >> (16 * (t & 1))) & 0xFFFFu)) : 0u;
-}
-
-// Pair p of a group of G -> (i, j), i < j, pairs in the order (0,1), (0,2), ..., (G-2,G-1): the largest i with
-// i * (2G - 1 - i) / 2 <= p.  (b - sqrt(b^2 - 8p)) / 2, b = 2G - 1, is an integer exactly at the first pair of an i;
-// the added 1/128 keeps rounding from missing it and is too little to reach the next one (G <= 16).
-__device__ __forceinline__ void pair_members(int p, int G, int *i, int *j) {
-    const float b = (float)(2 * G - 1);
-    const int a = (int)((b - __builtin_amdgcn_sqrtf(b * b - 8.0f * (float)p)) * 0.5f + 0.0078125f);
-    *i = a;
-    *j = p - a * (2 * G - 1 - a) / 2 + a + 1;
-}
-
-// One row of the table: eq = positions of b that equal the row's symbol of a.
-__device__ __forceinline__ void prefix_row(unsigned eq, unsigned &pv, unsigned &mv) {
-    const unsigned xv = eq | mv;
-    const unsigned xh = (((eq & pv) + pv) ^ pv) | eq;
-    const unsigned ph = ((mv | ~(xh | pv)) << 1) | 1u;
-    const unsigned mh = (pv & xh) << 1;
-    pv = mh | ~(xv | ph);
-    mv = ph & xv;
-}
-// bits 0 .. n-1, 0 <= n <= 32
-__device__ __forceinline__ unsigned low_bits(int n) { return n >= 32 ? 0xFFFFFFFFu : (1u << n) - 1u; }
-// cell (r, c) once row r is complete
-__device__ __forceinline__ int prefix_cell(int r, int c, unsigned pv, unsigned mv) {
-    return r + __popc(pv & low_bits(c)) - __popc(mv & low_bits(c));
 }
 #endif
 

@@ -10,7 +10,7 @@
 //   - the decisions  d_K < d_L  (Eq. 2) and  d_K < d_L or tau_K >= tau_H  (Eq. 3) in integers.
 //
 // Work decomposition, as for the equal-length gate: one lane owns one pair and runs its table bit-parallel
-// (prefix_match.h).  Cell (r, c) of the table of two sequences is the distance of their prefixes of lengths r and c, so
+// (prefix_pairs.h).  Cell (r, c) of the table of two sequences is the distance of their prefixes of lengths r and c, so
 // one pass serves every requested K: the lane reads cell (K, len_j) when row K is complete, and keeps the masks of row
 // end_i for the K beyond it.  The same equality masks give the bigrams: bit u of eq_t & (eq_{t+1} >> 1) says that b holds
 // bigram t of a at position u; a bigram position is the first occurrence of its bigram in every prefix that contains it,
@@ -25,7 +25,7 @@
 // registers: 18 against 33 us.
 #include <type_traits>
 
-#include "prefix_match.h"
+#include "prefix_pairs.h"
 
 static_assert(sizeof(sr_signals_t) == 64, "sr_signals_t is part of the C boundary");
 

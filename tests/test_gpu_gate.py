@@ -138,3 +138,25 @@ def test_gate_by_comparison(n_groups, G, lens):
     s_ref, r_ref = oracle.gate_batch(acts, lens, 0.25)
     s_gpu, r_gpu = run_gpu(acts, lens, 0.25)
     assert np.array_equal(s_gpu, s_ref) and np.array_equal(r_gpu, r_ref)
+
+
+@pytest.mark.parametrize("n_groups,G,lens,stride", [(9001, 8, [15, 10, 5], 15), (9001, 8, [16], 16), (8193, 7, [9, 13], 13), (2049, 16, [16, 9], 30),
+                                                    (4097, 12, [9], 9), (4099, 8, [32, 17], 32), (601, 11, [29], 29), (1025, 16, [32], 33),
+                                                    (70000, 2, [24], 25), (3, 5, [9], 9), (1, 2, [18], 18)])
+@pytest.mark.parametrize("beyond", [False, True])
+def test_gate_tables(n_groups, G, lens, stride, beyond):
+    """Tables of symbols in their range (0 .. 63) and, with one symbol just beyond it in every hundredth group, workgroups that hash and
+    workgroups that do not in one launch: up to 16 steps, beyond 16 with one and with two pairs a lane; rows that end inside a
+    16-byte piece, no element behind the last one; odd groups, a ragged last workgroup, a prefix length asked for twice."""
+    rng = np.random.default_rng(n_groups + G)
+    lead = rng.integers(0, 64, size=(n_groups, 1, stride))
+    acts = np.where(rng.random((n_groups, G, stride)) < 0.8, lead, rng.integers(0, 64, size=(n_groups, G, stride))).astype(np.int32)
+    acts[0] = acts[0, :1]                           # a group that agrees
+    acts[-1, :, 0], acts[-1, 0, -1] = 63, 0
+    if beyond:
+        acts[::100, 0, lens[0] - 1] = 64
+        acts[50::100, G - 1, 0] = -1
+    lens = lens + lens[:1]
+    s_ref, r_ref = oracle.gate_batch(acts, lens, 0.25)
+    s_gpu, r_gpu = run_gpu(acts, lens, 0.25)
+    assert np.array_equal(s_gpu, s_ref) and np.array_equal(r_gpu, r_ref)
