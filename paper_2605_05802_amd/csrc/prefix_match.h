@@ -30,8 +30,9 @@ __host__ __device__ constexpr int prefix_act_stride(int kmax) { return kmax % 8 
 // Compare, or build tables?  The symbols are not known here, so both kinds count.  Up to eight steps comparing costs little more
 // than tables of symbols in their range and much less than hashing (65 536 groups of 8, 5 steps: gate 20.5 us; with tables 17.8
 // and 31; 3 members: 6.3, 7.9 and 13).  Longer prefixes share a table among G - 1 pairs: up to `few` members comparing is
-// still the better of the two where the groups fill the chip (65 536 groups of 5, 12 steps: gate 17.5 us, tables 15.3 and 32), but
-// not in too few wavefronts (2000 groups of 5, 32 steps: gate 6.1 with tables; 64 groups of 3 10.0 by comparison and 7.7).
+// still the better of the two where the groups fill the chip (65 536 groups of 5, 12 steps: gate 17.5 us, tables 15.3 and 32;
+// groups of 3: signals 30, tables 32 and 49), but not in too few wavefronts (64 groups of 3, 32 steps: gate 10.0 us by
+// comparison, 7.7 with tables).
 inline bool prefix_direct(int n_groups, int G, int L, int few) {
     return L <= 8 || (G <= few && (long long)n_groups * G >= 1500LL * L);
 }
@@ -292,13 +293,13 @@ __device__ __forceinline__ void prefix_mark(char *lds, const PrefixGeom &q, int 
 #pragma unroll
     for (int u = 0; u < kPrefixVecs; ++u) {
         if (!R::used(u, rows)) break;
-        const int r = R::row(u, rows), c = R::step(u), g = small_div(r, inv_G), m = r - g * q.G;
+        const int r = R::row(u, rows), c = R::step(u), g = small_div(r, inv_G), m = r - __mul24(g, q.G);
         unsigned id[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) id[e] = (unsigned)(x.v[u][e] * q.row_bytes);
+        for (int e = 0; e < 4; ++e) id[e] = (unsigned)__mul24(x.v[u][e], q.row_bytes);
         *(uint2 *)(lds + (r * R::kSteps + c) * 2) = make_uint2(id[0] | id[1] << 16, id[2] | id[3] << 16);
         if (c < q.L) {                               // steps from L on set bits of symbol 0 that nobody looks at
-            char *t = lds + q.body + g * (kPrefixSyms * q.row_bytes) + prefix_column<KIND>(m);
+            char *t = lds + q.body + __mul24(g, kPrefixSyms * q.row_bytes) + prefix_column<KIND>(m);
             const unsigned bit = 1u << (c + prefix_shift<KIND>(m));
 #pragma unroll
             for (int e = 0; e < 4; ++e) atomicOr((unsigned *)(t + id[e]), bit << e);

@@ -9,23 +9,25 @@
 //     observation counts, the step-K action entropy and the number of finished members;
 //   - the decisions  d_K < d_L  (Eq. 2) and  d_K < d_L or tau_K >= tau_H  (Eq. 3) in integers.
 //
-// Work decomposition, as for the equal-length gate: one lane owns one pair and runs its table bit-parallel
-// (prefix_pairs.h).  Cell (r, c) of the table of two sequences is the distance of their prefixes of lengths r and c, so
-// one pass serves every requested K: the lane reads cell (K, len_j) when row K is complete, and keeps the masks of row
-// end_i for the K beyond it.  The same equality masks give the bigrams: bit u of eq_t & (eq_{t+1} >> 1) says that b holds
-// bigram t of a at position u; a bigram position is the first occurrence of its bigram in every prefix that contains it,
-// so one mask of first occurrences per member and one mask per position of a serve every K.
-// What is per member (first occurrences, step-K counts, entropy terms) is done by one lane per member and K, what is
-// per pair (quotients included) by the pair lanes; one thread per (K, group) is left with adding the pair terms in pair
-// order (i, j), i < j, and the entropy terms in member order, so that the floating-point results do not depend on
-// scheduling.
-// Bound: vector ALU (70 % busy).  65 536 groups of 8 with early finishers, K = 5, 10, 15: 126 us; 361 us with one table cell
-// at a time, K * K compares per pair for the bigrams and the quotients left to the thread of a (K, group).  At 32 steps
-// 272 against 1266 us, at G = 16 and 16 steps 112 against 990 us (16 384 groups).  Groups of 3, 12 steps, symbols compared in
-// registers: 18 against 33 us.
-#include <type_traits>
+// Work decomposition, as for the equal-length gate: a lane runs the tables of one pair, or of two, bit-parallel
+// (prefix_match.h).  Cell (r, c) of the table of two sequences is the distance of their prefixes of lengths r and c, so
+// one pass serves every requested K: once row K is complete the lane reads cell (K, len_j), or, if a has ended at row
+// end_i < K, where the lane's state stays as it was at that row, cell (end_i, len_j).  The same equality masks give the
+// bigrams: bit u of eq_t & (eq_{t+1} >> 1) says that b holds bigram t of a at position u, so the positions of b whose bigram
+// the first r steps of a hold are a running OR, and the bigrams that the two prefixes share are those positions of it that
+// are the first occurrence of their bigram in b.
+// What is per member (first occurrences, step-K counts) is done by a lane per member (and K): the members that hold its
+// step-K action are one column of the symbol's table row.  Logarithms and quotients of counts come from small tables of a
+// workgroup.  Four wavefronts add the terms of every (K, group): pair terms in pair order (i, j), i < j, entropy terms in
+// member order, so that the floating-point results do not depend on scheduling.
+// Bound: vector ALU (70 % busy, 1570 instructions per wavefront: 300 of them the recurrence, 160 the evaluation at the three K, 150
+// the quotients, 200 the sums), with four workgroups per compute unit by LDS.  65 536 groups of 8 with early finishers, K = 5,
+// 10, 15: 64 us; 126 with a lane per pair, masks of one member per LDS read, bigrams compared position by position for
+// every K, a division per pair and K and a logarithm per member and K.  32 steps 122 against 417 us, 16 384 groups of 16 with
+// 16 steps 70 against 153, one group of 8 with 15 steps 9.8 against 12.5.
+#include <stddef.h>
 
-#include "prefix_pairs.h"
+#include "prefix_match.h"
 
 static_assert(sizeof(sr_signals_t) == 64, "sr_signals_t is part of the C boundary");
 
@@ -33,267 +35,462 @@ namespace sr {
 namespace {
 
 constexpr int kSigThreads = 256;
-constexpr int kSigLds = 52 * 1024;                   // three workgroups per compute unit where the shape allows it
-constexpr int kSigLdsMost = 64 * 1024;               // G = 16 with 32 steps and 8 prefix lengths needs 58.6 KiB
+constexpr int kSigLds = 52 * 1024;                   // LDS of symbols, tables and sums: three workgroups per compute unit or more
+constexpr int kSigHashLds = 40 * 1024;               // ... where symbols are hashed: four
+constexpr int kSigTerms = 24 * 1024;                 // LDS that the quotients may take: three K of sixteen groups of 8 at once
 constexpr int kSigMaxLens = 8;
 constexpr long long kLcm32 = 144403552893600LL;      // lcm(1..32)
 
 struct SigLens {
     int n;
-    int len[kSigMaxLens];
+    unsigned wanted;                  // bit k: prefix length k + 1 is asked for
+    unsigned long long packed;        // six bits per length: an argument that lanes index comes through the slowest memory there is
     long long d_bound;                // d_K < d_L  <=>  lev_scaled < d_bound
     long long tau_num;                // tau_K >= tau_H  <=>  n_done * 1e6 >= tau_num * G
-    long long lcm_over[33];           // lcm(1..32) / n
+    __device__ int len(int l) const { return (int)(packed >> (6 * l)) & 63; }
+    __device__ int slot(int K) const { return __popc(wanted & ((1u << (K - 1)) - 1u)); }     // index among the distinct lengths
 };
 
-// What the workgroup keeps behind the prefix tables: byte offsets, 8-byte arrays first.
+// What the workgroup keeps behind symbols and tables: byte offsets, 8-byte arrays first.
 struct SigLds {
-    int d, j, h, out, pair, obs, hold, end, first, total;
+    int out, lcm, recip, p, log_p, repeats, code, obs, at, end, first, hold, total;
+    int code_stride;                  // pairs of a group, made odd: the groups' terms in different banks
 };
-__host__ __device__ inline SigLds sig_lds(int G, int pairs, int groups, int n_lens) {
+__host__ __device__ inline SigLds sig_lds(int G, int groups, int n_lens) {
     SigLds o;
-    const int P = n_lens * groups * pairs, R = n_lens * groups * G;
+    const int pairs = G * (G - 1) / 2, members = groups * G;
+    o.code_stride = pairs | 1;
     o.out = 0;                                    // [K][group] sr_signals_t
-    o.d = o.out + n_lens * groups * 64;           // [K][pair] double: distance / longer length
-    o.j = o.d + P * 8;                            // [K][pair] double: Jaccard term
-    o.h = o.j + P * 8;                            // [K][member] double: log p of an action, at its first holder
-    o.obs = o.h + R * 8;                          // [K][member] o_{i,K}
-    o.hold = o.obs + R * 4;                       // [K][member] see below
-    o.end = o.hold + R * 4;                       // [member]
-    o.first = o.end + groups * G * 4;             // [member] positions of first occurrences of bigrams
-    o.pair = o.first + groups * G * 4;            // [K][pair] 16 bits: distance | longer length << 6 | equal prefixes << 12
-    o.total = o.pair + round_up(P * 2, 16);
+    o.lcm = o.out + n_lens * groups * 64;         // lcm(1..32) / n
+    o.recip = o.lcm + 33 * 8;                     // 1 / n, n = 1 .. 63 (0: 0)
+    o.p = o.recip + 64 * 8;                       // 0, then c / n, 1 <= c <= n <= G
+    o.log_p = o.p + (G * (G + 1) / 2 + 1) * 8;    // log(c / n)
+    o.repeats = o.log_p + (G * (G + 1) / 2 + 1) * 8;    // [K][group] members whose prefix an earlier member has
+    o.code = o.repeats + n_lens * groups * 4;     // [distinct K][group][pair] see SigCode
+    o.obs = o.code + n_lens * groups * o.code_stride * 4;        // [K][member] o_{i,K}
+    o.at = o.obs + n_lens * members * 4;          // [K][group] bits of the members that reach step K | finished by K << 24
+    o.end = o.at + n_lens * groups * 4;           // [member]
+    o.first = o.end + members * 4;                // [member] positions of first occurrences of bigrams
+    o.hold = o.first + members * 4;               // [K][member] holders of its step-K action if it is the first of them, | 32 the
+    o.total = round_up(o.hold + n_lens * members * 2, 16);       // first to hold its observation (16 bits)
     return o;
 }
 
-template <int KMAX, bool DIRECT>
+// One pair's integers at one K; distance 0 means equal prefixes
+struct SigCode {
+    __device__ static unsigned pack(int lev, int longer, int inter, int uni, unsigned j) {
+        return (unsigned)(lev | longer << 6 | inter << 12) | ((unsigned)uni << 17 | j << 23);
+    }
+    __device__ static int lev(unsigned c) { return c & 63; }
+    __device__ static int longer(unsigned c) { return (c >> 6) & 63; }       // of the two prefixes
+    __device__ static int inter(unsigned c) { return (c >> 12) & 31; }       // shared bigrams
+    __device__ static int uni(unsigned c) { return (c >> 17) & 63; }         // bigrams of either
+    __device__ static int j(unsigned c) { return c >> 23; }                  // the pair's second member
+};
+
+// Members of a group as bits: even ones 0 .. 7, odd ones 16 .. 23, so that a word with the masks of two members adds its two bits
+// with one shift
+__device__ __forceinline__ int member_bit(int m) { return (m >> 1) + 16 * (m & 1); }
+__device__ __forceinline__ unsigned members_before(int m) { return ((1u << ((m + 1) >> 1)) - 1u) | ((1u << (m >> 1)) - 1u) << 16; }
+constexpr unsigned kMembers = 0xFF00FFu;
+
+// a / b correctly rounded for whole numbers 0 <= a, b < 64 (0 / 0: 0), r = the rounded 1 / b: the remainder of a * r is exact,
+// and one correction with a rounded reciprocal gives the rounded quotient (Markstein 1990; every such a, b compared with the division)
+__device__ __forceinline__ double small_quotient(int a, int b, double r) {
+    const double q = (double)a * r;
+    return __builtin_fma(__builtin_fma(-q, (double)b, (double)a), r, q);
+}
+
+// positions of b whose bigram is that of a at rows t, t + 1: eq_t & (eq_{t+1} >> 1), in every mask
+template <int KIND>
+__device__ __forceinline__ PrefixBits<KIND> bigram_bits(PrefixBits<KIND> eq, PrefixBits<KIND> next) {
+    if constexpr (KIND == PREFIX_TWO16) {
+        typedef typename PrefixBits<KIND>::u16x2 u16x2;
+        return {eq.x & __builtin_bit_cast(unsigned, __builtin_bit_cast(u16x2, next.x) >> (unsigned short)1)};
+    } else if constexpr (KIND == PREFIX_TWO32) {
+        return {{eq.x[0] & (next.x[0] >> 1), eq.x[1] & (next.x[1] >> 1)}};
+    } else {
+        return {eq.x & (next.x >> 1)};
+    }
+}
+template <int KIND>
+__device__ __forceinline__ PrefixBits<KIND> bits_or(PrefixBits<KIND> a, PrefixBits<KIND> b) {
+    if constexpr (KIND == PREFIX_TWO32) return {{a.x[0] | b.x[0], a.x[1] | b.x[1]}};
+    else return {a.x | b.x};
+}
+template <int KIND>
+__device__ __forceinline__ PrefixBits<KIND> bits_select(bool c, PrefixBits<KIND> a, PrefixBits<KIND> b) {
+    if constexpr (KIND == PREFIX_TWO32) return {{c ? a.x[0] : b.x[0], c ? a.x[1] : b.x[1]}};
+    else return {c ? a.x : b.x};
+}
+
+// The state of a lane's table(s): vertical differences, positions of b whose bigrams a holds, the last row's equality mask
+template <int KIND>
+struct SigState {
+    typedef PrefixBits<KIND> Bits;
+    Bits pv = Bits::all(0xFFFFFFFFu), mv = Bits::all(0), held = Bits::all(0), last = Bits::all(0);
+    // row r (1-based) of a sequence that ends at `end`
+    __device__ __forceinline__ void row(Bits eq, int r, int end) {
+        Bits p = pv, m = mv;
+        prefix_row(eq, p, m);
+        const Bits h = bits_or<KIND>(held, bigram_bits<KIND>(last, eq));
+        const bool live = r <= end;
+        pv = bits_select<KIND>(live, p, pv);
+        mv = bits_select<KIND>(live, m, mv);
+        held = bits_select<KIND>(live, h, held);
+        last = eq;
+    }
+    // the pair (., j) in half h at step K; li, lj: lengths of its prefixes, na: distinct bigrams of the first
+    __device__ __forceinline__ unsigned code(int h, unsigned j, int li, int lj, int na, unsigned first_b) const {
+        const unsigned cols = KIND == PREFIX_TWO16 ? (1u << lj) - 1u : low_bits(lj);
+        const unsigned b = first_b & (cols >> 1);     // a prefix of length n holds bigram positions 0 .. n-2
+        const int lev = li + __popc(pv.half(h) & cols) - __popc(mv.half(h) & cols);
+        const int inter = __popc(held.half(h) & b);
+        return SigCode::pack(lev, max(li, lj), inter, na + __popc(b) - inter, j);
+    }
+};
+
+// KMAX == 0: equality masks from tables; otherwise a pair a lane, symbols compared in registers, at most KMAX steps
+template <int KIND, int KMAX>
 __global__ __launch_bounds__(kSigThreads) void signals_kernel(
     const int32_t *__restrict__ actions, const int32_t *__restrict__ obs, const int32_t *__restrict__ end_step,
-    int n_groups, int stride, int pairs, PrefixGeom q, SigLens lens, sr_signals_t *__restrict__ out) {
-    extern __shared__ __align__(16) char lds[];
-    __shared__ long long s_lcm[33];                          // lcm(1..32) / n
-    const int tid = threadIdx.x, nt = blockDim.x, G = q.G, NL = lens.n;
+    int n_groups, int stride, PrefixGeom q, SigLens lens, int sums_at, int terms_at_once, sr_signals_t *__restrict__ out) {
+    extern __shared__ __align__(16) char lds[];      // symbols and tables, later the quotients; from sums_at on SigLds
+    constexpr bool TABLES = KMAX == 0;
+    const int tid = threadIdx.x, nt = blockDim.x, G = q.G, NL = lens.n, L = q.L;
     const int g0 = blockIdx.x * q.groups;
     const int n_here = min(q.groups, n_groups - g0);
-    const int rows = n_here * G, n_pairs = q.groups * pairs, n_rows = q.groups * G;
-    const PrefixLds off = prefix_lds(q, q.groups, KMAX, DIRECT);
-    const SigLds so = sig_lds(G, pairs, q.groups, NL);
-    char *mine = lds + off.total;
+    const int rows = n_here * G, n_rows = q.groups * G, pairs = G * (G - 1) / 2;
+    const SigLds so = sig_lds(G, q.groups, NL);
+    char *mine = lds + sums_at;
     sr_signals_t *s_out = (sr_signals_t *)(mine + so.out);
-    double *s_d = (double *)(mine + so.d), *s_j = (double *)(mine + so.j), *s_h = (double *)(mine + so.h);
+    double *s_lcm = (double *)(mine + so.lcm), *s_recip = (double *)(mine + so.recip), *s_p = (double *)(mine + so.p), *s_log_p = (double *)(mine + so.log_p);
+    unsigned *s_code = (unsigned *)(mine + so.code), *s_at = (unsigned *)(mine + so.at), *s_first = (unsigned *)(mine + so.first);
+    unsigned *s_repeats = (unsigned *)(mine + so.repeats);
     int32_t *s_obs = (int32_t *)(mine + so.obs), *s_end = (int32_t *)(mine + so.end);
-    // holders of the member's step-K action if it is the first of them, | 32 the first to hold its observation
-    // | 64 its prefix reaches step K | 128 it has finished by step K
-    int *s_hold = (int *)(mine + so.hold);
-    unsigned *s_first = (unsigned *)(mine + so.first);
-    uint16_t *s_pair = (uint16_t *)(mine + so.pair);
-    const float inv_G = 1.0f / (float)G, inv_rows = 1.0f / (float)rows;
-
-    if (tid < 33) s_lcm[tid] = lens.lcm_over[tid];
-    for (int i = tid; i < rows; i += nt) s_end[i] = end_step ? max(end_step[(size_t)g0 * G + i], 0) : 0x7FFFFFFF;
-    for (int w = tid; w < NL * rows; w += nt) {
-        const int l = min((int)(((float)w + 0.5f) * inv_rows), NL - 1), r = w - l * rows;
-        s_obs[l * n_rows + r] = obs ? obs[((size_t)g0 * G + r) * stride + lens.len[l] - 1] : 0;
-    }
+    uint16_t *s_hold = (uint16_t *)(mine + so.hold);
+    const float inv_G = 1.0f / (float)G;
     const int32_t *src = actions + (size_t)g0 * G * stride;
-    if constexpr (DIRECT) prefix_stage<KMAX>(lds, q, rows, src, stride);
-    else prefix_build<KMAX>(lds, q, off, rows, src, stride);
-    // what stands for a member's step: its symbol, or the element of the group that represents it
-    using Step = std::conditional_t<DIRECT, int32_t, uint16_t>;
-    constexpr int SS = DIRECT ? prefix_act_stride(KMAX) : KMAX;
-    const Step *steps = (const Step *)(lds + (DIRECT ? off.act : off.id));
-
-    if constexpr (DIRECT) {
-        // One lane per member: the positions that are the first occurrence of their bigram
-        for (int r = tid; r < rows; r += nt) {
-            int32_t b[KMAX];
-            prefix_symbols<KMAX>(lds, r, 0, b);
-            unsigned eq[KMAX], first = 0;
-            prefix_equal<KMAX>(b, b, eq);
+    PrefixRows<KIND> x;
+    if constexpr (TABLES) x.load(q, rows, src, stride, g0 + n_here == n_groups ? rows - 1 : -1);
+    // what else comes from global memory is requested before anything is waited for
+    const float inv_rows = 1.0f / (float)rows;
+    auto obs_item = [&](int w, int *l, int *r) { *l = min((int)(((float)w + 0.5f) * inv_rows), NL - 1); *r = w - *l * rows; };
+    auto load_obs = [&](int w) {
+        int l, r;
+        obs_item(w, &l, &r);
+        return obs ? obs[((size_t)g0 * G + r) * stride + lens.len(l) - 1] : 0;
+    };
+    auto load_end = [&](int i) { return end_step ? max(end_step[(size_t)g0 * G + i], 0) : 0x7FFFFFFF; };
+    int32_t obs_v[2] = {0, 0}, end_v = 0;
 #pragma unroll
-            for (int t = 0; t + 1 < KMAX; ++t) first |= (eq[t] & (eq[t + 1] >> 1) & low_bits(t)) == 0u ? 1u << t : 0u;
-            s_first[r] = first & low_bits(q.L - 1);
-        }
+    for (int u = 0; u < 2; ++u)
+        if (tid + u * nt < NL * rows) obs_v[u] = load_obs(tid + u * nt);
+    if (tid < rows) end_v = load_end(tid);
+    for (int w = tid; w < NL * q.groups; w += nt) {
+        s_repeats[w] = 0;
+        s_out[w].lev_scaled = 0;
+        s_out[w].lev_sum = 0;
+    }
+    if constexpr (TABLES) prefix_zero(lds, q.body, q.groups * kPrefixSyms * q.row_bytes);
+    for (int w = tid, u = 0; w < NL * rows; w += nt, ++u) {
+        int l, r;
+        obs_item(w, &l, &r);
+        s_obs[l * n_rows + r] = u == 0 ? obs_v[0] : u == 1 ? obs_v[1] : load_obs(w);
+    }
+    for (int i = tid; i < rows; i += nt) s_end[i] = i == tid ? end_v : load_end(i);
+    bool direct = true;                               // all groups in one round
+    if constexpr (TABLES) {
+        direct = prefix_all_fit(x.fits(rows));
     } else {
-        // One lane per (member, position): is it the first occurrence of its bigram?  A member's lanes are neighbours, so
-        // the wavefront's vote holds the members' masks side by side.
-        constexpr int KP = KMAX <= 16 ? 16 : 32;
-        for (int e0 = 0; e0 < rows * KP; e0 += nt) {             // whole wavefronts take part
-            const int e = e0 + tid, r = e / KP, t = e % KP;
-            bool first = false;
-            if (r < rows && t + 1 < q.L) {
-                const unsigned here = prefix_mask<KMAX>(lds, q, r, steps[r * SS + t]);
-                const unsigned next = prefix_mask<KMAX>(lds, q, r, steps[r * SS + t + 1]);
-                first = (here & (next >> 1) & low_bits(t)) == 0u;
-            }
-            const unsigned long long vote = __ballot(first);
-            if (t == 0 && r < rows) s_first[r] = (unsigned)(vote >> (tid & 63)) & low_bits(KP);
-        }
+        prefix_stage<KMAX ? KMAX : 8>(lds, q, rows, src, stride);
     }
-    // One lane per (member, K): members that reach step K, and whether this one is the first to hold its action or
-    // observation
-    for (int w = tid; w < NL * rows; w += nt) {
-        const int l = min((int)(((float)w + 0.5f) * inv_rows), NL - 1), r = w - l * rows, g = small_div(r, inv_G), K = lens.len[l];
-        int hold = s_end[r] <= K ? 128 : 0;
-        if (s_end[r] >= K) {
-            const unsigned a = steps[r * SS + K - 1];
-            const int32_t o = s_obs[l * n_rows + r];
-            int n_at = 0, count = 0;
-            bool first_act = true, first_obs = true;
+    // members that reach step K, and how many have finished by then
+    for (int w = tid; w < NL * n_here; w += nt) {
+        const int l = min((int)(((float)w + 0.5f) * (1.0f / (float)n_here)), NL - 1), g = w - l * n_here, K = lens.len(l);
+        unsigned at = 0, done = 0;
 #pragma unroll 4
-            for (int i = g * G; i < g * G + G; ++i) {
-                const bool at = s_end[i] >= K, same = at & ((unsigned)steps[i * SS + K - 1] == a);
-                n_at += at ? 1 : 0;
-                count += same ? 1 : 0;
-                first_act &= !((i < r) & same);
-                first_obs &= !((i < r) & at & (s_obs[l * n_rows + i] == o));
-            }
-            hold |= 64 | (first_act ? count : 0) | (first_obs ? 32 : 0);
-            if (first_act) s_h[l * n_rows + r] = log((double)count / (double)n_at);
+        for (int m = 0; m < G; ++m) {
+            const int end = s_end[g * G + m];
+            at |= (end >= K ? 1u : 0u) << member_bit(m);
+            done += end <= K ? 1u : 0u;
         }
-        s_hold[l * n_rows + r] = hold;
+        s_at[l * q.groups + g] = at | done << 24;
     }
-    __syncthreads();
 
-    // per pair
-    const int gl = (int)(((float)tid + 0.5f) * (1.0f / (float)pairs));     // group within the block
-    if (gl < n_here) {
-        int i, j;
-        pair_members(tid - gl * pairs, G, &i, &j);
-        const int ri = gl * G + i, rj = gl * G + j;
-        const int ei = s_end[ri], ej = s_end[rj];
-        unsigned wanted = 0;                          // bit k: prefix length k + 1 is asked for
-        for (int l = 0; l < NL; ++l) wanted |= 1u << (lens.len[l] - 1);
-        int res[kSigMaxLens];
-#pragma unroll
-        for (int l = 0; l < kSigMaxLens; ++l) res[l] = 0;
+    // 1 / n, lcm(1..32) / n, c / n and log(c / n): the last wavefront, which often has no pairs, while the others run theirs
+    auto small_tables = [&] {
+        const int n = nt - 1 - tid;
+        const double r = n ? 1.0 / (double)n : 0.0;
+        s_recip[n] = r;
+        if (n < 33) s_lcm[n] = rint((double)kLcm32 * r);     // exact: below 2^48, the product off by less than 1/16
+        if (n == 0) s_p[0] = s_log_p[0] = 0.0;
+        for (int e = n; e < G * (G + 1) / 2; e += 64) {       // n * (n - 1) / 2 + c
+            const int n = (int)((1.0f + __builtin_amdgcn_sqrtf(8.0f * (float)e + 1.0f)) * 0.5f + 0.0078125f), c = e - n * (n - 1) / 2 + 1;
+            const double share = (double)c / (double)n;
+            s_p[e + 1] = share;
+            s_log_p[e + 1] = log(share);
+        }
+    };
+    const int gl = small_div(tid, 1.0f / (float)q.lanes);      // group within the block
+    int pi, pj;
+    prefix_lane<KIND>(tid - gl * q.lanes, G, &pi, &pj);
 
-        unsigned pv = 0xFFFFFFFFu, mv = 0, pv_end = 0xFFFFFFFFu, mv_end = 0;      // row 0: distance from the empty prefix
-        unsigned big[KMAX], eq_last = 0;              // big[t]: positions of b that hold bigram t of a
-        int32_t b[DIRECT ? KMAX : 4];
-        if constexpr (DIRECT) prefix_symbols<KMAX>(lds, rj, 0, b);
+    // groups s0 .. s0 + n - 1, `group_bytes` of tables each
+    auto evaluate = [&](int s0, int n, int group_bytes) __attribute__((always_inline)) {
+        const int r_lo = s0 * G, here = min(n * G, rows - r_lo);
+        auto table = [&](int g) { return lds + q.body + (g - s0) * group_bytes; };
+        // Half of the workgroup, a lane per member: the positions that are the first occurrence of their bigram
+        auto first_bigrams = [&](int r, int g, int m) __attribute__((always_inline)) {
+            unsigned again = 0, last = 0;
+            if constexpr (TABLES) {
+                const int shift = prefix_shift<KIND>(m);
+                const char *column = table(g) + prefix_column<KIND>(m);
+#pragma unroll 1
+                for (int t0 = 0; t0 < L; t0 += 8) {
+                    unsigned id[8], eq[8];
+                    prefix_ids8<KIND>(lds, r, t0, id);
 #pragma unroll
-        for (int r0 = 0; r0 < KMAX; r0 += 8) {
-            unsigned eq[8];
-            if (r0 < q.L) {                           // uniform
-                if constexpr (DIRECT) {
-                    int32_t a[8];
-                    prefix_symbols<KMAX>(lds, ri, r0, a);
-                    prefix_equal<KMAX>(a, b, eq);
-                } else {
-                    prefix_masks8<KMAX>(lds, q, off, ri, rj, r0, eq);
-                }
+                    for (int t = 0; t < 8; ++t) eq[t] = *(const unsigned *)(column + id[t]) >> shift;
 #pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const int r = r0 + t + 1;
-                    prefix_row(eq[t], pv, mv);
-                    if (ei == r) { pv_end = pv; mv_end = mv; }
-                    if ((wanted >> (r - 1)) & 1u) {   // uniform
-                        const int d = prefix_cell(r, min(r, ej), pv, mv);
-#pragma unroll
-                        for (int l = 0; l < kSigMaxLens; ++l)
-                            if (l < NL && lens.len[l] == r) res[l] = d;
+                    for (int t = 0; t < 8; ++t) {
+                        // bigram t0 + t - 1 at an earlier position
+                        const unsigned before = last & (eq[t] >> 1) & ((1u << (t0 + t) >> 1) - 1u);
+                        again |= (min(before, 1u) << (t0 + t)) >> 1;
+                        last = eq[t];
                     }
                 }
             } else {
+                int32_t b[KMAX ? KMAX : 8];
+                unsigned eq[KMAX ? KMAX : 8];
+                prefix_symbols<KMAX ? KMAX : 8>(lds, r, 0, b);
+                prefix_equal<KMAX ? KMAX : 8>(b, b, eq);
 #pragma unroll
-                for (int t = 0; t < 8; ++t) eq[t] = 0;
+                for (int t = 0; t + 1 < KMAX; ++t) again |= min(eq[t] & (eq[t + 1] >> 1) & low_bits(t), 1u) << t;
             }
-            if (r0 > 0) big[r0 - 1] = eq_last & (eq[0] >> 1);
-#pragma unroll
-            for (int t = 0; t < 7; ++t) big[r0 + t] = eq[t] & (eq[t + 1] >> 1);
-            eq_last = eq[7];
-        }
-        const unsigned first_a = s_first[ri], first_b = s_first[rj];
-#pragma unroll
-        for (int l = 0; l < kSigMaxLens; ++l) {
-            if (l < NL) {
-                const int K = lens.len[l], li = min(K, ei), lj = min(K, ej);
-                const int lev = ei < K ? prefix_cell(li, lj, pv_end, mv_end) : res[l];
-                // a prefix of length n holds bigram positions 0 .. n-2
-                const unsigned ma = low_bits(max(li - 1, 0)), mb = low_bits(max(lj - 1, 0));
-                unsigned held = 0;
-#pragma unroll
-                for (int t = 0; t < KMAX - 1; ++t) held |= (big[t] & mb) != 0u ? 1u << t : 0u;
-                const int inter = __popc(first_a & ma & held);
-                const int uni = __popc(first_a & ma) + __popc(first_b & mb) - inter;
-                const int longer = max(li, lj);
-                s_d[l * n_pairs + tid] = longer > 0 ? (double)lev / (double)longer : 0.0;
-                s_j[l * n_pairs + tid] = uni > 0 ? 1.0 - (double)inter / (double)uni : 0.0;
-                s_pair[l * n_pairs + tid] = (uint16_t)(lev | longer << 6 | (lev == 0 && li == lj ? 1 << 12 : 0));
+            s_first[r] = ~again & low_bits(L - 1);
+        };
+        // The other half, a lane per (member, K): is it the first to hold its action (and how many do), and its observation?
+        auto first_holders = [&](int l, int r, int g, int m) __attribute__((always_inline)) {
+            const int K = lens.len(l);
+            const unsigned at = s_at[l * q.groups + g] & kMembers;
+            const int32_t *go = s_obs + l * n_rows + g * G;
+            const int32_t o = go[m];
+            unsigned same = 0, same_obs = 0;
+            if constexpr (TABLES) {
+                const unsigned *row = (const unsigned *)(table(g) + ((const uint16_t *)lds)[r * PrefixRows<KIND>::kSteps + K - 1]);
+#pragma unroll 4
+                for (int c = 0; c < q.Q; ++c) {
+                    if constexpr (KIND == PREFIX_TWO16) same |= ((row[c] >> (K - 1)) & 0x10001u) << c;
+                    else same |= ((row[2 * c] >> (K - 1)) & 1u) << c | ((row[2 * c + 1] >> (K - 1)) & 1u) << (c + 16);
+                }
+            } else {
+                constexpr int SS = prefix_act_stride(KMAX ? KMAX : 8);
+                const int32_t *act = (const int32_t *)lds + g * G * SS + K - 1, a = act[m * SS];
+#pragma unroll 4
+                for (int i = 0; i < G; ++i) same |= (act[i * SS] == a ? 1u : 0u) << member_bit(i);
+            }
+#pragma unroll 4
+            for (int i = 0; i < G; ++i) same_obs |= (go[i] == o ? 1u : 0u) << member_bit(i);
+            const unsigned before = at & members_before(m);
+            int hold = ((same & before) == 0u ? __popc(same & at) : 0) | ((same_obs & before) == 0u ? 32 : 0);
+            if (!((at >> member_bit(m)) & 1u)) hold = 0;
+            s_hold[l * n_rows + r] = (uint16_t)hold;
+        };
+        int half = nt >> 7 << 6;                                 // whole wavefronts
+        if (here > nt - half || half == 0) half = 0;             // more members than that: all lanes do both in turn
+        if (half == 0 || tid < half) {
+            const float inv_here = 1.0f / (float)here;
+            for (int w = tid; w < NL * here; w += half ? half : nt) {
+                const int l = min((int)(((float)w + 0.5f) * inv_here), NL - 1), r = r_lo + w - l * here, g = small_div(r, inv_G);
+                first_holders(l, r, g, r - g * G);
             }
         }
+        if (tid >= half) {
+            for (int r = r_lo + tid - half; r < r_lo + here; r += nt - half) {
+                const int g = small_div(r, inv_G);
+                first_bigrams(r, g, r - g * G);
+            }
+        }
+        __syncthreads();
+        if (s0 == 0 && tid >= nt - 64) small_tables();
+
+        if (gl >= s0 && gl < min(s0 + n, n_here)) {
+            constexpr int HALVES = KIND == PREFIX_ONE32 ? 1 : 2;
+            const int ri = gl * G + pi, ei = s_end[ri];
+            const unsigned first_a = s_first[ri];
+            unsigned first_b[HALVES];
+            int ej[HALVES], at[HALVES];
+#pragma unroll
+            for (int h = 0; h < HALVES; ++h) {
+                const int j = pj + h, rj = gl * G + min(j, G - 1);
+                ej[h] = s_end[rj];
+                first_b[h] = s_first[rj];
+                at[h] = j > pi && j < G ? gl * so.code_stride + pi * (2 * G - 1 - pi) / 2 + j - pi - 1 : -1;
+            }
+            SigState<KIND> s;
+            auto store = [&](int K) __attribute__((always_inline)) {
+                unsigned *c = s_code + lens.slot(K) * (q.groups * so.code_stride);
+                const int li = min(K, ei), na = __popc(first_a & (low_bits(li) >> 1));
+                unsigned x[HALVES];
+#pragma unroll
+                for (int h = 0; h < HALVES; ++h) x[h] = s.code(h, pj + h, li, min(K, ej[h]), na, first_b[h]);
+#pragma unroll
+                for (int h = 0; h < HALVES; ++h)
+                    if (HALVES == 1 || at[h] >= 0) c[at[h]] = x[h];
+            };
+            if constexpr (TABLES) {
+                const char *column = table(gl) + prefix_column<KIND>(pj);
+#pragma unroll 1
+                for (int r0 = 0; r0 < L; r0 += 8) {
+                    unsigned id[8];
+                    PrefixBits<KIND> eq[8];
+                    prefix_ids8<KIND>(lds, ri, r0, id);
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) eq[t] = prefix_masks<KIND>(column, id[t]);
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) {
+                        s.row(eq[t], r0 + t + 1, ei);
+                        if ((lens.wanted >> (r0 + t)) & 1u) store(r0 + t + 1);        // uniform
+                    }
+                }
+            } else {
+                int32_t b[KMAX ? KMAX : 8];
+                prefix_symbols<KMAX ? KMAX : 8>(lds, gl * G + pj, 0, b);
+#pragma unroll 1
+                for (int r0 = 0; r0 < L; r0 += 8) {
+                    unsigned eq[8];
+                    int32_t a[8];
+                    prefix_symbols<KMAX ? KMAX : 8>(lds, ri, r0, a);
+                    prefix_equal<KMAX ? KMAX : 8>(a, b, eq);
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) {
+                        s.row({eq[t]}, r0 + t + 1, ei);
+                        if ((lens.wanted >> (r0 + t)) & 1u) store(r0 + t + 1);        // uniform
+                    }
+                }
+            }
+        }
+    };
+    if constexpr (TABLES) {
+        if (direct) {
+            prefix_mark<KIND>(lds, q, rows, x);
+            __syncthreads();
+            evaluate(0, q.groups, kPrefixSyms * q.row_bytes);
+        } else {
+            for (int s0 = 0; s0 < n_here; s0 += q.hash_groups) {
+                __syncthreads();                      // nobody reads the tables of the round before
+                prefix_hash<KIND>(lds, q, rows, x, s0, q.hash_groups);
+                evaluate(s0, q.hash_groups, round_up(prefix_hash_rows(q), 16));
+            }
+        }
+    } else {
+        __syncthreads();
+        evaluate(0, q.groups, 0);
     }
     __syncthreads();
 
-    // Four sums per (K, group), a wavefront for each where the workgroup has four: pair terms in pair order, entropy
-    // terms in member order.
+    // The quotients of terms_at_once prefix lengths, in parallel, then the sums: those of quotients in pair order
     const int n_rec = NL * n_here, waves = nt >> 6;
-    const float inv_here = 1.0f / (float)n_here;
-    for (int kind = tid >> 6; kind < 4; kind += waves) {
-        for (int w = tid & 63; w < n_rec; w += 64) {
-            const int l = min((int)(((float)w + 0.5f) * inv_here), NL - 1), g = w - l * n_here;
-            sr_signals_t *o = s_out + l * q.groups + g;
-            if (kind < 2) {
-                const double *t = (kind == 0 ? s_d : s_j) + l * n_pairs + g * pairs;
-                double sum = 0.0;
+    const float inv_n = 1.0f / (float)n_here;
+    const int distinct = __popc(lens.wanted), per_len = q.groups * so.code_stride;
+    double *s_d = (double *)lds, *s_j = s_d + terms_at_once * per_len;
+    for (int u0 = 0; u0 < distinct; u0 += terms_at_once) {
+        const int n_terms = min(terms_at_once, distinct - u0) * per_len;
+        if (u0) __syncthreads();
+        for (int k = tid; k < n_terms; k += nt) {
+            const unsigned c = s_code[u0 * per_len + k];
+            const int longer = SigCode::longer(c), uni = SigCode::uni(c);
+            s_d[k] = small_quotient(SigCode::lev(c), longer, s_recip[longer]);
+            s_j[k] = uni > 0 ? 1.0 - small_quotient(SigCode::inter(c), uni, s_recip[uni]) : 0.0;
+        }
+        __syncthreads();
+        // a lane per (K, group), a wavefront for each kind of sum where the workgroup has four
+        for (int kind = tid >> 6; kind < (u0 ? 2 : 4); kind += waves) {
+            const int parts = kind == 2 && n_rec < 64 ? 64 / n_rec : 1;      // whole numbers: as many lanes as there are
+            const float inv_parts = 1.0f / (float)parts;
+            for (int w = tid & 63; w < n_rec * parts; w += 64) {
+                const int rec = (int)(((float)w + 0.5f) * inv_parts), l = min((int)(((float)rec + 0.5f) * inv_n), NL - 1), g = rec - l * n_here;
+                const int u = lens.slot(lens.len(l)), slot = l * q.groups + g;
+                sr_signals_t *o = s_out + slot;
+                if (kind < 2) {
+                    if (u < u0 || u >= u0 + terms_at_once) continue;
+                    const double *t = (kind == 0 ? s_d : s_j) + (u - u0) * per_len + g * so.code_stride;
+                    double sum = 0.0;
+#pragma unroll 8
+                    for (int k = 0; k < pairs; ++k) sum += t[k];
+                    sum /= (double)pairs;
+                    if (kind == 0) o->d_K = sum;
+                    else o->bigram_jaccard = sum;
+                } else if (kind == 2) {
+                    // at most 60 terms of at most lcm(1..32): whole numbers below 2^53, which 64-bit floats add exactly (and without
+                    // 64-bit multiplications)
+                    const unsigned *code = s_code + u * per_len + g * so.code_stride;
+                    long long scaled = 0;
+                    int lev_sum = 0;
+                    unsigned repeats = 0;             // members whose prefix an earlier member has
+                    for (int k = w - rec * parts; k < pairs;) {
+                        double some = 0.0;
+                        const int end = min(k + 60 * parts, pairs);
 #pragma unroll 4
-                for (int k = 0; k < pairs; ++k) sum += t[k];
-                sum /= (double)pairs;
-                if (kind == 0) o->d_K = sum;
-                else o->bigram_jaccard = sum;
-            } else if (kind == 2) {
-                const uint16_t *t = s_pair + l * n_pairs + g * pairs;
-                long long scaled = 0;
-                int lev_sum = 0;
-                unsigned repeats = 0;                 // members whose prefix an earlier member has
-                int i = 0, j = 1;
+                        for (; k < end; k += parts) {
+                            const unsigned c = code[k];
+                            const int lev = SigCode::lev(c);
+                            lev_sum += lev;
+                            some = __builtin_fma((double)lev, s_lcm[SigCode::longer(c)], some);
+                            repeats |= (lev == 0 ? 1u : 0u) << SigCode::j(c);
+                        }
+                        scaled += (long long)some;
+                    }
+                    if (parts == 1) {
+                        o->lev_scaled = scaled;
+                        o->lev_sum = lev_sum;
+                        s_repeats[slot] = repeats;
+                    } else {
+                        atomicAdd((unsigned long long *)&o->lev_scaled, (unsigned long long)scaled);
+                        atomicAdd(&o->lev_sum, lev_sum);
+                        atomicOr(&s_repeats[slot], repeats);
+                    }
+                } else {
+                    const uint16_t *hold = s_hold + l * n_rows + g * G;
+                    const unsigned at = s_at[slot];
+                    const int n_at = __popc(at & kMembers), row = n_at * (n_at - 1) / 2;
+                    int ua = 0, uo = 0;
+                    double H = 0.0;
 #pragma unroll 4
-                for (int k = 0; k < pairs; ++k) {
-                    const int x = t[k], lev = x & 63;
-                    lev_sum += lev;
-                    scaled += lev * s_lcm[(x >> 6) & 63];
-                    repeats |= (unsigned)(x >> 12) << j;
-                    if (++j == G) { ++i; j = i + 1; }
+                    for (int k = 0; k < G; ++k) {
+                        const int h = hold[k], holders = h & 31;
+                        uo += h >> 5;
+                        ua += holders ? 1 : 0;
+                        const int at_row = holders ? row + holders : 0;      // entry 0 is 0
+                        H = __builtin_fma(-s_p[at_row], s_log_p[at_row], H);
+                    }
+                    o->action_entropy = H;
+                    o->n_at_step = n_at;
+                    o->unique_action = ua;
+                    o->unique_obs = obs ? uo : 0;
+                    o->n_done = (int)(at >> 24);
                 }
-                o->lev_scaled = scaled;
-                o->lev_sum = lev_sum;
-                o->unique_prefix = G - __popc(repeats);
-            } else {
-                const int *t = s_hold + l * n_rows + g * G;
-                const double *lg = s_h + l * n_rows + g * G;
-                int n_at = 0, n_done = 0, ua = 0, uo = 0;
-                for (int k = 0; k < G; ++k) {
-                    n_at += (t[k] >> 6) & 1;
-                    n_done += t[k] >> 7;
-                    uo += (t[k] >> 5) & 1;
-                    ua += (t[k] & 31) ? 1 : 0;
-                }
-                double H = 0.0;
-                for (int k = 0; k < G; ++k)
-                    if (t[k] & 31) H = __builtin_fma(-((double)(t[k] & 31) / (double)n_at), lg[k], H);
-                o->action_entropy = H;
-                o->n_at_step = n_at;
-                o->unique_action = ua;
-                o->unique_obs = obs ? uo : 0;
-                o->n_done = n_done;
             }
         }
     }
     __syncthreads();
-    for (int w = tid; w < n_rec; w += nt) {
-        const int l = min((int)(((float)w + 0.5f) * inv_here), NL - 1), g = w - l * n_here;
-        sr_signals_t *o = s_out + l * q.groups + g;
-        o->cut_d = (uint8_t)(o->lev_scaled < lens.d_bound);
-        o->cut_or = (uint8_t)(o->cut_d || (long long)o->n_done * 1000000LL >= lens.tau_num * G);
-        for (int i = 0; i < 6; ++i) o->reserved[i] = 0;
-    }
-    __syncthreads();
     for (int w = tid; w < n_rec * 4; w += nt) {              // 16 bytes per lane, whole records of a K in a row
-        const int rec = w >> 2, l = min((int)(((float)rec + 0.5f) * inv_here), NL - 1), g = rec - l * n_here;
-        ((uint4 *)(out + (size_t)l * n_groups + g0 + g))[w & 3] = ((const uint4 *)(s_out + l * q.groups + g))[w & 3];
+        const int rec = w >> 2, l = min((int)(((float)rec + 0.5f) * inv_n), NL - 1), g = rec - l * n_here;
+        const sr_signals_t *o = s_out + l * q.groups + g;
+        uint4 v = ((const uint4 *)o)[w & 3];
+        if ((w & 3) == 2) v.x = (unsigned)(G - __popc(s_repeats[l * q.groups + g]));                       // unique_prefix
+        if ((w & 3) == 3) {                                                                                // cut_d, cut_or, reserved
+            const bool cut = o->lev_scaled < lens.d_bound, either = cut || (long long)o->n_done * 1000000LL >= lens.tau_num * G;
+            v.z = (cut ? 1u : 0u) | (either ? 0x100u : 0u);
+            v.w = 0;
+        }
+        ((uint4 *)(out + (size_t)l * n_groups + g0 + g))[w & 3] = v;
     }
 }
+
+static_assert(offsetof(sr_signals_t, unique_prefix) == 32 && offsetof(sr_signals_t, cut_d) == 56 && offsetof(sr_signals_t, cut_or) == 57,
+              "pieces 2 and 3 of a record");
 
 __global__ void assemble_gate_kernel(const int32_t *__restrict__ src, const int32_t *__restrict__ live_actions,
                                      const int32_t *__restrict__ fin_actions, int n_slots, int max_turns,
@@ -349,7 +546,8 @@ extern "C" int sr_signals_batch(const int32_t *actions, const int32_t *obs, cons
     for (int l = 0; l < n_lens; ++l) {
         const int K = prefix_lens[l];
         if (K < 1 || K > 32 || K > stride) return SR_E_ARG;
-        lens.len[l] = K;
+        lens.packed |= (unsigned long long)K << (6 * l);
+        lens.wanted |= 1u << (K - 1);
         maxlen = K > maxlen ? K : maxlen;
     }
     // d_K < d_L  <=>  lev_scaled * 1e6 < num * P * lcm  <=>  lev_scaled < ceil(num * P * lcm / 1e6)
@@ -357,25 +555,45 @@ extern "C" int sr_signals_batch(const int32_t *actions, const int32_t *obs, cons
     lens.d_bound = (long long)((num * P * (__int128)kLcm32 + 999999) / 1000000);
     lens.tau_num = (long long)__builtin_llround(tau_H * 1e6);
     if (n_groups == 0) return SR_OK;
-    const int pairs = G * (G - 1) / 2;
-    const bool direct = prefix_direct(n_groups, G, maxlen, 3);
-    const int kmax = maxlen <= 8 ? 8 : maxlen <= 16 ? 16 : maxlen <= 24 ? 24 : 32;
-    for (int n = 1; n <= 32; ++n) lens.lcm_over[n] = kLcm32 / n;
-    PrefixGeom q{};
-    const int extra = sig_lds(G, pairs, 1, n_lens).total;
-    if (!prefix_geometry(n_groups, G, maxlen, kmax, direct, kSigLds, extra, &q) &&
-        !prefix_geometry(n_groups, G, maxlen, kmax, direct, kSigLdsMost, extra, &q))
-        return SR_E_ARG;
-    const size_t lds = prefix_lds(q, q.groups, kmax, direct).total + (size_t)sig_lds(G, pairs, q.groups, n_lens).total;
-    dim3 grid((n_groups + q.groups - 1) / q.groups), block(q.threads);
+    // LDS behind symbols and tables: at most `extra` for every group, and `fixed`
+    const int extra = sig_lds(G, 2, n_lens).total - sig_lds(G, 1, n_lens).total + 16, fixed = sig_lds(G, 1, n_lens).total - extra + 16;
     hipStream_t st = (hipStream_t)stream;
-#define SR_SIG(K, DIRECT) \
-    signals_kernel<K, DIRECT><<<grid, block, lds, st>>>(actions, obs, end_step, n_groups, stride, pairs, q, lens, out)
-    switch (kmax) {                       // up to eight steps there are no tables
-        case 8: SR_SIG(8, true); break;
-        case 16: if (direct) SR_SIG(16, true); else SR_SIG(16, false); break;
-        case 24: if (direct) SR_SIG(24, true); else SR_SIG(24, false); break;
-        default: if (direct) SR_SIG(32, true); else SR_SIG(32, false); break;
+    PrefixGeom q{};
+    // quotients take the place of symbols and tables: of every length at once up to kSigTerms bytes
+    int distinct = 0, terms_at_once = 0, sums_at = 0;
+    for (unsigned w = lens.wanted; w; w &= w - 1) ++distinct;
+    auto place = [&] {
+        const int per_len = q.groups * sig_lds(G, q.groups, n_lens).code_stride * 16, room = q.total > kSigTerms ? q.total : kSigTerms;
+        terms_at_once = room / per_len < 1 ? 1 : room / per_len < distinct ? room / per_len : distinct;
+        sums_at = round_up(q.total > terms_at_once * per_len ? q.total : terms_at_once * per_len, 16);
+    };
+#define SR_SIG(KIND, KMAX)                                                                              \
+    (place(), signals_kernel<KIND, KMAX><<<dim3(ceil_div(n_groups, q.groups)), dim3(q.threads),          \
+                                           sums_at + sig_lds(G, q.groups, n_lens).total, st>>>(         \
+        actions, obs, end_step, n_groups, stride, q, lens, sums_at, terms_at_once, out))
+    // Up to eight steps the tables are nevertheless cheaper for large groups that fill the chip (65 536 groups of 8, 5 steps: 60 us,
+    // 70 with arbitrary symbols, 70 by comparison; 8 steps: 60, 87 and 70; groups of 16: 230, 254 and 343)
+    const bool many = (long long)n_groups * G >= 32000 && (G >= 12 || (G >= 8 && maxlen <= 6));
+    // a launch that does not fill the chip takes whole workgroups: four wavefronts share the phases of a group
+    auto fill = [&] { if (ceil_div(n_groups, q.groups) <= 512 && q.groups <= 4) q.threads = kSigThreads; };
+    if (prefix_direct(n_groups, G, maxlen, 3) && !many) {
+        const int kmax = maxlen <= 8 ? 8 : maxlen <= 16 ? 16 : maxlen <= 24 ? 24 : 32;
+        if (!prefix_geometry_direct(n_groups, G, maxlen, kmax, kSigLds - fixed, extra, &q)) return SR_E_ARG;
+        fill();
+        switch (kmax) {
+            case 8: SR_SIG(PREFIX_ONE32, 8); break;
+            case 16: SR_SIG(PREFIX_ONE32, 16); break;
+            case 24: SR_SIG(PREFIX_ONE32, 24); break;
+            default: SR_SIG(PREFIX_ONE32, 32); break;
+        }
+    } else {
+        // beyond 16 steps a pair a lane where the pairs leave eight wavefronts per compute unit or fewer, as in the gate
+        const int kind = maxlen <= 16 ? PREFIX_TWO16 : (long long)n_groups * G * (G - 1) / 2 <= 256 * 512 ? PREFIX_ONE32 : PREFIX_TWO32;
+        if (!prefix_geometry_tables(n_groups, G, maxlen, kind, kSigLds - fixed, kSigHashLds - fixed, extra, &q)) return SR_E_ARG;
+        fill();
+        if (kind == PREFIX_TWO16) SR_SIG(PREFIX_TWO16, 0);
+        else if (kind == PREFIX_TWO32) SR_SIG(PREFIX_TWO32, 0);
+        else SR_SIG(PREFIX_ONE32, 0);
     }
 #undef SR_SIG
     SR_HIP(hipGetLastError());

@@ -127,3 +127,25 @@ def test_signals_by_comparison(n_groups, G, lens):
     end[::7, 0] = 0
     end[::11, :2] = 0
     check(acts, lens, d_L=0.25, tau_H=0.5, obs=obs, end=end)
+
+
+@pytest.mark.parametrize("n_groups,G,lens,stride", [(9001, 8, [15, 10, 5], 15), (4099, 8, [16, 1], 16), (2049, 16, [16, 9], 30), (4097, 12, [9, 2], 9),
+                                                    (9001, 8, [6, 3], 7), (3001, 16, [8, 1], 8), (4099, 8, [32, 17], 32), (601, 11, [29], 29),
+                                                    (1025, 16, [32, 31, 30, 29, 28, 27, 26, 25], 33), (3, 5, [9], 9), (1, 2, [18], 18), (513, 7, [2, 9], 9)])
+@pytest.mark.parametrize("beyond", [False, True])
+def test_signals_tables(n_groups, G, lens, stride, beyond):
+    """Tables of symbols in their range and, with one symbol just beyond it in every hundredth group, workgroups that hash: up to 16
+    steps, beyond with one and with two pairs a lane, short prefixes of large groups; quotients of all lengths at once and in
+    several rounds; rows that end inside a 16-byte piece; a prefix length asked for twice; members that finish at once."""
+    rng = np.random.default_rng(n_groups + G)
+    lead = rng.integers(0, 64, size=(n_groups, 1, stride))
+    acts = np.where(rng.random((n_groups, G, stride)) < 0.8, lead, rng.integers(0, 64, size=(n_groups, G, stride))).astype(np.int32)
+    acts[0] = acts[0, :1]
+    if beyond:
+        acts[::100, 0, lens[0] - 1] = 64
+        acts[50::100, G - 1, 0] = -1
+    obs = rng.integers(-1, 2, size=acts.shape).astype(np.int32)
+    end = np.where(rng.random((n_groups, G)) < 0.35, rng.integers(0, stride + 1, size=(n_groups, G)), RUNNING).astype(np.int32)
+    lens = (lens + lens[:1])[:8]
+    check(acts, lens, d_L=0.25, tau_H=0.5, obs=obs, end=end)
+    check(acts, lens, d_L=0.25, tau_H=0.5)

@@ -73,3 +73,17 @@ def test_small_lm_heads_are_scored_through_stored_logits(plan):
             tiles = -(-M // 256) * -(-vocab // 256)
             assert rows == (M if M > 256 and tiles <= 16 else 256)
             assert rows == 256 or rows * vocab <= 16 * 65536
+
+
+def test_quotients_of_small_numbers_are_correctly_rounded():
+    """The signals kernel divides whole numbers below 64 by multiplying with the rounded reciprocal and correcting once with the
+    remainder: the same double as the division, for every pair."""
+    libm = ctypes.CDLL("libm.so.6")
+    libm.fma.argtypes, libm.fma.restype = [ctypes.c_double] * 3, ctypes.c_double
+    for b in range(1, 64):
+        r = 1.0 / b
+        for a in range(64):
+            q = a * r
+            assert libm.fma(libm.fma(-q, float(b), float(a)), r, q) == a / b
+        if b <= 32:                                   # lcm(1..32) / b from the same reciprocal
+            assert round(144403552893600.0 * r) * b == 144403552893600
