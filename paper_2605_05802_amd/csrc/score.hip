@@ -17,10 +17,11 @@
 // deviation; exactly zero when all rewards of the group are equal) and the group's share of
 // sum_i A_i log p(tau_i).  The shares are added in group order, by one lane, so that the loss is the
 // same to the last bit whatever the launch shape: a chain of dependent 64-bit additions, which is
-// what bounds the call from a few hundred groups on.  The lane therefore reads from LDS only
-// (grpo_sum_kernel: the other wavefronts bring in the next chunk meanwhile); reading the shares from
-// global memory itself cost it 80 ns per group (336 us at 4096 groups of 8, 30 us now; 512 groups and fewer, in
-// one launch, are not bound by it).
+// what bounds the call from a few hundred groups on.  The lane reads from LDS only, and finds no zeros there: a share of
+// exactly zero, which every group with equal rewards has, changes no sum, so the wavefronts that bring the shares in leave
+// them out.  4096 groups of 8, two fifths of them with equal rewards: 16.7 us; 30 with every share added and a group's
+// rewards read one after another, 336 with the shares read from global memory by the adding lane.  65 536 groups: 189 us
+// (292 without a zero among them), 348 before.
 #include <mutex>
 
 #include "sr_internal.h"
@@ -137,23 +138,80 @@ __global__ void accumulate_logprob_kernel(const float *__restrict__ tok_lp, int 
     logprob[u] = acc;
 }
 
-// acc + v[0] + ... + v[n-1], in that order; v in LDS
-__device__ __forceinline__ double add_in_order(double acc, const double *v, int n) {
-    int i = 0;
-    for (; i + 16 <= n; i += 16) {
-        double x[16];
+constexpr int kAddBlock = 32;          // shares added between two looks at LDS (16: 17.8 instead of 16.7 us; reading a block ahead: 19.8)
+
+// Up to 64 shares, one per lane of a wavefront (0 where there is none), appended to v[0 .. n) without the zeros, in lane order;
+// returns the new n.
+__device__ __forceinline__ int append_shares(double *v, int n, double x) {
+    const unsigned long long some = __ballot(x != 0.0);          // NaN is not 0
+    const int lane = threadIdx.x & 63;
+    if (x != 0.0) v[n + __popcll(some & ((1ull << lane) - 1ull))] = x;
+    return n + __popcll(some);
+}
+// v[n .. next multiple of kAddBlock) = 0, by one wavefront; returns the number of blocks.  Zeros change no sum: it starts as +0 and
+// no sum of it and others rounds to -0.
+__device__ __forceinline__ int pad_shares(double *v, int n) {
+    const int end = (n + kAddBlock - 1) / kAddBlock * kAddBlock, lane = threadIdx.x & 63;
+    if (n + lane < end) v[n + lane] = 0.0;
+    return end / kAddBlock;
+}
+// acc + v[0] + ... + v[kAddBlock * blocks - 1], in that order; v in LDS
+__device__ __forceinline__ double add_in_order(double acc, const double *v, int blocks) {
+    for (int b = 0; b < blocks; ++b) {
+        double x[kAddBlock];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) x[k] = v[i + k];
+        for (int k = 0; k < kAddBlock; ++k) x[k] = v[b * kAddBlock + k];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) acc += x[k];
+        for (int k = 0; k < kAddBlock; ++k) acc += x[k];
     }
-    for (; i < n; ++i) acc += v[i];
     return acc;
 }
 
 constexpr int kShareThreads = 64;      // many small workgroups: the groups spread over the compute units
-constexpr int kOneBlock = 512;         // up to so many groups one workgroup does shares and sum in one launch
-constexpr int kSumChunk = 2048;        // shares per LDS buffer of the ordered sum
+// Up to so many groups and members one workgroup does shares and sum in one launch: groups of 8 400 of them (7.6 us either way; 37: 4.3
+// and 5.6), of 16 200 (7.4 either way; 512: 14.0 and 8.8), of 2 all 512 (6.4 and 7.6)
+constexpr int kOneBlock = 512, kOneMembers = 3200;
+constexpr int kSegment = 512;          // shares that one wavefront brings in, without zeros, ...
+constexpr int kSegments = 4;           // ... and how many of these an LDS buffer of the ordered sum holds
+
+// Advantages and share of one group of at most MOST members, everything requested before anything is used; MOST = 0: of any size.
+template <int MOST>
+__device__ __forceinline__ double group_share(const double *__restrict__ lp, const float *__restrict__ r, int G, double eps,
+                                              float *__restrict__ adv) {
+    float rr[MOST ? MOST : 1];
+    double ll[MOST ? MOST : 1];
+#pragma unroll
+    for (int i = 0; i < MOST; ++i) rr[i] = r[min(i, G - 1)];
+#pragma unroll
+    for (int i = 0; i < MOST; ++i) ll[i] = lp[min(i, G - 1)];
+    auto each = [&](auto &&f) __attribute__((always_inline)) {   // f(i, reward, log-likelihood) in member order
+        if constexpr (MOST > 0) {
+#pragma unroll
+            for (int i = 0; i < MOST; ++i)
+                if (i < G) f(i, rr[i], ll[i]);       // uniform
+        } else {
+            for (int i = 0; i < G; ++i) f(i, r[i], lp[i]);
+        }
+    };
+    const float r0 = MOST ? rr[0] : r[0];
+    bool all_equal = true;
+    double mean = 0.0;
+    each([&](int, float x, double) {
+        all_equal &= x == r0;
+        mean += (double)x;
+    });
+    mean /= G;
+    double var = 0.0;
+    each([&](int, float x, double) { var += ((double)x - mean) * ((double)x - mean); });
+    const double sigma = sqrt(var / G);
+    double acc = 0.0;
+    each([&](int i, float x, double l) {
+        const double A = all_equal ? 0.0 : ((double)x - mean) / (sigma + eps);
+        if (adv) adv[i] = (float)A;
+        acc += A * l;
+    });
+    return acc;
+}
 
 // ONE: a single workgroup of kOneBlock threads holds every group and adds the shares itself
 template <bool ONE>
@@ -161,49 +219,58 @@ __global__ void grpo_share_kernel(const double *__restrict__ logprob, const floa
                                   int G, double eps, float *__restrict__ adv, double *__restrict__ share,
                                   double *__restrict__ loss) {
     __shared__ __align__(16) double s_share[ONE ? kOneBlock : 1];
+    __shared__ int s_blocks[ONE ? kOneBlock / 64 : 1];
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
+    double mine = 0.0;
     if (g < n_groups) {
-        const float *r = rewards + (size_t)g * G;
-        bool all_equal = true;
-        double mean = 0.0;
-        for (int i = 0; i < G; ++i) {
-            all_equal &= r[i] == r[0];
-            mean += (double)r[i];
-        }
-        mean /= G;
-        double var = 0.0;
-        for (int i = 0; i < G; ++i) var += ((double)r[i] - mean) * ((double)r[i] - mean);
-        const double sigma = sqrt(var / G);
-        double acc = 0.0;
-        for (int i = 0; i < G; ++i) {
-            const double A = all_equal ? 0.0 : ((double)r[i] - mean) / (sigma + eps);
-            if (adv) adv[(size_t)g * G + i] = (float)A;
-            acc += A * logprob[(size_t)g * G + i];
-        }
-        share[g] = acc;
-        if (ONE) s_share[g] = acc;
+        const size_t at = (size_t)g * G;
+        float *a = adv ? adv + at : nullptr;
+        mine = G <= 4    ? group_share<4>(logprob + at, rewards + at, G, eps, a)
+               : G <= 8  ? group_share<8>(logprob + at, rewards + at, G, eps, a)
+               : G <= 16 ? group_share<16>(logprob + at, rewards + at, G, eps, a)
+                         : group_share<0>(logprob + at, rewards + at, G, eps, a);
+        share[g] = mine;
     }
     if (!ONE) return;
+    const int wave = threadIdx.x >> 6;
+    const int blocks = pad_shares(s_share + wave * 64, append_shares(s_share + wave * 64, 0, mine));
+    if ((threadIdx.x & 63) == 0) s_blocks[wave] = blocks;
     __syncthreads();
-    if (threadIdx.x == 0) *loss = -add_in_order(0.0, s_share, n_groups) / ((double)n_groups * G);
+    if (threadIdx.x == 0) {
+        double acc = 0.0;
+        for (int w = 0; w < kOneBlock / 64; ++w) acc = add_in_order(acc, s_share + w * 64, s_blocks[w]);
+        *loss = -acc / ((double)n_groups * G);
+    }
 }
 
 __global__ __launch_bounds__(256) void grpo_sum_kernel(const double *__restrict__ share, int n_groups, int G,
                                                        double *__restrict__ loss) {
-    __shared__ __align__(16) double buf[2][kSumChunk];
-    const int n_chunks = (n_groups + kSumChunk - 1) / kSumChunk;
-    auto fetch = [&](int c, int from, int step) {
-        const int n = min(kSumChunk, n_groups - c * kSumChunk);
-        for (int i = from; i < n; i += step) buf[c & 1][i] = share[(size_t)c * kSumChunk + i];
+    constexpr int kChunk = kSegments * kSegment;
+    __shared__ __align__(16) double buf[2][kChunk];
+    __shared__ int s_blocks[2][kSegments];
+    const int n_chunks = (n_groups + kChunk - 1) / kChunk;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    auto fetch = [&](int c, int seg) {                // by one wavefront
+        double x[kSegment / 64];
+        const int at = c * kChunk + seg * kSegment + lane;
+#pragma unroll
+        for (int j = 0; j < kSegment / 64; ++j) x[j] = at + 64 * j < n_groups ? share[at + 64 * j] : 0.0;
+        double *v = buf[c & 1] + seg * kSegment;
+        int n = 0;
+#pragma unroll
+        for (int j = 0; j < kSegment / 64; ++j) n = append_shares(v, n, x[j]);
+        const int blocks = pad_shares(v, n);
+        if (lane == 0) s_blocks[c & 1][seg] = blocks;
     };
-    fetch(0, threadIdx.x, 256);
+    fetch(0, wave);
     double acc = 0.0;
     for (int c = 0; c < n_chunks; ++c) {
         __syncthreads();                 // chunk c is in LDS, and nobody reads the other buffer any more
-        if (threadIdx.x >= 64) {
-            if (c + 1 < n_chunks) fetch(c + 1, threadIdx.x - 64, 192);
-        } else if (threadIdx.x == 0) {
-            acc = add_in_order(acc, buf[c & 1], min(kSumChunk, n_groups - c * kSumChunk));
+        if (wave > 0) {
+            if (c + 1 < n_chunks)
+                for (int seg = wave - 1; seg < kSegments; seg += 3) fetch(c + 1, seg);
+        } else if (lane == 0) {
+            for (int seg = 0; seg < kSegments; ++seg) acc = add_in_order(acc, buf[c & 1] + seg * kSegment, s_blocks[c & 1][seg]);
         }
     }
     if (threadIdx.x == 0) *loss = -acc / ((double)n_groups * G);
@@ -211,7 +278,7 @@ __global__ __launch_bounds__(256) void grpo_sum_kernel(const double *__restrict_
 
 int launch_grpo_loss(const double *logprob, const float *rewards, int n_groups, int G, double eps, float *advantages,
                      double *share, double *loss, hipStream_t stream) {
-    if (n_groups <= kOneBlock) {
+    if (n_groups <= kOneBlock && (long long)n_groups * G <= kOneMembers) {
         grpo_share_kernel<true><<<dim3(1), dim3(kOneBlock), 0, stream>>>(logprob, rewards, n_groups, G, eps, advantages,
                                                                          share, loss);
         SR_HIP(hipGetLastError());

@@ -291,3 +291,33 @@ def test_scoring_counts_every_column_of_the_last_tile(plan, vocab, heavy):
     assert np.abs(lp.cpu().numpy() - ref).max() <= bound
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("n_groups,G", [(1, 1), (5, 3), (512, 4), (513, 4), (400, 8), (401, 8), (200, 16), (201, 16), (355, 9), (70, 33), (188, 17),
+                                        (4096, 5), (8193, 2), (10000, 17)])
+@pytest.mark.parametrize("equal", [0.0, 0.5, 1.0])
+def test_loss_leaves_out_shares_of_zero(n_groups, G, equal):
+    """Every size class of a group, on both sides of the rule for one launch, without, with some and with nothing but groups whose
+    rewards are equal: advantages as in Eq. 1, the loss the shares added in index order, to the last bit."""
+    rng = np.random.default_rng(n_groups + G)
+    lp = -rng.uniform(1.0, 400.0, size=(n_groups, G))
+    r = rng.integers(0, 3, size=(n_groups, G)).astype(np.float32)
+    same = rng.random(n_groups) < equal
+    r[same] = r[same, :1]
+    adv = torch.full((n_groups, G), 7.0, dtype=torch.float32, device="cuda")
+    share = torch.full((n_groups,), 7.0, dtype=torch.float64, device="cuda")
+    loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+    sr.sr_grpo_loss(torch.from_numpy(lp).cuda(), torch.from_numpy(r).cuda(), G, 1e-6, adv, share, loss)
+    torch.cuda.synchronize()
+    shares, acc = share.cpu().numpy(), np.float64(0.0)
+    for x in shares:
+        acc = acc + x
+    assert loss.item() == -acc / (n_groups * G)
+    sd = r.astype(np.float64).std(axis=1, keepdims=True)
+    want = np.where((r == r[:, :1]).all(axis=1, keepdims=True), 0.0, (r - r.mean(axis=1, keepdims=True, dtype=np.float64)) / (sd + 1e-6))
+    assert (adv.cpu().numpy()[same] == 0).all() and (shares[same] == 0).all()
+    assert np.allclose(adv.cpu().numpy(), want, rtol=1e-6, atol=1e-7)
+    assert np.allclose(shares, (want * lp).sum(axis=1), rtol=0, atol=1e-8)
+    lp[-1, 0], r[-1, 0] = np.nan, 5.0                # a share that is not a number is not left out
+    sr.sr_grpo_loss(torch.from_numpy(lp).cuda(), torch.from_numpy(r).cuda(), G, 1e-6, adv, share, loss)
+    assert np.isnan(loss.item())
