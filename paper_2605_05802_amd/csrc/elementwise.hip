@@ -25,6 +25,30 @@ __device__ __forceinline__ void block_sums_512(float (&v)[ROWS], float (*s_red)[
         v[r] = ((s_red[r][0] + s_red[r][1]) + (s_red[r][2] + s_red[r][3])) + ((s_red[r][4] + s_red[r][5]) + (s_red[r][6] + s_red[r][7]));
 }
 
+// lo += p[s * stride .. + 3], hi += p[s * stride + apart .. + 3] for s = 0 .. n-1, in that order, N of them requested before
+// the first is added.  More than four at a time gains nothing (nine, for the norm behind a projection in nine splits: 6.5 us at
+// 128 rows either way, 4.9 instead of 4.5 at 8) and costs registers.
+template <int N>
+__device__ __forceinline__ void add_partials_exactly(const float *p, size_t stride, int apart, f32x4 &lo, f32x4 &hi) {
+    f32x4 pl[N], ph[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        const float *q = p + (size_t)u * stride;
+        pl[u] = *(const f32x4 *)q;
+        ph[u] = *(const f32x4 *)(q + apart);
+    }
+#pragma unroll
+    for (int u = 0; u < N; ++u) { lo += pl[u]; hi += ph[u]; }
+}
+__device__ __forceinline__ void add_partials(const float *p, size_t stride, int n, int apart, f32x4 &lo, f32x4 &hi) {
+    for (; n >= 4; n -= 4, p += 4 * stride) add_partials_exactly<4>(p, stride, apart, lo, hi);
+    switch (n) {                                     // uniform
+        case 1: return add_partials_exactly<1>(p, stride, apart, lo, hi);
+        case 2: return add_partials_exactly<2>(p, stride, apart, lo, hi);
+        case 3: return add_partials_exactly<3>(p, stride, apart, lo, hi);
+    }
+}
+
 // x = resid (+ partials) or embedding row; resid <- x (if write_resid); out <- bf16(x * rsqrt(mean(x^2)+eps) * gain)
 // H <= 8192: each thread keeps its (at most 2 x 8) values per row in registers between the two passes.
 // A workgroup takes ROWS consecutive output rows and requests all of their data before the first reduction:
@@ -50,11 +74,12 @@ __global__ __launch_bounds__(512) void resid_norm_kernel(NormArgs a) {
         const int m = blockIdx.x * ROWS + r;
         ss[r] = 0.f;
         if (m >= a.rows_out) continue;               // uniform across the workgroup
-        const size_t row = (size_t)(m / a.src_dup) * a.src_stride + a.src_off;
+        const size_t row = (size_t)quotient(m, a.by_dup) * a.src_stride + a.src_off;
         float *x = a.resid + row * a.H;
         const uint16_t *e = nullptr;
         if (a.embed) {
-            const int tok = a.tokens[(size_t)(m / a.tok_chunk) * a.tok_stride + a.tok_off + m % a.tok_chunk];
+            const int unit = quotient(m, a.by_chunk);
+            const int tok = a.tokens[(size_t)unit * a.tok_stride + a.tok_off + m - unit * a.tok_chunk];
             e = a.embed + (size_t)tok * a.H;
         }
 #pragma unroll
@@ -73,23 +98,7 @@ __global__ __launch_bounds__(512) void resid_norm_kernel(NormArgs a) {
                 } else {
                     f32x4 lo = *(const f32x4 *)(x + v * 8), hi = *(const f32x4 *)(x + v * 8 + 4);
                     const float *p0 = a.partials + row * a.H + v * 8;
-                    int s = 0;
-                    for (; s + 4 <= a.n_partials; s += 4) {          // four independent loads in flight,
-                        f32x4 pl[4], ph[4];                          // added in split order
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const float *p = p0 + (size_t)(s + u) * a.partial_stride;
-                            pl[u] = *(const f32x4 *)p;
-                            ph[u] = *(const f32x4 *)(p + 4);
-                        }
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) { lo += pl[u]; hi += ph[u]; }
-                    }
-                    for (; s < a.n_partials; ++s) {
-                        const float *p = p0 + (size_t)s * a.partial_stride;
-                        lo += *(const f32x4 *)p;
-                        hi += *(const f32x4 *)(p + 4);
-                    }
+                    add_partials(p0, a.partial_stride, a.n_partials, 4, lo, hi);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) { f[i] = lo[i]; f[4 + i] = hi[i]; }
                 }
@@ -139,48 +148,45 @@ __global__ __launch_bounds__(512) void resid_norm_kernel(NormArgs a) {
 // batches, where tens of thousands of one-wavefront blocks would cost more than they move.  A thread owns four
 // consecutive dims i .. i+3 of the low half of a head and their rotation partners i + d/2 .. (16-byte loads of the
 // fp32 partials); d/8 threads make a head.
+// EARLY (decode): what does not depend on the partial sums (bias, rotation) is requested before them; a full chip hides that
+// round trip, and needs the registers.
+template <bool EARLY>
 __global__ __launch_bounds__(640) void qkv_post_kernel(QkvPostArgs a) {
     const int half = a.d >> 1, tph = half >> 2;               // threads per head
-    const int m = blockIdx.x, head = blockIdx.y * (blockDim.x / tph) + threadIdx.x / tph, i = (threadIdx.x % tph) * 4;
+    const int at = (int)(((float)threadIdx.x + 0.5f) * __builtin_amdgcn_rcpf((float)tph));       // 640 at most: far from an integer
+    const int m = blockIdx.x, head = blockIdx.y * a.heads_per_block + at, i = ((int)threadIdx.x - at * tph) * 4;
     if (head >= a.n_q + 2 * a.n_kv) return;
-    const int unit = m / a.chunk, ci = m - unit * a.chunk;
+    const int unit = quotient(m, a.by_chunk), ci = m - unit * a.chunk;
     const int pos = a.pos0 + ci;
-    const int q_cols = a.n_q * a.d, kv_cols = a.n_kv * a.d;
-    int col0;
-    const uint16_t *bias;
-    int kind, h;                                          // 0 q, 1 k, 2 v
-    if (head < a.n_q) { kind = 0; h = head; col0 = h * a.d; bias = a.bq ? a.bq + h * a.d : nullptr; }
-    else if (head < a.n_q + a.n_kv) { kind = 1; h = head - a.n_q; col0 = q_cols + h * a.d; bias = a.bk ? a.bk + h * a.d : nullptr; }
-    else { kind = 2; h = head - a.n_q - a.n_kv; col0 = q_cols + kv_cols + h * a.d; bias = a.bv ? a.bv + h * a.d : nullptr; }
-
+    const int kind = head < a.n_q ? 0 : head < a.n_q + a.n_kv ? 1 : 2;       // 0 q, 1 k, 2 v
+    const int h = kind == 0 ? head : kind == 1 ? head - a.n_q : head - a.n_q - a.n_kv;
+    const uint16_t *bias = kind == 0 ? a.bq : kind == 1 ? a.bk : a.bv;
+    // the page table does not change while the kernel runs: a uniform entry comes through a scalar load
+    const int page = ((const __attribute__((address_space(4))) int32_t *)(uintptr_t)a.page_table)[(size_t)unit * a.pt_row_stride *
+                                                                                           a.pt_stride + (pos >> a.page_shift)];
+    uint2 blo = make_uint2(0, 0), bhi = make_uint2(0, 0);
+    f32x4 c = {1.f, 1.f, 1.f, 1.f}, sn = {0.f, 0.f, 0.f, 0.f};
+    auto fetch = [&] {
+        if (bias) {
+            blo = *(const uint2 *)(bias + h * a.d + i);
+            bhi = *(const uint2 *)(bias + h * a.d + i + half);
+        }
+        if (kind != 2) {
+            c = *(const f32x4 *)(a.rope_cos + (size_t)pos * half + i);
+            sn = *(const f32x4 *)(a.rope_sin + (size_t)pos * half + i);
+        }
+    };
+    if (EARLY) fetch();
     f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = {0.f, 0.f, 0.f, 0.f};
-    {
-        const float *p0 = a.partials + (size_t)m * a.ld + col0 + i;
-        int s = 0;
-        for (; s + 4 <= a.n_partials; s += 4) {                  // independent loads, adds in split order
-            f32x4 pl[4], ph[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float *p = p0 + (size_t)(s + u) * a.partial_stride;
-                pl[u] = *(const f32x4 *)p;
-                ph[u] = *(const f32x4 *)(p + half);
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) { lo += pl[u]; hi += ph[u]; }
-        }
-        for (; s < a.n_partials; ++s) {
-            const float *p = p0 + (size_t)s * a.partial_stride;
-            lo += *(const f32x4 *)p;
-            hi += *(const f32x4 *)(p + half);
-        }
-    }
+    add_partials(a.partials + (size_t)m * a.ld + head * a.d + i, a.partial_stride, a.n_partials, half, lo, hi);
+    if (!EARLY) fetch();
     if (bias) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) { lo[e] += bf16_to_f32(bias[i + e]); hi[e] += bf16_to_f32(bias[i + half + e]); }
+        lo += f32x4{__uint_as_float(blo.x << 16), __uint_as_float(blo.x & 0xFFFF0000u), __uint_as_float(blo.y << 16),
+                    __uint_as_float(blo.y & 0xFFFF0000u)};
+        hi += f32x4{__uint_as_float(bhi.x << 16), __uint_as_float(bhi.x & 0xFFFF0000u), __uint_as_float(bhi.y << 16),
+                    __uint_as_float(bhi.y & 0xFFFF0000u)};
     }
     if (kind != 2) {
-        const f32x4 c = *(const f32x4 *)(a.rope_cos + (size_t)pos * half + i);
-        const f32x4 sn = *(const f32x4 *)(a.rope_sin + (size_t)pos * half + i);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const float rlo = lo[e] * c[e] - hi[e] * sn[e], rhi = hi[e] * c[e] + lo[e] * sn[e];
@@ -195,9 +201,8 @@ __global__ __launch_bounds__(640) void qkv_post_kernel(QkvPostArgs a) {
         *(uint2 *)(q + i + half) = phi;
         return;
     }
-    const int page = a.page_table[(size_t)unit * a.pt_row_stride * a.pt_stride + pos / a.page_tokens];
-    const int tok = pos % a.page_tokens, blk = tok >> 5, t = tok & 31;
-    const size_t base = ((((size_t)page * a.n_kv + h) * (a.page_tokens >> 5)) + blk) * (size_t)(32 * a.d);
+    const int tok = pos & (a.page_tokens - 1), blk = tok >> 5, t = tok & 31;
+    const size_t base = ((((size_t)page * a.n_kv + h) << (a.page_shift - 5)) + blk) * (size_t)(32 * a.d);
     if (kind == 1) {
         // K block [d/32][32 tok][32]: four consecutive dims stay inside one 32-dim group
         uint16_t *k = a.kpool + base;
@@ -253,10 +258,14 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float *__restrict__ 
             best = better(best, MaxIdx{row[v] * inv_temperature - logf(-logf(u)), v});
         }
     } else {
-        for (int v = threadIdx.x; v < nvec; v += 1024) {
-            const f32x4 x = *(const f32x4 *)(row + v * 4);
+        for (int v0 = threadIdx.x; v0 < nvec; v0 += 4096) {      // four loads in flight; past the end the last one again
+            f32x4 x[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) best = better(best, MaxIdx{x[e], v * 4 + e});
+            for (int u = 0; u < 4; ++u) x[u] = *(const f32x4 *)(row + min(v0 + u * 1024, nvec - 1) * 4);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) best = better(best, MaxIdx{x[u][e], min(v0 + u * 1024, nvec - 1) * 4 + e});
         }
         for (int v = nvec * 4 + threadIdx.x; v < vocab; v += 1024) best = better(best, MaxIdx{row[v], v});
     }
@@ -305,9 +314,12 @@ __global__ void copy_pages_kernel(uint4 *kpool, uint4 *vpool, size_t layer_vec, 
 
 }  // namespace
 
-int launch_resid_norm(const NormArgs &a, hipStream_t stream) {
+int launch_resid_norm(const NormArgs &args, hipStream_t stream) {
+    NormArgs a = args;
     if (a.rows_out <= 0) return SR_OK;
-    if (a.H % 8 || a.H > 8192) return SR_E_ARG;
+    if (a.H % 8 || a.H > 8192 || a.src_dup < 1 || (a.embed && a.tok_chunk < 1)) return SR_E_ARG;
+    a.by_dup = fast_div(a.src_dup);
+    a.by_chunk = fast_div(a.embed ? a.tok_chunk : 1);
     if (a.out32) resid_norm_kernel<true, 1><<<dim3(a.rows_out), dim3(512), 0, stream>>>(a);
     else if (a.rows_out >= 2048) resid_norm_kernel<false, 4><<<dim3(ceil_div(a.rows_out, 4)), dim3(512), 0, stream>>>(a);
     else resid_norm_kernel<false, 1><<<dim3(a.rows_out), dim3(512), 0, stream>>>(a);
@@ -315,9 +327,12 @@ int launch_resid_norm(const NormArgs &a, hipStream_t stream) {
     return SR_OK;
 }
 
-int launch_qkv_post(const QkvPostArgs &a, hipStream_t stream) {
+int launch_qkv_post(const QkvPostArgs &args, hipStream_t stream) {
+    QkvPostArgs a = args;
     if (a.rows <= 0) return SR_OK;
-    if (a.d > 128 || a.d % 32 || a.rows > 0x7FFFFFF) return SR_E_ARG;
+    if (a.d > 128 || a.d % 32 || a.rows > 0x7FFFFFF || a.chunk < 1) return SR_E_ARG;
+    a.by_chunk = fast_div(a.chunk);
+    a.page_shift = 31 - __builtin_clz(a.page_tokens);
     const int heads_per_wave = 64 / (a.d / 8);                 // d/8 threads per head
     const int heads = a.n_q + 2 * a.n_kv;
     int waves = 1;                                             // wavefronts per block
@@ -325,7 +340,10 @@ int launch_qkv_post(const QkvPostArgs &a, hipStream_t stream) {
         waves = ceil_div(heads, heads_per_wave);
         if (waves > 10) waves = 10;
     }
-    qkv_post_kernel<<<dim3(a.rows, ceil_div(heads, heads_per_wave * waves)), dim3(64 * waves), 0, stream>>>(a);
+    a.heads_per_block = heads_per_wave * waves;
+    const dim3 grid(a.rows, ceil_div(heads, heads_per_wave * waves)), block(64 * waves);
+    if (waves == 1) qkv_post_kernel<true><<<grid, block, 0, stream>>>(a);
+    else qkv_post_kernel<false><<<grid, block, 0, stream>>>(a);
     SR_HIP(hipGetLastError());
     return SR_OK;
 }

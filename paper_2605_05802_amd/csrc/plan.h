@@ -14,14 +14,28 @@ namespace sr {
 SR_HD inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 SR_HD inline int round_up(int a, int b) { return ceil_div(a, b) * b; }
 
+// n / d for 0 <= n < 2^31 by a multiplication: mul = ceil(2^shift / d) with shift = 31 + ceil(log2 d), so that mul exceeds
+// 2^shift / d by less than 2^(shift - 31) / d.  A division by a number that only the launch knows takes the scalar unit about
+// 35 dependent instructions, and the kernels of a decode step began with up to twelve of them.
+struct FastDiv { unsigned mul, shift; };
+inline FastDiv fast_div(int d) {
+    unsigned s = 31;
+    while ((1ull << (s - 31)) < (unsigned long long)d) ++s;
+    return FastDiv{(unsigned)(((1ull << s) + d - 1) / d), s};
+}
+SR_HD inline int quotient(int n, FastDiv f) { return (int)(((unsigned long long)(unsigned)n * f.mul) >> f.shift); }
+
 // Attention whose query tiles share K/V blocks: workgroup `wg` -> set (unit, kv head, split) and which of the set's `per_set`
 // workgroups.  Consecutive workgroups go to consecutive XCDs.  Of every eight sets each goes to one XCD, whose L2 then
 // serves the set's workgroups; the last n_sets % 8 sets are dealt out over all XCDs, because whole sets would leave
 // XCDs idle (one group's prompt of 5000 tokens and two kv heads of 128: 549 us on two XCDs, 202 on eight).
-SR_HD inline void shared_tiles_of(int wg, int n_sets, int per_set, int *set, int *part) {
-    const int rest0 = (n_sets & ~7) * per_set, t = wg - rest0;
-    *set = t < 0 ? (wg >> 3) / per_set * 8 + (wg & 7) : (n_sets & ~7) + t / per_set;
-    *part = t < 0 ? (wg >> 3) % per_set : t % per_set;
+SR_HD inline void shared_tiles_of(int wg, int n_sets, int per_set, FastDiv by_set, int *set, int *part) {
+    const int rest0 = (n_sets & ~7) * per_set, t = wg - rest0, n = t < 0 ? wg >> 3 : t, q = quotient(n, by_set);
+    *set = t < 0 ? q * 8 + (wg & 7) : (n_sets & ~7) + q;
+    *part = n - q * per_set;
+}
+inline void shared_tiles_of(int wg, int n_sets, int per_set, int *set, int *part) {
+    shared_tiles_of(wg, n_sets, per_set, fast_div(per_set), set, part);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -190,6 +190,7 @@ struct NormArgs {
     int write_resid;         // 0: leave resid untouched (several output rows may share one source row)
     int H, mt_total;
     float eps;
+    FastDiv by_dup, by_chunk;  // set by launch_resid_norm: divisions by src_dup and tok_chunk
 };
 int launch_resid_norm(const NormArgs &a, hipStream_t stream);
 
@@ -208,6 +209,8 @@ struct QkvPostArgs {
     int rows, chunk;         // row m = unit (m / chunk), token (m % chunk) of the chunk
     int pos0;                // absolute position of the chunk's first token
     int n_q, n_kv, d, page_tokens;
+    FastDiv by_chunk;        // set by launch_qkv_post, as the next two: log2(page_tokens), heads per workgroup
+    int page_shift, heads_per_block;
 };
 int launch_qkv_post(const QkvPostArgs &a, hipStream_t stream);
 
@@ -246,6 +249,8 @@ struct AttnPhase {
     const int32_t *unit_row0, *unit_count, *row_unit;
     float *part_o;       // [items][16*rt][d] fp32 un-normalised outputs
     float *part_ml;      // [items][16*rt][2] running max (scaled logits) and sum
+    // set by launch_attention: divisions by items_per_unit, n_splits and workgroups per (unit, kv head, split) of shared tiles
+    FastDiv by_items, by_splits, by_set;
 };
 
 struct AttnArgs {
@@ -259,6 +264,10 @@ struct AttnArgs {
     // arithmetic of the merge, and no merge is launched.
     uint16_t *direct_out;
     int out_mt_total;
+    // set by launch_attention
+    FastDiv by_kv;
+    int page_shift, n_rep;       // log2(page_tokens); n_q / n_kv
+    float inv_rep;
 };
 // The shared-prompt phase of a decode step: whether its query tiles share their blocks through LDS (a workgroup's fourth
 // wavefront may be idle, not half of them) and its splits -- 256 tokens each; where tiles share, only as many as give every

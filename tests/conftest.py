@@ -35,6 +35,7 @@ extern "C" {
 void shared_tiles(int n_sets, int per_set, int *set, int *part) {
     for (int wg = 0; wg < n_sets * per_set; ++wg) sr::shared_tiles_of(wg, n_sets, per_set, set + wg, part + wg);
 }
+int divide(int n, int d) { return sr::quotient(n, sr::fast_div(d)); }
 int stream_waves(int M, int N, int ks, int swiglu) { return sr::stream_waves(M, N, ks, swiglu); }
 int plan_kernel(int M, int N, int ks, int mt_total, int swiglu, int splits) {
     return sr::plan_gemm(M, N, ks, mt_total, swiglu, splits, 16).kernel;

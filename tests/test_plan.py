@@ -22,6 +22,17 @@ def test_shared_query_tiles_use_every_xcd(plan, n_sets, per_set):
     assert max(load) <= -(-n // 8)
 
 
+def test_division_by_multiplication(plan):
+    """Every divisor up to 4096 and some large ones, at both sides of multiples up to 2^31 - 1."""
+    top = 2 ** 31 - 1
+    for d in list(range(1, 4097)) + [65535, 65536, 1000003, 2 ** 30, 2 ** 30 + 1, top]:
+        k = top // d
+        for m in {0, 1, k // 2, k - 1, k}:
+            for n in {m * d - 1, m * d, m * d + d - 1, m * d + 1}:
+                if 0 <= n <= top:
+                    assert plan.divide(n, d) == n // d, (n, d)
+
+
 @pytest.mark.parametrize("M", [1, 128, 129, 192, 193, 256, 257])
 def test_small_matrices_leave_the_streaming_kernel_at_193_rows(plan, M):
     """Matrices of up to 16 MB lost 10 % on the streaming kernel at 193 to 256 rows; larger ones gain up to half."""
