@@ -1,6 +1,6 @@
 // Projection GEMMs  Y[M][N] = X[M][K] * W[N][K]^T  on the bf16 matrix cores, for more than 256 rows (up to there the
 // weight stream bounds all but small matrices: gemm_stream.hip).  W and X are stored pre-tiled in MFMA operand order.  Three
-// kernels, chosen per launch by measured cost (plan_gemm in plan.h): 128 x 128 tiles, tiles of 256 to 384 rows x 128 to 256
+// kernels, chosen per launch by measured cost (plan_gemm in plan.h): 128 x 128 tiles, tiles of 256 to 384 rows x 64 to 256
 // features, and all rows of a batch of a few hundred in one workgroup of 160 features.
 #include <type_traits>
 
@@ -233,6 +233,7 @@ __global__ __launch_bounds__(kPfThreads) void gemm_prefill_kernel(GemmArgs a, in
         asm volatile("" ::: "memory");
     };
 
+    f32x4 up[RT];                           // see the SwiGLU epilogue
     f32x4 acc[NT][RT];                      // [feature tile][row tile]: lane (c, g) holds features 4g .. 4g+3 of row c
 #pragma unroll
     for (int i = 0; i < NT; ++i)
@@ -266,12 +267,14 @@ __global__ __launch_bounds__(kPfThreads) void gemm_prefill_kernel(GemmArgs a, in
 #pragma unroll
                 for (int j = 0; j < RT; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[set][i], xf[set][j], acc[i][j], 0, 0, 0);
+            constexpr int PER = RT * NT >= 2 * (NT + RT) ? 2 : 1;    // MFMAs between two LDS reads
+            static_assert(RT * NT >= NT + RT, "at least one");
 #pragma unroll
             for (int f = 0; f < NT + RT; ++f) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);   // 2 MFMAs
+                __builtin_amdgcn_sched_group_barrier(0x008, PER, 0); // MFMAs
                 __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // 1 LDS read
             }
-            __builtin_amdgcn_sched_group_barrier(0x008, RT * NT - 2 * (NT + RT), 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, RT * NT - PER * (NT + RT), 0);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -329,26 +332,49 @@ __global__ __launch_bounds__(kPfThreads) void gemm_prefill_kernel(GemmArgs a, in
             }
         }
     } else {
-        static_assert(NT % 2 == 0, "gate and up tiles come in pairs");
+        // Packed tiles alternate gate and up.  With an odd NT the middle pair's gate is the last tile of the first wavefront column
+        // and its up the first of the second, which hands it over through LDS.
+        constexpr bool ODD = NT % 2 != 0;
+        if constexpr (ODD) {
+            __syncthreads();                         // nobody reads fragments any more
+            f32x4 *mid = (f32x4 *)pf_lds;            // [row tile][lane]
+            if (wn == 1) {
+#pragma unroll
+                for (int j = 0; j < RT; ++j) mid[(wm * RT + j) * 64 + lane] = acc[0][j];
+            }
+            __syncthreads();
+            if (wn == 0) {
+#pragma unroll
+                for (int j = 0; j < RT; ++j) up[j] = mid[(wm * RT + j) * 64 + lane];
+            }
+        }
         uint16_t *out = (uint16_t *)a.out;
+        auto store = [&](int m, int f, const f32x4 &gate, const f32x4 &up4) __attribute__((always_inline)) {   // features f .. f + 3
+            if (f < a.ld_out) {
+                float r[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) r[e] = gate[e] / (1.0f + __expf(-gate[e])) * up4[e];
+                *(uint2 *)(out + frag_offset(m, f, a.mt_total)) = make_uint2(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]));
+            }
+        };
 #pragma unroll
         for (int j = 0; j < RT; ++j) {
             const int m = (mb * 4 * RT + wm * RT + j) * 16 + c;
-            if (m < a.M) {
+            if (m >= a.M) continue;
+            if constexpr (ODD) {
+                const int f0 = nb * NT * 16 + 4 * g;             // features of the workgroup's first pair
+                if (wn == 0) {
 #pragma unroll
-                for (int i = 0; i < NT / 2; ++i) {   // tile 2i = gate, tile 2i + 1 = up of features f .. f+15
-                    const int f = (nb * NT + wn * (NT / 2) + i) * 16 + 4 * g;
-                    if (f < a.ld_out) {
-                        float r[4];
+                    for (int i = 0; i < NT / 2; ++i) store(m, f0 + i * 16, acc[2 * i][j], acc[2 * i + 1][j]);
+                    store(m, f0 + NT / 2 * 16, acc[NT - 1][j], up[j]);
+                } else {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const float gt = acc[2 * i][j][e];
-                            r[e] = gt / (1.0f + __expf(-gt)) * acc[2 * i + 1][j][e];
-                        }
-                        *(uint2 *)(out + frag_offset(m, f, a.mt_total)) =
-                            make_uint2(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]));
-                    }
+                    for (int i = 0; i < NT / 2; ++i)
+                        store(m, f0 + (NT / 2 + 1 + i) * 16, acc[2 * i + 1][j], acc[2 * i + 2][j]);
                 }
+            } else {
+#pragma unroll
+                for (int i = 0; i < NT / 2; ++i) store(m, (nb * NT + wn * (NT / 2) + i) * 16 + 4 * g, acc[2 * i][j], acc[2 * i + 1][j]);
             }
         }
     }
@@ -739,10 +765,11 @@ int launch_gemm(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream) {
     if (plan.kernel == KERNEL_MID) return launch_mid(a, epi, stream);
     const TileShape t = kTileShapes[plan.kernel];
 #define SR_TILE_CASE(E, NT, RT) if (epi == E && t.nt == NT && t.rt == RT) return launch_tiles<E, NT, RT>(a, stream);
-    SR_TILE_CASE(EPI_SWIGLU, 8, 4) SR_TILE_CASE(EPI_SWIGLU, 6, 4) SR_TILE_CASE(EPI_SWIGLU, 6, 5)
+    SR_TILE_CASE(EPI_SWIGLU, 8, 4) SR_TILE_CASE(EPI_SWIGLU, 6, 4) SR_TILE_CASE(EPI_SWIGLU, 5, 4) SR_TILE_CASE(EPI_SWIGLU, 6, 5)
     SR_TILE_CASE(EPI_F32, 8, 4) SR_TILE_CASE(EPI_F32, 7, 4) SR_TILE_CASE(EPI_F32, 6, 4) SR_TILE_CASE(EPI_F32, 5, 4)
     SR_TILE_CASE(EPI_F32, 6, 5) SR_TILE_CASE(EPI_F32, 5, 5) SR_TILE_CASE(EPI_F32, 4, 5)
     SR_TILE_CASE(EPI_F32, 4, 6)
+    SR_TILE_CASE(EPI_F32, 2, 4) SR_TILE_CASE(EPI_F32, 3, 4) SR_TILE_CASE(EPI_F32, 2, 5) SR_TILE_CASE(EPI_F32, 3, 5)
     return SR_E_ARG;
 }
 

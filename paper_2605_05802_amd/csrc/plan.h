@@ -108,7 +108,13 @@ inline int pick_splits(int M, int N, int ks_total) {
 // 8192, 5120, 4096, 2048, 1280, 768, 512 and 296 rows; k = K / 3584.  A launch has about 3 us of its own, the same for all.
 //   64 RT x 32 NT tiles, one to a CU: a round takes 2.33 RT (NT + 1.5) k.  O at 4096 rows 86 (NT = 7) and 88 (8), QKV at
 //     8192 rows 186 (6, three rounds), 202 (7, three), 207 (5, four) and 212 (8, three), O at 5120 rows 126 (5), 142 (6),
-//     155 (7) and 165 (8), two rounds each.  Every shape is looked at: what decides is how full the last round is.
+//     155 (7) and 165 (8), two rounds each.  Every shape is looked at: what decides is how full the last round is.  The
+//     narrow ones (NT = 2, 3) give a few hundred rows a whole round where 128 x 128 tiles need two or more K splits (16 384
+//     columns at 296 rows: 45 us with {2, 5} and 55 with 128 x 128; QKV at 296 rows 19.4 and 22.0, at 512 rows 25.8 with {3, 4}
+//     and 31.1; O at 640 rows 23 and 30; 2304 columns, K = 512, 2048 rows 11.7 and 16.7).  SwiGLU takes NT = 8 and 6, and
+//     {5, 4} from K = 3072 on (gate|up at 512 rows: 130 us, all rows in one workgroup 138; at K = 2048 they are even, at 1024 and
+//     below it is 2 to 8 % slower); {7, 4} is within 2 % either way of {8, 4} up to 3000 rows and 4 % slower at 4096, {5, 5} within
+//     3 % of {6, 5}.
 //   128 x 128 tiles, two to a CU: 39 k up to 256 of them and 60 k up to 512 (16 384 matrix rows at 512 rows: 24.1 us at K = 1024,
 //     {6, 4} 27.1; 38.8 and 42.6 at 2048); then 0.166 k a tile up to 1024 rows, and above 0.095 k a tile and 15 k (W read
 //     through L2 by many row blocks), from 16 384 matrix rows on, which no L2 holds, 0.137 k (22 016 rows, K = 4096: 541 us
@@ -117,7 +123,9 @@ inline int pick_splits(int M, int N, int ks_total) {
 //     fp32 matrix is cheapest there).  Only for matrices of 16 384 rows and more, where it makes a round of workgroups.
 //   S splits divide k, cost a fixed 6 and S times the output, written here and read by the next kernel, at 4.5 TB/s.
 struct TileShape { int nt, rt; };
-constexpr TileShape kTileShapes[] = {{8, 4}, {7, 4}, {6, 4}, {5, 4}, {6, 5}, {5, 5}, {4, 5}, {4, 6}};      // {5, 6} and up spill
+constexpr TileShape kTileShapes[] = {{8, 4}, {7, 4}, {6, 4}, {5, 4}, {6, 5}, {5, 5}, {4, 5}, {4, 6},      // {5, 6} and up spill
+                                     {2, 4}, {3, 4}, {2, 5}, {3, 5}};
+inline bool swiglu_shape(TileShape t, int ks_total) { return t.nt == 8 || t.nt == 6 || (t.nt == 5 && t.rt == 4 && ks_total >= 96); }
 enum { KERNEL_128 = -2, KERNEL_MID = -1 };             // otherwise an index into kTileShapes
 
 struct GemmPlan { int kernel, splits; };
@@ -141,7 +149,7 @@ inline GemmPlan plan_gemm(int M, int N, int ks_total, int mt_total, bool swiglu,
         offer(KERNEL_128, k / S * t128_us);
         for (int i = 0; i < (int)(sizeof kTileShapes / sizeof kTileShapes[0]); ++i) {
             const int nt = kTileShapes[i].nt, rt = kTileShapes[i].rt, mb = ceil_div(M, 64 * rt);
-            if ((swiglu && nt != 8 && nt != 6) || mb * 4 * rt > mt_total || S > ks_total / kPfBufs) continue;
+            if ((swiglu && !swiglu_shape(kTileShapes[i], ks_total)) || mb * 4 * rt > mt_total || S > ks_total / kPfBufs) continue;
             const long long rounds = ((long long)mb * ceil_div(N, 32 * nt) * S + 255) / 256;
             offer(i, rounds * 2.33 * rt * (nt + 1.5) * k / S);
         }

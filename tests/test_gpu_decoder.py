@@ -975,6 +975,37 @@ def test_tiled_kernels_by_name(plan, n_groups, ffn, vocab, gate_up, lm_head):
     assert worst <= LOGIT_TOL and mism == 0
 
 
+@pytest.mark.parametrize("n_groups,vocab,lm_head", [
+    (33, 528, "tiles 2x4"), (55, 6160, "tiles 2x4"),      # 264 rows: a last block of 8; 440 rows
+    (37, 14352, "tiles 2x5"), (97, 4624, "tiles 2x5"),    # 296 rows: one block; 776 rows: three
+    (55, 10256, "tiles 3x4"), (125, 4112, "tiles 3x4"),   # 440 and 1000 rows
+    (33, 20496, "tiles 3x5"), (71, 8208, "tiles 3x5"),    # 264 and 568 rows
+])
+def test_narrow_tiles_by_name(plan, n_groups, vocab, lm_head):
+    """Tiles of 64 and 96 features: every logit of a decode step, with a ragged last row block and column block."""
+    rows = n_groups * 8
+    assert plan.kernel(rows, vocab, 128) == lm_head
+    shape = synth.ModelShape(1, 128, 2, 1, 64, 160, vocab)
+    cfg = synth.EpisodeConfig("narrow", n_groups, 8, 4, 1, 1, 1, 64, (), 0.3, 0.0)
+    rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=72, page_tokens=32, kv_pool_bytes=1 << 28)
+    print(f"narrow {rows} rows, {lm_head}: worst |dlogit| = {worst:.3e}, mismatches = {mism}, near ties = {near}")
+    assert worst <= LOGIT_TOL and mism == 0
+
+
+def test_gate_up_on_tiles_with_an_odd_number_of_feature_tiles(plan):
+    """440 rows against 16 416 packed gate|up rows at hidden 3072: five feature tiles per wavefront, so the middle pair's gate and up
+    meet through LDS; ragged last row and column blocks."""
+    assert plan.kernel(440, 16416, 3072, swiglu=True) == "tiles 5x4"
+    shape = synth.ModelShape(1, 3072, 2, 1, 64, 8208, 512)
+    cfg = synth.EpisodeConfig("odd-tiles", 55, 8, 4, 1, 1, 1, 64, (), 0.3, 0.0)
+    info = {}
+    rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=74, page_tokens=32, kv_pool_bytes=1 << 28,
+                                                     contract_rows=[0, 100, 263, 439], info=info)
+    tol = tolerance(info["contract_max"])
+    print(f"odd tiles: worst |dlogit| = {worst:.3e}, bound {tol:.3e}, mismatches = {mism}, near ties = {near}")
+    assert worst <= tol and all(g < gap_rule(tol) for g in info["mismatch_gaps"])
+
+
 def test_fp32_tiles_of_320_rows_by_192_features(plan):
     """5935 prompt rows: the QKV projection of 2304 rows runs on tiles of 320 rows x 192 features, a ragged last row block."""
     assert plan.kernel(5935, 2304, 512) == "tiles 6x5" and plan.projection_splits(5935, 2304, 16, 512) == 1
