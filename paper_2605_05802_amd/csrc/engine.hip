@@ -512,14 +512,13 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
         y.causal_pos0 = ctx - 1;
         y.causal_stride = 0;
         const int priv = ctx - c->shared_tokens;
-        // about 1024 wavefronts in the private phase (with the shared phase's, 6-8 per CU: measured 4-10 % faster
-        // than 12 per CU at 128 and at 80 rows, at every context length), each at least 128 tokens long; a
-        // function of the context length and the batch shape only, never of the row
-        const int per_split = p.n_units * s.n_kv_heads;
-        y.n_splits = (1024 + per_split / 2) / per_split;
-        if (y.n_splits > ceil_div(priv, 128)) y.n_splits = ceil_div(priv, 128);
-        if (y.n_splits < 1) y.n_splits = 1;
-        if (y.n_splits > kMaxAttnSplits) y.n_splits = kMaxAttnSplits;
+        // a function of the context length and the batch shape only, never of the row
+        long long shared_waves = 0;
+        if (n_ph) {
+            const long long sets = (long long)ph[0].n_units * s.n_kv_heads * ph[0].n_splits;
+            shared_waves = sets * (ph[0].share && y.rt == 1 ? round_up(ph[0].items_per_unit, 4) : ph[0].items_per_unit);
+        }
+        y.n_splits = private_splits((long long)p.n_units * s.n_kv_heads, shared_waves, priv, kMaxAttnSplits);
         y.split_tokens = round_up(ceil_div(priv, y.n_splits), 32);
         // a sequence's private tokens are read by one work item per kv head: streamed past the caches once the
         // stream is long enough to gain from it (measured: slower below a few hundred tokens, 8 % faster at 1900)

@@ -177,4 +177,37 @@ inline int score_rows(int M, int vocab, int rows) {
     return (long long)ceil_div(M, 256) * ceil_div(vocab, 256) <= 16 && M > rows ? M : rows;
 }
 
+// ---------------------------------------------------------------------------------------------
+// decode attention
+// ---------------------------------------------------------------------------------------------
+// K/V splits of the sequences' private contexts in a decode step.  waves1: wavefronts of the private phase with one split
+// (sequences x kv heads); shared_waves: those of the shared-prompt phase in the same launch; tokens: private tokens of a
+// sequence.  At first about 1024 wavefronts, at least 128 tokens each, at most 16.  But a launch takes as long as its
+// fullest compute unit, and 256 of them take the workgroups (four wavefronts) in rounds: fewer splits are taken where the
+// rounds they save outweigh the longer chain of 32-token blocks.  The three terms of the cost were fitted to attention and
+// merge at 28 query and 4 kv heads of 128, 1 to 200 groups of 2, 4, 8 and 16, private contexts of 150 to 1000 tokens (147 shapes,
+// each with up to eight splits): 2.4 % on average, nothing more than 3 % slower.  In us, before and after: 8 groups of 8 with 500
+// tokens 27.8 with four splits (384 workgroups), 25.2 with two (256); 20 groups 55.0 with two (640), 47.4 with one (480);
+// 24 groups of 4 with 150 tokens 26.7 and 21.5.  A second split where one leaves the last of its rounds emptier by 8 %: 37
+// groups of 8, 300 tokens, 66.7 -> 62.8, 1000 tokens 153 -> 141; 28 groups, whose 784 workgroups begin a fourth
+// round, 48.6 -> 54.3, keep one.  Whole steps of four layers at 37 groups 1293 -> 1268 us, of two at 16 groups of 4 344 -> 333, at
+// 6 groups of 8 319 -> 313.
+inline int private_splits(long long waves1, long long shared_waves, int tokens, int max_splits) {
+    int most = (int)((1024 + waves1 / 2) / waves1);
+    if (most > ceil_div(tokens, 128)) most = ceil_div(tokens, 128);
+    if (most > max_splits) most = max_splits;
+    if (most < 1) most = 1;
+    auto wgs = [&](int s) { return (double)((shared_waves + waves1 * s + 3) / 4); };
+    auto rounds = [&](int s) { return (double)(((shared_waves + waves1 * s + 3) / 4 + 255) / 256); };
+    auto filled = [&](int s) { return wgs(s) > 256 ? wgs(s) / (256 * rounds(s)) : 1.0; };
+    auto cost = [&](int s) {
+        return (1 + 0.15 * (rounds(s) - 1)) / filled(s) + 0.06 * ceil_div(ceil_div(tokens, s), 32) / rounds(s);
+    };
+    int best = most;
+    for (int s = most - 1; s >= 1; --s)
+        if (cost(s) < cost(best) - 1e-9) best = s;
+    if (most == 1 && max_splits > 1 && tokens >= 256 && filled(2) >= 0.85 && filled(2) >= filled(1) + 0.08) best = 2;
+    return best;
+}
+
 }  // namespace sr

@@ -86,6 +86,25 @@ def test_small_lm_heads_are_scored_through_stored_logits(plan):
             assert rows == 256 or rows * vocab <= 16 * 65536
 
 
+@pytest.mark.parametrize("waves1,shared,tokens,splits", [
+    (256, 512, 500, 2), (640, 1280, 500, 1), (768, 1152, 300, 1), (512, 1024, 500, 2), (32, 64, 500, 4),
+    (1184, 1184, 300, 2), (1184, 1184, 255, 1), (896, 1344, 300, 1), (2048, 2048, 300, 1), (1, 0, 100000, 16)])
+def test_private_splits_where_measured(plan, waves1, shared, tokens, splits):
+    assert plan.private_splits(waves1, shared, tokens, 16) == splits
+
+
+def test_private_splits_stay_within_their_limits(plan):
+    """At most what about 1024 wavefronts of 128 tokens each would take, or two; never none, never beyond the buffers' limit."""
+    for waves1 in [*range(1, 70), 129, 255, 256, 257, 500, 1023, 1024, 1025, 1184, 2048, 4096, 200000]:
+        for shared in (0, 1, 4, 63, 256, 1024, 1184, 100000):
+            for tokens in (1, 31, 32, 127, 128, 129, 255, 256, 480, 1000, 16384, 1 << 20):
+                for limit in (1, 3, 16):
+                    most = max(1, min((1024 + waves1 // 2) // waves1, -(-tokens // 128), limit))
+                    s = plan.private_splits(waves1, shared, tokens, limit)
+                    assert 1 <= s <= max(most, min(2, limit))
+                    assert s == 1 or -(-tokens // s) >= 32
+
+
 def test_quotients_of_small_numbers_are_correctly_rounded():
     """The signals kernel divides whole numbers below 64 by multiplying with the rounded reciprocal and correcting once with the
     remainder: the same double as the division, for every pair."""
