@@ -447,7 +447,7 @@ def main():
         "prefill_chunk": prefill_obj,
         "kernel_ms_per_profiled_step": {k: v[1] / max(len(rows), 1) for k, v in res["kernel_times"].items()},
         "gate": {"groups_per_s": gate_gps, "ms_per_launch": gate_ms, "workload": "65536 groups x G=8, prefixes 5/10/15",
-                 "kernel": "one lane per pair, bit-parallel table rows, equality masks from LDS",
+                 "kernel": "a lane per two pairs, bit-parallel table rows, equality masks from LDS",
                  "antidiagonal_lds_variant_ms_per_launch": gate_ms_ad,
                  "antidiagonal_lds_variant_groups_per_s": 65536 / (gate_ms_ad * 1e-3)},
         "score_pass": score,
