@@ -136,10 +136,19 @@ inline GemmPlan plan_gemm(int M, int N, int ks_total, int mt_total, bool swiglu,
     const int s_lo = splits ? splits : 1;
     int s_hi = splits ? splits : max_splits;
     if (!splits && s_hi > ks_total / 32) s_hi = ks_total / 32;         // at least 32 k-steps each: filling the pipeline is not free
+    // what does not depend on S: workgroups of a split, of each shape that may run
+    constexpr int n_shapes = sizeof kTileShapes / sizeof kTileShapes[0];
+    long long tiles[n_shapes];
+    for (int i = 0; i < n_shapes; ++i) {
+        const int nt = kTileShapes[i].nt, rt = kTileShapes[i].rt, mb = ceil_div(M, 64 * rt);
+        const bool may = (!swiglu || swiglu_shape(kTileShapes[i], ks_total)) && mb * 4 * rt <= mt_total;
+        tiles[i] = may ? (long long)mb * ceil_div(N, 32 * nt) : 0;
+    }
     GemmPlan best{KERNEL_128, s_lo};
     double least = 0.0;
     for (int S = s_lo; S == s_lo || S <= s_hi; ++S) {
         const double more = (swiglu ? 0.0 : 8.0e-6 / 4.5 * S * M * N) + (S > 1 ? 6.0 : 0.0);
+        if (least != 0.0 && more >= least) break;         // grows with S: nothing from here on is cheaper
         auto offer = [&](int kernel, double us) {
             if (least == 0.0 || us + more < least) { least = us + more; best = GemmPlan{kernel, S}; }
         };
@@ -147,12 +156,9 @@ inline GemmPlan plan_gemm(int M, int N, int ks_total, int mt_total, bool swiglu,
         const double t128_us = n128 <= 256 ? 39.0 : n128 <= (M > 1024 ? 473 : 512) ? 60.0 : M <= 1024 ? 0.166 * n128
                                : (N < 16384 ? 0.095 : 0.137) * n128 + 15.0;
         offer(KERNEL_128, k / S * t128_us);
-        for (int i = 0; i < (int)(sizeof kTileShapes / sizeof kTileShapes[0]); ++i) {
-            const int nt = kTileShapes[i].nt, rt = kTileShapes[i].rt, mb = ceil_div(M, 64 * rt);
-            if ((swiglu && !swiglu_shape(kTileShapes[i], ks_total)) || mb * 4 * rt > mt_total || S > ks_total / kPfBufs) continue;
-            const long long rounds = ((long long)mb * ceil_div(N, 32 * nt) * S + 255) / 256;
-            offer(i, rounds * 2.33 * rt * (nt + 1.5) * k / S);
-        }
+        if (S <= ks_total / kPfBufs)
+            for (int i = 0; i < n_shapes; ++i)
+                if (tiles[i]) offer(i, ((tiles[i] * S + 255) >> 8) * 2.33 * kTileShapes[i].rt * (kTileShapes[i].nt + 1.5) * k / S);
         if (S == 1 && M <= (swiglu ? 512 : 384) && N >= 16384)
             offer(KERNEL_MID, k * ceil_div(ceil_div(N, 160), 256) * (M <= 384 ? 108.0 : 139.0));
     }
