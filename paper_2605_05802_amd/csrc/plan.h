@@ -111,7 +111,9 @@ inline int pick_splits(int M, int N, int ks_total) {
 //     155 (7) and 165 (8), two rounds each.  Every shape is looked at: what decides is how full the last round is.  The
 //     narrow ones (NT = 2, 3) give a few hundred rows a whole round where 128 x 128 tiles need two or more K splits (16 384
 //     columns at 296 rows: 45 us with {2, 5} and 55 with 128 x 128; QKV at 296 rows 19.4 and 22.0, at 512 rows 25.8 with {3, 4}
-//     and 31.1; O at 640 rows 23 and 30; 2304 columns, K = 512, 2048 rows 11.7 and 16.7).  SwiGLU takes NT = 8 and 6, and
+//     and 31.1; O at 640 rows 23 and 30; 2304 columns, K = 512, 2048 rows 11.7 and 16.7).  Not beyond
+//     2048 rows, where every block of so few columns reads all of X again (512 columns at 3840 rows: K = 8192 45.3 us with {2, 4}
+//     and 38.8 with {4, 5}, K = 1792 22.6 and 18.1 with 128 x 128).  SwiGLU takes NT = 8 and 6, and
 //     {5, 4} from K = 3072 on (gate|up at 512 rows: 130 us, all rows in one workgroup 138; at K = 2048 they are even, at 1024 and
 //     below it is 2 to 8 % slower); {7, 4} is within 2 % either way of {8, 4} up to 3000 rows and 4 % slower at 4096, {5, 5} within
 //     3 % of {6, 5}.
@@ -123,6 +125,7 @@ inline int pick_splits(int M, int N, int ks_total) {
 //     fp32 matrix is cheapest there).  Only for matrices of 16 384 rows and more, where it makes a round of workgroups.
 //   S splits divide k, cost a fixed 6 and S times the output, written here and read by the next kernel, at 4.5 TB/s.
 struct TileShape { int nt, rt; };
+constexpr int kNarrowRows = 2048;
 constexpr TileShape kTileShapes[] = {{8, 4}, {7, 4}, {6, 4}, {5, 4}, {6, 5}, {5, 5}, {4, 5}, {4, 6},      // {5, 6} and up spill
                                      {2, 4}, {3, 4}, {2, 5}, {3, 5}};
 inline bool swiglu_shape(TileShape t, int ks_total) { return t.nt == 8 || t.nt == 6 || (t.nt == 5 && t.rt == 4 && ks_total >= 96); }
@@ -141,7 +144,7 @@ inline GemmPlan plan_gemm(int M, int N, int ks_total, int mt_total, bool swiglu,
     long long tiles[n_shapes];
     for (int i = 0; i < n_shapes; ++i) {
         const int nt = kTileShapes[i].nt, rt = kTileShapes[i].rt, mb = ceil_div(M, 64 * rt);
-        const bool may = (!swiglu || swiglu_shape(kTileShapes[i], ks_total)) && mb * 4 * rt <= mt_total;
+        const bool may = (!swiglu || swiglu_shape(kTileShapes[i], ks_total)) && (nt > 3 || M <= kNarrowRows) && mb * 4 * rt <= mt_total;
         tiles[i] = may ? (long long)mb * ceil_div(N, 32 * nt) : 0;
     }
     GemmPlan best{KERNEL_128, s_lo};
