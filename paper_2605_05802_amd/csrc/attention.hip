@@ -55,9 +55,9 @@ struct PageWindow {
         first = page;
         entry = pt[min(page + (int)(threadIdx.x & 63), last)];
     }
-    // of tokens t_lo .. t_end - 1, t_end > t_lo
+    // of tokens t_lo .. t_end - 1; nothing behind the page of t_end - 1 is read, whatever t_lo is
     __device__ __forceinline__ PageWindow(const int32_t *table, int page_shift, int t_lo, int t_end)
-        : pt(table), shift(page_shift), last(max(t_end - 1, t_lo) >> page_shift) { load(t_lo >> page_shift); }
+        : pt(table), shift(page_shift), last((t_end - 1) >> page_shift) { load(min(t_lo >> page_shift, last)); }
     // token t, uniform and within the range; the first page asked for never decreases
     __device__ __forceinline__ int page(int t) {
         const int i = t >> shift;
@@ -593,6 +593,8 @@ int launch_attention(const AttnArgs &args, const AttnPhase *phase_args, int n_ph
         if ((p.t_begin & 31) || (p.split_tokens & 31) || p.split_tokens <= 0 || p.q_per_item * n_rep > 16 * p.rt ||
             p.rt != phases[0].rt)
             return SR_E_ARG;
+        // no split without a token of its own
+        if (n[i] && p.t_begin + (long long)(p.n_splits - 1) * p.split_tokens >= p.t_end) return SR_E_ARG;
     }
     if (a.direct_out && (n_phases != 1 || phases[0].n_splits != 1)) return SR_E_ARG;
     const long long n_items = n[0] + n[1];

@@ -518,8 +518,9 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
             const long long sets = (long long)ph[0].n_units * s.n_kv_heads * ph[0].n_splits;
             shared_waves = sets * (ph[0].share && y.rt == 1 ? round_up(ph[0].items_per_unit, 4) : ph[0].items_per_unit);
         }
-        y.n_splits = private_splits((long long)p.n_units * s.n_kv_heads, shared_waves, priv, kMaxAttnSplits);
-        y.split_tokens = round_up(ceil_div(priv, y.n_splits), 32);
+        const TokenSplits sp = token_splits(priv, private_splits((long long)p.n_units * s.n_kv_heads, shared_waves, priv, kMaxAttnSplits));
+        y.n_splits = sp.n;
+        y.split_tokens = sp.tokens;
         // a sequence's private tokens are read by one work item per kv head: streamed past the caches once the
         // stream is long enough to gain from it (measured: slower below a few hundred tokens, 8 % faster at 1900)
         y.stream_loads = priv >= 512 ? 1 : 0;
@@ -551,8 +552,9 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
             if ((size_t)x.n_splits * rows > c->part_rows_cap) x.n_splits = (int)(c->part_rows_cap / rows);
             if (x.n_splits < 1) x.n_splits = 1;
         }
-        x.split_tokens = round_up(ceil_div(ctx, x.n_splits), 32);
-        x.n_splits = ceil_div(ctx, x.split_tokens);      // rounding may leave the last ones nothing
+        const TokenSplits sp = token_splits(ctx, x.n_splits);
+        x.n_splits = sp.n;
+        x.split_tokens = sp.tokens;
         add_phase(x);
     }
     if (part_rows > c->part_rows_cap) return SR_E_NOMEM;

@@ -189,6 +189,15 @@ inline int score_rows(int M, int vocab, int rows) {
 // ---------------------------------------------------------------------------------------------
 // decode attention
 // ---------------------------------------------------------------------------------------------
+// `want` splits of a token range, or fewer: each holds a multiple of 32 tokens, and rounding up may leave the last ones nothing
+// (2080 tokens in 16 splits of 160: the last three).  Work items of an empty split would look for pages behind the context, take
+// a wavefront and add a row to the merge.
+struct TokenSplits { int n, tokens; };
+inline TokenSplits token_splits(int tokens, int want) {
+    const int each = round_up(ceil_div(tokens, want), 32);
+    return TokenSplits{ceil_div(tokens, each), each};
+}
+
 // K/V splits of the sequences' private contexts in a decode step.  waves1: wavefronts of the private phase with one split
 // (sequences x kv heads); shared_waves: those of the shared-prompt phase in the same launch; tokens: private tokens of a
 // sequence.  At first about 1024 wavefronts, at least 128 tokens each, at most 16.  But a launch takes as long as its

@@ -261,7 +261,8 @@ extern "C" int sr_probe_decode_attention(int n_groups, int G, int shared_tokens,
     if (shared_tokens) set_shared_phase(&x, shared_tokens, n_kv, 16);
     y.n_units = M; y.q_per_unit = 1; y.q_per_item = 1; y.items_per_unit = 1; y.rt = 1; y.pt_row_stride = 1;
     y.t_begin = shared_tokens; y.t_end = ctx; y.causal_pos0 = ctx - 1;
-    y.n_splits = priv_splits; y.split_tokens = round_up(ceil_div(priv_tokens, priv_splits), 32);
+    const TokenSplits sp = token_splits(priv_tokens, priv_splits);
+    y.n_splits = sp.n; y.split_tokens = sp.tokens;
     y.stream_loads = priv_tokens >= 512;
     const size_t items0 = (size_t)x.n_units * n_kv * x.items_per_unit * x.n_splits, items1 = (size_t)M * n_kv * y.n_splits;
     int rc = SR_OK;

@@ -273,7 +273,7 @@ struct AttnArgs {
 // wavefront may be idle, not half of them) and its splits -- 256 tokens each; where tiles share, only as many as give every
 // CU a workgroup of this phase (swept at 16 x 8, 37 x 8 and 32 x 16 sequences: 4, 2 and 2 splits of prompts of 1024, 1024
 // and 4096 tokens; sixteen splits of the last one took 147 us plus 46 us of merge instead of 119 + 22).
-inline int set_shared_phase(AttnPhase *x, int shared_tokens, int n_kv, int max_splits) {
+inline void set_shared_phase(AttnPhase *x, int shared_tokens, int n_kv, int max_splits) {
     x->share = x->items_per_unit >= 3;
     x->n_splits = ceil_div(shared_tokens, 256);
     if (x->share) {
@@ -281,8 +281,9 @@ inline int set_shared_phase(AttnPhase *x, int shared_tokens, int n_kv, int max_s
         if (x->n_splits > enough) x->n_splits = enough;
     }
     if (x->n_splits > max_splits) x->n_splits = max_splits;
-    x->split_tokens = round_up(ceil_div(shared_tokens, x->n_splits), 32);
-    return x->n_splits;
+    const TokenSplits sp = token_splits(shared_tokens, x->n_splits);
+    x->n_splits = sp.n;
+    x->split_tokens = sp.tokens;
 }
 // One launch over one or two phases (same rt); phases whose token range is empty contribute no work.
 int launch_attention(const AttnArgs &a, const AttnPhase *phases, int n_phases, hipStream_t stream);

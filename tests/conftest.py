@@ -45,6 +45,7 @@ int tile_rt(int i) { return sr::kTileShapes[i].rt; }
 int split_steps(int M, int N, int ks, int mt_total, int splits) { return sr::split_steps(M, N, ks, mt_total, splits); }
 int score_rows(int M, int vocab, int rows) { return sr::score_rows(M, vocab, rows); }
 int private_splits(int waves1, int shared_waves, int tokens, int most) { return sr::private_splits(waves1, shared_waves, tokens, most); }
+int token_splits(int tokens, int want, int *each) { const sr::TokenSplits s = sr::token_splits(tokens, want); *each = s.tokens; return s.n; }
 int projection_splits(int M, int N, int ks, int mt_total) { return sr::projection_splits(M, N, ks, mt_total); }
 }
 """

@@ -105,6 +105,23 @@ def test_private_splits_stay_within_their_limits(plan):
                     assert s == 1 or -(-tokens // s) >= 32
 
 
+def test_no_attention_split_is_empty(plan):
+    """Every split of a token range begins within it, and the splits cover it: for any number of splits asked for (the prompt, a
+    prefill chunk's context, a probe), and for the number that decode asks for."""
+    each = ctypes.c_int()
+
+    def check(tokens, want):
+        n = plan.token_splits(tokens, want, ctypes.byref(each))
+        assert 1 <= n <= want and each.value % 32 == 0, (tokens, want)
+        assert (n - 1) * each.value < tokens <= n * each.value, (tokens, want, n, each.value)
+
+    for tokens in [*range(1, 4200), 5000, 8191, 16384, 100001, 1 << 20]:
+        for want in range(1, 17):
+            check(tokens, want)
+        for waves1 in (4, 32, 64, 100, 150, 256):
+            check(tokens, plan.private_splits(waves1, 64, tokens, 16))
+
+
 def test_quotients_of_small_numbers_are_correctly_rounded():
     """The signals kernel divides whole numbers below 64 by multiplying with the rounded reciprocal and correcting once with the
     remainder: the same double as the division, for every pair."""
