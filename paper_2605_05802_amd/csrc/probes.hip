@@ -244,10 +244,12 @@ extern "C" int sr_probe_decode_attention(int n_groups, int G, int shared_tokens,
     uint4 *merged = nullptr;
     const int mt_total = ceil_div(M, 16);
     std::vector<int32_t> pt((size_t)M * max_pages);
+    const int hot_private = n_pages < 6 ? n_pages - 2 : 4;          // and the page behind it (there are two at least)
     for (int u = 0; u < M; ++u)
         for (int j = 0; j < max_pages; ++j) {
             int page = j < shared_pages ? (u / G) * shared_pages + j : n_groups * shared_pages + (j - shared_pages) * M + u;
-            if (hot) page = j < shared_pages ? j % 4 : 4 + (j & 1);
+            if (hot) page = j < shared_pages ? j % 4 : hot_private + (j & 1);
+            if (page < 0 || page >= n_pages) return SR_E_ARG;
             pt[(size_t)u * max_pages + j] = page;
         }
     AttnPhase x{}, y{};

@@ -62,3 +62,13 @@ def test_decode_attention_probe_phases_and_merge():
     expect_arg_error(sr.sr_probe_decode_attention, 16, 8, 1000, 1000, 2, 3)     # prompt not in whole pages
     expect_arg_error(sr.sr_probe_decode_attention, 16, 8, 0, 1000, 2, 1)        # no shared prompt to time
     expect_arg_error(sr.sr_probe_decode_attention, 16, 1, 1024, 1000, 2, 3)     # a group is at least two members
+
+
+@pytest.mark.parametrize("groups,G,shared,priv,splits,phases", [(1, 2, 0, 1, 1, 2), (1, 5, 0, 64, 16, 2), (1, 2, 64, 1, 16, 7),
+                                                                (8, 8, 1024, 2080, 16, 7), (3, 16, 0, 33, 2, 6)])
+@pytest.mark.parametrize("hot", [False, True])
+def test_decode_attention_probe_of_few_pages_and_few_tokens(groups, G, shared, priv, splits, phases, hot):
+    """Fewer pages than the cached variant rotates through (the probe checks every page number against its pool), and more splits
+    than there are blocks of 32 tokens."""
+    us, nbytes = sr.sr_probe_decode_attention(groups, G, shared, priv, splits, phases, hot, 4)
+    assert 0 < us < 1000 and nbytes == 2048 * ((groups * shared if phases & 1 else 0) + groups * G * priv)
