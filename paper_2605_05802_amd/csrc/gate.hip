@@ -27,12 +27,6 @@ int64_t gate_bound(double d_L, int G, int K) {
 
 namespace {
 
-constexpr int kGateThreads = 256;
-constexpr int kGateLds = 40 * 1024;      // LDS of one workgroup: four workgroups or more per compute unit
-// ... where symbols are hashed, whose tables are larger: 65 536 groups of 12, 12 steps 95 us, 109 with 16 KiB, 113 with 32, 147 with 40
-// (groups of 8, 15 steps: 86, 80, 89 and 113); 40 and more take occupancy from calls that hash nothing (20 -> 26 us)
-constexpr int kGateHashLds = 24 * 1024;
-
 __device__ __forceinline__ unsigned min3u(unsigned a, unsigned b, unsigned c) {
     return min(a, min(b, c));
 }
@@ -68,7 +62,7 @@ __device__ __forceinline__ void write_sums(const unsigned *s_sum, int groups, in
 
 // Equality masks from tables
 template <int KIND>
-__global__ __launch_bounds__(kGateThreads) void gate_table_kernel(
+__global__ __launch_bounds__(kPrefixThreads) void gate_table_kernel(
     const int32_t *__restrict__ actions, int n_groups, int stride, PrefixGeom q, GateLens lens,
     int32_t *__restrict__ sums, uint8_t *__restrict__ retire) {
     extern __shared__ __align__(16) char lds[];      // element ids, tables, sums
@@ -127,7 +121,7 @@ __global__ __launch_bounds__(kGateThreads) void gate_table_kernel(
 
 // A lane per pair, symbols compared in registers
 template <int KMAX>
-__global__ __launch_bounds__(kGateThreads) void gate_direct_kernel(
+__global__ __launch_bounds__(kPrefixThreads) void gate_direct_kernel(
     const int32_t *__restrict__ actions, int n_groups, int stride, PrefixGeom q, GateLens lens,
     int32_t *__restrict__ sums, uint8_t *__restrict__ retire) {
     extern __shared__ __align__(16) char lds[];      // symbols, sums
@@ -182,17 +176,17 @@ __global__ __launch_bounds__(kGateThreads) void gate_direct_kernel(
 // side by side and checked against each other.
 // ---------------------------------------------------------------------------------------------
 template <int SEG>
-__global__ __launch_bounds__(kGateThreads) void gate_antidiag_kernel(
+__global__ __launch_bounds__(kPrefixThreads) void gate_antidiag_kernel(
     const int32_t *__restrict__ actions, int n_groups, int G, int stride, int pairs, int maxlen, GateLens lens,
     int32_t *__restrict__ sums, uint8_t *__restrict__ retire) {
-    constexpr int kSlots = kGateThreads / SEG;             // pairs that advance together
+    constexpr int kSlots = kPrefixThreads / SEG;           // pairs that advance together
     __shared__ int32_t s_act[16 * SEG];                      // [member][step], the first SEG steps
     __shared__ unsigned s_d[3][kSlots][SEG + 1];             // anti-diagonals d-2, d-1, d of every slot, by table row
     __shared__ int s_sum[8];
 
     const int tid = threadIdx.x, g = blockIdx.x;
     if (tid < 8) s_sum[tid] = 0;
-    for (int i = tid; i < G * SEG; i += kGateThreads) {
+    for (int i = tid; i < G * SEG; i += kPrefixThreads) {
         const int r = i / SEG, c = i - r * SEG;
         s_act[i] = (c < stride) ? actions[((size_t)g * G + r) * stride + c] : -1 - c;
     }
@@ -248,7 +242,7 @@ int launch_gate_antidiag(const int32_t *actions, int n_groups, int G, int stride
     int maxlen = 0;
     for (int l = 0; l < lens.n; ++l) maxlen = lens.len[l] > maxlen ? lens.len[l] : maxlen;
     const int pairs = G * (G - 1) / 2;
-    dim3 grid(n_groups), block(kGateThreads);
+    dim3 grid(n_groups), block(kPrefixThreads);
     if (maxlen <= 16)
         gate_antidiag_kernel<16><<<grid, block, 0, stream>>>(actions, n_groups, G, stride, pairs, maxlen, lens, sums, retire);
     else
@@ -262,35 +256,24 @@ int launch_gate(const int32_t *actions, int n_groups, int G, int stride, const G
     if (n_groups <= 0) return SR_OK;
     int maxlen = 0;
     for (int l = 0; l < lens.n; ++l) maxlen = lens.len[l] > maxlen ? lens.len[l] : maxlen;
-    PrefixGeom q{};
-    if (!prefix_direct(n_groups, G, maxlen, 6)) {
-        // Beyond 16 steps a lane with two pairs has twice the instructions: one pair where that still leaves no more than eight
-        // wavefronts per compute unit (300 groups of 8, 32 steps: 6.6 us, 7.6 with two; 2000 groups 6.2)
-        const int kind = maxlen <= 16 ? PREFIX_TWO16 : (long long)n_groups * G * (G - 1) / 2 <= 256 * 512 ? PREFIX_ONE32 : PREFIX_TWO32;
-        if (!prefix_geometry_tables(n_groups, G, maxlen, kind, kGateLds, kGateHashLds, 16, &q)) return SR_E_ARG;
-        const dim3 grid(ceil_div(n_groups, q.groups)), block(q.threads);
-        const size_t lds = q.total + 16 * q.groups;
-#define SR_GATE(KIND) gate_table_kernel<KIND><<<grid, block, lds, stream>>>(actions, n_groups, stride, q, lens, sums, retire)
-        if (kind == PREFIX_TWO16) SR_GATE(PREFIX_TWO16);
-        else if (kind == PREFIX_TWO32) SR_GATE(PREFIX_TWO32);
-        else SR_GATE(PREFIX_ONE32);
-#undef SR_GATE
-        SR_HIP(hipGetLastError());
-        return SR_OK;
-    }
-    const int kmax = maxlen <= 4 ? 4 : maxlen <= 8 ? 8 : maxlen <= 12 ? 12 : maxlen <= 16 ? 16 : maxlen <= 24 ? 24 : 32;
-    if (!prefix_geometry_direct(n_groups, G, maxlen, kmax, kGateLds, 16, &q)) return SR_E_ARG;
-    const dim3 grid(ceil_div(n_groups, q.groups)), block(q.threads);
-    const size_t lds = q.total + 16 * q.groups;
-#define SR_GATE(K) gate_direct_kernel<K><<<grid, block, lds, stream>>>(actions, n_groups, stride, q, lens, sums, retire)
-    switch (kmax) {
-        case 4: SR_GATE(4); break;
-        case 8: SR_GATE(8); break;
-        case 12: SR_GATE(12); break;
-        case 16: SR_GATE(16); break;
-        case 24: SR_GATE(24); break;
-        default: SR_GATE(32); break;
-    }
+    GateLayout t;
+    if (!gate_layout(n_groups, G, maxlen, &t)) return SR_E_ARG;
+    const dim3 grid(ceil_div(n_groups, t.q.groups)), block(t.q.threads);
+#define SR_TABLES(KIND) gate_table_kernel<KIND><<<grid, block, t.lds, stream>>>(actions, n_groups, stride, t.q, lens, sums, retire)
+#define SR_GATE(K) gate_direct_kernel<K><<<grid, block, t.lds, stream>>>(actions, n_groups, stride, t.q, lens, sums, retire)
+    if (t.direct) {
+        switch (t.size) {
+            case 4: SR_GATE(4); break;
+            case 8: SR_GATE(8); break;
+            case 12: SR_GATE(12); break;
+            case 16: SR_GATE(16); break;
+            case 24: SR_GATE(24); break;
+            default: SR_GATE(32); break;
+        }
+    } else if (t.size == PREFIX_TWO16) SR_TABLES(PREFIX_TWO16);
+    else if (t.size == PREFIX_TWO32) SR_TABLES(PREFIX_TWO32);
+    else SR_TABLES(PREFIX_ONE32);
+#undef SR_TABLES
 #undef SR_GATE
     SR_HIP(hipGetLastError());
     return SR_OK;

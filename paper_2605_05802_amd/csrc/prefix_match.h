@@ -18,112 +18,12 @@
 // are larger, and the groups of a workgroup take turns in the LDS, as many at a time as fit.
 //
 // Comparison.  Every pair compares its 2 * K symbols in registers: 2 * K * K more instructions per pair, and nothing to build.
-// prefix_direct says which.
+// prefix_direct says which (prefix_plan.h, as how a workgroup lays out its groups).
 #pragma once
+#include "prefix_plan.h"
 #include "sr_internal.h"
 
 namespace sr {
-
-// row of the directly compared symbols: an odd multiple of 16 bytes, the rows of sixteen consecutive members in different banks
-__host__ __device__ constexpr int prefix_act_stride(int kmax) { return kmax % 8 == 4 ? kmax : kmax + 4; }
-
-// Compare, or build tables?  The symbols are not known here, so both kinds count.  Up to eight steps comparing costs little more
-// than tables of symbols in their range and much less than hashing (65 536 groups of 8, 5 steps: gate 20.5 us; with tables 17.8
-// and 31; 3 members: 6.3, 7.9 and 13).  Longer prefixes share a table among G - 1 pairs: up to `few` members comparing is
-// still the better of the two where the groups fill the chip (65 536 groups of 5, 12 steps: gate 17.5 us, tables 15.3 and 32;
-// groups of 3: signals 30, tables 32 and 49), but not in too few wavefronts (64 groups of 3, 32 steps: gate 10.0 us by
-// comparison, 7.7 with tables).
-inline bool prefix_direct(int n_groups, int G, int L, int few) {
-    return L <= 8 || (G <= few && (long long)n_groups * G >= 1500LL * L);
-}
-
-// How a workgroup lays out its groups; L = longest requested prefix.
-struct PrefixGeom {
-    int G, L, Q;          // Q = member pairs: columns of the tables
-    int groups, threads;  // groups per workgroup and its size
-    int lanes;            // lanes per group: its pairs when comparing, (member, member pair) combinations with tables
-    // tables only: bytes of LDS
-    int row_bytes;        // one symbol's masks
-    int body;             // offset of the tables, behind the element ids [member][16 or 32] (16 bits: symbol * row_bytes)
-    int slots_log2;       // hash slots per group: a power of two, at least twice its elements
-    int hash_groups;      // groups that take part in a round where symbols are hashed
-    int total;
-};
-constexpr int kPrefixSyms = 64;         // table rows of a group whose symbols need no hashing
-
-// How a lane runs its pairs: two in the halves of a register (up to 16 steps), two in a register each, or one.  The last takes
-// more lanes and a shorter chain of instructions each: for launches that do not fill the chip.
-enum PrefixKind { PREFIX_TWO16, PREFIX_TWO32, PREFIX_ONE32 };
-__host__ __device__ constexpr int prefix_steps(int kind) { return kind == PREFIX_TWO16 ? 16 : 32; }
-// a group's tables when its symbols are hashed: a row per element, the slots, the symbols themselves
-__host__ __device__ inline int prefix_hash_rows(const PrefixGeom &q) { return q.G * q.L * q.row_bytes; }
-__host__ __device__ inline int prefix_hash_bytes(const PrefixGeom &q) {
-    return round_up(prefix_hash_rows(q), 16) + (4 << q.slots_log2) + round_up(q.G * q.L * 4, 16);
-}
-
-// Groups per workgroup: the count that fills whole wavefronts of lanes best within 256 lanes.  A few groups (an episode's
-// gate) are spread over the compute units first: no workgroup takes more than its share of 512.
-inline bool prefix_geometry_direct(int n_groups, int G, int L, int kmax, int lds_limit, int extra, PrefixGeom *q) {
-    *q = PrefixGeom{};
-    q->G = G;
-    q->L = L;
-    q->lanes = G * (G - 1) / 2;
-    double best = 0.0;
-    for (int n = 1; n * q->lanes <= 256 && n <= ceil_div(n_groups, 512); ++n) {
-        if (n * (G * prefix_act_stride(kmax) * 4 + extra) > lds_limit) break;
-        const double use = (double)(n * q->lanes) / round_up(n * q->lanes, 64);
-        if (use >= best) {
-            best = use;
-            q->groups = n;
-        }
-    }
-    q->total = q->groups * G * prefix_act_stride(kmax) * 4;
-    // lanes for the pairs, and no more than eight elements a lane while the symbols are staged (small groups have more
-    // elements than pairs: 16384 groups of 2 with 32 arbitrary symbols take the gate 10.5 us, 25.5 with 64 lanes)
-    const int lanes = q->groups * q->lanes, build = ceil_div(q->groups * G * (kmax <= 16 ? kmax : 32), 8);
-    q->threads = round_up(lanes > build ? lanes : build, 64);
-    if (q->threads > 256) q->threads = 256;
-    return q->groups > 0;
-}
-
-constexpr int kPrefixVecs = 4;          // 16-byte pieces of the members' rows that a lane loads at most
-inline bool prefix_geometry_tables(int n_groups, int G, int L, int kind, int lds_limit, int hash_lds, int extra, PrefixGeom *q) {
-    *q = PrefixGeom{};
-    q->G = G;
-    q->L = L;
-    q->Q = ceil_div(G, 2);
-    q->lanes = kind == PREFIX_ONE32 ? G * (G - 1) / 2 : q->Q * q->Q - (G & 1);
-    q->row_bytes = q->Q * (kind == PREFIX_TWO16 ? 4 : 8);
-    q->slots_log2 = 4;
-    while ((1 << q->slots_log2) < 2 * G * L) ++q->slots_log2;
-    const int steps = prefix_steps(kind), hash = prefix_hash_bytes(*q);
-    auto body = [&](int n) { const int b = n * kPrefixSyms * q->row_bytes; return round_up(b > hash ? b : hash, 16); };
-    double best = 0.0;
-    for (int n = 1; n * q->lanes <= 256 && n * G * (steps / 4) <= 256 * kPrefixVecs && n <= ceil_div(n_groups, 512); ++n) {
-        if (n * (G * steps * 2 + extra) + body(n) > lds_limit) break;
-        const double use = (double)(n * q->lanes) / round_up(n * q->lanes, 64);
-        if (use >= best) {
-            best = use;
-            q->groups = n;
-        }
-    }
-    if (q->groups == 0) return false;
-    q->body = round_up(q->groups * G * steps * 2, 16);
-    // hashed symbols: all groups at once where that costs no workgroup its place; otherwise two at least
-    const int all = q->groups * hash, most = lds_limit - q->groups * extra - q->body;
-    int room = hash_lds - q->groups * extra - q->body;
-    if (room < 2 * hash) room = 2 * hash;
-    if (room > most || ceil_div(n_groups, q->groups) <= 512) room = most;
-    int bytes = round_up(room < all ? room / hash * hash : all, 16);
-    if (bytes < body(q->groups)) bytes = body(q->groups);
-    q->hash_groups = bytes / hash;
-    if (q->hash_groups > q->groups) q->hash_groups = q->groups;
-    q->total = q->body + bytes;
-    const int lanes = q->groups * q->lanes, build = ceil_div(q->groups * G * steps, ceil_div(n_groups, q->groups) <= 1024 ? 2 : 8);
-    q->threads = round_up(lanes > build ? lanes : build, 64);
-    if (q->threads > 256) q->threads = 256;
-    return true;
-}
 
 #ifdef __HIPCC__
 // x / d for 0 <= x < 2^14 and 1 <= d <= 64, inv = 1.0f / d: the distance of (x + 1/2) / d from an integer is at least 1/128,

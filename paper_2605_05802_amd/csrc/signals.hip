@@ -34,10 +34,6 @@ static_assert(sizeof(sr_signals_t) == 64, "sr_signals_t is part of the C boundar
 namespace sr {
 namespace {
 
-constexpr int kSigThreads = 256;
-constexpr int kSigLds = 52 * 1024;                   // LDS of symbols, tables and sums: three workgroups per compute unit or more
-constexpr int kSigHashLds = 40 * 1024;               // ... where symbols are hashed: four
-constexpr int kSigTerms = 24 * 1024;                 // LDS that the quotients may take: three K of sixteen groups of 8 at once
 constexpr int kSigMaxLens = 8;
 constexpr long long kLcm32 = 144403552893600LL;      // lcm(1..32)
 
@@ -50,31 +46,6 @@ struct SigLens {
     __device__ int len(int l) const { return (int)(packed >> (6 * l)) & 63; }
     __device__ int slot(int K) const { return __popc(wanted & ((1u << (K - 1)) - 1u)); }     // index among the distinct lengths
 };
-
-// What the workgroup keeps behind symbols and tables: byte offsets, 8-byte arrays first.
-struct SigLds {
-    int out, lcm, recip, p, log_p, repeats, code, obs, at, end, first, hold, total;
-    int code_stride;                  // pairs of a group, made odd: the groups' terms in different banks
-};
-__host__ __device__ inline SigLds sig_lds(int G, int groups, int n_lens) {
-    SigLds o;
-    const int pairs = G * (G - 1) / 2, members = groups * G;
-    o.code_stride = pairs | 1;
-    o.out = 0;                                    // [K][group] sr_signals_t
-    o.lcm = o.out + n_lens * groups * 64;         // lcm(1..32) / n
-    o.recip = o.lcm + 33 * 8;                     // 1 / n, n = 1 .. 63 (0: 0)
-    o.p = o.recip + 64 * 8;                       // 0, then c / n, 1 <= c <= n <= G
-    o.log_p = o.p + (G * (G + 1) / 2 + 1) * 8;    // log(c / n)
-    o.repeats = o.log_p + (G * (G + 1) / 2 + 1) * 8;    // [K][group] members whose prefix an earlier member has
-    o.code = o.repeats + n_lens * groups * 4;     // [distinct K][group][pair] see SigCode
-    o.obs = o.code + n_lens * groups * o.code_stride * 4;        // [K][member] o_{i,K}
-    o.at = o.obs + n_lens * members * 4;          // [K][group] bits of the members that reach step K | finished by K << 24
-    o.end = o.at + n_lens * groups * 4;           // [member]
-    o.first = o.end + members * 4;                // [member] positions of first occurrences of bigrams
-    o.hold = o.first + members * 4;               // [K][member] holders of its step-K action if it is the first of them, | 32 the
-    o.total = round_up(o.hold + n_lens * members * 2, 16);       // first to hold its observation (16 bits)
-    return o;
-}
 
 // One pair's integers at one K; distance 0 means equal prefixes
 struct SigCode {
@@ -152,7 +123,7 @@ struct SigState {
 
 // KMAX == 0: equality masks from tables; otherwise a pair a lane, symbols compared in registers, at most KMAX steps
 template <int KIND, int KMAX>
-__global__ __launch_bounds__(kSigThreads) void signals_kernel(
+__global__ __launch_bounds__(kPrefixThreads) void signals_kernel(
     const int32_t *__restrict__ actions, const int32_t *__restrict__ obs, const int32_t *__restrict__ end_step,
     int n_groups, int stride, PrefixGeom q, SigLens lens, int sums_at, int terms_at_once, sr_signals_t *__restrict__ out) {
     extern __shared__ __align__(16) char lds[];      // symbols and tables, later the quotients; from sums_at on SigLds
@@ -555,46 +526,22 @@ extern "C" int sr_signals_batch(const int32_t *actions, const int32_t *obs, cons
     lens.d_bound = (long long)((num * P * (__int128)kLcm32 + 999999) / 1000000);
     lens.tau_num = (long long)__builtin_llround(tau_H * 1e6);
     if (n_groups == 0) return SR_OK;
-    // LDS behind symbols and tables: at most `extra` for every group, and `fixed`
-    const int extra = sig_lds(G, 2, n_lens).total - sig_lds(G, 1, n_lens).total + 16, fixed = sig_lds(G, 1, n_lens).total - extra + 16;
+    SignalsLayout t;
+    if (!signals_layout(n_groups, G, maxlen, n_lens, __builtin_popcount(lens.wanted), &t)) return SR_E_ARG;
+    const dim3 grid(ceil_div(n_groups, t.q.groups)), block(t.q.threads);
     hipStream_t st = (hipStream_t)stream;
-    PrefixGeom q{};
-    // quotients take the place of symbols and tables: of every length at once up to kSigTerms bytes
-    int distinct = 0, terms_at_once = 0, sums_at = 0;
-    for (unsigned w = lens.wanted; w; w &= w - 1) ++distinct;
-    auto place = [&] {
-        const int per_len = q.groups * sig_lds(G, q.groups, n_lens).code_stride * 16, room = q.total > kSigTerms ? q.total : kSigTerms;
-        terms_at_once = room / per_len < 1 ? 1 : room / per_len < distinct ? room / per_len : distinct;
-        sums_at = round_up(q.total > terms_at_once * per_len ? q.total : terms_at_once * per_len, 16);
-    };
-#define SR_SIG(KIND, KMAX)                                                                              \
-    (place(), signals_kernel<KIND, KMAX><<<dim3(ceil_div(n_groups, q.groups)), dim3(q.threads),          \
-                                           sums_at + sig_lds(G, q.groups, n_lens).total, st>>>(         \
-        actions, obs, end_step, n_groups, stride, q, lens, sums_at, terms_at_once, out))
-    // Up to eight steps the tables are nevertheless cheaper for large groups that fill the chip (65 536 groups of 8, 5 steps: 60 us,
-    // 70 with arbitrary symbols, 70 by comparison; 8 steps: 60, 87 and 70; groups of 16: 230, 254 and 343)
-    const bool many = (long long)n_groups * G >= 32000 && (G >= 12 || (G >= 8 && maxlen <= 6));
-    // a launch that does not fill the chip takes whole workgroups: four wavefronts share the phases of a group
-    auto fill = [&] { if (ceil_div(n_groups, q.groups) <= 512 && q.groups <= 4) q.threads = kSigThreads; };
-    if (prefix_direct(n_groups, G, maxlen, 3) && !many) {
-        const int kmax = maxlen <= 8 ? 8 : maxlen <= 16 ? 16 : maxlen <= 24 ? 24 : 32;
-        if (!prefix_geometry_direct(n_groups, G, maxlen, kmax, kSigLds - fixed, extra, &q)) return SR_E_ARG;
-        fill();
-        switch (kmax) {
+#define SR_SIG(KIND, KMAX) \
+    signals_kernel<KIND, KMAX><<<grid, block, t.lds, st>>>(actions, obs, end_step, n_groups, stride, t.q, lens, t.sums_at, t.terms_at_once, out)
+    if (t.direct) {
+        switch (t.size) {
             case 8: SR_SIG(PREFIX_ONE32, 8); break;
             case 16: SR_SIG(PREFIX_ONE32, 16); break;
             case 24: SR_SIG(PREFIX_ONE32, 24); break;
             default: SR_SIG(PREFIX_ONE32, 32); break;
         }
-    } else {
-        // beyond 16 steps a pair a lane where the pairs leave eight wavefronts per compute unit or fewer, as in the gate
-        const int kind = maxlen <= 16 ? PREFIX_TWO16 : (long long)n_groups * G * (G - 1) / 2 <= 256 * 512 ? PREFIX_ONE32 : PREFIX_TWO32;
-        if (!prefix_geometry_tables(n_groups, G, maxlen, kind, kSigLds - fixed, kSigHashLds - fixed, extra, &q)) return SR_E_ARG;
-        fill();
-        if (kind == PREFIX_TWO16) SR_SIG(PREFIX_TWO16, 0);
-        else if (kind == PREFIX_TWO32) SR_SIG(PREFIX_TWO32, 0);
-        else SR_SIG(PREFIX_ONE32, 0);
-    }
+    } else if (t.size == PREFIX_TWO16) SR_SIG(PREFIX_TWO16, 0);
+    else if (t.size == PREFIX_TWO32) SR_SIG(PREFIX_TWO32, 0);
+    else SR_SIG(PREFIX_ONE32, 0);
 #undef SR_SIG
     SR_HIP(hipGetLastError());
     return SR_OK;
