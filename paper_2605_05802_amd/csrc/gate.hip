@@ -11,9 +11,9 @@
 // table serves every requested prefix length.
 //
 // Bound: memory and vector ALU about equally; the 64 MB of input alone would take 13 us.  65 536 groups of 8, prefixes 5, 10 and
-// 15: 18.3 us; 41.8 with a lane per pair, masks of one member per LDS read and 4-byte loads of the symbols.  32 steps: 42
-// against 132 us, groups of 16 with 16 steps 62 against 144.  With symbols beyond the tables' range (all different) 86 us, 104
-// before.  Compared in registers: groups of 5, 12 steps 17.5 us.
+// 15: 18.5 us; 42.2 with a lane per pair, masks of one member per LDS read and 4-byte loads of the symbols.  32 steps: 37
+// against 121 us, 16 384 groups of 16 with 16 steps 14 against 29.  Symbols of 64 and more: see prefix_turns.  Compared in registers:
+// groups of 5, 12 steps 13.9 us.
 #include "prefix_match.h"
 
 namespace sr {
@@ -74,9 +74,9 @@ __global__ __launch_bounds__(kPrefixThreads) void gate_table_kernel(
     const int n_here = min(q.groups, n_groups - g0), rows = n_here * G;
     PrefixRows<KIND> x;
     x.load(q, rows, actions + (size_t)g0 * G * stride, stride, g0 + n_here == n_groups ? rows - 1 : -1);
-    prefix_zero(lds, q.body, q.groups * kPrefixSyms * q.row_bytes);
+    prefix_zero(lds, q.body, q.groups * kPrefixSyms * q.row_bytes, tid);
     for (int i = tid; i < 4 * q.groups; i += blockDim.x) s_sum[i] = 0;
-    const bool direct = prefix_all_fit(x.fits(rows));
+    const unsigned beyond = prefix_beyond<KIND>(rows, x);
 
     const int gl = small_div(tid, 1.0f / (float)q.lanes);      // group within the block
     int i, j;
@@ -104,15 +104,15 @@ __global__ __launch_bounds__(kPrefixThreads) void gate_table_kernel(
             }
         }
     };
-    if (direct) {
-        prefix_mark<KIND>(lds, q, rows, x);
+    if (beyond == 0) {
+        prefix_mark<KIND, true>(lds, q, rows, x, 0, q.groups, kPrefixSyms * q.row_bytes);
         __syncthreads();
         pairs(0, q.groups, kPrefixSyms * q.row_bytes);
     } else {
-        for (int s0 = 0; s0 < n_here; s0 += q.hash_groups) {
-            __syncthreads();                          // nobody reads the tables of the round before
-            prefix_hash<KIND>(lds, q, rows, x, s0, q.hash_groups);
-            pairs(s0, q.hash_groups, round_up(prefix_hash_rows(q), 16));
+        const PrefixTurns t = prefix_turns(q, n_here, beyond);
+        for (int s0 = 0; s0 < n_here; s0 += t.groups) {
+            prefix_turn<KIND>(lds, q, rows, x, s0, t);
+            pairs(s0, t.groups, t.group_bytes);
         }
     }
     __syncthreads();

@@ -12,10 +12,11 @@
 // LDS read gives a lane those of two neighbouring members, and the lane runs one a against both: the pairs (i, 2q) and
 // (i, 2q + 1).  Up to 16 steps the two masks are the halves of one register, and a step of the recurrence is one bitwise or
 // packed 16-bit instruction for both pairs; beyond, two registers.  A group of eight takes 16 lanes instead of 28.
-// Symbols below 64 (action ids of a turn are tokens modulo a small number) index the tables as they are.  Where some
-// symbol of the workgroup is not, every symbol is first replaced by the index of one element of its group that holds it
-// (hash insertion in LDS, compare-and-swap on the slot; which of several equal elements wins does not matter); such tables
-// are larger, and the groups of a workgroup take turns in the LDS, as many at a time as fit.
+// Small symbols (action ids of a turn are tokens modulo a small number) index the tables as they are: the groups of a workgroup
+// all at once where every symbol is below 64, otherwise with as many rows as the largest symbol of the workgroup asks for, the
+// groups taking turns in the LDS, as many at a time as fit.  Where fewer would fit than by hashing, every symbol is first
+// replaced by the index of one element of its group that holds it (hash insertion in LDS, compare-and-swap on the slot; which
+// of several equal elements wins does not matter), with turns too.
 //
 // Comparison.  Every pair compares its 2 * K symbols in registers: 2 * K * K more instructions per pair, and nothing to build.
 // prefix_direct says which (prefix_plan.h, as how a workgroup lays out its groups).
@@ -133,15 +134,15 @@ struct PrefixRows {
 
     __device__ static bool used(int u, int rows) { return u * (int)blockDim.x < rows * kRowVecs; }       // uniform
     // lanes beyond the last row take it once more
-    __device__ static int row(int u, int rows) { return min((int)(threadIdx.x + u * blockDim.x) / kRowVecs, rows - 1); }
-    __device__ static int step(int u) { return ((int)(threadIdx.x + u * blockDim.x) % kRowVecs) * 4; }
+    __device__ static int row(int u, int rows, int tid) { return min((tid + u * (int)blockDim.x) / kRowVecs, rows - 1); }
+    __device__ static int step(int u, int tid) { return ((tid + u * (int)blockDim.x) % kRowVecs) * 4; }
 
     __device__ __forceinline__ void load(const PrefixGeom &q, int rows, const int32_t *__restrict__ src, int stride, int tail) {
         typedef int32_t piece __attribute__((ext_vector_type(4), aligned(4)));
 #pragma unroll
         for (int u = 0; u < kPrefixVecs; ++u) {
             if (!used(u, rows)) break;
-            const int r = row(u, rows), c = step(u);
+            const int r = row(u, rows, threadIdx.x), c = step(u, threadIdx.x);
             const int32_t *p = src + (size_t)r * stride + c;
             piece x = {0, 0, 0, 0};
             if (c < q.L) {
@@ -162,6 +163,16 @@ struct PrefixRows {
         }
         return any < (unsigned)kPrefixSyms;
     }
+    // of this lane's symbols, as unsigned numbers
+    __device__ __forceinline__ unsigned largest(int rows) const {
+        unsigned most = 0;
+#pragma unroll
+        for (int u = 0; u < kPrefixVecs; ++u) {
+            if (!used(u, rows)) break;
+            most = max(most, max(max((unsigned)v[u][0], (unsigned)v[u][1]), max((unsigned)v[u][2], (unsigned)v[u][3])));
+        }
+        return most;
+    }
 };
 
 // byte offset of the word that holds member m's mask within a table row, and the mask's shift in it
@@ -170,36 +181,62 @@ __device__ __forceinline__ int prefix_column(int m) { return KIND == PREFIX_TWO1
 template <int KIND>
 __device__ __forceinline__ int prefix_shift(int m) { return KIND == PREFIX_TWO16 ? (m & 1) * 16 : 0; }
 
-__device__ __forceinline__ void prefix_zero(char *lds, int from, int bytes) {
-    for (int i = threadIdx.x * 16; i < bytes; i += blockDim.x * 16) *(uint4 *)(lds + from + i) = make_uint4(0, 0, 0, 0);
+// threadIdx.x anew in every turn: what the compiler works out from it ahead of the turns costs 20 to 30 registers, and with them a
+// fourth of the wavefronts (signals of 65 536 groups of 8: 72 us instead of 62, whatever the symbols)
+__device__ __forceinline__ int turn_tid() {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    return tid;
 }
 
-// Do all lanes' symbols index the tables as they are?  A barrier, behind which the tables are zero too.
-__device__ __forceinline__ bool prefix_all_fit(bool fits) {
-    __shared__ int s_fits[4];
-    s_fits[threadIdx.x >> 6] = __all(fits) ? 1 : 0;              // every lane of a wavefront writes the same
-    __syncthreads();
-    bool every = true;
-#pragma unroll 1
-    for (int w = 0; w < (int)blockDim.x >> 6; ++w) every &= s_fits[w] != 0;
-    return __builtin_amdgcn_readfirstlane(every);
+__device__ __forceinline__ void prefix_zero(char *lds, int from, int bytes, int tid) {
+    for (int i = tid * 16; i < bytes; i += blockDim.x * 16) *(uint4 *)(lds + from + i) = make_uint4(0, 0, 0, 0);
 }
 
-// Tables of all groups from symbols that need no hashing; the tables are zero.  The caller's barrier follows.
+// 0 if all of the workgroup's symbols index tables of kPrefixSyms rows, otherwise the largest of them, as an unsigned number.
+// A barrier, behind which the tables are zero too.
 template <int KIND>
-__device__ __forceinline__ void prefix_mark(char *lds, const PrefixGeom &q, int rows, const PrefixRows<KIND> &x) {
+__device__ __forceinline__ unsigned prefix_beyond(int rows, const PrefixRows<KIND> &x) {
+    __shared__ unsigned s_most[4];
+    unsigned most = 0;
+    if (!__all(x.fits(rows))) {                                  // the wavefront's: within rows of 16 lanes by rotation, then across them
+        most = x.largest(rows);
+        most = max(most, (unsigned)__builtin_amdgcn_update_dpp(0, (int)most, 0x128, 0xF, 0xF, false));
+        most = max(most, (unsigned)__builtin_amdgcn_update_dpp(0, (int)most, 0x124, 0xF, 0xF, false));
+        most = max(most, (unsigned)__builtin_amdgcn_update_dpp(0, (int)most, 0x122, 0xF, 0xF, false));
+        most = max(most, (unsigned)__builtin_amdgcn_update_dpp(0, (int)most, 0x121, 0xF, 0xF, false));
+        const auto h = __builtin_amdgcn_permlane32_swap(most, most, false, false);
+        most = max(h[0], h[1]);
+        const auto q = __builtin_amdgcn_permlane16_swap(most, most, false, false);
+        most = max(q[0], q[1]);
+    }
+    s_most[threadIdx.x >> 6] = most;                             // every lane of a wavefront writes the same
+    __syncthreads();
+    most = 0;
+#pragma unroll 1
+    for (int w = 0; w < (int)blockDim.x >> 6; ++w) most = max(most, s_most[w]);
+    return __builtin_amdgcn_readfirstlane(most);
+}
+
+// Tables of the groups g0 .. g0 + n - 1 (ALL: of every group), `group_bytes` each, from symbols that index them as they are; the
+// tables are zero.  The caller's barrier follows.
+template <int KIND, bool ALL>
+__device__ __forceinline__ void prefix_mark(char *lds, const PrefixGeom &q, int rows, const PrefixRows<KIND> &x, int g0, int n,
+                                            int group_bytes) {
     typedef PrefixRows<KIND> R;
     const float inv_G = 1.0f / (float)q.G;
+    const int tid = ALL ? (int)threadIdx.x : turn_tid();
 #pragma unroll
     for (int u = 0; u < kPrefixVecs; ++u) {
         if (!R::used(u, rows)) break;
-        const int r = R::row(u, rows), c = R::step(u), g = small_div(r, inv_G), m = r - __mul24(g, q.G);
+        const int r = R::row(u, rows, tid), c = R::step(u, tid), g = small_div(r, inv_G), m = r - __mul24(g, q.G);
+        if (!ALL && (unsigned)(g - g0) >= (unsigned)n) continue;
         unsigned id[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) id[e] = (unsigned)__mul24(x.v[u][e], q.row_bytes);
         *(uint2 *)(lds + (r * R::kSteps + c) * 2) = make_uint2(id[0] | id[1] << 16, id[2] | id[3] << 16);
         if (c < q.L) {                               // steps from L on set bits of symbol 0 that nobody looks at
-            char *t = lds + q.body + __mul24(g, kPrefixSyms * q.row_bytes) + prefix_column<KIND>(m);
+            char *t = lds + q.body + __mul24(ALL ? g : g - g0, group_bytes) + prefix_column<KIND>(m);
             const unsigned bit = 1u << (c + prefix_shift<KIND>(m));
 #pragma unroll
             for (int e = 0; e < 4; ++e) atomicOr((unsigned *)(t + id[e]), bit << e);
@@ -211,15 +248,15 @@ __device__ __forceinline__ void prefix_mark(char *lds, const PrefixGeom &q, int 
 template <int KIND>
 __device__ __forceinline__ void prefix_hash(char *lds, const PrefixGeom &q, int rows, const PrefixRows<KIND> &x, int g0, int n) {
     typedef PrefixRows<KIND> R;
-    const int tid = threadIdx.x, nt = blockDim.x, GL = q.G * q.L, r0 = g0 * q.G, here = min(n * q.G, rows - r0);
+    const int tid = turn_tid(), nt = blockDim.x, GL = q.G * q.L, r0 = g0 * q.G, here = min(n * q.G, rows - r0);
     const int slots_at = q.body + q.hash_groups * round_up(prefix_hash_rows(q), 16);
     unsigned *slots = (unsigned *)(lds + slots_at);
     int32_t *act = (int32_t *)(lds + slots_at + (q.hash_groups * 4 << q.slots_log2));
-    prefix_zero(lds, q.body, slots_at - q.body + (q.hash_groups * 4 << q.slots_log2));        // masks and slots
+    prefix_zero(lds, q.body, slots_at - q.body + (q.hash_groups * 4 << q.slots_log2), tid);        // masks and slots
 #pragma unroll
     for (int u = 0; u < kPrefixVecs; ++u) {
         if (!R::used(u, rows)) break;
-        const int r = R::row(u, rows) - r0, c = R::step(u);
+        const int r = R::row(u, rows, tid) - r0, c = R::step(u, tid);
         if (r >= 0 && r < here) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -252,6 +289,21 @@ __device__ __forceinline__ void prefix_hash(char *lds, const PrefixGeom &q, int 
                  1u << (c + prefix_shift<KIND>(m)));
     }
     __syncthreads();
+}
+
+// Tables of a turn's groups, from g0 on, in the place of the turn before.  Begins and ends with a barrier.
+template <int KIND>
+__device__ __forceinline__ void prefix_turn(char *lds, const PrefixGeom &q, int rows, const PrefixRows<KIND> &x, int g0,
+                                            const PrefixTurns &t) {
+    __syncthreads();                                 // nobody reads the tables of the turn before
+    if (t.hashed) {
+        prefix_hash<KIND>(lds, q, rows, x, g0, t.groups);
+    } else {
+        prefix_zero(lds, q.body, t.groups * t.group_bytes, turn_tid());
+        __syncthreads();
+        prefix_mark<KIND, false>(lds, q, rows, x, g0, t.groups, t.group_bytes);
+        __syncthreads();
+    }
 }
 
 // Eight steps of member row `r`, from step c on (a multiple of eight): table rows as byte offsets

@@ -29,7 +29,7 @@ struct PrefixGeom {
     int row_bytes;        // one symbol's masks
     int body;             // offset of the tables, behind the element ids [member][16 or 32] (16 bits: symbol * row_bytes)
     int slots_log2;       // hash slots per group: a power of two, at least twice its elements
-    int hash_groups;      // groups that take part in a round where symbols are hashed
+    int hash_groups;      // groups that take part in a turn where symbols are hashed
     int total;
 };
 constexpr int kPrefixSyms = 64;         // table rows of a group whose symbols need no hashing
@@ -42,6 +42,37 @@ SR_HD constexpr int prefix_steps(int kind) { return kind == PREFIX_TWO16 ? 16 : 
 SR_HD inline int prefix_hash_rows(const PrefixGeom &q) { return q.G * q.L * q.row_bytes; }
 SR_HD inline int prefix_hash_bytes(const PrefixGeom &q) {
     return round_up(prefix_hash_rows(q), 16) + (4 << q.slots_log2) + round_up(q.G * q.L * 4, 16);
+}
+
+// x / d for 0 <= x < 2^14 and 1 <= d < 2^14.  On the device by a reciprocal, a few instructions instead of 35: (x + 1/2) / d is 1 / 2d
+// or more from an integer, and the three roundings move it by less than 2^-21 x / d
+SR_HD inline int short_quotient(int x, int d) {
+#ifdef __HIP_DEVICE_COMPILE__
+    return (int)(((float)x + 0.5f) * __builtin_amdgcn_rcpf((float)d));
+#else
+    return x / d;
+#endif
+}
+
+// How the groups of a workgroup take turns when some symbol is not below kPrefixSyms; `most`: the largest symbol.  Tables with a row
+// for every number up to it where at least as many groups fit as by hashing, which is so for every symbol below the number of a
+// group's elements.  65 536 groups of 8, prefixes 5, 10 and 15, gate / signals in us: symbols below 64 18.5 / 61.5, all groups at once;
+// below 100 25.8 / 78.1 in turns, hashed 50.0 / 108 (and with 16-bit masks of one member a read, whose tables held 120 symbols, 42.1 /
+// 120); below 200 34.2 / 96.7, hashed 50.9 / 110; below 1000 53.5 / 116, hashed; all different 82 / 148.  32 steps, below 128: 66 / 124,
+// hashed 147 / 352.
+struct PrefixTurns {
+    bool hashed;
+    int groups, group_bytes;            // groups of a turn; one group's tables
+};
+SR_HD inline PrefixTurns prefix_turns(const PrefixGeom &q, int n_here, unsigned most) {
+    if (most < 2048) {                               // no group has more rows, hashed or not
+        const int pieces = (((int)most + 1) * q.row_bytes + 15) >> 4, fit = short_quotient((q.total - q.body) >> 4, pieces);
+        if (fit >= q.hash_groups) {
+            const int turns = short_quotient(n_here + fit - 1, fit);
+            return PrefixTurns{false, short_quotient(n_here + turns - 1, turns), pieces * 16};       // turns of equal size
+        }
+    }
+    return PrefixTurns{true, q.hash_groups, round_up(prefix_hash_rows(q), 16)};
 }
 
 // Groups per workgroup: the count that fills whole wavefronts of lanes best within 256 lanes.  A few groups (an episode's

@@ -163,16 +163,16 @@ __global__ __launch_bounds__(kPrefixThreads) void signals_kernel(
         s_out[w].lev_scaled = 0;
         s_out[w].lev_sum = 0;
     }
-    if constexpr (TABLES) prefix_zero(lds, q.body, q.groups * kPrefixSyms * q.row_bytes);
+    if constexpr (TABLES) prefix_zero(lds, q.body, q.groups * kPrefixSyms * q.row_bytes, tid);
     for (int w = tid, u = 0; w < NL * rows; w += nt, ++u) {
         int l, r;
         obs_item(w, &l, &r);
         s_obs[l * n_rows + r] = u == 0 ? obs_v[0] : u == 1 ? obs_v[1] : load_obs(w);
     }
     for (int i = tid; i < rows; i += nt) s_end[i] = i == tid ? end_v : load_end(i);
-    bool direct = true;                               // all groups in one round
+    unsigned beyond = 0;
     if constexpr (TABLES) {
-        direct = prefix_all_fit(x.fits(rows));
+        beyond = prefix_beyond<KIND>(rows, x);
     } else {
         prefix_stage<KMAX ? KMAX : 8>(lds, q, rows, src, stride);
     }
@@ -189,7 +189,8 @@ __global__ __launch_bounds__(kPrefixThreads) void signals_kernel(
         s_at[l * q.groups + g] = at | done << 24;
     }
 
-    // 1 / n, lcm(1..32) / n, c / n and log(c / n): the last wavefront, which often has no pairs, while the others run theirs
+    // 1 / n, lcm(1..32) / n, c / n and log(c / n): the last wavefront, ahead of its pairs, if it has any, while the others begin theirs;
+    // where groups take turns, ahead of the first (within them it costs 30 registers, 127 instead of 96)
     auto small_tables = [&] {
         const int n = nt - 1 - tid;
         const double r = n ? 1.0 / (double)n : 0.0;
@@ -208,7 +209,7 @@ __global__ __launch_bounds__(kPrefixThreads) void signals_kernel(
     prefix_lane<KIND>(tid - gl * q.lanes, G, &pi, &pj);
 
     // groups s0 .. s0 + n - 1, `group_bytes` of tables each
-    auto evaluate = [&](int s0, int n, int group_bytes) __attribute__((always_inline)) {
+    auto evaluate = [&](int s0, int n, int group_bytes, int tid, bool with_tables) __attribute__((always_inline)) {
         const int r_lo = s0 * G, here = min(n * G, rows - r_lo);
         auto table = [&](int g) { return lds + q.body + (g - s0) * group_bytes; };
         // Half of the workgroup, a lane per member: the positions that are the first occurrence of their bigram
@@ -284,7 +285,7 @@ __global__ __launch_bounds__(kPrefixThreads) void signals_kernel(
             }
         }
         __syncthreads();
-        if (s0 == 0 && tid >= nt - 64) small_tables();
+        if (with_tables && tid >= nt - 64) small_tables();
 
         if (gl >= s0 && gl < min(s0 + n, n_here)) {
             constexpr int HALVES = KIND == PREFIX_ONE32 ? 1 : 2;
@@ -344,20 +345,21 @@ __global__ __launch_bounds__(kPrefixThreads) void signals_kernel(
         }
     };
     if constexpr (TABLES) {
-        if (direct) {
-            prefix_mark<KIND>(lds, q, rows, x);
+        if (beyond == 0) {
+            prefix_mark<KIND, true>(lds, q, rows, x, 0, q.groups, kPrefixSyms * q.row_bytes);
             __syncthreads();
-            evaluate(0, q.groups, kPrefixSyms * q.row_bytes);
+            evaluate(0, q.groups, kPrefixSyms * q.row_bytes, tid, true);
         } else {
-            for (int s0 = 0; s0 < n_here; s0 += q.hash_groups) {
-                __syncthreads();                      // nobody reads the tables of the round before
-                prefix_hash<KIND>(lds, q, rows, x, s0, q.hash_groups);
-                evaluate(s0, q.hash_groups, round_up(prefix_hash_rows(q), 16));
+            const PrefixTurns t = prefix_turns(q, n_here, beyond);
+            if (tid >= nt - 64) small_tables();
+            for (int s0 = 0; s0 < n_here; s0 += t.groups) {
+                prefix_turn<KIND>(lds, q, rows, x, s0, t);
+                evaluate(s0, t.groups, t.group_bytes, turn_tid(), false);
             }
         }
     } else {
         __syncthreads();
-        evaluate(0, q.groups, 0);
+        evaluate(0, q.groups, 0, tid, true);
     }
     __syncthreads();
 

@@ -30,8 +30,35 @@ def pytest_collection_modifyitems(config, items):
 
 
 PLAN_SOURCE = """
-#include "plan.h"
+#include "prefix_plan.h"
 extern "C" {
+// out: symbols compared in registers, kind or size, groups, threads, lanes, row_bytes, body, hash_groups, total, LDS of a workgroup
+static void layout(const sr::PrefixGeom &q, bool direct, int size, int lds, int *out) {
+    const int v[] = {direct, size, q.groups, q.threads, q.lanes, q.row_bytes, q.body, q.hash_groups, q.total, lds};
+    for (int i = 0; i < 10; ++i) out[i] = v[i];
+}
+int gate_layout(int n_groups, int G, int L, int *out) {
+    sr::GateLayout t;
+    if (!sr::gate_layout(n_groups, G, L, &t)) return 0;
+    layout(t.q, t.direct, t.size, t.lds, out);
+    return 1;
+}
+int signals_layout(int n_groups, int G, int L, int n_lens, int distinct, int *out) {
+    sr::SignalsLayout t;
+    if (!sr::signals_layout(n_groups, G, L, n_lens, distinct, &t)) return 0;
+    layout(t.q, t.direct, t.size, t.lds, out);
+    return 1;
+}
+// turns of a full workgroup of that layout (n_lens = 0: the gate's): hashed, groups of a turn, bytes of a group's tables
+void prefix_turns(int n_groups, int G, int L, int n_lens, unsigned most, int *out) {
+    sr::GateLayout g;
+    sr::SignalsLayout s;
+    if (n_lens) sr::signals_layout(n_groups, G, L, n_lens, n_lens, &s);
+    else sr::gate_layout(n_groups, G, L, &g);
+    const sr::PrefixGeom &q = n_lens ? s.q : g.q;
+    const sr::PrefixTurns t = sr::prefix_turns(q, q.groups, most);
+    out[0] = t.hashed; out[1] = t.groups; out[2] = t.group_bytes;
+}
 void shared_tiles(int n_sets, int per_set, int *set, int *part) {
     for (int wg = 0; wg < n_sets * per_set; ++wg) sr::shared_tiles_of(wg, n_sets, per_set, set + wg, part + wg);
 }

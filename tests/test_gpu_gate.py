@@ -160,3 +160,18 @@ def test_gate_tables(n_groups, G, lens, stride, beyond):
     s_ref, r_ref = oracle.gate_batch(acts, lens, 0.25)
     s_gpu, r_gpu = run_gpu(acts, lens, 0.25)
     assert np.array_equal(s_gpu, s_ref) and np.array_equal(r_gpu, r_ref)
+
+
+# alphabets: just beyond 64; an action modulus of 100; elements of a group; the first that does not fit a turn at its shape, and more
+@pytest.mark.parametrize("n_groups,G,lens,stride", [(9001, 8, [15, 10, 5], 15), (2049, 16, [16, 9], 30), (4099, 8, [32, 17], 32), (601, 11, [29], 29),
+                                                    (70000, 2, [24], 25), (5, 8, [12], 12), (1, 2, [18], 18)])
+@pytest.mark.parametrize("alphabet", [65, 100, 129, 257, 600, 5000])
+def test_gate_symbols_beyond_the_tables_of_64(n_groups, G, lens, stride, alphabet):
+    """Groups in turns, with as many table rows as the largest symbol asks for, and hashed where those would not fit."""
+    rng = np.random.default_rng(alphabet + G)
+    lead = rng.integers(0, alphabet, size=(n_groups, 1, stride))
+    acts = np.where(rng.random((n_groups, G, stride)) < 0.7, lead, rng.integers(0, alphabet, size=(n_groups, G, stride))).astype(np.int32)
+    acts[0, :, -1], acts[-1, 0, :] = alphabet - 1, alphabet - 1
+    s_ref, r_ref = oracle.gate_batch(acts, lens, 0.25)
+    s_gpu, r_gpu = run_gpu(acts, lens, 0.25)
+    assert np.array_equal(s_gpu, s_ref) and np.array_equal(r_gpu, r_ref)

@@ -149,3 +149,13 @@ def test_signals_tables(n_groups, G, lens, stride, beyond):
     lens = (lens + lens[:1])[:8]
     check(acts, lens, d_L=0.25, tau_H=0.5, obs=obs, end=end)
     check(acts, lens, d_L=0.25, tau_H=0.5)
+
+
+@pytest.mark.parametrize("n_groups,G,lens,stride", [(9001, 8, [15, 10, 5], 15), (2049, 16, [16, 9], 30), (4099, 8, [32, 17], 32), (601, 11, [29], 29),
+                                                    (3001, 16, [8, 1], 8), (5, 8, [12], 12), (1, 2, [18], 18)])
+@pytest.mark.parametrize("alphabet", [65, 100, 129, 257, 600, 5000])
+def test_signals_symbols_beyond_the_tables_of_64(n_groups, G, lens, stride, alphabet):
+    """Groups in turns, with as many table rows as the largest symbol asks for, and hashed where those would not fit."""
+    acts, obs, end = make(n_groups, G, stride, alphabet, seed=alphabet + G)
+    acts[0, :, -1], acts[-1, 0, :] = alphabet - 1, alphabet - 1
+    check(acts, lens, d_L=0.25, tau_H=0.5, obs=obs, end=end)

@@ -122,6 +122,33 @@ def test_no_attention_split_is_empty(plan):
             check(tokens, plan.private_splits(waves1, 64, tokens, 16))
 
 
+@pytest.mark.parametrize("n_lens", [0, 1, 3, 8])
+@pytest.mark.parametrize("G", range(2, 17))
+def test_symbols_below_the_elements_of_a_group_are_not_hashed(plan, n_lens, G):
+    """Gate (no n_lens) and signals: symbols below 64 or the number of a group's elements index the tables as they are, whatever the
+    shape; the groups of a turn lie within the workgroup's tables and their ids within 16 bits; turns of equal size."""
+    v, t = (ctypes.c_int * 10)(), (ctypes.c_int * 3)()
+    for n_groups in (1, 3, 300, 2000, 5000, 16384, 65536):
+        for K in range(max(1, n_lens), 33):
+            ok = plan.signals_layout(n_groups, G, K, n_lens, n_lens, v) if n_lens else plan.gate_layout(n_groups, G, K, v)
+            assert ok
+            direct, _, groups, _, _, row_bytes, body, hash_groups, total, _ = v
+            if direct:
+                continue
+            for most in {64, 99, 127, max(64, G * K) - 1, G * K, 255, 511, 1000, 4095, 4096, 2 ** 31, 2 ** 32 - 1}:
+                plan.prefix_turns(n_groups, G, K, n_lens, ctypes.c_uint(most), t)
+                hashed, per_turn, group_bytes = t
+                if most < max(64, G * K):
+                    assert not hashed, (n_groups, G, K, most)
+                if hashed:
+                    assert per_turn == hash_groups
+                else:
+                    assert group_bytes >= (most + 1) * row_bytes and group_bytes % 16 == 0 and most * row_bytes < 65536
+                    assert per_turn * group_bytes <= total - body
+                    turns = -(-groups // per_turn)
+                    assert per_turn == -(-groups // turns) and turns <= -(-groups // hash_groups)
+
+
 def test_quotients_of_small_numbers_are_correctly_rounded():
     """The signals kernel divides whole numbers below 64 by multiplying with the rounded reciprocal and correcting once with the
     remainder: the same double as the division, for every pair."""
