@@ -224,8 +224,10 @@ inline bool signals_layout(int n_groups, int G, int maxlen, int n_lens, int dist
         t->size = maxlen <= 16 ? PREFIX_TWO16 : (long long)n_groups * G * (G - 1) / 2 <= 256 * 512 ? PREFIX_ONE32 : PREFIX_TWO32;
         if (!prefix_geometry_tables(n_groups, G, maxlen, t->size, kSigLds - fixed, kSigHashLds - fixed, extra, &q)) return false;
     }
-    // a launch that does not fill the chip takes whole workgroups: four wavefronts share the phases of a group
-    if (ceil_div(n_groups, q.groups) <= 512 && q.groups <= 4) q.threads = kPrefixThreads;
+    // A launch that does not fill the chip takes whole workgroups: four wavefronts share the phases of a group.  By comparison up to
+    // four workgroups per compute unit, which are resident together (16 384 groups of 2 or 3, 5 steps: 9.4 and 10.0 -> 7.8 us, 2, 4 and 8
+    // steps: 13.5 and 12.6 -> 8.7 and 9.1; at 2048 workgroups no gain)
+    if (ceil_div(n_groups, q.groups) <= (t->direct ? 1024 : q.groups <= 4 ? 512 : 0)) q.threads = kPrefixThreads;
     // quotients take the place of symbols and tables: of every length at once up to kSigTerms bytes
     const SigLds sums = sig_lds(G, q.groups, n_lens);
     const int per_len = q.groups * sums.code_stride * 16, room = q.total > kSigTerms ? q.total : kSigTerms;

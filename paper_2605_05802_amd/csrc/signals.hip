@@ -164,6 +164,23 @@ __global__ __launch_bounds__(kPrefixThreads) void signals_kernel(
         s_out[w].lev_sum = 0;
     }
     if constexpr (TABLES) prefix_zero(lds, q.body, q.groups * kPrefixSyms * q.row_bytes, tid);
+    // 1 / n, lcm(1..32) / n, c / n and log(c / n), by the last wavefront.  With tables of symbols ahead of its pairs, while the others
+    // begin theirs, or ahead of the groups' first turn (within the turns: 127 registers instead of 96).  By comparison at once, where
+    // the pairs leave one or two wavefronts' work and the last one's chain would follow it (65 536 groups of 3, 20 steps: 31.7 -> 29.3 us).
+    auto small_tables = [&] {
+        const int n = nt - 1 - tid;
+        const double r = n ? 1.0 / (double)n : 0.0;
+        s_recip[n] = r;
+        if (n < 33) s_lcm[n] = rint((double)kLcm32 * r);     // exact: below 2^48, the product off by less than 1/16
+        if (n == 0) s_p[0] = s_log_p[0] = 0.0;
+        for (int e = n; e < G * (G + 1) / 2; e += 64) {       // n * (n - 1) / 2 + c
+            const int n = (int)((1.0f + __builtin_amdgcn_sqrtf(8.0f * (float)e + 1.0f)) * 0.5f + 0.0078125f), c = e - n * (n - 1) / 2 + 1;
+            const double share = (double)c / (double)n;
+            s_p[e + 1] = share;
+            s_log_p[e + 1] = log(share);
+        }
+    };
+    if (!TABLES && tid >= nt - 64) small_tables();
     for (int w = tid, u = 0; w < NL * rows; w += nt, ++u) {
         int l, r;
         obs_item(w, &l, &r);
@@ -189,21 +206,6 @@ __global__ __launch_bounds__(kPrefixThreads) void signals_kernel(
         s_at[l * q.groups + g] = at | done << 24;
     }
 
-    // 1 / n, lcm(1..32) / n, c / n and log(c / n): the last wavefront, ahead of its pairs, if it has any, while the others begin theirs;
-    // where groups take turns, ahead of the first (within them it costs 30 registers, 127 instead of 96)
-    auto small_tables = [&] {
-        const int n = nt - 1 - tid;
-        const double r = n ? 1.0 / (double)n : 0.0;
-        s_recip[n] = r;
-        if (n < 33) s_lcm[n] = rint((double)kLcm32 * r);     // exact: below 2^48, the product off by less than 1/16
-        if (n == 0) s_p[0] = s_log_p[0] = 0.0;
-        for (int e = n; e < G * (G + 1) / 2; e += 64) {       // n * (n - 1) / 2 + c
-            const int n = (int)((1.0f + __builtin_amdgcn_sqrtf(8.0f * (float)e + 1.0f)) * 0.5f + 0.0078125f), c = e - n * (n - 1) / 2 + 1;
-            const double share = (double)c / (double)n;
-            s_p[e + 1] = share;
-            s_log_p[e + 1] = log(share);
-        }
-    };
     const int gl = small_div(tid, 1.0f / (float)q.lanes);      // group within the block
     int pi, pj;
     prefix_lane<KIND>(tid - gl * q.lanes, G, &pi, &pj);
@@ -270,7 +272,9 @@ __global__ __launch_bounds__(kPrefixThreads) void signals_kernel(
             s_hold[l * n_rows + r] = (uint16_t)hold;
         };
         int half = nt >> 7 << 6;                                 // whole wavefronts
-        if (here > nt - half || half == 0) half = 0;             // more members than that: all lanes do both in turn
+        // all lanes do both in turn where there are more members than that, and beyond eight steps by comparison, where first_bigrams
+        // is as long as a pair and keeps the wavefronts busy that have pairs (65 536 groups of 2, 32 steps: 31.0 -> 28.2 us)
+        if (KMAX > 8 || here > nt - half || half == 0) half = 0;
         if (half == 0 || tid < half) {
             const float inv_here = 1.0f / (float)here;
             for (int w = tid; w < NL * here; w += half ? half : nt) {
@@ -285,7 +289,7 @@ __global__ __launch_bounds__(kPrefixThreads) void signals_kernel(
             }
         }
         __syncthreads();
-        if (with_tables && tid >= nt - 64) small_tables();
+        if (TABLES && with_tables && tid >= nt - 64) small_tables();
 
         if (gl >= s0 && gl < min(s0 + n, n_here)) {
             constexpr int HALVES = KIND == PREFIX_ONE32 ? 1 : 2;
@@ -329,8 +333,9 @@ __global__ __launch_bounds__(kPrefixThreads) void signals_kernel(
             } else {
                 int32_t b[KMAX ? KMAX : 8];
                 prefix_symbols<KMAX ? KMAX : 8>(lds, gl * G + pj, 0, b);
-#pragma unroll 1
-                for (int r0 = 0; r0 < L; r0 += 8) {
+#pragma unroll
+                for (int r0 = 0; r0 < KMAX; r0 += 8) {
+                    if (r0 >= L) break;               // uniform
                     unsigned eq[8];
                     int32_t a[8];
                     prefix_symbols<KMAX ? KMAX : 8>(lds, ri, r0, a);
