@@ -110,24 +110,29 @@ inline int pick_splits(int M, int N, int ks_total) {
 //     8192 rows 186 (6, three rounds), 202 (7, three), 207 (5, four) and 212 (8, three), O at 5120 rows 126 (5), 142 (6),
 //     155 (7) and 165 (8), two rounds each.  Every shape is looked at: what decides is how full the last round is.  The
 //     narrow ones (NT = 2, 3) give a few hundred rows a whole round where 128 x 128 tiles need two or more K splits (16 384
-//     columns at 296 rows: 45 us with {2, 5} and 55 with 128 x 128; QKV at 296 rows 19.4 and 22.0, at 512 rows 25.8 with {3, 4}
-//     and 31.1; O at 640 rows 23 and 30; 2304 columns, K = 512, 2048 rows 11.7 and 16.7).  Not beyond
-//     2048 rows, where every block of so few columns reads all of X again (512 columns at 3840 rows: K = 8192 45.3 us with {2, 4}
-//     and 38.8 with {4, 5}, K = 1792 22.6 and 18.1 with 128 x 128).  SwiGLU takes NT = 8 and 6, and
-//     {5, 4} from K = 3072 on (gate|up at 512 rows: 130 us, all rows in one workgroup 138; at K = 2048 they are even, at 1024 and
-//     below it is 2 to 8 % slower); {7, 4} is within 2 % either way of {8, 4} up to 3000 rows and 4 % slower at 4096, {5, 5} within
-//     3 % of {6, 5}.
-//   128 x 128 tiles, two to a CU: 39 k up to 256 of them and 60 k up to 512 (16 384 matrix rows at 512 rows: 24.1 us at K = 1024,
+//     columns at 296 rows: 45 us with {2, 5} and 55 with 128 x 128).  Every one of their many column blocks reads all of X again, so
+//     they count as 0.4 to 1 features more (`edge`).  With the 1.5 of the others they won where they lose (us with the kernel that reads the
+//     result; without edge -> now): QKV at 600 rows {2, 4} 47.3 -> {4, 5} in three splits 42.2, at 700 48.9 -> 46.0 (128 x 128), at 1000
+//     {3, 4} 55.2 -> {5, 4} in two 53.5; O at 800 rows {2, 4} 53.7 -> {4, 5} in three 47.6, at 1000 54.4 -> 50.9 (128 x 128), at 1600
+//     {3, 5} 76.4 -> {5, 5} in two 69.6.  They still win where they should: O at 600 rows {2, 5} in two 36.8 (128 x 128 in three 42.2),
+//     at 740 {3, 4} in two 39.3 (45.8), QKV at 1280 {3, 4} 58.4 ({6, 4} in two 60.8), at 1600 {3, 5} 71.0 (77.0); 512 columns,
+//     K = 8192 at 2560 rows {3, 4} in four 40.4 ({4, 5} in eight 42.0).  The model with hidden 512, where projections are short and a change of kernel
+//     costs about a us, takes them from 1281 rows on (whole prefill of 360 rows 208 -> 202 us).
+//     SwiGLU takes NT = 8 and 6, and {5, 4} from K = 3072 on, which counts as 0.65 more (gate|up at 450 rows: 124 us, all rows in one
+//     workgroup 138; at 900 rows 238, {6, 5} 225; at 1000 in a warm loop 268, {8, 4} 254; at K = 2048 they are even, at 1024 and below it
+//     is 2 to 8 % slower); {7, 4} is within 2 % either way of {8, 4} up to 3000 rows and 4 % slower at 4096, {5, 5} within 3 % of {6, 5}.
+//   128 x 128 tiles, two to a CU: 39 k up to 256 of them (36 k up to 512 rows: O at 450 rows in two splits 29.3 us with the norm behind it,
+//     {3, 4} in three 30.6) and 60 k up to 512 (16 384 matrix rows at 512 rows: 24.1 us at K = 1024,
 //     {6, 4} 27.1; 38.8 and 42.6 at 2048); then 0.166 k a tile up to 1024 rows, and above 0.095 k a tile and 15 k (W read
 //     through L2 by many row blocks), from 16 384 matrix rows on, which no L2 holds, 0.137 k (22 016 rows, K = 4096: 541 us
 //     at 2560 rows and 658 at 3072, where tiles of {6, 5} and {6, 4} take 349 and 458).
 //   All rows in one workgroup of 160 features, up to 512 rows: 108 k a round up to 384 rows, 139 k up to 512 (SwiGLU only: no
 //     fp32 matrix is cheapest there).  Only for matrices of 16 384 rows and more, where it makes a round of workgroups.
 //   S splits divide k, cost a fixed 6 and S times the output, written here and read by the next kernel, at 4.5 TB/s.
-struct TileShape { int nt, rt; };
-constexpr int kNarrowRows = 2048;
-constexpr TileShape kTileShapes[] = {{8, 4}, {7, 4}, {6, 4}, {5, 4}, {6, 5}, {5, 5}, {4, 5}, {4, 6},      // {5, 6} and up spill
-                                     {2, 4}, {3, 4}, {2, 5}, {3, 5}};
+struct TileShape { int nt, rt; double edge; };
+constexpr TileShape kTileShapes[] = {{8, 4, 1.5}, {7, 4, 1.5}, {6, 4, 1.5}, {5, 4, 1.5}, {6, 5, 1.5}, {5, 5, 1.5}, {4, 5, 1.5}, {4, 6, 1.5},
+                                     {2, 4, 2.5}, {3, 4, 1.9}, {2, 5, 1.9}, {3, 5, 2.0}};      // {5, 6} and up spill
+inline double edge(TileShape t, bool swiglu) { return swiglu && t.nt == 5 ? 2.15 : t.edge; }
 inline bool swiglu_shape(TileShape t, int ks_total) { return t.nt == 8 || t.nt == 6 || (t.nt == 5 && t.rt == 4 && ks_total >= 96); }
 enum { KERNEL_128 = -2, KERNEL_MID = -1 };             // otherwise an index into kTileShapes
 
@@ -142,10 +147,12 @@ inline GemmPlan plan_gemm(int M, int N, int ks_total, int mt_total, bool swiglu,
     // what does not depend on S: workgroups of a split, of each shape that may run
     constexpr int n_shapes = sizeof kTileShapes / sizeof kTileShapes[0];
     long long tiles[n_shapes];
+    double round[n_shapes];
     for (int i = 0; i < n_shapes; ++i) {
         const int nt = kTileShapes[i].nt, rt = kTileShapes[i].rt, mb = ceil_div(M, 64 * rt);
-        const bool may = (!swiglu || swiglu_shape(kTileShapes[i], ks_total)) && (nt > 3 || M <= kNarrowRows) && mb * 4 * rt <= mt_total;
+        const bool may = (!swiglu || swiglu_shape(kTileShapes[i], ks_total)) && mb * 4 * rt <= mt_total;
         tiles[i] = may ? (long long)mb * ceil_div(N, 32 * nt) : 0;
+        round[i] = rt * (nt + edge(kTileShapes[i], swiglu));
     }
     GemmPlan best{KERNEL_128, s_lo};
     double least = 0.0;
@@ -156,12 +163,12 @@ inline GemmPlan plan_gemm(int M, int N, int ks_total, int mt_total, bool swiglu,
             if (least == 0.0 || us + more < least) { least = us + more; best = GemmPlan{kernel, S}; }
         };
         const long long n128 = t128 * S;
-        const double t128_us = n128 <= 256 ? 39.0 : n128 <= (M > 1024 ? 473 : 512) ? 60.0 : M <= 1024 ? 0.166 * n128
+        const double t128_us = n128 <= 256 ? (M <= 512 ? 36.0 : 39.0) : n128 <= (M > 1024 ? 473 : 512) ? 60.0 : M <= 1024 ? 0.166 * n128
                                : (N < 16384 ? 0.095 : 0.137) * n128 + 15.0;
         offer(KERNEL_128, k / S * t128_us);
         if (S <= ks_total / kPfBufs)
             for (int i = 0; i < n_shapes; ++i)
-                if (tiles[i]) offer(i, ((tiles[i] * S + 255) >> 8) * 2.33 * kTileShapes[i].rt * (kTileShapes[i].nt + 1.5) * k / S);
+                if (tiles[i]) offer(i, ((tiles[i] * S + 255) >> 8) * round[i] * 2.33 * k / S);      // equal shapes stay equal
         if (S == 1 && M <= (swiglu ? 512 : 384) && N >= 16384)
             offer(KERNEL_MID, k * ceil_div(ceil_div(N, 160), 256) * (M <= 384 ? 108.0 : 139.0));
     }

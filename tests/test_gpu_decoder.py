@@ -976,7 +976,7 @@ def test_tiled_kernels_by_name(plan, n_groups, ffn, vocab, gate_up, lm_head):
 
 
 @pytest.mark.parametrize("n_groups,vocab,lm_head", [
-    (33, 528, "tiles 2x4"), (55, 6160, "tiles 2x4"),      # 264 rows: a last block of 8; 440 rows
+    (81, 5392, "tiles 2x4"), (95, 5424, "tiles 2x4"),     # 648 and 760 rows: three blocks
     (37, 14352, "tiles 2x5"), (97, 4624, "tiles 2x5"),    # 296 rows: one block; 776 rows: three
     (55, 10256, "tiles 3x4"), (125, 4112, "tiles 3x4"),   # 440 and 1000 rows
     (33, 20496, "tiles 3x5"), (71, 8208, "tiles 3x5"),    # 264 and 568 rows

@@ -86,6 +86,24 @@ def test_small_lm_heads_are_scored_through_stored_logits(plan):
             assert rows == 256 or rows * vocab <= 16 * 65536
 
 
+@pytest.mark.parametrize("M,N,K,kernel,splits", [
+    (600, 4608, 3584, "tiles 4x5", 3), (700, 4608, 3584, "128", 1), (900, 4608, 3584, "tiles 5x4", 2), (1000, 4608, 3584, "tiles 5x4", 2),
+    (800, 3584, 3584, "tiles 4x5", 3), (1000, 3584, 3584, "128", 1), (1280, 3584, 3584, "tiles 5x4", 2), (1600, 3584, 3584, "tiles 5x5", 2),
+    (450, 3584, 3584, "128", 2), (512, 3584, 3584, "128", 2), (360, 2304, 512, "128", 1), (600, 512, 1792, "128", 2),
+    # ... and where they do gain
+    (296, 4608, 3584, "tiles 2x5", 3), (450, 4608, 3584, "tiles 3x4", 2), (600, 3584, 3584, "tiles 2x5", 2), (740, 3584, 3584, "tiles 3x4", 2),
+    (1280, 4608, 3584, "tiles 3x4", 1), (1600, 4608, 3584, "tiles 3x5", 1), (2560, 512, 8192, "tiles 2x5", 4), (2560, 2304, 512, "tiles 3x4", 1)])
+def test_narrow_tiles_only_where_they_gain(plan, M, N, K, kernel, splits):
+    """Kernel and K splits that measured fastest, or within 2 % of it, among all shapes, the kernel that adds the splits included."""
+    ks = -(-(-(-K // 32)) // 16) * 16
+    assert plan.projection_splits(M, N, ks, 512) == splits and plan.kernel(M, N, K, splits=splits) == kernel
+
+
+@pytest.mark.parametrize("M,kernel", [(450, "tiles 5x4"), (512, "tiles 5x4"), (800, "tiles 6x5"), (960, "tiles 6x5"), (1000, "tiles 8x4")])
+def test_gate_up_tiles_of_160_only_up_to_512_rows(plan, M, kernel):
+    assert plan.kernel(M, 37888, 3584, swiglu=True) == kernel
+
+
 @pytest.mark.parametrize("waves1,shared,tokens,splits", [
     (256, 512, 500, 2), (640, 1280, 500, 1), (768, 1152, 300, 1), (512, 1024, 500, 2), (32, 64, 500, 4),
     (1184, 1184, 300, 2), (1184, 1184, 255, 1), (896, 1344, 300, 1), (2048, 2048, 300, 1), (1, 0, 100000, 16)])
