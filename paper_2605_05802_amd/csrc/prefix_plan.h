@@ -173,6 +173,7 @@ inline bool gate_layout(int n_groups, int G, int maxlen, GateLayout *t) {
 // ---------------------------------------------------------------------------------------------
 constexpr int kSigLds = 52 * 1024;                   // LDS of symbols, tables and sums: three workgroups per compute unit or more
 constexpr int kSigHashLds = 40 * 1024;               // ... where symbols are hashed: four
+constexpr int kSigThird = 53744;                      // a third of a compute unit's LDS, in its granules of 1280 bytes, less the kernels' own 16
 constexpr int kSigTerms = 24 * 1024;                 // LDS that the quotients may take: three K of sixteen groups of 8 at once
 
 // What the workgroup keeps behind symbols and tables: byte offsets, 8-byte arrays first.
@@ -228,9 +229,11 @@ inline bool signals_layout(int n_groups, int G, int maxlen, int n_lens, int dist
     // four workgroups per compute unit, which are resident together (16 384 groups of 2 or 3, 5 steps: 9.4 and 10.0 -> 7.8 us, 2, 4 and 8
     // steps: 13.5 and 12.6 -> 8.7 and 9.1; at 2048 workgroups no gain)
     if (ceil_div(n_groups, q.groups) <= (t->direct ? 1024 : q.groups <= 4 ? 512 : 0)) q.threads = kPrefixThreads;
-    // quotients take the place of symbols and tables: of every length at once up to kSigTerms bytes
+    // quotients take the place of symbols and tables: of every length at once up to kSigTerms bytes, while three workgroups fit
     const SigLds sums = sig_lds(G, q.groups, n_lens);
-    const int per_len = q.groups * sums.code_stride * 16, room = q.total > kSigTerms ? q.total : kSigTerms;
+    const int per_len = q.groups * sums.code_stride * 16, left = kSigThird - sums.total;
+    int room = left < kSigTerms ? left : kSigTerms;
+    if (room < q.total) room = q.total;
     t->terms_at_once = room / per_len < 1 ? 1 : room / per_len < distinct ? room / per_len : distinct;
     t->sums_at = round_up(q.total > t->terms_at_once * per_len ? q.total : t->terms_at_once * per_len, 16);
     t->lds = t->sums_at + sums.total;

@@ -159,3 +159,10 @@ def test_signals_symbols_beyond_the_tables_of_64(n_groups, G, lens, stride, alph
     acts, obs, end = make(n_groups, G, stride, alphabet, seed=alphabet + G)
     acts[0, :, -1], acts[-1, 0, :] = alphabet - 1, alphabet - 1
     check(acts, lens, d_L=0.25, tau_H=0.5, obs=obs, end=end)
+
+
+@pytest.mark.parametrize("n_groups,G,lens", [(65537, 3, [8, 7, 6, 5, 4, 3]), (40000, 2, [8, 7, 6, 5, 4, 3, 2, 1])])
+def test_signals_quotients_in_rounds_by_comparison(n_groups, G, lens):
+    """More prefix lengths than have their quotients in LDS at a time."""
+    acts, obs, end = make(n_groups, G, max(lens), 4, seed=n_groups)
+    check(acts, lens, d_L=0.25, tau_H=0.5, obs=obs, end=end)

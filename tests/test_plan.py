@@ -167,6 +167,23 @@ def test_symbols_below_the_elements_of_a_group_are_not_hashed(plan, n_lens, G):
                     assert per_turn == -(-groups // turns) and turns <= -(-groups // hash_groups)
 
 
+@pytest.mark.parametrize("G", range(2, 17))
+def test_gate_and_signals_fit_the_lds_that_their_occupancy_counts_on(plan, G):
+    """Nothing is refused, and a workgroup stays within 40 KiB (gate: four per compute unit) or a third of 160 KiB (signals) whatever the
+    number of groups, steps and prefix lengths; whole wavefronts, and lanes for every pair of the workgroup's groups."""
+    v = (ctypes.c_int * 10)()
+    for n_groups in (1, 2, 100, 511, 513, 1000, 2000, 5000, 8000, 16384, 30000, 65536, 200000):
+        for K in range(1, 33):
+            for n_lens in range(9):
+                for distinct in ({0} if n_lens == 0 else {1, (n_lens + 1) // 2, min(n_lens, K)}):
+                    ok = plan.signals_layout(n_groups, G, K, n_lens, distinct, v) if n_lens else plan.gate_layout(n_groups, G, K, v)
+                    assert ok
+                    direct, size, groups, threads, lanes, row_bytes, body, hash_groups, total, lds = v
+                    assert total <= lds and 3 * (-(-(lds + 16) // 1280)) * 1280 <= 160 * 1024, (n_groups, K, n_lens, distinct, lds)
+                    assert n_lens or lds <= 40 * 1024
+                    assert groups >= 1 and threads % 64 == 0 and groups * lanes <= threads <= 256
+
+
 def test_quotients_of_small_numbers_are_correctly_rounded():
     """The signals kernel divides whole numbers below 64 by multiplying with the rounded reciprocal and correcting once with the
     remainder: the same double as the division, for every pair."""
