@@ -27,8 +27,8 @@
 namespace sr {
 
 #ifdef __HIPCC__
-// x / d for 0 <= x < 2^14 and 1 <= d <= 64, inv = 1.0f / d: the distance of (x + 1/2) / d from an integer is at least 1/128,
-// far beyond the rounding of two 32-bit operations on values below 2^14
+// x / d for 0 <= x < 2^14 and d >= 1 (members, steps, the up to 120 lanes of a group), inv = 1.0f / d: (x + 1/2) / d is 1 / 2d or more
+// from an integer, and the roundings of inv and of the product move it by less than 2^-22 (x + 1) / d
 __device__ __forceinline__ int small_div(int x, float inv) { return (int)(((float)x + 0.5f) * inv); }
 
 // ---------------------------------------------------------------------------------------------

@@ -1,6 +1,7 @@
 """The rules that lay work out over the chip (csrc/plan.h), evaluated on the CPU."""
 import ctypes
 
+import numpy as np
 import pytest
 
 
@@ -196,3 +197,13 @@ def test_quotients_of_small_numbers_are_correctly_rounded():
             assert libm.fma(libm.fma(-q, float(b), float(a)), r, q) == a / b
         if b <= 32:                                   # lcm(1..32) / b from the same reciprocal
             assert round(144403552893600.0 * r) * b == 144403552893600
+
+
+def test_small_divisions_by_a_rounded_reciprocal():
+    """Indexes of lanes, members and steps: (x + 1/2) times the rounded 1 / d in single precision, cut off, is x / d for every x below 2^14 and
+    every d of the kernels (up to 16 members, 32 steps, 120 lanes, and beyond)."""
+    x = np.arange(1 << 14)
+    for d in range(1, 1025):
+        for inv in (np.float32(1) / np.float32(d), np.nextafter(np.float32(1) / np.float32(d), np.float32(0)), np.nextafter(np.float32(1) / np.float32(d), np.float32(2))):
+            q = ((x.astype(np.float32) + np.float32(0.5)) * np.float32(inv)).astype(np.int64)
+            assert np.array_equal(q, x // d), d
