@@ -171,9 +171,9 @@ __global__ __launch_bounds__(kPrefixThreads) void gate_direct_kernel(
 // length-k prefixes, appears on anti-diagonal 2k in lane k.  A segment never straddles a wavefront,
 // and a wavefront's LDS accesses complete in program order, so no workgroup barrier is needed
 // between anti-diagonals.  Half of a segment's lanes are idle in the triangular ramp-up and
-// ramp-down and every step is an LDS round trip, which is why the lane-per-pair kernel above is the
-// one the library uses; sr_gate_batch_antidiag exposes this one so that the two can be measured
-// side by side and checked against each other.
+// ramp-down and every step is an LDS round trip, which is why the library uses the kernels above;
+// sr_gate_batch_antidiag exposes this one so that the two can be measured side by side and checked
+// against each other.
 // ---------------------------------------------------------------------------------------------
 template <int SEG>
 __global__ __launch_bounds__(kPrefixThreads) void gate_antidiag_kernel(

@@ -211,7 +211,9 @@ inline TokenSplits token_splits(int tokens, int want) {
 // fullest compute unit, and 256 of them take the workgroups (four wavefronts) in rounds: fewer splits are taken where the
 // rounds they save outweigh the longer chain of 32-token blocks.  The three terms of the cost were fitted to attention and
 // merge at 28 query and 4 kv heads of 128, 1 to 200 groups of 2, 4, 8 and 16, private contexts of 150 to 1000 tokens (147 shapes,
-// each with up to eight splits): 2.4 % on average, nothing more than 3 % slower.  In us, before and after: 8 groups of 8 with 500
+// each with up to eight splits): 2.4 % on average, nothing more than 3 % slower; whole steps of two layers there and at 14 query and 2 kv
+// heads of 128 and 4 and 2 of 64 (150 of them, 2 to 100 groups, private contexts of 150 to 1000): 2 % on average, up to 10 % faster, and
+// 3 % slower at most (14 heads: 28 groups of 8 with 150 tokens, 32 of 16 with 1000).  In us, before and after: 8 groups of 8 with 500
 // tokens 27.8 with four splits (384 workgroups), 25.2 with two (256); 20 groups 55.0 with two (640), 47.4 with one (480);
 // 24 groups of 4 with 150 tokens 26.7 and 21.5.  A second split where one leaves the last of its rounds emptier by 8 %: 37
 // groups of 8, 300 tokens, 66.7 -> 62.8, 1000 tokens 153 -> 141; 28 groups, whose 784 workgroups begin a fourth

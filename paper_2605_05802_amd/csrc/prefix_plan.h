@@ -10,12 +10,12 @@ constexpr int kPrefixThreads = 256;     // most threads of a workgroup
 // row of the directly compared symbols: an odd multiple of 16 bytes, the rows of sixteen consecutive members in different banks
 SR_HD constexpr int prefix_act_stride(int kmax) { return kmax % 8 == 4 ? kmax : kmax + 4; }
 
-// Compare, or build tables?  The symbols are not known here, so both kinds count.  Up to eight steps comparing costs little more
-// than tables of symbols in their range and much less than hashing (65 536 groups of 8, 5 steps: gate 20.5 us; with tables 17.8
-// and 31; 3 members: 6.3, 7.9 and 13).  Longer prefixes share a table among G - 1 pairs: up to `few` members comparing is
-// still the better of the two where the groups fill the chip (65 536 groups of 5, 12 steps: gate 17.5 us, tables 15.3 and 32;
-// groups of 3: signals 30, tables 32 and 49), but not in too few wavefronts (64 groups of 3, 32 steps: gate 10.0 us by
-// comparison, 7.7 with tables).
+// Compare, or build tables?  The symbols are not known here, and comparing takes the same time whatever they are, where tables win with
+// symbols below 64, are about even below 100 and lose up to three times with all different ones: comparing is taken where the most that it
+// can lose is less than the most that tables can.  Up to eight steps (65 536 groups of 8, 5 steps: gate 17.0 us; with tables 13.2, 24.8 and
+// 31.4; 8 steps 17.8, and 12.8, 19.0 and 49.0; 3 members, 5 steps 8.7, and 9.1, 11.2 and 13.9).  Longer prefixes share a table among
+// G - 1 pairs: up to `few` members where the groups fill the chip (65 536 groups of 5, 12 steps: gate 14.0 us, and 11.0, 16.2 and 42.8; groups
+// of 3: signals 17.8, and 18.0, 24.7 and 41.8), but not in too few wavefronts (64 groups of 3, 32 steps: gate 9.7 us, with tables 7.9).
 inline bool prefix_direct(int n_groups, int G, int L, int few) {
     return L <= 8 || (G <= few && (long long)n_groups * G >= 1500LL * L);
 }
@@ -213,8 +213,9 @@ inline bool signals_layout(int n_groups, int G, int maxlen, int n_lens, int dist
     // LDS behind symbols and tables: at most `extra` for every group, and `fixed`
     const int extra = sig_lds(G, 2, n_lens).total - sig_lds(G, 1, n_lens).total + 16, fixed = sig_lds(G, 1, n_lens).total - extra + 16;
     PrefixGeom &q = t->q;
-    // Up to eight steps the tables are nevertheless cheaper for large groups that fill the chip (65 536 groups of 8, 5 steps: 60 us,
-    // 70 with arbitrary symbols, 70 by comparison; 8 steps: 60, 87 and 70; groups of 16: 230, 254 and 343)
+    // Up to eight steps the tables are nevertheless cheaper for large groups that fill the chip (65 536 groups of 8, 5 steps: 47.4 us by
+    // comparison, 34.8 with tables of symbols below 64, 42.5 below 100, 49.2 all different; 8 steps: 48.1, and 39.1, 42.8 and 78.6; groups
+    // of 16, 8 steps: 232, and 142, 147 and 217)
     const bool many = (long long)n_groups * G >= 32000 && (G >= 12 || (G >= 8 && maxlen <= 6));
     t->direct = prefix_direct(n_groups, G, maxlen, 3) && !many;
     if (t->direct) {

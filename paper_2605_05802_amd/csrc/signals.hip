@@ -22,9 +22,9 @@
 // member order, so that the floating-point results do not depend on scheduling.
 // Bound: vector ALU (70 % busy, 1570 instructions per wavefront: 300 of them the recurrence, 160 the evaluation at the three K, 150
 // the quotients, 200 the sums), with four workgroups per compute unit by LDS.  65 536 groups of 8 with early finishers, K = 5,
-// 10, 15: 64 us; 126 with a lane per pair, masks of one member per LDS read, bigrams compared position by position for
-// every K, a division per pair and K and a logarithm per member and K.  32 steps 122 against 417 us, 16 384 groups of 16 with
-// 16 steps 70 against 153, one group of 8 with 15 steps 9.8 against 12.5.
+// 10, 15: 61.4 us; 120 with a lane per pair, masks of one member per LDS read, bigrams compared position by position for
+// every K, a division per pair and K and a logarithm per member and K.  32 steps 80 against 283 us, 16 384 groups of 16 with
+// 16 steps 43 against 114, 16 groups of 8 with K = 5, 10, 15 8.3 against 12.7.  Symbols of 64 and more: see prefix_turns.
 #include <stddef.h>
 
 #include "prefix_match.h"
