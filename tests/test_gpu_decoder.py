@@ -1006,6 +1006,17 @@ def test_gate_up_on_tiles_with_an_odd_number_of_feature_tiles(plan):
     assert worst <= tol and all(g < gap_rule(tol) for g in info["mismatch_gaps"])
 
 
+@pytest.mark.parametrize("prompt,kernel", [(491, "tiles 3x4"), (599, "tiles 3x5")])
+def test_narrow_tiles_of_thousands_of_rows(plan, prompt, kernel):
+    """2455 and 2995 prompt rows: the QKV projection of 2304 rows on tiles of 96 features, a ragged last row block."""
+    assert plan.kernel(5 * prompt, 2304, 512) == kernel and plan.projection_splits(5 * prompt, 2304, 16, 512) == 1
+    shape = synth.ModelShape(1, 512, 14, 2, 128, 688, 512)
+    cfg = synth.EpisodeConfig("narrow-qkv", 5, 2, prompt, 1, 3, 1, 16, (), 0.3, 0.0)
+    rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=31, page_tokens=32, kv_pool_bytes=1 << 28)
+    print(f"narrow QKV tiles: worst |dlogit| = {worst:.3e}, mismatches = {mism}, near ties = {near}")
+    assert worst <= LOGIT_TOL and mism == 0
+
+
 def test_fp32_tiles_of_320_rows_by_192_features(plan):
     """5935 prompt rows: the QKV projection of 2304 rows runs on tiles of 320 rows x 192 features, a ragged last row block."""
     assert plan.kernel(5935, 2304, 512) == "tiles 6x5" and plan.projection_splits(5935, 2304, 16, 512) == 1
