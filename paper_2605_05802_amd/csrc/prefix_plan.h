@@ -101,7 +101,12 @@ inline bool prefix_geometry_direct(int n_groups, int G, int L, int kmax, int lds
 }
 
 constexpr int kPrefixVecs = 4;          // 16-byte pieces of the members' rows that a lane loads at most
-inline bool prefix_geometry_tables(int n_groups, int G, int L, int kind, int lds_limit, int hash_lds, int extra, PrefixGeom *q) {
+// Of the counts that fill the wavefronts equally well the largest within `lds_limit` bytes is taken; with two pairs in a register, and more
+// workgroups than two per compute unit, the largest within `four` bytes, of which four workgroups fit: groups of four had taken 51 KB
+// (65 536 groups of 4, 16 steps, signals: 88.6 -> 76.3 us with all different symbols, 76.1 before the tables held pairs; 21.9 -> 21.1 with
+// symbols below 64; with three prefix lengths 92.9 -> 73.6 and 33.3 -> 29.5; groups of 6 139 -> 114 and 52.9 -> 45.8).  With two registers
+// groups of 5 lose what they gain (20 steps: 143 -> 112, and 46.3 -> 50.0).
+inline bool prefix_geometry_tables(int n_groups, int G, int L, int kind, int lds_limit, int four, int hash_lds, int extra, PrefixGeom *q) {
     *q = PrefixGeom{};
     q->G = G;
     q->L = L;
@@ -114,9 +119,11 @@ inline bool prefix_geometry_tables(int n_groups, int G, int L, int kind, int lds
     auto body = [&](int n) { const int b = n * kPrefixSyms * q->row_bytes; return round_up(b > hash ? b : hash, 16); };
     double best = 0.0;
     for (int n = 1; n * q->lanes <= 256 && n * G * (steps / 4) <= 256 * kPrefixVecs && n <= ceil_div(n_groups, 512); ++n) {
-        if (n * (G * steps * 2 + extra) + body(n) > lds_limit) break;
+        const int bytes = n * (G * steps * 2 + extra) + body(n);
+        if (bytes > lds_limit) break;
         const double use = (double)(n * q->lanes) / round_up(n * q->lanes, 64);
-        if (use >= best) {
+        const bool roomy = kind != PREFIX_TWO16 || bytes <= four || ceil_div(n_groups, n) <= 512;
+        if (use > best || (use == best && roomy)) {
             best = use;
             q->groups = n;
         }
@@ -162,7 +169,7 @@ inline bool gate_layout(int n_groups, int G, int maxlen, GateLayout *t) {
         // Beyond 16 steps a lane with two pairs has twice the instructions: one pair where that still leaves no more than eight
         // wavefronts per compute unit (300 groups of 8, 32 steps: 6.6 us, 7.6 with two; 2000 groups 6.2)
         t->size = maxlen <= 16 ? PREFIX_TWO16 : (long long)n_groups * G * (G - 1) / 2 <= 256 * 512 ? PREFIX_ONE32 : PREFIX_TWO32;
-        if (!prefix_geometry_tables(n_groups, G, maxlen, t->size, kGateLds, kGateHashLds, 16, &t->q)) return false;
+        if (!prefix_geometry_tables(n_groups, G, maxlen, t->size, kGateLds, kGateLds, kGateHashLds, 16, &t->q)) return false;
     }
     t->lds = t->q.total + 16 * t->q.groups;           // and the sums
     return true;
@@ -224,7 +231,7 @@ inline bool signals_layout(int n_groups, int G, int maxlen, int n_lens, int dist
     } else {
         // beyond 16 steps a pair a lane where the pairs leave eight wavefronts per compute unit or fewer, as in the gate
         t->size = maxlen <= 16 ? PREFIX_TWO16 : (long long)n_groups * G * (G - 1) / 2 <= 256 * 512 ? PREFIX_ONE32 : PREFIX_TWO32;
-        if (!prefix_geometry_tables(n_groups, G, maxlen, t->size, kSigLds - fixed, kSigHashLds - fixed, extra, &q)) return false;
+        if (!prefix_geometry_tables(n_groups, G, maxlen, t->size, kSigLds - fixed, kSigHashLds - fixed, kSigHashLds - fixed, extra, &q)) return false;
     }
     // A launch that does not fill the chip takes whole workgroups: four wavefronts share the phases of a group.  By comparison up to
     // four workgroups per compute unit, which are resident together (16 384 groups of 2 or 3, 5 steps: 9.4 and 10.0 -> 7.8 us, 2, 4 and 8

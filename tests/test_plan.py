@@ -185,6 +185,17 @@ def test_gate_and_signals_fit_the_lds_that_their_occupancy_counts_on(plan, G):
                     assert groups >= 1 and threads % 64 == 0 and groups * lanes <= threads <= 256
 
 
+@pytest.mark.parametrize("G", [4, 5, 6, 8, 12, 16])
+def test_signals_of_up_to_16_steps_fit_four_workgroups_per_compute_unit(plan, G):
+    """... where there are more than 1024 of them: groups of four had taken 51 KB of LDS, and with all different symbols a sixth more time than
+    a lane per pair."""
+    v = (ctypes.c_int * 10)()
+    for K in range(9, 17):
+        for n_lens in (1, 2, 3):
+            assert plan.signals_layout(65536, G, K, n_lens, n_lens, v) and not v[0]
+            assert 65536 / v[2] > 1024 and 4 * (-(-(v[9] + 16) // 1280)) * 1280 <= 160 * 1024, (K, n_lens, v[9])
+
+
 def test_quotients_of_small_numbers_are_correctly_rounded():
     """The signals kernel divides whole numbers below 64 by multiplying with the rounded reciprocal and correcting once with the
     remainder: the same double as the division, for every pair."""
