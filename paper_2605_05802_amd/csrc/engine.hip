@@ -228,7 +228,7 @@ int timed(sr_ctx *c, int kc, hipStream_t st, F &&launch) {
 
 void plan_packed(AllocPlan &plan, PackedMat *m, int n_rows, int K) {
     m->N = n_rows;
-    m->ks = round_up(ceil_div(K, 32), 16);       // the GEMMs consume k-steps in groups of 16
+    m->ks = padded_k_steps(K);
     // row padding covers every workgroup width of the projection kernels
     int rows = 0;
     for (int w : {160, 192, 224, 256, 320})
@@ -807,9 +807,9 @@ static int init_impl(sr_ctx *c) {
     const int d = s.head_dim;
     c->n_seq0 = c->n_groups0 * c->G;
     c->qkv_cols = (s.n_q_heads + 2 * s.n_kv_heads) * d;
-    c->ks_h = round_up(s.hidden / 32, 16);       // k extents padded to groups of 16 k-steps (zeros)
-    c->ks_q = round_up(s.n_q_heads * d / 32, 16);
-    c->ks_f = round_up(ceil_div(s.ffn, 32), 16);
+    c->ks_h = padded_k_steps(s.hidden);
+    c->ks_q = padded_k_steps(s.n_q_heads * d);
+    c->ks_f = padded_k_steps(s.ffn);
     const int max_rows = o.max_prefill_rows > 0 ? o.max_prefill_rows : 8192;
     c->R = round_up(max_rows > c->n_seq0 ? max_rows : c->n_seq0, 256);
     c->mt_total = c->R / 16;

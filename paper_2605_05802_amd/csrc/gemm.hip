@@ -755,7 +755,7 @@ int launch_mid(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream) {
 int launch_gemm(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream) {
     if (a.M <= 0) return SR_OK;
     const int m_blocks = ceil_div(a.M, 128);
-    if (m_blocks * 8 > a.mt_total || a.splits < 1 || m_blocks > 65535 || a.splits > 65535 || a.ks_total % 16)
+    if (m_blocks * 8 > a.mt_total || a.splits < 1 || m_blocks > 65535 || a.splits > 65535 || a.ks_total % kPF)
         return SR_E_ARG;
     if (a.wide) return launch_gemm_stream(a, epi, stream);
     if (epi == EPI_LSE) return launch_tiles<EPI_LSE, 8, 4>(a, stream);

@@ -53,6 +53,9 @@ constexpr int kMaxSplitK = 16;
 // k-steps that a kernel's splits cover a multiple of: kPfBufs (its LDS buffers) where tiles of kTileShapes run, kPF (the
 // k-steps of W it holds in registers) in the other kernels
 constexpr int kPfBufs = 4, kPF = 8;
+// k-steps of 32 that hold K, the projections' inner dimension, padded with zeros to whole groups of kPF, which is what every kernel
+// consumes at a time.  (Padded to twice that, the model with hidden size 256 multiplied as many zeros as weights.)
+inline int padded_k_steps(int K) { return round_up(ceil_div(K, 32), kPF); }
 
 // Projections of up to kStreamRows rows go to the weight-streaming kernel, except that above kStreamThinRows rows small
 // matrices (up to 8192 rows and 16 MB) stay on the tiled kernels: with seven or eight row tiles a k-step of the streaming
@@ -100,7 +103,7 @@ inline int pick_splits(int M, int N, int ks_total) {
     // rows: O at K = 1024 12.2 -> 8.2 us, at 2048 12.9 -> 10.0, at 3584 16.0 -> 15.1; from 4096 on nothing changes; a whole
     // step at hidden 1024 166 -> 148).  But a scoring pass split into several agrees with one pass to 1e-3 only while
     // batches on both sides of 128 rows group the sums of a short inner dimension alike; split further it was 1.4e-3.
-    if (M > 128 && s > units / 4) s = units / 4;
+    if (M > 128 && s > (units + 1) / 4) s = (units + 1) / 4;     // seven groups (K = 1792) as eight
     return s < 1 ? 1 : s;
 }
 
@@ -143,7 +146,7 @@ inline GemmPlan plan_gemm(int M, int N, int ks_total, int mt_total, bool swiglu,
     const long long t128 = (long long)ceil_div(M, 128) * ceil_div(N, 128);
     const int s_lo = splits ? splits : 1;
     int s_hi = splits ? splits : max_splits;
-    if (!splits && s_hi > ks_total / 32) s_hi = ks_total / 32;         // at least 32 k-steps each: filling the pipeline is not free
+    if (!splits && s_hi > (ks_total + 8) / 32) s_hi = (ks_total + 8) / 32;     // at least 32 k-steps each (28 of 56): filling the pipeline is not free
     // what does not depend on S: workgroups of a split, of each shape that may run
     constexpr int n_shapes = sizeof kTileShapes / sizeof kTileShapes[0];
     long long tiles[n_shapes];

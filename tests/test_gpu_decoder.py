@@ -1047,3 +1047,15 @@ def test_weight_streaming_widths_by_name(plan, n_groups, G, ffn, vocab, gate_up,
     rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=79, page_tokens=32, kv_pool_bytes=1 << 28)
     print(f"stream {rows} rows, {gate_up} / {lm_head}: worst |dlogit| = {worst:.3e}, mismatches = {mism}, near ties = {near}")
     assert worst <= LOGIT_TOL and mism == 0
+
+
+@pytest.mark.parametrize("n_groups", [5, 25, 41])
+@pytest.mark.parametrize("hidden,q_heads,ffn", [(256, 12, 1296), (768, 28, 272)])
+def test_inner_dimensions_of_an_odd_number_of_groups(n_groups, hidden, q_heads, ffn):
+    """K of 1, 3, 5 (41 k-steps), 7 and 2 (9 k-steps) groups of eight k-steps at 40, 200 and 328 rows: streaming and tiled kernels,
+    the last group partly padding."""
+    shape = synth.ModelShape(1, hidden, q_heads, 2, 64, ffn, 512)
+    cfg = synth.EpisodeConfig("odd-k", n_groups, 8, 8, 1, 2, 2, 64, (), 0.3, 0.0)
+    rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=81, page_tokens=32, kv_pool_bytes=1 << 28)
+    print(f"odd K {hidden}/{ffn} {n_groups * 8}: worst |dlogit| = {worst:.3e}, mismatches = {mism}, near ties = {near}")
+    assert worst <= LOGIT_TOL and mism == 0

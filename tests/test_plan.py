@@ -218,3 +218,17 @@ def test_small_divisions_by_a_rounded_reciprocal():
         for inv in (np.float32(1) / np.float32(d), np.nextafter(np.float32(1) / np.float32(d), np.float32(0)), np.nextafter(np.float32(1) / np.float32(d), np.float32(2))):
             q = ((x.astype(np.float32) + np.float32(0.5)) * np.float32(inv)).astype(np.int64)
             assert np.array_equal(q, x // d), d
+
+
+@pytest.mark.parametrize("K", [32, 256, 257, 272, 512, 688, 1792, 3584, 18944])
+@pytest.mark.parametrize("M", [8, 128, 129, 200, 256, 257, 512, 3000])
+def test_inner_dimensions_of_an_odd_number_of_groups(plan, K, M):
+    """K is padded to whole groups of eight k-steps and no further, and no projection has more K splits than groups of what its
+    kernel deals out; seven groups (1792) are split above 128 rows as eight are."""
+    ks = plan.padded_k_steps(K)
+    assert ks % 8 == 0 and 0 <= ks * 32 - K < 256
+    for N in (256, 512, 2304, 4608, 16384):
+        splits = plan.projection_splits(M, N, ks, 512)
+        assert 1 <= splits <= max(1, ks // plan.split_steps(M, N, ks, 512, splits))
+    if K == 1792 and 128 < M <= 256:
+        assert plan.projection_splits(M, 512, ks, 512) == plan.projection_splits(M, 512, 64, 512) == 2
