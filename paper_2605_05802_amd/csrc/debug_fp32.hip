@@ -5,7 +5,7 @@
 // cores.  What is NOT different is everything that could hide an indexing mistake behind rounding noise:
 // the page tables and copy-on-write, the (unit, kv head, split, query tile) decomposition of attention and
 // its partial-result format and merge, the k-step ranges of the projections' K splits and the order in
-// which the consumers add the partial sums, the packed weight layout (read here element by element),
+// which the consumers add the partial sums (where projections leave any: not in gemm_thin.hip), the packed weight layout (read here element by element),
 // token selection, gate and compaction.  Against an exact evaluation this path differs by single-precision
 // rounding only.  Speed is not a goal: tiles are small and go through LDS once.
 #include "sr_internal.h"
@@ -117,10 +117,10 @@ __global__ __launch_bounds__(64) void dbg_qkv_post_kernel(DbgQkvPostArgs x) {
     else { kind = 2; h = head - a.n_q - a.n_kv; col0 = q_cols + kv_cols + h * a.d; bias = a.bv ? a.bv + h * a.d : nullptr; }
 
     float lo = 0.f, hi = 0.f;
-    const float *p0 = a.partials + (size_t)m * a.ld + col0 + i;
+    const float *p0 = a.partials + (size_t)m * a.ld + col0 + qkv_column(i);
     for (int s = 0; s < a.n_partials; ++s) {              // split order, as the normal path
         lo += p0[(size_t)s * a.partial_stride];
-        hi += p0[(size_t)s * a.partial_stride + half];
+        hi += p0[(size_t)s * a.partial_stride + 16];
     }
     if (bias) { lo += bf16_to_f32(bias[i]); hi += bf16_to_f32(bias[i + half]); }
     if (kind != 2) {

@@ -2,7 +2,7 @@
 // KV page write), greedy argmax, and small utilities.  All reductions run in a fixed order
 // that does not depend on the row index or on the batch size, so a sequence's numbers do not
 // change when other rows enter or leave the batch.
-#include "sr_internal.h"
+#include "epilogue.h"
 
 namespace sr {
 namespace {
@@ -156,68 +156,17 @@ __global__ __launch_bounds__(640) void qkv_post_kernel(QkvPostArgs a) {
     const int at = (int)(((float)threadIdx.x + 0.5f) * __builtin_amdgcn_rcpf((float)tph));       // 640 at most: far from an integer
     const int m = blockIdx.x, head = blockIdx.y * a.heads_per_block + at, i = ((int)threadIdx.x - at * tph) * 4;
     if (head >= a.n_q + 2 * a.n_kv) return;
-    const int unit = quotient(m, a.by_chunk), ci = m - unit * a.chunk;
-    const int pos = a.pos0 + ci;
-    const int kind = head < a.n_q ? 0 : head < a.n_q + a.n_kv ? 1 : 2;       // 0 q, 1 k, 2 v
-    const int h = kind == 0 ? head : kind == 1 ? head - a.n_q : head - a.n_q - a.n_kv;
-    const uint16_t *bias = kind == 0 ? a.bq : kind == 1 ? a.bk : a.bv;
+    const int unit = quotient(m, a.by_chunk);
+    QkvExtras x;
+    x.pos = a.pos0 + m - unit * a.chunk;
     // the page table does not change while the kernel runs: a uniform entry comes through a scalar load
-    const int page = ((const __attribute__((address_space(4))) int32_t *)(uintptr_t)a.page_table)[(size_t)unit * a.pt_row_stride *
-                                                                                           a.pt_stride + (pos >> a.page_shift)];
-    uint2 blo = make_uint2(0, 0), bhi = make_uint2(0, 0);
-    f32x4 c = {1.f, 1.f, 1.f, 1.f}, sn = {0.f, 0.f, 0.f, 0.f};
-    auto fetch = [&] {
-        if (bias) {
-            blo = *(const uint2 *)(bias + h * a.d + i);
-            bhi = *(const uint2 *)(bias + h * a.d + i + half);
-        }
-        if (kind != 2) {
-            c = *(const f32x4 *)(a.rope_cos + (size_t)pos * half + i);
-            sn = *(const f32x4 *)(a.rope_sin + (size_t)pos * half + i);
-        }
-    };
-    if (EARLY) fetch();
+    x.page = ((const __attribute__((address_space(4))) int32_t *)(uintptr_t)a.page_table)[(size_t)unit * a.pt_row_stride *
+                                                                                         a.pt_stride + (x.pos >> a.page_shift)];
+    if (EARLY) fetch_bias_and_rotation(a, head, i, x);
     f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = {0.f, 0.f, 0.f, 0.f};
-    add_partials(a.partials + (size_t)m * a.ld + head * a.d + i, a.partial_stride, a.n_partials, half, lo, hi);
-    if (!EARLY) fetch();
-    if (bias) {
-        lo += f32x4{__uint_as_float(blo.x << 16), __uint_as_float(blo.x & 0xFFFF0000u), __uint_as_float(blo.y << 16),
-                    __uint_as_float(blo.y & 0xFFFF0000u)};
-        hi += f32x4{__uint_as_float(bhi.x << 16), __uint_as_float(bhi.x & 0xFFFF0000u), __uint_as_float(bhi.y << 16),
-                    __uint_as_float(bhi.y & 0xFFFF0000u)};
-    }
-    if (kind != 2) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float rlo = lo[e] * c[e] - hi[e] * sn[e], rhi = hi[e] * c[e] + lo[e] * sn[e];
-            lo[e] = rlo; hi[e] = rhi;
-        }
-    }
-    const uint2 plo = make_uint2(pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]));
-    const uint2 phi = make_uint2(pack_bf16x2(hi[0], hi[1]), pack_bf16x2(hi[2], hi[3]));
-    if (kind == 0) {
-        uint16_t *q = a.q_out + ((size_t)m * a.n_q + h) * a.d;
-        *(uint2 *)(q + i) = plo;
-        *(uint2 *)(q + i + half) = phi;
-        return;
-    }
-    const int tok = pos & (a.page_tokens - 1), blk = tok >> 5, t = tok & 31;
-    const size_t base = ((((size_t)page * a.n_kv + h) << (a.page_shift - 5)) + blk) * (size_t)(32 * a.d);
-    if (kind == 1) {
-        // K block [d/32][32 tok][32]: four consecutive dims stay inside one 32-dim group
-        uint16_t *k = a.kpool + base;
-        *(uint2 *)(k + (((i >> 5) * 32 + t) << 5) + (i & 31)) = plo;
-        const int i2 = i + half;
-        *(uint2 *)(k + (((i2 >> 5) * 32 + t) << 5) + (i2 & 31)) = phi;
-    } else {
-        uint16_t *v = a.vpool + base;
-        const int slot = 8 * ((t & 15) >> 2) + 4 * (t >> 4) + (t & 3);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            v[(i + e) * 32 + slot] = f32_to_bf16(lo[e]);
-            v[(i + half + e) * 32 + slot] = f32_to_bf16(hi[e]);
-        }
-    }
+    add_partials(a.partials + (size_t)m * a.ld + head * a.d + qkv_column(i), a.partial_stride, a.n_partials, 16, lo, hi);
+    if (!EARLY) fetch_bias_and_rotation(a, head, i, x);
+    finish_qkv(a, m, head, i, lo, hi, x);
 }
 
 struct MaxIdx {
@@ -331,8 +280,7 @@ int launch_qkv_post(const QkvPostArgs &args, hipStream_t stream) {
     QkvPostArgs a = args;
     if (a.rows <= 0) return SR_OK;
     if (a.d > 128 || a.d % 32 || a.rows > 0x7FFFFFF || a.chunk < 1) return SR_E_ARG;
-    a.by_chunk = fast_div(a.chunk);
-    a.page_shift = 31 - __builtin_clz(a.page_tokens);
+    set_divisions(&a);
     const int heads_per_wave = 64 / (a.d / 8);                 // d/8 threads per head
     const int heads = a.n_q + 2 * a.n_kv;
     int waves = 1;                                             // wavefronts per block

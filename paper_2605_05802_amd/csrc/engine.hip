@@ -152,6 +152,8 @@ struct sr_ctx {
     size_t partial_elems = 0, part_rows_cap = 0;
     uint4 *xn = nullptr, *attn_out = nullptr, *act = nullptr;
     uint16_t *q = nullptr;
+    float *squares = nullptr;                   // [kThinRows][squares_ld]: see RowScale
+    int squares_ld = 0;
 
     // single-precision debugging path (o.fp32_debug): fp32 twins of the activation buffers and of the KV pool
     bool dbg = false;
@@ -409,8 +411,9 @@ int choose_splits(sr_ctx *c, int M, const PackedMat &W, int ld_out, int *splits,
 }
 
 int gemm(sr_ctx *c, const uint4 *X, const PackedMat &W, int M, GemmEpilogue epi, void *out, int ld_out,
-         int *splits_out, hipStream_t st) {
+         int *splits_out, hipStream_t st, const RowScale &scale = RowScale{}) {
     GemmArgs a{};
+    a.scale = scale;
     a.X = X;
     a.W = (const uint4 *)W.p;
     a.M = M;
@@ -568,6 +571,28 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
     da.q32 = c->q32;
     da.direct_out32 = direct && dbg ? c->attn32 : nullptr;
 
+    // Thin projections of a few rows finish in their own kernel.  O and down then leave x * gain of the next norm in c->xn and `folded`
+    // says how the projection behind it finishes that norm; else there are partial sums, a norm kernel, and X is normalised.
+    const RowScale fold{c->squares, c->squares_ld, 1.0f / (float)H, s.rms_eps};
+    RowScale folded{};
+    const bool thin_q = !dbg && thin_qkv(M, c->qkv_cols, c->ks_h), thin_o = !dbg && thin_resid(M, H, c->ks_q);
+    const bool thin_d = thin_q && thin_resid(M, H, c->ks_f);
+    auto resid_args = [&](const uint4 *X, const PackedMat &W, const uint16_t *gain) {
+        ThinArgs t{};
+        t.X = X;
+        t.W = (const uint4 *)W.p;
+        t.M = M;
+        t.N = H;
+        t.mt_total = c->mt_total;
+        t.ks_total = W.ks;
+        t.resid = c->resid;
+        t.gain = gain;
+        t.xg = (uint16_t *)c->xn;
+        t.squares = c->squares;
+        t.squares_ld = c->squares_ld;
+        return t;
+    };
+
     for (int l = 0; l < s.n_layers; ++l) {
         const LayerW &w = c->L[l];
         NormArgs na{};
@@ -594,16 +619,11 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
             na.n_partials = n_part;
             na.partial_stride = part_stride;
         }
-        SR_TRY(timed(c, SR_KC_NORM, st, [&] { return launch_resid_norm(na, st); }));
+        if (!folded.squares) SR_TRY(timed(c, SR_KC_NORM, st, [&] { return launch_resid_norm(na, st); }));
 
         int sp = 1;
-        SR_TRY(timed(c, SR_KC_GEMM_QKV, st, [&] {
-            return dbg ? gemm32(c, c->xn32, H, w.qkv, M, EPI_F32, c->partials, c->qkv_cols, &sp, st)
-                       : gemm(c, c->xn, w.qkv, M, EPI_F32, c->partials, c->qkv_cols, &sp, st);
-        }));
         QkvPostArgs qa{};
         qa.partials = c->partials;
-        qa.n_partials = sp;
         qa.partial_stride = (size_t)round_up(M, 128) * c->qkv_cols;
         qa.ld = c->qkv_cols;
         qa.bq = s.qkv_bias ? w.bq : nullptr;
@@ -624,6 +644,24 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
         qa.n_kv = s.n_kv_heads;
         qa.d = s.head_dim;
         qa.page_tokens = c->o.page_tokens;
+        if (thin_q) {
+            ThinArgs t{};
+            t.X = c->xn;
+            t.W = (const uint4 *)w.qkv.p;
+            t.M = M;
+            t.N = c->qkv_cols;
+            t.mt_total = c->mt_total;
+            t.ks_total = w.qkv.ks;
+            t.scale = folded;
+            t.qkv = qa;
+            SR_TRY(timed(c, SR_KC_GEMM_QKV, st, [&] { return launch_thin_qkv(t, st); }));
+        } else {
+            SR_TRY(timed(c, SR_KC_GEMM_QKV, st, [&] {
+                return dbg ? gemm32(c, c->xn32, H, w.qkv, M, EPI_F32, c->partials, c->qkv_cols, &sp, st)
+                           : gemm(c, c->xn, w.qkv, M, EPI_F32, c->partials, c->qkv_cols, &sp, st);
+            }));
+            qa.n_partials = sp;
+        }
         if (dbg) {
             DbgQkvPostArgs dq{};
             dq.base = qa;
@@ -637,7 +675,7 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
             SR_TRY(timed(c, p.decode ? SR_KC_ATTN_DECODE : SR_KC_ATTN_PREFILL, st,
                          [&] { return launch_dbg_attention(da, ph, n_ph, st); }));
         } else {
-            SR_TRY(timed(c, SR_KC_QKV_POST, st, [&] { return launch_qkv_post(qa, st); }));
+            if (!thin_q) SR_TRY(timed(c, SR_KC_QKV_POST, st, [&] { return launch_qkv_post(qa, st); }));
             aa.kpool = qa.kpool;
             aa.vpool = qa.vpool;
             SR_TRY(timed(c, p.decode ? SR_KC_ATTN_DECODE : SR_KC_ATTN_PREFILL, st,
@@ -649,27 +687,41 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
             }));
         }
 
-        SR_TRY(timed(c, SR_KC_GEMM_O, st, [&] {
-            return dbg ? gemm32(c, c->attn32, qd, w.o, M, EPI_F32, c->partials, H, &sp, st)
-                       : gemm(c, c->attn_out, w.o, M, EPI_F32, c->partials, H, &sp, st);
-        }));
-        na.embed = nullptr;
-        na.tokens = nullptr;
-        na.partials = c->partials;
-        na.n_partials = sp;
-        na.partial_stride = (size_t)round_up(M, 128) * H;
-        na.gain = w.norm2;
-        SR_TRY(timed(c, SR_KC_NORM, st, [&] { return launch_resid_norm(na, st); }));
+        if (thin_o) {
+            SR_TRY(timed(c, SR_KC_GEMM_O, st, [&] { return launch_thin_resid(resid_args(c->attn_out, w.o, w.norm2), st); }));
+            folded = fold;
+        } else {
+            SR_TRY(timed(c, SR_KC_GEMM_O, st, [&] {
+                return dbg ? gemm32(c, c->attn32, qd, w.o, M, EPI_F32, c->partials, H, &sp, st)
+                           : gemm(c, c->attn_out, w.o, M, EPI_F32, c->partials, H, &sp, st);
+            }));
+            na.embed = nullptr;
+            na.tokens = nullptr;
+            na.partials = c->partials;
+            na.n_partials = sp;
+            na.partial_stride = (size_t)round_up(M, 128) * H;
+            na.gain = w.norm2;
+            SR_TRY(timed(c, SR_KC_NORM, st, [&] { return launch_resid_norm(na, st); }));
+            folded = RowScale{};
+        }
 
         SR_TRY(timed(c, SR_KC_GEMM_GATE_UP, st, [&] {
             return dbg ? gemm32(c, c->xn32, H, w.gu, M, EPI_SWIGLU, c->act32, s.ffn, nullptr, st)
-                       : gemm(c, c->xn, w.gu, M, EPI_SWIGLU, c->act, c->ks_f * 32, nullptr, st);
+                       : gemm(c, c->xn, w.gu, M, EPI_SWIGLU, c->act, c->ks_f * 32, nullptr, st, folded);
         }));
-        SR_TRY(timed(c, SR_KC_GEMM_DOWN, st, [&] {
-            return dbg ? gemm32(c, c->act32, s.ffn, w.down, M, EPI_F32, c->partials, H, &sp, st)
-                       : gemm(c, c->act, w.down, M, EPI_F32, c->partials, H, &sp, st);
-        }));
-        n_part = sp;
+        if (thin_d) {
+            const uint16_t *next = l + 1 < s.n_layers ? c->L[l + 1].norm1 : c->final_norm;
+            SR_TRY(timed(c, SR_KC_GEMM_DOWN, st, [&] { return launch_thin_resid(resid_args(c->act, w.down, next), st); }));
+            folded = fold;
+            n_part = 0;
+        } else {
+            SR_TRY(timed(c, SR_KC_GEMM_DOWN, st, [&] {
+                return dbg ? gemm32(c, c->act32, s.ffn, w.down, M, EPI_F32, c->partials, H, &sp, st)
+                           : gemm(c, c->act, w.down, M, EPI_F32, c->partials, H, &sp, st);
+            }));
+            folded = RowScale{};
+            n_part = sp;
+        }
         part_stride = (size_t)round_up(M, 128) * H;
     }
 
@@ -741,6 +793,8 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
     }
 
     if (p.want_logits) {
+        // every row's logits, and the last projection has left x * gain of the final norm
+        const bool as_is = folded.squares && p.chunk == 1 && p.logit_dup == 1;
         NormArgs na{};
         na.resid = c->resid;
         na.partials = c->partials;
@@ -757,11 +811,11 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
         na.H = H;
         na.mt_total = c->mt_total;
         na.eps = s.rms_eps;
-        SR_TRY(timed(c, SR_KC_NORM, st, [&] { return launch_resid_norm(na, st); }));
+        if (!as_is) SR_TRY(timed(c, SR_KC_NORM, st, [&] { return launch_resid_norm(na, st); }));
         float *dst = c->d_logits[c->cur] + (size_t)p.logit_row0 * s.vocab;
         SR_TRY(timed(c, SR_KC_GEMM_LM_HEAD, st, [&] {
             return dbg ? gemm32(c, c->xn32, H, c->lm, na.rows_out, EPI_F32, dst, s.vocab, nullptr, st)
-                       : gemm(c, c->xn, c->lm, na.rows_out, EPI_F32, dst, s.vocab, nullptr, st);
+                       : gemm(c, c->xn, c->lm, na.rows_out, EPI_F32, dst, s.vocab, nullptr, st, as_is ? folded : RowScale{});
         }));
     }
     return SR_OK;
@@ -807,6 +861,7 @@ static int init_impl(sr_ctx *c) {
     const int d = s.head_dim;
     c->n_seq0 = c->n_groups0 * c->G;
     c->qkv_cols = (s.n_q_heads + 2 * s.n_kv_heads) * d;
+    c->squares_ld = round_up(s.hidden / 16, 4);
     c->ks_h = padded_k_steps(s.hidden);
     c->ks_q = padded_k_steps(s.n_q_heads * d);
     c->ks_f = padded_k_steps(s.ffn);
@@ -892,6 +947,7 @@ static int init_impl(sr_ctx *c) {
     plan.want(&c->attn_out, R * (size_t)(c->ks_q * 32) / 8);
     plan.want(&c->act, R * (size_t)(c->ks_f * 32) / 8);
     plan.want(&c->q, R * (size_t)s.n_q_heads * d);
+    plan.want(&c->squares, (size_t)kThinRows * c->squares_ld);
     plan.want(&c->part_o, c->part_rows_cap * d);
     plan.want(&c->part_ml, c->part_rows_cap * 2);
     SR_TRY(plan.commit(c));
@@ -908,6 +964,7 @@ static int init_impl(sr_ctx *c) {
     SR_HIP(hipMemset(c->xn, 0, R * (size_t)(c->ks_h * 32) * 2));
     SR_HIP(hipMemset(c->attn_out, 0, R * (size_t)(c->ks_q * 32) * 2));
     SR_HIP(hipMemset(c->act, 0, R * (size_t)(c->ks_f * 32) * 2));
+    SR_HIP(hipMemset(c->squares, 0, (size_t)kThinRows * c->squares_ld * 4));
     SR_HIP(hipMemset(c->d_pt, 0, n_seq * c->max_pages * 4));
     for (int i = 0; i < 2; ++i) {
         SR_TRY(launch_fill_i32(c->d_actions[i], n_seq * o.max_turns, -1, nullptr));
@@ -1003,18 +1060,18 @@ int sr_load_weights(sr_ctx *c, const sr_weights *w, void *stream) {
     SR_TRY(clear_padding(c->lm, st));
     // tied: the LM head is the embedding matrix, packed like any other projection
     SR_TRY(launch_pack_rows((const uint16_t *)(s.tied_lm_head ? w->embed : w->lm_head), s.vocab, H, c->lm.p, c->lm.ks,
-                            0, 0, 0, st));
+                            0, 0, 0, 0, st));
     for (int l = 0; l < s.n_layers; ++l) {
         const sr_layer_weights &x = w->layers[l];
         LayerW &y = c->L[l];
         for (const PackedMat *m : {&y.qkv, &y.o, &y.gu, &y.down}) SR_TRY(clear_padding(*m, st));
-        SR_TRY(launch_pack_rows((const uint16_t *)x.wq, qd, H, y.qkv.p, y.qkv.ks, 0, 0, 0, st));
-        SR_TRY(launch_pack_rows((const uint16_t *)x.wk, kd, H, y.qkv.p, y.qkv.ks, qd, 0, 0, st));
-        SR_TRY(launch_pack_rows((const uint16_t *)x.wv, kd, H, y.qkv.p, y.qkv.ks, qd + kd, 0, 0, st));
-        SR_TRY(launch_pack_rows((const uint16_t *)x.wo, H, qd, y.o.p, y.o.ks, 0, 0, 0, st));
-        SR_TRY(launch_pack_rows((const uint16_t *)x.wg, s.ffn, H, y.gu.p, y.gu.ks, 0, 1, 0, st));
-        SR_TRY(launch_pack_rows((const uint16_t *)x.wu, s.ffn, H, y.gu.p, y.gu.ks, 0, 1, 1, st));
-        SR_TRY(launch_pack_rows((const uint16_t *)x.wd, H, s.ffn, y.down.p, y.down.ks, 0, 0, 0, st));
+        SR_TRY(launch_pack_rows((const uint16_t *)x.wq, qd, H, y.qkv.p, y.qkv.ks, 0, 0, 0, s.head_dim, st));
+        SR_TRY(launch_pack_rows((const uint16_t *)x.wk, kd, H, y.qkv.p, y.qkv.ks, qd, 0, 0, s.head_dim, st));
+        SR_TRY(launch_pack_rows((const uint16_t *)x.wv, kd, H, y.qkv.p, y.qkv.ks, qd + kd, 0, 0, s.head_dim, st));
+        SR_TRY(launch_pack_rows((const uint16_t *)x.wo, H, qd, y.o.p, y.o.ks, 0, 0, 0, 0, st));
+        SR_TRY(launch_pack_rows((const uint16_t *)x.wg, s.ffn, H, y.gu.p, y.gu.ks, 0, 1, 0, 0, st));
+        SR_TRY(launch_pack_rows((const uint16_t *)x.wu, s.ffn, H, y.gu.p, y.gu.ks, 0, 1, 1, 0, st));
+        SR_TRY(launch_pack_rows((const uint16_t *)x.wd, H, s.ffn, y.down.p, y.down.ks, 0, 0, 0, 0, st));
         if (s.qkv_bias) {
             SR_TRY(copy_vec(y.bq, x.bq, qd, st));
             SR_TRY(copy_vec(y.bk, x.bk, kd, st));

@@ -660,11 +660,15 @@ constexpr int kPackSteps = 8;
 template <bool ALIGNED>                    // the source pointer is a multiple of 16 bytes
 __global__ __launch_bounds__(256) void pack_rows_kernel(const uint16_t *__restrict__ src, int n_rows, int K,
                                                         uint16_t *__restrict__ dst, int ks_total, int dst_row0,
-                                                        int interleave16, int which) {
+                                                        int interleave16, int which, int half_tiles) {
     const int tile = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int i = tile * 16 + (lane & 15), kg = lane >> 4;
     if (i >= n_rows) return;
-    const size_t ptile = interleave16 ? 2 * tile + which : (dst_row0 >> 4) + tile;
+    size_t ptile = interleave16 ? 2 * tile + which : (dst_row0 >> 4) + tile;
+    if (half_tiles) {                                    // tiles of a head's low half, then of its high half -> in turn
+        const int u = tile % (2 * half_tiles);
+        ptile += (u < half_tiles ? 2 * u : 2 * (u - half_tiles) + 1) - u;
+    }
     const int ks0 = blockIdx.y * kPackSteps;
     const uint16_t *row = src + (size_t)i * K;
     uint4 v[kPackSteps];
@@ -692,14 +696,14 @@ __global__ __launch_bounds__(256) void pack_rows_kernel(const uint16_t *__restri
 }  // namespace
 
 int launch_pack_rows(const uint16_t *src, int n_rows, int K, uint16_t *dst, int ks_total, int dst_row0,
-                     int interleave16, int which, hipStream_t stream) {
+                     int interleave16, int which, int head_dim, hipStream_t stream) {
     if (n_rows <= 0 || ks_total <= 0) return SR_OK;
-    if (K % 8 || dst_row0 % 16) return SR_E_ARG;
+    if (K % 8 || dst_row0 % 16 || (head_dim && (head_dim % 32 || n_rows % head_dim))) return SR_E_ARG;
     const dim3 grid(ceil_div(ceil_div(n_rows, 16), 4), ceil_div(ks_total, kPackSteps)), block(256);
     if (((uintptr_t)src & 15) == 0)
-        pack_rows_kernel<true><<<grid, block, 0, stream>>>(src, n_rows, K, dst, ks_total, dst_row0, interleave16, which);
+        pack_rows_kernel<true><<<grid, block, 0, stream>>>(src, n_rows, K, dst, ks_total, dst_row0, interleave16, which, head_dim / 32);
     else
-        pack_rows_kernel<false><<<grid, block, 0, stream>>>(src, n_rows, K, dst, ks_total, dst_row0, interleave16, which);
+        pack_rows_kernel<false><<<grid, block, 0, stream>>>(src, n_rows, K, dst, ks_total, dst_row0, interleave16, which, head_dim / 32);
     SR_HIP(hipGetLastError());
     return SR_OK;
 }
@@ -758,6 +762,7 @@ int launch_gemm(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream) {
     if (m_blocks * 8 > a.mt_total || a.splits < 1 || m_blocks > 65535 || a.splits > 65535 || a.ks_total % kPF)
         return SR_E_ARG;
     if (a.wide) return launch_gemm_stream(a, epi, stream);
+    if (a.scale.squares) return SR_E_ARG;
     if (epi == EPI_LSE) return launch_tiles<EPI_LSE, 8, 4>(a, stream);
     if (epi == EPI_SWIGLU && a.splits != 1) return SR_E_ARG;
     const GemmPlan plan = plan_gemm(a.M, a.N, a.ks_total, a.mt_total, epi == EPI_SWIGLU, a.splits, a.splits);

@@ -1,6 +1,6 @@
 // Decode-time projection GEMM  Y[M][N] = X[M][K] * W[N][K]^T  for M <= 256 on the bf16 matrix cores:
 // the weight-streaming kernel that carries most of a decode step's HBM traffic.
-#include "sr_internal.h"
+#include "epilogue.h"
 
 namespace sr {
 namespace {
@@ -49,10 +49,12 @@ __device__ __forceinline__ u32x4 load_w_stream(const u32x4 *p) { return __builti
 // ---------------------------------------------------------------------------------------------
 constexpr int kRing = 8;                   // k-steps of W in flight per computing wavefront (16 measured slower at every width)
 constexpr int kStBufs = 3;                 // LDS chunk buffers: the loader runs two chunks ahead
-constexpr int st_lds_bytes(int mt32) { return kStBufs * chunk_steps(mt32) * kstep_vec(mt32) * 16; }
+constexpr int st_x_bytes(int mt32) { return kStBufs * chunk_steps(mt32) * kstep_vec(mt32) * 16; }
+// ... and, where a norm is finished, a float for every computing thread behind them (RowScale)
+constexpr int st_lds_bytes(int mt32, int waves, bool scaled) { return st_x_bytes(mt32) + (scaled ? 256 * waves : 0); }
 
 // RING = k-steps of W each computing wavefront keeps in flight (2 KiB per k-step)
-template <int EPI, int WAVES, int MT32, int RING>
+template <int EPI, int WAVES, int MT32, int RING, bool SCALED>
 __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(GemmArgs a) {
     extern __shared__ u32x4 lds_dyn[];     // [kStBufs][k-step in chunk][16-row tile][lane]
     constexpr int kKC = chunk_steps(MT32), kStepVec = kstep_vec(MT32), kChunkVec = kKC * kStepVec;
@@ -109,6 +111,11 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(GemmArgs 
     const int sub = r32 >> 4;                       // which 16-row tile of the pair
     const int slot0 = (r32 & 15) + 16 * g2;         // lane slot for k-half 0; k-half 1 is +32
 
+    // The norm in front of this projection: its sums of squares are dealt out over the computing threads, requested before the first
+    // weights and added up behind them.  (By the loader, in a few round trips before the first barrier, it cost 3.5 us at 8 rows.)
+    RowSquares<64 * WAVES> squares;
+    if constexpr (SCALED) squares.request(a.scale, a.M, tid);
+
     f32x16 acc[MT32];
 #pragma unroll
     for (int i = 0; i < MT32; ++i)
@@ -127,6 +134,7 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(GemmArgs 
             w0[i] = load_w_stream(wp0 + (size_t)(ks0 + i) * 64);
             w1[i] = load_w_stream(wp1 + (size_t)(ks0 + i) * 64);
         }
+        if constexpr (SCALED) squares.leave(a.scale, (float *)lds_dyn + st_x_bytes(MT32) / 4, tid);
         __syncthreads();                                         // barrier 0: chunk 0 is in LDS
 
         int buf = 0;
@@ -213,6 +221,11 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(GemmArgs 
 
     // accumulator of row tile mt: lane (r32 = batch row within the tile, g2) holds, in register v,
     // output feature 8 * (v / 4) + 4 * g2 + v % 4 of the wavefront's 32
+    if constexpr (SCALED) {
+        const float *left = (const float *)lds_dyn + st_x_bytes(MT32) / 4;
+#pragma unroll
+        for (int mt = 0; mt < MT32; ++mt) acc[mt] *= squares.scale(a.scale, left, mt * 32 + r32);
+    }
     if constexpr (EPI == EPI_F32) {
         float *out = (float *)a.out + (size_t)sp * a.split_stride;
 #pragma unroll
@@ -263,23 +276,25 @@ int launch_gemm_stream(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream) 
     dim3 sgrid(ceil_div(a.N, 32 * a.wide), 1, epi == EPI_F32 ? a.splits : 1), lblock(64 * (a.wide + 1));
     const int mt32 = ceil_div(a.M, 32);
     hipError_t attr = hipSuccess;
-#define SR_STREAM_CASE(E, W, T)                                                                            \
-    (attr = hipFuncSetAttribute((const void *)gemm_stream_kernel<E, W, T, kRing>,                          \
-                        hipFuncAttributeMaxDynamicSharedMemorySize, st_lds_bytes(T)),                      \
-     gemm_stream_kernel<E, W, T, kRing><<<sgrid, lblock, st_lds_bytes(T), stream>>>(a))
-#define SR_STREAM_MT(E, W)                                                                                 \
-    (mt32 == 1 ? SR_STREAM_CASE(E, W, 1) : mt32 == 2 ? SR_STREAM_CASE(E, W, 2)                             \
-     : mt32 == 3 ? SR_STREAM_CASE(E, W, 3) : mt32 == 4 ? SR_STREAM_CASE(E, W, 4)                           \
-     : mt32 == 5 ? SR_STREAM_CASE(E, W, 5) : mt32 == 6 ? SR_STREAM_CASE(E, W, 6)                           \
-     : mt32 == 7 ? SR_STREAM_CASE(E, W, 7) : SR_STREAM_CASE(E, W, 8))
+    const bool scaled = a.scale.squares != nullptr;
+#define SR_STREAM_CASE(E, W, T, S)                                                                         \
+    (attr = hipFuncSetAttribute((const void *)gemm_stream_kernel<E, W, T, kRing, S>,                       \
+                        hipFuncAttributeMaxDynamicSharedMemorySize, st_lds_bytes(T, W, S)),                \
+     gemm_stream_kernel<E, W, T, kRing, S><<<sgrid, lblock, st_lds_bytes(T, W, S), stream>>>(a))
+#define SR_STREAM_SCALED(E, W, T) (scaled ? SR_STREAM_CASE(E, W, T, true) : SR_STREAM_CASE(E, W, T, false))
     // nine and eleven wavefronts put three on one SIMD: 168 registers, too few for more than four row tiles
 #define SR_STREAM_MT4(E, W)                                                                                \
-    (mt32 == 1 ? SR_STREAM_CASE(E, W, 1) : mt32 == 2 ? SR_STREAM_CASE(E, W, 2)                             \
-     : mt32 == 3 ? SR_STREAM_CASE(E, W, 3) : SR_STREAM_CASE(E, W, 4))
+    (mt32 == 1 ? SR_STREAM_SCALED(E, W, 1) : mt32 == 2 ? SR_STREAM_SCALED(E, W, 2)                         \
+     : mt32 == 3 ? SR_STREAM_SCALED(E, W, 3) : SR_STREAM_SCALED(E, W, 4))
+#define SR_STREAM_MT(E, W)                                                                                 \
+    (mt32 <= 4 ? SR_STREAM_MT4(E, W)                                                                       \
+     : mt32 == 5 ? SR_STREAM_CASE(E, W, 5, false) : mt32 == 6 ? SR_STREAM_CASE(E, W, 6, false)             \
+     : mt32 == 7 ? SR_STREAM_CASE(E, W, 7, false) : SR_STREAM_CASE(E, W, 8, false))
 #define SR_STREAM_W(E)                                                                                     \
     (a.wide == 2 ? SR_STREAM_MT(E, 2) : a.wide == 4 ? SR_STREAM_MT(E, 4)                                   \
      : a.wide == 5 ? SR_STREAM_MT(E, 5) : a.wide == 8 ? SR_STREAM_MT4(E, 8) : SR_STREAM_MT4(E, 10))
-    if (mt32 > 4 && a.wide >= 8) return SR_E_ARG;
+    if (mt32 > 4 && (a.wide >= 8 || scaled)) return SR_E_ARG;
+    if (scaled && (a.scale.ld % 4 || a.splits != 1)) return SR_E_ARG;
     if (epi == EPI_F32) SR_STREAM_W(EPI_F32); else SR_STREAM_W(EPI_SWIGLU);
     SR_HIP(attr);
     SR_HIP(hipGetLastError());

@@ -107,6 +107,26 @@ inline int pick_splits(int M, int N, int ks_total) {
     return s < 1 ? 1 : s;
 }
 
+// Thin projections of up to kThinRows rows that finish in the kernel (gemm_thin.hip).  A workgroup reads its own part of W and all of X,
+// at about 50 KB / us, and saves the kernel that adds partial sums (norm or QKV epilogue, 3.3 to 5 us) and their way through
+// memory; gemm_stream_kernel shares X between several times as many features.  The limits are where the two come out even.  Whole
+// calls of two layers, us, without these -> with them: K = 3584, decode of 8 rows 246 -> 227, 16 rows (all but down) 249 -> 244, 24
+// rows (none; QKV or O alone would be +- 1 %) 252; hidden 256, decode of 32 rows 80 -> 65, 128 rows 104 -> 89, prefill of 40 rows 98 -> 82;
+// hidden 512 with down projections of 8192 inputs (which stay), 8 rows 95 -> 90, 32 rows 107 -> 99; QKV at 64 rows there 108 -> 110.
+constexpr int kThinRows = 128;
+inline long long thin_bytes(int M, int features, int N, int ks_total) {
+    const int rows = M <= 8 ? 8 : round_up(M, 16), rounds = ceil_div(ceil_div(N, features), 256);
+    return (long long)rounds * (features + rows) * ks_total * 64;
+}
+// O and down.  Eight rows at any depth where the matrix has a workgroup for most compute units: down of the 7B shape streams no
+// faster otherwise (23 and 24 us).
+inline bool thin_resid(int M, int N, int ks_total) {
+    return M <= kThinRows && (thin_bytes(M, 16, N, ks_total) <= 256 << 10 || (M <= 8 && N >= 3200 && N <= 4096));
+}
+inline bool thin_qkv(int M, int N, int ks_total) {
+    return M <= kThinRows && thin_bytes(M, 32, N, ks_total) <= (M <= 32 ? 360 << 10 : 88 << 10);
+}
+
 // The tiled kernels: which one, and how many K splits.  Times in us, from launches of the 7B shape's projections at
 // 8192, 5120, 4096, 2048, 1280, 768, 512 and 296 rows; k = K / 3584.  A launch has about 3 us of its own, the same for all.
 //   64 RT x 32 NT tiles, one to a CU: a round takes 2.33 RT (NT + 1.5) k.  O at 4096 rows 86 (NT = 7) and 88 (8), QKV at

@@ -128,9 +128,12 @@ int launch_extract_gate(const sr_signals_t *sig, int n_groups, int use_or, int32
 // ---------------------------------------------------------------------------------------------
 // Pack rows [row0, row0+n_rows) of a row-major bf16 matrix src[*][K] into the weight layout of
 // dst (ks_total k-steps per row tile), placing source row row0+i at packed row dst_row0 + f(i):
-// f(i) = i (interleave16 == 0) or, for the gate|up pair, 32*(i/16) + 16*which + i%16.
+// f(i) = i (interleave16 == 0) or, for the gate|up pair, 32*(i/16) + 16*which + i%16.  head_dim != 0: the rows are heads of that many
+// dims, and dim i < head_dim/2 of a head goes to place qkv_column(i) of it, its rotation partner i + head_dim/2 16 places further
+// on, so that one lane of a projection holds both.
 int launch_pack_rows(const uint16_t *src, int n_rows, int K, uint16_t *dst, int ks_total, int dst_row0,
-                     int interleave16, int which, hipStream_t stream);
+                     int interleave16, int which, int head_dim, hipStream_t stream);
+__host__ __device__ inline int qkv_column(int i) { return 32 * (i >> 4) + (i & 15); }
 
 // ---------------------------------------------------------------------------------------------
 // GEMM  Y[M][N] = X[M][K] * W[N][K]^T, X fragment-major bf16, W packed bf16, fp32 accumulate
@@ -152,6 +155,14 @@ struct ScoreOut {
     int rows_per_unit;
 };
 
+// RMSNorm folded into the projections on both sides of it: the projection in front of it leaves x * gain in bf16 and sums of squares
+// of x over 16 features at a time, the one behind it multiplies its results by 1 / sqrt(sum / H + eps), row by row.
+struct RowScale {
+    const float *squares;    // [128 rows][ld], zero behind the last, or null: X is normalised as it stands
+    int ld;                  // a multiple of 4
+    float inv_h, eps;
+};
+
 struct GemmArgs {
     const uint4 *X;
     const uint4 *W;
@@ -165,6 +176,7 @@ struct GemmArgs {
     int ld_out;          // EPI_F32: row stride (elements); EPI_SWIGLU: k-steps*32 of the output matrix
     size_t split_stride; // EPI_F32: elements between consecutive splits
     ScoreOut score;      // EPI_LSE
+    RowScale scale;      // the weight-streaming kernel, up to 128 rows
 };
 
 // The weight-streaming kernel with a loader wavefront (a.wide != 0, M <= 256); launch_gemm dispatches to it.
@@ -209,10 +221,34 @@ struct QkvPostArgs {
     int rows, chunk;         // row m = unit (m / chunk), token (m % chunk) of the chunk
     int pos0;                // absolute position of the chunk's first token
     int n_q, n_kv, d, page_tokens;
-    FastDiv by_chunk;        // set by launch_qkv_post, as the next two: log2(page_tokens), heads per workgroup
+    FastDiv by_chunk;        // set by the launch, as the next two: log2(page_tokens), heads per workgroup (launch_qkv_post)
     int page_shift, heads_per_block;
 };
+inline void set_divisions(QkvPostArgs *a) {
+    a->by_chunk = fast_div(a->chunk);
+    a->page_shift = 31 - __builtin_clz(a->page_tokens);
+}
 int launch_qkv_post(const QkvPostArgs &a, hipStream_t stream);
+
+// ---------------------------------------------------------------------------------------------
+// thin projections of a few rows: K dealt out over the wavefronts of a workgroup, no partial sums in memory
+// ---------------------------------------------------------------------------------------------
+struct ThinArgs {
+    const uint4 *X;
+    const uint4 *W;
+    int M, N, mt_total, ks_total;
+    RowScale scale;          // of X
+    // O and down: resid += X W^T, and what the projection behind the next norm reads
+    float *resid;            // [M][N]
+    const uint16_t *gain;    // [N] bf16, of the norm that follows
+    uint16_t *xg;            // fragment-major bf16 [M][N]: resid * gain
+    float *squares;          // [M][squares_ld]: a sum for every 16 features
+    int squares_ld;
+    // QKV: everything but the partial sums (qkv.partials is not read)
+    QkvPostArgs qkv;
+};
+int launch_thin_resid(const ThinArgs &a, hipStream_t stream);
+int launch_thin_qkv(const ThinArgs &a, hipStream_t stream);
 
 // greedy[r] = lowest index of the largest logit of row r; tok = forced ? forced[r] : greedy[r];
 // chosen[r] = tok; if actions != null: actions[r*max_turns + turn_idx] = tok % action_mod.

@@ -1059,3 +1059,32 @@ def test_inner_dimensions_of_an_odd_number_of_groups(n_groups, hidden, q_heads, 
     rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=81, page_tokens=32, kv_pool_bytes=1 << 28)
     print(f"odd K {hidden}/{ffn} {n_groups * 8}: worst |dlogit| = {worst:.3e}, mismatches = {mism}, near ties = {near}")
     assert worst <= LOGIT_TOL and mism == 0
+
+
+@pytest.mark.parametrize("n_groups,G", [(1, 2), (1, 8), (3, 3), (2, 8), (3, 6), (4, 8), (11, 3), (8, 8), (13, 5), (16, 8), (26, 5)])
+@pytest.mark.parametrize("hidden,n_q,n_kv,d,ffn", [(224, 6, 2, 64, 304), (96, 3, 1, 128, 1296)])
+def test_projections_that_finish_in_their_own_kernel(plan, n_groups, G, hidden, n_q, n_kv, d, ffn):
+    """Row counts on both sides of 8, 16, 32, 64 and 128 with a norm over 14 and 6 sums of squares (no multiple of four), two layers,
+    chunks of three tokens besides the decode steps, half the prompt page copied; the group that converges leaves."""
+    rows, ks = n_groups * G, plan.padded_k_steps
+    thin = rows <= 128
+    assert plan.thin_qkv(rows, (n_q + 2 * n_kv) * d, ks(hidden)) == thin and plan.thin_resid(rows, hidden, ks(n_q * d)) == thin
+    shape = synth.ModelShape(2, hidden, n_q, n_kv, d, ffn, 272)
+    cfg = synth.EpisodeConfig("thin", n_groups, G, 40, 2, 3, 2, 16, (1,), 0.3, 0.4)
+    rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=83, page_tokens=32)
+    print(f"thin {rows} x {hidden}: worst |dlogit| = {worst:.3e}, mismatches = {mism}, near ties = {near}")
+    assert worst <= LOGIT_TOL and mism == 0
+
+
+@pytest.mark.parametrize("n_groups,G", [(1, 8), (1, 2), (2, 8)])
+def test_wide_projections_of_up_to_16_rows_that_finish_in_their_own_kernel(plan, n_groups, G):
+    """Hidden 3200 with a down projection of 6400 inputs (in its own kernel up to 8 rows only), two layers: 200 sums of squares a row."""
+    rows = n_groups * G
+    assert plan.thin_resid(rows, 3200, 200) == (rows <= 8) and plan.thin_resid(rows, 3200, 48) and plan.thin_qkv(rows, 2048, 104)
+    shape = synth.ModelShape(2, 3200, 12, 2, 128, 6400, 512)
+    cfg = synth.EpisodeConfig("thin-wide", n_groups, G, 6, 1, 1, 2, 16, (), 0.3, 0.0)
+    info = {}
+    rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=84, page_tokens=32, contract_rows=[0, rows - 1], info=info)
+    tol = tolerance(info["contract_max"])
+    print(f"thin wide {rows}: worst |dlogit| = {worst:.3e}, bound {tol:.3e}, mismatches = {mism}, near ties = {near}")
+    assert worst <= tol and all(g < gap_rule(tol) for g in info["mismatch_gaps"])

@@ -232,3 +232,18 @@ def test_inner_dimensions_of_an_odd_number_of_groups(plan, K, M):
         assert 1 <= splits <= max(1, ks // plan.split_steps(M, N, ks, 512, splits))
     if K == 1792 and 128 < M <= 256:
         assert plan.projection_splits(M, 512, ks, 512) == plan.projection_splits(M, 512, 64, 512) == 2
+
+
+def test_thin_projections_where_they_come_out_ahead(plan):
+    """Up to 128 rows of small matrices, up to 8 (all) and 16 (not down) of the 7B shape's; never above 128 rows, the size of their buffer."""
+    for M in (1, 8):
+        assert plan.thin_qkv(M, 4608, 112) and plan.thin_resid(M, 3584, 112) and plan.thin_resid(M, 3584, 592)
+    for M in (9, 16):
+        assert plan.thin_qkv(M, 4608, 112) and plan.thin_resid(M, 3584, 112) and not plan.thin_resid(M, 3584, 592)
+    assert not plan.thin_qkv(17, 4608, 112) and not plan.thin_resid(17, 3584, 112)
+    for M in (1, 32, 128):
+        assert plan.thin_qkv(M, 512, 8) and plan.thin_resid(M, 256, 8) and plan.thin_resid(M, 256, 24)
+    assert plan.thin_qkv(32, 2304, 16) and not plan.thin_qkv(64, 2304, 16) and not plan.thin_resid(8, 512, 256)
+    for M in (129, 200, 4000):
+        for N in (16, 256, 3584):
+            assert not plan.thin_qkv(M, N, 8) and not plan.thin_resid(M, N, 8)
