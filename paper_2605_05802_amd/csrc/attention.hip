@@ -12,7 +12,8 @@
 // four lanes, then  O^T += V^T P^T  where the probabilities of the two 16-token
 // tiles are packed, in-lane, into the P^T operand (the V block's slot order matches).
 // Splits leave (un-normalised O, running max, running sum); a merge kernel combines the splits
-// of the shared-prompt phase and of the private phase in fixed order.
+// of the shared-prompt phase and of the private phase in fixed order.  Short contexts of a few sequences take one kernel for all of
+// it (attn_whole_kernel).
 //
 // Group batching: during decode the prompt pages shared by the G members of a group are read
 // once per group (the members' G*n_rep query rows form the row tiles of the work item)
@@ -165,18 +166,11 @@ __device__ __forceinline__ void load_queries(const AttnArgs &a, const AttnPhase 
 // ---------------------------------------------------------------------------------------------
 // One work item alone (a sequence's private context during decode; units with few query tiles).
 // ---------------------------------------------------------------------------------------------
-template <int D, int RT>
-__device__ __forceinline__ void single_item(const AttnArgs &a, const AttnPhase &p, int item, int lane) {
+// finish(o, mrun, lrun, limit, first query token) takes the results.
+template <int D, int RT, typename F>
+__device__ __forceinline__ void walk_item(const AttnArgs &a, const AttnPhase &p, int unit, int kvh, int split, int qtile, int lane, F &&finish) {
     constexpr int KS = D / 32;     // k-steps of the QK^T contraction
     constexpr int DT = D / 16;     // 16-wide tiles of the head dimension
-
-    // item -> (unit, kv head, split, q tile): the q tiles of one split are neighbours
-    int rest = quotient(item, p.by_items);
-    const int qtile = item - rest * p.items_per_unit;
-    const int set = rest;
-    rest = quotient(set, p.by_splits);
-    const int split = set - rest * p.n_splits;
-    const int unit = quotient(rest, a.by_kv), kvh = rest - unit * a.n_kv;
 
     const int c = lane & 15, g = lane >> 4;
     const int u_row0 = p.unit_row0 ? table_entry(p.unit_row0, unit) : unit * p.q_per_unit;   // first query token of the unit
@@ -286,7 +280,18 @@ __device__ __forceinline__ void single_item(const AttnArgs &a, const AttnPhase &
     };
     if (p.stream_loads) block_loop(std::true_type{});       // uniform: one of two copies of the loop runs
     else block_loop(std::false_type{});
-    store_item<D, RT>(a, p, o, mrun, lrun, limit, item, (size_t)u_row0 + qtile * p.q_per_item, kvh, c, g);
+    finish(o, mrun, lrun, limit, (size_t)u_row0 + qtile * p.q_per_item);
+}
+
+template <int D, int RT>
+__device__ __forceinline__ void single_item(const AttnArgs &a, const AttnPhase &p, int item, int lane) {
+    // item -> (unit, kv head, split, q tile): the q tiles of one split are neighbours
+    const int set = quotient(item, p.by_items), qtile = item - set * p.items_per_unit;
+    const int rest = quotient(set, p.by_splits), split = set - rest * p.n_splits;
+    const int unit = quotient(rest, a.by_kv), kvh = rest - unit * a.n_kv;
+    walk_item<D, RT>(a, p, unit, kvh, split, qtile, lane, [&](const auto &o, const auto &mrun, const auto &lrun, const auto &limit, size_t first_tok) {
+        store_item<D, RT>(a, p, o, mrun, lrun, limit, item, first_tok, kvh, lane & 15, lane >> 4);
+    });
 }
 
 // One launch may cover two phases (decode: the shared-prompt phase followed by the private phase), so
@@ -468,6 +473,53 @@ __global__ __launch_bounds__(256, 3) void attn_decode_kernel(AttnArgs a, AttnPha
     }
 }
 
+// Decode over a short context: a workgroup per (sequence, kv head), whose wavefronts share the whole context out, prompt included, and
+// merge through LDS with the arithmetic of attn_merge_kernel.  The members of a group then read the prompt once each instead of once
+// together, but nothing goes through memory and the merge launch is gone (whole_context says where that pays).  Bound: a chain of
+// a quarter of the context's blocks.
+template <int D>
+__global__ __launch_bounds__(64 * kWholeWaves) void attn_whole_kernel(AttnArgs a, AttnPhase p) {
+    constexpr int DT = D / 16, WAVES = kWholeWaves;
+    __shared__ f32x4 s_o[WAVES][DT][64];             // [dims dt * 16 + 4 g of row c]
+    __shared__ float s_m[WAVES][16], s_l[WAVES][16];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int unit = quotient(blockIdx.x, a.by_kv), kvh = (int)blockIdx.x - unit * a.n_kv;
+    const int c = lane & 15, g = lane >> 4;
+    size_t tok = 0;
+    walk_item<D, 1>(a, p, unit, kvh, wave, 0, lane, [&](const auto &o, const auto &mrun, const auto &lrun, const auto &, size_t first_tok) {
+        tok = first_tok;
+        const float l = row_sum(lrun[0]);
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) s_o[wave][dt][lane] = o[dt][0];
+        if (g == 0) { s_m[wave][c] = mrun[0]; s_l[wave][c] = l; }
+    });
+    __syncthreads();
+    if (c >= a.n_rep) return;
+    float m[WAVES], l[WAVES], best = kNegBig, den = 0.f;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        m[w] = s_m[w][c];
+        l[w] = s_l[w][c];
+        best = fmaxf(best, l[w] > 0.f ? m[w] : kNegBig);
+    }
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        m[w] = l[w] > 0.f ? exp2f(m[w] - best) : 0.f;
+        den += l[w] * m[w];
+    }
+    const int col = (kvh * a.n_rep + c) * D + 4 * g;
+#pragma unroll
+    for (int dt = wave; dt < DT; dt += WAVES) {
+        f32x4 num = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) num += s_o[w][dt][lane] * m[w];
+        float r[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = den > 0.f ? num[e] / den : 0.f;
+        *(uint2 *)(a.direct_out + frag_offset((int)tok, col + dt * 16, a.out_mt_total)) = make_uint2(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]));
+    }
+}
+
 // One phase of the merge: partial result i of (query token, query head) lies in row base + i * step of the phase's items
 struct MergePhase {
     const int32_t *unit_row0, *row_unit;
@@ -572,6 +624,30 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(MergeArgs a) {
 }
 
 }  // namespace
+
+int launch_attention_whole(const AttnArgs &args, int n_seq, int ctx, hipStream_t stream) {
+    AttnArgs a = args;
+    if (n_seq <= 0) return SR_OK;
+    a.n_rep = a.n_q / a.n_kv;
+    const long long wgs = (long long)n_seq * a.n_kv;
+    if (a.n_rep > 16 || ctx < 1 || !a.direct_out || wgs > 0x7FFFFFFF) return SR_E_ARG;
+    a.by_kv = fast_div(a.n_kv);
+    a.inv_rep = 1.0f / (float)a.n_rep;
+    a.page_shift = 31 - __builtin_clz(a.page_tokens);
+    AttnPhase p{};
+    p.n_units = n_seq;
+    p.q_per_unit = p.q_per_item = p.items_per_unit = p.pt_row_stride = p.rt = 1;
+    p.t_end = ctx;
+    p.causal_pos0 = ctx - 1;
+    p.n_splits = kWholeWaves;
+    p.split_tokens = round_up(ceil_div(ctx, kWholeWaves), 32);     // the last wavefronts may have none
+    const dim3 grid((unsigned)wgs), block(64 * kWholeWaves);
+    if (a.d == 128) attn_whole_kernel<128><<<grid, block, 0, stream>>>(a, p);
+    else if (a.d == 64) attn_whole_kernel<64><<<grid, block, 0, stream>>>(a, p);
+    else return SR_E_ARG;
+    SR_HIP(hipGetLastError());
+    return SR_OK;
+}
 
 int launch_attention(const AttnArgs &args, const AttnPhase *phase_args, int n_phases, hipStream_t stream) {
     if (n_phases < 1 || n_phases > 2) return SR_E_ARG;

@@ -3,7 +3,8 @@
 // The same decoder with every activation, the stored keys and values and the attention probabilities in
 // fp32 and every contraction as plain fused multiply-adds -- no bf16 rounding of operands, no matrix
 // cores.  What is NOT different is everything that could hide an indexing mistake behind rounding noise:
-// the page tables and copy-on-write, the (unit, kv head, split, query tile) decomposition of attention and
+// the page tables and copy-on-write, the (unit, kv head, split, query tile) decomposition of attention (that of
+// more sequences or longer contexts: see whole_context) and
 // its partial-result format and merge, the k-step ranges of the projections' K splits and the order in
 // which the consumers add the partial sums (where projections leave any: not in gemm_thin.hip), the packed weight layout (read here element by element),
 // token selection, gate and compaction.  Against an exact evaluation this path differs by single-precision

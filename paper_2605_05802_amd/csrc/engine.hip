@@ -482,7 +482,10 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
         part_rows += items * 16 * x.rt;
         ph[n_ph++] = x;
     };
-    if (p.decode) {
+    const bool whole = p.decode && !c->dbg && whole_context((long long)p.n_units * s.n_kv_heads, s.head_dim, ctx);
+    if (whole) {
+        // one launch and no partial results: no phases
+    } else if (p.decode) {
         if (c->shared_tokens > 0) {
             AttnPhase x{};
             x.n_units = c->n_live_groups;
@@ -562,7 +565,7 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
     }
     if (part_rows > c->part_rows_cap) return SR_E_NOMEM;
     // one partial result per query row: the attention kernel writes the merged output itself
-    const bool direct = n_ph == 1 && ph[0].n_splits == 1;
+    const bool direct = whole || (n_ph == 1 && ph[0].n_splits == 1);
     const bool dbg = c->dbg;
     const int qd = s.n_q_heads * s.head_dim;
     aa.direct_out = direct && !dbg ? (uint16_t *)c->attn_out : nullptr;
@@ -679,7 +682,7 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
             aa.kpool = qa.kpool;
             aa.vpool = qa.vpool;
             SR_TRY(timed(c, p.decode ? SR_KC_ATTN_DECODE : SR_KC_ATTN_PREFILL, st,
-                         [&] { return launch_attention(aa, ph, n_ph, st); }));
+                         [&] { return whole ? launch_attention_whole(aa, M, ctx, st) : launch_attention(aa, ph, n_ph, st); }));
         }
         if (!direct) {
             SR_TRY(timed(c, SR_KC_ATTN_MERGE, st, [&] {

@@ -260,4 +260,16 @@ inline int private_splits(long long waves1, long long shared_waves, int tokens, 
     return best;
 }
 
+// Decode attention over the whole context in one launch (attn_whole_kernel) instead of shared prompt and private context side by side
+// and a merge.  It saves 4 to 8 us a layer where its workgroups, one to a (sequence, kv head), are one round of the compute units,
+// and pays with every member reading the prompt for itself: even at 1000 to 1300 tokens of head size 128 and about twice that
+// of 64.  More workgroups keep the other kernel busy too (512: 1 to 3 % faster below 300 tokens, 4 % slower at 1000) and stay there.
+// Whole steps of two layers, us, two launches -> one: 4 and 2 kv heads of 64, 32 sequences, 272 tokens 54.4 -> 47.8, 688 61.7 -> 51.7, 1356
+// 60.9 -> 57.3, 2432 63.3 -> 65.2; 28 and 4 of 128, 8 sequences, 272 tokens 225 -> 215, 832 229.5 -> 226.6, 1356 230.4 -> 230.8; 64
+// sequences, 832 tokens 273 -> 268.  Eight wavefronts to a workgroup are never faster than four.
+constexpr int kWholeWaves = 4;
+inline bool whole_context(long long workgroups, int head_dim, int ctx) {
+    return workgroups <= 256 && (long long)ctx * head_dim <= 1024 * 128;
+}
+
 }  // namespace sr

@@ -295,7 +295,7 @@ struct AttnArgs {
     const int32_t *page_table;
     int pt_stride, page_tokens, n_q, n_kv, d;
     float scale;
-    // Non-null only when every query row gets exactly one partial result (one phase, one split): the attention
+    // Non-null only when every query row gets exactly one partial result (one phase, one split; or the whole context): the attention
     // kernel then normalises and writes the fragment-major bf16 output [query tokens][n_q*d] itself, with the
     // arithmetic of the merge, and no merge is launched.
     uint16_t *direct_out;
@@ -323,6 +323,10 @@ inline void set_shared_phase(AttnPhase *x, int shared_tokens, int n_kv, int max_
 }
 // One launch over one or two phases (same rt); phases whose token range is empty contribute no work.
 int launch_attention(const AttnArgs &a, const AttnPhase *phases, int n_phases, hipStream_t stream);
+
+// Decode of n_seq sequences with `ctx` tokens each, the one being decoded included: the whole context in one launch; a.direct_out is
+// required.
+int launch_attention_whole(const AttnArgs &a, int n_seq, int ctx, hipStream_t stream);
 
 // Merge the partial results of up to two phases into out (fragment-major bf16 [query tokens][n_q*d]) or, when
 // out32 is non-null (single-precision debugging path), into out32 (row-major fp32, same shape).

@@ -1088,3 +1088,36 @@ def test_wide_projections_of_up_to_16_rows_that_finish_in_their_own_kernel(plan,
     tol = tolerance(info["contract_max"])
     print(f"thin wide {rows}: worst |dlogit| = {worst:.3e}, bound {tol:.3e}, mismatches = {mism}, near ties = {near}")
     assert worst <= tol and all(g < gap_rule(tol) for g in info["mismatch_gaps"])
+
+
+@pytest.mark.parametrize("n_groups,G,n_q,n_kv,d,page,prompt", [
+    (1, 2, 4, 4, 64, 32, 1), (2, 3, 16, 1, 128, 64, 95), (3, 5, 6, 2, 64, 128, 200), (2, 8, 7, 1, 128, 32, 700), (40, 3, 8, 2, 64, 32, 129),
+])
+def test_short_contexts_in_one_launch(plan, n_groups, G, n_q, n_kv, d, page, prompt):
+    """1 to 16 query heads to a kv head; contexts of one block to 23, so that some of the four wavefronts have none, a part or several;
+    prompts that end inside a page; members that finish early."""
+    shape = synth.ModelShape(1, 96, n_q, n_kv, d, 208, 272)
+    cfg = synth.EpisodeConfig("whole", n_groups, G, prompt, 2, 3, 3, 16, (2,), 0.3, 0.4)
+    assert plan.whole_context(n_groups * G * n_kv, d, prompt + 12)
+    finish = (lambda K, r: K == 1 and r in (0, G + 1)) if n_groups == 3 else None
+    rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=85, page_tokens=page)
+    print(f"whole {n_groups}x{G} {n_q}/{n_kv}x{d} {prompt}: worst |dlogit| = {worst:.3e}, mismatches = {mism}, near ties = {near}")
+    assert worst <= LOGIT_TOL and mism == 0
+
+
+@pytest.mark.parametrize("n_q,n_kv,d,G,page,prompt,obs", [
+    (14, 2, 64, 5, 32, 2060, 17),      # three query tiles per group, an idle fourth
+    (7, 1, 128, 16, 64, 1100, 5),      # eight tiles per group, two workgroups of them
+    (12, 4, 128, 12, 128, 1030, 33),   # 128-token pages, four query heads' worth of padding rows
+    (4, 2, 64, 4, 32, 2050, 1),        # one query tile: not shared
+])
+def test_shared_prompts_beyond_the_contexts_of_one_launch(plan, n_q, n_kv, d, G, page, prompt, obs):
+    """Shared prompt and private context side by side and merged, in groups that lose members."""
+    shape = synth.ModelShape(1, 256, n_q, n_kv, d, 256, 512)
+    cfg = synth.EpisodeConfig("two-phase", 2, G, prompt, 2, obs, 2, 16, (), 0.3, 0.5)
+    assert not plan.whole_context(2 * G * n_kv, d, prompt + obs)
+    rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=32, page_tokens=page, sigma=0.05,
+                                                     finish_fn=lambda K, r: K == 1 and r in (0, G + 1, G + 2))
+    print(f"two phases {n_q}/{n_kv}x{d} G={G}: worst |dlogit| = {worst:.3e}, mismatches = {mism}, near ties = {near}")
+    assert stats["seqs_finished"] == 3
+    assert worst <= LOGIT_TOL and mism == 0

@@ -247,3 +247,9 @@ def test_thin_projections_where_they_come_out_ahead(plan):
     for M in (129, 200, 4000):
         for N in (16, 256, 3584):
             assert not plan.thin_qkv(M, N, 8) and not plan.thin_resid(M, N, 8)
+
+
+def test_whole_contexts_where_they_come_out_ahead(plan):
+    """Up to 1024 tokens of 128 dims and 2048 of 64, for one round of workgroups."""
+    assert plan.whole_context(256, 128, 1024) and plan.whole_context(64, 64, 2048) and plan.whole_context(1, 64, 1)
+    assert not plan.whole_context(256, 128, 1025) and not plan.whole_context(64, 64, 2049) and not plan.whole_context(257, 128, 32)
