@@ -170,6 +170,15 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a) {
 // instead of standing in front of its first MFMA.  With eight wavefronts (two per SIMD) there are 256 registers for
 // 4 * RT * NT accumulators and two sets of NT + RT fragments.
 //
+// MFMAs, LDS reads and copies are issued in the order in which they are written, a copy behind every second of the first MFMAs: a
+// copy takes half a dozen scalar instructions, and those of a whole k-step in front of its first MFMA, where both wavefronts of a SIMD
+// stand at the same time, kept the matrix pipes idle for 200 to 330 cycles a k-step.  For the same reason addresses are added up, not
+// multiplied out, and wavefronts with one copy less have a loop without branches of their own.  Cycles a k-step (of which MFMAs), before ->
+// now: {NT, RT} = {7, 4} 1218 -> 970 (896), {6, 4} 1096 -> 847 (768), {5, 4} 936 -> 750 (640), {4, 5} 952 -> 730 (640), {8, 4} 1245 -> 1140
+// (1024) in one round of workgroups, 1265 -> 1250 in eight.  The chip answers with a lower clock (1.9 -> 1.65 GHz), so that 8192 rows
+// of down take 830 -> 749 us, QKV 222 -> 196, O 165 -> 151; 296 rows of down 45.4 -> 40.7, 512 of gate|up 134 -> 117.  The MFMA is the
+// 16x16x32 form: 32x32x16 draws more power for the same product (the loop without copies 1.95 against 1.75 PFLOP/s).
+//
 // The tiles are numbered split by split, in panels of eight row blocks, column by column, and every XCD takes a contiguous eighth of
 // that order: the 32 workgroups that run together on one XCD form an 8 x 4 block of tiles (2048 rows x 128 * NT
 // features) whose operands they share through that XCD's L2, and no XCD has more than one tile above its share.
@@ -201,36 +210,23 @@ __global__ __launch_bounds__(kPfThreads) void gemm_prefill_kernel(GemmArgs a, in
     const int n_stages = ks1 - ks0;
 
     // copies of one k-step: tiles wave, wave + 8, ...
-    const bool full = TILES % 8 == 0 || wave + 8 * (COPIES - 1) < TILES;
-    const char *src[COPIES];
-    size_t step[COPIES];
+    const char *src[COPIES];               // of the next k-step to copy
+    unsigned step[COPIES];
 #pragma unroll
     for (int k = 0; k < COPIES; ++k) {
         const int tile = min(wave + 8 * k, TILES - 1);
         const bool is_w = tile < 2 * NT;
-        step[k] = is_w ? (size_t)1024 : (size_t)a.mt_total * 1024;
+        step[k] = is_w ? 1024u : (unsigned)a.mt_total * 1024u;
         src[k] = (is_w ? (const char *)a.W + (size_t)(nb * 2 * NT + tile) * a.ks_total * 1024
                        : (const char *)a.X + (size_t)(mb * 4 * RT + tile - 2 * NT) * 1024) + (size_t)ks0 * step[k];
     }
     const unsigned voff = lane * 16;
-    const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(__attribute__((address_space(3))) void *)pf_lds);
-    auto copy_stage = [&](int st, int buf) {         // past the end: a harmless re-read of the last k-step, never consumed
-        const int ks = min(st, n_stages - 1);
-        const unsigned base = lds0 + (unsigned)(buf * SV + wave * 64) * 16;
-#pragma unroll
-        for (int k = 0; k < COPIES; ++k)
-            if (k + 1 < COPIES || full) lds_dma16_uniform(src[k] + ks * step[k], voff, base + (unsigned)k * 8 * 1024);
-    };
-    // all LDS reads of this wavefront are done and at most `stages` k-steps of its copies are still on their way; then the
-    // barrier
-    auto wait_and_meet = [&](auto stages) __attribute__((always_inline)) {
-        constexpr int S = decltype(stages)::value;
-        static_assert(COPIES * 3 < 16, "the count's low four bits");
-        if (full) __builtin_amdgcn_s_waitcnt(0x0070 | (COPIES * S));
-        else __builtin_amdgcn_s_waitcnt(0x0070 | ((COPIES - 1) * S));
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
+    const unsigned lds0 =
+        __builtin_amdgcn_readfirstlane((unsigned)(size_t)(__attribute__((address_space(3))) void *)pf_lds) + wave * 1024;
+    // more: there is a k-step behind this one; else the next copy reads the last one again, and nothing consumes it
+    auto copy = [&](int k, int buf, bool more) __attribute__((always_inline)) {
+        lds_dma16_uniform(src[k], voff, lds0 + (unsigned)(buf * SV * 16 + k * 8 * 1024));
+        src[k] += more ? step[k] : 0u;
     };
 
     f32x4 up[RT];                           // see the SwiGLU epilogue
@@ -242,42 +238,55 @@ __global__ __launch_bounds__(kPfThreads) void gemm_prefill_kernel(GemmArgs a, in
 
     const int woff = wn * NT * 64 + lane, xoff = (2 * NT + wm * RT) * 64 + lane;
     bf16x8 wf[2][NT], xf[2][RT];           // [k-step parity]
-    auto read_frags = [&](int set, int buf) __attribute__((always_inline)) {
+    auto read_frag = [&](int f, int set, int buf) __attribute__((always_inline)) {
         const u32x4 *base = pf_lds + buf * SV;
-#pragma unroll
-        for (int j = 0; j < RT; ++j) xf[set][j] = __builtin_bit_cast(bf16x8, base[xoff + j * 64]);
-#pragma unroll
-        for (int i = 0; i < NT; ++i) wf[set][i] = __builtin_bit_cast(bf16x8, base[woff + i * 64]);
+        if (f < RT) xf[set][f] = __builtin_bit_cast(bf16x8, base[xoff + f * 64]);
+        else wf[set][f - RT] = __builtin_bit_cast(bf16x8, base[woff + (f - RT) * 64]);
     };
 
+    // C: this wavefront's copies per k-step
+    auto run = [&](auto copies) __attribute__((always_inline)) {
+        constexpr int C = decltype(copies)::value;
+        // all LDS reads of this wavefront are done and at most `stages` k-steps of its copies are still on their way; then the
+        // barrier
+        auto wait_and_meet = [&](auto stages) __attribute__((always_inline)) {
+            constexpr int S = decltype(stages)::value;
+            static_assert(C * S < 16, "the count's low four bits");
+            __builtin_amdgcn_s_waitcnt(0x0070 | (C * S));
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        };
 #pragma unroll
-    for (int i = 0; i < kPfBufs; ++i) copy_stage(i, i);
-    wait_and_meet(std::integral_constant<int, 3>{});
-    read_frags(0, 0);
-    for (int s0 = 0; s0 < n_stages; s0 += kPfBufs) {          // a split is a multiple of four k-steps
+        for (int i = 0; i < kPfBufs; ++i)
 #pragma unroll
-        for (int q = 0; q < kPfBufs; ++q) {
-            const int s = s0 + q, set = q & 1;
-            wait_and_meet(std::integral_constant<int, 2>{});      // k-step s + 1 has landed; k-step s is in everybody's registers
-            copy_stage(s + kPfBufs, q);              // into the buffer of k-step s
-            __builtin_amdgcn_sched_barrier(0);
-            read_frags(set ^ 1, (q + 1) % kPfBufs);
+            for (int k = 0; k < C; ++k) copy(k, i, i + 1 < n_stages);
+        wait_and_meet(std::integral_constant<int, 3>{});
 #pragma unroll
-            for (int i = 0; i < NT; ++i)
+        for (int f = 0; f < NT + RT; ++f) read_frag(f, 0, 0);
+        for (int s0 = 0; s0 < n_stages; s0 += kPfBufs) {          // a split is a multiple of four k-steps
 #pragma unroll
-                for (int j = 0; j < RT; ++j)
+            for (int q = 0; q < kPfBufs; ++q) {
+                const int s = s0 + q, set = q & 1;
+                wait_and_meet(std::integral_constant<int, 2>{});      // k-step s + 1 has landed; k-step s is in everybody's registers
+                const bool more = s + kPfBufs + 1 < n_stages;
+                constexpr int MFMAS = RT * NT, READS = NT + RT, PER = MFMAS >= 2 * READS ? 2 : 1;    // MFMAs per LDS read
+                static_assert(MFMAS >= PER * READS && MFMAS >= 2 * C, "everything fits between the MFMAs");
+#pragma unroll
+                for (int m = 0; m < MFMAS; ++m) {
+                    const int i = m / RT, j = m % RT;
+                    __builtin_amdgcn_sched_barrier(0);
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[set][i], xf[set][j], acc[i][j], 0, 0, 0);
-            constexpr int PER = RT * NT >= 2 * (NT + RT) ? 2 : 1;    // MFMAs between two LDS reads
-            static_assert(RT * NT >= NT + RT, "at least one");
-#pragma unroll
-            for (int f = 0; f < NT + RT; ++f) {
-                __builtin_amdgcn_sched_group_barrier(0x008, PER, 0); // MFMAs
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // 1 LDS read
+                    if (m % PER == PER - 1 && m / PER < READS) read_frag(m / PER, set ^ 1, (q + 1) % kPfBufs);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (m % 2 && m / 2 < C) copy(m / 2, q, more);         // into the buffer of k-step s
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
-            __builtin_amdgcn_sched_group_barrier(0x008, RT * NT - PER * (NT + RT), 0);
-            __builtin_amdgcn_sched_barrier(0);
         }
-    }
+    };
+    if (TILES % 8 == 0 || wave + 8 * (COPIES - 1) < TILES) run(std::integral_constant<int, COPIES>{});
+    else run(std::integral_constant<int, COPIES - 1>{});
     __builtin_amdgcn_s_waitcnt(0x0070);              // the copies past the end have landed before LDS goes away
 
     const int c = lane & 15, g = lane >> 4;
