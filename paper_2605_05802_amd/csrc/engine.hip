@@ -399,14 +399,13 @@ struct Pass {
     int score_chunk_len, score_unit0;
 };
 
-// K splits of a projection whose partial sums go to c->partials (the same choice on the normal and on the
-// single-precision debugging path)
-int choose_splits(sr_ctx *c, int M, const PackedMat &W, int ld_out, int *splits, size_t *split_stride) {
-    *split_stride = (size_t)round_up(M, 128) * ld_out;
-    *splits = projection_splits(M, W.N, W.ks, c->mt_total);
-    if (M > 128)                                     // larger batches may split only as far as the buffer allows
-        while (*splits > 1 && *split_stride * *splits > c->partial_elems) --*splits;
-    if (*split_stride * *splits > c->partial_elems) return SR_E_ARG;
+// Kernel and K splits of a projection, the same splits on the normal and on the single-precision debugging path.  split: the partial
+// sums go to c->partials, as many as it holds.
+int plan_one(sr_ctx *c, int M, const PackedMat &W, bool swiglu, bool split, int ld_out, ProjectionPlan *p, size_t *split_stride) {
+    *split_stride = split ? (size_t)round_up(M, 128) * ld_out : 0;
+    const size_t room = split ? c->partial_elems / *split_stride : 1;
+    if (room < 1) return SR_E_ARG;
+    *p = plan_projection(M, W.N, W.ks, c->mt_total, swiglu, room < kMaxSplitK ? (int)room : kMaxSplitK);
     return SR_OK;
 }
 
@@ -422,12 +421,14 @@ int gemm(sr_ctx *c, const uint4 *X, const PackedMat &W, int M, GemmEpilogue epi,
     a.ks_total = W.ks;
     a.out = out;
     a.ld_out = ld_out;
-    a.splits = 1;
-    a.wide = stream_waves(M, W.N, W.ks, epi == EPI_SWIGLU);
-    if (epi == EPI_F32 && splits_out) {
-        SR_TRY(choose_splits(c, M, W, ld_out, &a.splits, &a.split_stride));
-        *splits_out = a.splits;
-    }
+    ProjectionPlan p;
+    SR_TRY(plan_one(c, M, W, epi == EPI_SWIGLU, epi == EPI_F32 && splits_out, ld_out, &p, &a.split_stride));
+    a.wide = p.wide;
+    a.nt = p.nt;
+    a.rt = p.rt;
+    a.splits = p.splits;
+    a.split_steps = split_steps(M, W.N, W.ks, c->mt_total, a.splits);
+    if (splits_out) *splits_out = a.splits;
     return launch_gemm(a, epi, st);
 }
 
@@ -443,11 +444,10 @@ int gemm32(sr_ctx *c, const float *X, int K, const PackedMat &W, int M, GemmEpil
     a.ks_total = W.ks;
     a.out = out;
     a.ld_out = ld_out;
-    a.splits = 1;
-    if (epi == EPI_F32 && splits_out) {
-        SR_TRY(choose_splits(c, M, W, ld_out, &a.splits, &a.split_stride));
-        *splits_out = a.splits;
-    }
+    ProjectionPlan p;
+    SR_TRY(plan_one(c, M, W, epi == EPI_SWIGLU, epi == EPI_F32 && splits_out, ld_out, &p, &a.split_stride));
+    a.splits = p.splits;
+    if (splits_out) *splits_out = a.splits;
     a.split_steps = split_steps(M, W.N, W.ks, c->mt_total, a.splits);
     return launch_dbg_gemm(a, epi, st);
 }
@@ -767,6 +767,7 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
             ga.mt_total = c->mt_total;
             ga.ks_total = c->lm.ks;
             ga.splits = 1;
+            ga.split_steps = kPF;
             ga.score = c->score;
             ga.score.target = c->score_target;
             ga.score.lse_ld = round_up(M, 256);

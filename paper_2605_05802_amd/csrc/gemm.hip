@@ -1,6 +1,6 @@
 // Projection GEMMs  Y[M][N] = X[M][K] * W[N][K]^T  on the bf16 matrix cores, for more than 256 rows (up to there the
 // weight stream bounds all but small matrices: gemm_stream.hip).  W and X are stored pre-tiled in MFMA operand order.  Three
-// kernels, chosen per launch by measured cost (plan_gemm in plan.h): 128 x 128 tiles, tiles of 256 to 384 rows x 64 to 256
+// kernels, chosen per launch by measured cost (plan_projection in plan.h): 128 x 128 tiles, tiles of 128 to 384 rows x 64 to 256
 // features, and all rows of a batch of a few hundred in one workgroup of 160 features.
 #include <type_traits>
 
@@ -159,7 +159,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_kernel(GemmArgs a) {
 // ---------------------------------------------------------------------------------------------
 // Kernel for more than 256 rows: compute bound, so the tile is sized for the matrix cores.
 //
-// A workgroup owns 64 * RT rows x 32 * NT features and one split of K (see plan_gemm for which).  Eight wavefronts in a
+// A workgroup owns 64 * RT rows x 32 * NT features and one split of K (see plan_projection for which).  Eight wavefronts in a
 // 2 x 4 arrangement each take 16 * NT features x 16 * RT rows with 16x16x32 MFMAs; both operands reach them
 // through LDS, so every byte crosses the vector-memory path once per workgroup.  Each wavefront copies its share of a
 // k-step from global memory straight into LDS (direct-to-LDS loads issued from inline assembly and waited for by hand),
@@ -206,7 +206,7 @@ __global__ __launch_bounds__(kPfThreads) void gemm_prefill_kernel(GemmArgs a, in
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave & 1, wm = wave >> 1;
     int ks0, ks1;
-    split_range(a.ks_total, kPfBufs, a.splits, sp, &ks0, &ks1);
+    split_range(a.ks_total, a.split_steps, a.splits, sp, &ks0, &ks1);
     const int n_stages = ks1 - ks0;
 
     // copies of one k-step: tiles wave, wave + 8, ...
@@ -725,7 +725,9 @@ int launch_tiles(const GemmArgs &a, hipStream_t stream) {
     SR_HIP(hipFuncSetAttribute((const void *)gemm_prefill_kernel<EPI, NT, RT>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                pf_lds_bytes(NT, RT)));
     const int mb = ceil_div(a.M, 64 * RT), nb = ceil_div(a.N, 32 * NT), per_xcd = ceil_div(mb * nb * a.splits, 8);
-    if (mb * 4 * RT > a.mt_total || a.splits > a.ks_total / kPfBufs || (EPI != EPI_F32 && a.splits != 1)) return SR_E_ARG;
+    if (mb * 4 * RT > a.mt_total || (a.split_steps != kPfBufs && a.split_steps != kPF) || a.splits > a.ks_total / a.split_steps ||
+        (EPI != EPI_F32 && a.splits != 1))
+        return SR_E_ARG;
     gemm_prefill_kernel<EPI, NT, RT><<<dim3((unsigned)(per_xcd * 8)), dim3(kPfThreads), pf_lds_bytes(NT, RT), stream>>>(a, mb, nb, per_xcd);
     SR_HIP(hipGetLastError());
     return SR_OK;
@@ -774,16 +776,22 @@ int launch_gemm(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream) {
     if (a.scale.squares) return SR_E_ARG;
     if (epi == EPI_LSE) return launch_tiles<EPI_LSE, 8, 4>(a, stream);
     if (epi == EPI_SWIGLU && a.splits != 1) return SR_E_ARG;
-    const GemmPlan plan = plan_gemm(a.M, a.N, a.ks_total, a.mt_total, epi == EPI_SWIGLU, a.splits, a.splits);
-    if (plan.kernel == KERNEL_128) return launch_tiles128(a, epi, stream);
-    if (plan.kernel == KERNEL_MID) return launch_mid(a, epi, stream);
-    const TileShape t = kTileShapes[plan.kernel];
-#define SR_TILE_CASE(E, NT, RT) if (epi == E && t.nt == NT && t.rt == RT) return launch_tiles<E, NT, RT>(a, stream);
-    SR_TILE_CASE(EPI_SWIGLU, 8, 4) SR_TILE_CASE(EPI_SWIGLU, 6, 4) SR_TILE_CASE(EPI_SWIGLU, 5, 4) SR_TILE_CASE(EPI_SWIGLU, 6, 5)
-    SR_TILE_CASE(EPI_F32, 8, 4) SR_TILE_CASE(EPI_F32, 7, 4) SR_TILE_CASE(EPI_F32, 6, 4) SR_TILE_CASE(EPI_F32, 5, 4)
-    SR_TILE_CASE(EPI_F32, 6, 5) SR_TILE_CASE(EPI_F32, 5, 5) SR_TILE_CASE(EPI_F32, 4, 5)
-    SR_TILE_CASE(EPI_F32, 4, 6)
-    SR_TILE_CASE(EPI_F32, 2, 4) SR_TILE_CASE(EPI_F32, 3, 4) SR_TILE_CASE(EPI_F32, 2, 5) SR_TILE_CASE(EPI_F32, 3, 5)
+    int nt = a.nt, rt = a.rt;
+    if (!nt) {
+        const GemmPlan plan = plan_gemm(a.M, a.N, a.ks_total, a.mt_total, epi == EPI_SWIGLU, a.splits, a.splits);
+        if (plan.kernel == KERNEL_128) return launch_tiles128(a, epi, stream);
+        if (plan.kernel == KERNEL_MID) return launch_mid(a, epi, stream);
+        nt = kTileShapes[plan.kernel].nt;
+        rt = kTileShapes[plan.kernel].rt;
+    }
+#define SR_TILE_F32(NT, RT) if (epi == EPI_F32 && nt == NT && rt == RT) return launch_tiles<EPI_F32, NT, RT>(a, stream);
+#define SR_TILE_SWIGLU(NT, RT) if (epi == EPI_SWIGLU && nt == NT && rt == RT) return launch_tiles<EPI_SWIGLU, NT, RT>(a, stream);
+    SR_TILE_SWIGLU(8, 4) SR_TILE_SWIGLU(7, 4) SR_TILE_SWIGLU(6, 4) SR_TILE_SWIGLU(5, 4) SR_TILE_SWIGLU(6, 5) SR_TILE_SWIGLU(5, 5)
+    SR_TILE_SWIGLU(8, 3) SR_TILE_SWIGLU(7, 3) SR_TILE_SWIGLU(5, 3)
+    SR_TILE_F32(8, 4) SR_TILE_F32(7, 4) SR_TILE_F32(6, 4) SR_TILE_F32(5, 4) SR_TILE_F32(4, 4) SR_TILE_F32(3, 4) SR_TILE_F32(2, 4)
+    SR_TILE_F32(6, 5) SR_TILE_F32(5, 5) SR_TILE_F32(4, 5) SR_TILE_F32(3, 5) SR_TILE_F32(2, 5) SR_TILE_F32(4, 6)
+    SR_TILE_F32(7, 3) SR_TILE_F32(5, 3) SR_TILE_F32(4, 3) SR_TILE_F32(3, 3)
+    SR_TILE_F32(8, 2) SR_TILE_F32(7, 2) SR_TILE_F32(6, 2) SR_TILE_F32(5, 2) SR_TILE_F32(4, 2)
     return SR_E_ARG;
 }
 

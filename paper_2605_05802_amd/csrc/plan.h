@@ -208,6 +208,58 @@ inline int projection_splits(int M, int N, int ks_total, int mt_total) {
     return M <= kStreamRows ? pick_splits(M, N, ks_total) : plan_gemm(M, N, ks_total, mt_total, false, 0, kMaxSplitK).splits;
 }
 
+// ---- which kernel a projection runs on and its K splits ----
+// wide: computing wavefronts of the streaming kernel; nt, rt: tiles of 32 nt features x 64 rt rows; neither: what plan_gemm says.
+struct ProjectionPlan { int wide, nt, rt, splits; };
+
+// From 96 k-steps (K = 3072) on tiles may also have 128 or 192 rows, and a batch of a few hundred rows then takes whole rounds of them;
+// up to 2048 rows, beyond which large tiles fill any number of rounds.  With K = 512 a launch is mostly its beginning and end, and a
+// matrix of a few hundred rows is all splits (512 rows, K = 8192: whole steps of 384 rows 213 us as plan_gemm has it, 217 this way).
+constexpr int kDeepSteps = 96, kDeepCols = 2048, kDeepRows = 2048;
+struct DeepShape { int nt, rt; bool f32, swiglu; };
+constexpr DeepShape kDeepShapes[] = {
+    {4, 2, true, false}, {5, 2, true, false}, {6, 2, true, false}, {7, 2, true, false}, {8, 2, true, false}, {3, 3, true, false},
+    {4, 3, true, false}, {5, 3, true, true}, {7, 3, true, true}, {8, 3, false, true}, {2, 4, true, false}, {3, 4, true, false},
+    {4, 4, true, false}, {5, 4, true, true}, {6, 4, true, true}, {7, 4, true, true}, {8, 4, true, true}, {2, 5, true, false},
+    {3, 5, true, false}, {4, 5, true, false}, {5, 5, true, true}, {6, 5, true, true}, {4, 6, true, false}};
+// us that 112 k-steps of such a tile take: matrix instructions, and the operands' way through L2 and LDS, where a row tile costs more
+// than a feature tile (its 64 rows are four 16-row tiles, the features' 32 two).  Fitted, with the constants below, to launches of
+// every shape and number of splits at 31 batches of 72 to 2048 rows of the 7B shape's projections and a 16 384-row LM head (8000
+// launches); {4, 3} 34.7 measured, {5, 4} 51.1, {8, 4} 72.1.  At the 19 of these above 256 rows its choice is within 0.3 % of the
+// fastest on average and 2.9 % at most, plan_gemm's within 4.6 % on average: at 576 rows gate|up 152 -> 125 us, QKV 36.0 -> 29.6, down 84.7 -> 76.6; at 384 the LM
+// head 63.5 -> 52.0 and down 65.4 -> 58.7; at 896 gate|up 221 -> 198, O 37.6 -> 33.6.  Whole decode steps of two layers: 336 rows 649 ->
+// 621 us, 384 671 -> 639, 416 763 -> 725, 576 917 -> 805, 640 935 -> 899, 768 1046 -> 970, 960 1328 -> 1225.
+// Up to 256 rows the streaming kernel keeps them: tiles take less time there in a loop of their own (down at 192 rows 41 -> 36 us), but
+// with activations that another kernel has just written, and a chip that then runs at a lower clock, whole steps of 72 to 192
+// rows were 3 to 8 % slower with down on tiles, of 176 to 224 rows 4 % with gate|up on them, and of 240 and 256 rows as fast.
+inline double deep_us(int nt, int rt) { return 1.22 * nt * rt + 1.97 * nt + 3.8 * rt + (rt == 2 ? 4.0 : 2.0); }
+
+// max_splits 1: nothing adds partial sums behind it.
+inline ProjectionPlan plan_projection(int M, int N, int ks_total, int mt_total, bool swiglu, int max_splits) {
+    ProjectionPlan p{stream_waves(M, N, ks_total, swiglu), 0, 0, 1};
+    if (max_splits > 1) p.splits = projection_splits(M, N, ks_total, mt_total);
+    if (p.splits > max_splits) p.splits = max_splits;
+    if (ks_total < kDeepSteps || N < kDeepCols || M <= kStreamRows || M > kDeepRows) return p;
+    const int units = ks_total / kPfBufs;
+    int most = (ks_total + 8) / 32;
+    if (most > max_splits) most = max_splits;
+    if (most > kMaxSplitK) most = kMaxSplitK;
+    double least = 0.0;
+    for (int S = 1; S <= most; ++S) {
+        const double partials = swiglu ? 0.0 : 1.5e-6 * S * M * N;        // written, and read by the kernel behind
+        if (least != 0.0 && partials >= least) break;
+        const double steps = ceil_div(units, S) * (kPfBufs / 112.0);
+        for (const DeepShape &t : kDeepShapes) {
+            const int mb = ceil_div(M, 64 * t.rt);
+            if (!(swiglu ? t.swiglu : t.f32) || mb * 4 * t.rt > mt_total) continue;
+            const int rounds = (mb * ceil_div(N, 32 * t.nt) * S + 255) >> 8;
+            const double us = partials + rounds * (1.2 + steps * deep_us(t.nt, t.rt));
+            if (least == 0.0 || us < least) { least = us; p = ProjectionPlan{0, t.nt, t.rt, S}; }
+        }
+    }
+    return p;
+}
+
 // Scoring through stored logits: rows of the LM head at a time.  All of them where it has at most 16 tiles of 256 x 256, too few for
 // the epilogue that reduces its rows (512 rows of 1024 columns: 23.5 us for the projection and 4.8 for the reduction behind
 // it; 8.9 and 4.4 with stored logits; the whole call with two layers at hidden 256 167 -> 147 us).

@@ -170,8 +170,10 @@ struct GemmArgs {
     int mt_total;        // row tiles in X (and in a fragment-major output)
     int ks_total;        // k-steps (K padded to 32) in X and W
     int splits;          // split-K factor (EPI_F32 only)
+    int split_steps;     // k-steps that the tile kernel deals out at a time (split_steps in plan.h)
     int wide;            // M <= 256 only: 2, 4, 5, 8 or 10 (M <= 128) = computing wavefronts per workgroup (32 features
                          // each) of the weight-streaming kernel; 0 = one of the tiled kernels
+    int nt, rt;          // tiles of 32 nt features x 64 rt rows; 0 = the kernel that plan_gemm names
     void *out;
     int ld_out;          // EPI_F32: row stride (elements); EPI_SWIGLU: k-steps*32 of the output matrix
     size_t split_stride; // EPI_F32: elements between consecutive splits

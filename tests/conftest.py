@@ -78,6 +78,11 @@ int thin_resid(int M, int N, int ks) { return sr::thin_resid(M, N, ks); }
 int thin_qkv(int M, int N, int ks) { return sr::thin_qkv(M, N, ks); }
 int padded_k_steps(int K) { return sr::padded_k_steps(K); }
 int projection_splits(int M, int N, int ks, int mt_total) { return sr::projection_splits(M, N, ks, mt_total); }
+int plan_projection(int M, int N, int ks, int mt_total, int swiglu, int max_splits, int *out) {
+    const sr::ProjectionPlan p = sr::plan_projection(M, N, ks, mt_total, swiglu, max_splits);
+    out[0] = p.nt; out[1] = p.rt; out[2] = p.splits;
+    return p.wide;
+}
 }
 """
 
@@ -102,5 +107,12 @@ def plan(tmp_path_factory):
             return f"tiles {lib.tile_nt(k)}x{lib.tile_rt(k)}"
         return "128" if k == -2 else "rows16" if M <= 384 else "rows32"
 
+    def projection(M, N, K, swiglu=False, max_splits=1):
+        """The final choice, (kernel, K splits): deep projections of a few hundred rows have tile shapes that the others have not."""
+        ks, out = lib.padded_k_steps(K), (ctypes.c_int * 3)()
+        lib.plan_projection(M, N, ks, 512, int(swiglu), max_splits, out)
+        return (f"tiles {out[0]}x{out[1]}" if out[0] else kernel(M, N, K, swiglu, out[2])), out[2]
+
     lib.kernel = kernel
+    lib.projection = projection
     return lib

@@ -1006,6 +1006,35 @@ def test_gate_up_on_tiles_with_an_odd_number_of_feature_tiles(plan):
     assert worst <= tol and all(g < gap_rule(tol) for g in info["mismatch_gaps"])
 
 
+@pytest.mark.parametrize("n_groups,ffn,vocab,gate_up,down,lm_head", [
+    (33, 4112, 2064, "5x3", "3x3", "4x2"),           # 264 rows
+    (49, 3088, 10256, "5x3", "5x2", "4x3"),          # 392
+    (73, 8208, 10256, "5x5", "6x2", "7x2"),          # 584
+    (65, 8208, 16400, "7x3", "5x3", "7x3"),          # 520
+    (81, 8208, 10256, "7x4", "5x3", "4x4"),          # 648
+    (97, 6160, 2064, "8x3", "8x2", "4x2"),           # 776
+])
+def test_tiles_of_deep_projections_by_name(plan, n_groups, ffn, vocab, gate_up, down, lm_head):
+    """Tiles of 128 and 192 rows, and the others that deep projections take besides: gate|up, down (split along K) and LM head of a decode
+    step at hidden 3072 on the tiles named here, with ragged last row and column blocks.
+
+    The bound is the general rule, 2 E_c, with the contract mode's largest distance E_c over one sequence in 24: the largest of n errors of
+    deviation s is about s sqrt(2 ln n), so that four sequences of 648 (4.6 s) would put 2 E_c 6 % below what it is over all.  A token
+    other than the exact one needs an exact top-2 gap below the sum of two logits' errors."""
+    rows = n_groups * 8
+    assert plan.projection(rows, 2 * ffn, 3072, swiglu=True)[0] == f"tiles {gate_up}"
+    name, splits = plan.projection(rows, 3072, ffn, max_splits=16)
+    assert name == f"tiles {down}" and splits > 1 and plan.projection(rows, vocab, 3072)[0] == f"tiles {lm_head}"
+    shape = synth.ModelShape(1, 3072, 2, 1, 64, ffn, vocab)
+    cfg = synth.EpisodeConfig("deep-tiles", n_groups, 8, 4, 1, 1, 1, 64, (), 0.3, 0.0)
+    info = {}
+    rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=75, page_tokens=32, kv_pool_bytes=1 << 28,
+                                                     contract_rows=list(range(0, rows, 24)), info=info)
+    tol = tolerance(info["contract_max"])
+    print(f"deep tiles {rows}: worst |dlogit| = {worst:.3e}, bound {tol:.3e}, mismatches = {mism}, near ties = {near}")
+    assert worst <= tol and all(g <= 2 * worst for g in info["mismatch_gaps"])
+
+
 @pytest.mark.parametrize("prompt,kernel", [(491, "tiles 3x4"), (599, "tiles 3x5")])
 def test_narrow_tiles_of_thousands_of_rows(plan, prompt, kernel):
     """2455 and 2995 prompt rows: the QKV projection of 2304 rows on tiles of 96 features, a ragged last row block."""

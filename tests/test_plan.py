@@ -253,3 +253,30 @@ def test_whole_contexts_where_they_come_out_ahead(plan):
     """Up to 1024 tokens of 128 dims and 2048 of 64, for one round of workgroups."""
     assert plan.whole_context(256, 128, 1024) and plan.whole_context(64, 64, 2048) and plan.whole_context(1, 64, 1)
     assert not plan.whole_context(256, 128, 1025) and not plan.whole_context(64, 64, 2049) and not plan.whole_context(257, 128, 32)
+
+
+@pytest.mark.parametrize("M,N,K,swiglu,kernel,splits", [
+    (296, 37888, 3584, True, "tiles 5x5", 1), (384, 37888, 3584, True, "tiles 5x3", 1), (512, 37888, 3584, True, "tiles 5x4", 1),
+    (576, 37888, 3584, True, "tiles 7x3", 1), (768, 37888, 3584, True, "tiles 7x4", 1), (896, 37888, 3584, True, "tiles 8x3", 1),
+    (2048, 37888, 3584, True, "tiles 8x4", 1), (296, 3584, 18944, False, "tiles 4x5", 9), (384, 3584, 18944, False, "tiles 7x3", 8),
+    (768, 3584, 18944, False, "tiles 7x3", 4), (384, 3584, 3584, False, "tiles 4x2", 3), (704, 3584, 3584, False, "tiles 4x3", 2),
+    (512, 4608, 3584, False, "tiles 5x2", 2), (640, 4608, 3584, False, "tiles 6x2", 2)])
+def test_deep_projections_of_a_few_hundred_rows(plan, M, N, K, swiglu, kernel, splits):
+    """Kernel and K splits within 2.9 % of the fastest of all shapes measured there, the partial sums' way included."""
+    assert plan.projection(M, N, K, swiglu, 1 if swiglu else 16) == (kernel, splits)
+
+
+def test_projections_without_tile_shapes_of_their_own(plan):
+    """Up to 256 and beyond 2048 rows, and below 3072 inputs, the choice is plan_gemm's and the streaming kernel's, splits included; never more
+    splits than asked for, nor a split of less than two groups of eight k-steps."""
+    for M in (1, 128, 256, 257, 600, 2048, 2049, 8192):
+        for N, K in ((3584, 3584), (3584, 18944), (4608, 3072), (2304, 512), (16384, 2048), (37888, 3584)):
+            ks = plan.padded_k_steps(K)
+            for most in (1, 2, 16):
+                name, splits = plan.projection(M, N, K, max_splits=most)
+                assert 1 <= splits <= most and (splits == 1 or ks // splits >= 8)
+                if not 256 < M <= 2048 or K < 3072:
+                    want = min(most, plan.projection_splits(M, N, ks, 512)) if most > 1 else 1
+                    assert (name, splits) == (plan.kernel(M, N, K, splits=want), want)
+                else:
+                    assert name.startswith("tiles")
