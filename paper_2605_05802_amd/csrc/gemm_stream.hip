@@ -33,11 +33,13 @@ __device__ __forceinline__ u32x4 load_w_stream(const u32x4 *p) { return __builti
 // never wait for an activation and keep no staging registers, and the loader's wait for its own
 // copies stalls nobody.
 //
-// The MFMA is the 32x32x16 form: with one workgroup per CU all wavefronts stall at the same
-// barriers, and a single wavefront keeps the matrix pipe far busier with 32x32 tiles than with
-// 16x16 ones.  Its operands (32 rows x 16 k) are assembled from the 16-row fragment layout by
-// addressing: lane (r = lane % 32, g = lane / 32) of k-half h takes the 16 bytes of row tile r / 16,
-// lane slot (r % 16) + 16 * (2h + g).
+// Two forms of the MFMA.  LEAN is 16x16x32, whose operands are 16-row tiles as they lie in memory; it draws less power for the same
+// product (2.12 against 1.88 PFLOP/s in a loop without memory), and from 65 rows on the chip's clock follows: whole steps of two
+// layers at the 7B width 348 -> 347 us at 128 rows, 386 -> 379 at 144, 430 -> 428 at 192, 471 -> 461 at 224, 512 -> 500 at 256 (on a warmer
+// card 359 -> 342, 398 -> 378, 446 -> 434, 485 -> 477, 528 -> 520), prefill of 8 x 17 tokens 838 -> 811; up to 64 rows no difference.  32x32x16 has half the instructions, and a launch of a few k-steps spends 0.2 to 0.3 us less on fetching them (hidden 256, 160
+// rows: a step 109.4 us, LEAN 111.4): short launches keep it (stream_lean).  Its operands (32 rows x 16 k) are assembled from the
+// 16-row fragment layout by addressing: lane (r = lane % 32, g = lane / 32) of k-half h takes the 16 bytes of row tile r / 16, lane slot
+// (r % 16) + 16 * (2h + g).
 //
 // MT32 = number of 32-row tiles computed (M <= 32 * MT32): smaller batches skip the idle rows'
 // copies, LDS reads and MFMAs.  Up to four tiles the fragments of a whole k-step are read ahead; five to eight
@@ -53,8 +55,8 @@ constexpr int st_x_bytes(int mt32) { return kStBufs * chunk_steps(mt32) * kstep_
 // ... and, where a norm is finished, a float for every computing thread behind them (RowScale)
 constexpr int st_lds_bytes(int mt32, int waves, bool scaled) { return st_x_bytes(mt32) + (scaled ? 256 * waves : 0); }
 
-// RING = k-steps of W each computing wavefront keeps in flight (2 KiB per k-step)
-template <int EPI, int WAVES, int MT32, int RING, bool SCALED>
+// RING = k-steps of W each computing wavefront keeps in flight (2 KiB per k-step); LEAN: the 16x16x32 MFMA
+template <int EPI, int WAVES, int MT32, int RING, bool SCALED, bool LEAN>
 __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(GemmArgs a) {
     extern __shared__ u32x4 lds_dyn[];     // [kStBufs][k-step in chunk][16-row tile][lane]
     constexpr int kKC = chunk_steps(MT32), kStepVec = kstep_vec(MT32), kChunkVec = kKC * kStepVec;
@@ -107,26 +109,41 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(GemmArgs 
     }
 
     const int nt32 = nb * WAVES + wave;             // this wavefront's 32 output features
-    const int r32 = lane & 31, g2 = lane >> 5;
-    const int sub = r32 >> 4;                       // which 16-row tile of the pair
-    const int slot0 = (r32 & 15) + 16 * g2;         // lane slot for k-half 0; k-half 1 is +32
-
     // The norm in front of this projection: its sums of squares are dealt out over the computing threads, requested before the first
     // weights and added up behind them.  (By the loader, in a few round trips before the first barrier, it cost 3.5 us at 8 rows.)
     RowSquares<64 * WAVES> squares;
     if constexpr (SCALED) squares.request(a.scale, a.M, tid);
 
-    f32x16 acc[MT32];
+    // LEAN: acc16[row tile][feature tile], lane (c, g) holds features 4g .. 4g+3 of row c.  Else acc32[32 rows], lane (r32 = row, g2)
+    // holds, in register v, feature 8 * (v / 4) + 4 * g2 + v % 4 of the wavefront's 32.
+    const int c = lane & 15, g = lane >> 4, r32 = lane & 31, g2 = lane >> 5;
+    f32x4 acc16[LEAN ? 2 * MT32 : 1][2];
+    f32x16 acc32[LEAN ? 1 : MT32];
 #pragma unroll
-    for (int i = 0; i < MT32; ++i)
+    for (auto &t : acc16)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
+        for (f32x4 &x : t) x = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (f32x16 &t : acc32)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) t[v] = 0.f;
 
     if (ks0 < ks1) {
-        const u32x4 *wp0 = (const u32x4 *)a.W + ((size_t)(nt32 * 2 + sub) * a.ks_total) * 64 + slot0;
-        const u32x4 *wp1 = wp0 + 32;
-        const int xoff = sub * 64 + slot0;          // + mt32 * 128 + h * 32 inside a k-step of a buffer
         constexpr int NF = 2 * MT32;                // X fragments per k-step
+        // The two W fragments of a k-step: LEAN the feature tiles, else the k-halves of both
+        const int sub = LEAN ? 0 : r32 >> 4, slot0 = LEAN ? lane : (r32 & 15) + 16 * g2;
+        const u32x4 *wp0 = (const u32x4 *)a.W + ((size_t)(nt32 * 2 + sub) * a.ks_total) * 64 + slot0;
+        const u32x4 *wp1 = wp0 + (LEAN ? (size_t)a.ks_total * 64 : 32);
+        // X fragment f: LEAN row tile f, else k-half f % 2 of rows 32 (f / 2) ..
+        const int xoff = sub * 64 + slot0;
+        auto x_at = [](int f) { return LEAN ? f * 64 : (f >> 1) * 128 + (f & 1) * 32; };
+        auto multiply = [&](int f, const bf16x8 &wa, const bf16x8 &wb, const bf16x8 &x) __attribute__((always_inline)) {
+            if constexpr (LEAN) {
+                acc16[f][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa, x, acc16[f][0], 0, 0, 0);
+                acc16[f][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wb, x, acc16[f][1], 0, 0, 0);
+            } else acc32[f >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f & 1 ? wb : wa, x, acc32[f >> 1], 0, 0, 0);
+        };
+        constexpr int PER = LEAN ? 2 : 1;           // MFMAs per X fragment
 
         u32x4 w0[RING], w1[RING];
 #pragma unroll
@@ -144,74 +161,41 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(GemmArgs 
                 const int kc0 = ks + q * kKC;
                 const u32x4 *xb = &lds_dyn[buf * kChunkVec + xoff];
                 buf = buf == kStBufs - 1 ? 0 : buf + 1;
-                if constexpr (MT32 <= 4) {
-                    bf16x8 xf[2][NF];                                // [parity][mt32 * 2 + k-half]
+                // STEPS parts of the chunk, each with NX fragments that are read while the part before it is multiplied: whole k-steps, or
+                // their halves (LEAN of the rows, else of k)
+                constexpr int HALVES = MT32 <= 4 ? 1 : 2, PARTS = HALVES * kKC, NX = NF / HALVES;
+                auto part = [](int p, int j) { return HALVES == 1 ? j : LEAN ? (p & 1) * MT32 + j : 2 * j + (p & 1); };      // its fragments
+                bf16x8 xf[2][NX];
 #pragma unroll
-                    for (int f = 0; f < NF; ++f)
-                        xf[0][f] = __builtin_bit_cast(bf16x8, xb[(f >> 1) * 128 + (f & 1) * 32]);
+                for (int j = 0; j < NX; ++j) xf[0][j] = __builtin_bit_cast(bf16x8, xb[x_at(part(0, j))]);
 #pragma unroll
-                    for (int kk = 0; kk < kKC; ++kk) {
-                        const int i = q * kKC + kk;
-                        __builtin_amdgcn_sched_barrier(0);
-                        const bf16x8 wa = __builtin_bit_cast(bf16x8, w0[i]);
-                        const bf16x8 wb = __builtin_bit_cast(bf16x8, w1[i]);
-                        if (kk + 1 < kKC) {
+                for (int p = 0; p < PARTS; ++p) {
+                    const int kk = p / HALVES, i = q * kKC + kk;
+                    __builtin_amdgcn_sched_barrier(0);
+                    const bf16x8 wa = __builtin_bit_cast(bf16x8, w0[i]), wb = __builtin_bit_cast(bf16x8, w1[i]);
+                    if (p + 1 < PARTS) {
 #pragma unroll
-                            for (int f = 0; f < NF; ++f)
-                                xf[(kk + 1) & 1][f] =
-                                    __builtin_bit_cast(bf16x8, xb[(kk + 1) * kStepVec + (f >> 1) * 128 + (f & 1) * 32]);
-                        }
-#pragma unroll
-                        for (int mt = 0; mt < MT32; ++mt) {
-                            acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, xf[kk & 1][mt * 2], acc[mt], 0, 0, 0);
-                            acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wb, xf[kk & 1][mt * 2 + 1], acc[mt], 0, 0, 0);
-                        }
-                        const int kn = min(kc0 + kk + RING, last);  // refill the slot just consumed
-                        w0[i] = load_w_stream(wp0 + (size_t)kn * 64);
-                        w1[i] = load_w_stream(wp1 + (size_t)kn * 64);
-                        if (kk + 1 < kKC) {
-#pragma unroll
-                            for (int f = 0; f < NF; ++f) {
-                                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // 1 MFMA
-                                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // 1 LDS read
-                            }
-                        } else {
-                            __builtin_amdgcn_sched_group_barrier(0x008, NF, 0);
-                        }
-                        __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);           // W refills
+                        for (int j = 0; j < NX; ++j)
+                            xf[(p + 1) & 1][j] = __builtin_bit_cast(bf16x8, xb[(p + 1) / HALVES * kStepVec + x_at(part(p + 1, j))]);
                     }
-                } else {
-                    bf16x8 xf[2][MT32];                              // [k-half parity][mt32]
 #pragma unroll
-                    for (int mt = 0; mt < MT32; ++mt) xf[0][mt] = __builtin_bit_cast(bf16x8, xb[mt * 128]);
+                    for (int j = 0; j < NX; ++j) multiply(part(p, j), wa, wb, xf[p & 1][j]);
+                    // refill the slots just consumed
+                    const int kn = min(kc0 + kk + RING, last);
+                    const bool done0 = HALVES == 1 || !LEAN ? p % HALVES == 0 : p % 2 == 1, done1 = p % HALVES == HALVES - 1;
+                    if (done0) w0[i] = load_w_stream(wp0 + (size_t)kn * 64);
+                    if (done1) w1[i] = load_w_stream(wp1 + (size_t)kn * 64);
+                    if (p + 1 < PARTS) {
 #pragma unroll
-                    for (int hh = 0; hh < 2 * kKC; ++hh) {           // k-step hh / 2, half hh % 2
-                        const int i = q * kKC + (hh >> 1);
-                        __builtin_amdgcn_sched_barrier(0);
-                        const bf16x8 wa = __builtin_bit_cast(bf16x8, (hh & 1) ? w1[i] : w0[i]);
-                        if (hh + 1 < 2 * kKC) {
-#pragma unroll
-                            for (int mt = 0; mt < MT32; ++mt)
-                                xf[(hh + 1) & 1][mt] =
-                                    __builtin_bit_cast(bf16x8, xb[((hh + 1) >> 1) * kStepVec + mt * 128 + ((hh + 1) & 1) * 32]);
+                        for (int j = 0; j < NX; ++j) {
+                            __builtin_amdgcn_sched_group_barrier(0x008, PER, 0); // MFMAs
+                            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // 1 LDS read
                         }
-#pragma unroll
-                        for (int mt = 0; mt < MT32; ++mt)
-                            acc[mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, xf[hh & 1][mt], acc[mt], 0, 0, 0);
-                        const int kn = min(kc0 + (hh >> 1) + RING, last);   // refill the slot half just consumed
-                        if (hh & 1) w1[i] = load_w_stream(wp1 + (size_t)kn * 64);
-                        else w0[i] = load_w_stream(wp0 + (size_t)kn * 64);
-                        if (hh + 1 < 2 * kKC) {
-#pragma unroll
-                            for (int f = 0; f < MT32; ++f) {
-                                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // 1 MFMA
-                                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // 1 LDS read
-                            }
-                        } else {
-                            __builtin_amdgcn_sched_group_barrier(0x008, MT32, 0);
-                        }
-                        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);           // W refill
+                    } else {
+                        __builtin_amdgcn_sched_group_barrier(0x008, PER * NX, 0);
                     }
+                    if (done0 && done1) __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);           // W refills
+                    else if (done0 || done1) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 __syncthreads();
@@ -219,49 +203,54 @@ __global__ __launch_bounds__(64 * (WAVES + 1)) void gemm_stream_kernel(GemmArgs 
         }
     }
 
-    // accumulator of row tile mt: lane (r32 = batch row within the tile, g2) holds, in register v,
-    // output feature 8 * (v / 4) + 4 * g2 + v % 4 of the wavefront's 32
     if constexpr (SCALED) {
+        // four (two) lanes have the same rows: each forms a quarter (half) of their factors
         const float *left = (const float *)lds_dyn + st_x_bytes(MT32) / 4;
+        constexpr int ROWS = LEAN ? 16 : 32, LANES = 64 / ROWS, TILES = 32 * MT32 / ROWS;
+        float mine[(TILES + LANES - 1) / LANES];
+        const int which = LEAN ? g : g2, row = LEAN ? c : r32;
 #pragma unroll
-        for (int mt = 0; mt < MT32; ++mt) acc[mt] *= squares.scale(a.scale, left, mt * 32 + r32);
+        for (int u = 0; u * LANES < TILES; ++u) mine[u] = squares.scale(a.scale, left, (LANES * u + which) * ROWS + row);
+#pragma unroll
+        for (int t = 0; t < TILES; ++t) {
+            const float f = __shfl(mine[t / LANES], t % LANES * ROWS + row);
+            if constexpr (LEAN) {
+                acc16[t][0] *= f;
+                acc16[t][1] *= f;
+            } else acc32[t] *= f;
+        }
     }
-    if constexpr (EPI == EPI_F32) {
-        float *out = (float *)a.out + (size_t)sp * a.split_stride;
+    // Four consecutive features from n on of row m; of SwiGLU's 32, 0 .. 15 are gate and 16 .. 31 the matching up features.
+    auto store = [&](int m, int n, const f32x4 &v) __attribute__((always_inline)) {
+        if (n < a.N) *(f32x4 *)((float *)a.out + (size_t)sp * a.split_stride + (size_t)m * a.ld_out + n) = v;
+    };
+    auto store_swiglu = [&](int m, int f, const f32x4 &gate, const f32x4 &up) __attribute__((always_inline)) {
+        if (f >= a.ld_out) return;
+        float r[4];
 #pragma unroll
-        for (int mt = 0; mt < MT32; ++mt) {
-            const int m = mt * 32 + r32;
-            if (m < a.M) {
+        for (int e = 0; e < 4; ++e) r[e] = gate[e] / (1.0f + __expf(-gate[e])) * up[e];
+        *(uint2 *)((uint16_t *)a.out + frag_offset(m, f, a.mt_total)) = make_uint2(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]));
+    };
+    if constexpr (LEAN) {
 #pragma unroll
-                for (int vq = 0; vq < 4; ++vq) {
-                    const int n = nt32 * 32 + 8 * vq + 4 * g2;
-                    if (n < a.N)
-                        *(f32x4 *)(out + (size_t)m * a.ld_out + n) =
-                            f32x4{acc[mt][4 * vq], acc[mt][4 * vq + 1], acc[mt][4 * vq + 2], acc[mt][4 * vq + 3]};
-                }
-            }
+        for (int t = 0; t < 2 * MT32; ++t) {
+            const int m = t * 16 + c;
+            if (m >= a.M) continue;
+            if constexpr (EPI == EPI_F32) {
+                store(m, nt32 * 32 + 4 * g, acc16[t][0]);
+                store(m, nt32 * 32 + 16 + 4 * g, acc16[t][1]);
+            } else store_swiglu(m, nt32 * 16 + 4 * g, acc16[t][0], acc16[t][1]);
         }
     } else {
-        // packed rows 0..15 of the 32 are gate features, 16..31 the matching up features
-        uint16_t *out = (uint16_t *)a.out;
 #pragma unroll
         for (int mt = 0; mt < MT32; ++mt) {
             const int m = mt * 32 + r32;
-            if (m < a.M) {
+            if (m >= a.M) continue;
+            auto four = [&](int vq) { return f32x4{acc32[mt][4 * vq], acc32[mt][4 * vq + 1], acc32[mt][4 * vq + 2], acc32[mt][4 * vq + 3]}; };
 #pragma unroll
-                for (int vq = 0; vq < 2; ++vq) {
-                    const int f = nt32 * 16 + 8 * vq + 4 * g2;
-                    if (f < a.ld_out) {
-                        float r[4];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const float gt = acc[mt][4 * vq + e];
-                            r[e] = gt / (1.0f + __expf(-gt)) * acc[mt][4 * (vq + 2) + e];
-                        }
-                        uint2 v = make_uint2(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]));
-                        *(uint2 *)(out + frag_offset(m, f, a.mt_total)) = v;
-                    }
-                }
+            for (int vq = 0; vq < (EPI == EPI_F32 ? 4 : 2); ++vq) {
+                if constexpr (EPI == EPI_F32) store(m, nt32 * 32 + 8 * vq + 4 * g2, four(vq));
+                else store_swiglu(m, nt32 * 16 + 8 * vq + 4 * g2, four(vq), four(vq + 2));
             }
         }
     }
@@ -277,22 +266,28 @@ int launch_gemm_stream(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream) 
     const int mt32 = ceil_div(a.M, 32);
     hipError_t attr = hipSuccess;
     const bool scaled = a.scale.squares != nullptr;
-#define SR_STREAM_CASE(E, W, T, S)                                                                         \
-    (attr = hipFuncSetAttribute((const void *)gemm_stream_kernel<E, W, T, kRing, S>,                       \
+    const bool lean = stream_lean(a.M, a.ks_total, epi == EPI_F32 ? a.splits : 1);
+#define SR_STREAM_CASE(E, W, T, S, L)                                                                      \
+    (attr = hipFuncSetAttribute((const void *)gemm_stream_kernel<E, W, T, kRing, S, L>,                    \
                         hipFuncAttributeMaxDynamicSharedMemorySize, st_lds_bytes(T, W, S)),                \
-     gemm_stream_kernel<E, W, T, kRing, S><<<sgrid, lblock, st_lds_bytes(T, W, S), stream>>>(a))
-#define SR_STREAM_SCALED(E, W, T) (scaled ? SR_STREAM_CASE(E, W, T, true) : SR_STREAM_CASE(E, W, T, false))
-    // nine and eleven wavefronts put three on one SIMD: 168 registers, too few for more than four row tiles
-#define SR_STREAM_MT4(E, W)                                                                                \
-    (mt32 == 1 ? SR_STREAM_SCALED(E, W, 1) : mt32 == 2 ? SR_STREAM_SCALED(E, W, 2)                         \
-     : mt32 == 3 ? SR_STREAM_SCALED(E, W, 3) : SR_STREAM_SCALED(E, W, 4))
+     gemm_stream_kernel<E, W, T, kRing, S, L><<<sgrid, lblock, st_lds_bytes(T, W, S), stream>>>(a))
+#define SR_STREAM_SCALED(E, W, T, L) (scaled ? SR_STREAM_CASE(E, W, T, true, L) : SR_STREAM_CASE(E, W, T, false, L))
+#define SR_STREAM_TALL(E, W, T) (lean ? SR_STREAM_CASE(E, W, T, false, true) : SR_STREAM_CASE(E, W, T, false, false))
+    // from 65 rows on a norm is finished in front of short inner dimensions only (plan.h, thin_qkv)
+#define SR_STREAM_LEAN(E, W, T) (scaled ? SR_STREAM_CASE(E, W, T, true, false) : SR_STREAM_TALL(E, W, T))
+    // nine and eleven wavefronts put three on one SIMD: 168 registers, too few for more than four row tiles, and for four without LEAN
+#define SR_STREAM_MT4(E, W, LEAN)                                                                          \
+    (mt32 == 1 ? SR_STREAM_SCALED(E, W, 1, false) : mt32 == 2 ? SR_STREAM_SCALED(E, W, 2, false)           \
+     : mt32 == 3 ? LEAN(E, W, 3) : LEAN(E, W, 4))
+#define SR_STREAM_ALWAYS(E, W, T) SR_STREAM_SCALED(E, W, T, true)
 #define SR_STREAM_MT(E, W)                                                                                 \
-    (mt32 <= 4 ? SR_STREAM_MT4(E, W)                                                                       \
-     : mt32 == 5 ? SR_STREAM_CASE(E, W, 5, false) : mt32 == 6 ? SR_STREAM_CASE(E, W, 6, false)             \
-     : mt32 == 7 ? SR_STREAM_CASE(E, W, 7, false) : SR_STREAM_CASE(E, W, 8, false))
+    (mt32 <= 4 ? SR_STREAM_MT4(E, W, SR_STREAM_LEAN)                                                       \
+     : mt32 == 5 ? SR_STREAM_TALL(E, W, 5) : mt32 == 6 ? SR_STREAM_TALL(E, W, 6)                           \
+     : mt32 == 7 ? SR_STREAM_TALL(E, W, 7) : SR_STREAM_TALL(E, W, 8))
 #define SR_STREAM_W(E)                                                                                     \
     (a.wide == 2 ? SR_STREAM_MT(E, 2) : a.wide == 4 ? SR_STREAM_MT(E, 4)                                   \
-     : a.wide == 5 ? SR_STREAM_MT(E, 5) : a.wide == 8 ? SR_STREAM_MT4(E, 8) : SR_STREAM_MT4(E, 10))
+     : a.wide == 5 ? SR_STREAM_MT(E, 5)                                                                    \
+     : a.wide == 8 ? SR_STREAM_MT4(E, 8, SR_STREAM_ALWAYS) : SR_STREAM_MT4(E, 10, SR_STREAM_ALWAYS))
     if (mt32 > 4 && (a.wide >= 8 || scaled)) return SR_E_ARG;
     if (scaled && (a.scale.ld % 4 || a.splits != 1)) return SR_E_ARG;
     if (epi == EPI_F32) SR_STREAM_W(EPI_F32); else SR_STREAM_W(EPI_SWIGLU);

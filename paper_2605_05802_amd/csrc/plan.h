@@ -90,6 +90,9 @@ inline int stream_waves(int M, int N, int ks_total, bool swiglu) {
     return best;
 }
 
+// The streaming kernel's MFMA of less power, from 65 rows and 24 k-steps of a split on (gemm_stream.hip)
+inline bool stream_lean(int M, int ks_total, int splits) { return M > 64 && ks_total / splits >= 24; }
+
 // K splits up to kStreamRows rows, whichever kernel it is
 inline int pick_splits(int M, int N, int ks_total) {
     const int n_blocks = ceil_div(N, 32 * stream_waves(M < kStreamThinRows ? M : kStreamThinRows, N, ks_total, false));

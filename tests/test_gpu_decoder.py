@@ -1078,6 +1078,21 @@ def test_weight_streaming_widths_by_name(plan, n_groups, G, ffn, vocab, gate_up,
     assert worst <= LOGIT_TOL and mism == 0
 
 
+@pytest.mark.parametrize("n_groups,ffn,gate_up", [(9, 8208, 4), (12, 20464, 5), (16, 2064, 2), (17, 20464, 5), (24, 8208, 4), (28, 8208, 4),
+                                                  (32, 20464, 5)])
+def test_weight_streaming_with_the_mfma_of_less_power(plan, n_groups, ffn, gate_up):
+    """Three to eight 32-row tiles at 24 k-steps and more: gate|up at every width and the LM head (beyond 128 rows QKV and O too, and down where
+    its splits are long enough), ragged last rows and columns."""
+    rows = n_groups * 8
+    assert plan.kernel(rows, 2 * ffn, 768, swiglu=True) == f"stream {gate_up}" and plan.kernel(rows, 16400, 768) == "stream 4"
+    assert plan.stream_lean(rows, 24, 1) and not plan.stream_lean(rows, 16, 1) and not plan.stream_lean(64, 24, 1)
+    shape = synth.ModelShape(1, 768, 4, 2, 64, ffn, 16400)
+    cfg = synth.EpisodeConfig("lean", n_groups, 8, 4, 1, 1, 1, 64, (), 0.3, 0.0)
+    rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=83, page_tokens=32, kv_pool_bytes=1 << 28)
+    print(f"lean {rows} rows, {ffn}: worst |dlogit| = {worst:.3e}, mismatches = {mism}, near ties = {near}")
+    assert worst <= LOGIT_TOL and mism == 0
+
+
 @pytest.mark.parametrize("n_groups", [5, 25, 41])
 @pytest.mark.parametrize("hidden,q_heads,ffn", [(256, 12, 1296), (768, 28, 272)])
 def test_inner_dimensions_of_an_odd_number_of_groups(n_groups, hidden, q_heads, ffn):
