@@ -54,16 +54,19 @@ struct StagingRing {
     bool busy[kSlots] = {};
     int next = 0, cur = 0;
 
-    int init(size_t bytes) {
+    // slots of `bytes` each: what they take of the context's pinned memory
+    size_t plan(size_t bytes) {
         slot_bytes = (bytes + 255) & ~(size_t)255;
-        SR_HIP(hipHostMalloc((void **)&base, slot_bytes * kSlots, hipHostMallocDefault));
+        return slot_bytes * kSlots;
+    }
+    int init(char *at) {
+        base = at;
         for (int i = 0; i < kSlots; ++i) SR_HIP(hipEventCreateWithFlags(&ev[i], hipEventDisableTiming));
         return SR_OK;
     }
     void destroy() {
         for (int i = 0; i < kSlots; ++i)
             if (ev[i]) (void)hipEventDestroy(ev[i]);
-        if (base) (void)hipHostFree(base);
         base = nullptr;
     }
     // the next slot, free to be written by the host
@@ -110,6 +113,7 @@ struct sr_ctx {
     std::vector<int> live_orig_group;
     std::vector<std::vector<int>> pages;       // per live sequence
     StagingRing pt_ring, rows_ring, units_ring, gate_ring, copies_ring;   // pinned staging of the uploads below
+    char *pinned = nullptr;                     // h_retire and the rings, one allocation: each one costs 30 us, and 11 to give back
     uint8_t *h_retire = nullptr;                // pinned [n_groups0]
     int32_t *h_rows = nullptr;                  // current slot of rows_ring: [n_seq0]
 
@@ -853,7 +857,7 @@ void sr_destroy(sr_ctx *c) {
     c->units_ring.destroy();
     c->gate_ring.destroy();
     c->copies_ring.destroy();
-    if (c->h_retire) (void)hipHostFree(c->h_retire);
+    if (c->pinned) (void)hipHostFree(c->pinned);
     for (auto &r : c->prof) { (void)hipEventDestroy(r.a); (void)hipEventDestroy(r.b); }
     for (hipEvent_t e : c->event_pool) (void)hipEventDestroy(e);
     delete c;
@@ -898,12 +902,22 @@ static int init_impl(sr_ctx *c) {
     c->end_step.assign(c->n_seq0, INT_MAX);
     c->fin_index.assign(c->n_seq0, -1);
     c->pages.assign(c->n_seq0, {});
-    SR_TRY(c->units_ring.init((size_t)(2 * c->n_groups0 + c->n_seq0) * 4 + 16));
-    SR_TRY(c->gate_ring.init((size_t)2 * c->n_seq0 * 4 + 16));
-    SR_TRY(c->copies_ring.init((size_t)c->n_seq0 * sizeof(int2) + 16));
-    SR_TRY(c->pt_ring.init((size_t)c->n_seq0 * c->max_pages * 4 + 16));
-    SR_TRY(c->rows_ring.init((size_t)c->n_seq0 * 4 + 16));
-    SR_HIP(hipHostMalloc((void **)&c->h_retire, c->n_groups0 + 16, hipHostMallocDefault));
+    const size_t n_seq0 = c->n_seq0;
+    const std::pair<StagingRing *, size_t> rings[] = {
+        {&c->units_ring, c->units_ring.plan((2 * (size_t)c->n_groups0 + n_seq0) * 4 + 16)},
+        {&c->gate_ring, c->gate_ring.plan(2 * n_seq0 * 4 + 16)},
+        {&c->copies_ring, c->copies_ring.plan(n_seq0 * sizeof(int2) + 16)},
+        {&c->pt_ring, c->pt_ring.plan(n_seq0 * c->max_pages * 4 + 16)},
+        {&c->rows_ring, c->rows_ring.plan(n_seq0 * 4 + 16)}};
+    size_t pinned_bytes = c->n_groups0 + 16;
+    for (const auto &r : rings) pinned_bytes += r.second;
+    SR_HIP(hipHostMalloc((void **)&c->pinned, pinned_bytes, hipHostMallocDefault));
+    char *at = c->pinned;
+    for (const auto &r : rings) {
+        SR_TRY(r.first->init(at));
+        at += r.second;
+    }
+    c->h_retire = (uint8_t *)at;
 
     // device buffers
     const size_t n_seq = c->n_seq0, n_grp = c->n_groups0, R = c->R, kv_elems = c->layer_stride * s.n_layers;
@@ -914,8 +928,7 @@ static int init_impl(sr_ctx *c) {
     if (dec_rows * n_max * kMaxSplitK > c->partial_elems) c->partial_elems = dec_rows * n_max * kMaxSplitK;
     c->part_rows_cap = 2 * R * s.n_q_heads + n_seq * s.n_kv_heads * 32 * (2 * kMaxAttnSplits + 1);
     AllocPlan plan;
-    plan.want(&c->rope_cos, rope_elems);
-    plan.want(&c->rope_sin, rope_elems);
+    plan.want(&c->rope_cos, 2 * rope_elems);
     if (c->dbg) {
         plan.want(&c->kpool32, kv_elems);
         plan.want(&c->vpool32, kv_elems);
@@ -979,20 +992,11 @@ static int init_impl(sr_ctx *c) {
         for (int i = 0; i < c->n_seq0; ++i) ids[i] = i;
         SR_HIP(hipMemcpy(c->d_orig[0], ids.data(), ids.size() * 4, hipMemcpyHostToDevice));
     }
-    // RoPE tables, computed in double: angle = pos * theta^(-2i/d)
-    {
-        const int half = d / 2;
-        std::vector<float> hc(rope_elems), hs(rope_elems);
-        for (int i = 0; i < half; ++i) {
-            const double inv_freq = pow((double)s.rope_theta, -2.0 * i / d);
-            for (int pos = 0; pos < o.max_seq_len; ++pos) {
-                hc[(size_t)pos * half + i] = (float)cos(pos * inv_freq);
-                hs[(size_t)pos * half + i] = (float)sin(pos * inv_freq);
-            }
-        }
-        SR_HIP(hipMemcpy(c->rope_cos, hc.data(), hc.size() * 4, hipMemcpyHostToDevice));
-        SR_HIP(hipMemcpy(c->rope_sin, hs.data(), hs.size() * 4, hipMemcpyHostToDevice));
-    }
+    // cosines, then sines
+    c->rope_sin = c->rope_cos + rope_elems;
+    std::vector<float> rope(2 * rope_elems);
+    rope_tables(o.max_seq_len, d, s.rope_theta, rope.data(), rope.data() + rope_elems);
+    SR_HIP(hipMemcpy(c->rope_cos, rope.data(), rope.size() * 4, hipMemcpyHostToDevice));
     SR_HIP(hipDeviceSynchronize());
     return SR_OK;
 }

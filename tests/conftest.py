@@ -76,6 +76,7 @@ int token_splits(int tokens, int want, int *each) { const sr::TokenSplits s = sr
 int whole_context(int workgroups, int head_dim, int ctx) { return sr::whole_context(workgroups, head_dim, ctx); }
 int thin_resid(int M, int N, int ks) { return sr::thin_resid(M, N, ks); }
 int thin_qkv(int M, int N, int ks) { return sr::thin_qkv(M, N, ks); }
+void rope_tables(int len, int d, double theta, float *c, float *s) { sr::rope_tables(len, d, theta, c, s); }
 int padded_k_steps(int K) { return sr::padded_k_steps(K); }
 int projection_splits(int M, int N, int ks, int mt_total) { return sr::projection_splits(M, N, ks, mt_total); }
 int stream_lean(int M, int ks, int splits) { return sr::stream_lean(M, ks, splits); }

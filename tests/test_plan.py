@@ -280,3 +280,18 @@ def test_projections_without_tile_shapes_of_their_own(plan):
                     assert (name, splits) == (plan.kernel(M, N, K, splits=want), want)
                 else:
                     assert name.startswith("tiles")
+
+
+@pytest.mark.parametrize("length,d,theta", [(1, 64, 1e6), (31, 128, 1e6), (32, 64, 1e4), (33, 128, 1e4), (1208, 128, 1e6), (16389, 64, 5e5)])
+def test_rope_tables_by_sums_of_angles(plan, length, d, theta):
+    """Against a cosine and a sine for every entry: angles of up to `length` are rounded to 2^-53 of themselves on both sides and the sum adds
+    a few 2^-53, so entries agree but for those next to a rounding boundary of single precision, which may go either way."""
+    half = d // 2
+    got = np.empty((2, length, half), dtype=np.float32)
+    at = lambda x: x.ctypes.data_as(ctypes.POINTER(ctypes.c_float))
+    plan.rope_tables(length, d, ctypes.c_double(theta), at(got[0]), at(got[1]))
+    angle = np.arange(length)[:, None] * theta ** (-2.0 * np.arange(half) / d)
+    bound = 4 * (length + 4) * 2.0 ** -53
+    for table, exact in zip(got, (np.cos(angle), np.sin(angle))):
+        assert np.all(np.abs(table - exact) <= np.spacing(np.abs(exact).astype(np.float32)) / 2 + bound)
+        assert np.mean(table != exact.astype(np.float32)) < 1e-4
