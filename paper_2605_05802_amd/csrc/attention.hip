@@ -317,6 +317,12 @@ __global__ __launch_bounds__(256, RT == 1 ? 3 : 2) void attn_kernel(AttnArgs a, 
 // register (PageWindow): as a vector load behind the copies, whose wait drained them, they kept one block in flight
 // instead of two; scalar loads kept two, but their wait covers the LDS reads.  Prompts of 4096 (32 groups of 16) 120.8 -> 112.6 us
 // with the private contexts and the merge, of 1024 (16 groups of 8) 43.5 -> 42.2; no change in prefill.
+//
+// In LDS a 1 KiB tile of 16 rows lies as the MFMA's lanes take it, lane (c, g)'s 16 bytes at 16 (c + 16 g): the copy's source address
+// is what is permuted.  As the tile lies in the page, reads counted conflict cycles worth a quarter of the kernel's.  Four
+// fragments are on their way before the first MFMA of a product; the compiler had kept two and waited for both.  Prefill of 128 x 64
+// tokens 278 -> 270 us a launch (order of the page: 275), of 128 x 32 91 -> 87.  The vector unit is 82 % busy there: softmax
+// and the issue of MFMAs.
 // ---------------------------------------------------------------------------------------------
 constexpr int kShBufs = 3;
 
@@ -379,12 +385,23 @@ __device__ __forceinline__ void shared_tiles(const AttnArgs &a, const AttnPhase 
     auto copy = [&](int blk, int buf) __attribute__((always_inline)) {      // past the end: a harmless re-read of the last block
         const int t0 = t_lo + 32 * min(blk, n_blocks - 1), page = pages.page(t0);
         const int in_page = (t0 & (a.page_tokens - 1)) >> 5;
-        const size_t base = ((((size_t)page * a.n_kv + kvh) << (page_shift - 5)) + in_page) * SLOTS + wave * (SEGS * 64) + lane;
+        const size_t base = ((((size_t)page * a.n_kv + kvh) << (page_shift - 5)) + in_page) * SLOTS + wave * (SEGS * 64) + c * 4 + g;
         const unsigned dst = lds0 + (unsigned)(buf * 2 * SLOTS + wave * (SEGS * 64)) * 16;
 #pragma unroll
         for (int i = 0; i < SEGS; ++i) lds_dma16((const u32x4 *)a.kpool + base + i * 64, dst + i * 1024);
 #pragma unroll
         for (int i = 0; i < SEGS; ++i) lds_dma16((const u32x4 *)a.vpool + base + i * 64, dst + (SLOTS + i * 64) * 16);
+    };
+
+    // N fragments from LDS, each for RT MFMAs: four are requested before the first MFMA, the others as their registers become free
+    auto reads_ahead = [](auto n) __attribute__((always_inline)) {
+        constexpr int N = decltype(n)::value, AHEAD = 4;
+        __builtin_amdgcn_sched_group_barrier(0x100, AHEAD, 0);         // LDS reads
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, RT, 0);        // MFMAs
+            if (i + AHEAD < N) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
     };
 
     if (n_blocks > 0) {
@@ -404,6 +421,7 @@ __device__ __forceinline__ void shared_tiles(const AttnArgs &a, const AttnPhase 
             buf = buf == kShBufs - 1 ? 0 : buf + 1;
             if (t0 >= t_hi) continue;               // uniform per wavefront: invisible to all its rows
             f32x4 s[RT][2];
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
@@ -413,11 +431,13 @@ __device__ __forceinline__ void shared_tiles(const AttnArgs &a, const AttnPhase 
             for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
                 for (int tt = 0; tt < 2; ++tt) {
-                    const bf16x8 kf = __builtin_bit_cast(bf16x8, kb[(ks * 32 + tt * 16 + c) * 4 + g]);
+                    const bf16x8 kf = __builtin_bit_cast(bf16x8, kb[(ks * 2 + tt) * 64 + lane]);
 #pragma unroll
                     for (int rt = 0; rt < RT; ++rt)
                         s[rt][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[rt][ks], s[rt][tt], 0, 0, 0);
                 }
+            reads_ahead(std::integral_constant<int, 2 * KS>{});
+            __builtin_amdgcn_sched_barrier(0);
             bf16x8 pf[RT];
             float alpha[RT];
             if (t0 + 32 <= t_vis) {
@@ -441,11 +461,13 @@ __device__ __forceinline__ void shared_tiles(const AttnArgs &a, const AttnPhase 
             }
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt) {
-                const bf16x8 vf = __builtin_bit_cast(bf16x8, vb[(dt * 16 + c) * 4 + g]);
+                const bf16x8 vf = __builtin_bit_cast(bf16x8, vb[dt * 64 + lane]);
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt)
                     o[dt][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[rt], o[dt][rt], 0, 0, 0);
             }
+            reads_ahead(std::integral_constant<int, DT>{});
+            __builtin_amdgcn_sched_barrier(0);
         }
         __builtin_amdgcn_s_waitcnt(0x0F70);        // the copies past the end have landed before LDS goes away
     }
