@@ -431,7 +431,7 @@ int gemm(sr_ctx *c, const uint4 *X, const PackedMat &W, int M, GemmEpilogue epi,
     a.nt = p.nt;
     a.rt = p.rt;
     a.splits = p.splits;
-    a.split_steps = split_steps(M, W.N, W.ks, c->mt_total, a.splits);
+    a.split_steps = p.steps;
     if (splits_out) *splits_out = a.splits;
     return launch_gemm(a, epi, st);
 }
@@ -451,8 +451,8 @@ int gemm32(sr_ctx *c, const float *X, int K, const PackedMat &W, int M, GemmEpil
     ProjectionPlan p;
     SR_TRY(plan_one(c, M, W, epi == EPI_SWIGLU, epi == EPI_F32 && splits_out, ld_out, &p, &a.split_stride));
     a.splits = p.splits;
+    a.split_steps = p.steps;
     if (splits_out) *splits_out = a.splits;
-    a.split_steps = split_steps(M, W.N, W.ks, c->mt_total, a.splits);
     return launch_dbg_gemm(a, epi, st);
 }
 

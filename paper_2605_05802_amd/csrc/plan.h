@@ -52,8 +52,8 @@ SR_HD inline void split_range(int ks_total, int unit, int splits, int sp, int *k
 }
 
 constexpr int kMaxSplitK = 16;
-// k-steps that a kernel's splits cover a multiple of: kPfBufs (its LDS buffers) where tiles of kTileShapes run, kPF (the
-// k-steps of W it holds in registers) in the other kernels
+// k-steps that a kernel's splits cover a multiple of: kPfBufs (its LDS buffers) where tiles of 32 nt features x 64 rt rows run, kPF
+// (the k-steps of W it holds in registers) in the other kernels
 constexpr int kPfBufs = 4, kPF = 8;
 // k-steps of 32 that hold K, the projections' inner dimension, padded with zeros to whole groups of kPF, which is what every kernel
 // consumes at a time.  (Padded to twice that, the model with hidden size 256 multiplied as many zeros as weights.)
@@ -203,7 +203,7 @@ inline GemmPlan plan_gemm(int M, int N, int ks_total, int mt_total, bool swiglu,
     return best;
 }
 
-// What split_range deals out at a time in the kernel that a projection with these splits runs on
+// What split_range deals out at a time in the kernel that plan_gemm (or the streaming rule) names for a projection with these splits
 inline int split_steps(int M, int N, int ks_total, int mt_total, int splits) {
     if (splits == 1 || stream_waves(M, N, ks_total, false)) return kPF;
     return plan_gemm(M, N, ks_total, mt_total, false, splits, splits).kernel >= 0 ? kPfBufs : kPF;
@@ -215,7 +215,8 @@ inline int projection_splits(int M, int N, int ks_total, int mt_total) {
 
 // ---- which kernel a projection runs on and its K splits ----
 // wide: computing wavefronts of the streaming kernel; nt, rt: tiles of 32 nt features x 64 rt rows; neither: what plan_gemm says.
-struct ProjectionPlan { int wide, nt, rt, splits; };
+// steps: what split_range deals out at a time, in that kernel and in the debugging path that mirrors it.
+struct ProjectionPlan { int wide, nt, rt, splits, steps; };
 
 // From 96 k-steps (K = 3072) on tiles may also have 128 or 192 rows, and a batch of a few hundred rows then takes whole rounds of them;
 // up to 2048 rows, beyond which large tiles fill any number of rounds.  With K = 512 a launch is mostly its beginning and end, and a
@@ -241,9 +242,10 @@ inline double deep_us(int nt, int rt) { return 1.22 * nt * rt + 1.97 * nt + 3.8 
 
 // max_splits 1: nothing adds partial sums behind it.
 inline ProjectionPlan plan_projection(int M, int N, int ks_total, int mt_total, bool swiglu, int max_splits) {
-    ProjectionPlan p{stream_waves(M, N, ks_total, swiglu), 0, 0, 1};
+    ProjectionPlan p{stream_waves(M, N, ks_total, swiglu), 0, 0, 1, kPF};
     if (max_splits > 1) p.splits = projection_splits(M, N, ks_total, mt_total);
     if (p.splits > max_splits) p.splits = max_splits;
+    p.steps = split_steps(M, N, ks_total, mt_total, p.splits);
     if (ks_total < kDeepSteps || N < kDeepCols || M <= kStreamRows || M > kDeepRows) return p;
     const int units = ks_total / kPfBufs;
     int most = (ks_total + 8) / 32;
@@ -259,7 +261,7 @@ inline ProjectionPlan plan_projection(int M, int N, int ks_total, int mt_total, 
             if (!(swiglu ? t.swiglu : t.f32) || mb * 4 * t.rt > mt_total) continue;
             const int rounds = (mb * ceil_div(N, 32 * t.nt) * S + 255) >> 8;
             const double us = partials + rounds * (1.2 + steps * deep_us(t.nt, t.rt));
-            if (least == 0.0 || us < least) { least = us; p = ProjectionPlan{0, t.nt, t.rt, S}; }
+            if (least == 0.0 || us < least) { least = us; p = ProjectionPlan{0, t.nt, t.rt, S, kPfBufs}; }
         }
     }
     return p;

@@ -170,7 +170,7 @@ struct GemmArgs {
     int mt_total;        // row tiles in X (and in a fragment-major output)
     int ks_total;        // k-steps (K padded to 32) in X and W
     int splits;          // split-K factor (EPI_F32 only)
-    int split_steps;     // k-steps that the tile kernel deals out at a time (split_steps in plan.h)
+    int split_steps;     // k-steps that the tile kernel deals out at a time (ProjectionPlan::steps)
     int wide;            // M <= 256 only: 2, 4, 5, 8 or 10 (M <= 128) = computing wavefronts per workgroup (32 features
                          // each) of the weight-streaming kernel; 0 = one of the tiled kernels
     int nt, rt;          // tiles of 32 nt features x 64 rt rows; 0 = the kernel that plan_gemm names
@@ -347,7 +347,7 @@ struct DbgGemmArgs {
     int ldx;                 // = K, the valid inner dimension
     const uint16_t *W;
     int M, N, ks_total, splits;
-    int split_steps;         // dealing unit of the K splits: that of the kernel the normal path runs (plan.h)
+    int split_steps;         // dealing unit of the K splits: that of the kernel the normal path runs (ProjectionPlan::steps)
     float *out;
     int ld_out;
     size_t split_stride;

@@ -85,6 +85,11 @@ int plan_projection(int M, int N, int ks, int mt_total, int swiglu, int max_spli
     out[0] = p.nt; out[1] = p.rt; out[2] = p.splits;
     return p.wide;
 }
+// first k-step of every split of that plan, and the end of the last
+void split_ranges(int M, int N, int ks, int mt_total, int swiglu, int max_splits, int *from) {
+    const sr::ProjectionPlan p = sr::plan_projection(M, N, ks, mt_total, swiglu, max_splits);
+    for (int sp = 0; sp < p.splits; ++sp) sr::split_range(ks, p.steps, p.splits, sp, from + sp, from + sp + 1);
+}
 }
 """
 

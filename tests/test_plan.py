@@ -65,16 +65,36 @@ def test_tiled_kernel_choice_of_wide_matrices(plan):
 
 
 def test_debug_path_deals_k_out_like_the_kernel_it_mirrors(plan):
-    """The single-precision debugging path covers the same k-step ranges per split as the kernel that the normal path runs: tiles
-    deal out four k-steps at a time, the streaming kernel and the 128 x 128 tiles eight."""
+    """The single-precision debugging path covers the same k-step ranges per split as the kernel that the normal path runs, because both
+    take them from the plan of the projection: tiles deal out four k-steps at a time, the streaming kernel and the 128 x 128
+    tiles eight."""
     tiled = 0
-    for M in (64, 136, 224, 257, 296, 384, 512, 600, 768, 1536, 2048):
+    for M in (64, 136, 224, 257, 296, 384, 512, 600, 768, 1536, 2048, 2304):
         for N, ks in ((3584, 592), (1504, 400), (1024, 592), (2048, 352), (3584, 112)):
-            s = plan.projection_splits(M, N, ks, 512)
-            on_tiles = s > 1 and plan.stream_waves(M, N, ks, 0) == 0 and plan.plan_kernel(M, N, ks, 512, 0, s) >= 0
-            assert plan.split_steps(M, N, ks, 512, s) == (4 if on_tiles else 8)
-            tiled += on_tiles and (ks // 8) % s != 0       # the two units give different ranges
+            name, s = plan.projection(M, N, 32 * ks, max_splits=16)
+            cuts, unit = split_cuts(plan, M, N, ks, s), 4 if name.startswith("tiles") else 8
+            assert cuts[0] == 0 and cuts[-1] == ks and all((b - a) % unit == 0 and b > a for a, b in zip(cuts, cuts[1:]))
+            assert max(np.diff(cuts)) - min(np.diff(cuts)) <= unit
+            tiled += unit == 4 and s > 1 and (ks // 8) % s != 0       # the two units give different ranges
     assert tiled >= 3
+
+
+def split_cuts(plan, M, N, ks, splits):
+    out = (ctypes.c_int * 17)()
+    plan.split_ranges(M, N, ks, 512, 0, 16, out)
+    return list(out)[:splits + 1]
+
+
+def test_no_split_is_longer_than_the_tile_rule_reckons_with(plan):
+    """A launch lasts as long as its longest split, which the rule takes to be the groups of four k-steps divided evenly.  Where plan_gemm
+    would have taken the 128 x 128 tiles, groups of eight were dealt out instead: 516 to 614 rows of 2048 features at K = 4096 had
+    splits of 48 k-steps and were reckoned with 44."""
+    for M in range(257, 2049, 23):
+        for N in (2048, 3072, 3584, 4608, 5120, 10240):
+            for ks in (96, 112, 128, 160, 344, 432, 592):
+                name, s = plan.projection(M, N, 32 * ks, max_splits=16)
+                if name.startswith("tiles") and s > 1:
+                    assert max(np.diff(split_cuts(plan, M, N, ks, s))) == 4 * -(-(ks // 4) // s), (M, N, ks, name, s)
 
 
 def test_small_lm_heads_are_scored_through_stored_logits(plan):
