@@ -164,6 +164,12 @@ inline double edge(TileShape t, bool swiglu) { return swiglu && t.nt == 5 ? 2.15
 inline bool swiglu_shape(TileShape t, int ks_total) { return t.nt == 8 || t.nt == 6 || (t.nt == 5 && t.rt == 4 && ks_total >= 96); }
 enum { KERNEL_128 = -2, KERNEL_MID = -1 };             // otherwise an index into kTileShapes
 
+// us that n tiles of 128 x 128 take per 112 k-steps (see above)
+inline double tiles128_us(int M, int N, long long n) {
+    if (n <= 256) return M <= 512 ? 36.0 : 39.0;
+    if (n <= (M > 1024 ? 473 : 512)) return 60.0;
+    return M <= 1024 ? 0.166 * n : (N < 16384 ? 0.095 : 0.137) * n + 15.0;
+}
 struct GemmPlan { int kernel, splits; };
 // splits: 0 = choose up to max_splits, otherwise given
 inline GemmPlan plan_gemm(int M, int N, int ks_total, int mt_total, bool swiglu, int splits, int max_splits) {
@@ -190,10 +196,7 @@ inline GemmPlan plan_gemm(int M, int N, int ks_total, int mt_total, bool swiglu,
         auto offer = [&](int kernel, double us) {
             if (least == 0.0 || us + more < least) { least = us + more; best = GemmPlan{kernel, S}; }
         };
-        const long long n128 = t128 * S;
-        const double t128_us = n128 <= 256 ? (M <= 512 ? 36.0 : 39.0) : n128 <= (M > 1024 ? 473 : 512) ? 60.0 : M <= 1024 ? 0.166 * n128
-                               : (N < 16384 ? 0.095 : 0.137) * n128 + 15.0;
-        offer(KERNEL_128, k / S * t128_us);
+        offer(KERNEL_128, k / S * tiles128_us(M, N, t128 * S));
         if (S <= ks_total / kPfBufs)
             for (int i = 0; i < n_shapes; ++i)
                 if (tiles[i]) offer(i, ((tiles[i] * S + 255) >> 8) * round[i] * 2.33 * k / S);      // equal shapes stay equal
@@ -252,6 +255,10 @@ inline ProjectionPlan plan_projection(int M, int N, int ks_total, int mt_total, 
     if (most > max_splits) most = max_splits;
     if (most > kMaxSplitK) most = kMaxSplitK;
     double least = 0.0;
+    // The SwiGLU shapes are all wide and tall.  Matrices of a few thousand rows fill the compute units better with 128 x 128 tiles, where
+    // plan_gemm takes them: gate|up at K = 4096, 4096 and 8192 packed rows, 37 to 39 us at 280 and 512 rows, 52 to 54 on {5, 3}.
+    if (swiglu && plan_gemm(M, N, ks_total, mt_total, true, 1, 1).kernel == KERNEL_128)
+        least = ks_total / 112.0 * tiles128_us(M, N, (long long)ceil_div(M, 128) * ceil_div(N, 128));
     for (int S = 1; S <= most; ++S) {
         const double partials = swiglu ? 0.0 : 1.5e-6 * S * M * N;        // written, and read by the kernel behind
         if (least != 0.0 && partials >= least) break;

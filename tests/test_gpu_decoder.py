@@ -1007,22 +1007,22 @@ def test_gate_up_on_tiles_with_an_odd_number_of_feature_tiles(plan):
 
 
 @pytest.mark.parametrize("n_groups,ffn,vocab,gate_up,down,lm_head", [
-    (33, 4112, 2064, "5x3", "3x3", "4x2"),           # 264 rows
-    (49, 3088, 10256, "5x3", "5x2", "4x3"),          # 392
+    (33, 5456, 2064, "5x3", "3x3", "4x2"),           # 264 rows
+    (49, 3088, 10256, "128", "5x2", "4x3"),          # 392
     (73, 8208, 10256, "5x5", "6x2", "7x2"),          # 584
     (65, 8208, 16400, "7x3", "5x3", "7x3"),          # 520
     (81, 8208, 10256, "7x4", "5x3", "4x4"),          # 648
     (97, 6160, 2064, "8x3", "8x2", "4x2"),           # 776
 ])
 def test_tiles_of_deep_projections_by_name(plan, n_groups, ffn, vocab, gate_up, down, lm_head):
-    """Tiles of 128 and 192 rows, and the others that deep projections take besides: gate|up, down (split along K) and LM head of a decode
+    """Tiles of 128 and 192 rows, and the others that deep projections take besides (128 x 128 for a small gate|up): gate|up, down (split along K) and LM head of a decode
     step at hidden 3072 on the tiles named here, with ragged last row and column blocks.
 
     The bound is the general rule, 2 E_c, with the contract mode's largest distance E_c over one sequence in 24: the largest of n errors of
     deviation s is about s sqrt(2 ln n), so that four sequences of 648 (4.6 s) would put 2 E_c 6 % below what it is over all.  A token
     other than the exact one needs an exact top-2 gap below the sum of two logits' errors."""
     rows = n_groups * 8
-    assert plan.projection(rows, 2 * ffn, 3072, swiglu=True)[0] == f"tiles {gate_up}"
+    assert plan.projection(rows, 2 * ffn, 3072, swiglu=True)[0].removeprefix("tiles ") == gate_up
     name, splits = plan.projection(rows, 3072, ffn, max_splits=16)
     assert name == f"tiles {down}" and splits > 1 and plan.projection(rows, vocab, 3072)[0] == f"tiles {lm_head}"
     shape = synth.ModelShape(1, 3072, 2, 1, 64, ffn, vocab)

@@ -286,6 +286,13 @@ def test_deep_projections_of_a_few_hundred_rows(plan, M, N, K, swiglu, kernel, s
     assert plan.projection(M, N, K, swiglu, 1 if swiglu else 16) == (kernel, splits)
 
 
+@pytest.mark.parametrize("M,N,K,kernel", [(264, 4096, 4096, "128"), (280, 8192, 4096, "128"), (512, 8192, 4096, "128"), (768, 4096, 3072, "128"),
+                                          (264, 10912, 3072, "tiles 5x3"), (768, 8192, 4096, "tiles 5x3"), (512, 22016, 4096, "tiles 6x4")])
+def test_deep_gate_up_of_a_few_thousand_rows(plan, M, N, K, kernel):
+    """Too few features for tiles of 160 and more to fill the compute units: 128 x 128 as before (37 to 39 us at K = 4096; 52 to 54 on {5, 3})."""
+    assert plan.projection(M, N, K, True) == (kernel, 1)
+
+
 def test_projections_without_tile_shapes_of_their_own(plan):
     """Up to 256 and beyond 2048 rows, and below 3072 inputs, the choice is plan_gemm's and the streaming kernel's, splits included; never more
     splits than asked for, nor a split of less than two groups of eight k-steps."""
