@@ -34,10 +34,10 @@ __device__ __forceinline__ u32x4 load_w_stream(const u32x4 *p) { return __builti
 // copies stalls nobody.
 //
 // Two forms of the MFMA.  LEAN is 16x16x32, whose operands are 16-row tiles as they lie in memory; it draws less power for the same
-// product (2.12 against 1.88 PFLOP/s in a loop without memory), and from 65 rows on the chip's clock follows: whole steps of two
-// layers at the 7B width 348 -> 347 us at 128 rows, 386 -> 379 at 144, 430 -> 428 at 192, 471 -> 461 at 224, 512 -> 500 at 256 (on a warmer
-// card 359 -> 342, 398 -> 378, 446 -> 434, 485 -> 477, 528 -> 520), prefill of 8 x 17 tokens 838 -> 811; up to 64 rows no difference.  32x32x16 has half the instructions, and a launch of a few k-steps spends 0.2 to 0.3 us less on fetching them (hidden 256, 160
-// rows: a step 109.4 us, LEAN 111.4): short launches keep it (stream_lean).  Its operands (32 rows x 16 k) are assembled from the
+// product (2.12 against 1.88 PFLOP/s in a loop without memory), and from 65 rows on the chip's clock follows: gate|up at the 7B
+// shape 46.99 -> 46.52 us at 72 rows, 56.5 -> 55.8 at 144, 68.8 -> 66.1 at 224, 76.8 -> 72.7 at 256; prefill of 8 x 17 tokens 838 -> 811; up to 64
+// rows no difference.  32x32x16 has half the instructions, and short launches and those that leave the chip partly idle keep it
+// (stream_lean).  Its operands (32 rows x 16 k) are assembled from the
 // 16-row fragment layout by addressing: lane (r = lane % 32, g = lane / 32) of k-half h takes the 16 bytes of row tile r / 16, lane slot
 // (r % 16) + 16 * (2h + g).
 //
@@ -266,27 +266,27 @@ int launch_gemm_stream(const GemmArgs &a, GemmEpilogue epi, hipStream_t stream) 
     const int mt32 = ceil_div(a.M, 32);
     hipError_t attr = hipSuccess;
     const bool scaled = a.scale.squares != nullptr;
-    const bool lean = stream_lean(a.M, a.ks_total, epi == EPI_F32 ? a.splits : 1);
+    const bool lean = stream_lean(a.M, a.wide, a.ks_total, epi == EPI_F32 ? a.splits : 1, scaled);
 #define SR_STREAM_CASE(E, W, T, S, L)                                                                      \
     (attr = hipFuncSetAttribute((const void *)gemm_stream_kernel<E, W, T, kRing, S, L>,                    \
                         hipFuncAttributeMaxDynamicSharedMemorySize, st_lds_bytes(T, W, S)),                \
      gemm_stream_kernel<E, W, T, kRing, S, L><<<sgrid, lblock, st_lds_bytes(T, W, S), stream>>>(a))
 #define SR_STREAM_SCALED(E, W, T, L) (scaled ? SR_STREAM_CASE(E, W, T, true, L) : SR_STREAM_CASE(E, W, T, false, L))
-#define SR_STREAM_TALL(E, W, T) (lean ? SR_STREAM_CASE(E, W, T, false, true) : SR_STREAM_CASE(E, W, T, false, false))
-    // from 65 rows on a norm is finished in front of short inner dimensions only (plan.h, thin_qkv)
+#define SR_STREAM_PLAIN(E, W, T) SR_STREAM_CASE(E, W, T, false, false)
+#define SR_STREAM_TALL(E, W, T) (lean ? SR_STREAM_CASE(E, W, T, false, true) : SR_STREAM_PLAIN(E, W, T))
 #define SR_STREAM_LEAN(E, W, T) (scaled ? SR_STREAM_CASE(E, W, T, true, false) : SR_STREAM_TALL(E, W, T))
     // nine and eleven wavefronts put three on one SIMD: 168 registers, too few for more than four row tiles, and for four without LEAN
 #define SR_STREAM_MT4(E, W, LEAN)                                                                          \
     (mt32 == 1 ? SR_STREAM_SCALED(E, W, 1, false) : mt32 == 2 ? SR_STREAM_SCALED(E, W, 2, false)           \
      : mt32 == 3 ? LEAN(E, W, 3) : LEAN(E, W, 4))
 #define SR_STREAM_ALWAYS(E, W, T) SR_STREAM_SCALED(E, W, T, true)
-#define SR_STREAM_MT(E, W)                                                                                 \
+#define SR_STREAM_MT(E, W, TALLEST)                                                                        \
     (mt32 <= 4 ? SR_STREAM_MT4(E, W, SR_STREAM_LEAN)                                                       \
      : mt32 == 5 ? SR_STREAM_TALL(E, W, 5) : mt32 == 6 ? SR_STREAM_TALL(E, W, 6)                           \
-     : mt32 == 7 ? SR_STREAM_TALL(E, W, 7) : SR_STREAM_TALL(E, W, 8))
+     : mt32 == 7 ? TALLEST(E, W, 7) : TALLEST(E, W, 8))
 #define SR_STREAM_W(E)                                                                                     \
-    (a.wide == 2 ? SR_STREAM_MT(E, 2) : a.wide == 4 ? SR_STREAM_MT(E, 4)                                   \
-     : a.wide == 5 ? SR_STREAM_MT(E, 5)                                                                    \
+    (a.wide == 2 ? SR_STREAM_MT(E, 2, SR_STREAM_PLAIN) : a.wide == 4 ? SR_STREAM_MT(E, 4, SR_STREAM_TALL)  \
+     : a.wide == 5 ? SR_STREAM_MT(E, 5, SR_STREAM_TALL)                                                    \
      : a.wide == 8 ? SR_STREAM_MT4(E, 8, SR_STREAM_ALWAYS) : SR_STREAM_MT4(E, 10, SR_STREAM_ALWAYS))
     if (mt32 > 4 && (a.wide >= 8 || scaled)) return SR_E_ARG;
     if (scaled && (a.scale.ld % 4 || a.splits != 1)) return SR_E_ARG;

@@ -92,8 +92,21 @@ inline int stream_waves(int M, int N, int ks_total, bool swiglu) {
     return best;
 }
 
-// The streaming kernel's MFMA of less power, from 65 rows and 24 k-steps of a split on (gemm_stream.hip)
-inline bool stream_lean(int M, int ks_total, int splits) { return M > 64 && ks_total / splits >= 24; }
+// Whether the streaming kernel of `wide` computing wavefronts takes the 16x16x32 MFMA, which draws less power, instead of the 32x32x16,
+// which has half the instructions (gemm_stream.hip).  From 65 rows on, where the chip's clock follows the power.
+//   4 and 5 wavefronts: from 24 k-steps of a split on (76.8 -> 72.7 us for gate|up of the 7B shape at 256 rows, 51.5 and 51.8 at 128; a
+//     launch of fewer k-steps spends 0.2 to 0.3 us more on fetching its instructions).
+//   2 wavefronts: up to 192 rows and from K = 3072 on only (gate|up of 16 384 rows, K = 3072, 160 rows: 30.4 -> 29.7 us; QKV, O and LM head at
+//     K = 5120 28.8 -> 28.1).  Shorter ones leave the chip partly idle and lose (K = 896 at 160 rows: 12.6 -> 13.2 us, K = 2048 14.05
+//     -> 14.4), and so do 224 and 256 rows at any K (K = 3584: 22.1 -> 22.9 and 23.8 -> 25.0; K = 4096 at 224 rows 38.5 -> 39.8).
+//   8 and 10 wavefronts have registers for nothing else beyond 64 rows.
+// Where a norm is finished the 2 to 5 wavefronts keep 32x32x16: above 64 rows that is in front of short inner dimensions (thin_resid).
+inline bool stream_lean(int M, int wide, int ks_total, int splits, bool scaled) {
+    if (M <= 64) return false;
+    if (wide >= 8) return true;
+    if (scaled) return false;
+    return wide >= 4 ? ks_total / splits >= 24 : M <= 192 && ks_total >= 96;
+}
 
 // K splits up to kStreamRows rows, whichever kernel it is
 inline int pick_splits(int M, int N, int ks_total) {

@@ -79,7 +79,7 @@ int thin_qkv(int M, int N, int ks) { return sr::thin_qkv(M, N, ks); }
 void rope_tables(int len, int d, double theta, float *c, float *s) { sr::rope_tables(len, d, theta, c, s); }
 int padded_k_steps(int K) { return sr::padded_k_steps(K); }
 int projection_splits(int M, int N, int ks, int mt_total) { return sr::projection_splits(M, N, ks, mt_total); }
-int stream_lean(int M, int ks, int splits) { return sr::stream_lean(M, ks, splits); }
+int stream_lean(int M, int wide, int ks, int splits, int scaled) { return sr::stream_lean(M, wide, ks, splits, scaled); }
 int plan_projection(int M, int N, int ks, int mt_total, int swiglu, int max_splits, int *out) {
     const sr::ProjectionPlan p = sr::plan_projection(M, N, ks, mt_total, swiglu, max_splits);
     out[0] = p.nt; out[1] = p.rt; out[2] = p.splits;

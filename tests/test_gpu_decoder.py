@@ -1081,16 +1081,32 @@ def test_weight_streaming_widths_by_name(plan, n_groups, G, ffn, vocab, gate_up,
 @pytest.mark.parametrize("n_groups,ffn,gate_up", [(9, 8208, 4), (12, 20464, 5), (16, 2064, 2), (17, 20464, 5), (24, 8208, 4), (28, 8208, 4),
                                                   (32, 20464, 5)])
 def test_weight_streaming_with_the_mfma_of_less_power(plan, n_groups, ffn, gate_up):
-    """Three to eight 32-row tiles at 24 k-steps and more: gate|up at every width and the LM head (beyond 128 rows QKV and O too, and down where
-    its splits are long enough), ragged last rows and columns."""
+    """Three to eight 32-row tiles at 24 k-steps and more: gate|up of four and five wavefronts and the LM head (and down where its splits are
+    long enough), ragged last rows and columns; the narrow ones keep the other form."""
     rows = n_groups * 8
     assert plan.kernel(rows, 2 * ffn, 768, swiglu=True) == f"stream {gate_up}" and plan.kernel(rows, 16400, 768) == "stream 4"
-    assert plan.stream_lean(rows, 24, 1) and not plan.stream_lean(rows, 16, 1) and not plan.stream_lean(64, 24, 1)
+    assert plan.stream_lean(rows, 4, 24, 1, 0) and plan.stream_lean(rows, gate_up, 24, 1, 0) == (gate_up >= 4)
     shape = synth.ModelShape(1, 768, 4, 2, 64, ffn, 16400)
     cfg = synth.EpisodeConfig("lean", n_groups, 8, 4, 1, 1, 1, 64, (), 0.3, 0.0)
     rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=83, page_tokens=32, kv_pool_bytes=1 << 28)
     print(f"lean {rows} rows, {ffn}: worst |dlogit| = {worst:.3e}, mismatches = {mism}, near ties = {near}")
     assert worst <= LOGIT_TOL and mism == 0
+
+
+@pytest.mark.parametrize("n_groups", [9, 16, 17, 24, 25])
+def test_narrow_weight_streams_with_the_mfma_of_less_power(plan, n_groups):
+    """Two wavefronts at K = 3072: gate|up, QKV (split) and LM head, three to six 32-row tiles; gate|up of 200 rows on the other form."""
+    rows, lean = n_groups * 8, n_groups < 25
+    assert plan.kernel(rows, 4128, 3072, swiglu=True) == "stream 2" and plan.stream_lean(rows, 2, 96, 1, 0) == lean
+    assert (plan.kernel(rows, 1040, 3072) == "stream 2") == lean
+    shape = synth.ModelShape(1, 3072, 4, 2, 64, 2064, 1040)
+    cfg = synth.EpisodeConfig("narrow-lean", n_groups, 8, 4, 1, 1, 1, 64, (), 0.3, 0.0)
+    info = {}
+    rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=86, page_tokens=32, kv_pool_bytes=1 << 28,
+                                                     contract_rows=list(range(0, rows, 8)), info=info)
+    tol = tolerance(info["contract_max"])
+    print(f"narrow lean {rows}: worst |dlogit| = {worst:.3e}, bound {tol:.3e}, mismatches = {mism}, near ties = {near}")
+    assert worst <= tol and all(g < gap_rule(tol) for g in info["mismatch_gaps"])
 
 
 @pytest.mark.parametrize("n_groups", [5, 25, 41])

@@ -53,6 +53,19 @@ def test_workgroup_widths_of_wide_matrices(plan, N, M, waves):
     assert plan.stream_waves(M, N, 112, 0) == waves
 
 
+def test_mfma_form_of_the_weight_streams(plan):
+    """16x16x32 where it measured faster: four and five wavefronts from 65 rows and 24 k-steps on, two at K >= 3072 up to 192 rows only, eight and
+    ten always (registers), never the first three in front of a norm's factors, and never up to 64 rows."""
+    for M in (1, 64, 65, 128, 129, 192, 193, 256):
+        for ks, splits in ((8, 1), (24, 1), (32, 1), (32, 2), (64, 2), (96, 4), (112, 1), (160, 5), (592, 16)):
+            for wide in (4, 5):
+                assert plan.stream_lean(M, wide, ks, splits, 0) == (M > 64 and ks // splits >= 24)
+                assert not plan.stream_lean(M, wide, ks, splits, 1)
+            assert plan.stream_lean(M, 2, ks, splits, 0) == (64 < M <= 192 and ks >= 96)
+            assert not plan.stream_lean(M, 2, ks, splits, 1)
+            assert plan.stream_lean(M, 8, ks, splits, 1) == plan.stream_lean(M, 10, ks, splits, 0) == (M > 64)
+
+
 def test_tiled_kernel_choice_of_wide_matrices(plan):
     """More than 1024 rows against 16 384 matrix rows or more: never the 128 x 128 tiles (658 us where others took 458).  512 such
     tiles are one round of two to a CU: 8192 and 16 384 matrix rows at 1024 and 512 rows take them."""
