@@ -136,10 +136,16 @@ inline long long thin_bytes(int M, int features, int N, int ks_total) {
     const int rows = M <= 8 ? 8 : round_up(M, 16), rounds = ceil_div(ceil_div(N, features), 256);
     return (long long)rounds * (features + rows) * ks_total * 64;
 }
+// Sums of squares that every workgroup of the projection behind adds up (a float for each row and 16 of the N features, rows as RowSquares
+// deals them out).  Up to 24 KB that is hidden behind its weights; beyond, it costs more than the norm kernel saves.  Whole decode steps of two
+// layers with O in its own kernel, against without: 80 rows at hidden 768 (24 KB) 1 % faster, 896 (28 KB) 1 % slower, 1024 (32 KB) 4 %,
+// 1280 (40 KB) 4 %; hidden 4096 with 256 inputs, 16 rows (16 KB) 3 % faster, 48 (64 KB) 1.4 % slower, 80 to 128 (128 KB) 4 to 5 %.
+inline int squares_bytes(int M, int N) { return (M <= 8 ? 8 : M <= 16 ? 16 : M <= 32 ? 32 : M <= 64 ? 64 : 128) * (N / 4); }
 // O and down.  Eight rows at any depth where the matrix has a workgroup for most compute units: down of the 7B shape streams no
-// faster otherwise (23 and 24 us).
+// faster otherwise (23 and 24 us; whole steps with all three at hidden 3200 and 4096 10 % faster than without any, down alone 4 %).
 inline bool thin_resid(int M, int N, int ks_total) {
-    return M <= kThinRows && (thin_bytes(M, 16, N, ks_total) <= 256 << 10 || (M <= 8 && N >= 3200 && N <= 4096));
+    return M <= kThinRows && squares_bytes(M, N) <= 24 << 10 &&
+           (thin_bytes(M, 16, N, ks_total) <= 256 << 10 || (M <= 8 && N >= 3200 && N <= 4096));
 }
 inline bool thin_qkv(int M, int N, int ks_total) {
     return M <= kThinRows && thin_bytes(M, 32, N, ks_total) <= (M <= 32 ? 360 << 10 : 88 << 10);

@@ -282,6 +282,13 @@ def test_thin_projections_where_they_come_out_ahead(plan):
             assert not plan.thin_qkv(M, N, 8) and not plan.thin_resid(M, N, 8)
 
 
+@pytest.mark.parametrize("M,N,ks,thin", [(64, 1024, 32, True), (65, 1024, 32, False), (80, 768, 24, True), (80, 896, 32, False), (128, 768, 24, True),
+                                         (16, 4096, 8, True), (17, 4096, 8, False), (48, 4096, 8, False), (128, 4096, 8, False), (8, 8192, 8, True)])
+def test_sums_of_squares_that_fit_behind_the_weights(plan, M, N, ks, thin):
+    """Up to 24 KB of them for each workgroup behind; more made whole steps 1 to 5 % slower than the norm kernel does."""
+    assert plan.thin_resid(M, N, ks) == thin
+
+
 def test_whole_contexts_where_they_come_out_ahead(plan):
     """Up to 1024 tokens of 128 dims and 2048 of 64, for one round of workgroups."""
     assert plan.whole_context(256, 128, 1024) and plan.whole_context(64, 64, 2048) and plan.whole_context(1, 64, 1)
