@@ -656,13 +656,7 @@ int launch_attention_whole(const AttnArgs &args, int n_seq, int ctx, hipStream_t
     a.by_kv = fast_div(a.n_kv);
     a.inv_rep = 1.0f / (float)a.n_rep;
     a.page_shift = 31 - __builtin_clz(a.page_tokens);
-    AttnPhase p{};
-    p.n_units = n_seq;
-    p.q_per_unit = p.q_per_item = p.items_per_unit = p.pt_row_stride = p.rt = 1;
-    p.t_end = ctx;
-    p.causal_pos0 = ctx - 1;
-    p.n_splits = kWholeWaves;
-    p.split_tokens = round_up(ceil_div(ctx, kWholeWaves), 32);     // the last wavefronts may have none
+    const AttnPhase p = whole_phase(n_seq, ctx);
     const dim3 grid((unsigned)wgs), block(64 * kWholeWaves);
     if (a.d == 128) attn_whole_kernel<128><<<grid, block, 0, stream>>>(a, p);
     else if (a.d == 64) attn_whole_kernel<64><<<grid, block, 0, stream>>>(a, p);

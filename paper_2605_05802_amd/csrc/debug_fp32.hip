@@ -3,11 +3,12 @@
 // The same decoder with every activation, the stored keys and values and the attention probabilities in
 // fp32 and every contraction as plain fused multiply-adds -- no bf16 rounding of operands, no matrix
 // cores.  What is NOT different is everything that could hide an indexing mistake behind rounding noise:
-// the page tables and copy-on-write, the (unit, kv head, split, query tile) decomposition of attention (that of
-// more sequences or longer contexts: see whole_context) and
+// the page tables and copy-on-write, the (unit, kv head, split, query tile) decomposition of attention and
 // its partial-result format and merge, the k-step ranges of the projections' K splits and the order in
-// which the consumers add the partial sums (where projections leave any: not in gemm_thin.hip), the packed weight layout (read here element by element),
-// token selection, gate and compaction.  Against an exact evaluation this path differs by single-precision
+// which the consumers add the partial sums, the packed weight layout (read here element by element),
+// token selection, gate and compaction.  What the normal path does within one kernel, because it has few rows (gemm_thin.hip,
+// attn_whole_kernel), is divided here as its wavefronts divide it, into splits whose results are added or merged in their
+// order; a norm that it finishes behind the next projection is finished in front of it.  Against an exact evaluation this path differs by single-precision
 // rounding only.  Speed is not a goal: tiles are small and go through LDS once.
 #include "sr_internal.h"
 

@@ -98,7 +98,12 @@ __global__ __launch_bounds__(512) void resid_norm_kernel(NormArgs a) {
                 } else {
                     f32x4 lo = *(const f32x4 *)(x + v * 8), hi = *(const f32x4 *)(x + v * 8 + 4);
                     const float *p0 = a.partials + row * a.H + v * 8;
-                    add_partials(p0, a.partial_stride, a.n_partials, 4, lo, hi);
+                    if (F32OUT && a.sums_first) {
+                        f32x4 slo = {0.f, 0.f, 0.f, 0.f}, shi = {0.f, 0.f, 0.f, 0.f};
+                        add_partials(p0, a.partial_stride, a.n_partials, 4, slo, shi);
+                        lo += slo;
+                        hi += shi;
+                    } else add_partials(p0, a.partial_stride, a.n_partials, 4, lo, hi);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) { f[i] = lo[i]; f[4 + i] = hi[i]; }
                 }

@@ -438,7 +438,7 @@ int gemm(sr_ctx *c, const uint4 *X, const PackedMat &W, int M, GemmEpilogue epi,
 
 // The same projection on the single-precision debugging path: X row-major fp32 [M][K]
 int gemm32(sr_ctx *c, const float *X, int K, const PackedMat &W, int M, GemmEpilogue epi, float *out, int ld_out,
-           int *splits_out, hipStream_t st) {
+           int *splits_out, hipStream_t st, bool thin = false) {
     DbgGemmArgs a{};
     a.X = X;
     a.ldx = K;
@@ -450,6 +450,11 @@ int gemm32(sr_ctx *c, const float *X, int K, const PackedMat &W, int M, GemmEpil
     a.ld_out = ld_out;
     ProjectionPlan p;
     SR_TRY(plan_one(c, M, W, epi == EPI_SWIGLU, epi == EPI_F32 && splits_out, ld_out, &p, &a.split_stride));
+    if (thin) {                                      // the wavefronts of gemm_thin.hip
+        p.splits = kThinSplits;
+        p.steps = 1;
+        if (a.split_stride * kThinSplits > c->partial_elems) return SR_E_ARG;
+    }
     a.splits = p.splits;
     a.split_steps = p.steps;
     if (splits_out) *splits_out = a.splits;
@@ -486,9 +491,10 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
         part_rows += items * 16 * x.rt;
         ph[n_ph++] = x;
     };
-    const bool whole = p.decode && !c->dbg && whole_context((long long)p.n_units * s.n_kv_heads, s.head_dim, ctx);
+    const bool whole = p.decode && whole_context((long long)p.n_units * s.n_kv_heads, s.head_dim, ctx);
     if (whole) {
-        // one launch and no partial results: no phases
+        // one launch and no partial results; on the debugging path its wavefronts' shares of the context, as splits
+        if (c->dbg) add_phase(whole_phase(p.n_units, ctx));
     } else if (p.decode) {
         if (c->shared_tokens > 0) {
             AttnPhase x{};
@@ -569,8 +575,8 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
     }
     if (part_rows > c->part_rows_cap) return SR_E_NOMEM;
     // one partial result per query row: the attention kernel writes the merged output itself
-    const bool direct = whole || (n_ph == 1 && ph[0].n_splits == 1);
     const bool dbg = c->dbg;
+    const bool direct = (whole && !dbg) || (n_ph == 1 && ph[0].n_splits == 1);
     const int qd = s.n_q_heads * s.head_dim;
     aa.direct_out = direct && !dbg ? (uint16_t *)c->attn_out : nullptr;
     aa.out_mt_total = c->mt_total;
@@ -579,10 +585,11 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
     da.direct_out32 = direct && dbg ? c->attn32 : nullptr;
 
     // Thin projections of a few rows finish in their own kernel.  O and down then leave x * gain of the next norm in c->xn and `folded`
-    // says how the projection behind it finishes that norm; else there are partial sums, a norm kernel, and X is normalised.
+    // says how the projection behind it finishes that norm; else there are partial sums, a norm kernel, and X is normalised.  The
+    // debugging path leaves the sums of their wavefronts as partial sums, which are added to each other before anything else.
     const RowScale fold{c->squares, c->squares_ld, 1.0f / (float)H, s.rms_eps};
     RowScale folded{};
-    const bool thin_q = !dbg && thin_qkv(M, c->qkv_cols, c->ks_h), thin_o = !dbg && thin_resid(M, H, c->ks_q);
+    const bool thin_q = thin_qkv(M, c->qkv_cols, c->ks_h), thin_o = thin_resid(M, H, c->ks_q);
     const bool thin_d = thin_q && thin_resid(M, H, c->ks_f);
     auto resid_args = [&](const uint4 *X, const PackedMat &W, const uint16_t *gain) {
         ThinArgs t{};
@@ -625,6 +632,7 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
             na.partials = c->partials;
             na.n_partials = n_part;
             na.partial_stride = part_stride;
+            na.sums_first = thin_d;
         }
         if (!folded.squares) SR_TRY(timed(c, SR_KC_NORM, st, [&] { return launch_resid_norm(na, st); }));
 
@@ -651,7 +659,7 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
         qa.n_kv = s.n_kv_heads;
         qa.d = s.head_dim;
         qa.page_tokens = c->o.page_tokens;
-        if (thin_q) {
+        if (thin_q && !dbg) {
             ThinArgs t{};
             t.X = c->xn;
             t.W = (const uint4 *)w.qkv.p;
@@ -664,7 +672,7 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
             SR_TRY(timed(c, SR_KC_GEMM_QKV, st, [&] { return launch_thin_qkv(t, st); }));
         } else {
             SR_TRY(timed(c, SR_KC_GEMM_QKV, st, [&] {
-                return dbg ? gemm32(c, c->xn32, H, w.qkv, M, EPI_F32, c->partials, c->qkv_cols, &sp, st)
+                return dbg ? gemm32(c, c->xn32, H, w.qkv, M, EPI_F32, c->partials, c->qkv_cols, &sp, st, thin_q)
                            : gemm(c, c->xn, w.qkv, M, EPI_F32, c->partials, c->qkv_cols, &sp, st);
             }));
             qa.n_partials = sp;
@@ -694,12 +702,12 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
             }));
         }
 
-        if (thin_o) {
+        if (thin_o && !dbg) {
             SR_TRY(timed(c, SR_KC_GEMM_O, st, [&] { return launch_thin_resid(resid_args(c->attn_out, w.o, w.norm2), st); }));
             folded = fold;
         } else {
             SR_TRY(timed(c, SR_KC_GEMM_O, st, [&] {
-                return dbg ? gemm32(c, c->attn32, qd, w.o, M, EPI_F32, c->partials, H, &sp, st)
+                return dbg ? gemm32(c, c->attn32, qd, w.o, M, EPI_F32, c->partials, H, &sp, st, thin_o)
                            : gemm(c, c->attn_out, w.o, M, EPI_F32, c->partials, H, &sp, st);
             }));
             na.embed = nullptr;
@@ -707,6 +715,7 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
             na.partials = c->partials;
             na.n_partials = sp;
             na.partial_stride = (size_t)round_up(M, 128) * H;
+            na.sums_first = thin_o;
             na.gain = w.norm2;
             SR_TRY(timed(c, SR_KC_NORM, st, [&] { return launch_resid_norm(na, st); }));
             folded = RowScale{};
@@ -716,14 +725,14 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
             return dbg ? gemm32(c, c->xn32, H, w.gu, M, EPI_SWIGLU, c->act32, s.ffn, nullptr, st)
                        : gemm(c, c->xn, w.gu, M, EPI_SWIGLU, c->act, c->ks_f * 32, nullptr, st, folded);
         }));
-        if (thin_d) {
+        if (thin_d && !dbg) {
             const uint16_t *next = l + 1 < s.n_layers ? c->L[l + 1].norm1 : c->final_norm;
             SR_TRY(timed(c, SR_KC_GEMM_DOWN, st, [&] { return launch_thin_resid(resid_args(c->act, w.down, next), st); }));
             folded = fold;
             n_part = 0;
         } else {
             SR_TRY(timed(c, SR_KC_GEMM_DOWN, st, [&] {
-                return dbg ? gemm32(c, c->act32, s.ffn, w.down, M, EPI_F32, c->partials, H, &sp, st)
+                return dbg ? gemm32(c, c->act32, s.ffn, w.down, M, EPI_F32, c->partials, H, &sp, st, thin_d)
                            : gemm(c, c->act, w.down, M, EPI_F32, c->partials, H, &sp, st);
             }));
             folded = RowScale{};
@@ -739,6 +748,7 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
         na.partials = c->partials;
         na.n_partials = n_part;
         na.partial_stride = part_stride;
+        na.sums_first = thin_d;
         na.gain = c->final_norm;
         na.out = c->xn;
         na.out32 = dbg ? c->xn32 : nullptr;
@@ -808,6 +818,7 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
         na.partials = c->partials;
         na.n_partials = n_part;
         na.partial_stride = part_stride;
+        na.sums_first = thin_d;
         na.gain = c->final_norm;
         na.out = c->xn;
         na.out32 = dbg ? c->xn32 : nullptr;

@@ -18,14 +18,16 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // their half of X's 16-row tiles.  Alone, in us, this kernel against gemm_stream_kernel without what follows it (norm 4.4 us at 8 rows,
 // QKV epilogue 4.6): K = 3584, 8 rows: O 6.4 / 7.0, QKV 9.6 / 8.6, down 22.6 / 24.4; 16 rows: 7.7 / 7.4, 11.1 / 8.7, 28.8 / 24.8; K = 256, 32
 // rows: 2.7 / 2.8 and 3.0 / 3.2.  More wavefronts and deeper rings are no faster.
-constexpr int kWaves = 4;
+constexpr int kWaves = kThinSplits;
 constexpr int ring_steps(int mt) { return mt == 1 ? 8 : mt == 2 ? 4 : 2; }
 
 // X as it is needed by both kernels: acc[NT][MT] of this wavefront's k-steps
 template <int NT, int MT, bool HALF>
 __device__ __forceinline__ void multiply(const ThinArgs &a, int wave, int lane, f32x4 (&acc)[NT][MT]) {
     constexpr int D = ring_steps(MT);
-    const int k0 = wave * a.ks_total / kWaves, k1 = (wave + 1) * a.ks_total / kWaves, last = k1 - 1;
+    int k0, k1;
+    split_range(a.ks_total, 1, kWaves, wave, &k0, &k1);
+    const int last = k1 - 1;
 #pragma unroll
     for (int i = 0; i < NT; ++i)
 #pragma unroll

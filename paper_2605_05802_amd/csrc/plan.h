@@ -131,7 +131,8 @@ inline int pick_splits(int M, int N, int ks_total) {
 // calls of two layers, us, without these -> with them: K = 3584, decode of 8 rows 246 -> 227, 16 rows (all but down) 249 -> 244, 24
 // rows (none; QKV or O alone would be +- 1 %) 252; hidden 256, decode of 32 rows 80 -> 65, 128 rows 104 -> 89, prefill of 40 rows 98 -> 82;
 // hidden 512 with down projections of 8192 inputs (which stay), 8 rows 95 -> 90, 32 rows 107 -> 99; QKV at 64 rows there 108 -> 110.
-constexpr int kThinRows = 128;
+// K is dealt out evenly over kThinSplits wavefronts, k-step by k-step (split_range with a unit of one).
+constexpr int kThinRows = 128, kThinSplits = 4;
 inline long long thin_bytes(int M, int features, int N, int ks_total) {
     const int rows = M <= 8 ? 8 : round_up(M, 16), rounds = ceil_div(ceil_div(N, features), 256);
     return (long long)rounds * (features + rows) * ks_total * 64;

@@ -192,6 +192,7 @@ struct NormArgs {
     float *resid;            // [rows][H] fp32 residual stream (updated in place)
     const float *partials;   // [n_partials][rows][H] fp32 to be added first, or null
     int n_partials;
+    int sums_first;          // single-precision debugging path: partials are added to each other and then to resid (gemm_thin.hip)
     size_t partial_stride;
     const int32_t *tokens;   // embedding mode (embed != null): resid[m] = embed[tokens[index(m)]], with
     int tok_chunk, tok_stride, tok_off;  //   index(m) = (m / tok_chunk) * tok_stride + tok_off + m % tok_chunk
@@ -327,7 +328,17 @@ inline void set_shared_phase(AttnPhase *x, int shared_tokens, int n_kv, int max_
 int launch_attention(const AttnArgs &a, const AttnPhase *phases, int n_phases, hipStream_t stream);
 
 // Decode of n_seq sequences with `ctx` tokens each, the one being decoded included: the whole context in one launch; a.direct_out is
-// required.
+// required.  whole_phase: the same as a phase whose splits are the launch's wavefronts, the last of which may have no tokens.
+inline AttnPhase whole_phase(int n_seq, int ctx) {
+    AttnPhase p{};
+    p.n_units = n_seq;
+    p.q_per_unit = p.q_per_item = p.items_per_unit = p.pt_row_stride = p.rt = 1;
+    p.t_end = ctx;
+    p.causal_pos0 = ctx - 1;
+    p.n_splits = kWholeWaves;
+    p.split_tokens = round_up(ceil_div(ctx, kWholeWaves), 32);
+    return p;
+}
 int launch_attention_whole(const AttnArgs &a, int n_seq, int ctx, hipStream_t stream);
 
 // Merge the partial results of up to two phases into out (fragment-major bf16 [query tokens][n_q*d]) or, when
