@@ -1,7 +1,7 @@
 // Row-wise kernels between the GEMMs: residual update + RMSNorm, QKV epilogue (bias, RoPE,
-// KV page write), greedy argmax, and small utilities.  All reductions run in a fixed order
-// that does not depend on the row index or on the batch size, so a sequence's numbers do not
-// change when other rows enter or leave the batch.
+// KV page write), greedy argmax, and small utilities.  All reductions of these kernels run in a fixed order that does not depend on
+// the row index or on the batch size.  (K splits and attention splits do depend on the batch size, and so does the order in which a
+// norm that is finished behind the next projection adds up its squares: see RowSquares.  Rows of one batch are treated alike everywhere.)
 #include "epilogue.h"
 
 namespace sr {

@@ -5,7 +5,9 @@
 namespace sr {
 
 // RowScale: the sums of squares of a row, dealt out over THREADS threads, each of which adds those of one row; then the row's factor.
-// request() where the round trip is hidden, leave() ahead of a barrier, scale() behind it.
+// request() where the round trip is hidden, leave() ahead of a barrier, scale() behind it.  The order of the sum is the same for all rows of a
+// launch, but follows the power of two that holds M and THREADS: a sequence's factor may change in its last bits with the
+// batch, and between QKV, gate|up and LM head, as the sums of a projection do with its K splits.
 template <int THREADS>
 struct RowSquares {
     static constexpr int N = 4;      // values of 16 bytes that a thread requests at once; the first ones of more are added on the way

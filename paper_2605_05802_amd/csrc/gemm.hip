@@ -390,11 +390,12 @@ __global__ __launch_bounds__(kPfThreads) void gemm_prefill_kernel(GemmArgs a, in
 }
 
 // ---------------------------------------------------------------------------------------------
-// Batches of a few hundred rows (decode steps of a 512-sequence batch) against a wide matrix: neither a weight
-// stream (the matrix pipe, not HBM, bounds 512 rows) nor a large tiled GEMM (two row blocks of 256 leave 1.16 rounds
-// of tiles and fetch every weight from HBM with only two workgroups sharing it).  One workgroup takes ALL rows (up
-// to 512) of 160 packed features, so every weight byte is fetched from HBM exactly once and the 37 888 packed
-// gate|up rows of the 7B shape break into 237 workgroups, one round.  Eight wavefronts, each 64 rows x 160 features
+// Batches of 321 to 512 rows against a wide matrix (more than 32 784 rows) of less than 3072 inputs; with more inputs tiles of
+// 160 to 256 features and 192 to 320 rows are faster (plan_projection: gate|up of the 7B shape at 512 rows 117 us, a round of this
+// kernel 139).  Neither a weight stream (the matrix pipe, not HBM, bounds 512 rows) nor a large tiled GEMM (two row blocks of 256 leave
+// 1.16 rounds of tiles and fetch every weight from HBM with only two workgroups sharing it).  One workgroup takes ALL rows (up
+// to 512) of 160 packed features, so every weight byte is fetched from HBM exactly once and 37 888 packed
+// gate|up rows break into 237 workgroups, one round.  Eight wavefronts, each 64 rows x 160 features
 // (2 x 5 accumulator tiles of 32 x 32 = 160 registers; seven LDS fragment reads per ten MFMAs).  Both operands go
 // global -> LDS with direct-to-LDS loads, one barrier per k-step: X (32 KiB per k-step, L2 resident) two k-steps
 // ahead through three buffers, W (10 KiB per k-step, from HBM) five k-steps ahead through six;

@@ -152,30 +152,31 @@ inline bool thin_qkv(int M, int N, int ks_total) {
     return M <= kThinRows && thin_bytes(M, 32, N, ks_total) <= (M <= 32 ? 360 << 10 : 88 << 10);
 }
 
-// The tiled kernels: which one, and how many K splits.  Times in us, from launches of the 7B shape's projections at
-// 8192, 5120, 4096, 2048, 1280, 768, 512 and 296 rows; k = K / 3584.  A launch has about 3 us of its own, the same for all.
+// The tiled kernels: which one, and how many K splits, except where plan_projection below decides by itself: 257 to 2048 rows of 2048 features
+// and more from K = 3072 on.  Times in us, fitted to launches of the 7B shape's projections at 8192, 5120, 4096, 2048, 1280, 768, 512 and
+// 296 rows, of which those up to 2048 rows are launches that plan_projection has taken over since (marked *): they are why
+// the prices are what they are, and the prices go on deciding shorter inner dimensions.  k = K / 3584.  A launch has about 3
+// us of its own, the same for all.
 //   64 RT x 32 NT tiles, one to a CU: a round takes 2.33 RT (NT + 1.5) k.  O at 4096 rows 86 (NT = 7) and 88 (8), QKV at
 //     8192 rows 186 (6, three rounds), 202 (7, three), 207 (5, four) and 212 (8, three), O at 5120 rows 126 (5), 142 (6),
 //     155 (7) and 165 (8), two rounds each.  Every shape is looked at: what decides is how full the last round is.  The
-//     narrow ones (NT = 2, 3) give a few hundred rows a whole round where 128 x 128 tiles need two or more K splits (16 384
+//     narrow ones (NT = 2, 3) give a few hundred rows a whole round where 128 x 128 tiles need two or more K splits (* 16 384
 //     columns at 296 rows: 45 us with {2, 5} and 55 with 128 x 128).  Every one of their many column blocks reads all of X again, so
-//     they count as 0.4 to 1 features more (`edge`).  With the 1.5 of the others they won where they lose (us with the kernel that reads the
-//     result; without edge -> now): QKV at 600 rows {2, 4} 47.3 -> {4, 5} in three splits 42.2, at 700 48.9 -> 46.0 (128 x 128), at 1000
-//     {3, 4} 55.2 -> {5, 4} in two 53.5; O at 800 rows {2, 4} 53.7 -> {4, 5} in three 47.6, at 1000 54.4 -> 50.9 (128 x 128), at 1600
-//     {3, 5} 76.4 -> {5, 5} in two 69.6.  They still win where they should: O at 600 rows {2, 5} in two 36.8 (128 x 128 in three 42.2),
-//     at 740 {3, 4} in two 39.3 (45.8), QKV at 1280 {3, 4} 58.4 ({6, 4} in two 60.8), at 1600 {3, 5} 71.0 (77.0); 512 columns,
-//     K = 8192 at 2560 rows {3, 4} in four 40.4 ({4, 5} in eight 42.0).  The model with hidden 512, where projections are short and a change of kernel
-//     costs about a us, takes them from 1281 rows on (whole prefill of 360 rows 208 -> 202 us).
-//     SwiGLU takes NT = 8 and 6, and {5, 4} from K = 3072 on, which counts as 0.65 more (gate|up at 450 rows: 124 us, all rows in one
-//     workgroup 138; at 900 rows 238, {6, 5} 225; at 1000 in a warm loop 268, {8, 4} 254; at K = 2048 they are even, at 1024 and below it
-//     is 2 to 8 % slower); {7, 4} is within 2 % either way of {8, 4} up to 3000 rows and 4 % slower at 4096, {5, 5} within 3 % of {6, 5}.
-//   128 x 128 tiles, two to a CU: 39 k up to 256 of them (36 k up to 512 rows: O at 450 rows in two splits 29.3 us with the norm behind it,
+//     they count as 0.4 to 1 features more (`edge`).  With the 1.5 of the others they won where they lose (* without edge -> with it: QKV at 600
+//     rows {2, 4} 47.3 -> {4, 5} in three splits 42.2; O at 800 rows {2, 4} 53.7 -> {4, 5} in three 47.6).  They still win where they should:
+//     512 columns, K = 8192 at 2560 rows {3, 4} in four 40.4 ({4, 5} in eight 42.0).  The model with hidden 512, where projections are
+//     short and a change of kernel costs about a us, takes them from 1281 rows on (whole prefill of 360 rows 208 -> 202 us).
+//     SwiGLU takes NT = 8 and 6, and {5, 4} from K = 3072 on, which counts as 0.65 more (* at 900 rows 238, {6, 5} 225; * at 1000 in a warm
+//     loop 268, {8, 4} 254; at K = 2048 they are even, at 1024 and below it is 2 to 8 % slower); {7, 4} is within 2 % either way of
+//     {8, 4} up to 3000 rows and 4 % slower at 4096, {5, 5} within 3 % of {6, 5}.
+//   128 x 128 tiles, two to a CU: 39 k up to 256 of them (36 k up to 512 rows: * O at 450 rows in two splits 29.3 us with the norm behind it,
 //     {3, 4} in three 30.6) and 60 k up to 512 (16 384 matrix rows at 512 rows: 24.1 us at K = 1024,
 //     {6, 4} 27.1; 38.8 and 42.6 at 2048); then 0.166 k a tile up to 1024 rows, and above 0.095 k a tile and 15 k (W read
-//     through L2 by many row blocks), from 16 384 matrix rows on, which no L2 holds, 0.137 k (22 016 rows, K = 4096: 541 us
-//     at 2560 rows and 658 at 3072, where tiles of {6, 5} and {6, 4} take 349 and 458).
+//     through L2 by many row blocks), from 16 384 matrix rows on, which no L2 holds, 0.137 k (22 016 rows, K = 4096: 658 us at
+//     3072 rows, where tiles of {6, 4} take 458).
 //   All rows in one workgroup of 160 features, up to 512 rows: 108 k a round up to 384 rows, 139 k up to 512 (SwiGLU only: no
-//     fp32 matrix is cheapest there).  Only for matrices of 16 384 rows and more, where it makes a round of workgroups.
+//     fp32 matrix is cheapest there).  Only for matrices of 16 384 rows and more, where it makes a round of workgroups; cheapest
+//     for some of more than 32 784 rows at 321 to 512 rows.
 //   S splits divide k, cost a fixed 6 and S times the output, written here and read by the next kernel, at 4.5 TB/s.
 struct TileShape { int nt, rt; double edge; };
 constexpr TileShape kTileShapes[] = {{8, 4, 1.5}, {7, 4, 1.5}, {6, 4, 1.5}, {5, 4, 1.5}, {6, 5, 1.5}, {5, 5, 1.5}, {4, 5, 1.5}, {4, 6, 1.5},
@@ -248,16 +249,20 @@ constexpr int kDeepSteps = 96, kDeepCols = 2048, kDeepRows = 2048;
 struct DeepShape { int nt, rt; bool f32, swiglu; };
 constexpr DeepShape kDeepShapes[] = {
     {4, 2, true, false}, {5, 2, true, false}, {6, 2, true, false}, {7, 2, true, false}, {8, 2, true, false}, {3, 3, true, false},
-    {4, 3, true, false}, {5, 3, true, true}, {7, 3, true, true}, {8, 3, false, true}, {2, 4, true, false}, {3, 4, true, false},
-    {4, 4, true, false}, {5, 4, true, true}, {6, 4, true, true}, {7, 4, true, true}, {8, 4, true, true}, {2, 5, true, false},
-    {3, 5, true, false}, {4, 5, true, false}, {5, 5, true, true}, {6, 5, true, true}, {4, 6, true, false}};
+    {4, 3, true, false}, {5, 3, true, true}, {7, 3, true, true}, {8, 3, false, true}, {3, 4, true, false}, {4, 4, true, false},
+    {5, 4, true, true}, {6, 4, true, true}, {7, 4, true, true}, {8, 4, true, true}, {3, 5, true, false}, {4, 5, true, false},
+    {5, 5, true, true}, {6, 5, true, true}, {4, 6, true, false}};
 // us that 112 k-steps of such a tile take: matrix instructions, and the operands' way through L2 and LDS, where a row tile costs more
 // than a feature tile (its 64 rows are four 16-row tiles, the features' 32 two).  Fitted, with the constants below, to launches of
 // every shape and number of splits at 31 batches of 72 to 2048 rows of the 7B shape's projections and a 16 384-row LM head (8000
 // launches); {4, 3} 34.7 measured, {5, 4} 51.1, {8, 4} 72.1.  At the 19 of these above 256 rows its choice is within 0.3 % of the
 // fastest on average and 2.9 % at most, plan_gemm's within 4.6 % on average: at 576 rows gate|up 152 -> 125 us, QKV 36.0 -> 29.6, down 84.7 -> 76.6; at 384 the LM
 // head 63.5 -> 52.0 and down 65.4 -> 58.7; at 896 gate|up 221 -> 198, O 37.6 -> 33.6.  Whole decode steps of two layers: 336 rows 649 ->
-// 621 us, 384 671 -> 639, 416 763 -> 725, 576 917 -> 805, 640 935 -> 899, 768 1046 -> 970, 960 1328 -> 1225.
+// 621 us, 384 671 -> 639, 416 763 -> 725, 576 917 -> 805, 640 935 -> 899, 768 1046 -> 970, 960 1328 -> 1225.  At other widths, fitted to none
+// (264 to 2000 rows; plan_gemm's choice -> this one): hidden 5120, gate|up of 27 648 rows at 440, 576 and 1280 rows 112 -> 108, 183 -> 159 and 295 ->
+// 260, its down 66 -> 63, 76.5 -> 74 and 144 -> 131; hidden 4096, 28 672 rows 95 -> 89, 150 -> 130 and 234 -> 216; hidden 6144, 32 768 rows 146 ->
+// 143, 245 -> 193 and 382 -> 356.  Of 300 projections there 11 are 4 to 7 % slower, all short (down of hidden 4096 at 512 rows 55.5 -> 59;
+// O of 5120 at 440 32.7 -> 34.3).  Shapes of {2, 4} and {2, 5} are not among them: no size of this range chose them.
 // Up to 256 rows the streaming kernel keeps them: tiles take less time there in a loop of their own (down at 192 rows 41 -> 36 us), but
 // with activations that another kernel has just written, and a chip that then runs at a lower clock, whole steps of 72 to 192
 // rows were 3 to 8 % slower with down on tiles, of 176 to 224 rows 4 % with gate|up on them, and of 240 and 256 rows as fast.

@@ -5,6 +5,8 @@ against the fp64 checker); greedy tokens identical except where the checker's to
 The GPU is teacher-forced with the checker's tokens so that one early near-tie cannot derail
 every later comparison; its own greedy choice is still read back and compared at every step.
 """
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -61,6 +63,15 @@ def gap_rule(tol):
     """Greedy tokens may differ only where the exact top-2 gap is below 1e-2 -- a third of the 3e-2 logit bound; where
     the logit bound is the derived one, the gap rule keeps that ratio."""
     return GAP_RULE * tol / LOGIT_TOL
+
+
+def likely_mismatches(gaps, contract_mean):
+    """(spread, number) of greedy tokens other than the exact one over many rows with these exact top-2 gaps, `gap_rule` being meant for
+    a few.  A logit's error is the contract mode's and one more of the same size (`tolerance`), both sums of many roundings: normal with
+    sqrt(pi / 2) times the mean distance for a deviation (here the largest mean of a row: rather too many).  The difference of two logits then has twice that, and a token
+    differs where it exceeds the gap."""
+    spread = 2.0 * math.sqrt(math.pi / 2) * contract_mean
+    return spread, sum(0.5 * math.erfc(g / (spread * math.sqrt(2))) for g in gaps if g >= GAP_RULE)
 
 
 def run_and_compare(shape, cfg, seed, *, page_tokens=32, max_prefill_rows=0, sigma=0.02, weights=None,
@@ -353,11 +364,12 @@ def test_mid_size_batch_takes_mixed_tiles_and_split_k():
     assert worst <= LOGIT_TOL and mism == 0
 
 
-def test_mid_size_batch_at_the_full_hidden_size():
+def test_mid_size_batch_at_the_full_hidden_size(plan):
     """The same regime at the inner dimension of the 7B shape (hidden 3584, 28 query / 4 kv heads of 128, one layer):
     384 rows per decode step, fewer after the gate, so the QKV, O and down projections run split along K = 3584 /
-    16896 on the tiled kernels and the gate|up projection on the all-rows kernel (at 384 rows); every logit
+    16896 on tiles of 128 to 192 rows and the gate|up projection on tiles of 192 (at 384 rows); every logit
     of every row against the checker, bound by the general rule (the contract mode on six sequences)."""
+    assert plan.projection(384, 2 * 16896, 3584, swiglu=True)[0] == "tiles 5x3" and plan.projection(384, 3584, 16896, max_splits=16)[1] > 1
     shape = synth.ModelShape(1, 3584, 28, 4, 128, 16896, 1024)
     cfg = synth.EpisodeConfig("mid-3584", 48, 8, 8, 2, 2, 2, 64, (1,), 0.3, 0.4)
     info = {}
@@ -1095,12 +1107,13 @@ def test_gate_up_on_tiles_with_an_odd_number_of_feature_tiles(plan):
     (97, 6160, 2064, "8x3", "8x2", "4x2"),           # 776
 ])
 def test_tiles_of_deep_projections_by_name(plan, n_groups, ffn, vocab, gate_up, down, lm_head):
-    """Tiles of 128 and 192 rows, and the others that deep projections take besides (128 x 128 for a small gate|up): gate|up, down (split along K) and LM head of a decode
-    step at hidden 3072 on the tiles named here, with ragged last row and column blocks.
+    """Tiles of 128 and 192 rows, and the others that deep projections take besides (128 x 128 for a small gate|up): gate|up, down (split
+    along K) and LM head of a decode step at hidden 3072 on the tiles named here, with ragged last row and column blocks.
 
-    The bound is the general rule, 2 E_c, with the contract mode's largest distance E_c over one sequence in 24: the largest of n errors of
-    deviation s is about s sqrt(2 ln n), so that four sequences of 648 (4.6 s) would put 2 E_c 6 % below what it is over all.  A token
-    other than the exact one needs an exact top-2 gap below the sum of two logits' errors."""
+    The bounds are the general rules, with the contract mode's largest distance over one sequence in 24: the largest of n errors of
+    deviation s is about s sqrt(2 ln n), so that four sequences of 648 (4.6 s) would put twice it 6 % below what it is over all.  Of
+    several hundred tokens compared at once some differ at gaps above a third of the bound: as many as the contract mode's mean distance and
+    the exact gaps lead to expect (two deviations of a count above that, and two), none at 4.5 deviations (1 in 3e5)."""
     rows = n_groups * 8
     assert plan.projection(rows, 2 * ffn, 3072, swiglu=True)[0].removeprefix("tiles ") == gate_up
     name, splits = plan.projection(rows, 3072, ffn, max_splits=16)
@@ -1111,8 +1124,10 @@ def test_tiles_of_deep_projections_by_name(plan, n_groups, ffn, vocab, gate_up, 
     rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=75, page_tokens=32, kv_pool_bytes=1 << 28,
                                                      contract_rows=list(range(0, rows, 24)), info=info)
     tol = tolerance(info["contract_max"])
-    print(f"deep tiles {rows}: worst |dlogit| = {worst:.3e}, bound {tol:.3e}, mismatches = {mism}, near ties = {near}")
-    assert worst <= tol and all(g <= 2 * worst for g in info["mismatch_gaps"])
+    spread, expected = likely_mismatches(rec["gaps"][0][0], info["contract_mean"])
+    print(f"deep tiles {rows}: worst |dlogit| = {worst:.3e}, bound {tol:.3e}, mismatches = {mism} ({expected:.1f} expected), near ties = {near}, "
+          f"gaps {[round(g / spread, 2) for g in info['mismatch_gaps']]} x {spread:.4f}")
+    assert worst <= tol and mism <= expected + 2 * math.sqrt(expected) + 2 and all(g < 4.5 * spread for g in info["mismatch_gaps"])
 
 
 @pytest.mark.parametrize("prompt,kernel", [(491, "tiles 3x4"), (599, "tiles 3x5")])
