@@ -491,7 +491,7 @@ int forward(sr_ctx *c, const Pass &p, hipStream_t st) {
         part_rows += items * 16 * x.rt;
         ph[n_ph++] = x;
     };
-    const bool whole = p.decode && whole_context((long long)p.n_units * s.n_kv_heads, s.head_dim, ctx);
+    const bool whole = p.decode && whole_context(p.n_units, s.n_kv_heads, s.head_dim, ctx, c->n_live_groups, c->G, c->shared_tokens);
     if (whole) {
         // one launch and no partial results; on the debugging path its wavefronts' shares of the context, as splits
         if (c->dbg) add_phase(whole_phase(p.n_units, ctx));

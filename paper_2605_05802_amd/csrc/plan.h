@@ -390,9 +390,17 @@ inline int private_splits(long long waves1, long long shared_waves, int tokens, 
 // Whole steps of two layers, us, two launches -> one: 4 and 2 kv heads of 64, 32 sequences, 272 tokens 54.4 -> 47.8, 688 61.7 -> 51.7, 1356
 // 60.9 -> 57.3, 2432 63.3 -> 65.2; 28 and 4 of 128, 8 sequences, 272 tokens 225 -> 215, 832 229.5 -> 226.6, 1356 230.4 -> 230.8; 64
 // sequences, 832 tokens 273 -> 268.  Eight wavefronts to a workgroup are never faster than four.
+// What the members of a group read again of their `shared` prompt tokens comes from L2 where the workgroups of a kv head lie on one XCD
+// (consecutive workgroups go to consecutive XCDs, so that is where n_kv is a multiple of 8), and from HBM once for every other XCD that they lie
+// on.  4 us of launches pay for about 40 MB of that.  us a layer gained by one launch, around 256 workgroups, by MB read again: n_kv = 8, 0 MB
+// 3.8 (G = 2) and 4.8 (G = 8); n_kv = 4, 14 MB 1.4, 39 MB -0.9 and 52 MB -2.2 (G = 2); n_kv = 2, 29 MB 0.3; n_kv = 5 with G = 8, 43 MB
+// -0.7, 64 MB -3.4 and 86 MB -5.8 (whole decode steps of hidden 3200, 48 sequences, 900 tokens 206 -> 220); n_kv = 1, 74 MB -4.0.
 constexpr int kWholeWaves = 4;
-inline bool whole_context(long long workgroups, int head_dim, int ctx) {
-    return workgroups <= 256 && (long long)ctx * head_dim <= 1024 * 128;
+constexpr long long kWholeRereads = 36 << 20;
+inline bool whole_context(long long seqs, int n_kv, int head_dim, int ctx, int groups, int G, int shared) {
+    if (seqs * n_kv > 256 || (long long)ctx * head_dim > 1024 * 128) return false;
+    const int xcds = n_kv % 8 == 0 ? 1 : n_kv % 4 == 0 ? 2 : n_kv % 2 == 0 ? 4 : 8, reads = G < xcds ? G : xcds;
+    return (long long)groups * n_kv * shared * head_dim * 4 * (reads - 1) <= kWholeRereads;
 }
 
 }  // namespace sr

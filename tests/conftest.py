@@ -73,7 +73,9 @@ int split_steps(int M, int N, int ks, int mt_total, int splits) { return sr::spl
 int score_rows(int M, int vocab, int rows) { return sr::score_rows(M, vocab, rows); }
 int private_splits(int waves1, int shared_waves, int tokens, int most) { return sr::private_splits(waves1, shared_waves, tokens, most); }
 int token_splits(int tokens, int want, int *each) { const sr::TokenSplits s = sr::token_splits(tokens, want); *each = s.tokens; return s.n; }
-int whole_context(int workgroups, int head_dim, int ctx) { return sr::whole_context(workgroups, head_dim, ctx); }
+int whole_context(int n_kv, int head_dim, int ctx, int groups, int G, int shared) {
+    return sr::whole_context((long long)groups * G, n_kv, head_dim, ctx, groups, G, shared);
+}
 int thin_resid(int M, int N, int ks) { return sr::thin_resid(M, N, ks); }
 int thin_qkv(int M, int N, int ks) { return sr::thin_qkv(M, N, ks); }
 void rope_tables(int len, int d, double theta, float *c, float *s) { sr::rope_tables(len, d, theta, c, s); }

@@ -725,7 +725,7 @@ def test_debug_path_divides_every_sum_as_the_normal_path_does(plan, what, n_grou
     if what != "context" and (plan.thin_resid(rows, H, ks) if resid else plan.thin_qkv(rows, cols, ks)):
         assert found == [q * ks // 4 for q in (1, 2, 3)]
     if what == "context":
-        assert found == ([2, 4] if plan.whole_context(rows * 2, 64, 233) else [5])
+        assert found == ([2, 4] if plan.whole_context(2, 64, 233, n_groups, 8, 160) else [5])
 
 
 def test_full_width_long_shared_prompt_every_row():
@@ -761,7 +761,7 @@ def test_group_of_16_with_a_long_shared_prompt(plan):
     of sequence and kv head.)"""
     shape = synth.ModelShape(2, 512, 14, 2, 128, 1024, 2048)
     cfg = synth.EpisodeConfig("g16-long", 2, 16, 1030, 2, 70, 3, 64, (1,), 0.25, 0.5)
-    assert not plan.whole_context(2 * 16 * 2, 128, cfg.prompt_len)
+    assert not plan.whole_context(2, 128, cfg.prompt_len, 2, 16, cfg.prompt_len // 64 * 64)
     info = {}
     rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=8, page_tokens=64, contract_rows=[0, 9, 17, 31],
                                                      info=info)
@@ -1253,7 +1253,7 @@ def test_short_contexts_in_one_launch(plan, n_groups, G, n_q, n_kv, d, page, pro
     prompts that end inside a page; members that finish early."""
     shape = synth.ModelShape(1, 96, n_q, n_kv, d, 208, 272)
     cfg = synth.EpisodeConfig("whole", n_groups, G, prompt, 2, 3, 3, 16, (2,), 0.3, 0.4)
-    assert plan.whole_context(n_groups * G * n_kv, d, prompt + 12)
+    assert plan.whole_context(n_kv, d, prompt + 12, n_groups, G, prompt // page * page)
     finish = (lambda K, r: K == 1 and r in (0, G + 1)) if n_groups == 3 else None
     rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=85, page_tokens=page)
     print(f"whole {n_groups}x{G} {n_q}/{n_kv}x{d} {prompt}: worst |dlogit| = {worst:.3e}, mismatches = {mism}, near ties = {near}")
@@ -1270,7 +1270,7 @@ def test_shared_prompts_beyond_the_contexts_of_one_launch(plan, n_q, n_kv, d, G,
     """Shared prompt and private context side by side and merged, in groups that lose members."""
     shape = synth.ModelShape(1, 256, n_q, n_kv, d, 256, 512)
     cfg = synth.EpisodeConfig("two-phase", 2, G, prompt, 2, obs, 2, 16, (), 0.3, 0.5)
-    assert not plan.whole_context(2 * G * n_kv, d, prompt + obs)
+    assert not plan.whole_context(n_kv, d, prompt + obs, 2, G, prompt // page * page)
     rec, stats, worst, mism, near = run_and_compare(shape, cfg, seed=32, page_tokens=page, sigma=0.05,
                                                      finish_fn=lambda K, r: K == 1 and r in (0, G + 1, G + 2))
     print(f"two phases {n_q}/{n_kv}x{d} G={G}: worst |dlogit| = {worst:.3e}, mismatches = {mism}, near ties = {near}")

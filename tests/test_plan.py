@@ -290,8 +290,20 @@ def test_sums_of_squares_that_fit_behind_the_weights(plan, M, N, ks, thin):
 
 def test_whole_contexts_where_they_come_out_ahead(plan):
     """Up to 1024 tokens of 128 dims and 2048 of 64, for one round of workgroups."""
-    assert plan.whole_context(256, 128, 1024) and plan.whole_context(64, 64, 2048) and plan.whole_context(1, 64, 1)
-    assert not plan.whole_context(256, 128, 1025) and not plan.whole_context(64, 64, 2049) and not plan.whole_context(257, 128, 32)
+    assert plan.whole_context(8, 128, 1024, 4, 8, 0) and plan.whole_context(8, 64, 2048, 1, 8, 0) and plan.whole_context(1, 64, 1, 1, 2, 0)
+    assert not plan.whole_context(8, 128, 1025, 4, 8, 0) and not plan.whole_context(8, 64, 2049, 1, 8, 0)
+    assert not plan.whole_context(8, 128, 32, 3, 11, 0)
+
+
+@pytest.mark.parametrize("n_kv,d,groups,G,shared,whole", [
+    (8, 128, 16, 2, 900, True), (8, 128, 4, 8, 900, True),            # a group's kv head on one XCD
+    (4, 128, 8, 8, 900, True), (4, 128, 32, 2, 400, True), (4, 128, 32, 2, 832, False),
+    (2, 128, 16, 8, 576, True), (5, 128, 6, 8, 384, False), (5, 128, 6, 8, 896, False), (5, 128, 3, 8, 384, True), (5, 128, 3, 16, 576, True),
+    (1, 64, 32, 8, 640, True), (1, 64, 32, 8, 1280, False), (7, 128, 1, 8, 960, True)])
+def test_whole_contexts_where_members_read_the_prompt_from_one_l2(plan, n_kv, d, groups, G, shared, whole):
+    """One launch as long as what the members read again from HBM stays below 36 MB: with five kv heads they lie on eight XCDs, and 48
+    sequences with a prompt of 900 tokens took 206 us a step in two launches and 220 in one."""
+    assert plan.whole_context(n_kv, d, shared + 40, groups, G, shared) == whole
 
 
 @pytest.mark.parametrize("M,N,K,swiglu,kernel,splits", [
